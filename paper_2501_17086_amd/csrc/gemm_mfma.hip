@@ -1,7 +1,7 @@
 // bf16 GEMM on the gfx950 matrix cores (v_mfma_f32_32x32x16_bf16, fp32
 // accumulate) for the VJP and parameter-gradient contractions.
 //
-// Shape of the kernels
+// Shape of the kernel
 //   workgroup   8 wavefronts, output tile 256 x 256, one workgroup per CU; a
 //               wavefront owns 128 x 64 = 4 x 2 MFMA blocks of 32 x 32 (128
 //               accumulator registers per lane).  The 256 x 256 tile keeps the
@@ -46,23 +46,21 @@
 //   accumulator the MFMAs are issued with the operands exchanged (B fragment
 //               first), which leaves a lane with one output row and groups of
 //               four consecutive output columns.
-//   two kernels lean: every tile inside the matrix, K a multiple of 32 per
-//               split, the hot epilogues.  Straight-line: its epilogues issue a
+//   lean        every tile inside the matrix, K a multiple of 32 per split, the hot
+//               epilogues.  Straight-line: its epilogues issue a
 //               known number of memory operations, so the copies stay counted
 //               across them.  bf16 tiles leave through 4 KB of wave-private LDS
 //               so that every global access covers whole 128-byte lines; fp32
 //               tiles (parameter gradients, one per 256+ slices) are stored
-//               from the registers, 16 bytes per lane.
-//               general: any size whose contiguous dimensions are multiples of
-//               8 and every epilogue; chunks outside the matrix are copied from
-//               a zero-filled device array, rows/columns outside are not
-//               stored, the pipeline drains after a tile's epilogue.
+//               from the registers, 16 bytes per lane.  Every other size, the
+//               remaining epilogues and launches with few tiles go to
+//               gemm_tile.hip; launch_gemm_mfma at the end of this file decides.
 //   tile order  workgroup ids are dealt round-robin to the 8 XCDs (one L2
 //               each): id % 8 selects a contiguous eighth of the tile list,
 //               the workgroups of an XCD take consecutive tiles of it, and the
 //               list walks 8 x 8 blocks of tiles, so the tiles an XCD works on
 //               at one time share operand panels.
-#include "hbp_common.h"
+#include "gemm_device.h"
 #include <atomic>
 #include <type_traits>
 
@@ -70,50 +68,15 @@ namespace hbp {
 
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float float2v __attribute__((ext_vector_type(2)));
-typedef short short4v __attribute__((ext_vector_type(4)));
-typedef short short8v __attribute__((ext_vector_type(8)));
-typedef float float16v __attribute__((ext_vector_type(16)));
 
-constexpr int BM = 256, BN = 256, BK = 32, NST = 4, NW = 8, NTHR = 64 * NW;
+constexpr int BM = 256, BN = 256, BK = 32, NW = 8, NTHR = 64 * NW;
 constexpr int A_BYTES = BM * BK * 2;            // 16 KB
 constexpr int B_BYTES = BN * BK * 2;            // 16 KB
 constexpr int STAGE_BYTES = A_BYTES + B_BYTES;  // 32 KB
-constexpr int LDS_BYTES = NST * STAGE_BYTES;    // 128 KB
 constexpr int GROUP_M = 8;                      // tile rows per block of the tile walk
 constexpr int PER_SLICE = 4;                    // copies per wave per slice (2 for A, 2 for B)
-
-__device__ uint4 g_zero_chunks[64];  // source of out-of-range chunks (zero-initialised)
-
-// 16 bytes per lane, global -> LDS at lds_base + lane * 16.  lds_base is
-// wave-uniform.  The compiler does not see this write to LDS: callers order it
-// against LDS reads with a counted wait + a workgroup barrier.
-__device__ __forceinline__ void dma16(const void* gptr, unsigned lds_base) {
-  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off\n"
-               :: "v"(gptr), "s"(lds_base) : "memory");
-}
-// the same with a wave-uniform 64-bit base and a 32-bit unsigned byte offset per lane
-__device__ __forceinline__ void dma16_s(unsigned off, const void* sbase_in, unsigned lds_base) {
-  // (the base is uniform by construction; say so where the register allocator has moved it to vector registers)
-  const unsigned long long b = reinterpret_cast<unsigned long long>(sbase_in);
-  const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)b);
-  const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(b >> 32));
-  const unsigned long long u = (unsigned long long)lo | ((unsigned long long)hi << 32);
-  const void* sbase = reinterpret_cast<const void*>(u);
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1\n"
-               :: "v"(off), "s"(sbase), "s"(lds_base) : "memory");
-}
-// at most N vector-memory operations outstanding (N <= 63), and no LDS operation
-template <int N>
-__device__ __forceinline__ void wait_vm_lds() {
-  __builtin_amdgcn_s_waitcnt(0x0070 | (N & 15) | ((N >> 4) << 14));
-}
-template <int N>
-__device__ __forceinline__ void wait_vm() {
-  __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
-}
 
 // Byte offset of this lane's chunk of copy i (of 2) relative to the first
 // element of the tile's slice (the same for every slice and tile of a launch).
@@ -130,34 +93,6 @@ __device__ __forceinline__ unsigned lane_src_offset(long ld, int i, int wave, in
     return (unsigned)(k * ld + 8 * c) * 2u;
   }
 }
-// Edge path: copies one operand tile's share of a slice (2 copies of 1 KB per
-// wave) with every chunk checked against the matrix.  `base` points at the
-// tile's first row (KC) or first column (RC), k0 is the slice's first
-// contraction index.
-template <bool KC>
-__device__ __forceinline__ void issue_tile(const bf16_t* base, long ld, long rows_left, long k0, long k_end,
-                                           unsigned lds_tile, int wave, int lane) {
-  const bf16_t* slice = KC ? base + k0 : base + k0 * ld;   // uniform
-#pragma unroll
-  for (int i = 0; i < 256 / 16 / NW; ++i) {
-    const int j = wave + NW * i;                // copy index within the tile: 1 KB each
-    bool ok;
-    const bf16_t* src;
-    if (KC) {                                   // [256 rows][4 chunks]; chunk c of row r sits at c ^ (r/4 % 4)
-      const int r = 16 * j + (lane >> 2);
-      const int c = (lane & 3) ^ ((r >> 2) & 3);
-      ok = r < rows_left && k0 + 8 * c < k_end;
-      src = slice + (long)r * ld + 8 * c;
-    } else {                                    // [32 k][32 chunks]; chunk c of row k sits at c ^ 4*(k % 4)
-      const int k = 2 * j + (lane >> 5);
-      const int c = (lane & 31) ^ (4 * (k & 3));
-      ok = 8 * c < rows_left && k0 + k < k_end;
-      src = slice + (long)k * ld + 8 * c;
-    }
-    dma16(ok ? (const void*)src : (const void*)(g_zero_chunks + lane), lds_tile + (unsigned)j * 1024u);
-  }
-}
-
 // 32 rows x 16 k fragment: lane l holds row (l % 32), k = kk + 8*(l/32) .. +7
 template <bool KC>
 __device__ __forceinline__ bf16x8 frag(const unsigned char* tile, int row0, int kk, int lane) {
@@ -180,13 +115,6 @@ __device__ __forceinline__ bf16x8 frag(const unsigned char* tile, int row0, int 
   }
 }
 
-__device__ __forceinline__ float gelu_f(float a) {
-  return 0.5f * a * (1.0f + erff(a * 0.70710678118654752440f));
-}
-__device__ __forceinline__ float gelu_grad_f(float a) {
-  return 0.5f * (1.0f + erff(a * 0.70710678118654752440f)) + a * __expf(-0.5f * a * a) * 0.39894228040143267794f;
-}
-
 // 4 consecutive elements <-> 4 floats
 __device__ __forceinline__ unsigned pack2(float a, float b) {   // round to nearest even (v_cvt_pk_bf16_f32)
   const float2v v = {a, b};
@@ -195,11 +123,6 @@ __device__ __forceinline__ unsigned pack2(float a, float b) {   // round to near
 __device__ __forceinline__ void unpack4(uint2 r, float (&o)[4]) {
   o[0] = __uint_as_float(r.x << 16); o[1] = __uint_as_float(r.x & 0xFFFF0000u);
   o[2] = __uint_as_float(r.y << 16); o[3] = __uint_as_float(r.y & 0xFFFF0000u);
-}
-__device__ __forceinline__ void load4(const bf16_t* p, float (&o)[4]) { unpack4(*reinterpret_cast<const uint2*>(p), o); }
-__device__ __forceinline__ void load4(const float* p, float (&o)[4]) {
-  const float4 a = *reinterpret_cast<const float4*>(p);
-  o[0] = a.x; o[1] = a.y; o[2] = a.z; o[3] = a.w;
 }
 __device__ __forceinline__ void store4(bf16_t* p, const float (&v)[4]) {
   *reinterpret_cast<uint2*>(p) = make_uint2(pack2(v[0], v[1]), pack2(v[2], v[3]));
@@ -245,279 +168,6 @@ enum FastEpi {
   FAST_RESID = 6,      // C(bf16) = acc + lambda[n] * aux   (forward: x_{l+1}; lambda NULL = 1)
   FAST_ACT_GELU = 7    // C(bf16) = gelu(acc), out2(bf16) = gelu'(acc)   (forward: z and act')
 };
-
-template <bool A_KC, bool B_KC, bool ACT>
-__global__ __launch_bounds__(NTHR, 1) void gemm_mfma_kernel(GemmArgs g, int tiles_m, int tiles_n, long total,
-                                                            long per_xcd) {
-  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int grp = wave >> 2;           // phase group
-  const int wm0 = grp * 128, wn0 = (wave & 3) * 64;
-  const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
-
-  // tiles of this workgroup: t_first, t_first + t_stride, ... below t_end
-  const int xcd = blockIdx.x & 7;
-  const int t_stride = gridDim.x >> 3;
-  const int t_first = xcd * (int)per_xcd + (blockIdx.x >> 3);
-  const int t_end = (xcd + 1) * per_xcd < total ? (xcd + 1) * (int)per_xcd : (int)total;
-  if (t_first >= t_end) return;
-
-  const long lda = A_KC ? g.a_sm : g.a_sk;
-  const long ldb = B_KC ? g.b_sn : g.b_sk;
-
-  // ---- producer: the next slice of the stream to copy ----
-  // All of its state is wave-uniform (scalar registers) and advanced
-  // incrementally; the only per-lane values are two 32-bit source offsets.
-  const bf16_t* pa = nullptr;  // producer tile's first row of A / first column of B
-  const bf16_t* pb = nullptr;
-  const bf16_t* qa = nullptr;  // the same, at the next slice to copy
-  const bf16_t* qb = nullptr;
-  const long step_a = A_KC ? BK : BK * lda;   // elements per slice
-  const long step_b = B_KC ? BK : BK * ldb;
-  int pt = t_first - t_stride;   // producer tile (moved onto its first tile by the first produce())
-  TileCoord pc;
-  int p_left = 0;             // slices of the producer tile still to copy
-  long k_next = 0;            // first contraction index of the next slice
-  bool p_inside = false;      // the producer tile lies fully inside the matrix
-  bool p_valid = true;
-  unsigned p_lds = lds0 + (unsigned)wave * 1024u;   // LDS address of this wave's first copy in the next stage
-  int p_stage = 0;
-  int issued = 0;             // slices issued so far
-  // A wave's second copy is 128 rows (KC) or 16 k rows (RC) after its first, where the
-  // swizzle repeats: same lane offset, base moved by a uniform amount.
-  const unsigned offA = lane_src_offset<A_KC>(lda, 0, wave, lane);
-  const unsigned offB = lane_src_offset<B_KC>(ldb, 0, wave, lane);
-  const long second_a = (A_KC ? 128 : 16) * lda, second_b = (B_KC ? 128 : 16) * ldb;
-  auto produce = [&]() {
-    if (!p_valid) return;
-    if (p_left == 0) {        // next tile with a non-empty k range
-      p_valid = false;
-      for (pt += t_stride; pt < t_end; pt += t_stride) {
-        pc = decode_tile(g, pt, tiles_m, tiles_n);
-        if (pc.KT > 0) { p_valid = true; break; }
-      }
-      if (!p_valid) return;
-      p_left = pc.KT;
-      k_next = pc.k_begin;
-      p_inside = pc.m0 + BM <= g.M && pc.n0 + BN <= g.N;
-      pa = reinterpret_cast<const bf16_t*>(g.A) + pc.batch * g.a_sb + (A_KC ? pc.m0 * lda : pc.m0);
-      pb = reinterpret_cast<const bf16_t*>(g.B) + pc.batch * g.b_sb + (B_KC ? pc.n0 * ldb : pc.n0);
-      qa = A_KC ? pa + k_next : pa + k_next * lda;
-      qb = B_KC ? pb + k_next : pb + k_next * ldb;
-    }
-    if (p_inside && k_next + BK <= pc.k_end) {
-      // interior tile, full slice: a wave-uniform base plus one 32-bit offset per lane
-      dma16_s(offA, qa, p_lds);
-      dma16_s(offA, qa + second_a, p_lds + NW * 1024u);
-      dma16_s(offB, qb, p_lds + A_BYTES);
-      dma16_s(offB, qb + second_b, p_lds + A_BYTES + NW * 1024u);
-    } else {
-      const unsigned st0 = p_lds - (unsigned)wave * 1024u;
-      issue_tile<A_KC>(pa, lda, g.M - pc.m0, k_next, pc.k_end, st0, wave, lane);
-      issue_tile<B_KC>(pb, ldb, g.N - pc.n0, k_next, pc.k_end, st0 + A_BYTES, wave, lane);
-    }
-    qa += step_a;
-    qb += step_b;
-    k_next += BK;
-    --p_left;
-    ++issued;
-    if (++p_stage == NST) { p_stage = 0; p_lds -= (NST - 1) * STAGE_BYTES; } else p_lds += STAGE_BYTES;
-  };
-
-  // ---- consumer ----
-  // acc[i][j]: lane l, element r  <->  output row wm0 + 32 i + l % 32,
-  //                                    column wn0 + 32 j + 8 (r / 4) + 4 (l / 32) + r % 4
-  float16v acc[4][2];
-  bf16x8 fa[4][2], fb[2][2];
-  auto load_frags = [&](const unsigned char* st) {
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) fb[j][h] = frag<B_KC>(st + A_BYTES, wn0 + 32 * j, 16 * h, lane);
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) fa[i][h] = frag<A_KC>(st, wm0 + 32 * i, 16 * h, lane);
-  };
-  auto mma_slice = [&](bool first) {
-    if (first) {     // first slice of a tile: the accumulators start from zero
-      const float16v zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[j][0], fa[i][0], zero, 0, 0, 0);
-    } else {
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[j][0], fa[i][0], acc[i][j], 0, 0, 0);
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[j][1], fa[i][1], acc[i][j], 0, 0, 0);
-  };
-
-  // ---- epilogue of one tile, general form: every access guarded, every mode ----
-  auto epilogue = [&](const TileCoord& tc) {
-    const int rl = lane & 31, ch = (lane >> 5) * 4;
-    const float* lam = g.lambda ? g.lambda + tc.batch * g.lambda_sb : nullptr;
-    const bool use_aux = g.mode == EPI_MUL_AUX || g.mode == EPI_MUL_1MZ2 || g.mode == EPI_RESID ||
-                         g.mode == EPI_ADD_AUX;
-    const bf16_t* aux = reinterpret_cast<const bf16_t*>(g.aux) + tc.batch * g.aux_sb;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const long row = tc.m0 + wm0 + 32 * i + rl;
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const long col = tc.n0 + wn0 + 32 * j + 8 * q + ch;
-          if (row >= g.M || col >= g.N) continue;
-          float v[4];
-#pragma unroll
-          for (int x = 0; x < 4; ++x) v[x] = acc[i][j][4 * q + x];
-          const long off = row * g.ldc + col;
-          if (g.split_k > 1) {
-            store4(reinterpret_cast<float*>(g.C) + ((long)tc.split * g.batch + tc.batch) * g.c_sb + off, v);
-            continue;
-          }
-          if (g.addf) {
-            float t[4];
-            load4(g.addf + tc.batch * g.addf_sb + off, t);
-#pragma unroll
-            for (int x = 0; x < 4; ++x) v[x] += t[x];
-          }
-          float t[4] = {0.f, 0.f, 0.f, 0.f};
-          if (use_aux) load4(aux + off, t);
-          switch (g.mode) {
-            case EPI_MUL_AUX:
-#pragma unroll
-              for (int x = 0; x < 4; ++x) v[x] *= t[x];
-              break;
-            case EPI_MUL_1MZ2:
-#pragma unroll
-              for (int x = 0; x < 4; ++x) v[x] *= (1.f - t[x] * t[x]);
-              break;
-            case EPI_ACT_GELU:
-              if (ACT) {
-                float d[4];
-#pragma unroll
-                for (int x = 0; x < 4; ++x) { d[x] = gelu_grad_f(v[x]); v[x] = gelu_f(v[x]); }
-                store4(reinterpret_cast<bf16_t*>(g.out2) + tc.batch * g.out2_sb + off, d);
-              }
-              break;
-            case EPI_ACT_TANH:
-              if (ACT) {
-#pragma unroll
-                for (int x = 0; x < 4; ++x) v[x] = tanhf(v[x]);
-              }
-              break;
-            case EPI_RESID:
-              if (g.lambda_mn) {
-                float l4[4];
-                load4(reinterpret_cast<const bf16_t*>(g.lambda_mn) + tc.batch * g.aux_sb + off, l4);
-#pragma unroll
-                for (int x = 0; x < 4; ++x) v[x] = fmaf(l4[x], t[x], v[x]);
-              } else if (lam) {
-                float l4[4];
-                load4(lam + col, l4);
-#pragma unroll
-                for (int x = 0; x < 4; ++x) v[x] = fmaf(l4[x], t[x], v[x]);
-              } else {
-#pragma unroll
-                for (int x = 0; x < 4; ++x) v[x] += t[x];
-              }
-              break;
-            case EPI_ADD_AUX:
-#pragma unroll
-              for (int x = 0; x < 4; ++x) v[x] += t[x];
-              break;
-            default: break;
-          }
-          if (g.c_is_f32)
-            store4(reinterpret_cast<float*>(g.C) + tc.batch * g.c_sb + off, v);
-          else
-            store4(reinterpret_cast<bf16_t*>(g.C) + tc.batch * g.c_sb + off, v);
-        }
-    }
-  };
-
-  // ---- the stream ----
-  // Barrier intervals ("ticks"): group 0 loads slice c in tick 2c and multiplies
-  // it in tick 2c+1; group 1 does the same one tick later.  Slice c+3 is issued
-  // in the load phase of slice c into the stage of slice c-1, which the last
-  // reader (group 1, tick 2c-1) has left.  Every wave waits for its own share
-  // of slice c+1 at the end of its load phase of slice c, two barriers or more
-  // before the first reader of slice c+1 starts.
-#pragma unroll 1
-  for (int s = 0; s < NST - 1; ++s) produce();
-  if (issued == 0) return;
-  if (issued >= 3) wait_vm<2 * PER_SLICE>(); else if (issued == 2) wait_vm<PER_SLICE>(); else wait_vm<0>();
-  __builtin_amdgcn_s_barrier();            // slice 0 is in LDS
-  if (grp == 1) __builtin_amdgcn_s_barrier();   // group 1 runs one tick behind
-
-  int ct = t_first - t_stride; // consumer tile (moved onto its first tile below)
-  TileCoord cc, ec;
-  cc.KT = 0;
-  int ck = 0;                  // slice of the consumer tile being multiplied
-  int c_stage = 0;             // its stage
-  int consumed = 0;            // its index in the stream
-  bool epi_pending = false;    // tile ec is complete in the accumulators
-  int epi_age = 0;             // load phases whose wait still sees the last epilogue's operations
-  while (true) {
-    // ---------------- load phase ----------------
-    if (epi_pending) {
-      epilogue(ec);
-      epi_age = 2;
-      epi_pending = false;
-    }
-    if (ck == cc.KT) {         // first slice of the next tile (same walk as the producer's)
-      do {
-        ct += t_stride;
-        cc = decode_tile(g, ct, tiles_m, tiles_n);
-      } while (cc.KT == 0);
-      ck = 0;
-    }
-    produce();                 // slice consumed + 3, into the stage of slice consumed - 1
-    load_frags(smem + c_stage * STAGE_BYTES);
-    const bool has_next = consumed + 1 < issued;   // the producer is always ahead while slices remain
-    {
-      // this wave's share of slice consumed+1 has landed once only what was issued after it is outstanding
-      const int younger = has_next ? issued - consumed - 2 : 0;
-      if (epi_age > 0) {        // the epilogue's stores and loads are not counted: drain
-        wait_vm_lds<0>();
-        --epi_age;
-      } else {
-        if (younger >= 2) wait_vm_lds<2 * PER_SLICE>();
-        else if (younger == 1) wait_vm_lds<PER_SLICE>();
-        else wait_vm_lds<0>();
-      }
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_sched_barrier(0);
-    // ---------------- compute phase ----------------
-    __builtin_amdgcn_s_setprio(1);
-    mma_slice(ck == 0);
-    __builtin_amdgcn_s_setprio(0);
-    __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_sched_barrier(0);
-    if (++ck == cc.KT) { epi_pending = true; ec = cc; }
-    if (++c_stage == NST) c_stage = 0;
-    if (!has_next) break;
-    ++consumed;
-  }
-  if (epi_pending) epilogue(ec);
-  if (grp == 0) __builtin_amdgcn_s_barrier();   // matches group 1's last barrier
-}
-
 
 // Straight-line epilogue from the registers for a tile fully inside the matrix (fp32 output).
 template <int FAST>
@@ -678,12 +328,7 @@ __device__ __forceinline__ void epilogue_staged_fn(const GemmArgs& g, const Tile
         if (TWO_OUT) {
           float dz[4];
 #pragma unroll
-          for (int x = 0; x < 4; ++x) {
-            const float a = v[x];
-            const float phi = 0.5f * (1.0f + erff(a * 0.70710678118654752440f));
-            v[x] = a * phi;
-            dz[x] = phi + a * __expf(-0.5f * a * a) * 0.39894228040143267794f;
-          }
+          for (int x = 0; x < 4; ++x) gelu_both(v[x], v[x], dz[x]);
           second[4 * j + qd] = make_uint2(pack2(dz[0], dz[1]), pack2(dz[2], dz[3]));
         }
         *reinterpret_cast<uint2*>(m_base + (((4 * j + qd) ^ m_sw) << 4)) = make_uint2(pack2(v[0], v[1]), pack2(v[2], v[3]));
@@ -982,26 +627,68 @@ hipError_t launch_lean(const GemmArgs& g, hipStream_t s) {
   return one_at_a_time ? launch_lean_walk<A_KC, B_KC, FAST, true, false>(g, s)
                        : launch_lean_walk<A_KC, B_KC, FAST, false, false>(g, s);
 }
-// every tile inside the matrix, every tile's share of K a whole number of slices
-inline bool lean_ok(const GemmArgs& g) {
-  return g.M % BM == 0 && g.N % BN == 0 && g.K % ((long)g.split_k * BK) == 0;
+// The lean kernel's share of a chip whose compute units take one 256 x 256 tile each at a time: below about 0.55 of the
+// last round filled (up to 140 tiles, or 257 to 281) the tiles of 128 x 128 are faster.  Measured, lean / 128 tile:
+// 64 tiles (8192 x 512 x 2048) 39.3 / 27.7 us, 128 tiles (2048 x 4096 x 1024) 29.0 / 25.0, 192 tiles (4096 x 3072 x 768
+// with GELU) 47.9 / 64.8, 256 tiles (8192 x 2048 x 512) 28.8 / 31.0, (16384 x 1024 x 4096) 110 / 179.
+inline bool fills_chip(long tiles) { return tiles * 100 >= (tiles + 255) / 256 * 256 * 55; }
+// Sizes that are no multiple of the tile: from two rounds of whole tiles on, these go to the lean kernel and the rest to
+// the tile kernel in launches of its own; below, everything to the tile kernel (3000 x 1000 x 4000, batch 4, 132 whole
+// tiles: 163 us in parts, 122 us whole).
+constexpr long SPLIT_FROM = 512;
+
+// 128 x 128 tiles once they give most compute units one, else 64 x 64.  Measured, 128 / 64: 24 tiles of 128 (1000 x 328 x
+// 1304) 18.9 / 10.1 us, 128 tiles (2048 x 1024 x 4096) 42.3 / 28.0, 192 tiles (4096 x 768 x 3072) 36.4 / 37.2, 288 tiles
+// (1000 x 328 x 1304, batch 12) 27.1 / 33.4, 768 tiles (3000 x 1000 x 4000, batch 4) 122 / 222.
+inline hipError_t launch_tile_for(const GemmArgs& g, hipStream_t s) {
+  const long tiles = (g.M + 127) / 128 * ((g.N + 127) / 128) * g.batch * g.split_k;
+  return launch_gemm_tile(g, tiles >= 192 ? 128 : 64, s);
 }
 
-template <bool A_KC, bool B_KC, bool ACT>
-hipError_t launch_variant(const GemmArgs& g, hipStream_t s) {
-  static std::atomic<bool> attr_set[MAX_DEVICES];
-  auto kern = gemm_mfma_kernel<A_KC, B_KC, ACT>;
-  {
-    hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kern), LDS_BYTES + 8192, attr_set);
-    if (e != hipSuccess) return e;
+// does the lean kernel have this pairing's epilogue?
+inline bool has_lean(const GemmArgs& g, bool a_kc, bool b_kc) {
+  if (!a_kc) return g.mode == EPI_STORE && !g.addf && (g.c_is_f32 || g.split_k > 1);     // parameter gradients
+  if (g.addf || g.c_is_f32 || g.split_k > 1) return false;
+  if (g.mode == EPI_STORE || g.mode == EPI_MUL_AUX || g.mode == EPI_MUL_1MZ2 || g.mode == EPI_ADD_AUX) return true;
+  if (g.mode == EPI_ACT_GELU) return b_kc && g.out2;                                     // forward
+  return g.mode == EPI_RESID && b_kc && g.aux && !g.lambda_mn;
+}
+template <bool B_KC>
+hipError_t launch_lean_kc(const GemmArgs& g, hipStream_t s) {
+  switch (g.mode) {
+    case EPI_STORE: return launch_lean<true, B_KC, FAST_STORE>(g, s);
+    case EPI_MUL_AUX: return launch_lean<true, B_KC, FAST_MUL_AUX>(g, s);
+    case EPI_MUL_1MZ2: return launch_lean<true, B_KC, FAST_MUL_1MZ2>(g, s);
+    case EPI_ADD_AUX: return launch_lean<true, B_KC, FAST_ADD_AUX>(g, s);
+    default: break;
   }
-  const int tiles_m = (int)((g.M + BM - 1) / BM), tiles_n = (int)((g.N + BN - 1) / BN);
-  const long total = (long)tiles_m * tiles_n * g.batch * g.split_k;
-  const long per_xcd = (total + 7) / 8;
-  const long wg_per_xcd = per_xcd < 32 ? per_xcd : 32;   // 32 CUs per XCD, one workgroup each
-  hipLaunchKernelGGL(kern, dim3((unsigned)(wg_per_xcd * 8)), dim3(NTHR), LDS_BYTES, s, g, tiles_m, tiles_n, total,
-                     per_xcd);
-  return hipGetLastError();
+  if constexpr (B_KC) {
+    if (g.mode == EPI_ACT_GELU) return launch_lean<true, true, FAST_ACT_GELU>(g, s);
+    if (g.mode == EPI_RESID) return launch_lean<true, true, FAST_RESID>(g, s);
+  }
+  return hipErrorInvalidValue;
+}
+hipError_t launch_lean_for(const GemmArgs& g, bool a_kc, bool b_kc, hipStream_t s) {
+  if (!a_kc) return launch_lean<false, false, FAST_STORE_F32>(g, s);
+  return b_kc ? launch_lean_kc<true>(g, s) : launch_lean_kc<false>(g, s);
+}
+
+// rows m0 .. m1 and columns n0 .. n1 of a product
+GemmArgs part_of(const GemmArgs& g, long m0, long m1, long n0, long n1) {
+  GemmArgs p = g;
+  p.M = m1 - m0;
+  p.N = n1 - n0;
+  p.A = reinterpret_cast<const bf16_t*>(g.A) + m0 * g.a_sm;
+  p.B = reinterpret_cast<const bf16_t*>(g.B) + n0 * g.b_sn;
+  const long o = m0 * g.ldc + n0;
+  if (g.c_is_f32 || g.split_k > 1) p.C = reinterpret_cast<float*>(g.C) + o;
+  else p.C = reinterpret_cast<bf16_t*>(g.C) + o;
+  if (g.aux) p.aux = reinterpret_cast<const bf16_t*>(g.aux) + o;
+  if (g.out2) p.out2 = reinterpret_cast<bf16_t*>(g.out2) + o;
+  if (g.addf) p.addf = g.addf + o;
+  if (g.lambda) p.lambda = g.lambda + n0;
+  if (g.lambda_mn) p.lambda_mn = reinterpret_cast<const bf16_t*>(g.lambda_mn) + o;
+  return p;
 }
 
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
@@ -1025,85 +712,21 @@ bool launch_gemm_mfma(const GemmArgs& g, hipStream_t s, hipError_t* err) {
   if (g.split_k > 1 && g.mode != EPI_STORE) return false;
   if (g.M <= 0 || g.N <= 0 || g.K <= 0 || g.batch <= 0 || g.split_k <= 0) return false;
   const bool act = g.mode == EPI_ACT_GELU || g.mode == EPI_ACT_TANH;
-  const bool plain = g.mode == EPI_STORE && !g.addf;
-  const bool lean = lean_ok(g);
-  const bool bf16_out = !g.addf && !g.c_is_f32 && g.split_k == 1;
-  if (a_kc && b_rc && !act) {            // VJP contractions
-    // Row or column counts that are no multiple of the tile (any number of tokens, any width): the whole tiles go
-    // to the aligned kernel, the remaining columns and then the remaining rows to the general one in launches of
-    // their own.  The parts write disjoint blocks of C.
-    const bool fast_mode = g.mode == EPI_STORE || g.mode == EPI_MUL_AUX || g.mode == EPI_MUL_1MZ2 || g.mode == EPI_ADD_AUX;
-    if (!lean && bf16_out && fast_mode && g.K % BK == 0) {
-      if (g.N > BN && g.N % BN != 0) {
-        GemmArgs head = g, tail = g;
-        head.N = g.N / BN * BN;
-        tail.N = g.N - head.N;
-        tail.B = reinterpret_cast<const bf16_t*>(g.B) + head.N;
-        tail.C = reinterpret_cast<bf16_t*>(g.C) + head.N;
-        if (g.aux) tail.aux = reinterpret_cast<const bf16_t*>(g.aux) + head.N;
-        hipError_t e1 = hipSuccess;
-        if (!launch_gemm_mfma(head, s, &e1)) { *err = launch_variant<true, false, false>(g, s); return true; }
-        if (e1 != hipSuccess) { *err = e1; return true; }
-        *err = launch_variant<true, false, false>(tail, s);
-        return true;
-      }
-      if (g.M > BM && g.M % BM != 0 && g.N % BN == 0) {
-        GemmArgs head = g, tail = g;
-        head.M = g.M / BM * BM;
-        tail.M = g.M - head.M;
-        tail.A = reinterpret_cast<const bf16_t*>(g.A) + head.M * g.a_sm;
-        tail.C = reinterpret_cast<bf16_t*>(g.C) + head.M * g.ldc;
-        if (g.aux) tail.aux = reinterpret_cast<const bf16_t*>(g.aux) + head.M * g.ldc;
-        hipError_t e1 = hipSuccess;
-        if (!launch_gemm_mfma(head, s, &e1)) { *err = launch_variant<true, false, false>(g, s); return true; }
-        if (e1 != hipSuccess) { *err = e1; return true; }
-        *err = launch_variant<true, false, false>(tail, s);
-        return true;
-      }
+  if (!(a_kc && (b_kc || (b_rc && !act))) && !(a_rc && b_rc && !act)) return false;
+  if (has_lean(g, a_kc, b_kc) && g.K % ((long)g.split_k * BK) == 0) {
+    const long hm = g.M / BM * BM, hn = g.N / BN * BN;
+    const long tiles = (hm / BM) * (hn / BN) * g.batch * g.split_k;
+    if (hm == g.M && hn == g.N) {
+      if (fills_chip(tiles)) { *err = launch_lean_for(g, a_kc, b_kc, s); return true; }
+    } else if (tiles >= SPLIT_FROM) {
+      // the whole tiles, then the remaining columns of all rows, then the remaining rows (disjoint blocks of C)
+      *err = launch_lean_for(part_of(g, 0, hm, 0, hn), a_kc, b_kc, s);
+      if (*err == hipSuccess && hn < g.N) *err = launch_tile_for(part_of(g, 0, g.M, hn, g.N), s);
+      if (*err == hipSuccess && hm < g.M) *err = launch_tile_for(part_of(g, hm, g.M, 0, hn), s);
+      return true;
     }
-    if (lean && bf16_out && g.mode == EPI_STORE) *err = launch_lean<true, false, FAST_STORE>(g, s);
-    else if (lean && bf16_out && g.mode == EPI_MUL_AUX) *err = launch_lean<true, false, FAST_MUL_AUX>(g, s);
-    else if (lean && bf16_out && g.mode == EPI_MUL_1MZ2) *err = launch_lean<true, false, FAST_MUL_1MZ2>(g, s);
-    else if (lean && bf16_out && g.mode == EPI_ADD_AUX) *err = launch_lean<true, false, FAST_ADD_AUX>(g, s);
-    else *err = launch_variant<true, false, false>(g, s);
-  } else if (a_rc && b_rc && !act) {     // parameter gradients
-    // the same split for widths that are no multiple of the tile (fp32 result or split-K partial sums)
-    if (!lean && plain && (g.c_is_f32 || g.split_k > 1) && g.K % ((long)g.split_k * BK) == 0) {
-      const bool by_rows = g.M > BM && g.M % BM != 0;
-      const bool by_cols = !by_rows && g.N > BN && g.N % BN != 0 && g.M % BM == 0;
-      if (by_rows || by_cols) {
-        GemmArgs head = g, tail = g;
-        if (by_rows) {
-          head.M = g.M / BM * BM;
-          tail.M = g.M - head.M;
-          tail.A = reinterpret_cast<const bf16_t*>(g.A) + head.M;          // a_sm == 1
-          tail.C = reinterpret_cast<float*>(g.C) + head.M * g.ldc;
-        } else {
-          head.N = g.N / BN * BN;
-          tail.N = g.N - head.N;
-          tail.B = reinterpret_cast<const bf16_t*>(g.B) + head.N;          // b_sn == 1
-          tail.C = reinterpret_cast<float*>(g.C) + head.N;
-        }
-        hipError_t e1 = hipSuccess;
-        if (!launch_gemm_mfma(head, s, &e1)) { *err = launch_variant<false, false, false>(g, s); return true; }
-        if (e1 != hipSuccess) { *err = e1; return true; }
-        *err = launch_variant<false, false, false>(tail, s);
-        return true;
-      }
-    }
-    if (lean && plain && (g.c_is_f32 || g.split_k > 1)) *err = launch_lean<false, false, FAST_STORE_F32>(g, s);
-    else *err = launch_variant<false, false, false>(g, s);
-  } else if (a_kc && b_kc) {             // forward; VJP contractions against transposed weights
-    if (lean && bf16_out && g.mode == EPI_ACT_GELU && g.out2) *err = launch_lean<true, true, FAST_ACT_GELU>(g, s);
-    else if (lean && bf16_out && g.mode == EPI_RESID && g.aux && !g.lambda_mn) *err = launch_lean<true, true, FAST_RESID>(g, s);
-    else if (lean && bf16_out && g.mode == EPI_STORE) *err = launch_lean<true, true, FAST_STORE>(g, s);
-    else if (lean && bf16_out && g.mode == EPI_MUL_AUX) *err = launch_lean<true, true, FAST_MUL_AUX>(g, s);
-    else if (lean && bf16_out && g.mode == EPI_MUL_1MZ2) *err = launch_lean<true, true, FAST_MUL_1MZ2>(g, s);
-    else if (lean && bf16_out && g.mode == EPI_ADD_AUX) *err = launch_lean<true, true, FAST_ADD_AUX>(g, s);
-    else *err = act ? launch_variant<true, true, true>(g, s) : launch_variant<true, true, false>(g, s);
-  } else {
-    return false;
   }
+  *err = launch_tile_for(g, s);
   return true;
 }
 

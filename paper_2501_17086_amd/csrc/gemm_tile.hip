@@ -1,0 +1,284 @@
+// bf16 GEMM on the matrix cores for the shapes the 256 x 256 kernel does not serve well: sizes that are no multiple of
+// its tile, few output tiles, and every epilogue it does not have.
+//
+//   workgroup   256 threads (2 x 2 wavefronts), one output tile of 128 x 128 or 64 x 64; two workgroups share a
+//               compute unit (64 KB of LDS each), so that one's epilogue and fill run under the other's products.
+//   K pipeline  slices of 32 (128-wide tile) or 64 (64-wide) of both operands go global -> LDS directly through a ring
+//               of four 16 KB stages, three slices ahead; one counted wait and one barrier per slice.
+//   edges       a lane's source row (or its chunk of 8 rows) is clamped to the matrix once per tile, so the main loop is
+//               the same for every tile; what such lanes produce is never stored.  Only a last, partial slice of
+//               the contraction is special: its chunks past the end are copied from a zero-filled device array.
+//   layouts     as in gemm_mfma.hip: KC (contraction contiguous, 16-byte LDS reads) and RC (rows contiguous,
+//               ds_read_b64_tr_b16), the 64 banks spread by an XOR of the 16-byte chunk index on both sides.
+//   epilogue    32 rows of a wavefront's block at a time through LDS as fp32, so that every global access (aux, old
+//               state, results) covers consecutive 16-byte pieces of a row; all modes, each access guarded.
+#include "gemm_device.h"
+
+namespace hbp {
+
+namespace {
+
+constexpr int NST = 4, NTHR = 256;
+
+// One operand tile of T rows x BK of the contraction in LDS.
+template <int T, int BK, bool KC>
+struct Tile {
+  static constexpr int BYTES = T * BK * 2;
+  static constexpr int COPIES = BYTES / 1024 / 4;                // per wavefront and slice, 1 KB each
+  static constexpr int CPR = KC ? BK / 8 : T / 8;                // 16-byte chunks per LDS row
+  // the XOR on the chunk index of LDS row r (KC: a matrix row; RC: a contraction index)
+  static __device__ __forceinline__ int swz(int r) {
+    if (KC) return BK == 32 ? (r >> 2) & 3 : (r >> 1) & 7;
+    return T == 128 ? 4 * (r & 3) : 4 * ((r >> 1) & 1);
+  }
+  // LDS row and logical chunk of this lane's 16 bytes of copy i
+  static __device__ __forceinline__ int lane_row(int i, int wave, int lane) { return (wave + 4 * i) * (64 / CPR) + lane / CPR; }
+  static __device__ __forceinline__ int lane_chunk(int i, int wave, int lane) {
+    return (lane % CPR) ^ swz(lane_row(i, wave, lane));
+  }
+  // byte offset from the tile's first element at the slice's first contraction index; rows_left > 0 rows are there
+  static __device__ __forceinline__ unsigned source(long ld, long rows_left, int i, int wave, int lane) {
+    const int r = lane_row(i, wave, lane), c = lane_chunk(i, wave, lane);
+    if (KC) return (unsigned)((r < rows_left ? r : rows_left - 1) * ld + 8 * c) * 2u;
+    return (unsigned)(r * ld + (8 * c < rows_left ? 8 * c : rows_left - 8)) * 2u;
+  }
+  // is this lane's chunk of a slice that has k_left < BK contraction indices inside?
+  static __device__ __forceinline__ bool in_tail(long k_left, int i, int wave, int lane) {
+    return (KC ? 8 * lane_chunk(i, wave, lane) : lane_row(i, wave, lane)) < k_left;
+  }
+  // 32 rows x 16 k fragment: lane l holds row row0 + l % 32, k = kk + 8 (l / 32) .. + 7
+  static __device__ __forceinline__ bf16x8 frag(const unsigned char* tile, int row0, int kk, int lane) {
+    if (KC) {
+      const int r = row0 + (lane & 31);
+      const int c = (kk >> 3) + (lane >> 5);
+      return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(tile + r * (2 * BK) + ((c ^ swz(r)) << 4)));
+    }
+    typedef __attribute__((address_space(3))) short4v* lds_p;
+    const int s = lane & 15;
+    const int e = row0 + 16 * ((lane >> 4) & 1) + 4 * (s & 3);
+    const int k = kk + 8 * (lane >> 5) + (s >> 2);               // (swz(k + 4) == swz(k))
+    const unsigned char* p = tile + k * (2 * T) + (((e >> 3) ^ swz(k)) << 4) + (e & 7) * 2;
+    const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_p)(p));
+    const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_p)(p + 8 * T));
+    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+  }
+};
+
+// T x T output tile per workgroup.  ACT: the forward's activations (kept out of the other kernels' registers).
+template <int T, int BK, bool A_KC, bool B_KC, bool ACT>
+__global__ __launch_bounds__(NTHR, 2) void gemm_tile_kernel(GemmArgs g, int tiles_m, int tiles_n, int total, int per_xcd) {
+  typedef Tile<T, BK, A_KC> TA;
+  typedef Tile<T, BK, B_KC> TB;
+  constexpr int STAGE = TA::BYTES + TB::BYTES;
+  constexpr int PER = TA::COPIES + TB::COPIES;             // copies per wavefront and slice
+  constexpr int W = T / 2, NB = W / 32;                    // a wavefront's block: W x W, NB x NB MFMA blocks
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[NST * STAGE];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm0 = (wave >> 1) * W, wn0 = (wave & 1) * W;
+  const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
+
+  // ids are dealt to the 8 XCDs in turn: each takes a contiguous eighth of the tile list, in blocks of 8 tile rows
+  const int t = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
+  if (t >= total) return;
+  const unsigned tiles_mn = (unsigned)tiles_m * tiles_n;
+  const unsigned zb = (unsigned)t / tiles_mn, rem = (unsigned)t - zb * tiles_mn;
+  const unsigned gr = rem / (8u * tiles_n), in_gr = rem - gr * 8u * tiles_n;
+  const unsigned left = tiles_m - gr * 8u, gm = left < 8u ? left : 8u;
+  const long m0 = (long)(gr * 8u + in_gr % gm) * T, n0 = (long)(in_gr / gm) * T;
+  const long batch = zb / (unsigned)g.split_k;
+  const int split = (int)(zb % (unsigned)g.split_k);
+  const long kchunk = ((g.K + g.split_k - 1) / g.split_k + 31) / 32 * 32;   // (32 whatever BK: the shares do not depend on the tile)
+  const long k_begin = (long)split * kchunk;
+  const long k_end = k_begin + kchunk < g.K ? k_begin + kchunk : g.K;
+  const int KT = k_end > k_begin ? (int)((k_end - k_begin + BK - 1) / BK) : 0;
+
+  const long lda = A_KC ? g.a_sm : g.a_sk, ldb = B_KC ? g.b_sn : g.b_sk;
+  const bf16_t* pa = reinterpret_cast<const bf16_t*>(g.A) + batch * g.a_sb + (A_KC ? m0 * lda + k_begin : m0 + k_begin * lda);
+  const bf16_t* pb = reinterpret_cast<const bf16_t*>(g.B) + batch * g.b_sb + (B_KC ? n0 * ldb + k_begin : n0 + k_begin * ldb);
+  const long step_a = A_KC ? BK : BK * lda, step_b = B_KC ? BK : BK * ldb;
+  unsigned offa[TA::COPIES], offb[TB::COPIES];
+#pragma unroll
+  for (int i = 0; i < TA::COPIES; ++i) offa[i] = TA::source(lda, g.M - m0, i, wave, lane);
+#pragma unroll
+  for (int i = 0; i < TB::COPIES; ++i) offb[i] = TB::source(ldb, g.N - n0, i, wave, lane);
+
+  auto issue = [&](int s) __attribute__((always_inline)) {
+    const unsigned dst = lds0 + (unsigned)(s % NST) * STAGE + (unsigned)wave * 1024u;
+    const long k_left = k_end - k_begin - (long)s * BK;
+    if (k_left >= BK) {
+#pragma unroll
+      for (int i = 0; i < TA::COPIES; ++i) dma16_s(offa[i], pa, dst + 4096u * i);
+#pragma unroll
+      for (int i = 0; i < TB::COPIES; ++i) dma16_s(offb[i], pb, dst + TA::BYTES + 4096u * i);
+    } else {
+#pragma unroll
+      for (int i = 0; i < TA::COPIES; ++i)
+        dma16(TA::in_tail(k_left, i, wave, lane) ? reinterpret_cast<const void*>(reinterpret_cast<const char*>(pa) + offa[i])
+                                                 : reinterpret_cast<const void*>(g_zero_chunks + lane), dst + 4096u * i);
+#pragma unroll
+      for (int i = 0; i < TB::COPIES; ++i)
+        dma16(TB::in_tail(k_left, i, wave, lane) ? reinterpret_cast<const void*>(reinterpret_cast<const char*>(pb) + offb[i])
+                                                 : reinterpret_cast<const void*>(g_zero_chunks + lane),
+              dst + TA::BYTES + 4096u * i);
+    }
+    pa += step_a;
+    pb += step_b;
+  };
+
+  // acc[i][j]: lane l, element r  <->  row wm0 + 32 i + l % 32, column wn0 + 32 j + 8 (r / 4) + 4 (l / 32) + r % 4
+  float16v acc[NB][NB];
+#pragma unroll
+  for (int i = 0; i < NB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+#pragma unroll 1
+  for (int s = 0; s < NST - 1 && s < KT; ++s) issue(s);
+#pragma unroll 1
+  for (int s = 0; s < KT; ++s) {
+    // this wavefront's share of slice s has landed once only the copies of the slices after it are outstanding
+    if (s + 2 < KT) wait_vm<2 * PER>();
+    else if (s + 2 == KT) wait_vm<PER>();
+    else wait_vm<0>();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_barrier();            // slice s is complete; everyone has read slice s - 1
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
+    if (s + NST - 1 < KT) issue(s + NST - 1);
+    const unsigned char* st = smem + (s % NST) * STAGE;
+    bf16x8 fa[NB][BK / 16], fb[NB][BK / 16];
+#pragma unroll
+    for (int h = 0; h < BK / 16; ++h) {
+#pragma unroll
+      for (int j = 0; j < NB; ++j) fb[j][h] = TB::frag(st + TA::BYTES, wn0 + 32 * j, 16 * h, lane);
+#pragma unroll
+      for (int i = 0; i < NB; ++i) fa[i][h] = TA::frag(st, wm0 + 32 * i, 16 * h, lane);
+    }
+#pragma unroll
+    for (int h = 0; h < BK / 16; ++h)
+#pragma unroll
+      for (int i = 0; i < NB; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[j][h], fa[i][h], acc[i][j], 0, 0, 0);
+  }
+
+  // ---- epilogue ----
+  constexpr int LD = W + 4;                                // floats per staged row (16-byte aligned, banks spread)
+  constexpr int LPR = W / 8, RPP = 64 / LPR, PASSES = 32 / RPP;
+  static_assert(4 * 32 * LD * 4 <= NST * STAGE, "the staging area reuses the ring");
+  __syncthreads();                                         // the last slice has been read by everyone
+  float* stg = reinterpret_cast<float*>(smem) + wave * 32 * LD;
+  const long off_b = batch * g.c_sb;
+  const bf16_t* aux = g.aux ? reinterpret_cast<const bf16_t*>(g.aux) + batch * g.aux_sb : nullptr;
+  const bf16_t* lmn = g.lambda_mn ? reinterpret_cast<const bf16_t*>(g.lambda_mn) + batch * g.aux_sb : nullptr;
+  const float* lam = g.lambda ? g.lambda + batch * g.lambda_sb : nullptr;
+  const bool use_aux = g.split_k == 1 && (g.mode == EPI_MUL_AUX || g.mode == EPI_MUL_1MZ2 || g.mode == EPI_RESID ||
+                                          g.mode == EPI_ADD_AUX);
+  const long col = n0 + wn0 + 8 * (lane % LPR);
+  const long col_in = col < g.N ? col : g.N - 8;           // (loads are clamped, stores guarded)
+  float lm[8];
+#pragma unroll
+  for (int x = 0; x < 8; ++x) lm[x] = 1.f;
+  if (!ACT && use_aux && lam && !lmn) load8(lam + col_in, lm);
+#pragma unroll
+  for (int i = 0; i < NB; ++i) {
+    const long row0 = m0 + wm0 + 32 * i + lane / LPR;
+    Raw8<bf16_t> ra[PASSES];
+    if (!ACT && use_aux) {
+#pragma unroll
+      for (int ps = 0; ps < PASSES; ++ps) {
+        const long row = row0 + ps * RPP < g.M ? row0 + ps * RPP : g.M - 1;
+        ra[ps].load(aux + row * g.ldc + col_in);
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        *reinterpret_cast<float4*>(stg + (lane & 31) * LD + 32 * j + 8 * q + 4 * (lane >> 5)) =
+            make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
+    __builtin_amdgcn_wave_barrier();                       // (a wavefront's LDS operations execute in order)
+#pragma unroll
+    for (int ps = 0; ps < PASSES; ++ps) {
+      const long row = row0 + ps * RPP;
+      float v[8];
+      load8(stg + (lane / LPR + ps * RPP) * LD + 8 * (lane % LPR), v);
+      if (row >= g.M || col >= g.N) continue;
+      const long off = row * g.ldc + col;
+      if (g.split_k > 1) {
+        store8(reinterpret_cast<float*>(g.C) + ((long)split * g.batch + batch) * g.c_sb + off, v);
+        continue;
+      }
+      if (g.addf) {
+        float f[8];
+        load8(g.addf + batch * g.addf_sb + off, f);
+#pragma unroll
+        for (int x = 0; x < 8; ++x) v[x] += f[x];
+      }
+      if (ACT) {
+        if (g.mode == EPI_ACT_GELU) {
+          float dz[8];
+#pragma unroll
+          for (int x = 0; x < 8; ++x) gelu_both(v[x], v[x], dz[x]);
+          store8(reinterpret_cast<bf16_t*>(g.out2) + batch * g.out2_sb + off, dz);
+        } else {
+#pragma unroll
+          for (int x = 0; x < 8; ++x) v[x] = tanhf(v[x]);
+        }
+      } else if (use_aux) {
+        float f[8];
+        ra[ps].unpack(f);
+        if (g.mode == EPI_MUL_AUX) {
+#pragma unroll
+          for (int x = 0; x < 8; ++x) v[x] *= f[x];
+        } else if (g.mode == EPI_MUL_1MZ2) {
+#pragma unroll
+          for (int x = 0; x < 8; ++x) v[x] *= (1.f - f[x] * f[x]);
+        } else if (g.mode == EPI_ADD_AUX) {
+#pragma unroll
+          for (int x = 0; x < 8; ++x) v[x] += f[x];
+        } else {
+          float l8[8];
+          if (lmn) load8(lmn + off, l8);
+#pragma unroll
+          for (int x = 0; x < 8; ++x) v[x] = fmaf(lmn ? l8[x] : lm[x], f[x], v[x]);
+        }
+      }
+      if (g.c_is_f32) store8(reinterpret_cast<float*>(g.C) + off_b + off, v);
+      else store8(reinterpret_cast<bf16_t*>(g.C) + off_b + off, v);
+    }
+    __builtin_amdgcn_wave_barrier();                       // the next rows' writes stay behind these reads
+  }
+}
+
+template <int T, int BK, bool A_KC, bool B_KC, bool ACT>
+hipError_t launch_one(const GemmArgs& g, hipStream_t s) {
+  const long tiles_m = (g.M + T - 1) / T, tiles_n = (g.N + T - 1) / T;
+  const long total = tiles_m * tiles_n * g.batch * g.split_k;
+  if (total > (1L << 28)) return hipErrorInvalidValue;
+  const long per_xcd = (total + 7) / 8;
+  hipLaunchKernelGGL((gemm_tile_kernel<T, BK, A_KC, B_KC, ACT>), dim3((unsigned)(8 * per_xcd)), dim3(NTHR), 0, s, g,
+                     (int)tiles_m, (int)tiles_n, (int)total, (int)per_xcd);
+  return hipGetLastError();
+}
+template <int T, int BK>
+hipError_t launch_pairing(const GemmArgs& g, hipStream_t s) {
+  const bool a_kc = g.a_sk == 1, b_kc = g.b_sk == 1;
+  if (a_kc && b_kc)
+    return g.mode == EPI_ACT_GELU || g.mode == EPI_ACT_TANH ? launch_one<T, BK, true, true, true>(g, s)
+                                                            : launch_one<T, BK, true, true, false>(g, s);
+  return a_kc ? launch_one<T, BK, true, false, false>(g, s) : launch_one<T, BK, false, false, false>(g, s);
+}
+
+}  // namespace
+
+hipError_t launch_gemm_tile(const GemmArgs& g, int tile, hipStream_t s) {
+  return tile == 128 ? launch_pairing<128, 32>(g, s) : launch_pairing<64, 64>(g, s);
+}
+
+}  // namespace hbp

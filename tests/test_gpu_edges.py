@@ -1,0 +1,31 @@
+"""GPU parity at the sizes where a kernel's tiling can go wrong: one element past a tile, one short of it, the smallest
+call, and the sizes at which a dispatch changes kernels.  Same oracle and bars as test_gpu_parity."""
+import numpy as np
+import pytest
+
+from paper_2501_17086_amd import synth
+from tests import helpers as H
+from tests.test_gpu_parity import B, W, _check_backward, _setup  # noqa: F401  (B is the fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+def _forward_matches(B, w):
+    inp, st, sv, p = _setup(B, w)
+    B.hbp_forward(p)
+    for l in range(w.L + 1):
+        H.assert_close(H.to_np(p.x)[l], sv["x"][l], H.TOL[w.dtype], f"{w.name} x[{l}]")
+    return inp, st, sv, p
+
+
+# tokens, width, inner width: around the 64- and 128-wide output tiles and the 64- and 32-deep slices (a contraction that
+# ends inside a slice), enough tiles for the 128-wide ones (2 blocks x 23 x 8 of them), and two rounds of whole 256-wide
+# tiles plus remainders of rows and columns in launches of their own
+@pytest.mark.parametrize("N,d,d_ff", [(1, 8, 8), (7, 56, 64), (63, 64, 72), (65, 72, 128), (127, 120, 136),
+                                      (129, 128, 264), (191, 136, 1032), (2900, 264, 1000), (8200, 512, 2056)])
+def test_products_around_the_tile_edges(B, N, d, d_ff):
+    w = synth.scaled(W["resnet_like"], name=f"mlp_{N}_{d}_{d_ff}", L=2, N=N, d=d, d_ff=d_ff, w2_scale=0.7, ks=(1,))
+    inp, st, sv, p = _forward_matches(B, w)
+    H.assert_close(H.to_np(p.z), sv["z"], H.TOL["bf16"], f"{w.name} z")
+    H.assert_close(H.to_np(p.dphi), sv["dphi"], H.TOL["bf16"], f"{w.name} act'")
+    _check_backward(B, w, p, st, sv, inp, w.name)
