@@ -98,8 +98,8 @@ typedef enum { HBP_F32 = 0, HBP_BF16 = 1 } hbp_dtype;
  * [L/2,N,d_ff]; qkv [L/2,N,3d], attn_o [L/2,N,d] (the attention's output before Wo) and lse [L/2, N heads] are
  * written by hbp_forward and read by the backward calls; x, y, rinv, lambda, e, g are per state / block as for
  * HBP_MLP.  post = HBP_POST_NONE, or HBP_POST_RMS with norm = HBP_NORM_NONE (post-norm layers, the RoBERTa paragraph of the
- * appendix: use gamma around 0.8); d_in = 0; dh a multiple of 8 (bf16 with dh = 64 runs on the matrix cores, any other
- * case on plain kernels that need seq_len <= 8192). */
+ * appendix: use gamma around 0.8); d_in = 0; dh a multiple of 8 (bf16 with dh <= 128 runs on the matrix cores, any other
+ * case on plain kernels); seq_len <= 8192 unless bf16 with dh = 64. */
 typedef enum { HBP_MLP = 0, HBP_RNN = 1, HBP_GATED = 2, HBP_LSTM = 3, HBP_GRU = 4, HBP_TRANSFORMER = 5 } hbp_kind;
 /* GELU is the exact erf form a*Phi(a); IDENTITY makes blocks linear (tests). */
 typedef enum { HBP_ACT_GELU_ERF = 0, HBP_ACT_TANH = 1, HBP_ACT_IDENTITY = 2 } hbp_act;

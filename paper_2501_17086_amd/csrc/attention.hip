@@ -4,7 +4,8 @@
 // dk = dS^T q / sqrt(dh).  P is never stored: the forward keeps one number per (head, query), the base-2 logarithm of
 // the row's sum of exp2(s log2 e), and the backward kernels rebuild P tile by tile from q and k.
 //
-// bf16 storage with dh = 64 runs on the matrix cores (v_mfma_f32_32x32x16_bf16).  A workgroup of four wavefronts owns
+// bf16 storage with heads of up to 128 columns runs on the matrix cores (v_mfma_f32_32x32x16_bf16; the width is padded
+// to 32, 64 or 128).  A workgroup of four wavefronts owns
 // four tiles of 32 queries (forward, dq) or 32 keys (dk, dv), one per wavefront, and streams the other side's tiles
 // through a ring of LDS buffers that all four read:
 //   - the MFMA is issued so that a lane owns one query (dk/dv kernel: one key) and its 16 accumulator registers run
@@ -14,11 +15,11 @@
 //     registers: the contraction index of an MFMA is a dummy, so it is enough that the other operand is fetched
 //     in the same (permuted) order of keys, which the transposing LDS read ds_read_b64_tr_b16 does from the tile;
 //   - tiles reach LDS by direct copies (global_load_lds_dwordx4, no staging registers) issued three steps ahead, each
-//     wavefront copying a quarter of every tile; the loop holds no other global load, so a counted s_waitcnt tells a
+//     wavefront copying a quarter of every pair of tiles; the loop holds no other global load, so a counted s_waitcnt tells a
 //     wavefront that its share of the next tile has landed, and one barrier per step completes the hand-over;
 //   - dq on one side and dk, dv on the other are two kernels that each rebuild S: seven products instead of five,
 //     no atomics, results bitwise repeatable.
-// Everything else (fp32 storage, other head widths) takes plain one-wavefront-per-query (per-key) kernels.
+// Everything else (fp32 storage, wider heads) takes plain one-wavefront-per-query (per-key) kernels.
 #include "hbp_common.h"
 
 #include <type_traits>
@@ -165,7 +166,7 @@ __global__ __launch_bounds__(64) void attn_bwd_kv_plain_kernel(AttnArgs a) {
 }
 
 // ------------------------------------------------------------------------------------------------------------
-// matrix-core kernels: bf16, dh = 64
+// matrix-core kernels: bf16, dh <= 128
 // ------------------------------------------------------------------------------------------------------------
 // mfma(X, Y, acc): lane l, element r of acc  +=  sum_k X[8 (r/4) + 4 (l/32) + r%4][k] * Y[l % 32][k], where for one
 // step of 16 k-values a lane's 8 operand elements are k = 8 (l/32) .. + 7 of row l % 32 of X and of Y.  Only the
@@ -176,37 +177,37 @@ __device__ __forceinline__ float16v mfma(bf16x8 x, bf16x8 y, float16v acc) {
 __device__ __forceinline__ int tile_row_of(int r, int hh) { return 8 * (r >> 2) + 4 * hh + (r & 3); }
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }   // v_exp_f32: exp2(-inf) = 0
 
-// A wavefront's LDS tile: 32 rows x 64 bf16 (128-byte rows), 16-byte chunk c of row r at chunk c ^ ((r >> 1) & 7).
-__device__ __forceinline__ int swz(int r) { return (r >> 1) & 7; }
+// An LDS tile: 32 rows of one head, DHP columns of bf16 (DHP = 32, 64 or 128: the head width rounded up).  The 16-byte
+// chunks of a row are spread over the 64 banks by an XOR: within any four consecutive rows the XOR (with the row's
+// place in the 256 bytes that the banks span) moves a group of four chunks to four different places, which is what a
+// transposing read of four rows touches at once, and within any sixteen rows it moves a single chunk to all places, for
+// the reads along a row.
+template <int DHP>
+struct Geo {
+  static constexpr int RB = 2 * DHP;                 // bytes per row
+  static constexpr int TB = 32 * RB;                 // ... per tile
+  static constexpr int CPR = RB / 16;                // chunks per row
+  static constexpr int RPC = 64 / CPR;               // rows per copy of 1 KB
+  static constexpr int COPIES = TB / 1024;           // copies per tile
+  static constexpr int PW = 2 * COPIES / 4;          // copies per wavefront of a pair of tiles, four wavefronts sharing it
+  static constexpr int KK = DHP / 16;                // steps of 16 columns
+  static constexpr int MB = DHP / 32;                // blocks of 32 columns
+  static __device__ __forceinline__ int swz(int r) {
+    if (DHP == 32) return (r >> 2) & 3;
+    if (DHP == 64) return (((r >> 1) & 1) << 2) | ((r >> 2) & 3);
+    return ((r & 3) << 2) | ((r >> 2) & 3);
+  }
+};
 
 // Addresses: a wavefront-uniform pointer to row 0 of the 32-row tile plus one 32-bit byte offset per lane, which is
-// the same for every whole tile (LaneOffsets, computed once); a tile that runs past the last row re-reads that row
-// instead (CLAMP: rows_left < 32 rows are there).
-struct LaneOffsets {
-  unsigned frag;       // fragment loads: row l % 32, 16 bytes at column 8 (l / 32)  (+ 32 bytes per step kk)
-  unsigned ldb;        // row stride in bytes
-};
-__device__ __forceinline__ LaneOffsets lane_offsets(unsigned ldb, int lane) {
-  LaneOffsets o;
-  o.ldb = ldb;
-  o.frag = (unsigned)(lane & 31) * ldb + (unsigned)(lane >> 5) * 16u;
-  return o;
-}
+// the same for every whole tile (computed once); a tile that runs past the last row re-reads that row instead.  A head
+// narrower than DHP: the chunks past its width repeat its last one (finite wherever the head is) and meet zeros in the
+// other operand of every product that contracts over them; results in those columns are not stored.
+//
 // Tiles reach LDS by direct copies (global_load_lds_dwordx4: 16 bytes per lane from memory to lds_base + 16 lane,
-// no staging registers), issued steps ahead into a ring of buffers.  A copy instruction fills 8 rows of the tile; the
-// chunk swizzle is applied on the memory side: LDS position (row r, slot c) receives chunk c ^ swz(r) of the row.  The
-// compiler sees neither the LDS write nor when it lands: a counted wait (copies_in_flight) and the workgroup's barrier
-// (workgroup_handover) come before the reads.
-struct CopyOffsets { unsigned o[4]; };
-__device__ __forceinline__ CopyOffsets copy_offsets(unsigned ldb, int lane) {
-  CopyOffsets c;
-#pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const int r = 8 * u + (lane >> 3);
-    c.o[u] = (unsigned)r * ldb + (unsigned)(((lane & 7) ^ swz(r)) << 4);
-  }
-  return c;
-}
+// no staging registers), issued steps ahead into a ring of buffers.  The chunk swizzle is applied on the memory side:
+// LDS position (row r, slot c) receives chunk c ^ swz(r) of the row.  The compiler sees neither the LDS write nor when
+// it lands: a counted wait (copies_in_flight) and the workgroup's barrier (workgroup_handover) come before the reads.
 __device__ __forceinline__ void copy16_to_lds(unsigned off, const void* sbase_in, unsigned lds_base) {
   // (the base is uniform by construction; say so where the register allocator has moved it to vector registers)
   const unsigned long long b = reinterpret_cast<unsigned long long>(sbase_in);
@@ -220,37 +221,56 @@ __device__ __forceinline__ void copy16_to_lds(unsigned off, const void* sbase_in
 __device__ __forceinline__ void copy4_to_lds(const void* gptr, unsigned lds_base) {
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off\n" :: "v"(gptr), "s"(lds_base) : "memory");
 }
-// 32 rows x 128 bytes from `base` (row 0 of the tile, wave-uniform) to the tile at LDS address lds_tile; CLAMP: only
-// rows_left < 32 rows exist, the others repeat the last one
-template <bool CLAMP>
-__device__ __forceinline__ void copy_tile(const unsigned char* base, const CopyOffsets& co, unsigned ldb, int rows_left,
-                                          unsigned lds_tile, int lane) {
+// this lane's byte offset into a tile (row stride ldb) for copy u, rows from rows_left on repeating the last one;
+// dh8: chunks that the head has
+template <int DHP>
+__device__ __forceinline__ unsigned copy_offset(unsigned ldb, int u, int rows_left, int dh8, int lane) {
+  typedef Geo<DHP> G;
+  const int r = G::RPC * u + lane / G::CPR;
+  int c = (lane % G::CPR) ^ G::swz(r);
+  c = c < dh8 ? c : dh8 - 1;
+  return (unsigned)(r < rows_left ? r : rows_left - 1) * ldb + (unsigned)c * 16u;
+}
+// a whole tile by one wavefront
+template <int DHP>
+__device__ __forceinline__ void copy_tile(const unsigned char* base, unsigned ldb, int rows_left, int dh8, unsigned lds_tile,
+                                          int lane) {
 #pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    unsigned off = co.o[u];
-    if (CLAMP) {
-      const int r = 8 * u + (lane >> 3);
-      off = (unsigned)(r < rows_left ? r : rows_left - 1) * ldb + (unsigned)(((lane & 7) ^ swz(r)) << 4);
+  for (int u = 0; u < Geo<DHP>::COPIES; ++u)
+    copy16_to_lds(copy_offset<DHP>(ldb, u, rows_left, dh8, lane), base, lds_tile + 1024u * u);
+}
+// A pair of tiles filled by the four wavefronts of a workgroup together, PW copies each: half of them of either tile
+// (32 columns: one copy each, of the first tile by wavefronts 0 and 1).
+template <int DHP>
+struct PairCopy {
+  typedef Geo<DHP> G;
+  static constexpr int H = G::PW < 2 ? 1 : G::PW / 2;
+  unsigned off[G::PW];
+  static __device__ __forceinline__ int tile(int w, int i) { return G::PW == 1 ? w >> 1 : i / H; }
+  static __device__ __forceinline__ int part(int w, int i) { return G::PW == 1 ? w & 1 : w * H + i % H; }
+  static __device__ __forceinline__ unsigned offset(unsigned ldb0, unsigned ldb1, int rows_left, int dh8, int w, int i, int lane) {
+    return copy_offset<DHP>(tile(w, i) ? ldb1 : ldb0, part(w, i), rows_left, dh8, lane);
+  }
+  __device__ __forceinline__ PairCopy(unsigned ldb0, unsigned ldb1, int dh8, int w, int lane) {
+#pragma unroll
+    for (int i = 0; i < G::PW; ++i) off[i] = offset(ldb0, ldb1, 32, dh8, w, i, lane);
+  }
+  // rows_left < 32: the tile that runs past the last row
+  __device__ __forceinline__ void issue(const unsigned char* t0, const unsigned char* t1, unsigned ldb0, unsigned ldb1, int rows_left,
+                                        int dh8, unsigned lds_pair, int w, int lane) const {
+    const unsigned dst = lds_pair + (unsigned)(G::PW == 1 ? w : w * H) * 1024u;
+    if (rows_left >= 32) {
+#pragma unroll
+      for (int i = 0; i < G::PW; ++i)
+        copy16_to_lds(off[i], tile(w, i) ? t1 : t0, dst + (G::PW == 1 ? 0u : (unsigned)(i / H) * G::TB + (unsigned)(i % H) * 1024u));
+    } else {
+#pragma unroll
+      for (int i = 0; i < G::PW; ++i)
+        copy16_to_lds(offset(ldb0, ldb1, rows_left, dh8, w, i, lane), tile(w, i) ? t1 : t0,
+                      dst + (G::PW == 1 ? 0u : (unsigned)(i / H) * G::TB + (unsigned)(i % H) * 1024u));
     }
-    copy16_to_lds(off, base, lds_tile + 1024u * u);
   }
-}
-// this lane's byte offset into a tile for the quarter copy of wavefront w (row 8 w + l / 8, chunk (l % 8) ^ swz(row))
-__device__ __forceinline__ unsigned quarter_offset(unsigned ldb, int w, int lane) {
-  const int r = 8 * w + (lane >> 3);
-  return (unsigned)r * ldb + (unsigned)(((lane & 7) ^ swz(r)) << 4);
-}
-// One wavefront's quarter of a tile copy (rows 8 w .. 8 w + 7): the four wavefronts of a workgroup fill a tile together.
-template <bool CLAMP>
-__device__ __forceinline__ void copy_tile_quarter(const unsigned char* base, unsigned own_off, unsigned ldb, int rows_left,
-                                                  unsigned lds_tile, int w, int lane) {
-  unsigned off = own_off;
-  if (CLAMP) {
-    const int r = 8 * w + (lane >> 3);
-    off = (unsigned)(r < rows_left ? r : rows_left - 1) * ldb + (unsigned)(((lane & 7) ^ swz(r)) << 4);
-  }
-  copy16_to_lds(off, base, lds_tile + 1024u * (unsigned)w);
-}
+};
 // at most N of this wavefront's copies still in flight (they land in issue order)
 template <int N>
 __device__ __forceinline__ void copies_in_flight() {
@@ -275,32 +295,39 @@ __device__ __forceinline__ unsigned lds_address(const void* p) {
   return (unsigned)(uintptr_t)(__attribute__((address_space(3))) const unsigned char*)p;
 }
 // operand fragment with the contraction along the tile's columns (step kk of 16 columns): lane holds row l % 32
+template <int DHP>
 __device__ __forceinline__ bf16x8 frag_cols_lds(const unsigned char* tile, int kk, int lane) {
+  typedef Geo<DHP> G;
   const int r = lane & 31, ch = 2 * kk + (lane >> 5);
-  return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(tile + r * 128 + ((ch ^ swz(r)) << 4)));
+  return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(tile + r * G::RB + ((ch ^ G::swz(r)) << 4)));
 }
-// the same straight from memory
-template <bool CLAMP>
-__device__ __forceinline__ bf16x8 frag_cols_mem(const unsigned char* base, const LaneOffsets& lo, int rows_left, int kk,
-                                                int lane) {
-  unsigned off = lo.frag;
-  if (CLAMP) {
-    const int r = lane & 31;
-    off = (unsigned)(r < rows_left ? r : rows_left - 1) * lo.ldb + (unsigned)(lane >> 5) * 16u;
-  }
-  return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(base + off + 32u * kk));
+// the same, zero past the head's width (the operand that is kept in registers)
+template <int DHP>
+__device__ __forceinline__ bf16x8 own_cols_lds(const unsigned char* tile, int kk, int dh8, int lane) {
+  const uint4 v = __builtin_bit_cast(uint4, frag_cols_lds<DHP>(tile, kk, lane));
+  const bool in = 2 * kk + (lane >> 5) < dh8;
+  return __builtin_bit_cast(bf16x8, make_uint4(in ? v.x : 0u, in ? v.y : 0u, in ? v.z : 0u, in ? v.w : 0u));
+}
+// the same straight from memory; rows from rows_left on repeat the last one
+__device__ __forceinline__ bf16x8 own_cols_mem(const unsigned char* base, unsigned ldb, int rows_left, int kk, int dh8, int lane) {
+  const int r = lane & 31, ch = 2 * kk + (lane >> 5);
+  const bool in = ch < dh8;
+  const uint4 v = *reinterpret_cast<const uint4*>(base + (unsigned)(r < rows_left ? r : rows_left - 1) * ldb + 16u * (in ? ch : 0));
+  return __builtin_bit_cast(bf16x8, make_uint4(in ? v.x : 0u, in ? v.y : 0u, in ? v.z : 0u, in ? v.w : 0u));
 }
 // operand fragment with the contraction along the tile's ROWS, in the order the accumulator of the first product
 // holds them: lane holds column 32 m + l % 32; its element i of step t is tile row 16 t + 8 (i/4) + 4 (l/32) + i%4
 // (= tile_row_of(8 t + i, l/32)).  ds_read_b64_tr_b16: within 16 lanes, lane j receives as element r' element j%4 of
 // the 8 bytes addressed by lane 4 r' + j/4.
+template <int DHP>
 __device__ __forceinline__ bf16x8 frag_rows_lds(const unsigned char* tile, int m, int t, int lane) {
+  typedef Geo<DHP> G;
   typedef __attribute__((address_space(3))) short4v* lds_p;
   const int s = lane & 15;
   const int e = 32 * m + 16 * ((lane >> 4) & 1) + 4 * (s & 3);
   const int r_lo = 16 * t + 4 * (lane >> 5) + (s >> 2), r_hi = r_lo + 8;
-  const unsigned char* p_lo = tile + r_lo * 128 + (((e >> 3) ^ swz(r_lo)) << 4) + (e & 7) * 2;
-  const unsigned char* p_hi = tile + r_hi * 128 + (((e >> 3) ^ swz(r_hi)) << 4) + (e & 7) * 2;
+  const unsigned char* p_lo = tile + r_lo * G::RB + (((e >> 3) ^ G::swz(r_lo)) << 4) + (e & 7) * 2;
+  const unsigned char* p_hi = tile + r_hi * G::RB + (((e >> 3) ^ G::swz(r_hi)) << 4) + (e & 7) * 2;
   const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_p)(p_lo));
   const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_p)(p_hi));
   return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
@@ -314,13 +341,23 @@ __device__ __forceinline__ bf16x8 pack8(const float* v) {
 __device__ __forceinline__ void store4b(bf16_t* p, float a, float b, float c, float d) {
   *reinterpret_cast<uint2*>(p) = make_uint2(pack_bf16x2(a, b), pack_bf16x2(c, d));
 }
-// a lane's 2 x 16 results (columns 32 m + tile_row_of(r, hh)) of its row, scaled
-__device__ __forceinline__ void store_row(bf16_t* row, const float16v& a0, const float16v& a1, float f, int hh) {
+// a lane's MB x 16 results (columns 32 m + tile_row_of(r, hh)) of its row, scaled; dh of them are there
+template <int MB>
+__device__ __forceinline__ void store_row(bf16_t* row, const float16v (&acc)[MB], float f, int dh, int hh) {
 #pragma unroll
-  for (int g = 0; g < 4; ++g) {
-    store4b(row + 8 * g + 4 * hh, a0[4 * g] * f, a0[4 * g + 1] * f, a0[4 * g + 2] * f, a0[4 * g + 3] * f);
-    store4b(row + 32 + 8 * g + 4 * hh, a1[4 * g] * f, a1[4 * g + 1] * f, a1[4 * g + 2] * f, a1[4 * g + 3] * f);
-  }
+  for (int m = 0; m < MB; ++m)
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+      if (32 * m + 8 * g < dh)
+        store4b(row + 32 * m + 8 * g + 4 * hh, acc[m][4 * g] * f, acc[m][4 * g + 1] * f, acc[m][4 * g + 2] * f,
+                acc[m][4 * g + 3] * f);
+}
+template <int MB>
+__device__ __forceinline__ void zero_acc(float16v (&acc)[MB]) {
+#pragma unroll
+  for (int m = 0; m < MB; ++m)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[m][r] = 0.f;
 }
 __device__ __forceinline__ float dot8(bf16x8 a, bf16x8 b) {
   const uint4 x = __builtin_bit_cast(uint4, a), y = __builtin_bit_cast(uint4, b);
@@ -335,7 +372,7 @@ __device__ __forceinline__ float dot8(bf16x8 a, bf16x8 b) {
 }
 
 constexpr int AT_WAVES = 4;    // wavefronts per workgroup: 4 tiles of 32 queries (dk/dv kernel: keys) that share the streamed tiles
-constexpr int AT_NST = 4;      // stages of the ring of streamed tile pairs (8 KB each): copies run AT_NST - 1 steps ahead
+constexpr int AT_NST = 4;      // stages of the ring of streamed tile pairs: copies run AT_NST - 1 steps ahead
 
 // Which (sequence, head) problem and which block of AT_WAVES tiles a workgroup takes.  Consecutive workgroup ids go to
 // the eight XCDs in turn, each with an L2 of its own, and all blocks of one problem stream the same k / v (q / do)
@@ -368,7 +405,7 @@ inline long attn_grid(const AttnArgs& a) {
 }
 
 // One (sequence, head): wavefront-uniform byte pointers to row 0 of q, k, v (row stride 6 d bytes) and of the
-// d-wide arrays (row stride 2 d bytes), all at the head's 64 columns.
+// d-wide arrays (row stride 2 d bytes), all at the head's columns.
 struct Head {
   const unsigned char* q; const unsigned char* k; const unsigned char* v;
   long wide_off;         // byte offset of row 0 of the head in a [tokens, d] array
@@ -380,26 +417,27 @@ __device__ __forceinline__ Head head_of(const AttnArgs& a, unsigned p) {
   const unsigned heads = (unsigned)a.heads;
   hd.h = p % heads;
   const unsigned seq = p / heads;
-  hd.d = (long)heads * 64;
+  hd.d = (long)heads * a.dh;
   hd.ld = 3 * hd.d;
   hd.tok0 = (long)seq * a.T;
-  hd.q = reinterpret_cast<const unsigned char*>(a.qkv) + (hd.tok0 * hd.ld + (long)hd.h * 64) * 2;
+  hd.q = reinterpret_cast<const unsigned char*>(a.qkv) + (hd.tok0 * hd.ld + (long)hd.h * a.dh) * 2;
   hd.k = hd.q + hd.d * 2;
   hd.v = hd.k + hd.d * 2;
-  hd.wide_off = (hd.tok0 * hd.d + (long)hd.h * 64) * 2;
+  hd.wide_off = (hd.tok0 * hd.d + (long)hd.h * a.dh) * 2;
   return hd;
 }
 
 // The three kernels share one shape.  A workgroup of four wavefronts owns four consecutive tiles of 32 queries
 // (dk/dv kernel: keys), one per wavefront, and streams the tiles of the other side through a ring of AT_NST buffer
-// pairs that all four read: at step t each wavefront waits for its own quarter of pair t, the workgroup meets at a
-// barrier (pair t complete; everyone done with pair t-1), the quarter copies of pair t + AT_NST - 1 go out into the
+// pairs that all four read: at step t each wavefront waits for its own share of pair t, the workgroup meets at a
+// barrier (pair t complete; everyone done with pair t-1), its copies of pair t + AT_NST - 1 go out into the
 // buffer just freed, and the wavefront computes on pair t (or skips it when the causal mask hides the whole tile from
 // its rows).  No global load is issued inside the loop other than these copies, so the counted wait is exact.
 
-template <bool CAUSAL>
+template <int DHP, bool PAD, bool CAUSAL>
 __global__ __launch_bounds__(64 * AT_WAVES, 2) void attn_fwd_mfma_kernel(AttnArgs a) {
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[AT_NST][2][4096];   // [stage][k | v]
+  typedef Geo<DHP> G;
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[AT_NST][2][G::TB];   // [stage][k | v]
   const int lane = threadIdx.x & 63, hh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int T = (int)a.T, nt = (T + 31) >> 5;
@@ -411,7 +449,8 @@ __global__ __launch_bounds__(64 * AT_WAVES, 2) void attn_fwd_mfma_kernel(AttnArg
   const bool live = qt < nt;                                       // a ragged workgroup's spare wavefronts only copy
   const unsigned p = bo.p;
   const Head hd = head_of(a, p);
-  const LaneOffsets lo = lane_offsets((unsigned)(hd.ld * 2), lane);
+  const unsigned ldb = (unsigned)(hd.ld * 2);
+  const int dh = PAD ? a.dh : DHP, dh8 = dh >> 3;
   const unsigned lds0 = lds_address(smem);
   const bool ragged = (T & 31) != 0;
   const int q0 = 32 * qt, qi = q0 + (lane & 31);
@@ -419,27 +458,20 @@ __global__ __launch_bounds__(64 * AT_WAVES, 2) void attn_fwd_mfma_kernel(AttnArg
   const int last_q = AT_WAVES * blk + AT_WAVES - 1 < nt - 1 ? AT_WAVES * blk + AT_WAVES - 1 : nt - 1;
   const int nkt = CAUSAL ? last_q + 1 : nt;                        // key tiles the workgroup streams
   const int own_nkt = CAUSAL ? qt + 1 : nt;                        // ... and those this wavefront's rows see
-  const unsigned own = quarter_offset(lo.ldb, wave, lane);
-  auto issue = [&](int kt) __attribute__((always_inline)) {        // this wavefront's quarters of the k and v tiles of key tile kt
-    const unsigned char* kb = hd.k + (long)(32 * kt) * lo.ldb;
-    const unsigned dst = lds0 + (unsigned)(kt % AT_NST) * 8192u;
-    if (ragged && kt == nt - 1) {
-      copy_tile_quarter<true>(kb, own, lo.ldb, T - 32 * kt, dst, wave, lane);
-      copy_tile_quarter<true>(kb + hd.d * 2, own, lo.ldb, T - 32 * kt, dst + 4096u, wave, lane);
-    } else {
-      copy_tile_quarter<false>(kb, own, lo.ldb, 32, dst, wave, lane);
-      copy_tile_quarter<false>(kb + hd.d * 2, own, lo.ldb, 32, dst + 4096u, wave, lane);
-    }
+  const PairCopy<DHP> pc(ldb, ldb, dh8, wave, lane);
+  auto issue = [&](int kt) __attribute__((always_inline)) {        // this wavefront's share of the k and v tiles of key tile kt
+    const unsigned char* kb = hd.k + (long)(32 * kt) * ldb;
+    pc.issue(kb, kb + hd.d * 2, ldb, ldb, ragged && kt == nt - 1 ? T - 32 * kt : 32, dh8,
+             lds0 + (unsigned)(kt % AT_NST) * (2u * G::TB), wave, lane);
   };
   for (int kt = 0; kt < AT_NST - 1 && kt < nkt; ++kt) issue(kt);
-  bf16x8 fq[4];
+  bf16x8 fq[G::KK];
 #pragma unroll
-  for (int kk = 0; kk < 4; ++kk) fq[kk] = frag_cols_mem<true>(hd.q + (long)(live ? q0 : 0) * lo.ldb, lo, live ? T - q0 : 1, kk, lane);
+  for (int kk = 0; kk < G::KK; ++kk) fq[kk] = own_cols_mem(hd.q + (long)(live ? q0 : 0) * ldb, ldb, live ? T - q0 : 1, kk, dh8, lane);
 #pragma unroll
-  for (int kk = 0; kk < 4; ++kk) landed(fq[kk]);
-  float16v o0, o1;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) { o0[r] = 0.f; o1[r] = 0.f; }
+  for (int kk = 0; kk < G::KK; ++kk) landed(fq[kk]);
+  float16v o[G::MB];
+  zero_acc(o);
   float m = -INFINITY, l = 0.f;
   // one tile of 32 keys; MASKED: the tile on the diagonal (causal) or the one that runs past the last key
   auto step = [&](int kt, auto masked_c) __attribute__((always_inline)) {
@@ -451,14 +483,16 @@ __global__ __launch_bounds__(64 * AT_WAVES, 2) void attn_fwd_mfma_kernel(AttnArg
 #pragma unroll
     for (int r = 0; r < 16; ++r) s[r] = 0.f;
     // every operand read of the step goes out here: those of the second product land while the scores are reduced
-    bf16x8 fk[4];
+    bf16x8 fk[G::KK], fv[G::MB][2];
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) fk[kk] = frag_cols_lds(tk, kk, lane);
-    const bf16x8 v00 = frag_rows_lds(tv, 0, 0, lane), v01 = frag_rows_lds(tv, 0, 1, lane);
-    const bf16x8 v10 = frag_rows_lds(tv, 1, 0, lane), v11 = frag_rows_lds(tv, 1, 1, lane);
+    for (int kk = 0; kk < G::KK; ++kk) fk[kk] = frag_cols_lds<DHP>(tk, kk, lane);
+#pragma unroll
+    for (int mb = 0; mb < G::MB; ++mb)
+#pragma unroll
+      for (int t = 0; t < 2; ++t) fv[mb][t] = frag_rows_lds<DHP>(tv, mb, t, lane);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) s = mfma(fk[kk], fq[kk], s);
+    for (int kk = 0; kk < G::KK; ++kk) s = mfma(fk[kk], fq[kk], s);
     float sv[16];
     float tmax = -INFINITY;
 #pragma unroll
@@ -480,16 +514,18 @@ __global__ __launch_bounds__(64 * AT_WAVES, 2) void attn_fwd_mfma_kernel(AttnArg
     l = l * alpha + ps;
     m = mn;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) { o0[r] *= alpha; o1[r] *= alpha; }
+    for (int mb = 0; mb < G::MB; ++mb)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o[mb][r] *= alpha;
     const bf16x8 p0 = pack8(sv), p1 = pack8(sv + 8);
-    o0 = mfma(v00, p0, o0);
-    o1 = mfma(v10, p0, o1);
-    o0 = mfma(v01, p1, o0);
-    o1 = mfma(v11, p1, o1);
+#pragma unroll
+    for (int mb = 0; mb < G::MB; ++mb) o[mb] = mfma(fv[mb][0], p0, o[mb]);
+#pragma unroll
+    for (int mb = 0; mb < G::MB; ++mb) o[mb] = mfma(fv[mb][1], p1, o[mb]);
   };
   // tile kt complete and visible to the workgroup, the buffer of tile kt - 1 free and refilled
   auto advance = [&](int kt) __attribute__((always_inline)) {
-    if (kt + AT_NST - 2 < nkt) copies_in_flight<2 * (AT_NST - 2)>();
+    if (kt + AT_NST - 2 < nkt) copies_in_flight<G::PW * (AT_NST - 2)>();
     else copies_in_flight<0>();
     workgroup_handover();
     if (kt + AT_NST - 1 < nkt) issue(kt + AT_NST - 1);
@@ -502,16 +538,17 @@ __global__ __launch_bounds__(64 * AT_WAVES, 2) void attn_fwd_mfma_kernel(AttnArg
   if (kt < n_own) { advance(kt); step(kt, std::true_type()); ++kt; }
   for (; kt < nkt; ++kt) advance(kt);
   if (live && qi < T) {
-    store_row(reinterpret_cast<bf16_t*>(reinterpret_cast<unsigned char*>(a.o) + hd.wide_off) + (long)qi * hd.d, o0, o1,
-              1.f / l, hh);
+    store_row(reinterpret_cast<bf16_t*>(reinterpret_cast<unsigned char*>(a.o) + hd.wide_off) + (long)qi * hd.d, o, 1.f / l,
+              dh, hh);
     if (hh == 0) a.lse[(long)p * a.T + qi] = m + log2f(l);
   }
 }
 
 // dq of four tiles of 32 queries; also leaves D = rowsum(do (.) o) of their queries for the dk/dv kernel
-template <bool CAUSAL>
+template <int DHP, bool PAD, bool CAUSAL>
 __global__ __launch_bounds__(64 * AT_WAVES, 2) void attn_bwd_q_mfma_kernel(AttnArgs a) {
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[AT_NST][2][4096];   // [stage][k | v]
+  typedef Geo<DHP> G;
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[AT_NST][2][G::TB];   // [stage][k | v]
   const int lane = threadIdx.x & 63, hh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int T = (int)a.T, nt = (T + 31) >> 5;
@@ -523,8 +560,8 @@ __global__ __launch_bounds__(64 * AT_WAVES, 2) void attn_bwd_q_mfma_kernel(AttnA
   const bool live = qt < nt;
   const unsigned p = bo.p;
   const Head hd = head_of(a, p);
-  const LaneOffsets lo = lane_offsets((unsigned)(hd.ld * 2), lane);
-  const LaneOffsets lw = lane_offsets((unsigned)(hd.d * 2), lane);
+  const unsigned ldb = (unsigned)(hd.ld * 2), ldw = (unsigned)(hd.d * 2);
+  const int dh = PAD ? a.dh : DHP, dh8 = dh >> 3;
   const unsigned lds0 = lds_address(smem);
   const bool ragged = (T & 31) != 0;
   const int q0 = live ? 32 * qt : 0, qi = 32 * qt + (lane & 31);
@@ -533,40 +570,33 @@ __global__ __launch_bounds__(64 * AT_WAVES, 2) void attn_bwd_q_mfma_kernel(AttnA
   const int last_q = AT_WAVES * blk + AT_WAVES - 1 < nt - 1 ? AT_WAVES * blk + AT_WAVES - 1 : nt - 1;
   const int nkt = CAUSAL ? last_q + 1 : nt;
   const int own_nkt = CAUSAL ? qt + 1 : nt;
-  const unsigned own = quarter_offset(lo.ldb, wave, lane);
+  const PairCopy<DHP> pc(ldb, ldb, dh8, wave, lane);
   auto issue = [&](int kt) __attribute__((always_inline)) {
-    const unsigned char* kb = hd.k + (long)(32 * kt) * lo.ldb;
-    const unsigned dst = lds0 + (unsigned)(kt % AT_NST) * 8192u;
-    if (ragged && kt == nt - 1) {
-      copy_tile_quarter<true>(kb, own, lo.ldb, T - 32 * kt, dst, wave, lane);
-      copy_tile_quarter<true>(kb + hd.d * 2, own, lo.ldb, T - 32 * kt, dst + 4096u, wave, lane);
-    } else {
-      copy_tile_quarter<false>(kb, own, lo.ldb, 32, dst, wave, lane);
-      copy_tile_quarter<false>(kb + hd.d * 2, own, lo.ldb, 32, dst + 4096u, wave, lane);
-    }
+    const unsigned char* kb = hd.k + (long)(32 * kt) * ldb;
+    pc.issue(kb, kb + hd.d * 2, ldb, ldb, ragged && kt == nt - 1 ? T - 32 * kt : 32, dh8,
+             lds0 + (unsigned)(kt % AT_NST) * (2u * G::TB), wave, lane);
   };
   for (int kt = 0; kt < AT_NST - 1 && kt < nkt; ++kt) issue(kt);
   float L2 = a.lse[(long)p * a.T + qc];
-  bf16x8 fq[4], fdo[4];
+  bf16x8 fq[G::KK], fdo[G::KK];
   float D = 0.f;
   {
-    const unsigned char* dob = reinterpret_cast<const unsigned char*>(a.dout) + hd.wide_off + (long)q0 * lw.ldb;
-    const unsigned char* ob = reinterpret_cast<const unsigned char*>(a.o) + hd.wide_off + (long)q0 * lw.ldb;
+    const unsigned char* dob = reinterpret_cast<const unsigned char*>(a.dout) + hd.wide_off + (long)q0 * ldw;
+    const unsigned char* ob = reinterpret_cast<const unsigned char*>(a.o) + hd.wide_off + (long)q0 * ldw;
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-      fq[kk] = frag_cols_mem<true>(hd.q + (long)q0 * lo.ldb, lo, T - q0, kk, lane);
-      fdo[kk] = frag_cols_mem<true>(dob, lw, T - q0, kk, lane);
-      D += dot8(fdo[kk], frag_cols_mem<true>(ob, lw, T - q0, kk, lane));
+    for (int kk = 0; kk < G::KK; ++kk) {
+      fq[kk] = own_cols_mem(hd.q + (long)q0 * ldb, ldb, T - q0, kk, dh8, lane);
+      fdo[kk] = own_cols_mem(dob, ldw, T - q0, kk, dh8, lane);
+      D += dot8(fdo[kk], own_cols_mem(ob, ldw, T - q0, kk, dh8, lane));
     }
     D += __shfl_xor(D, 32, 64);
     if (live && hh == 0 && qi < T) a.dsum[(long)p * a.T + qi] = D;
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) { landed(fq[kk]); landed(fdo[kk]); }
+    for (int kk = 0; kk < G::KK; ++kk) { landed(fq[kk]); landed(fdo[kk]); }
     landed(L2);
   }
-  float16v dq0, dq1;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) { dq0[r] = 0.f; dq1[r] = 0.f; }
+  float16v dq[G::MB];
+  zero_acc(dq);
   auto step = [&](int kt, auto masked_c) __attribute__((always_inline)) {
     constexpr bool MASKED = decltype(masked_c)::value;
     const int k0 = 32 * kt;
@@ -578,17 +608,26 @@ __global__ __launch_bounds__(64 * AT_WAVES, 2) void attn_bwd_q_mfma_kernel(AttnA
     // All operand reads of a phase go out before its first product (the compiler's counted waits then let the
     // products start as their operands arrive), and those of the third product while the scores become dS: a read
     // issued right before its product would expose the LDS latency a dozen times per step.
-    bf16x8 fk[4], fv[4];
+    // (128 columns: in two halves, the registers do not hold all of them at once)
+    constexpr int PART = G::KK < 4 ? G::KK : 4;
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) { fk[kk] = frag_cols_lds(tk, kk, lane); fv[kk] = frag_cols_lds(tv, kk, lane); }
-    __builtin_amdgcn_sched_barrier(0);
+    for (int k1 = 0; k1 < G::KK; k1 += PART) {
+      bf16x8 fk[PART], fv[PART];
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-      s = mfma(fk[kk], fq[kk], s);
-      dp = mfma(fv[kk], fdo[kk], dp);
+      for (int kk = 0; kk < PART; ++kk) { fk[kk] = frag_cols_lds<DHP>(tk, k1 + kk, lane); fv[kk] = frag_cols_lds<DHP>(tv, k1 + kk, lane); }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int kk = 0; kk < PART; ++kk) {
+        s = mfma(fk[kk], fq[k1 + kk], s);
+        dp = mfma(fv[kk], fdo[k1 + kk], dp);
+      }
+      if (k1 + PART < G::KK) __builtin_amdgcn_sched_barrier(0);
     }
-    const bf16x8 k00 = frag_rows_lds(tk, 0, 0, lane), k01 = frag_rows_lds(tk, 0, 1, lane);
-    const bf16x8 k10 = frag_rows_lds(tk, 1, 0, lane), k11 = frag_rows_lds(tk, 1, 1, lane);
+    bf16x8 kr[G::MB][2];
+#pragma unroll
+    for (int mb = 0; mb < G::MB; ++mb)
+#pragma unroll
+      for (int t = 0; t < 2; ++t) kr[mb][t] = frag_rows_lds<DHP>(tk, mb, t, lane);
     __builtin_amdgcn_sched_barrier(0);
     float ds[16];
 #pragma unroll
@@ -602,14 +641,14 @@ __global__ __launch_bounds__(64 * AT_WAVES, 2) void attn_bwd_q_mfma_kernel(AttnA
     }
     const bf16x8 d0 = pack8(ds), d1 = pack8(ds + 8);
     __builtin_amdgcn_sched_barrier(0);
-    dq0 = mfma(k00, d0, dq0);
-    dq1 = mfma(k10, d0, dq1);
-    dq0 = mfma(k01, d1, dq0);
-    dq1 = mfma(k11, d1, dq1);
+#pragma unroll
+    for (int mb = 0; mb < G::MB; ++mb) dq[mb] = mfma(kr[mb][0], d0, dq[mb]);
+#pragma unroll
+    for (int mb = 0; mb < G::MB; ++mb) dq[mb] = mfma(kr[mb][1], d1, dq[mb]);
   };
   // tile kt complete and visible to the workgroup, the buffer of tile kt - 1 free and refilled
   auto advance = [&](int kt) __attribute__((always_inline)) {
-    if (kt + AT_NST - 2 < nkt) copies_in_flight<2 * (AT_NST - 2)>();
+    if (kt + AT_NST - 2 < nkt) copies_in_flight<G::PW * (AT_NST - 2)>();
     else copies_in_flight<0>();
     workgroup_handover();
     if (kt + AT_NST - 1 < nkt) issue(kt + AT_NST - 1);
@@ -623,14 +662,16 @@ __global__ __launch_bounds__(64 * AT_WAVES, 2) void attn_bwd_q_mfma_kernel(AttnA
   for (; kt < nkt; ++kt) advance(kt);
   if (live && qi < T)
     store_row(reinterpret_cast<bf16_t*>(reinterpret_cast<unsigned char*>(a.dqkv) + (hd.q - reinterpret_cast<const unsigned char*>(a.qkv))) +
-                  (long)qi * hd.ld, dq0, dq1, a.scale, hh);
+                  (long)qi * hd.ld, dq, a.scale, dh, hh);
 }
 
-// dk, dv of four tiles of 32 keys (after the dq kernel: reads D)
-template <bool CAUSAL>
-__global__ __launch_bounds__(64 * AT_WAVES, 3) void attn_bwd_kv_mfma_kernel(AttnArgs a) {
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[AT_NST][2][4096];   // [stage][q | do]
-  __shared__ __attribute__((aligned(1024))) unsigned char own[AT_WAVES][4096];      // [wave]: the v rows of the wavefront's own keys
+// dk, dv of four tiles of 32 keys (after the dq kernel: reads D).  128-wide heads hold 128 accumulators and 64 operand
+// registers per lane: one workgroup per compute unit with all 512 registers; narrower ones fit three.
+template <int DHP, bool PAD, bool CAUSAL>
+__global__ __launch_bounds__(64 * AT_WAVES, DHP == 128 ? 1 : 3) void attn_bwd_kv_mfma_kernel(AttnArgs a) {
+  typedef Geo<DHP> G;
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[AT_NST][2][G::TB];   // [stage][q | do]
+  __shared__ __attribute__((aligned(1024))) unsigned char own[AT_WAVES][G::TB];     // [wave]: the v rows of the wavefront's own keys
   __shared__ __attribute__((aligned(256))) float stats[AT_WAVES][AT_NST][64];       // [wave][stage][L2 | D] (a copy per wavefront)
   const int lane = threadIdx.x & 63, hh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -642,8 +683,8 @@ __global__ __launch_bounds__(64 * AT_WAVES, 3) void attn_bwd_kv_mfma_kernel(Attn
   const bool live = kt < nt;
   const unsigned p = bo.p;
   const Head hd = head_of(a, p);
-  const LaneOffsets lo = lane_offsets((unsigned)(hd.ld * 2), lane);
-  const unsigned ldw = (unsigned)(hd.d * 2);
+  const unsigned ldb = (unsigned)(hd.ld * 2), ldw = (unsigned)(hd.d * 2);
+  const int dh = PAD ? a.dh : DHP, dh8 = dh >> 3;
   const unsigned char* dob = reinterpret_cast<const unsigned char*>(a.dout) + hd.wide_off;
   const unsigned lds0 = lds_address(smem), lds_s = lds_address(stats[wave]);
   const bool ragged = (T & 31) != 0;
@@ -654,35 +695,37 @@ __global__ __launch_bounds__(64 * AT_WAVES, 3) void attn_bwd_kv_mfma_kernel(Attn
   const float* stat_src = (hh == 0 ? a.lse : a.dsum) + (long)p * a.T;
   const int q_first = CAUSAL ? AT_WAVES * blk : 0;                 // query tiles the workgroup streams: q_first .. nt - 1
   const int own_first = CAUSAL ? kt : 0;                           // ... and the first one this wavefront's keys are seen by
-  const unsigned own_q = quarter_offset(lo.ldb, wave, lane), own_d = quarter_offset(ldw, wave, lane);
-  auto issue = [&](int qt) __attribute__((always_inline)) {       // quarters of the q and do tiles, and the statistics, of query tile qt
+  const PairCopy<DHP> pc(ldb, ldw, dh8, wave, lane);
+  auto issue = [&](int qt) __attribute__((always_inline)) {       // a share of the q and do tiles, and the statistics, of query tile qt
     const int q0 = 32 * qt, b = qt % AT_NST;
-    const unsigned dst = lds0 + (unsigned)b * 8192u;
-    int r = lane & 31;
-    if (ragged && qt == nt - 1) {
-      copy_tile_quarter<true>(hd.q + (long)q0 * lo.ldb, own_q, lo.ldb, T - q0, dst, wave, lane);
-      copy_tile_quarter<true>(dob + (long)q0 * ldw, own_d, ldw, T - q0, dst + 4096u, wave, lane);
-      r = r < T - q0 ? r : T - 1 - q0;
-    } else {
-      copy_tile_quarter<false>(hd.q + (long)q0 * lo.ldb, own_q, lo.ldb, 32, dst, wave, lane);
-      copy_tile_quarter<false>(dob + (long)q0 * ldw, own_d, ldw, 32, dst + 4096u, wave, lane);
-    }
+    const int left = ragged && qt == nt - 1 ? T - q0 : 32;
+    pc.issue(hd.q + (long)q0 * ldb, dob + (long)q0 * ldw, ldb, ldw, left, dh8, lds0 + (unsigned)b * (2u * G::TB), wave, lane);
+    const int r = (lane & 31) < left ? (lane & 31) : left - 1;
     copy4_to_lds(stat_src + q0 + r, lds_s + (unsigned)b * 256u);
   };
   // The wavefront's own v tile stays in LDS for the whole loop (copied before the ring's first tiles, so it has landed
   // when the first of those has), its own k tile in registers: LDS and registers then both leave room for three
-  // workgroups on a compute unit.
-  copy_tile<true>(hd.v + (long)k0 * lo.ldb, copy_offsets(lo.ldb, lane), lo.ldb, T - k0, lds_address(own[wave]), lane);
+  // workgroups on a compute unit (heads of up to 64 columns).
+  copy_tile<DHP>(hd.v + (long)k0 * ldb, ldb, T - k0, dh8, lds_address(own[wave]), lane);
   const unsigned char* ov = own[wave];
+  if (PAD) {          // the v tile is an operand that is contracted along its columns: zeros past the head's width
+    copies_in_flight<0>();
+    asm volatile("" ::: "memory");
+    for (int i = lane; i < 32 * (G::CPR - dh8); i += 64) {
+      const int r = i / (G::CPR - dh8), ch = dh8 + i % (G::CPR - dh8);
+      *reinterpret_cast<uint4*>(own[wave] + r * G::RB + ((ch ^ G::swz(r)) << 4)) = make_uint4(0u, 0u, 0u, 0u);
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
   for (int qt = q_first; qt < q_first + AT_NST - 1 && qt < nt; ++qt) issue(qt);
-  bf16x8 fk[4];
+  bf16x8 fk[G::KK];
 #pragma unroll
-  for (int kk = 0; kk < 4; ++kk) fk[kk] = frag_cols_mem<true>(hd.k + (long)k0 * lo.ldb, lo, T - k0, kk, lane);
+  for (int kk = 0; kk < G::KK; ++kk) fk[kk] = own_cols_mem(hd.k + (long)k0 * ldb, ldb, T - k0, kk, dh8, lane);
 #pragma unroll
-  for (int kk = 0; kk < 4; ++kk) landed(fk[kk]);
-  float16v dk0, dk1, dv0, dv1;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) { dk0[r] = 0.f; dk1[r] = 0.f; dv0[r] = 0.f; dv1[r] = 0.f; }
+  for (int kk = 0; kk < G::KK; ++kk) landed(fk[kk]);
+  float16v dk[G::MB], dv[G::MB];
+  zero_acc(dk);
+  zero_acc(dv);
   // one tile of 32 queries; MASKED: the tile on the diagonal (causal) or the one that runs past the last query
   auto step = [&](int qt, auto masked_c) __attribute__((always_inline)) {
     constexpr bool MASKED = decltype(masked_c)::value;
@@ -700,9 +743,9 @@ __global__ __launch_bounds__(64 * AT_WAVES, 3) void attn_bwd_kv_mfma_kernel(Attn
       dp[4 * g] = -d4.x; dp[4 * g + 1] = -d4.y; dp[4 * g + 2] = -d4.z; dp[4 * g + 3] = -d4.w;
     }
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-      s = mfma(frag_cols_lds(tq, kk, lane), fk[kk], s);
-      dp = mfma(frag_cols_lds(td, kk, lane), frag_cols_lds(ov, kk, lane), dp);
+    for (int kk = 0; kk < G::KK; ++kk) {
+      s = mfma(frag_cols_lds<DHP>(tq, kk, lane), fk[kk], s);
+      dp = mfma(frag_cols_lds<DHP>(td, kk, lane), frag_cols_lds<DHP>(ov, kk, lane), dp);
     }
     __builtin_amdgcn_sched_barrier(0);   // (keeps the second products' operand reads below: fewer live registers)
     float pr[16], ds[16];
@@ -717,17 +760,19 @@ __global__ __launch_bounds__(64 * AT_WAVES, 3) void attn_bwd_kv_mfma_kernel(Attn
     }
     const bf16x8 p0 = pack8(pr), p1 = pack8(pr + 8), d0 = pack8(ds), d1 = pack8(ds + 8);
     __builtin_amdgcn_sched_barrier(0);
-    dv0 = mfma(frag_rows_lds(td, 0, 0, lane), p0, dv0);
-    dv0 = mfma(frag_rows_lds(td, 0, 1, lane), p1, dv0);
-    dv1 = mfma(frag_rows_lds(td, 1, 0, lane), p0, dv1);
-    dv1 = mfma(frag_rows_lds(td, 1, 1, lane), p1, dv1);
-    dk0 = mfma(frag_rows_lds(tq, 0, 0, lane), d0, dk0);
-    dk0 = mfma(frag_rows_lds(tq, 0, 1, lane), d1, dk0);
-    dk1 = mfma(frag_rows_lds(tq, 1, 0, lane), d0, dk1);
-    dk1 = mfma(frag_rows_lds(tq, 1, 1, lane), d1, dk1);
+#pragma unroll
+    for (int mb = 0; mb < G::MB; ++mb) {
+      dv[mb] = mfma(frag_rows_lds<DHP>(td, mb, 0, lane), p0, dv[mb]);
+      dv[mb] = mfma(frag_rows_lds<DHP>(td, mb, 1, lane), p1, dv[mb]);
+    }
+#pragma unroll
+    for (int mb = 0; mb < G::MB; ++mb) {
+      dk[mb] = mfma(frag_rows_lds<DHP>(tq, mb, 0, lane), d0, dk[mb]);
+      dk[mb] = mfma(frag_rows_lds<DHP>(tq, mb, 1, lane), d1, dk[mb]);
+    }
   };
   auto advance = [&](int qt) __attribute__((always_inline)) {
-    if (qt + AT_NST - 2 < nt) copies_in_flight<3 * (AT_NST - 2)>();
+    if (qt + AT_NST - 2 < nt) copies_in_flight<(G::PW + 1) * (AT_NST - 2)>();
     else copies_in_flight<0>();
     workgroup_handover();
     if (qt + AT_NST - 1 < nt) issue(qt + AT_NST - 1);
@@ -743,8 +788,8 @@ __global__ __launch_bounds__(64 * AT_WAVES, 3) void attn_bwd_kv_mfma_kernel(Attn
   if (live && kj < T) {
     bf16_t* row = reinterpret_cast<bf16_t*>(reinterpret_cast<unsigned char*>(a.dqkv) + (hd.k - reinterpret_cast<const unsigned char*>(a.qkv))) +
                   (long)kj * hd.ld;
-    store_row(row, dk0, dk1, a.scale, hh);
-    store_row(row + hd.d, dv0, dv1, 1.f, hh);
+    store_row(row, dk, a.scale, dh, hh);
+    store_row(row + hd.d, dv, 1.f, dh, hh);
   }
 }
 
@@ -755,9 +800,10 @@ __global__ __launch_bounds__(64 * AT_WAVES, 3) void attn_bwd_kv_mfma_kernel(Attn
 // that is w + 1 and NT - w steps: every wavefront has the same number of steps.  Each tensor is read from memory once
 // (the two-kernel form reads q, k, v and do twice and keeps D in memory between the kernels); the arithmetic is that
 // of the two kernels, in the same order per output element.
-template <bool CAUSAL, int NT>
+template <int DHP, bool PAD, bool CAUSAL, int NT>
 __global__ __launch_bounds__(64 * NT, 1) void attn_bwd_short_mfma_kernel(AttnArgs a) {
-  __shared__ __attribute__((aligned(1024))) unsigned char tiles[4][NT][4096];   // [q | k | v | do][tile of 32 positions]
+  typedef Geo<DHP> G;
+  __shared__ __attribute__((aligned(1024))) unsigned char tiles[4][NT][G::TB];  // [q | k | v | do][tile of 32 positions]
   __shared__ __attribute__((aligned(256))) float stats[NT][64];                 // per tile: L2 of its 32 queries, then D
   const int lane = threadIdx.x & 63, hh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -766,9 +812,8 @@ __global__ __launch_bounds__(64 * NT, 1) void attn_bwd_short_mfma_kernel(AttnArg
   const bool ragged = (T & 31) != 0;
   const unsigned p = blockIdx.x;
   const Head hd = head_of(a, p);
-  const LaneOffsets lo = lane_offsets((unsigned)(hd.ld * 2), lane);
-  const unsigned ldw = (unsigned)(hd.d * 2);
-  const LaneOffsets lw = lane_offsets(ldw, lane);
+  const unsigned ldb = (unsigned)(hd.ld * 2), ldw = (unsigned)(hd.d * 2);
+  const int dh = PAD ? a.dh : DHP, dh8 = dh >> 3;
   const unsigned char* dob = reinterpret_cast<const unsigned char*>(a.dout) + hd.wide_off;
   const unsigned char* ob = reinterpret_cast<const unsigned char*>(a.o) + hd.wide_off;
   const int r0 = live ? 32 * wave : 0;                     // (a spare wavefront repeats tile 0's loads and keeps nothing)
@@ -776,18 +821,17 @@ __global__ __launch_bounds__(64 * NT, 1) void attn_bwd_short_mfma_kernel(AttnArg
   const float c = a.scale * LOG2E;
   // 1. the wavefront's four tiles (rows past the end repeat the last one), and the statistics of its queries
   if (live) {
-    const CopyOffsets co = copy_offsets(lo.ldb, lane), cw = copy_offsets(ldw, lane);
-    copy_tile<true>(hd.q + (long)r0 * lo.ldb, co, lo.ldb, T - r0, lds_address(tiles[0][wave]), lane);
-    copy_tile<true>(hd.k + (long)r0 * lo.ldb, co, lo.ldb, T - r0, lds_address(tiles[1][wave]), lane);
-    copy_tile<true>(hd.v + (long)r0 * lo.ldb, co, lo.ldb, T - r0, lds_address(tiles[2][wave]), lane);
-    copy_tile<true>(dob + (long)r0 * ldw, cw, ldw, T - r0, lds_address(tiles[3][wave]), lane);
+    copy_tile<DHP>(hd.q + (long)r0 * ldb, ldb, T - r0, dh8, lds_address(tiles[0][wave]), lane);
+    copy_tile<DHP>(hd.k + (long)r0 * ldb, ldb, T - r0, dh8, lds_address(tiles[1][wave]), lane);
+    copy_tile<DHP>(hd.v + (long)r0 * ldb, ldb, T - r0, dh8, lds_address(tiles[2][wave]), lane);
+    copy_tile<DHP>(dob + (long)r0 * ldw, ldw, T - r0, dh8, lds_address(tiles[3][wave]), lane);
   }
   float L2 = a.lse[(long)p * a.T + (ri < T ? ri : T - 1)];
   float D = 0.f;
 #pragma unroll
-  for (int kk = 0; kk < 4; ++kk)
-    D += dot8(frag_cols_mem<true>(dob + (long)r0 * ldw, lw, T - r0, kk, lane),
-              frag_cols_mem<true>(ob + (long)r0 * ldw, lw, T - r0, kk, lane));
+  for (int kk = 0; kk < G::KK; ++kk)
+    D += dot8(own_cols_mem(dob + (long)r0 * ldw, ldw, T - r0, kk, dh8, lane),
+              own_cols_mem(ob + (long)r0 * ldw, ldw, T - r0, kk, dh8, lane));
   D += __shfl_xor(D, 32, 64);
   if (hh == 0) { stats[wave][lane] = L2; stats[wave][32 + lane] = D; }
   copies_in_flight<0>();
@@ -796,12 +840,14 @@ __global__ __launch_bounds__(64 * NT, 1) void attn_bwd_short_mfma_kernel(AttnArg
   if (!live) return;
   // 2. the positions as queries: dq
   {
-    bf16x8 fq[4], fdo[4];
+    bf16x8 fq[G::KK], fdo[G::KK];
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) { fq[kk] = frag_cols_lds(tiles[0][wave], kk, lane); fdo[kk] = frag_cols_lds(tiles[3][wave], kk, lane); }
-    float16v dq0, dq1;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) { dq0[r] = 0.f; dq1[r] = 0.f; }
+    for (int kk = 0; kk < G::KK; ++kk) {
+      fq[kk] = own_cols_lds<DHP>(tiles[0][wave], kk, dh8, lane);
+      fdo[kk] = own_cols_lds<DHP>(tiles[3][wave], kk, dh8, lane);
+    }
+    float16v dq[G::MB];
+    zero_acc(dq);
     auto step = [&](int kt, auto masked_c) __attribute__((always_inline)) {
       constexpr bool MASKED = decltype(masked_c)::value;
       const unsigned char* tk = tiles[1][kt];
@@ -809,17 +855,20 @@ __global__ __launch_bounds__(64 * NT, 1) void attn_bwd_short_mfma_kernel(AttnArg
       float16v s, dp;
 #pragma unroll
       for (int r = 0; r < 16; ++r) { s[r] = 0.f; dp[r] = -D; }      // dp comes out as dP - D
-      bf16x8 fk[4], fv[4];
+      bf16x8 fk[G::KK], fv[G::KK];
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk) { fk[kk] = frag_cols_lds(tk, kk, lane); fv[kk] = frag_cols_lds(tv, kk, lane); }
+      for (int kk = 0; kk < G::KK; ++kk) { fk[kk] = frag_cols_lds<DHP>(tk, kk, lane); fv[kk] = frag_cols_lds<DHP>(tv, kk, lane); }
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {
+      for (int kk = 0; kk < G::KK; ++kk) {
         s = mfma(fk[kk], fq[kk], s);
         dp = mfma(fv[kk], fdo[kk], dp);
       }
-      const bf16x8 k00 = frag_rows_lds(tk, 0, 0, lane), k01 = frag_rows_lds(tk, 0, 1, lane);
-      const bf16x8 k10 = frag_rows_lds(tk, 1, 0, lane), k11 = frag_rows_lds(tk, 1, 1, lane);
+      bf16x8 kr[G::MB][2];
+#pragma unroll
+      for (int mb = 0; mb < G::MB; ++mb)
+#pragma unroll
+        for (int t = 0; t < 2; ++t) kr[mb][t] = frag_rows_lds<DHP>(tk, mb, t, lane);
       __builtin_amdgcn_sched_barrier(0);
       float ds[16];
 #pragma unroll
@@ -833,10 +882,10 @@ __global__ __launch_bounds__(64 * NT, 1) void attn_bwd_short_mfma_kernel(AttnArg
       }
       const bf16x8 d0 = pack8(ds), d1 = pack8(ds + 8);
       __builtin_amdgcn_sched_barrier(0);
-      dq0 = mfma(k00, d0, dq0);
-      dq1 = mfma(k10, d0, dq1);
-      dq0 = mfma(k01, d1, dq0);
-      dq1 = mfma(k11, d1, dq1);
+#pragma unroll
+      for (int mb = 0; mb < G::MB; ++mb) dq[mb] = mfma(kr[mb][0], d0, dq[mb]);
+#pragma unroll
+      for (int mb = 0; mb < G::MB; ++mb) dq[mb] = mfma(kr[mb][1], d1, dq[mb]);
     };
     const int n_own = CAUSAL ? wave + 1 : nt;
     const int n_plain = CAUSAL ? n_own - 1 : (ragged ? n_own - 1 : n_own);
@@ -845,16 +894,19 @@ __global__ __launch_bounds__(64 * NT, 1) void attn_bwd_short_mfma_kernel(AttnArg
     if (kt < n_own) step(kt, std::true_type());
     if (ri < T)
       store_row(reinterpret_cast<bf16_t*>(reinterpret_cast<unsigned char*>(a.dqkv) + (hd.q - reinterpret_cast<const unsigned char*>(a.qkv))) +
-                    (long)ri * hd.ld, dq0, dq1, a.scale, hh);
+                    (long)ri * hd.ld, dq, a.scale, dh, hh);
   }
   // 3. the positions as keys: dk, dv
   {
-    bf16x8 fk[4], fv[4];
+    bf16x8 fk[G::KK], fv[G::KK];
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) { fk[kk] = frag_cols_lds(tiles[1][wave], kk, lane); fv[kk] = frag_cols_lds(tiles[2][wave], kk, lane); }
-    float16v dk0, dk1, dv0, dv1;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) { dk0[r] = 0.f; dk1[r] = 0.f; dv0[r] = 0.f; dv1[r] = 0.f; }
+    for (int kk = 0; kk < G::KK; ++kk) {
+      fk[kk] = own_cols_lds<DHP>(tiles[1][wave], kk, dh8, lane);
+      fv[kk] = own_cols_lds<DHP>(tiles[2][wave], kk, dh8, lane);
+    }
+    float16v dk[G::MB], dv[G::MB];
+    zero_acc(dk);
+    zero_acc(dv);
     const float ninv_c = -1.0f / c;
     auto step = [&](int qt, auto masked_c) __attribute__((always_inline)) {
       constexpr bool MASKED = decltype(masked_c)::value;
@@ -870,19 +922,20 @@ __global__ __launch_bounds__(64 * NT, 1) void attn_bwd_short_mfma_kernel(AttnArg
         s[4 * g] = a4.x * ninv_c; s[4 * g + 1] = a4.y * ninv_c; s[4 * g + 2] = a4.z * ninv_c; s[4 * g + 3] = a4.w * ninv_c;
         dp[4 * g] = -d4.x; dp[4 * g + 1] = -d4.y; dp[4 * g + 2] = -d4.z; dp[4 * g + 3] = -d4.w;
       }
-      bf16x8 fqs[4], fds[4];
+      bf16x8 fqs[G::KK], fds[G::KK];
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk) { fqs[kk] = frag_cols_lds(tq, kk, lane); fds[kk] = frag_cols_lds(td, kk, lane); }
+      for (int kk = 0; kk < G::KK; ++kk) { fqs[kk] = frag_cols_lds<DHP>(tq, kk, lane); fds[kk] = frag_cols_lds<DHP>(td, kk, lane); }
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {
+      for (int kk = 0; kk < G::KK; ++kk) {
         s = mfma(fqs[kk], fk[kk], s);
         dp = mfma(fds[kk], fv[kk], dp);
       }
-      const bf16x8 t00 = frag_rows_lds(td, 0, 0, lane), t01 = frag_rows_lds(td, 0, 1, lane);
-      const bf16x8 t10 = frag_rows_lds(td, 1, 0, lane), t11 = frag_rows_lds(td, 1, 1, lane);
-      const bf16x8 u00 = frag_rows_lds(tq, 0, 0, lane), u01 = frag_rows_lds(tq, 0, 1, lane);
-      const bf16x8 u10 = frag_rows_lds(tq, 1, 0, lane), u11 = frag_rows_lds(tq, 1, 1, lane);
+      bf16x8 tr[G::MB][2], ur[G::MB][2];
+#pragma unroll
+      for (int mb = 0; mb < G::MB; ++mb)
+#pragma unroll
+        for (int t = 0; t < 2; ++t) { tr[mb][t] = frag_rows_lds<DHP>(td, mb, t, lane); ur[mb][t] = frag_rows_lds<DHP>(tq, mb, t, lane); }
       __builtin_amdgcn_sched_barrier(0);
       float pr[16], ds[16];
 #pragma unroll
@@ -896,14 +949,10 @@ __global__ __launch_bounds__(64 * NT, 1) void attn_bwd_short_mfma_kernel(AttnArg
       }
       const bf16x8 p0 = pack8(pr), p1 = pack8(pr + 8), d0 = pack8(ds), d1 = pack8(ds + 8);
       __builtin_amdgcn_sched_barrier(0);
-      dv0 = mfma(t00, p0, dv0);
-      dv1 = mfma(t10, p0, dv1);
-      dk0 = mfma(u00, d0, dk0);
-      dk1 = mfma(u10, d0, dk1);
-      dv0 = mfma(t01, p1, dv0);
-      dv1 = mfma(t11, p1, dv1);
-      dk0 = mfma(u01, d1, dk0);
-      dk1 = mfma(u11, d1, dk1);
+#pragma unroll
+      for (int mb = 0; mb < G::MB; ++mb) { dv[mb] = mfma(tr[mb][0], p0, dv[mb]); dk[mb] = mfma(ur[mb][0], d0, dk[mb]); }
+#pragma unroll
+      for (int mb = 0; mb < G::MB; ++mb) { dv[mb] = mfma(tr[mb][1], p1, dv[mb]); dk[mb] = mfma(ur[mb][1], d1, dk[mb]); }
     };
     int qt = CAUSAL ? wave : 0;
     if (CAUSAL) { step(qt, std::true_type()); ++qt; }
@@ -913,17 +962,64 @@ __global__ __launch_bounds__(64 * NT, 1) void attn_bwd_short_mfma_kernel(AttnArg
     if (ri < T) {
       bf16_t* row = reinterpret_cast<bf16_t*>(reinterpret_cast<unsigned char*>(a.dqkv) + (hd.k - reinterpret_cast<const unsigned char*>(a.qkv))) +
                     (long)ri * hd.ld;
-      store_row(row, dk0, dk1, a.scale, hh);
-      store_row(row + hd.d, dv0, dv1, 1.f, hh);
+      store_row(row, dk, a.scale, dh, hh);
+      store_row(row + hd.d, dv, 1.f, dh, hh);
     }
   }
 }
 
-inline bool use_mfma(int dtype, const AttnArgs& a) { return dtype == 1 && a.dh == 64; }
+// Every head the padded tiles hold goes to the matrix cores: even at 8 of 32 columns the plain kernels' serial dot products
+// lose (32-wide heads, 12 sequences of 100, 8 heads, 4 layers: backward 1733 us a sweep plain, 15 us here).  A head
+// of its tile's full width has the kernels without the guards (PAD = false): those cost 64-wide heads 2 % and a
+// wavefront of occupancy.
+inline bool use_mfma(int dtype, const AttnArgs& a) { return dtype == 1 && a.dh <= 128; }
+
+template <int DHP, bool PAD, bool CAUSAL>
+hipError_t launch_fwd(const AttnArgs& a, hipStream_t s) {
+  AttnArgs m = a;
+  m.by_problem = attn_grid(a) >= BY_PROBLEM_FROM;
+  hipLaunchKernelGGL((attn_fwd_mfma_kernel<DHP, PAD, CAUSAL>), dim3((unsigned)attn_grid(a)), dim3(64 * AT_WAVES), 0, s, m);
+  return hipGetLastError();
+}
+// sequences whose q, k, v and do fit into one compute unit's LDS: a whole problem per workgroup
+template <int DHP> constexpr long short_T() { return DHP == 128 ? 128 : 256; }
+template <int DHP, bool PAD, bool CAUSAL>
+hipError_t launch_bwd(const AttnArgs& a, hipStream_t s) {
+  if (a.T <= short_T<DHP>()) {
+    const long P = a.seqs * a.heads;
+    if (P > 0x7fffffffL) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)P);
+    if (a.T <= 128) {
+      hipLaunchKernelGGL((attn_bwd_short_mfma_kernel<DHP, PAD, CAUSAL, 4>), grid, dim3(256), 0, s, a);
+    } else {
+      if constexpr (DHP < 128) hipLaunchKernelGGL((attn_bwd_short_mfma_kernel<DHP, PAD, CAUSAL, 8>), grid, dim3(512), 0, s, a);
+    }
+    return hipGetLastError();
+  }
+  const dim3 grid((unsigned)attn_grid(a)), block(64 * AT_WAVES);
+  // dq is bound by its tile stream and gains from one XCD per problem; dk/dv is bound by its arithmetic and by the
+  // tail, and keeps the longest-first order (by_problem = 0 as the caller leaves it)
+  AttnArgs m = a;
+  m.by_problem = attn_grid(a) >= BY_PROBLEM_FROM;
+  hipLaunchKernelGGL((attn_bwd_q_mfma_kernel<DHP, PAD, CAUSAL>), grid, block, 0, s, m);
+  hipLaunchKernelGGL((attn_bwd_kv_mfma_kernel<DHP, PAD, CAUSAL>), grid, block, 0, s, a);
+  return hipGetLastError();
+}
+
+template <int DHP>
+hipError_t pick_fwd(const AttnArgs& a, hipStream_t s) {
+  if (a.dh == DHP) return a.causal ? launch_fwd<DHP, false, true>(a, s) : launch_fwd<DHP, false, false>(a, s);
+  return a.causal ? launch_fwd<DHP, true, true>(a, s) : launch_fwd<DHP, true, false>(a, s);
+}
+template <int DHP>
+hipError_t pick_bwd(const AttnArgs& a, hipStream_t s) {
+  if (a.dh == DHP) return a.causal ? launch_bwd<DHP, false, true>(a, s) : launch_bwd<DHP, false, false>(a, s);
+  return a.causal ? launch_bwd<DHP, true, true>(a, s) : launch_bwd<DHP, true, false>(a, s);
+}
 
 }  // namespace
 
-// the plain kernels hold a row (two rows) of T floats in LDS
+// the plain kernels hold a row (two rows) of T floats in LDS; the limit is the same for every width but 64
 bool attn_supported(int dtype, long T, int dh) {
   if (dtype == 1 && dh == 64) return T <= (1L << 20);
   return T <= 8192;
@@ -933,12 +1029,9 @@ hipError_t launch_attn_fwd(int dtype, const AttnArgs& a, hipStream_t s) {
   const long P = a.seqs * a.heads;
   if (use_mfma(dtype, a)) {
     if (attn_grid(a) > 0x7fffffffL) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)attn_grid(a)), block(64 * AT_WAVES);
-    AttnArgs m = a;
-    m.by_problem = attn_grid(a) >= BY_PROBLEM_FROM;
-    if (a.causal) hipLaunchKernelGGL(attn_fwd_mfma_kernel<true>, grid, block, 0, s, m);
-    else hipLaunchKernelGGL(attn_fwd_mfma_kernel<false>, grid, block, 0, s, m);
-    return hipGetLastError();
+    if (a.dh <= 32) return pick_fwd<32>(a, s);
+    if (a.dh <= 64) return pick_fwd<64>(a, s);
+    return pick_fwd<128>(a, s);
   }
   const dim3 grid((unsigned)P, (unsigned)a.T), block(64);
   const size_t lds = (size_t)a.T * 4;
@@ -950,32 +1043,10 @@ hipError_t launch_attn_fwd(int dtype, const AttnArgs& a, hipStream_t s) {
 hipError_t launch_attn_bwd(int dtype, const AttnArgs& a, hipStream_t s) {
   const long P = a.seqs * a.heads;
   if (use_mfma(dtype, a)) {
-    if (a.T <= 256) {        // a whole problem per workgroup
-      if (P > 0x7fffffffL) return hipErrorInvalidValue;
-      const dim3 grid((unsigned)P);
-      if (a.T <= 128) {
-        if (a.causal) hipLaunchKernelGGL((attn_bwd_short_mfma_kernel<true, 4>), grid, dim3(256), 0, s, a);
-        else hipLaunchKernelGGL((attn_bwd_short_mfma_kernel<false, 4>), grid, dim3(256), 0, s, a);
-      } else {
-        if (a.causal) hipLaunchKernelGGL((attn_bwd_short_mfma_kernel<true, 8>), grid, dim3(512), 0, s, a);
-        else hipLaunchKernelGGL((attn_bwd_short_mfma_kernel<false, 8>), grid, dim3(512), 0, s, a);
-      }
-      return hipGetLastError();
-    }
     if (attn_grid(a) > 0x7fffffffL) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)attn_grid(a)), block(64 * AT_WAVES);
-    // dq is bound by its tile stream and gains from one XCD per problem; dk/dv is bound by its arithmetic and by the
-    // tail, and keeps the longest-first order (by_problem = 0 as the caller leaves it)
-    AttnArgs m = a;
-    m.by_problem = attn_grid(a) >= BY_PROBLEM_FROM;
-    if (a.causal) {
-      hipLaunchKernelGGL(attn_bwd_q_mfma_kernel<true>, grid, block, 0, s, m);
-      hipLaunchKernelGGL(attn_bwd_kv_mfma_kernel<true>, grid, block, 0, s, a);
-    } else {
-      hipLaunchKernelGGL(attn_bwd_q_mfma_kernel<false>, grid, block, 0, s, m);
-      hipLaunchKernelGGL(attn_bwd_kv_mfma_kernel<false>, grid, block, 0, s, a);
-    }
-    return hipGetLastError();
+    if (a.dh <= 32) return pick_bwd<32>(a, s);
+    if (a.dh <= 64) return pick_bwd<64>(a, s);
+    return pick_bwd<128>(a, s);
   }
   const dim3 grid((unsigned)P, (unsigned)a.T), block(64);
   if (dtype == 0) {

@@ -29,3 +29,16 @@ def test_products_around_the_tile_edges(B, N, d, d_ff):
     H.assert_close(H.to_np(p.z), sv["z"], H.TOL["bf16"], f"{w.name} z")
     H.assert_close(H.to_np(p.dphi), sv["dphi"], H.TOL["bf16"], f"{w.name} act'")
     _check_backward(B, w, p, st, sv, inp, w.name)
+
+
+# head widths around the 32, 64 and 128 columns that the matrix-core kernels pad to (136: the plain kernels), on sequence
+# lengths of one ragged tile, one workgroup, past the whole-problem kernels (128 / 256 positions) and past a block of tiles
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("dh,T", [(8, 33), (16, 1), (24, 128), (32, 100), (32, 300), (40, 129), (56, 257), (64, 192), (72, 65),
+                                  (104, 161), (128, 32), (128, 128), (128, 200), (136, 40)])
+def test_attention_head_widths(B, dh, T, causal):
+    w = synth.scaled(W["gpt2_paper"], name=f"tfm_dh{dh}_T{T}", L=2, N=3 * T, seq_len=T, d=2 * dh, heads=2, d_ff=64, w1_std=0.0,
+                     w2_std=0.0, w2_scale=0.6, causal=causal, ks=(1, 2))
+    inp, st, sv, p = _forward_matches(B, w)
+    H.assert_close(H.to_np(p.attn_o), sv["o"][0::2], H.TOL["bf16"], f"{w.name} attention output")
+    _check_backward(B, w, p, st, sv, inp, w.name, exact=False)
