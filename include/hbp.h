@@ -39,6 +39,9 @@
  *    d > 4096 with HBP_NORM_RMS, k < 0, a required pointer that is NULL, a
  *    workspace smaller than hbp_workspace_size() reports.  A failed launch
  *    gives HBP_E_DEVICE.
+ *  - The recurrent kinds' forward pass and exact backpropagation run a whole chain in one launch (bf16, no norm, widths
+ *    up to 1024, batches of up to 64 rows at that width): at most 64 workgroups that wait for each other's results.
+ *    Up to four such launches may overlap on one GPU.
  *  - State between calls: none that changes results.  The library keeps (a) a
  *    flag per kernel and device saying that the kernel's shared-memory limit
  *    has been raised (set on the first launch, idempotent, safe from several

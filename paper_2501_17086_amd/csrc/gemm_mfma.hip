@@ -648,13 +648,17 @@ inline hipError_t launch_tile_for(const GemmArgs& g, hipStream_t s) {
 // does the lean kernel have this pairing's epilogue?
 inline bool has_lean(const GemmArgs& g, bool a_kc, bool b_kc) {
   if (!a_kc) return g.mode == EPI_STORE && !g.addf && (g.c_is_f32 || g.split_k > 1);     // parameter gradients
-  if (g.addf || g.c_is_f32 || g.split_k > 1) return false;
+  if (g.addf || g.split_k > 1) return false;
+  if (g.c_is_f32) return b_kc && g.mode == EPI_STORE;                                    // the recurrent kinds' U xin
   if (g.mode == EPI_STORE || g.mode == EPI_MUL_AUX || g.mode == EPI_MUL_1MZ2 || g.mode == EPI_ADD_AUX) return true;
   if (g.mode == EPI_ACT_GELU) return b_kc && g.out2;                                     // forward
   return g.mode == EPI_RESID && b_kc && g.aux && !g.lambda_mn;
 }
 template <bool B_KC>
 hipError_t launch_lean_kc(const GemmArgs& g, hipStream_t s) {
+  if constexpr (B_KC) {
+    if (g.c_is_f32) return launch_lean<true, true, FAST_STORE_F32>(g, s);
+  }
   switch (g.mode) {
     case EPI_STORE: return launch_lean<true, B_KC, FAST_STORE>(g, s);
     case EPI_MUL_AUX: return launch_lean<true, B_KC, FAST_MUL_AUX>(g, s);

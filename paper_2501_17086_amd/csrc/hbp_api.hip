@@ -34,7 +34,7 @@ inline bool tfm(const hbp_desc* d) { return d->kind == HBP_TRANSFORMER; }
 inline long head_w(const hbp_desc* d) { return d->d / d->heads; }
 
 struct Workspace {
-  size_t off_v, off_da, off_part, off_scan, off_wt, off_pre, off_m, off_tmp, off_dqkv, off_dsum, total;
+  size_t off_v, off_da, off_part, off_scan, off_wt, off_pre, off_m, off_tmp, off_dqkv, off_dsum, off_counter, total;
 };
 
 // split-K factor for a parameter-gradient GEMM with `tiles` output tiles and a
@@ -120,6 +120,9 @@ Workspace carve(const hbp_desc* d) {
   if (tfm(d)) o = align_up(o + (size_t)(d->L / 2) * d->N * 3 * d->d * es, 256);
   w.off_dsum = o;
   if (tfm(d)) o = align_up(o + (size_t)(d->L / 2) * d->N * d->heads * 4, 256);
+  // the chain kernels' start counter and what their workgroups exchange (2 MB)
+  w.off_counter = o;
+  if (recurrent(d) && d->dtype == HBP_BF16) o += 256 + recurrent_ring_bytes();
   w.total = o;
   return w;
 }
@@ -663,6 +666,42 @@ hbp_status hbp_check(const hbp_desc* desc, const hbp_buffers* bufs) {
   return HBP_OK;
 }
 
+namespace {
+// The whole chain along time in one launch (recurrent.hip), where the sizes allow it
+bool rec_args(const hbp_desc* d, const hbp_buffers* b, const Workspace& w, bool forward, RecArgs* out) {
+  if (!recurrent(d) || d->dtype != HBP_BF16 || d->norm != HBP_NORM_NONE) return false;
+  if (forward && d->act == HBP_ACT_GELU_ERF) return false;    // (two results per element)
+  const size_t es = esize(d);
+  RecArgs a{};
+  a.kind = d->kind == HBP_RNN ? 0 : d->kind == HBP_GATED ? 1 : d->kind == HBP_LSTM ? 2 : 3;
+  a.L = d->L; a.N = d->N; a.H = hidden_w(d); a.D = d->d; a.F = d->d_ff;
+  a.x = b->x; a.z = b->z;
+  a.lambda = d->lambda_kind == HBP_LAMBDA_CHANNEL ? reinterpret_cast<const float*>(b->lambda) : nullptr;
+  a.lambda_tok = d->lambda_kind == HBP_LAMBDA_TOKEN ? b->lambda : nullptr;
+  a.tanh_act = d->act == HBP_ACT_TANH;
+  a.counter = reinterpret_cast<int*>(at(b->workspace, w.off_counter));
+  a.ring = at(b->workspace, w.off_counter + 256);
+  if (forward) {
+    a.ux = reinterpret_cast<const float*>(at((const void*)b->workspace, w.off_da));
+    a.W1 = b->W1; a.W2 = b->W2;
+  } else {
+    a.g = b->g;
+    if (gru(d)) {       // [W_z; W_r]^T [H,2H], then W_n^T [H,H]
+      a.Wt1 = at(b->workspace, w.off_wt);
+      a.Wt2 = at(b->workspace, w.off_wt + (size_t)2 * d->d * d->d * es);
+    } else {            // W2^T [d_ff,d], then W1^T [H,d_ff]
+      a.Wt2 = at(b->workspace, w.off_wt);
+      a.Wt1 = at(b->workspace, w.off_wt + (size_t)d->d * d->d_ff * es);
+    }
+    a.e = d->loss_every_state ? b->e : nullptr;
+    a.dphi = d->act == HBP_ACT_GELU_ERF ? b->dphi : nullptr;
+  }
+  if (!recurrent_ok(a)) return false;
+  *out = a;
+  return true;
+}
+}  // namespace
+
 hbp_status hbp_forward(const hbp_desc* d, hbp_buffers* b, void* stream) {
   HBP_RUN(check_desc(d));
   HBP_RUN(check_bufs(d, b, NEED_FWD));
@@ -682,6 +721,14 @@ hbp_status hbp_forward(const hbp_desc* d, hbp_buffers* b, void* stream) {
     ga.ldc = d->d_ff; ga.batch = 1; ga.split_k = 1;
     ga.mode = EPI_STORE; ga.c_is_f32 = 1;
     HBP_RUN(run_gemm(d, ga, s, HBP_PROF_FORWARD));
+  }
+  {
+    RecArgs ra;
+    if (rec_args(d, b, w, true, &ra)) {
+      ProfScope ps(HBP_PROF_FORWARD, s);
+      HBP_TRY(launch_recurrent(ra, true, s));
+      return HBP_OK;
+    }
   }
   for (long l = 0; l < d->L; ++l) {
     const long wl = tfm(d) ? l / 2 : l;          // weight set and inner-state row of this block
@@ -1026,21 +1073,28 @@ hbp_status hbp_exact_backward(const hbp_desc* d, hbp_buffers* b, void* stream) {
     ProfScope ps(HBP_PROF_SCAN, s);
     HBP_TRY(launch_scan_post(d->dtype, pa, s));
   }
+  RecArgs ra;
+  const bool chain = rec_args(d, &bb, w, false, &ra);
   const bool skinny = step_skinny(d);
   // the step along the residual path in the same kernel (not for the LSTM, whose cell half is not a product)
   const bool fuse = skinny && d->norm == HBP_NORM_NONE && d->kind != HBP_LSTM;
-  if (skinny && gru(d)) {   // [W_z; W_r]^T [H,2H], then W_n^T [H,H]
+  if ((skinny || chain) && gru(d)) {   // [W_z; W_r]^T [H,2H], then W_n^T [H,H]
     ProfScope ps(HBP_PROF_OTHER, s);
     const long H = d->d;
     HBP_TRY(launch_transpose_bf16(bb.W1, at(bb.workspace, w.off_wt), (int)(2 * H), (int)H, s));
     HBP_TRY(launch_transpose_bf16(at(bb.W1, (size_t)2 * H * H * esize(d)),
                                   at(bb.workspace, w.off_wt + (size_t)2 * H * H * esize(d)), (int)H, (int)H, s));
-  } else if (skinny) {
+  } else if (skinny || chain) {
     ProfScope ps(HBP_PROF_OTHER, s);
     if (!cell(d))
       HBP_TRY(launch_transpose_bf16(bb.W2, at(bb.workspace, w.off_wt), (int)d->d, (int)d->d_ff, s));
     HBP_TRY(launch_transpose_bf16(bb.W1, at(bb.workspace, w.off_wt + (size_t)d->d * d->d_ff * esize(d)), (int)d->d_ff,
                                   (int)hidden_w(d), s));
+  }
+  if (chain) {
+    ProfScope ps(HBP_PROF_VJP1, s);
+    HBP_TRY(launch_recurrent(ra, false, s));
+    return HBP_OK;
   }
   for (long l = d->L - 1; l >= 0; --l) {
     HBP_RUN(vjp_stage1(d, &bb, w, l, l + 1, s, skinny));

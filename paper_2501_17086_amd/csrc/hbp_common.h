@@ -195,6 +195,30 @@ hipError_t launch_gemm_skinny(const SkinnyArgs& a, hipStream_t s);
 // dst[cols,rows] = src[rows,cols]^T, 2-byte elements
 hipError_t launch_transpose_bf16(const void* src, void* dst, int rows, int cols, hipStream_t s);
 
+// A chain along time in one launch (recurrent.hip): the forward pass, or exact backpropagation, of every step.  bf16.
+struct RecArgs {
+  int kind;             // 0 RNN, 1 gated cell, 2 LSTM, 3 standard GRU
+  long L, N, H, D, F;   // H: width of the hidden state that the products contract over; D, F: row widths of x / g and of z / da
+  void* x;              // [L+1,N,D]
+  void* z;              // [L,N,F]
+  const float* ux;      // forward: U xin, fp32 [L,N,F]
+  const void* W1;       // forward
+  const void* W2;       // forward (RNN)
+  const void* Wt1;      // backward: W1^T (GRU: [W_z; W_r]^T)
+  const void* Wt2;      // backward: W2^T (RNN), W_n^T (GRU)
+  const float* lambda;  // RNN: [L,D] or NULL
+  void* lambda_tok;     // [L,N,D] or NULL; written by the cells' forward
+  void* g;              // backward: [L+1,N,D], g[L] set
+  const void* e;        // backward: [L+1,N,D] added per state, or NULL
+  const void* dphi;     // backward (RNN): act' [L,N,F]; NULL: 1 - z^2 with tanh_act, else 1
+  int tanh_act;         // RNN: tanh, else the identity
+  int* counter;         // device scratch, one word
+  void* ring;           // device scratch, recurrent_ring_bytes()
+};
+size_t recurrent_ring_bytes();
+bool recurrent_ok(const RecArgs& a);
+hipError_t launch_recurrent(const RecArgs& a, bool forward, hipStream_t s);
+
 // out[i] = sum_s part[s][i], i < n
 hipError_t launch_splitk_reduce(const float* part, float* out, long n, int split, hipStream_t s);
 

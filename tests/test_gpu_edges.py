@@ -42,3 +42,53 @@ def test_attention_head_widths(B, dh, T, causal):
     inp, st, sv, p = _forward_matches(B, w)
     H.assert_close(H.to_np(p.attn_o), sv["o"][0::2], H.TOL["bf16"], f"{w.name} attention output")
     _check_backward(B, w, p, st, sv, inp, w.name, exact=False)
+
+
+_KINDS = {"rnn": ("gated_rnn_contractive", 1, 1), "token": ("gated_rnn_token_gates", 1, 1), "gated": ("gru_cell", 1, 2),
+          "lstm": ("lstm_cell", 2, 4), "gru": ("gru_std_cell", 1, 3)}
+
+
+def _chain(kind, L, N, H, inner=None, **kw):
+    base, dm, fm = _KINDS[kind]
+    return synth.scaled(W[base], name=f"{kind}_{L}_{N}_{H}", L=L, N=N, d=dm * H, d_ff=fm * (inner or H), d_in=16, ks=(1,), **kw)
+
+
+# chains along time in one launch: widths around a workgroup's 32 channels, the quarters of a contraction and the register
+# sizes (256 / 512 / 1024), batches around 16-row groups, chains of one step and of more than the four slots; 64 rows at
+# width 1024 take two row tiles per workgroup; 65 rows at that width and widths past 1024 go step by step
+@pytest.mark.parametrize("kind,L,N,H", [("rnn", 1, 1, 8), ("rnn", 9, 17, 264), ("rnn", 6, 64, 1024), ("token", 7, 15, 72),
+                                        ("gated", 2, 16, 32), ("gated", 9, 33, 136), ("gated", 5, 65, 1024), ("lstm", 1, 5, 24),
+                                        ("lstm", 9, 16, 520), ("lstm", 6, 64, 1024), ("gru", 3, 1, 40), ("gru", 9, 31, 256),
+                                        ("gru", 6, 48, 1000), ("gru", 4, 8, 1032)])
+def test_chains_along_time(B, kind, L, N, H):
+    w = _chain(kind, L, N, H)
+    inp, st, sv, p = _forward_matches(B, w)
+    _check_backward(B, w, p, st, sv, inp, w.name)
+
+
+@pytest.mark.parametrize("d,d_ff,act", [(40, 296, "tanh"), (296, 40, "tanh"), (64, 64, "identity")])
+def test_chains_along_time_of_two_widths(B, d, d_ff, act):
+    w = synth.scaled(W["gated_rnn_contractive"], name=f"rnn_{d}_{d_ff}_{act}", L=7, N=20, d=d, d_ff=d_ff, d_in=16, act=act,
+                     loss_every_state=act == "tanh", ks=(1,))
+    inp, st, sv, p = _forward_matches(B, w)
+    _check_backward(B, w, p, st, sv, inp, w.name)
+
+
+@pytest.mark.parametrize("kind", ["rnn", "gated", "lstm", "gru"])
+def test_chains_along_time_with_nan_rows_and_on_two_streams(B, kind):
+    """A row of NaNs of the pattern that marks an empty exchange slot runs through the chain as NaN and leaves the other
+    rows what they are without it; two chains at once on streams of their own do not disturb each other."""
+    import torch
+    w = _chain(kind, 12, 20, 64)
+    inp, st, sv, p = _setup(B, w)
+    q = B.allocate(w, inp)
+    q.x[0].view(torch.int16)[3] = -1
+    torch.cuda.synchronize()
+    s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
+    for b, s in ((p, s1), (q, s2)):
+        B.hbp_forward(b, stream=s.cuda_stream)
+        B.hbp_exact_backward(b, stream=s.cuda_stream)
+    torch.cuda.synchronize()
+    keep = [n for n in range(w.N) if n != 3]
+    assert torch.equal(p.x[:, keep], q.x[:, keep]) and torch.equal(p.g[:, keep], q.g[:, keep])
+    assert bool(q.x[1:, 3].isnan().all()) and not bool(p.x.isnan().any())
