@@ -338,6 +338,36 @@ __device__ __forceinline__ bf16x8 pack8(const float* v) {
                              pack_bf16x2(v[6], v[7]));
   return __builtin_bit_cast(bf16x8, w);
 }
+// what that rounding left over, rounded to bf16 itself: the two together hold 16 bits of the value
+__device__ __forceinline__ bf16x8 pack8_rest(const float* v, bf16x8 hi) {
+  const uint4 h = __builtin_bit_cast(uint4, hi);
+  const unsigned w[4] = {h.x, h.y, h.z, h.w};
+  float d[8];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    d[2 * i] = v[2 * i] - __uint_as_float(w[i] << 16);
+    d[2 * i + 1] = v[2 * i + 1] - __uint_as_float(w[i] & 0xFFFF0000u);
+  }
+  return pack8(d);
+}
+// The second products' operand, 16 probabilities (or dS) of a lane: in one bf16 part or (HILO) in two.
+template <bool HILO>
+struct Scores {
+  bf16x8 hi[2], lo[2];
+  __device__ __forceinline__ explicit Scores(const float (&v)[16]) {
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      hi[t] = pack8(v + 8 * t);
+      if (HILO) lo[t] = pack8_rest(v + 8 * t, hi[t]);
+    }
+  }
+  // acc += tile rows 16 t .. of `x` times part t
+  __device__ __forceinline__ float16v times(bf16x8 x, int t, float16v acc) const {
+    acc = mfma(x, hi[t], acc);
+    if (HILO) acc = mfma(x, lo[t], acc);
+    return acc;
+  }
+};
 __device__ __forceinline__ void store4b(bf16_t* p, float a, float b, float c, float d) {
   *reinterpret_cast<uint2*>(p) = make_uint2(pack_bf16x2(a, b), pack_bf16x2(c, d));
 }
@@ -427,6 +457,11 @@ __device__ __forceinline__ Head head_of(const AttnArgs& a, unsigned p) {
   return hd;
 }
 
+// 64-wide heads (PAD = false) round P and dS to bf16 once for the second products; every other width had plain kernels
+// that keep them in fp32, so there they enter as two bf16 parts: the error against 64 bits is that of the
+// plain kernels (it is the results' own rounding), at twice the second products.
+template <int DHP, bool PAD> constexpr bool two_parts() { return !(DHP == 64 && !PAD); }
+
 // The three kernels share one shape.  A workgroup of four wavefronts owns four consecutive tiles of 32 queries
 // (dk/dv kernel: keys), one per wavefront, and streams the tiles of the other side through a ring of AT_NST buffer
 // pairs that all four read: at step t each wavefront waits for its own share of pair t, the workgroup meets at a
@@ -437,6 +472,7 @@ __device__ __forceinline__ Head head_of(const AttnArgs& a, unsigned p) {
 template <int DHP, bool PAD, bool CAUSAL>
 __global__ __launch_bounds__(64 * AT_WAVES, 2) void attn_fwd_mfma_kernel(AttnArgs a) {
   typedef Geo<DHP> G;
+  constexpr bool HILO = two_parts<DHP, PAD>();
   __shared__ __attribute__((aligned(1024))) unsigned char smem[AT_NST][2][G::TB];   // [stage][k | v]
   const int lane = threadIdx.x & 63, hh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -517,11 +553,11 @@ __global__ __launch_bounds__(64 * AT_WAVES, 2) void attn_fwd_mfma_kernel(AttnArg
     for (int mb = 0; mb < G::MB; ++mb)
 #pragma unroll
       for (int r = 0; r < 16; ++r) o[mb][r] *= alpha;
-    const bf16x8 p0 = pack8(sv), p1 = pack8(sv + 8);
+    const Scores<HILO> pq(sv);
 #pragma unroll
-    for (int mb = 0; mb < G::MB; ++mb) o[mb] = mfma(fv[mb][0], p0, o[mb]);
+    for (int t = 0; t < 2; ++t)
 #pragma unroll
-    for (int mb = 0; mb < G::MB; ++mb) o[mb] = mfma(fv[mb][1], p1, o[mb]);
+      for (int mb = 0; mb < G::MB; ++mb) o[mb] = pq.times(fv[mb][t], t, o[mb]);
   };
   // tile kt complete and visible to the workgroup, the buffer of tile kt - 1 free and refilled
   auto advance = [&](int kt) __attribute__((always_inline)) {
@@ -548,6 +584,7 @@ __global__ __launch_bounds__(64 * AT_WAVES, 2) void attn_fwd_mfma_kernel(AttnArg
 template <int DHP, bool PAD, bool CAUSAL>
 __global__ __launch_bounds__(64 * AT_WAVES, 2) void attn_bwd_q_mfma_kernel(AttnArgs a) {
   typedef Geo<DHP> G;
+  constexpr bool HILO = two_parts<DHP, PAD>();
   __shared__ __attribute__((aligned(1024))) unsigned char smem[AT_NST][2][G::TB];   // [stage][k | v]
   const int lane = threadIdx.x & 63, hh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -627,7 +664,8 @@ __global__ __launch_bounds__(64 * AT_WAVES, 2) void attn_bwd_q_mfma_kernel(AttnA
 #pragma unroll
     for (int mb = 0; mb < G::MB; ++mb)
 #pragma unroll
-      for (int t = 0; t < 2; ++t) kr[mb][t] = frag_rows_lds<DHP>(tk, mb, t, lane);
+      for (int t = 0; t < 2; ++t)
+        if (G::MB < 4) kr[mb][t] = frag_rows_lds<DHP>(tk, mb, t, lane);
     __builtin_amdgcn_sched_barrier(0);
     float ds[16];
 #pragma unroll
@@ -639,12 +677,13 @@ __global__ __launch_bounds__(64 * AT_WAVES, 2) void attn_bwd_q_mfma_kernel(AttnA
       }
       ds[r] = pr * dp[r];
     }
-    const bf16x8 d0 = pack8(ds), d1 = pack8(ds + 8);
+    const Scores<HILO> dq_s(ds);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int mb = 0; mb < G::MB; ++mb) dq[mb] = mfma(kr[mb][0], d0, dq[mb]);
+    for (int t = 0; t < 2; ++t)
 #pragma unroll
-    for (int mb = 0; mb < G::MB; ++mb) dq[mb] = mfma(kr[mb][1], d1, dq[mb]);
+      for (int mb = 0; mb < G::MB; ++mb)
+        dq[mb] = dq_s.times(G::MB < 4 ? kr[mb][t] : frag_rows_lds<DHP>(tk, mb, t, lane), t, dq[mb]);
   };
   // tile kt complete and visible to the workgroup, the buffer of tile kt - 1 free and refilled
   auto advance = [&](int kt) __attribute__((always_inline)) {
@@ -670,6 +709,7 @@ __global__ __launch_bounds__(64 * AT_WAVES, 2) void attn_bwd_q_mfma_kernel(AttnA
 template <int DHP, bool PAD, bool CAUSAL>
 __global__ __launch_bounds__(64 * AT_WAVES, DHP == 128 ? 1 : 3) void attn_bwd_kv_mfma_kernel(AttnArgs a) {
   typedef Geo<DHP> G;
+  constexpr bool HILO = two_parts<DHP, PAD>();
   __shared__ __attribute__((aligned(1024))) unsigned char smem[AT_NST][2][G::TB];   // [stage][q | do]
   __shared__ __attribute__((aligned(1024))) unsigned char own[AT_WAVES][G::TB];     // [wave]: the v rows of the wavefront's own keys
   __shared__ __attribute__((aligned(256))) float stats[AT_WAVES][AT_NST][64];       // [wave][stage][L2 | D] (a copy per wavefront)
@@ -758,18 +798,16 @@ __global__ __launch_bounds__(64 * AT_WAVES, DHP == 128 ? 1 : 3) void attn_bwd_kv
       }
       ds[r] = pr[r] * dp[r];
     }
-    const bf16x8 p0 = pack8(pr), p1 = pack8(pr + 8), d0 = pack8(ds), d1 = pack8(ds + 8);
+    const Scores<HILO> ps(pr), ss(ds);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int mb = 0; mb < G::MB; ++mb) {
-      dv[mb] = mfma(frag_rows_lds<DHP>(td, mb, 0, lane), p0, dv[mb]);
-      dv[mb] = mfma(frag_rows_lds<DHP>(td, mb, 1, lane), p1, dv[mb]);
-    }
+    for (int mb = 0; mb < G::MB; ++mb)
 #pragma unroll
-    for (int mb = 0; mb < G::MB; ++mb) {
-      dk[mb] = mfma(frag_rows_lds<DHP>(tq, mb, 0, lane), d0, dk[mb]);
-      dk[mb] = mfma(frag_rows_lds<DHP>(tq, mb, 1, lane), d1, dk[mb]);
-    }
+      for (int t = 0; t < 2; ++t) dv[mb] = ps.times(frag_rows_lds<DHP>(td, mb, t, lane), t, dv[mb]);
+#pragma unroll
+    for (int mb = 0; mb < G::MB; ++mb)
+#pragma unroll
+      for (int t = 0; t < 2; ++t) dk[mb] = ss.times(frag_rows_lds<DHP>(tq, mb, t, lane), t, dk[mb]);
   };
   auto advance = [&](int qt) __attribute__((always_inline)) {
     if (qt + AT_NST - 2 < nt) copies_in_flight<(G::PW + 1) * (AT_NST - 2)>();
@@ -803,6 +841,7 @@ __global__ __launch_bounds__(64 * AT_WAVES, DHP == 128 ? 1 : 3) void attn_bwd_kv
 template <int DHP, bool PAD, bool CAUSAL, int NT>
 __global__ __launch_bounds__(64 * NT, 1) void attn_bwd_short_mfma_kernel(AttnArgs a) {
   typedef Geo<DHP> G;
+  constexpr bool HILO = two_parts<DHP, PAD>();
   __shared__ __attribute__((aligned(1024))) unsigned char tiles[4][NT][G::TB];  // [q | k | v | do][tile of 32 positions]
   __shared__ __attribute__((aligned(256))) float stats[NT][64];                 // per tile: L2 of its 32 queries, then D
   const int lane = threadIdx.x & 63, hh = lane >> 5;
@@ -880,12 +919,12 @@ __global__ __launch_bounds__(64 * NT, 1) void attn_bwd_short_mfma_kernel(AttnArg
         }
         ds[r] = pr * dp[r];
       }
-      const bf16x8 d0 = pack8(ds), d1 = pack8(ds + 8);
+      const Scores<HILO> dq_s(ds);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int mb = 0; mb < G::MB; ++mb) dq[mb] = mfma(kr[mb][0], d0, dq[mb]);
+      for (int t = 0; t < 2; ++t)
 #pragma unroll
-      for (int mb = 0; mb < G::MB; ++mb) dq[mb] = mfma(kr[mb][1], d1, dq[mb]);
+        for (int mb = 0; mb < G::MB; ++mb) dq[mb] = dq_s.times(kr[mb][t], t, dq[mb]);
     };
     const int n_own = CAUSAL ? wave + 1 : nt;
     const int n_plain = CAUSAL ? n_own - 1 : (ragged ? n_own - 1 : n_own);
@@ -947,12 +986,12 @@ __global__ __launch_bounds__(64 * NT, 1) void attn_bwd_short_mfma_kernel(AttnArg
         }
         ds[r] = pr[r] * dp[r];
       }
-      const bf16x8 p0 = pack8(pr), p1 = pack8(pr + 8), d0 = pack8(ds), d1 = pack8(ds + 8);
+      const Scores<HILO> ps(pr), ss(ds);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int mb = 0; mb < G::MB; ++mb) { dv[mb] = mfma(tr[mb][0], p0, dv[mb]); dk[mb] = mfma(ur[mb][0], d0, dk[mb]); }
+      for (int t = 0; t < 2; ++t)
 #pragma unroll
-      for (int mb = 0; mb < G::MB; ++mb) { dv[mb] = mfma(tr[mb][1], p1, dv[mb]); dk[mb] = mfma(ur[mb][1], d1, dk[mb]); }
+        for (int mb = 0; mb < G::MB; ++mb) { dv[mb] = ps.times(tr[mb][t], t, dv[mb]); dk[mb] = ss.times(ur[mb][t], t, dk[mb]); }
     };
     int qt = CAUSAL ? wave : 0;
     if (CAUSAL) { step(qt, std::true_type()); ++qt; }
@@ -969,7 +1008,7 @@ __global__ __launch_bounds__(64 * NT, 1) void attn_bwd_short_mfma_kernel(AttnArg
 }
 
 // Every head the padded tiles hold goes to the matrix cores: even at 8 of 32 columns the plain kernels' serial dot products
-// lose (32-wide heads, 12 sequences of 100, 8 heads, 4 layers: backward 1733 us a sweep plain, 15 us here).  A head
+// lose (32-wide heads, 12 sequences of 100, 8 heads, 4 layers: backward 1733 us a sweep plain, 16 us here).  A head
 // of its tile's full width has the kernels without the guards (PAD = false): those cost 64-wide heads 2 % and a
 // wavefront of occupancy.
 inline bool use_mfma(int dtype, const AttnArgs& a) { return dtype == 1 && a.dh <= 128; }
