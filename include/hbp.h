@@ -24,8 +24,7 @@
  *    parameter gradients and a per-channel lambda (HBP_LAMBDA_CHANNEL) are
  *    always fp32, a per-token lambda (HBP_LAMBDA_TOKEN) is in S.  bf16 storage
  *    runs the contractions on the matrix cores (bf16 x bf16 -> fp32 MFMA); fp32
- *    storage runs them on the vector ALUs (an LDS-tiled FMA kernel, no fp32
- *    MFMA): that path is for small reference problems.
+ *    storage runs them with fp32 products and sums (fp32 MFMA).
  *  - The library never allocates or frees device memory and never
  *    synchronises: kernels are enqueued on `stream` (a hipStream_t passed as
  *    void*; NULL = the default stream) and the call returns at once.  The

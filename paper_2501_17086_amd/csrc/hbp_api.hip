@@ -238,13 +238,15 @@ struct ProfScope {
   }
 };
 
+hipError_t launch_gemm(const hbp_desc* d, const GemmArgs& ga, hipStream_t s) {
+  hipError_t err = hipSuccess;
+  if (d->dtype == HBP_BF16 && launch_gemm_mfma(ga, s, &err)) return err;
+  return d->dtype == HBP_F32 && gemm_f32_ok(ga) ? launch_gemm_f32(ga, s) : launch_gemm_generic(d->dtype, ga, s);
+}
+
 hbp_status run_gemm(const hbp_desc* d, const GemmArgs& ga, hipStream_t s, int cls) {
   ProfScope ps(cls, s);
-  hipError_t err = hipSuccess;
-  if (d->dtype == HBP_BF16 && launch_gemm_mfma(ga, s, &err)) {
-    return err == hipSuccess ? HBP_OK : HBP_E_DEVICE;
-  }
-  HBP_TRY(launch_gemm_generic(d->dtype, ga, s));
+  HBP_TRY(launch_gemm(d, ga, s));
   return HBP_OK;
 }
 
@@ -395,9 +397,7 @@ hbp_status vjp_stage1(const hbp_desc* d, const hbp_buffers* b, const Workspace& 
       ga.b_sk = H; ga.b_sn = 1;
       ga.ldc = H; ga.batch = 1; ga.split_k = 1;
       ga.mode = EPI_STORE;
-      hipError_t err = hipSuccess;
-      if (!(d->dtype == HBP_BF16 && launch_gemm_mfma(ga, s, &err))) err = launch_gemm_generic(d->dtype, ga, s);
-      if (err != hipSuccess) return HBP_E_DEVICE;
+      HBP_TRY(launch_gemm(d, ga, s));
     }
     HBP_TRY(launch_gru_vjp2(d->dtype, tmp, at((const void*)b->x, so), at((const void*)b->z, fo),
                             e_in_vjp(d) ? at(b->e, so) : nullptr, da, rx_out, rows, H, s));

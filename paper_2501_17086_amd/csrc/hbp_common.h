@@ -150,6 +150,9 @@ struct GemmArgs {
 
 // storage type: 0 = fp32, 1 = bf16
 hipError_t launch_gemm_generic(int dtype, const GemmArgs& g, hipStream_t s);
+// the same for fp32 storage on the matrix cores, where the layout allows it
+bool gemm_f32_ok(const GemmArgs& g);
+hipError_t launch_gemm_f32(const GemmArgs& g, hipStream_t s);
 // fast bf16 MFMA path; returns false when the shape/layout is not covered
 bool launch_gemm_mfma(const GemmArgs& g, hipStream_t s, hipError_t* err);
 // the same contractions on tiles of 128 x 128 or 64 x 64, any size (called through launch_gemm_mfma, which checks the layout)

@@ -92,3 +92,14 @@ def test_chains_along_time_with_nan_rows_and_on_two_streams(B, kind):
     keep = [n for n in range(w.N) if n != 3]
     assert torch.equal(p.x[:, keep], q.x[:, keep]) and torch.equal(p.g[:, keep], q.g[:, keep])
     assert bool(q.x[1:, 3].isnan().all()) and not bool(p.x.isnan().any())
+
+
+# fp32 products: around the 32- and 64-wide tiles, contractions that end inside a chunk of 32 or leave a wavefront's
+# quarter empty, and enough blocks (40 x 4 x 4 tiles of 64) for the wide tiles
+@pytest.mark.parametrize("L,N,d,d_ff", [(2, 1, 8, 8), (2, 31, 40, 24), (3, 65, 32, 72), (2, 130, 264, 136), (40, 250, 72, 232)])
+def test_fp32_products_around_the_tile_edges(B, L, N, d, d_ff):
+    w = synth.scaled(W["mlp_small_f32"], name=f"f32_{N}_{d}_{d_ff}", L=L, N=N, d=d, d_ff=d_ff, norm="rms", lam="uniform",
+                     lam_lo=0.9, lam_hi=1.0, w2_scale=1 / np.sqrt(L), ks=(1, 2))
+    inp, st, sv, p = _forward_matches(B, w)
+    H.assert_close(H.to_np(p.dphi), sv["dphi"], H.TOL["f32"], f"{w.name} act'")
+    _check_backward(B, w, p, st, sv, inp, w.name)
