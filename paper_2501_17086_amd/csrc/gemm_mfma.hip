@@ -237,17 +237,31 @@ __device__ __forceinline__ void dma16_c(unsigned off, const void* sbase, unsigne
 // shape above the writes of the other (it emits no instruction).
 typedef unsigned uint4v __attribute__((ext_vector_type(4)));   // (a first-class vector: stays in registers)
 struct Quad16 { uint4v x0, x1, x2, x3; };   // 4 x 16 bytes per lane: 32 rows of the row layout
+template <int FAST> constexpr bool has_aux() {
+  return FAST == FAST_MUL_AUX || FAST == FAST_MUL_1MZ2 || FAST == FAST_ADD_AUX || FAST == FAST_RESID;
+}
+// the fused operand's 32 rows of a round (of 4) in the row layout
+__device__ __forceinline__ void fetch_aux(Quad16& q, const GemmArgs& g, const TileCoord& tc, int wm0, int wn0, int lane, int round) {
+  const bf16_t* a = reinterpret_cast<const bf16_t*>(g.aux) + tc.batch * g.aux_sb +
+                    (tc.m0 + wm0 + (lane >> 3) + 32 * round) * g.ldc + tc.n0 + wn0 + 8 * (lane & 7);
+  const long ld8 = 8 * g.ldc;
+  // (streamed once: non-temporal, so that it does not push the operand panels out of L2)
+  q.x0 = __builtin_nontemporal_load(reinterpret_cast<const uint4v*>(a));
+  q.x1 = __builtin_nontemporal_load(reinterpret_cast<const uint4v*>(a + ld8));
+  q.x2 = __builtin_nontemporal_load(reinterpret_cast<const uint4v*>(a + 2 * ld8));
+  q.x3 = __builtin_nontemporal_load(reinterpret_cast<const uint4v*>(a + 3 * ld8));
+}
+// qa, qb: the first two rounds' fused operand, fetched during the tile's last slices
 template <int FAST>
 __device__ __forceinline__ void epilogue_staged_fn(const GemmArgs& g, const TileCoord& tc, const float16v (&acc)[4][2],
-                                                   int wm0, int wn0, int lane, unsigned char* stg) {
-  constexpr bool HAS_AUX = FAST == FAST_MUL_AUX || FAST == FAST_MUL_1MZ2 || FAST == FAST_ADD_AUX || FAST == FAST_RESID;
+                                                   int wm0, int wn0, int lane, unsigned char* stg, const Quad16& qa, const Quad16& qb) {
+  constexpr bool HAS_AUX = has_aux<FAST>();
   constexpr bool TWO_OUT = FAST == FAST_ACT_GELU;
   // row layout: this lane's row within a group of 8 rows, and its chunk of the row
   const int rr = lane >> 3, rk = lane & 7;
   // MFMA layout: this lane's row within the 32, half-chunk (4 columns) within a chunk
   const int mr = lane & 31, mh = lane >> 5;
   const long off_row = (tc.m0 + wm0 + rr) * g.ldc + tc.n0 + wn0 + 8 * rk;     // row layout, first row group
-  const bf16_t* aux = reinterpret_cast<const bf16_t*>(g.aux) + tc.batch * g.aux_sb + off_row;
   bf16_t* cp = reinterpret_cast<bf16_t*>(g.C) + tc.batch * g.c_sb + off_row;
   bf16_t* cp2 = TWO_OUT ? reinterpret_cast<bf16_t*>(g.out2) + tc.batch * g.out2_sb + off_row : nullptr;
   const long ld8 = 8 * g.ldc;
@@ -273,14 +287,6 @@ __device__ __forceinline__ void epilogue_staged_fn(const GemmArgs& g, const Tile
   unsigned char* const p3 = row_at(rr + 24);
   unsigned char* const m_base = stg + mr * 128 + 8 * mh;
   const int m_sw = (mr >> 1) & 7;
-  auto fetch = [&](Quad16& q, int round) {
-    const bf16_t* a = aux + (long)(32 * round) * g.ldc;
-    // (streamed once: non-temporal, so that it does not push the operand panels out of L2)
-    q.x0 = __builtin_nontemporal_load(reinterpret_cast<const uint4v*>(a));
-    q.x1 = __builtin_nontemporal_load(reinterpret_cast<const uint4v*>(a + ld8));
-    q.x2 = __builtin_nontemporal_load(reinterpret_cast<const uint4v*>(a + 2 * ld8));
-    q.x3 = __builtin_nontemporal_load(reinterpret_cast<const uint4v*>(a + 3 * ld8));
-  };
   // 32 rows x 64 columns now in the staging tile (MFMA layout written): read as rows, store whole lines
   auto flush = [&](bf16_t* c) {
     __builtin_amdgcn_wave_barrier();
@@ -340,14 +346,16 @@ __device__ __forceinline__ void epilogue_staged_fn(const GemmArgs& g, const Tile
       flush(cp2 + (long)(32 * i) * g.ldc);
     }
   };
-  Quad16 qa = {}, qb = {};
-  if (HAS_AUX) { fetch(qa, 0); fetch(qb, 1); }
+  // (the residual sum's 32 coefficients per lane leave registers for one more round at a time only)
+  constexpr bool TIGHT = FAST == FAST_RESID;
+  Quad16 qc = {}, qd = {};
+  if (HAS_AUX) fetch_aux(qc, g, tc, wm0, wn0, lane, 2);
+  if (HAS_AUX && !TIGHT) fetch_aux(qd, g, tc, wm0, wn0, lane, 3);
   round(std::integral_constant<int, 0>(), qa);
-  if (HAS_AUX) fetch(qa, 2);
+  if (TIGHT) fetch_aux(qd, g, tc, wm0, wn0, lane, 3);
   round(std::integral_constant<int, 1>(), qb);
-  if (HAS_AUX) fetch(qb, 3);
-  round(std::integral_constant<int, 2>(), qa);
-  round(std::integral_constant<int, 3>(), qb);
+  round(std::integral_constant<int, 2>(), qc);
+  round(std::integral_constant<int, 3>(), qd);
 }
 template <int FAST> struct StagedOps {   // vector-memory operations per wave of one epilogue (a lower bound: the
   static constexpr int value = FAST == FAST_STORE_F32 ? 32 : FAST == FAST_STORE ? 16 : 32;   // waits stay safe with more)
@@ -464,12 +472,16 @@ __global__ __launch_bounds__(NTHR, 1) void gemm_mfma_lean_kernel(GemmArgs g, int
 
   float16v acc[4][2];
   bf16x8 fa[4][2], fb[2][2];
+  Quad16 aux0 = {}, aux1 = {};   // the first half of a tile's fused operand
+  TileCoord cc = decode_tile(g, t, tiles_m, tiles_n);   // the consumer's tile
   unsigned c_off = 0;      // byte offset of the consumer's stage
   int epi_recent = 0;      // waits that still see the last epilogue's operations
   constexpr int E = StagedOps<FAST>::value;
   constexpr int AHEAD = LEAN_NST - 1;                      // slices copied ahead of the one being multiplied
   constexpr int W_PLAIN = (AHEAD - 1) * PER_SLICE;
   constexpr int W_EPI = W_PLAIN + E > 63 ? 63 : W_PLAIN + E;
+  // the slice that the second step of a tile waits for was copied after the 8 early loads of the epilogue before
+  constexpr int E2 = has_aux<FAST>() ? E - 8 : E, W_EPI2 = W_PLAIN + E2 > 63 ? 63 : W_PLAIN + E2;
   // PAIR: a wave issues 4 copies of A and 2 of B in an even step, 2 of B in an odd one.  At the end of an even
   // step c the B of slice c + 1 (issued two steps before) must have landed: what may be outstanding is what was
   // issued after it, 2 + 4 + 2 copies (and a recent epilogue's operations); at the end of an odd step the pair
@@ -483,11 +495,20 @@ __global__ __launch_bounds__(NTHR, 1) void gemm_mfma_lean_kernel(GemmArgs g, int
   // the stage of slice c-1, which its last reader (group 1, tick 2c-1) has left.  Every wave waits
   // for its own share of slice c+1 at the end of its load phase of slice c, a barrier or more
   // before the first reader of slice c+1 starts.
-  auto step = [&](auto first_c, auto odd_c) {
+  // AUX 1: the tile's last slice but one, where the first half of the epilogue's fused operand is asked for (8 loads after
+  // the step's copies); AUX 2: the last slice: both steps' waits may leave those loads outstanding.
+  // last: a tile's last slice.  With a long epilogue (a fused operand, GELU) group 1 leaves out the barrier after it and
+  // meets it after its epilogue instead: the two groups' epilogues, chains of LDS and memory latencies, then run in
+  // the same tick, not one after the other.  Measured: 16384 x 4096 x 1024 with GELU 183 -> 174 us, 32768 x 1024 x 256 47 -> 41,
+  // 12 x 32768 x 1024 x 256 with act' 329 -> 325; plain stores 1 % slower, so not there.
+  constexpr bool TOGETHER = has_aux<FAST>() || FAST == FAST_ACT_GELU;
+  auto step = [&](auto first_c, auto odd_c, auto aux_c, bool last) {
     constexpr bool FIRST = decltype(first_c)::value;
+    constexpr int AUX = decltype(aux_c)::value, X = AUX ? 8 : 0;
     constexpr bool ODD = decltype(odd_c)::value;         // (PAIR only: the slice's place in its pair)
     const bool copying = p_more;
     if (copying) copy_slice();
+    if (AUX == 1) { fetch_aux(aux0, g, cc, wm0, wn0, lane, 0); fetch_aux(aux1, g, cc, wm0, wn0, lane, 1); }
     if (PAIR) {
       const unsigned char* stb = smem + 2 * PAIR_AREA + c_off;
       const unsigned char* sta = smem + c_aoff;
@@ -501,10 +522,10 @@ __global__ __launch_bounds__(NTHR, 1) void gemm_mfma_lean_kernel(GemmArgs g, int
         for (int i = 0; i < 4; ++i) fa[i][h] = frag_pair(sta, wm0 + 32 * i, (ODD ? 4 : 0) + 2 * h, lane);
       c_off = c_off == (LEAN_NST - 1) * B_BYTES ? 0u : c_off + B_BYTES;
       if (ODD) c_aoff ^= (unsigned)PAIR_AREA;
-      if (!copying) wait_vm_lds<0>();
-      else if (ODD) wait_vm_lds<W_ODD>();
+      if (!copying) wait_vm_lds<X>();
+      else if (ODD) wait_vm_lds<W_ODD + X>();
       else if (epi_recent > 0) { wait_vm_lds<W_EVEN_EPI>(); epi_recent = 0; }
-      else wait_vm_lds<W_EVEN>();
+      else wait_vm_lds<W_EVEN + X>();
     } else {
       const unsigned char* st = smem + c_off;
 #pragma unroll
@@ -518,9 +539,10 @@ __global__ __launch_bounds__(NTHR, 1) void gemm_mfma_lean_kernel(GemmArgs g, int
       c_off = c_off == (LEAN_NST - 1) * STAGE_BYTES ? 0u : c_off + STAGE_BYTES;
       // this wave's share of the next slice has landed once only what it issued for the slices after
       // that one (and a recent epilogue's operations, which lie among them) is outstanding
-      if (!copying) wait_vm_lds<0>();
-      else if (epi_recent > 0) { wait_vm_lds<W_EPI>(); --epi_recent; }
-      else wait_vm_lds<W_PLAIN>();
+      if (!copying) wait_vm_lds<X>();
+      else if (epi_recent > 1) { wait_vm_lds<W_EPI>(); --epi_recent; }
+      else if (epi_recent > 0) { wait_vm_lds<W_EPI2>(); --epi_recent; }
+      else wait_vm_lds<W_PLAIN + X>();
     }
     __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_barrier();
@@ -539,11 +561,10 @@ __global__ __launch_bounds__(NTHR, 1) void gemm_mfma_lean_kernel(GemmArgs g, int
         acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[j][1], fa[i][1], acc[i][j], 0, 0, 0);
     __builtin_amdgcn_s_setprio(0);
     __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_barrier();
+    if (!TOGETHER || !last || grp == 0) __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
   };
 
-  TileCoord cc = decode_tile(g, t, tiles_m, tiles_n);
   aim(cc);
   int pro = 0;             // slices copied before the first step
 #pragma unroll 1
@@ -556,22 +577,38 @@ __global__ __launch_bounds__(NTHR, 1) void gemm_mfma_lean_kernel(GemmArgs g, int
   __builtin_amdgcn_s_barrier();                 // slice 0 is in LDS
   if (grp == 1) __builtin_amdgcn_s_barrier();   // group 1 runs one tick behind
 
+  constexpr std::integral_constant<bool, false> no{};
+  constexpr std::integral_constant<bool, true> yes{};
+  constexpr std::integral_constant<int, 0> a0{};
+  constexpr std::integral_constant<int, has_aux<FAST>() ? 1 : 0> a1{};
+  constexpr std::integral_constant<int, has_aux<FAST>() ? 2 : 0> a2{};
   while (true) {
-    if (PAIR) {
-      step(std::true_type(), std::false_type());
-      step(std::false_type(), std::true_type());
+    if (!has_aux<FAST>()) {
+      step(yes, no, a0, !PAIR && cc.KT == 1);
+      if (PAIR) step(no, yes, a0, cc.KT == 2);
 #pragma unroll 1
-      for (int k = 2; k < cc.KT; k += 2) {
-        step(std::false_type(), std::false_type());
-        step(std::false_type(), std::true_type());
+      for (int k = PAIR ? 2 : 1; k < cc.KT; k += PAIR ? 2 : 1) {
+        step(no, no, a0, !PAIR && k + 1 == cc.KT);
+        if (PAIR) step(no, yes, a0, k + 2 == cc.KT);
       }
-    } else {
-      step(std::true_type(), std::false_type());
+    } else {                 // (at least four slices: the launcher sees to it)
+      step(yes, no, a0, false);
+      if (PAIR) step(no, yes, a0, false);
 #pragma unroll 1
-      for (int k = 1; k < cc.KT; ++k) step(std::false_type(), std::false_type());
+      for (int k = PAIR ? 4 : 3; k < cc.KT; k += PAIR ? 2 : 1) {
+        step(no, no, a0, false);
+        if (PAIR) step(no, yes, a0, false);
+      }
+      step(no, no, a1, false);
+      if (PAIR) step(no, yes, a2, true); else step(no, no, a2, true);
     }
     if (FAST == FAST_STORE_F32) epilogue_fast_fn<FAST>(g, cc, acc, wm0, wn0, lane);
-    else epilogue_staged_fn<FAST>(g, cc, acc, wm0, wn0, lane, smem + LEAN_NST * STAGE_BYTES + wave * 4096);
+    else epilogue_staged_fn<FAST>(g, cc, acc, wm0, wn0, lane, smem + LEAN_NST * STAGE_BYTES + wave * 4096, aux0, aux1);
+    if (TOGETHER && grp == 1) {
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_barrier();
+      __builtin_amdgcn_sched_barrier(0);
+    }
     epi_recent = AHEAD - 1;
     t += t_stride;
     if (t >= t_end) break;
@@ -717,7 +754,8 @@ bool launch_gemm_mfma(const GemmArgs& g, hipStream_t s, hipError_t* err) {
   if (g.M <= 0 || g.N <= 0 || g.K <= 0 || g.batch <= 0 || g.split_k <= 0) return false;
   const bool act = g.mode == EPI_ACT_GELU || g.mode == EPI_ACT_TANH;
   if (!(a_kc && (b_kc || (b_rc && !act))) && !(a_rc && b_rc && !act)) return false;
-  if (has_lean(g, a_kc, b_kc) && g.K % ((long)g.split_k * BK) == 0) {
+  // (a fused operand is asked for two slices before a tile's end, the first two being waited for otherwise: four at least)
+  if (has_lean(g, a_kc, b_kc) && g.K % ((long)g.split_k * BK) == 0 && (g.mode == EPI_STORE || g.K >= 4 * BK)) {
     const long hm = g.M / BM * BM, hn = g.N / BN * BN;
     const long tiles = (hm / BM) * (hn / BN) * g.batch * g.split_k;
     if (hm == g.M && hn == g.N) {

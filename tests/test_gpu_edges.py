@@ -103,3 +103,14 @@ def test_fp32_products_around_the_tile_edges(B, L, N, d, d_ff):
     inp, st, sv, p = _forward_matches(B, w)
     H.assert_close(H.to_np(p.dphi), sv["dphi"], H.TOL["f32"], f"{w.name} act'")
     _check_backward(B, w, p, st, sv, inp, w.name)
+
+
+# whole 256-wide tiles (144 of them), contractions of three (too few for the early loads of the fused operand), four and
+# five slices of 32, in pairs of slices (an even number) and singly
+@pytest.mark.parametrize("d", [96, 128, 160])
+def test_short_contractions_on_whole_tiles(B, d):
+    w = synth.scaled(W["resnet_like"], name=f"mlp_short_{d}", L=2, N=4608, d=d, d_ff=1024, w2_scale=0.7, ks=(1,))
+    inp, st, sv, p = _forward_matches(B, w)
+    H.assert_close(H.to_np(p.z), sv["z"], H.TOL["bf16"], f"{w.name} z")
+    H.assert_close(H.to_np(p.dphi), sv["dphi"], H.TOL["bf16"], f"{w.name} act'")
+    _check_backward(B, w, p, st, sv, inp, w.name)
