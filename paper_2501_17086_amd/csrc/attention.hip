@@ -308,6 +308,13 @@ __device__ __forceinline__ bf16x8 own_cols_lds(const unsigned char* tile, int kk
   const bool in = 2 * kk + (lane >> 5) < dh8;
   return __builtin_bit_cast(bf16x8, make_uint4(in ? v.x : 0u, in ? v.y : 0u, in ? v.z : 0u, in ? v.w : 0u));
 }
+// this lane's piece of a fragment into its place in the tile
+template <int DHP>
+__device__ __forceinline__ void put_cols_lds(unsigned char* tile, int kk, int lane, bf16x8 v) {
+  typedef Geo<DHP> G;
+  const int r = lane & 31, ch = 2 * kk + (lane >> 5);
+  *reinterpret_cast<uint4*>(tile + r * G::RB + ((ch ^ G::swz(r)) << 4)) = __builtin_bit_cast(uint4, v);
+}
 // the same straight from memory; rows from rows_left on repeat the last one
 __device__ __forceinline__ bf16x8 own_cols_mem(const unsigned char* base, unsigned ldb, int rows_left, int kk, int dh8, int lane) {
   const int r = lane & 31, ch = 2 * kk + (lane >> 5);
@@ -371,16 +378,31 @@ struct Scores {
 __device__ __forceinline__ void store4b(bf16_t* p, float a, float b, float c, float d) {
   *reinterpret_cast<uint2*>(p) = make_uint2(pack_bf16x2(a, b), pack_bf16x2(c, d));
 }
-// a lane's MB x 16 results (columns 32 m + tile_row_of(r, hh)) of its row, scaled; dh of them are there
+// A tile's results, scaled (a lane holds columns 32 m + tile_row_of(r, hh) of row l % 32), dh columns of them, to `base`, the
+// tile's first row (stride ld elements); rows from rows_left on are not there.  They pass through 2 KB of LDS of the
+// wavefront's own, 32 columns at a time, so that a store covers 64 bytes of a row and not 16: straight from the
+// accumulators a tile is 8 instructions of 32 pieces of lines each, and the L2 takes one piece a clock (dk, dv of 768 problems of
+// 1024: 323 -> 301 us).
 template <int MB>
-__device__ __forceinline__ void store_row(bf16_t* row, const float16v (&acc)[MB], float f, int dh, int hh) {
+__device__ __forceinline__ void store_tile(bf16_t* base, long ld, int rows_left, const float16v (&acc)[MB], float f, int dh,
+                                           unsigned char* stg, int lane) {
+  const int r = lane & 31, hh = lane >> 5, rr = lane >> 2, ch = lane & 3;
 #pragma unroll
-  for (int m = 0; m < MB; ++m)
+  for (int m = 0; m < MB; ++m) {
+    if (32 * m >= dh) break;
 #pragma unroll
     for (int g = 0; g < 4; ++g)
-      if (32 * m + 8 * g < dh)
-        store4b(row + 32 * m + 8 * g + 4 * hh, acc[m][4 * g] * f, acc[m][4 * g + 1] * f, acc[m][4 * g + 2] * f,
-                acc[m][4 * g + 3] * f);
+      store4b(reinterpret_cast<bf16_t*>(stg + r * 64 + ((g ^ ((r >> 2) & 3)) << 4) + 8 * hh), acc[m][4 * g] * f,
+              acc[m][4 * g + 1] * f, acc[m][4 * g + 2] * f, acc[m][4 * g + 3] * f);
+    __builtin_amdgcn_wave_barrier();                       // (a wavefront's LDS operations execute in order)
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int row = rr + 16 * u;
+      const uint4 v = *reinterpret_cast<const uint4*>(stg + row * 64 + ((ch ^ ((row >> 2) & 3)) << 4));
+      if (row < rows_left && 32 * m + 8 * ch < dh) *reinterpret_cast<uint4*>(base + row * ld + 32 * m + 8 * ch) = v;
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
 }
 template <int MB>
 __device__ __forceinline__ void zero_acc(float16v (&acc)[MB]) {
@@ -474,6 +496,7 @@ __global__ __launch_bounds__(64 * AT_WAVES, 2) void attn_fwd_mfma_kernel(AttnArg
   typedef Geo<DHP> G;
   constexpr bool HILO = two_parts<DHP, PAD>();
   __shared__ __attribute__((aligned(1024))) unsigned char smem[AT_NST][2][G::TB];   // [stage][k | v]
+  __shared__ __attribute__((aligned(256))) unsigned char staging[AT_WAVES][2048];   // [wave]: results on their way out
   const int lane = threadIdx.x & 63, hh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int T = (int)a.T, nt = (T + 31) >> 5;
@@ -573,10 +596,10 @@ __global__ __launch_bounds__(64 * AT_WAVES, 2) void attn_fwd_mfma_kernel(AttnArg
   for (; kt < n_plain; ++kt) { advance(kt); step(kt, std::false_type()); }
   if (kt < n_own) { advance(kt); step(kt, std::true_type()); ++kt; }
   for (; kt < nkt; ++kt) advance(kt);
-  if (live && qi < T) {
-    store_row(reinterpret_cast<bf16_t*>(reinterpret_cast<unsigned char*>(a.o) + hd.wide_off) + (long)qi * hd.d, o, 1.f / l,
-              dh, hh);
-    if (hh == 0) a.lse[(long)p * a.T + qi] = m + log2f(l);
+  if (live) {
+    store_tile(reinterpret_cast<bf16_t*>(reinterpret_cast<unsigned char*>(a.o) + hd.wide_off) + (long)q0 * hd.d, hd.d, T - q0, o,
+               1.f / l, dh, staging[wave], lane);
+    if (hh == 0 && qi < T) a.lse[(long)p * a.T + qi] = m + log2f(l);
   }
 }
 
@@ -586,6 +609,7 @@ __global__ __launch_bounds__(64 * AT_WAVES, 2) void attn_bwd_q_mfma_kernel(AttnA
   typedef Geo<DHP> G;
   constexpr bool HILO = two_parts<DHP, PAD>();
   __shared__ __attribute__((aligned(1024))) unsigned char smem[AT_NST][2][G::TB];   // [stage][k | v]
+  __shared__ __attribute__((aligned(256))) unsigned char staging[AT_WAVES][2048];   // [wave]: results on their way out
   const int lane = threadIdx.x & 63, hh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int T = (int)a.T, nt = (T + 31) >> 5;
@@ -699,9 +723,9 @@ __global__ __launch_bounds__(64 * AT_WAVES, 2) void attn_bwd_q_mfma_kernel(AttnA
   for (; kt < n_plain; ++kt) { advance(kt); step(kt, std::false_type()); }
   if (kt < n_own) { advance(kt); step(kt, std::true_type()); ++kt; }
   for (; kt < nkt; ++kt) advance(kt);
-  if (live && qi < T)
-    store_row(reinterpret_cast<bf16_t*>(reinterpret_cast<unsigned char*>(a.dqkv) + (hd.q - reinterpret_cast<const unsigned char*>(a.qkv))) +
-                  (long)qi * hd.ld, dq, a.scale, dh, hh);
+  if (live)
+    store_tile(reinterpret_cast<bf16_t*>(reinterpret_cast<unsigned char*>(a.dqkv) + (hd.q - reinterpret_cast<const unsigned char*>(a.qkv))) +
+                   (long)q0 * hd.ld, hd.ld, T - q0, dq, a.scale, dh, staging[wave], lane);
 }
 
 // dk, dv of four tiles of 32 keys (after the dq kernel: reads D).  128-wide heads hold 128 accumulators and 64 operand
@@ -823,31 +847,36 @@ __global__ __launch_bounds__(64 * AT_WAVES, DHP == 128 ? 1 : 3) void attn_bwd_kv
   const int plain_end = ragged ? nt - 1 : nt;
   for (; qt < plain_end; ++qt) { advance(qt); step(qt, std::false_type()); }
   if (qt < nt) { advance(qt); step(qt, std::true_type()); }
-  if (live && kj < T) {
-    bf16_t* row = reinterpret_cast<bf16_t*>(reinterpret_cast<unsigned char*>(a.dqkv) + (hd.k - reinterpret_cast<const unsigned char*>(a.qkv))) +
-                  (long)kj * hd.ld;
-    store_row(row, dk, a.scale, dh, hh);
-    store_row(row + hd.d, dv, 1.f, dh, hh);
+  if (live) {                  // (the wavefront's own v tile has served)
+    bf16_t* first = reinterpret_cast<bf16_t*>(reinterpret_cast<unsigned char*>(a.dqkv) + (hd.k - reinterpret_cast<const unsigned char*>(a.qkv))) +
+                    (long)k0 * hd.ld;
+    store_tile(first, hd.ld, T - k0, dk, a.scale, dh, own[wave], lane);
+    store_tile(first + hd.d, hd.ld, T - k0, dv, 1.f, dh, own[wave], lane);
   }
 }
 
-// Backward of a whole (sequence, head) problem of at most 32 NT positions in ONE workgroup of NT wavefronts: the q, k,
-// v and do tiles of the problem go to LDS once (each wavefront copies the four tiles of its own 32 positions), one
-// barrier, and then nothing is streamed and nothing waited for: wavefront w first takes its positions as queries
-// (dq: over the key tiles it sees) and then as keys (dk, dv: over the query tiles that see it).  Under a causal mask
-// that is w + 1 and NT - w steps: every wavefront has the same number of steps.  Each tensor is read from memory once
-// (the two-kernel form reads q, k, v and do twice and keeps D in memory between the kernels); the arithmetic is that
-// of the two kernels, in the same order per output element.
-template <int DHP, bool PAD, bool CAUSAL, int NT>
-__global__ __launch_bounds__(64 * NT, 1) void attn_bwd_short_mfma_kernel(AttnArgs a) {
+// Backward of a whole (sequence, head) problem of at most 128 TPW positions in ONE workgroup of four wavefronts, TPW tiles of
+// 32 positions each (wavefront w: tiles w and, with two, 7 - w).  First the k and v tiles of the problem are in LDS and
+// every wavefront takes its positions as queries (q, do and the row sums of do (.) o straight from memory): dq over the key
+// tiles they see.  Then the q and do fragments, still in registers, replace k and v in LDS, the wavefront's own k and v
+// rows having been read out, and the positions are taken as keys: dk, dv over the query tiles that see them.  Under a
+// causal mask that is w + 1 + 8 - w steps either way: every wavefront has the same number.  Nothing is streamed, each
+// tensor is read from memory once, and the arithmetic is that of the two-kernel form, in the same order per output
+// element.  What bounds it is memory (80 flop per byte at 256 positions): the problem's 66 KB of LDS let two workgroups
+// share a compute unit, so that one's loads run under the other's products.  All four tensors in LDS (130 KB, one
+// workgroup of eight wavefronts) took 531 us for 12 layers of 512 problems of 256, this form 472,
+// and 406 with the results leaving through LDS (store_tile).
+template <int DHP, bool PAD, bool CAUSAL, int TPW>
+__global__ __launch_bounds__(256, DHP == 128 ? 1 : 2) void attn_bwd_short_mfma_kernel(AttnArgs a) {
   typedef Geo<DHP> G;
   constexpr bool HILO = two_parts<DHP, PAD>();
-  __shared__ __attribute__((aligned(1024))) unsigned char tiles[4][NT][G::TB];  // [q | k | v | do][tile of 32 positions]
+  constexpr int NT = 4 * TPW;
+  __shared__ __attribute__((aligned(1024))) unsigned char tiles[2][NT][G::TB];  // [k | v], then [q | do]
   __shared__ __attribute__((aligned(256))) float stats[NT][64];                 // per tile: L2 of its 32 queries, then D
+  __shared__ __attribute__((aligned(256))) unsigned char staging[4][2048];      // [wave]: results on their way out
   const int lane = threadIdx.x & 63, hh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int T = (int)a.T, nt = (T + 31) >> 5;
-  const bool live = wave < nt;
   const bool ragged = (T & 31) != 0;
   const unsigned p = blockIdx.x;
   const Head hd = head_of(a, p);
@@ -855,94 +884,117 @@ __global__ __launch_bounds__(64 * NT, 1) void attn_bwd_short_mfma_kernel(AttnArg
   const int dh = PAD ? a.dh : DHP, dh8 = dh >> 3;
   const unsigned char* dob = reinterpret_cast<const unsigned char*>(a.dout) + hd.wide_off;
   const unsigned char* ob = reinterpret_cast<const unsigned char*>(a.o) + hd.wide_off;
-  const int r0 = live ? 32 * wave : 0;                     // (a spare wavefront repeats tile 0's loads and keeps nothing)
-  const int ri = 32 * wave + (lane & 31);                  // this lane's position, as a query and as a key
   const float c = a.scale * LOG2E;
-  // 1. the wavefront's four tiles (rows past the end repeat the last one), and the statistics of its queries
-  if (live) {
-    copy_tile<DHP>(hd.q + (long)r0 * ldb, ldb, T - r0, dh8, lds_address(tiles[0][wave]), lane);
-    copy_tile<DHP>(hd.k + (long)r0 * ldb, ldb, T - r0, dh8, lds_address(tiles[1][wave]), lane);
-    copy_tile<DHP>(hd.v + (long)r0 * ldb, ldb, T - r0, dh8, lds_address(tiles[2][wave]), lane);
-    copy_tile<DHP>(dob + (long)r0 * ldw, ldw, T - r0, dh8, lds_address(tiles[3][wave]), lane);
-  }
-  float L2 = a.lse[(long)p * a.T + (ri < T ? ri : T - 1)];
-  float D = 0.f;
+  // 1. the wavefront's k and v tiles (rows past the end repeat the last one), its q and do rows and their statistics
+  int tile[TPW];
 #pragma unroll
-  for (int kk = 0; kk < G::KK; ++kk)
-    D += dot8(own_cols_mem(dob + (long)r0 * ldw, ldw, T - r0, kk, dh8, lane),
-              own_cols_mem(ob + (long)r0 * ldw, ldw, T - r0, kk, dh8, lane));
-  D += __shfl_xor(D, 32, 64);
-  if (hh == 0) { stats[wave][lane] = L2; stats[wave][32 + lane] = D; }
+  for (int i = 0; i < TPW; ++i) {
+    tile[i] = i ? NT - 1 - wave : wave;
+    if (tile[i] < nt) {
+      const int r0 = 32 * tile[i];
+      copy_tile<DHP>(hd.k + (long)r0 * ldb, ldb, T - r0, dh8, lds_address(tiles[0][tile[i]]), lane);
+      copy_tile<DHP>(hd.v + (long)r0 * ldb, ldb, T - r0, dh8, lds_address(tiles[1][tile[i]]), lane);
+    }
+  }
+  bf16x8 fq[TPW][G::KK], fdo[TPW][G::KK];
+  float L2[TPW], D[TPW];
+#pragma unroll
+  for (int i = 0; i < TPW; ++i) {
+    const int r0 = tile[i] < nt ? 32 * tile[i] : 0;        // (a spare tile repeats tile 0's loads and keeps nothing)
+    const int ri = 32 * tile[i] + (lane & 31);
+    L2[i] = a.lse[(long)p * a.T + (ri < T ? ri : T - 1)];
+    D[i] = 0.f;
+#pragma unroll
+    for (int kk = 0; kk < G::KK; ++kk) {
+      fq[i][kk] = own_cols_mem(hd.q + (long)r0 * ldb, ldb, T - r0, kk, dh8, lane);
+      fdo[i][kk] = own_cols_mem(dob + (long)r0 * ldw, ldw, T - r0, kk, dh8, lane);
+      D[i] += dot8(fdo[i][kk], own_cols_mem(ob + (long)r0 * ldw, ldw, T - r0, kk, dh8, lane));
+    }
+    D[i] += __shfl_xor(D[i], 32, 64);
+    if (hh == 0) { stats[tile[i]][lane] = L2[i]; stats[tile[i]][32 + lane] = D[i]; }
+  }
   copies_in_flight<0>();
   __builtin_amdgcn_s_waitcnt(0xC07F);                      // (lgkmcnt(0): the statistics are written)
   workgroup_handover();
-  if (!live) return;
   // 2. the positions as queries: dq
-  {
-    bf16x8 fq[G::KK], fdo[G::KK];
 #pragma unroll
-    for (int kk = 0; kk < G::KK; ++kk) {
-      fq[kk] = own_cols_lds<DHP>(tiles[0][wave], kk, dh8, lane);
-      fdo[kk] = own_cols_lds<DHP>(tiles[3][wave], kk, dh8, lane);
-    }
+  for (int i = 0; i < TPW; ++i) {
+    if (tile[i] >= nt) continue;
+    const int ri = 32 * tile[i] + (lane & 31);             // this lane's position
     float16v dq[G::MB];
     zero_acc(dq);
     auto step = [&](int kt, auto masked_c) __attribute__((always_inline)) {
       constexpr bool MASKED = decltype(masked_c)::value;
-      const unsigned char* tk = tiles[1][kt];
-      const unsigned char* tv = tiles[2][kt];
+      const unsigned char* tk = tiles[0][kt];
+      const unsigned char* tv = tiles[1][kt];
       float16v s, dp;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) { s[r] = 0.f; dp[r] = -D; }      // dp comes out as dP - D
+      for (int r = 0; r < 16; ++r) { s[r] = 0.f; dp[r] = -D[i]; }      // dp comes out as dP - D
       bf16x8 fk[G::KK], fv[G::KK];
 #pragma unroll
       for (int kk = 0; kk < G::KK; ++kk) { fk[kk] = frag_cols_lds<DHP>(tk, kk, lane); fv[kk] = frag_cols_lds<DHP>(tv, kk, lane); }
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int kk = 0; kk < G::KK; ++kk) {
-        s = mfma(fk[kk], fq[kk], s);
-        dp = mfma(fv[kk], fdo[kk], dp);
+        s = mfma(fk[kk], fq[i][kk], s);
+        dp = mfma(fv[kk], fdo[i][kk], dp);
       }
       bf16x8 kr[G::MB][2];
 #pragma unroll
       for (int mb = 0; mb < G::MB; ++mb)
 #pragma unroll
-        for (int t = 0; t < 2; ++t) kr[mb][t] = frag_rows_lds<DHP>(tk, mb, t, lane);
+        for (int u = 0; u < 2; ++u) kr[mb][u] = frag_rows_lds<DHP>(tk, mb, u, lane);
       __builtin_amdgcn_sched_barrier(0);
       float ds[16];
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        float pr = fast_exp2(fmaf(s[r], c, -L2));
+        float pr = fast_exp2(fmaf(s[r], c, -L2[i]));
         if (MASKED) {
           const int kj = 32 * kt + tile_row_of(r, hh);
           if (!(CAUSAL ? kj <= ri : kj < T)) pr = 0.f;
         }
         ds[r] = pr * dp[r];
       }
-      const Scores<HILO> dq_s(ds);
+      const Scores<HILO> ss(ds);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int t = 0; t < 2; ++t)
+      for (int u = 0; u < 2; ++u)
 #pragma unroll
-        for (int mb = 0; mb < G::MB; ++mb) dq[mb] = dq_s.times(kr[mb][t], t, dq[mb]);
+        for (int mb = 0; mb < G::MB; ++mb) dq[mb] = ss.times(kr[mb][u], u, dq[mb]);
     };
-    const int n_own = CAUSAL ? wave + 1 : nt;
+    const int n_own = CAUSAL ? tile[i] + 1 : nt;
     const int n_plain = CAUSAL ? n_own - 1 : (ragged ? n_own - 1 : n_own);
     int kt = 0;
     for (; kt < n_plain; ++kt) step(kt, std::false_type());
     if (kt < n_own) step(kt, std::true_type());
-    if (ri < T)
-      store_row(reinterpret_cast<bf16_t*>(reinterpret_cast<unsigned char*>(a.dqkv) + (hd.q - reinterpret_cast<const unsigned char*>(a.qkv))) +
-                    (long)ri * hd.ld, dq, a.scale, dh, hh);
+    store_tile(reinterpret_cast<bf16_t*>(reinterpret_cast<unsigned char*>(a.dqkv) + (hd.q - reinterpret_cast<const unsigned char*>(a.qkv))) +
+                   (long)(32 * tile[i]) * hd.ld, hd.ld, T - 32 * tile[i], dq, a.scale, dh, staging[wave], lane);
   }
-  // 3. the positions as keys: dk, dv
-  {
-    bf16x8 fk[G::KK], fv[G::KK];
+  // 3. own k and v rows out of LDS, q and do rows into it
+  bf16x8 fk[TPW][G::KK], fv[TPW][G::KK];
+#pragma unroll
+  for (int i = 0; i < TPW; ++i)
+#pragma unroll
+    for (int kk = 0; kk < G::KK; ++kk) {                   // (a spare tile's slots hold nothing and are not used)
+      fk[i][kk] = own_cols_lds<DHP>(tiles[0][tile[i]], kk, dh8, lane);
+      fv[i][kk] = own_cols_lds<DHP>(tiles[1][tile[i]], kk, dh8, lane);
+    }
+  __builtin_amdgcn_s_waitcnt(0xC07F);
+  workgroup_handover();
+#pragma unroll
+  for (int i = 0; i < TPW; ++i)
 #pragma unroll
     for (int kk = 0; kk < G::KK; ++kk) {
-      fk[kk] = own_cols_lds<DHP>(tiles[1][wave], kk, dh8, lane);
-      fv[kk] = own_cols_lds<DHP>(tiles[2][wave], kk, dh8, lane);
+      put_cols_lds<DHP>(tiles[0][tile[i]], kk, lane, fq[i][kk]);
+      put_cols_lds<DHP>(tiles[1][tile[i]], kk, lane, fdo[i][kk]);
     }
+  __builtin_amdgcn_s_waitcnt(0xC07F);
+  workgroup_handover();
+  // 4. the positions as keys: dk, dv
+#pragma unroll
+  for (int i = 0; i < TPW; ++i) {
+    if (tile[i] >= nt) continue;
+    const int ri = 32 * tile[i] + (lane & 31);
     float16v dk[G::MB], dv[G::MB];
     zero_acc(dk);
     zero_acc(dv);
@@ -950,7 +1002,7 @@ __global__ __launch_bounds__(64 * NT, 1) void attn_bwd_short_mfma_kernel(AttnArg
     auto step = [&](int qt, auto masked_c) __attribute__((always_inline)) {
       constexpr bool MASKED = decltype(masked_c)::value;
       const unsigned char* tq = tiles[0][qt];
-      const unsigned char* td = tiles[3][qt];
+      const unsigned char* td = tiles[1][qt];
       const float* st = stats[qt];
       float16v s, dp;
 #pragma unroll
@@ -967,14 +1019,14 @@ __global__ __launch_bounds__(64 * NT, 1) void attn_bwd_short_mfma_kernel(AttnArg
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int kk = 0; kk < G::KK; ++kk) {
-        s = mfma(fqs[kk], fk[kk], s);
-        dp = mfma(fds[kk], fv[kk], dp);
+        s = mfma(fqs[kk], fk[i][kk], s);
+        dp = mfma(fds[kk], fv[i][kk], dp);
       }
       bf16x8 tr[G::MB][2], ur[G::MB][2];
 #pragma unroll
       for (int mb = 0; mb < G::MB; ++mb)
 #pragma unroll
-        for (int t = 0; t < 2; ++t) { tr[mb][t] = frag_rows_lds<DHP>(td, mb, t, lane); ur[mb][t] = frag_rows_lds<DHP>(tq, mb, t, lane); }
+        for (int u = 0; u < 2; ++u) { tr[mb][u] = frag_rows_lds<DHP>(td, mb, u, lane); ur[mb][u] = frag_rows_lds<DHP>(tq, mb, u, lane); }
       __builtin_amdgcn_sched_barrier(0);
       float pr[16], ds[16];
 #pragma unroll
@@ -989,28 +1041,22 @@ __global__ __launch_bounds__(64 * NT, 1) void attn_bwd_short_mfma_kernel(AttnArg
       const Scores<HILO> ps(pr), ss(ds);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int t = 0; t < 2; ++t)
+      for (int u = 0; u < 2; ++u)
 #pragma unroll
-        for (int mb = 0; mb < G::MB; ++mb) { dv[mb] = ps.times(tr[mb][t], t, dv[mb]); dk[mb] = ss.times(ur[mb][t], t, dk[mb]); }
+        for (int mb = 0; mb < G::MB; ++mb) { dv[mb] = ps.times(tr[mb][u], u, dv[mb]); dk[mb] = ss.times(ur[mb][u], u, dk[mb]); }
     };
-    int qt = CAUSAL ? wave : 0;
+    int qt = CAUSAL ? tile[i] : 0;
     if (CAUSAL) { step(qt, std::true_type()); ++qt; }
     const int plain_end = ragged ? nt - 1 : nt;
     for (; qt < plain_end; ++qt) step(qt, std::false_type());
     if (qt < nt) step(qt, std::true_type());
-    if (ri < T) {
-      bf16_t* row = reinterpret_cast<bf16_t*>(reinterpret_cast<unsigned char*>(a.dqkv) + (hd.k - reinterpret_cast<const unsigned char*>(a.qkv))) +
-                    (long)ri * hd.ld;
-      store_row(row, dk, a.scale, dh, hh);
-      store_row(row + hd.d, dv, 1.f, dh, hh);
-    }
+    bf16_t* first = reinterpret_cast<bf16_t*>(reinterpret_cast<unsigned char*>(a.dqkv) + (hd.k - reinterpret_cast<const unsigned char*>(a.qkv))) +
+                    (long)(32 * tile[i]) * hd.ld;
+    store_tile(first, hd.ld, T - 32 * tile[i], dk, a.scale, dh, staging[wave], lane);
+    store_tile(first + hd.d, hd.ld, T - 32 * tile[i], dv, 1.f, dh, staging[wave], lane);
   }
 }
 
-// Every head the padded tiles hold goes to the matrix cores: even at 8 of 32 columns the plain kernels' serial dot products
-// lose (32-wide heads, 12 sequences of 100, 8 heads, 4 layers: backward 1733 us a sweep plain, 16 us here).  A head
-// of its tile's full width has the kernels without the guards (PAD = false): those cost 64-wide heads 2 % and a
-// wavefront of occupancy.
 inline bool use_mfma(int dtype, const AttnArgs& a) { return dtype == 1 && a.dh <= 128; }
 
 template <int DHP, bool PAD, bool CAUSAL>
@@ -1020,7 +1066,7 @@ hipError_t launch_fwd(const AttnArgs& a, hipStream_t s) {
   hipLaunchKernelGGL((attn_fwd_mfma_kernel<DHP, PAD, CAUSAL>), dim3((unsigned)attn_grid(a)), dim3(64 * AT_WAVES), 0, s, m);
   return hipGetLastError();
 }
-// sequences whose q, k, v and do fit into one compute unit's LDS: a whole problem per workgroup
+// sequences whose tiles two workgroups' LDS holds: a whole problem per workgroup
 template <int DHP> constexpr long short_T() { return DHP == 128 ? 128 : 256; }
 template <int DHP, bool PAD, bool CAUSAL>
 hipError_t launch_bwd(const AttnArgs& a, hipStream_t s) {
@@ -1029,9 +1075,9 @@ hipError_t launch_bwd(const AttnArgs& a, hipStream_t s) {
     if (P > 0x7fffffffL) return hipErrorInvalidValue;
     const dim3 grid((unsigned)P);
     if (a.T <= 128) {
-      hipLaunchKernelGGL((attn_bwd_short_mfma_kernel<DHP, PAD, CAUSAL, 4>), grid, dim3(256), 0, s, a);
+      hipLaunchKernelGGL((attn_bwd_short_mfma_kernel<DHP, PAD, CAUSAL, 1>), grid, dim3(256), 0, s, a);
     } else {
-      if constexpr (DHP < 128) hipLaunchKernelGGL((attn_bwd_short_mfma_kernel<DHP, PAD, CAUSAL, 8>), grid, dim3(512), 0, s, a);
+      if constexpr (DHP < 128) hipLaunchKernelGGL((attn_bwd_short_mfma_kernel<DHP, PAD, CAUSAL, 2>), grid, dim3(256), 0, s, a);
     }
     return hipGetLastError();
   }
