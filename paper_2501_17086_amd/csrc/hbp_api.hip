@@ -527,7 +527,7 @@ hbp_status vjp_stage2(const hbp_desc* d, const hbp_buffers* b, const Workspace& 
 // gamma: 0 for the exact recurrence; in the iterations of hbp_backward the descriptor's
 hbp_status scan_stage(const hbp_desc* d, const hbp_buffers* b, const Workspace& w, long l_lo, long l_hi,
                       bool has_v, hipStream_t s, float gamma = 0.f, int force = 0, int m_parity = 0,
-                      bool exact_step = false) {
+                      bool exact_step = false, const void* top = nullptr) {
   if (d->post == HBP_POST_RMS) {
     // the whole chain from the top (an iteration, or w^0), or one layer of exact backpropagation
     const bool whole = !exact_step;
@@ -558,6 +558,7 @@ hbp_status scan_stage(const hbp_desc* d, const hbp_buffers* b, const Workspace& 
   sa.res_scale = 1.f - gamma;
   sa.blk_gamma = has_v ? gamma : 0.f;   // w^0 has no block term: only the residual path is rescaled
   sa.g = b->g;
+  sa.top = top;
   sa.dn = has_v ? at(b->workspace, w.off_v) : nullptr;
   sa.y = b->y;
   sa.rinv = b->rinv;
@@ -575,14 +576,19 @@ hbp_status scan_stage(const hbp_desc* d, const hbp_buffers* b, const Workspace& 
   return HBP_OK;
 }
 
+inline const void* e_top(const hbp_desc* d, const hbp_buffers* b) {
+  return d->loss_every_state ? at(b->e, (size_t)d->L * d->N * d->d * esize(d)) : b->e;
+}
+// where the scan of w^0 sets g[L] itself: no ReLU or norm that g[L] is first taken through
+inline bool scan_seeds(const hbp_desc* d) { return d->post == HBP_POST_NONE; }
+
 // g[L] := e_L
 hbp_status seed_top(const hbp_desc* d, const hbp_buffers* b, hipStream_t s) {
   if (d->post == HBP_POST_RMS) return HBP_OK;   // the post-norm scan seeds g[L] itself (through the last norm)
   const size_t es = esize(d);
   const size_t row = (size_t)d->N * d->d * es;
-  const void* src = d->loss_every_state ? at(b->e, (size_t)d->L * row) : b->e;
   ProfScope ps(HBP_PROF_OTHER, s);
-  HBP_TRY(hipMemcpyAsync(at(b->g, (size_t)d->L * row), src, row, hipMemcpyDeviceToDevice, s));
+  HBP_TRY(hipMemcpyAsync(at(b->g, (size_t)d->L * row), e_top(d, b), row, hipMemcpyDeviceToDevice, s));
   if (d->post == HBP_POST_RELU)   // g[L] is kept taken through the ReLU that made x_L, like every g[l >= 1]
     HBP_TRY(launch_mask_apply(d->dtype, at(b->g, (size_t)d->L * row), b->mask + (size_t)(d->L - 1) * d->N * d->d / 8,
                               d->N * d->d, s));
@@ -774,7 +780,8 @@ hbp_status hbp_forward(const hbp_desc* d, hbp_buffers* b, void* stream) {
       HBP_RUN(run_gemm(d, ga, s, HBP_PROF_FORWARD));
       if (d->post == HBP_POST_RMS) {     // post-norm: the norm after the residual sum, as for the MLP sub-blocks below
         ProfScope ps(HBP_PROF_FORWARD, s);
-        HBP_TRY(launch_rmsnorm_inplace(d->dtype, at(b->x, xo + (size_t)N * D * es), b->rinv + l * N, N, D, d->eps, s));
+        void* xn = at(b->x, xo + (size_t)N * D * es);
+        HBP_TRY(launch_rmsnorm_fwd(d->dtype, xn, xn, b->rinv + l * N, N, D, d->eps, s));
       }
       continue;
     }
@@ -912,8 +919,8 @@ hbp_status hbp_forward(const hbp_desc* d, hbp_buffers* b, void* stream) {
     }
     if (d->post == HBP_POST_RMS) {
       ProfScope ps(HBP_PROF_FORWARD, s);
-      HBP_TRY(launch_rmsnorm_inplace(d->dtype, at(b->x, xo + (size_t)d->N * d->d * es), b->rinv + l * d->N, d->N, d->d,
-                                     d->eps, s));
+      void* xn = at(b->x, xo + (size_t)d->N * d->d * es);
+      HBP_TRY(launch_rmsnorm_fwd(d->dtype, xn, xn, b->rinv + l * d->N, d->N, d->d, d->eps, s));
     }
     if (d->post == HBP_POST_RELU) {
       ProfScope ps(HBP_PROF_FORWARD, s);
@@ -933,9 +940,9 @@ hbp_status hbp_backward(const hbp_desc* d, int k, hbp_buffers* b, void* stream) 
   // y aliases x when there is no norm
   hbp_buffers bb = *b;
   if (d->norm == HBP_NORM_NONE) bb.y = bb.x;
-  HBP_RUN(seed_top(d, &bb, s));
   // w^0: the residual path alone
-  HBP_RUN(scan_stage(d, &bb, w, 0, d->L, false, s, d->gamma));
+  if (!scan_seeds(d)) HBP_RUN(seed_top(d, &bb, s));
+  HBP_RUN(scan_stage(d, &bb, w, 0, d->L, false, s, d->gamma, 0, 0, false, scan_seeds(d) ? e_top(d, &bb) : nullptr));
   // More than L iterations change nothing (Theorem 2: exact for k >= L - i).
   const long iters = k > d->L ? d->L : k;
   for (long it = 1; it <= iters; ++it) {
@@ -1000,10 +1007,10 @@ hbp_status hbp_initial_estimate(const hbp_desc* d, int algorithm, hbp_buffers* b
     return HBP_OK;
   }
   const Workspace w = carve(d);
-  HBP_RUN(seed_top(d, b, s));
+  if (!scan_seeds(d)) HBP_RUN(seed_top(d, b, s));
   return scan_stage(d, b, w, 0, d->L, false, s, d->gamma,
                     algorithm == HBP_SCAN_SEQUENTIAL ? 1 : algorithm == HBP_SCAN_CHUNKED ? 2 :
-                    algorithm == HBP_SCAN_SINGLE_PASS ? 3 : 0);
+                    algorithm == HBP_SCAN_SINGLE_PASS ? 3 : 0, 0, false, scan_seeds(d) ? e_top(d, b) : nullptr);
 }
 
 namespace {

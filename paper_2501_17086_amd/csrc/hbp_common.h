@@ -238,6 +238,7 @@ struct ScanArgs {
   const void* y;        // [L,N,d] storage (RMS only)
   const float* rinv;    // [L,N]   (RMS only)
   const void* e;        // [L+1,N,d] storage or NULL
+  const void* top;      // [N,d] storage or NULL: g[l_hi] is set from it first
   const float* lambda;  // [L,d] or NULL
   const void* lambda_tok;  // [L,N,d] storage, or NULL: coefficients per token (then lambda is NULL)
   long N, d;
@@ -295,7 +296,6 @@ struct PostScanArgs {
   float blk_gamma;      // mode 0: gamma lambda_l (.) g[l+1]^{old} is added to the block term (0: the old g is not read)
 };
 hipError_t launch_scan_post(int dtype, const PostScanArgs& a, hipStream_t s);
-hipError_t launch_rmsnorm_inplace(int dtype, void* x, float* rinv, long rows, long d, float eps, hipStream_t s);
 
 // x := max(x, 0) over n elements (n % 8 == 0), mask bit = 1 where x was positive; g := g (.) mask bits
 hipError_t launch_relu_mask(int dtype, void* x, uint8_t* mask, long n, hipStream_t s);
@@ -343,7 +343,7 @@ hipError_t launch_clip_factor(const float* const* grads, const long* sizes, int 
 hipError_t launch_optim(int dtype, int adamw, void* w, float* master, const float* g, float* m, float* v, long n,
                         const float* clip, const OptimArgs& o, hipStream_t s);
 
-// y = x * rinv, rinv = 1/sqrt(mean(x^2)+eps) for `rows` rows of width d
+// y = x * rinv, rinv = 1/sqrt(mean(x^2)+eps) for `rows` rows of width d <= 4096; y may be x
 hipError_t launch_rmsnorm_fwd(int dtype, const void* x, void* y, float* rinv, long rows, long d, float eps,
                               hipStream_t s);
 

@@ -29,7 +29,12 @@ __global__ __launch_bounds__(256) void scan_vec_kernel(ScanArgs a) {
   const T* e = reinterpret_cast<const T*>(a.e);
 
   float carry[8], gold[8];
-  load8(g + a.l_hi * layer + off, carry);
+  if (a.top) {
+    load8(reinterpret_cast<const T*>(a.top) + off, carry);
+    store8(g + a.l_hi * layer + off, carry);
+  } else {
+    load8(g + a.l_hi * layer + off, carry);
+  }
 #pragma unroll
   for (int i = 0; i < 8; ++i) gold[i] = carry[i];
   const bool use_old = GAMMA && a.blk_gamma != 0.f;
@@ -310,30 +315,70 @@ __global__ __launch_bounds__(256) void scan_rows_pipe_kernel(ScanArgs a) {
   }
 }
 
+// y = x / rms(x), rinv = 1/rms(x) per row of width d <= 8 LPR V: LPR lanes hold a row in registers (V vectors of 8 per lane), a
+// wavefront takes 64 / LPR rows at a time and ROUNDS such groups, whose loads are all on their way before the first is
+// reduced.  HBM-bound: the row is read once and written once; y may be x.  Measured (32768 rows of 256): 11.7 us with a
+// wavefront per row, half of its lanes idle, and a second pass over the row; 8.0 now.
+template <typename T, int LPR, int V, int ROUNDS>
+__global__ __launch_bounds__(256) void rmsnorm_kernel(const T* x, T* y, float* __restrict__ rinv, long rows, long d, float eps) {
+  const int lane = threadIdx.x & 63, li = lane % LPR;
+  const long group = ((long)blockIdx.x * 4 + (threadIdx.x >> 6)) * ROUNDS;
+  Raw8<T> raw[ROUNDS][V];
+#pragma unroll
+  for (int q = 0; q < ROUNDS; ++q) {
+    const long row = (group + q) * (64 / LPR) + lane / LPR;
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      const long c = (li + v * LPR) * 8;
+      raw[q][v] = Raw8<T>{};
+      if (row < rows && c < d) raw[q][v].load(x + row * d + c);
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < ROUNDS; ++q) {
+    const long row = (group + q) * (64 / LPR) + lane / LPR;
+    float ss = 0.f;
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      float t[8];
+      raw[q][v].unpack(t);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) ss = fmaf(t[i], t[i], ss);
+    }
+#pragma unroll
+    for (int o = LPR / 2; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
+    if (row >= rows) continue;
+    const float r = 1.0f / sqrtf(ss / (float)d + eps);
+    if (li == 0) rinv[row] = r;
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      const long c = (li + v * LPR) * 8;
+      if (c >= d) continue;
+      float t[8];
+      raw[q][v].unpack(t);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) t[i] *= r;
+      store8(y + row * d + c, t);
+    }
+  }
+}
+template <typename T, int LPR, int V, int ROUNDS>
+hipError_t launch_rmsnorm_as(const T* x, T* y, float* rinv, long rows, long d, float eps, hipStream_t s) {
+  const long per_wg = 4L * ROUNDS * (64 / LPR);
+  hipLaunchKernelGGL((rmsnorm_kernel<T, LPR, V, ROUNDS>), dim3((unsigned)((rows + per_wg - 1) / per_wg)), dim3(256), 0, s, x, y,
+                     rinv, rows, d, eps);
+  return hipGetLastError();
+}
+// the fewest lanes that hold a row; two groups per wavefront where there are rows enough to fill the chip all the same
 template <typename T>
-__global__ __launch_bounds__(256) void rmsnorm_fwd_kernel(const T* __restrict__ x, T* __restrict__ y,
-                                                          float* __restrict__ rinv, long rows, long d, float eps) {
-  const int lane = threadIdx.x & 63;
-  const long row = (long)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-  if (row >= rows) return;
-  const T* xr = x + row * d;
-  float ss = 0.f;
-  for (long c = lane * 8; c < d; c += 512) {
-    float v[8];
-    load8(xr + c, v);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) ss = fmaf(v[i], v[i], ss);
-  }
-  ss = wave_sum(ss);
-  const float r = 1.0f / sqrtf(ss / (float)d + eps);
-  if (lane == 0) rinv[row] = r;
-  for (long c = lane * 8; c < d; c += 512) {
-    float v[8];
-    load8(xr + c, v);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] *= r;
-    store8(y + row * d + c, v);
-  }
+hipError_t launch_rmsnorm(const T* x, T* y, float* rinv, long rows, long d, float eps, hipStream_t s) {
+  if (d <= 128) return launch_rmsnorm_as<T, 16, 1, 2>(x, y, rinv, rows, d, eps, s);
+  if (d <= 256) return launch_rmsnorm_as<T, 32, 1, 2>(x, y, rinv, rows, d, eps, s);
+  if (d <= 512) return rows >= 16384 ? launch_rmsnorm_as<T, 64, 1, 2>(x, y, rinv, rows, d, eps, s)
+                                     : launch_rmsnorm_as<T, 64, 1, 1>(x, y, rinv, rows, d, eps, s);
+  if (d <= 1024) return launch_rmsnorm_as<T, 64, 2, 1>(x, y, rinv, rows, d, eps, s);
+  if (d <= 2048) return launch_rmsnorm_as<T, 64, 4, 1>(x, y, rinv, rows, d, eps, s);
+  return d <= 4096 ? launch_rmsnorm_as<T, 64, 8, 1>(x, y, rinv, rows, d, eps, s) : hipErrorInvalidValue;
 }
 
 // ---------------------------------------------------------------------------
@@ -872,20 +917,33 @@ hipError_t launch_scan_sp(const ScanArgs& a, hipStream_t s) {
 }
 
 template <typename T>
-hipError_t launch_scan_t(const ScanArgs& a, hipStream_t s) {
-  if (a.l_hi <= a.l_lo) return hipSuccess;
+hipError_t launch_scan_t(const ScanArgs& args, hipStream_t s) {
+  ScanArgs a = args;
+  // only the walk without a norm reads the top state itself; the other forms find it in g
+  auto seed = [&]() -> hipError_t {
+    const void* top = a.top;
+    a.top = nullptr;
+    const size_t row = (size_t)(a.N * a.d) * sizeof(T);
+    return top ? hipMemcpyAsync(reinterpret_cast<char*>(a.g) + (size_t)a.l_hi * row, top, row, hipMemcpyDeviceToDevice, s) : hipSuccess;
+  };
+  if (a.l_hi <= a.l_lo) return seed();
   const bool gam = a.res_scale != 1.f || a.blk_gamma != 0.f;
   const bool rms = a.norm_rms && a.dn;
   constexpr int dtype = std::is_same<T, float>::value ? 0 : 1;
+  hipError_t e = hipSuccess;
   if (a.force == 3) {
     if (!a.chunk_ws || !sp_covers(dtype, a)) return hipErrorInvalidValue;
-    return launch_scan_sp(a, s);
+    e = seed();
+    return e == hipSuccess ? launch_scan_sp(a, s) : e;
   }
   if (a.force == 2) {
     if (!a.chunk_ws || rms || a.mask) return hipErrorInvalidValue;
-    return launch_scan_chunked<T>(a, s);
+    e = seed();
+    return e == hipSuccess ? launch_scan_chunked<T>(a, s) : e;
   }
   if (a.force == 0 && !a.mask && a.chunk_ws && use_chunked(a.l_hi - a.l_lo, a.N, a.d, rms)) {
+    e = seed();
+    if (e != hipSuccess) return e;
     // (the scratch of the three-pass form, which the callers size the workspace for, holds the single-pass form's)
     if (sp_covers(dtype, a) &&
         scan_sp_ws_bytes(a.l_hi - a.l_lo, a.N, a.d, a.lambda_tok != nullptr) <=
@@ -894,6 +952,8 @@ hipError_t launch_scan_t(const ScanArgs& a, hipStream_t s) {
     return launch_scan_chunked<T>(a, s);
   }
   if (a.norm_rms && a.dn) {
+    e = seed();
+    if (e != hipSuccess) return e;
     const int nch = (int)((a.d + 511) / 512);
     dim3 grid((unsigned)((a.N + 3) / 4)), block(256);
     if (gam) {
@@ -1337,31 +1397,6 @@ __global__ __launch_bounds__(256) void scan_post_split_kernel(PostScanArgs a) {
   }
 }
 
-template <typename T>
-__global__ __launch_bounds__(256) void rmsnorm_inplace_kernel(T* x, float* rinv, long rows, long d, float eps) {
-  const int lane = threadIdx.x & 63;
-  const long row = (long)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-  if (row >= rows) return;
-  T* xr = x + row * d;
-  float ss = 0.f;
-  for (long c = lane * 8; c < d; c += 512) {
-    float v[8];
-    load8(xr + c, v);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) ss = fmaf(v[i], v[i], ss);
-  }
-  ss = wave_sum(ss);
-  const float r = 1.0f / sqrtf(ss / (float)d + eps);
-  if (lane == 0) rinv[row] = r;
-  for (long c = lane * 8; c < d; c += 512) {
-    float v[8];
-    load8(xr + c, v);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] *= r;
-    store8(xr + c, v);
-  }
-}
-
 // x := max(x, 0) and one mask bit per element (1 where x was positive), 8 elements per thread
 template <typename T>
 __global__ __launch_bounds__(256) void relu_mask_kernel(T* __restrict__ x, uint8_t* __restrict__ mask, long nvec) {
@@ -1435,13 +1470,6 @@ hipError_t launch_scan_post(int dtype, const PostScanArgs& a, hipStream_t s) {
   return dtype == 0 ? launch_scan_post_t<float>(a, s) : launch_scan_post_t<bf16_t>(a, s);
 }
 
-hipError_t launch_rmsnorm_inplace(int dtype, void* x, float* rinv, long rows, long d, float eps, hipStream_t s) {
-  dim3 grid((unsigned)((rows + 3) / 4)), block(256);
-  if (dtype == 0) hipLaunchKernelGGL(rmsnorm_inplace_kernel<float>, grid, block, 0, s, (float*)x, rinv, rows, d, eps);
-  else hipLaunchKernelGGL(rmsnorm_inplace_kernel<bf16_t>, grid, block, 0, s, (bf16_t*)x, rinv, rows, d, eps);
-  return hipGetLastError();
-}
-
 hipError_t launch_relu_mask(int dtype, void* x, uint8_t* mask, long n, hipStream_t s) {
   const long nvec = n / 8;
   dim3 grid((unsigned)((nvec + 255) / 256)), block(256);
@@ -1464,13 +1492,8 @@ hipError_t launch_scan(int dtype, const ScanArgs& a, hipStream_t s) {
 
 hipError_t launch_rmsnorm_fwd(int dtype, const void* x, void* y, float* rinv, long rows, long d, float eps,
                               hipStream_t s) {
-  dim3 grid((unsigned)((rows + 3) / 4)), block(256);
-  if (dtype == 0)
-    hipLaunchKernelGGL(rmsnorm_fwd_kernel<float>, grid, block, 0, s, (const float*)x, (float*)y, rinv, rows, d, eps);
-  else
-    hipLaunchKernelGGL(rmsnorm_fwd_kernel<bf16_t>, grid, block, 0, s, (const bf16_t*)x, (bf16_t*)y, rinv, rows, d,
-                       eps);
-  return hipGetLastError();
+  return dtype == 0 ? launch_rmsnorm<float>((const float*)x, (float*)y, rinv, rows, d, eps, s)
+                    : launch_rmsnorm<bf16_t>((const bf16_t*)x, (bf16_t*)y, rinv, rows, d, eps, s);
 }
 
 }  // namespace hbp

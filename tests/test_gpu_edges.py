@@ -114,3 +114,17 @@ def test_short_contractions_on_whole_tiles(B, d):
     H.assert_close(H.to_np(p.z), sv["z"], H.TOL["bf16"], f"{w.name} z")
     H.assert_close(H.to_np(p.dphi), sv["dphi"], H.TOL["bf16"], f"{w.name} act'")
     _check_backward(B, w, p, st, sv, inp, w.name)
+
+
+# the norm's kernels: rows held by 16, 32 or 64 lanes and one to eight vectors per lane, the last partly past the width, and
+# a row count that leaves part of a wavefront without rows; in front of the block (y, rinv) and after the sum, in place
+@pytest.mark.parametrize("post", ["none", "rms"])
+@pytest.mark.parametrize("d,N", [(8, 1), (128, 33), (136, 5), (256, 17), (264, 7), (512, 3), (520, 9), (1024, 2), (1032, 6),
+                                 (2056, 5), (4096, 3)])
+def test_row_norms(B, d, N, post):
+    w = synth.scaled(W["resnet_like"], name=f"norm_{d}_{N}_{post}", L=2, N=N, d=d, d_ff=16, w2_scale=0.7, post=post,
+                     norm="rms" if post == "none" else "none", ks=(0,))
+    inp, st, sv, p = _forward_matches(B, w)
+    H.assert_close(H.to_np(p.rinv), sv["rpost" if post == "rms" else "rinv"], H.TOL["bf16"], f"{w.name} rinv")
+    if post == "none":
+        H.assert_close(H.to_np(p.y), sv["y"], H.TOL["bf16"], f"{w.name} y")
