@@ -131,30 +131,61 @@ __device__ __forceinline__ void store4(float* p, const float (&v)[4]) {
   *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
 }
 
-// coordinates of one output tile and its share of the contraction
+// Division of numbers below 2^31 by a fixed d: (n m) >> sh with m = floor(2^sh / d) + 1, sh = 31 + ceil(log2 d) (the method
+// of Granlund and Montgomery).  The hardware has no integer division, and a tile's coordinates took two 64-bit and five
+// 32-bit ones, twice per tile: about 1.5 us of a tile that takes 18.
+struct FastDiv {
+  unsigned m, sh;
+  __device__ __forceinline__ unsigned operator()(unsigned n) const { return (unsigned)(((unsigned long long)n * m) >> sh); }
+};
+inline FastDiv fast_div(unsigned d) {
+  unsigned s = 0;
+  while ((1ull << s) < d) ++s;
+  return {(unsigned)((1ull << (31 + s)) / d + 1), 31 + s};
+}
+// the tile walk of a launch: every tile's share of the contraction is KT slices
+struct Walk {
+  FastDiv by_mn, by_grp, by_split;
+  unsigned tiles_mn, grp_tiles;      // tiles per matrix, and per block of GROUP_M tile rows
+  int tiles_m, split, KT, total, per_xcd;
+};
+inline Walk make_walk(const GemmArgs& g) {
+  Walk w;
+  const unsigned tm = (unsigned)(g.M / BM), tn = (unsigned)(g.N / BN);
+  w.tiles_m = (int)tm;
+  w.tiles_mn = tm * tn;
+  w.grp_tiles = GROUP_M * tn;
+  w.split = g.split_k;
+  w.by_mn = fast_div(w.tiles_mn);
+  w.by_grp = fast_div(w.grp_tiles);
+  w.by_split = fast_div((unsigned)g.split_k);
+  w.KT = (int)(g.K / g.split_k / BK);
+  w.total = (int)((long)w.tiles_mn * g.batch * g.split_k);
+  w.per_xcd = (w.total + 7) / 8;
+  return w;
+}
+
+// coordinates of one output tile and the start of its share of the contraction
 struct TileCoord {
-  long batch, m0, n0, k_begin, k_end;
-  int split, KT;
+  long batch, m0, n0, k_begin;
+  int split;
 };
 
-__device__ __forceinline__ TileCoord decode_tile(const GemmArgs& g, int t, int tiles_m, int tiles_n) {
+__device__ __forceinline__ TileCoord decode_tile(const Walk& w, int t) {
   TileCoord c;
-  const unsigned tiles_mn = (unsigned)tiles_m * tiles_n;
-  const unsigned zb = (unsigned)t / tiles_mn;            // batch * split_k + split
-  const unsigned rem = (unsigned)t - zb * tiles_mn;
-  const unsigned grp = rem / ((unsigned)GROUP_M * tiles_n);
-  const unsigned in_grp = rem - grp * GROUP_M * tiles_n;
-  const unsigned left = tiles_m - grp * GROUP_M;
-  const unsigned gm = left < (unsigned)GROUP_M ? left : (unsigned)GROUP_M;
-  c.m0 = (long)(grp * GROUP_M + in_grp % gm) * BM;
-  c.n0 = (long)(in_grp / gm) * BN;
-  c.batch = zb / (unsigned)g.split_k;
-  c.split = (int)(zb % (unsigned)g.split_k);
-  long kchunk = (g.K + g.split_k - 1) / g.split_k;
-  kchunk = (kchunk + BK - 1) / BK * BK;
-  c.k_begin = (long)c.split * kchunk;
-  c.k_end = c.k_begin + kchunk < g.K ? c.k_begin + kchunk : g.K;
-  c.KT = c.k_end > c.k_begin ? (int)((c.k_end - c.k_begin + BK - 1) / BK) : 0;
+  const unsigned zb = w.by_mn((unsigned)t);              // batch * split_k + split
+  const unsigned rem = (unsigned)t - zb * w.tiles_mn;
+  const unsigned grp = w.by_grp(rem);
+  const unsigned in_grp = rem - grp * w.grp_tiles;
+  const unsigned left = (unsigned)w.tiles_m - grp * GROUP_M;
+  unsigned col = in_grp / GROUP_M, row = in_grp % GROUP_M;
+  if (left < (unsigned)GROUP_M) { col = in_grp / left; row = in_grp - col * left; }   // the last, lower block
+  c.m0 = (long)(grp * GROUP_M + row) * BM;
+  c.n0 = (long)col * BN;
+  const unsigned batch = w.by_split(zb);
+  c.batch = batch;
+  c.split = (int)(zb - batch * (unsigned)w.split);
+  c.k_begin = (long)c.split * w.KT * BK;
   return c;
 }
 
@@ -387,8 +418,7 @@ constexpr int LEAN_LDS = LEAN_NST * STAGE_BYTES + NW * 4096;
 // 128 bytes for A (chunk k of row r at chunk k ^ (r/2 % 8)), refilled at every even step with the pair two steps
 // ahead, and the ring of four 16 KB stages for B behind them; everything else is as without it.
 template <bool A_KC, bool B_KC, int FAST, bool ONE_AT_A_TIME, bool PAIR>
-__global__ __launch_bounds__(NTHR, 1) void gemm_mfma_lean_kernel(GemmArgs g, int tiles_m, int tiles_n, long total,
-                                                                 long per_xcd) {
+__global__ __launch_bounds__(NTHR, 1) void gemm_mfma_lean_kernel(GemmArgs g, Walk walk) {
   static_assert(!PAIR || A_KC, "pairs of slices are copied for a K-contiguous A only");
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -406,8 +436,9 @@ __global__ __launch_bounds__(NTHR, 1) void gemm_mfma_lean_kernel(GemmArgs g, int
   // (one trip to memory instead of eight, the rest served by the memory-side cache).
   const int wpx = gridDim.x >> 3;
   const int t_stride = ONE_AT_A_TIME ? (int)gridDim.x : wpx;
-  int t = (ONE_AT_A_TIME ? xcd * wpx : xcd * (int)per_xcd) + (blockIdx.x >> 3);
-  const int t_end = !ONE_AT_A_TIME && (xcd + 1) * per_xcd < total ? (xcd + 1) * (int)per_xcd : (int)total;
+  int t = (ONE_AT_A_TIME ? xcd * wpx : xcd * walk.per_xcd) + (int)(blockIdx.x >> 3);
+  const int t_end = !ONE_AT_A_TIME && (xcd + 1) * walk.per_xcd < walk.total ? (xcd + 1) * walk.per_xcd : walk.total;
+  const int KT = walk.KT;
   if (t >= t_end) return;
 
   const long lda = A_KC ? g.a_sm : g.a_sk;
@@ -434,7 +465,7 @@ __global__ __launch_bounds__(NTHR, 1) void gemm_mfma_lean_kernel(GemmArgs g, int
                                                 (A_KC ? c.m0 * lda + c.k_begin : c.m0 + c.k_begin * lda));
     qb = reinterpret_cast<const unsigned char*>(reinterpret_cast<const bf16_t*>(g.B) + c.batch * g.b_sb +
                                                 (B_KC ? c.n0 * ldb + c.k_begin : c.n0 + c.k_begin * ldb));
-    p_left = c.KT;
+    p_left = KT;
   };
   auto copy_slice = [&]() {
     if (PAIR) {
@@ -465,7 +496,7 @@ __global__ __launch_bounds__(NTHR, 1) void gemm_mfma_lean_kernel(GemmArgs g, int
     }
     if (--p_left == 0) {
       pt += t_stride;
-      if (pt < t_end) aim(decode_tile(g, pt, tiles_m, tiles_n));
+      if (pt < t_end) aim(decode_tile(walk, pt));
       else p_more = false;
     }
   };
@@ -473,7 +504,7 @@ __global__ __launch_bounds__(NTHR, 1) void gemm_mfma_lean_kernel(GemmArgs g, int
   float16v acc[4][2];
   bf16x8 fa[4][2], fb[2][2];
   Quad16 aux0 = {}, aux1 = {};   // the first half of a tile's fused operand
-  TileCoord cc = decode_tile(g, t, tiles_m, tiles_n);   // the consumer's tile
+  TileCoord cc = decode_tile(walk, t);   // the consumer's tile
   unsigned c_off = 0;      // byte offset of the consumer's stage
   int epi_recent = 0;      // waits that still see the last epilogue's operations
   constexpr int E = StagedOps<FAST>::value;
@@ -584,18 +615,18 @@ __global__ __launch_bounds__(NTHR, 1) void gemm_mfma_lean_kernel(GemmArgs g, int
   constexpr std::integral_constant<int, has_aux<FAST>() ? 2 : 0> a2{};
   while (true) {
     if (!has_aux<FAST>()) {
-      step(yes, no, a0, !PAIR && cc.KT == 1);
-      if (PAIR) step(no, yes, a0, cc.KT == 2);
+      step(yes, no, a0, !PAIR && KT == 1);
+      if (PAIR) step(no, yes, a0, KT == 2);
 #pragma unroll 1
-      for (int k = PAIR ? 2 : 1; k < cc.KT; k += PAIR ? 2 : 1) {
-        step(no, no, a0, !PAIR && k + 1 == cc.KT);
-        if (PAIR) step(no, yes, a0, k + 2 == cc.KT);
+      for (int k = PAIR ? 2 : 1; k < KT; k += PAIR ? 2 : 1) {
+        step(no, no, a0, !PAIR && k + 1 == KT);
+        if (PAIR) step(no, yes, a0, k + 2 == KT);
       }
     } else {                 // (at least four slices: the launcher sees to it)
       step(yes, no, a0, false);
       if (PAIR) step(no, yes, a0, false);
 #pragma unroll 1
-      for (int k = PAIR ? 4 : 3; k < cc.KT; k += PAIR ? 2 : 1) {
+      for (int k = PAIR ? 4 : 3; k < KT; k += PAIR ? 2 : 1) {
         step(no, no, a0, false);
         if (PAIR) step(no, yes, a0, false);
       }
@@ -612,7 +643,7 @@ __global__ __launch_bounds__(NTHR, 1) void gemm_mfma_lean_kernel(GemmArgs g, int
     epi_recent = AHEAD - 1;
     t += t_stride;
     if (t >= t_end) break;
-    cc = decode_tile(g, t, tiles_m, tiles_n);
+    cc = decode_tile(walk, t);
   }
   if (grp == 0) __builtin_amdgcn_s_barrier();   // matches group 1's last barrier
 }
@@ -640,12 +671,9 @@ hipError_t launch_lean_walk(const GemmArgs& g, hipStream_t s) {
     hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kern), LEAN_LDS, attr_set);
     if (e != hipSuccess) return e;
   }
-  const int tiles_m = (int)(g.M / BM), tiles_n = (int)(g.N / BN);
-  const long total = (long)tiles_m * tiles_n * g.batch * g.split_k;
-  const long per_xcd = (total + 7) / 8;
-  const long wg_per_xcd = per_xcd < 32 ? per_xcd : 32;
-  const int lds = LEAN_LDS;
-  hipLaunchKernelGGL(kern, dim3((unsigned)(wg_per_xcd * 8)), dim3(NTHR), lds, s, g, tiles_m, tiles_n, total, per_xcd);
+  const Walk walk = make_walk(g);
+  const int wg_per_xcd = walk.per_xcd < 32 ? walk.per_xcd : 32;
+  hipLaunchKernelGGL(kern, dim3((unsigned)(wg_per_xcd * 8)), dim3(NTHR), LEAN_LDS, s, g, walk);
   return hipGetLastError();
 }
 template <bool A_KC, bool B_KC, int FAST>
