@@ -511,8 +511,12 @@ __global__ __launch_bounds__(NTHR, 1) void gemm_mfma_lean_kernel(GemmArgs g, Wal
   constexpr int AHEAD = LEAN_NST - 1;                      // slices copied ahead of the one being multiplied
   constexpr int W_PLAIN = (AHEAD - 1) * PER_SLICE;
   constexpr int W_EPI = W_PLAIN + E > 63 ? 63 : W_PLAIN + E;
+  // EARLY: half of the fused operand is asked for before the tile's end, and the groups' epilogues run together (below).
+  // Not on the one-at-a-time walk, where the stream of copies is the limit: a backward pass over 96 blocks of 16384 x 8192
+  // x 2048 took 316 ms with it and with its second test of epi_recent in every slice, 311 without (before either: 311).
+  constexpr bool EARLY = has_aux<FAST>() && !ONE_AT_A_TIME;
   // the slice that the second step of a tile waits for was copied after the 8 early loads of the epilogue before
-  constexpr int E2 = has_aux<FAST>() ? E - 8 : E, W_EPI2 = W_PLAIN + E2 > 63 ? 63 : W_PLAIN + E2;
+  constexpr int E2 = EARLY ? E - 8 : E, W_EPI2 = W_PLAIN + E2 > 63 ? 63 : W_PLAIN + E2;
   // PAIR: a wave issues 4 copies of A and 2 of B in an even step, 2 of B in an odd one.  At the end of an even
   // step c the B of slice c + 1 (issued two steps before) must have landed: what may be outstanding is what was
   // issued after it, 2 + 4 + 2 copies (and a recent epilogue's operations); at the end of an odd step the pair
@@ -532,7 +536,7 @@ __global__ __launch_bounds__(NTHR, 1) void gemm_mfma_lean_kernel(GemmArgs g, Wal
   // meets it after its epilogue instead: the two groups' epilogues, chains of LDS and memory latencies, then run in
   // the same tick, not one after the other.  Measured: 16384 x 4096 x 1024 with GELU 183 -> 174 us, 32768 x 1024 x 256 47 -> 41,
   // 12 x 32768 x 1024 x 256 with act' 329 -> 325; plain stores 1 % slower, so not there.
-  constexpr bool TOGETHER = has_aux<FAST>() || FAST == FAST_ACT_GELU;
+  constexpr bool TOGETHER = EARLY || FAST == FAST_ACT_GELU;
   auto step = [&](auto first_c, auto odd_c, auto aux_c, bool last) {
     constexpr bool FIRST = decltype(first_c)::value;
     constexpr int AUX = decltype(aux_c)::value, X = AUX ? 8 : 0;
@@ -571,7 +575,7 @@ __global__ __launch_bounds__(NTHR, 1) void gemm_mfma_lean_kernel(GemmArgs g, Wal
       // this wave's share of the next slice has landed once only what it issued for the slices after
       // that one (and a recent epilogue's operations, which lie among them) is outstanding
       if (!copying) wait_vm_lds<X>();
-      else if (epi_recent > 1) { wait_vm_lds<W_EPI>(); --epi_recent; }
+      else if (EARLY && epi_recent > 1) { wait_vm_lds<W_EPI>(); --epi_recent; }
       else if (epi_recent > 0) { wait_vm_lds<W_EPI2>(); --epi_recent; }
       else wait_vm_lds<W_PLAIN + X>();
     }
@@ -611,10 +615,10 @@ __global__ __launch_bounds__(NTHR, 1) void gemm_mfma_lean_kernel(GemmArgs g, Wal
   constexpr std::integral_constant<bool, false> no{};
   constexpr std::integral_constant<bool, true> yes{};
   constexpr std::integral_constant<int, 0> a0{};
-  constexpr std::integral_constant<int, has_aux<FAST>() ? 1 : 0> a1{};
-  constexpr std::integral_constant<int, has_aux<FAST>() ? 2 : 0> a2{};
+  constexpr std::integral_constant<int, EARLY ? 1 : 0> a1{};
+  constexpr std::integral_constant<int, EARLY ? 2 : 0> a2{};
   while (true) {
-    if (!has_aux<FAST>()) {
+    if (!EARLY) {
       step(yes, no, a0, !PAIR && KT == 1);
       if (PAIR) step(no, yes, a0, KT == 2);
 #pragma unroll 1
@@ -633,6 +637,7 @@ __global__ __launch_bounds__(NTHR, 1) void gemm_mfma_lean_kernel(GemmArgs g, Wal
       step(no, no, a1, false);
       if (PAIR) step(no, yes, a2, true); else step(no, no, a2, true);
     }
+    if (has_aux<FAST>() && !EARLY) { fetch_aux(aux0, g, cc, wm0, wn0, lane, 0); fetch_aux(aux1, g, cc, wm0, wn0, lane, 1); }
     if (FAST == FAST_STORE_F32) epilogue_fast_fn<FAST>(g, cc, acc, wm0, wn0, lane);
     else epilogue_staged_fn<FAST>(g, cc, acc, wm0, wn0, lane, smem + LEAN_NST * STAGE_BYTES + wave * 4096, aux0, aux1);
     if (TOGETHER && grp == 1) {
