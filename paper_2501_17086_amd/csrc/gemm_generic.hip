@@ -1,5 +1,6 @@
-// Generic strided GEMM with fp32 FMA accumulation: the path for fp32 storage
-// and for shapes the MFMA kernels do not cover.  64x64 tile per workgroup,
+// Generic strided GEMM with fp32 FMA accumulation, for operands whose addresses
+// or strides the MFMA kernels cannot read in vectors (bf16 not a multiple of 8
+// elements, fp32 not a multiple of 4).  64x64 tile per workgroup,
 // 16-deep K slices staged through LDS, 4x4 outputs per thread.
 #include "hbp_common.h"
 
