@@ -1,6 +1,7 @@
 // Device helpers shared by the matrix-core GEMM kernels: direct global -> LDS copies, counted waits, vector types and
 // the activations of the forward epilogues.
 #pragma once
+#include "gelu.h"
 #include "hbp_common.h"
 
 namespace hbp {
@@ -41,27 +42,9 @@ __device__ __forceinline__ void wait_vm() {
   __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
 }
 
-// z = a Phi(a) (exact erf form) and its derivative Phi(a) + a phi(a), with phi the normal density and
-// Phi(-u) = phi(u) m(u), u >= 0: m, the Mills ratio, is a polynomial in t = 1 / (1 + p u) without a constant term (the form
-// of Hastings' approximations; p and the coefficients are a least-squares fit on 0 <= u <= 14, reweighted until the largest
-// relative error was 9e-8).  One exponential serves phi and Phi, and the left tail keeps its relative accuracy, which
-// 1 + erf loses to cancellation.  About 27 vector operations per element, where erff and an exponential of its own
-// are above 50: the epilogue of a 256 x 256 tile is bound by them.
+// GELU and its derivative, on v_exp_f32 and v_rcp_f32
 __device__ __forceinline__ void gelu_both(float a, float& z, float& dz) {
-  const float f = 0.39894228040143267794f * __builtin_amdgcn_exp2f(a * a * -0.72134752044448170368f);
-  const float t = __builtin_amdgcn_rcpf(fmaf(0.30459785906278414f, fabsf(a), 1.0f));
-  float m = 0.09215526492038636f;
-  m = fmaf(m, t, -0.38581881766212406f);
-  m = fmaf(m, t, 0.4720240713773309f);
-  m = fmaf(m, t, -0.10034110303417618f);
-  m = fmaf(m, t, 0.3058749542984055f);
-  m = fmaf(m, t, 0.25824452690273747f);
-  m = fmaf(m, t, 0.30667787234706945f);
-  m = fmaf(m, t, 0.3044974801909156f);
-  const float q = f * (m * t);
-  const float phi = a > 0.f ? 1.0f - q : q;
-  dz = fmaf(a, f, phi);
-  z = a * phi;
+  gelu_pair(a, z, dz, [](float x) { return __builtin_amdgcn_exp2f(x); }, [](float x) { return __builtin_amdgcn_rcpf(x); });
 }
 
 }  // namespace
