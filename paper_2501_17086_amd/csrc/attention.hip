@@ -11,7 +11,8 @@
 //   - the MFMA is issued so that a lane owns one query (dk/dv kernel: one key) and its 16 accumulator registers run
 //     over 16 of the streamed tile's 32 keys (queries): row statistics, the running rescale of the output and the
 //     factor dP - D are per-lane scalars (D and the row statistic enter as the accumulators' start values);
-//   - the scores of a lane, rounded to bf16, are fed back as the second product's operand straight from the
+//   - the scores of a lane, rounded to bf16 (64-wide heads) or cut into three bf16 parts that hold all of them (every other
+//     width, which plain kernels with fp32 scores served before), are fed back as the second product's operand straight from the
 //     registers: the contraction index of an MFMA is a dummy, so it is enough that the other operand is fetched
 //     in the same (permuted) order of keys, which the transposing LDS read ds_read_b64_tr_b16 does from the tile;
 //   - tiles reach LDS by direct copies (global_load_lds_dwordx4, no staging registers) issued three steps ahead, each
@@ -345,33 +346,41 @@ __device__ __forceinline__ bf16x8 pack8(const float* v) {
                              pack_bf16x2(v[6], v[7]));
   return __builtin_bit_cast(bf16x8, w);
 }
-// what that rounding left over, rounded to bf16 itself: the two together hold 16 bits of the value
-__device__ __forceinline__ bf16x8 pack8_rest(const float* v, bf16x8 hi) {
-  const uint4 h = __builtin_bit_cast(uint4, hi);
-  const unsigned w[4] = {h.x, h.y, h.z, h.w};
-  float d[8];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    d[2 * i] = v[2 * i] - __uint_as_float(w[i] << 16);
-    d[2 * i + 1] = v[2 * i + 1] - __uint_as_float(w[i] & 0xFFFF0000u);
-  }
-  return pack8(d);
-}
-// The second products' operand, 16 probabilities (or dS) of a lane: in one bf16 part or (HILO) in two.
-template <bool HILO>
+// The second products' operand, 16 probabilities (or dS) of a lane.  Rounded to bf16 once, or (EXACT) cut into three bf16
+// parts of 8 bits each that add up to the value itself: the products and sums are then those of fp32 operands.
+template <bool EXACT>
 struct Scores {
-  bf16x8 hi[2], lo[2];
+  static constexpr int PARTS = EXACT ? 3 : 1;
+  bf16x8 part[PARTS][2];
   __device__ __forceinline__ explicit Scores(const float (&v)[16]) {
+    if (!EXACT) {
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      hi[t] = pack8(v + 8 * t);
-      if (HILO) lo[t] = pack8_rest(v + 8 * t, hi[t]);
+      for (int t = 0; t < 2; ++t) part[0][t] = pack8(v + 8 * t);
+      return;
     }
+    float rest[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) rest[r] = v[r];
+#pragma unroll
+    for (int p = 0; p < PARTS; ++p)
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        unsigned w[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          float& x = rest[8 * t + 2 * i];
+          float& y = rest[8 * t + 2 * i + 1];
+          w[i] = __builtin_amdgcn_perm(__float_as_uint(y), __float_as_uint(x), 0x07060302u);   // the upper halves
+          x -= __uint_as_float(__float_as_uint(x) & 0xFFFF0000u);                             // (exact)
+          y -= __uint_as_float(__float_as_uint(y) & 0xFFFF0000u);
+        }
+        part[p][t] = __builtin_bit_cast(bf16x8, make_uint4(w[0], w[1], w[2], w[3]));
+      }
   }
-  // acc += tile rows 16 t .. of `x` times part t
+  // acc += tile rows 16 t .. of `x` times their scores
   __device__ __forceinline__ float16v times(bf16x8 x, int t, float16v acc) const {
-    acc = mfma(x, hi[t], acc);
-    if (HILO) acc = mfma(x, lo[t], acc);
+#pragma unroll
+    for (int p = 0; p < PARTS; ++p) acc = mfma(x, part[p][t], acc);
     return acc;
   }
 };
@@ -479,10 +488,9 @@ __device__ __forceinline__ Head head_of(const AttnArgs& a, unsigned p) {
   return hd;
 }
 
-// 64-wide heads (PAD = false) round P and dS to bf16 once for the second products; every other width had plain kernels
-// that keep them in fp32, so there they enter as two bf16 parts: the error against 64 bits is that of the
-// plain kernels (it is the results' own rounding), at twice the second products.
-template <int DHP, bool PAD> constexpr bool two_parts() { return !(DHP == 64 && !PAD); }
+// 64-wide heads (PAD = false) round P and dS to bf16 once for the second products; every other width is held to the plain
+// kernels, which keep them in fp32: there they enter whole, in three parts, at three times the second products.
+template <int DHP, bool PAD> constexpr bool exact_scores() { return !(DHP == 64 && !PAD); }
 
 // The three kernels share one shape.  A workgroup of four wavefronts owns four consecutive tiles of 32 queries
 // (dk/dv kernel: keys), one per wavefront, and streams the tiles of the other side through a ring of AT_NST buffer
@@ -494,7 +502,7 @@ template <int DHP, bool PAD> constexpr bool two_parts() { return !(DHP == 64 && 
 template <int DHP, bool PAD, bool CAUSAL>
 __global__ __launch_bounds__(64 * AT_WAVES, 2) void attn_fwd_mfma_kernel(AttnArgs a) {
   typedef Geo<DHP> G;
-  constexpr bool HILO = two_parts<DHP, PAD>();
+  constexpr bool EXACT = exact_scores<DHP, PAD>();
   __shared__ __attribute__((aligned(1024))) unsigned char smem[AT_NST][2][G::TB];   // [stage][k | v]
   __shared__ __attribute__((aligned(256))) unsigned char staging[AT_WAVES][2048];   // [wave]: results on their way out
   const int lane = threadIdx.x & 63, hh = lane >> 5;
@@ -576,7 +584,7 @@ __global__ __launch_bounds__(64 * AT_WAVES, 2) void attn_fwd_mfma_kernel(AttnArg
     for (int mb = 0; mb < G::MB; ++mb)
 #pragma unroll
       for (int r = 0; r < 16; ++r) o[mb][r] *= alpha;
-    const Scores<HILO> pq(sv);
+    const Scores<EXACT> pq(sv);
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
@@ -607,7 +615,7 @@ __global__ __launch_bounds__(64 * AT_WAVES, 2) void attn_fwd_mfma_kernel(AttnArg
 template <int DHP, bool PAD, bool CAUSAL>
 __global__ __launch_bounds__(64 * AT_WAVES, 2) void attn_bwd_q_mfma_kernel(AttnArgs a) {
   typedef Geo<DHP> G;
-  constexpr bool HILO = two_parts<DHP, PAD>();
+  constexpr bool EXACT = exact_scores<DHP, PAD>();
   __shared__ __attribute__((aligned(1024))) unsigned char smem[AT_NST][2][G::TB];   // [stage][k | v]
   __shared__ __attribute__((aligned(256))) unsigned char staging[AT_WAVES][2048];   // [wave]: results on their way out
   const int lane = threadIdx.x & 63, hh = lane >> 5;
@@ -701,7 +709,7 @@ __global__ __launch_bounds__(64 * AT_WAVES, 2) void attn_bwd_q_mfma_kernel(AttnA
       }
       ds[r] = pr * dp[r];
     }
-    const Scores<HILO> dq_s(ds);
+    const Scores<EXACT> dq_s(ds);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int t = 0; t < 2; ++t)
@@ -728,12 +736,13 @@ __global__ __launch_bounds__(64 * AT_WAVES, 2) void attn_bwd_q_mfma_kernel(AttnA
                    (long)q0 * hd.ld, hd.ld, T - q0, dq, a.scale, dh, staging[wave], lane);
 }
 
-// dk, dv of four tiles of 32 keys (after the dq kernel: reads D).  128-wide heads hold 128 accumulators and 64 operand
-// registers per lane: one workgroup per compute unit with all 512 registers; narrower ones fit three.
+// dk, dv of four tiles of 32 keys (after the dq kernel: reads D).  128-wide heads hold 128 accumulators and 32 operand
+// registers per lane, and the parts of two sets of scores: one workgroup per compute unit with all 512 registers; narrower
+// ones fit three, or two where the scores are in three parts of 64 columns (in three, 40 registers spill).
 template <int DHP, bool PAD, bool CAUSAL>
-__global__ __launch_bounds__(64 * AT_WAVES, DHP == 128 ? 1 : 3) void attn_bwd_kv_mfma_kernel(AttnArgs a) {
+__global__ __launch_bounds__(64 * AT_WAVES, DHP == 128 ? 1 : DHP == 64 && PAD ? 2 : 3) void attn_bwd_kv_mfma_kernel(AttnArgs a) {
   typedef Geo<DHP> G;
-  constexpr bool HILO = two_parts<DHP, PAD>();
+  constexpr bool EXACT = exact_scores<DHP, PAD>();
   __shared__ __attribute__((aligned(1024))) unsigned char smem[AT_NST][2][G::TB];   // [stage][q | do]
   __shared__ __attribute__((aligned(1024))) unsigned char own[AT_WAVES][G::TB];     // [wave]: the v rows of the wavefront's own keys
   __shared__ __attribute__((aligned(256))) float stats[AT_WAVES][AT_NST][64];       // [wave][stage][L2 | D] (a copy per wavefront)
@@ -822,7 +831,7 @@ __global__ __launch_bounds__(64 * AT_WAVES, DHP == 128 ? 1 : 3) void attn_bwd_kv
       }
       ds[r] = pr[r] * dp[r];
     }
-    const Scores<HILO> ps(pr), ss(ds);
+    const Scores<EXACT> ps(pr), ss(ds);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int mb = 0; mb < G::MB; ++mb)
@@ -869,7 +878,7 @@ __global__ __launch_bounds__(64 * AT_WAVES, DHP == 128 ? 1 : 3) void attn_bwd_kv
 template <int DHP, bool PAD, bool CAUSAL, int TPW>
 __global__ __launch_bounds__(256, DHP == 128 ? 1 : 2) void attn_bwd_short_mfma_kernel(AttnArgs a) {
   typedef Geo<DHP> G;
-  constexpr bool HILO = two_parts<DHP, PAD>();
+  constexpr bool EXACT = exact_scores<DHP, PAD>();
   constexpr int NT = 4 * TPW;
   __shared__ __attribute__((aligned(1024))) unsigned char tiles[2][NT][G::TB];  // [k | v], then [q | do]
   __shared__ __attribute__((aligned(256))) float stats[NT][64];                 // per tile: L2 of its 32 queries, then D
@@ -955,7 +964,7 @@ __global__ __launch_bounds__(256, DHP == 128 ? 1 : 2) void attn_bwd_short_mfma_k
         }
         ds[r] = pr * dp[r];
       }
-      const Scores<HILO> ss(ds);
+      const Scores<EXACT> ss(ds);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int u = 0; u < 2; ++u)
@@ -1026,7 +1035,10 @@ __global__ __launch_bounds__(256, DHP == 128 ? 1 : 2) void attn_bwd_short_mfma_k
 #pragma unroll
       for (int mb = 0; mb < G::MB; ++mb)
 #pragma unroll
-        for (int u = 0; u < 2; ++u) { tr[mb][u] = frag_rows_lds<DHP>(td, mb, u, lane); ur[mb][u] = frag_rows_lds<DHP>(tq, mb, u, lane); }
+        for (int u = 0; u < 2; ++u) {
+          tr[mb][u] = frag_rows_lds<DHP>(td, mb, u, lane);
+          if (!EXACT) ur[mb][u] = frag_rows_lds<DHP>(tq, mb, u, lane);
+        }
       __builtin_amdgcn_sched_barrier(0);
       float pr[16], ds[16];
 #pragma unroll
@@ -1038,12 +1050,31 @@ __global__ __launch_bounds__(256, DHP == 128 ? 1 : 2) void attn_bwd_short_mfma_k
         }
         ds[r] = pr[r] * dp[r];
       }
-      const Scores<HILO> ps(pr), ss(ds);
-      __builtin_amdgcn_sched_barrier(0);
+      const Scores<EXACT> ps(pr);
+      if (!EXACT) {
+        const Scores<EXACT> ss(ds);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int u = 0; u < 2; ++u)
+        for (int u = 0; u < 2; ++u)
 #pragma unroll
-        for (int mb = 0; mb < G::MB; ++mb) { dv[mb] = ps.times(tr[mb][u], u, dv[mb]); dk[mb] = ss.times(ur[mb][u], u, dk[mb]); }
+          for (int mb = 0; mb < G::MB; ++mb) { dv[mb] = ps.times(tr[mb][u], u, dv[mb]); dk[mb] = ss.times(ur[mb][u], u, dk[mb]); }
+      } else {                           // (one after the other: fewer live registers)
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int mb = 0; mb < G::MB; ++mb)
+#pragma unroll
+          for (int u = 0; u < 2; ++u) ur[mb][u] = frag_rows_lds<DHP>(tq, mb, u, lane);
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+          for (int mb = 0; mb < G::MB; ++mb) dv[mb] = ps.times(tr[mb][u], u, dv[mb]);
+        __builtin_amdgcn_sched_barrier(0);
+        const Scores<EXACT> ss(ds);
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+          for (int mb = 0; mb < G::MB; ++mb) dk[mb] = ss.times(ur[mb][u], u, dk[mb]);
+      }
     };
     int qt = CAUSAL ? tile[i] : 0;
     if (CAUSAL) { step(qt, std::true_type()); ++qt; }
