@@ -492,6 +492,115 @@ __device__ __forceinline__ Head head_of(const AttnArgs& a, unsigned p) {
 // kernels, which keep them in fp32: there they enter whole, in three parts, at three times the second products.
 template <int DHP, bool PAD> constexpr bool exact_scores() { return !(DHP == 64 && !PAD); }
 
+// Infinities and NaNs.  A product on the matrix cores meets every element of a tile, also those that the mask, the sequence's
+// end or the head's width leave out, and there 0 times an infinity is NaN; so are the second and third part of an infinite
+// score.  Where the scores are held whole, a row of a result that did not come out finite is therefore computed once more,
+// term by term over what it sees, as the plain kernels do: one wavefront, the columns over its lanes.  Finite data never
+// comes here; the test costs a product per accumulator and tile.
+template <int MB>
+__device__ __forceinline__ float not_finite(const float16v (&acc)[MB], float t) {     // NaN if any of them is not finite
+#pragma unroll
+  for (int m = 0; m < MB; ++m)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) t = fmaf(acc[m][r], 0.f, t);
+  return t;
+}
+// rows (bits) of this wavefront's tile in which a lane's t is NaN, rows_left of them
+__device__ __forceinline__ unsigned rows_to_redo(float t, int rows_left) {
+  const unsigned long long b = __ballot(t != t);
+  const unsigned rows = (unsigned)b | (unsigned)(b >> 32);
+  return rows_left < 32 ? rows & ((1u << rows_left) - 1u) : rows;
+}
+// out[c] += sum over 64 rows of w (lane j: row j) times column c of `rows`; a lane holds columns lane and lane + 64
+struct TwoColumns {
+  float v[2] = {0.f, 0.f};
+  __device__ __forceinline__ void add(float w, int n, const bf16_t* rows, long ld, int dh, int lane) {
+    for (int j = 0; j < n; ++j) {
+      const float wj = __shfl(w, j, 64);
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+        if (lane + 64 * u < dh) v[u] = fmaf(wj, Elem<bf16_t>::load(rows + j * ld + lane + 64 * u), v[u]);
+    }
+  }
+  __device__ __forceinline__ void store(bf16_t* out, float f, int dh, int lane) const {
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+      if (lane + 64 * u < dh) Elem<bf16_t>::store(out + lane + 64 * u, v[u] * f);
+  }
+};
+__device__ __forceinline__ void redo_fwd(const AttnArgs& a, const Head& hd, unsigned p, int i, int lane) {
+  const bf16_t* k = reinterpret_cast<const bf16_t*>(hd.k);
+  const bf16_t* q = reinterpret_cast<const bf16_t*>(hd.q) + i * hd.ld;
+  const int jn = a.causal ? i + 1 : (int)a.T;
+  const float c = a.scale * LOG2E;
+  float m = -INFINITY, sum = 0.f;
+  for (int j = lane; j < jn; j += 64) m = fmaxf(m, c * dot_rows(q, k + j * hd.ld, a.dh));
+  m = wave_max(m);
+  TwoColumns o;
+  for (int j0 = 0; j0 < jn; j0 += 64) {
+    float pr = 0.f;
+    if (j0 + lane < jn) {
+      pr = exp2f(c * dot_rows(q, k + (j0 + lane) * hd.ld, a.dh) - m);
+      sum += pr;
+    }
+    o.add(pr, jn - j0 < 64 ? jn - j0 : 64, k + j0 * hd.ld + hd.d, hd.ld, a.dh, lane);
+  }
+  sum = wave_sum(sum);
+#pragma unroll
+  for (int u = 0; u < 2; ++u) o.v[u] /= sum;
+  o.store(reinterpret_cast<bf16_t*>(reinterpret_cast<unsigned char*>(a.o) + hd.wide_off) + i * hd.d, 1.f, a.dh, lane);
+  if (lane == 0) a.lse[(long)p * a.T + i] = m + log2f(sum);
+}
+// D: of this query
+__device__ __forceinline__ void redo_q(const AttnArgs& a, const Head& hd, unsigned p, int i, float D, int lane) {
+  const bf16_t* k = reinterpret_cast<const bf16_t*>(hd.k);
+  const bf16_t* q = reinterpret_cast<const bf16_t*>(hd.q) + i * hd.ld;
+  const bf16_t* dout = reinterpret_cast<const bf16_t*>(reinterpret_cast<const unsigned char*>(a.dout) + hd.wide_off) + i * hd.d;
+  const int jn = a.causal ? i + 1 : (int)a.T;
+  const float c = a.scale * LOG2E, L2 = a.lse[(long)p * a.T + i];
+  TwoColumns dq;
+  for (int j0 = 0; j0 < jn; j0 += 64) {
+    float ds = 0.f;
+    if (j0 + lane < jn) {
+      const bf16_t* kj = k + (j0 + lane) * hd.ld;
+      ds = exp2f(c * dot_rows(q, kj, a.dh) - L2) * (dot_rows(dout, kj + hd.d, a.dh) - D);
+    }
+    dq.add(ds, jn - j0 < 64 ? jn - j0 : 64, k + j0 * hd.ld, hd.ld, a.dh, lane);
+  }
+  dq.store(reinterpret_cast<bf16_t*>(a.dqkv) + (q - reinterpret_cast<const bf16_t*>(a.qkv)), a.scale, a.dh, lane);
+}
+// D_of(i): D of query i
+template <typename F>
+__device__ __forceinline__ void redo_kv(const AttnArgs& a, const Head& hd, unsigned p, int j, F D_of, int lane) {
+  const bf16_t* q = reinterpret_cast<const bf16_t*>(hd.q);
+  const bf16_t* kj = reinterpret_cast<const bf16_t*>(hd.k) + j * hd.ld;
+  const bf16_t* dout = reinterpret_cast<const bf16_t*>(reinterpret_cast<const unsigned char*>(a.dout) + hd.wide_off);
+  const int T = (int)a.T;
+  const float c = a.scale * LOG2E;
+  TwoColumns dk, dv;
+  for (int i0 = a.causal ? j : 0; i0 < T; i0 += 64) {
+    float pr = 0.f, ds = 0.f;
+    const int i = i0 + lane, n = T - i0 < 64 ? T - i0 : 64;
+    if (i < T) {
+      pr = exp2f(c * dot_rows(q + i * hd.ld, kj, a.dh) - a.lse[(long)p * a.T + i]);
+      ds = pr * (dot_rows(dout + i * hd.d, kj + hd.d, a.dh) - D_of(i));
+    }
+    dk.add(ds, n, q + i0 * hd.ld, hd.ld, a.dh, lane);
+    dv.add(pr, n, dout + i0 * hd.d, hd.d, a.dh, lane);
+  }
+  bf16_t* out = reinterpret_cast<bf16_t*>(a.dqkv) + (kj - reinterpret_cast<const bf16_t*>(a.qkv));
+  dk.store(out, a.scale, a.dh, lane);
+  dv.store(out + hd.d, 1.f, a.dh, lane);
+}
+// f(row) for every row of the tile that came out not finite, after the tile's own stores
+template <typename F>
+__device__ __forceinline__ void redo_rows(float t, int rows_left, F f) {
+  unsigned rows = rows_to_redo(t, rows_left);
+  if (rows == 0) return;
+  copies_in_flight<0>();                                   // (stores too: what follows overwrites some of them)
+  for (; rows != 0; rows &= rows - 1) f(__ffs((int)rows) - 1);
+}
+
 // The three kernels share one shape.  A workgroup of four wavefronts owns four consecutive tiles of 32 queries
 // (dk/dv kernel: keys), one per wavefront, and streams the tiles of the other side through a ring of AT_NST buffer
 // pairs that all four read: at step t each wavefront waits for its own share of pair t, the workgroup meets at a
@@ -608,6 +717,7 @@ __global__ __launch_bounds__(64 * AT_WAVES, 2) void attn_fwd_mfma_kernel(AttnArg
     store_tile(reinterpret_cast<bf16_t*>(reinterpret_cast<unsigned char*>(a.o) + hd.wide_off) + (long)q0 * hd.d, hd.d, T - q0, o,
                1.f / l, dh, staging[wave], lane);
     if (hh == 0 && qi < T) a.lse[(long)p * a.T + qi] = m + log2f(l);
+    if (EXACT) redo_rows(not_finite(o, 0.f), T - q0, [&](int r) { redo_fwd(a, hd, p, q0 + r, lane); });
   }
 }
 
@@ -731,9 +841,11 @@ __global__ __launch_bounds__(64 * AT_WAVES, 2) void attn_bwd_q_mfma_kernel(AttnA
   for (; kt < n_plain; ++kt) { advance(kt); step(kt, std::false_type()); }
   if (kt < n_own) { advance(kt); step(kt, std::true_type()); ++kt; }
   for (; kt < nkt; ++kt) advance(kt);
-  if (live)
+  if (live) {
     store_tile(reinterpret_cast<bf16_t*>(reinterpret_cast<unsigned char*>(a.dqkv) + (hd.q - reinterpret_cast<const unsigned char*>(a.qkv))) +
                    (long)q0 * hd.ld, hd.ld, T - q0, dq, a.scale, dh, staging[wave], lane);
+    if (EXACT) redo_rows(not_finite(dq, 0.f), T - q0, [&](int r) { redo_q(a, hd, p, q0 + r, __shfl(D, r, 64), lane); });
+  }
 }
 
 // dk, dv of four tiles of 32 keys (after the dq kernel: reads D).  128-wide heads hold 128 accumulators and 32 operand
@@ -861,6 +973,9 @@ __global__ __launch_bounds__(64 * AT_WAVES, DHP == 128 ? 1 : DHP == 64 && PAD ? 
                     (long)k0 * hd.ld;
     store_tile(first, hd.ld, T - k0, dk, a.scale, dh, own[wave], lane);
     store_tile(first + hd.d, hd.ld, T - k0, dv, 1.f, dh, own[wave], lane);
+    if (EXACT)
+      redo_rows(not_finite(dv, not_finite(dk, 0.f)), T - k0,
+                [&](int r) { redo_kv(a, hd, p, k0 + r, [&](int i) { return a.dsum[(long)p * a.T + i]; }, lane); });
   }
 }
 
@@ -978,6 +1093,9 @@ __global__ __launch_bounds__(256, DHP == 128 ? 1 : 2) void attn_bwd_short_mfma_k
     if (kt < n_own) step(kt, std::true_type());
     store_tile(reinterpret_cast<bf16_t*>(reinterpret_cast<unsigned char*>(a.dqkv) + (hd.q - reinterpret_cast<const unsigned char*>(a.qkv))) +
                    (long)(32 * tile[i]) * hd.ld, hd.ld, T - 32 * tile[i], dq, a.scale, dh, staging[wave], lane);
+    if (EXACT)
+      redo_rows(not_finite(dq, 0.f), T - 32 * tile[i],
+                [&](int r) { redo_q(a, hd, p, 32 * tile[i] + r, __shfl(D[i], r, 64), lane); });
   }
   // 3. own k and v rows out of LDS, q and do rows into it
   bf16x8 fk[TPW][G::KK], fv[TPW][G::KK];
@@ -1085,6 +1203,9 @@ __global__ __launch_bounds__(256, DHP == 128 ? 1 : 2) void attn_bwd_short_mfma_k
                     (long)(32 * tile[i]) * hd.ld;
     store_tile(first, hd.ld, T - 32 * tile[i], dk, a.scale, dh, staging[wave], lane);
     store_tile(first + hd.d, hd.ld, T - 32 * tile[i], dv, 1.f, dh, staging[wave], lane);
+    if (EXACT)
+      redo_rows(not_finite(dv, not_finite(dk, 0.f)), T - 32 * tile[i],
+                [&](int r) { redo_kv(a, hd, p, 32 * tile[i] + r, [&](int n) { return stats[n >> 5][32 + (n & 31)]; }, lane); });
   }
 }
 

@@ -98,3 +98,129 @@ def test_backward_score_gradients(dh, heads, T, eps):
     dq, dk, dv = gradients(p, unit * 0, unit, v, do, torch.full((T,), BASE, device="cuda"))
     want = (T // 2) * 2.0 ** -BASE * bf(eps) / np.sqrt(dh)
     assert np.abs(dq[..., 0] / want - 1).max() < TOL, np.abs(dq[..., 0] / want - 1).max()
+
+
+# ---- infinities and NaNs reach what sees them, and nothing else: not what the mask, the sequence's end or a padded width leaves out ----
+WIDE = [(24, 2, 72), (32, 2, 100), (32, 2, 260), (40, 2, 40), (56, 2, 270), (104, 2, 100), (104, 2, 150), (128, 2, 130)]
+
+
+def heads_of(t, seqs, T, heads, parts):
+    """[N, parts d] -> parts x [seqs, heads, T, dh], float64"""
+    return np.moveaxis(t.double().cpu().numpy().reshape(seqs, T, parts, heads, -1), (2, 3), (0, 2))
+
+
+def visible(causal, i, T):
+    return slice(0, i + 1 if causal else T)
+
+
+def plain_forward(q, k, v, causal):
+    T, dh = q.shape
+    o, lse = np.empty_like(q), np.empty(T)
+    for i in range(T):
+        sl = visible(causal, i, T)
+        s = (k[sl] @ q[i]) / np.sqrt(dh)
+        m = np.fmax.reduce(s)
+        pr = np.exp(s - m)
+        o[i] = (pr[:, None] * v[sl]).sum(0) / pr.sum()
+        lse[i] = (m + np.log(pr.sum())) / np.log(2)
+    return o, lse
+
+
+def plain_backward(q, k, v, do, o, lse, causal):
+    T, dh = q.shape
+    dq, dk, dv = np.zeros_like(q), np.zeros_like(q), np.zeros_like(q)
+    for i in range(T):
+        sl = visible(causal, i, T)
+        pr = np.exp2((k[sl] @ q[i]) / np.sqrt(dh) / np.log(2) - lse[i])
+        ds = pr * (v[sl] @ do[i] - (do[i] * o[i]).sum())
+        dq[i] = (ds[:, None] * k[sl]).sum(0) / np.sqrt(dh)
+        dk[sl] += ds[:, None] * q[i] / np.sqrt(dh)
+        dv[sl] += pr[:, None] * do[i]
+    return dq, dk, dv
+
+
+def assert_same(got, want, what):
+    assert np.array_equal(np.isnan(got), np.isnan(want)), f"{what}: NaN"
+    inf = np.isinf(want)
+    assert np.array_equal(np.isinf(got), inf) and np.array_equal(got[inf], want[inf]), f"{what}: infinities"
+    m = np.isfinite(want)
+    assert np.linalg.norm(got[m] - want[m]) <= 1e-2 * np.linalg.norm(want[m]) + 1e-30, what
+
+
+@pytest.mark.parametrize("plant", ["nan", "inf_value", "inf_key"])
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("dh,heads,T", WIDE)
+def test_forward_with_infinities(dh, heads, T, causal, plant):
+    S, d = 2, dh * heads
+    p = block(dh, heads, T, seqs=S, causal=causal)
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    p.x[0] = torch.randn((S * T, d), generator=gen, device="cuda")
+    p.Wqkv[0] = torch.randn((3 * d, d), generator=gen, device="cuda") * (0.7 / np.sqrt(d))
+    # column 0 of the input overflows one column of one head: the last one, of the values or of the keys
+    p.x[0, :, 0] = 0
+    p.Wqkv[0, :, 0] = 0
+    last = dh - 1                                  # (of the first head)
+    if plant == "inf_key":                         # minus infinity against a positive query: a probability of zero
+        p.Wqkv[0, last] = 0
+        p.x[0, :, 1] = 1
+        p.Wqkv[0, :, 1] = 0
+        p.Wqkv[0, last, 1] = 1
+    p.Wqkv[0, (2 * d if plant == "inf_value" else d) + last, 0] = -100
+    t = T - 3
+    if plant == "nan":
+        p.x[0, t] = float("nan")
+    else:
+        p.x[0, t, 0] = 2e38
+    B.hbp_forward(p)
+    q, k, v = heads_of(p.qkv[0], S, T, heads, 3)
+    assert not np.isfinite(k if plant == "inf_key" else v).all()
+    got = heads_of(p.attn_o[0], S, T, heads, 1)[0]
+    lse = p.lse[0].double().cpu().numpy().reshape(S, heads, T)
+    with np.errstate(invalid="ignore"):
+        for s in range(S):
+            for h in range(heads):
+                o, L = plain_forward(q[s, h], k[s, h], v[s, h], causal)
+                assert_same(got[s, h], o, f"o, sequence {s}, head {h}")
+                assert_same(lse[s, h], L, f"lse, sequence {s}, head {h}")
+
+
+@pytest.mark.parametrize("plant", ["nan_value", "inf_value", "inf_key", "inf_query", "nan_gradient"])
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("dh,heads,T", WIDE)
+def test_backward_with_infinities(dh, heads, T, causal, plant):
+    """By token: the product with Wqkv carries what is not finite to all columns of its row."""
+    S, d = 2, dh * heads
+    p = block(dh, heads, T, seqs=S, causal=causal)
+    gen = torch.Generator(device="cuda").manual_seed(2)
+    p.Wqkv[0] = torch.eye(d, device="cuda").repeat(3, 1)
+    qkv = torch.randn((S * T, 3 * d), generator=gen, device="cuda").bfloat16()
+    qkv[:, dh - 1] = qkv[:, dh - 1].abs() + 0.25
+    do = torch.randn((S * T, d), generator=gen, device="cuda").bfloat16()
+    q, k, v = heads_of(qkv, S, T, heads, 3)
+    of = [[plain_forward(q[s, h], k[s, h], v[s, h], causal) for h in range(heads)] for s in range(S)]      # (of finite data)
+    o = torch.from_numpy(np.stack([[x[0] for x in r] for r in of])).permute(0, 2, 1, 3).reshape(S * T, d)
+    p.attn_o[0] = o.to("cuda")
+    p.lse[0] = torch.from_numpy(np.stack([[x[1] for x in r] for r in of]).reshape(-1)).to("cuda")
+    t = T - 3
+    col = {"inf_value": 2 * d, "inf_key": d, "inf_query": 0}
+    if plant == "nan_value":
+        qkv[t, 2 * d:] = float("nan")
+    elif plant == "nan_gradient":
+        do[t] = float("nan")
+    else:
+        qkv[t, col[plant] + dh - 1] = -float("inf")
+    p.qkv[0], p.e[:] = qkv, do
+    B.hbp_exact_backward(p)
+    q, k, v = heads_of(qkv, S, T, heads, 3)
+    g, oo = heads_of(do, S, T, heads, 1)[0], heads_of(p.attn_o[0], S, T, heads, 1)[0]
+    lse = p.lse[0].double().cpu().numpy().reshape(S, heads, T)
+    want = np.zeros((S, heads, T, dh))
+    with np.errstate(invalid="ignore"):
+        for s in range(S):
+            for h in range(heads):
+                want[s, h] = g[s, h] + sum(plain_backward(q[s, h], k[s, h], v[s, h], g[s, h], oo[s, h], lse[s, h], causal))
+    want = want.transpose(0, 2, 1, 3).reshape(S * T, d)
+    got = p.g[0].double().cpu().numpy()
+    bad = ~np.isfinite(want).all(1)
+    assert np.array_equal(~np.isfinite(got).all(1), bad), (np.flatnonzero(bad), np.flatnonzero(~np.isfinite(got).all(1)))
+    assert np.linalg.norm(got[~bad] - want[~bad]) <= 1e-2 * np.linalg.norm(want[~bad]) + 1e-30
