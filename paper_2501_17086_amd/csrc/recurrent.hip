@@ -63,17 +63,18 @@ struct Weights {
 };
 
 // The exchanged vectors of a launch: unit u, step slot, group, 16-row tile, block of 32 channels -> 1 KB, in which row r
-// and channels 8 q .. 8 q + 7 of the block are the 16 bytes of lane 16 q + r.
+// and channels 8 q .. 8 q + 7 of the block are the 16 bytes of lane 16 q + r; behind them 1 KB of zeros.
 struct Ring {
   char* base;
   int wpg, groups, rts, group;
   __device__ __forceinline__ unsigned at(int u, long step, int rt, int block) const {
     return (unsigned)((((u * REC_SLOTS + (int)(step & (REC_SLOTS - 1))) * groups + group) * rts + rt) * wpg + block) * 1024u;
   }
+  __device__ __forceinline__ unsigned zeros() const { return (unsigned)(REC_UNITS * REC_SLOTS * groups * rts * wpg) * 1024u; }
 };
 
-// This wavefront's operands of 16 RT rows out of a vector: its quarter of the blocks (past the last one: that one again,
-// its weights are zero).
+// This wavefront's operands of 16 RT rows out of a vector: its quarter of the blocks.  Past the last one it reads zeros: the
+// weights there are zeros too, but against a repeated block they would turn an infinity of its into NaN.
 template <int KQ, int RT>
 struct Operand {
   bf16x8 a[RT][KQ];
@@ -81,7 +82,7 @@ struct Operand {
   __device__ __forceinline__ void load(const Ring& ring, int u, long step, int wave, int lane, bool& dead) {
     typedef unsigned uint4v __attribute__((ext_vector_type(4)));
     const __amdgpu_buffer_rsrc_t rsrc =
-        __builtin_amdgcn_make_buffer_rsrc(ring.base, 0, REC_UNITS * REC_SLOTS * ring.groups * RT * ring.wpg * 1024, 0x00027000);
+        __builtin_amdgcn_make_buffer_rsrc(ring.base, 0, ring.zeros() + 1024, 0x00027000);
     for (int spins = 0;; ++spins) {
       uint4v q[RT][KQ];
       asm volatile("" ::: "memory");           // (every pass reads again)
@@ -89,9 +90,9 @@ struct Operand {
       for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
         for (int s = 0; s < KQ; ++s) {
-          const int kb = wave * KQ + s < ring.wpg ? wave * KQ + s : ring.wpg - 1;
+          const int kb = wave * KQ + s;
           // (a plain 16-byte load at device scope: sc1; every 4-byte word of it is either empty or whole)
-          q[rt][s] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane * 16, (int)ring.at(u, step, rt, kb), 16);
+          q[rt][s] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane * 16, (int)(kb < ring.wpg ? ring.at(u, step, rt, kb) : ring.zeros()), 16);
         }
       unsigned top = 0;
 #pragma unroll
@@ -536,10 +537,11 @@ __global__ __launch_bounds__(256, 1) void rec_backward_kernel(RecArgs a, int wpg
   }
 }
 
-// the empty word into every slot, and the counter at zero
+// the empty word into every slot (n 16-byte pieces), zeros into the block behind them, and the counter at zero
 __global__ __launch_bounds__(256) void rec_fill_kernel(uint4* p, long n, int* counter) {
   const long i = (long)blockIdx.x * 256 + threadIdx.x;
-  if (i < n) p[i] = make_uint4(REC_EMPTY, REC_EMPTY, REC_EMPTY, REC_EMPTY);
+  const unsigned w = i < n ? REC_EMPTY : 0u;
+  if (i < n + 64) p[i] = make_uint4(w, w, w, w);
   if (i == 0) *counter = 0;
 }
 
@@ -558,7 +560,7 @@ hipError_t launch_rec(const RecArgs& a, bool forward, hipStream_t s) {
   const long wpg = (rec_width(a) + REC_COLS - 1) / REC_COLS;
   const long wgs = (a.N + 16 * RT - 1) / (16 * RT) * wpg;
   const long n16 = REC_UNITS * REC_SLOTS * wgs * RT * 64;
-  hipLaunchKernelGGL(rec_fill_kernel, dim3((unsigned)((n16 + 255) / 256)), dim3(256), 0, s, reinterpret_cast<uint4*>(a.ring), n16,
+  hipLaunchKernelGGL(rec_fill_kernel, dim3((unsigned)((n16 + 64 + 255) / 256)), dim3(256), 0, s, reinterpret_cast<uint4*>(a.ring), n16,
                      a.counter);
   if (forward) hipLaunchKernelGGL((rec_forward_kernel<KIND, KQ, RT>), dim3((unsigned)wgs), dim3(256), 0, s, a, (int)wpg);
   else hipLaunchKernelGGL((rec_backward_kernel<KIND, KQ, RT>), dim3((unsigned)wgs), dim3(256), 0, s, a, (int)wpg);
@@ -578,7 +580,7 @@ hipError_t launch_rec_kind(const RecArgs& a, bool forward, hipStream_t s) {
 
 }  // namespace
 
-size_t recurrent_ring_bytes() { return (size_t)REC_UNITS * REC_SLOTS * REC_MAX_WG * 2 * 1024; }
+size_t recurrent_ring_bytes() { return (size_t)REC_UNITS * REC_SLOTS * REC_MAX_WG * 2 * 1024 + 1024; }
 // What fits: bf16, widths whose weights the registers hold (1024) and at most 64 workgroups (two row tiles each: 64 rows at
 // width 1024, 128 at 512).  Everything else goes step by step (7 us per product against 1.6).
 bool recurrent_ok(const RecArgs& a) {

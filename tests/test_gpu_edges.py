@@ -3,6 +3,7 @@ call, and the sizes at which a dispatch changes kernels.  Same oracle and bars a
 import numpy as np
 import pytest
 
+from oracle import hbp_oracle as O
 from paper_2501_17086_amd import synth
 from tests import helpers as H
 from tests.test_gpu_parity import B, W, _check_backward, _setup  # noqa: F401  (B is the fixture)
@@ -92,6 +93,43 @@ def test_chains_along_time_with_nan_rows_and_on_two_streams(B, kind):
     keep = [n for n in range(w.N) if n != 3]
     assert torch.equal(p.x[:, keep], q.x[:, keep]) and torch.equal(p.g[:, keep], q.g[:, keep])
     assert bool(q.x[1:, 3].isnan().all()) and not bool(p.x.isnan().any())
+
+
+# An infinity in the last block of 32 channels, at widths whose quarters of the contraction reach past it: saturated gates
+# stay finite, and gradients are infinite, not NaN.  One step, so that what follows does not mix the two.
+@pytest.mark.parametrize("kind", ["rnn", "token", "gated", "lstm", "gru"])
+@pytest.mark.parametrize("H_", [24, 72, 264, 600])
+def test_chains_along_time_with_infinities(B, kind, H_):
+    import torch
+    w = _chain(kind, 1, 5, H_)
+    inp, st, _, p = _setup(B, w)
+    c = w.d - 3                                    # (the LSTM's hidden part comes second)
+    inp["x0"][2, c] = np.inf
+    p.x[0, 2, c] = float("inf")
+    # positive weights of that channel: what it meets saturates upwards, the standard GRU's reset gate among it
+    col = H_ - 3
+    inp["W1"][:, col] = np.abs(inp["W1"][:, col]) + 2.0 ** -7
+    p.W1.copy_(torch.from_numpy(inp["W1"]))
+    st = H.oracle_stack(w, inp)
+    with np.errstate(invalid="ignore", over="ignore"):
+        sv = O.forward(st, inp["x0"], inp["xin"])
+        B.hbp_forward(p)
+        _same_numbers(H.to_np(p.x)[1], sv["x"][1], f"{w.name} x[1]")
+        # backward on a finite state
+        inp["x0"][2, c], p.x[0, 2, c] = 0, 0
+        sv = O.forward(st, inp["x0"], inp["xin"])
+        B.hbp_forward(p)
+        inp["e"][1, 2, c] = np.inf
+        p.e[1, 2, c] = float("inf")
+        B.hbp_exact_backward(p)
+        _same_numbers(H.to_np(p.g)[0], O.exact_backward(st, sv, inp["e"])[0], f"{w.name} g[0]")
+
+
+def _same_numbers(got, want, what):
+    assert np.array_equal(np.isnan(got), np.isnan(want)), f"{what}: NaN"
+    inf = np.isinf(want)
+    assert np.array_equal(np.isinf(got), inf) and np.array_equal(got[inf], want[inf]), f"{what}: infinities"
+    H.assert_close(np.where(np.isfinite(want), got, 0), np.where(np.isfinite(want), want, 0), H.TOL["bf16"], what)
 
 
 # fp32 products: around the 32- and 64-wide tiles, contractions that end inside a chunk of 32 or leave a wavefront's
