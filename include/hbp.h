@@ -39,8 +39,9 @@
  *    workspace smaller than hbp_workspace_size() reports.  A failed launch
  *    gives HBP_E_DEVICE.
  *  - The recurrent kinds' forward pass and exact backpropagation run a whole chain in one launch (bf16, no norm, widths
- *    up to 1024, batches of up to 64 rows at that width): at most 64 workgroups that wait for each other's results.
- *    Up to four such launches may overlap on one GPU.
+ *    up to 1024, batches of up to 64 rows at that width): at most 64 workgroups, of which up to 32 wait for each other's
+ *    results.  Any number of such calls may overlap.  Where 32 workgroups do not get to run side by side for a long time
+ *    (other work holds the GPU), one of them computes the chain alone: the same results, at 0.1 to 0.4 ms a step.
  *  - State between calls: none that changes results.  The library keeps (a) a
  *    flag per kernel and device saying that the kernel's shared-memory limit
  *    has been raised (set on the first launch, idempotent, safe from several

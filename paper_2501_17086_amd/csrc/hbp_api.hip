@@ -120,9 +120,9 @@ Workspace carve(const hbp_desc* d) {
   if (tfm(d)) o = align_up(o + (size_t)(d->L / 2) * d->N * 3 * d->d * es, 256);
   w.off_dsum = o;
   if (tfm(d)) o = align_up(o + (size_t)(d->L / 2) * d->N * d->heads * 4, 256);
-  // the chain kernels' start counter and what their workgroups exchange (2 MB)
+  // the chain kernels' counters and what their workgroups exchange (2 MB)
   w.off_counter = o;
-  if (recurrent(d) && d->dtype == HBP_BF16) o += 256 + recurrent_ring_bytes();
+  if (recurrent(d) && d->dtype == HBP_BF16) o += RECURRENT_COUNTER_BYTES + recurrent_ring_bytes();
   w.total = o;
   return w;
 }
@@ -686,7 +686,7 @@ bool rec_args(const hbp_desc* d, const hbp_buffers* b, const Workspace& w, bool 
   a.lambda_tok = d->lambda_kind == HBP_LAMBDA_TOKEN ? b->lambda : nullptr;
   a.tanh_act = d->act == HBP_ACT_TANH;
   a.counter = reinterpret_cast<int*>(at(b->workspace, w.off_counter));
-  a.ring = at(b->workspace, w.off_counter + 256);
+  a.ring = at(b->workspace, w.off_counter + RECURRENT_COUNTER_BYTES);
   if (forward) {
     a.ux = reinterpret_cast<const float*>(at((const void*)b->workspace, w.off_da));
     a.W1 = b->W1; a.W2 = b->W2;
@@ -706,9 +706,9 @@ bool rec_args(const hbp_desc* d, const hbp_buffers* b, const Workspace& w, bool 
   *out = a;
   return true;
 }
-}  // namespace
 
-hbp_status hbp_forward(const hbp_desc* d, hbp_buffers* b, void* stream) {
+// wait: of RecArgs
+hbp_status run_forward(const hbp_desc* d, hbp_buffers* b, void* stream, int wait) {
   HBP_RUN(check_desc(d));
   HBP_RUN(check_bufs(d, b, NEED_FWD));
   hipStream_t s = (hipStream_t)stream;
@@ -731,6 +731,7 @@ hbp_status hbp_forward(const hbp_desc* d, hbp_buffers* b, void* stream) {
   {
     RecArgs ra;
     if (rec_args(d, b, w, true, &ra)) {
+      ra.wait = wait;
       ProfScope ps(HBP_PROF_FORWARD, s);
       HBP_TRY(launch_recurrent(ra, true, s));
       return HBP_OK;
@@ -931,6 +932,10 @@ hbp_status hbp_forward(const hbp_desc* d, hbp_buffers* b, void* stream) {
   return HBP_OK;
 }
 
+}  // namespace
+
+hbp_status hbp_forward(const hbp_desc* d, hbp_buffers* b, void* stream) { return run_forward(d, b, stream, REC_WAIT); }
+
 hbp_status hbp_backward(const hbp_desc* d, int k, hbp_buffers* b, void* stream) {
   HBP_RUN(check_desc(d));
   if (k < 0) return HBP_E_INVALID_ARG;
@@ -1063,7 +1068,8 @@ hbp_status hbp_initial_estimate_static(const hbp_desc* d, hbp_buffers* b, void* 
   return HBP_OK;
 }
 
-hbp_status hbp_exact_backward(const hbp_desc* d, hbp_buffers* b, void* stream) {
+namespace {
+hbp_status run_exact_backward(const hbp_desc* d, hbp_buffers* b, void* stream, int wait) {
   HBP_RUN(check_desc(d));
   HBP_RUN(check_bufs(d, b, NEED_BWD));
   hipStream_t s = (hipStream_t)stream;
@@ -1099,6 +1105,7 @@ hbp_status hbp_exact_backward(const hbp_desc* d, hbp_buffers* b, void* stream) {
                                   (int)hidden_w(d), s));
   }
   if (chain) {
+    ra.wait = wait;
     ProfScope ps(HBP_PROF_VJP1, s);
     HBP_TRY(launch_recurrent(ra, false, s));
     return HBP_OK;
@@ -1109,6 +1116,14 @@ hbp_status hbp_exact_backward(const hbp_desc* d, hbp_buffers* b, void* stream) {
     if (!fuse) HBP_RUN(scan_stage(d, &bb, w, l, l + 1, true, s, 0.f, 0, 0, true));
   }
   return HBP_OK;
+}
+}  // namespace
+
+hbp_status hbp_exact_backward(const hbp_desc* d, hbp_buffers* b, void* stream) { return run_exact_backward(d, b, stream, REC_WAIT); }
+
+// For tests, not part of the interface: hbp_forward (or hbp_exact_backward) with another wait of RecArgs.
+__attribute__((visibility("default"))) hbp_status hbp_internal_chains(const hbp_desc* d, int forward, int wait, hbp_buffers* b, void* stream) {
+  return forward ? run_forward(d, b, stream, wait) : run_exact_backward(d, b, stream, wait);
 }
 
 hbp_status hbp_param_grads(const hbp_desc* d, hbp_buffers* b, void* stream) {

@@ -215,9 +215,13 @@ struct RecArgs {
   const void* e;        // backward: [L+1,N,D] added per state, or NULL
   const void* dphi;     // backward (RNN): act' [L,N,F]; NULL: 1 - z^2 with tanh_act, else 1
   int tanh_act;         // RNN: tanh, else the identity
-  int* counter;         // device scratch, one word
+  int* counter;         // device scratch, RECURRENT_COUNTER_BYTES
   void* ring;           // device scratch, recurrent_ring_bytes()
+  int wait;             // for the rest of a group to start: REC_WAIT, or (tests) REC_WAIT_NOT: give up at the first look,
+                        // REC_ALONE_ANYHOW: every group's first workgroup goes on alone
 };
+enum { REC_WAIT = 0, REC_WAIT_NOT = 1, REC_ALONE_ANYHOW = 2 };
+constexpr size_t RECURRENT_COUNTER_BYTES = 512;
 size_t recurrent_ring_bytes();
 bool recurrent_ok(const RecArgs& a);
 hipError_t launch_recurrent(const RecArgs& a, bool forward, hipStream_t s);

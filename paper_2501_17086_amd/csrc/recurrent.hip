@@ -17,11 +17,14 @@
 //     for its own reads, which a wavefront's earlier stores (the emptying among them) precede;
 //   - the four quarters of a product are added through LDS (one workgroup barrier per product), and the elementwise
 //     part of the cell runs on the sums, two channels of a row per thread, the state staying in registers.
-// Workgroups take their place in a group in the order they start (a device counter), so that one group of a launch at
-// most is incomplete at any time, and at most 64 are launched, a quarter of the compute units: four such launches on
-// streams of their own (the runtime's four hardware queues) fit the chip side by side, and every workgroup that is waited
-// for runs.  The waits are bounded all the same: after REC_SPIN_LIMIT polls a workgroup gives up for good and goes on with
-// the NaNs it read, so that a broken run is loud and the kernel ends.
+// Workgroups take their place in a group in the order they start (a device counter), and a group begins once all of its
+// workgroups have started: from then on each of them keeps running, so that every wait inside the chain ends.  One group of a
+// launch at most is incomplete at any time, and at most 64 workgroups are launched, a quarter of the compute units, so that
+// this is soon the case.  Where it is not, because other kernels hold the compute units, or incomplete groups of many launches
+// (nine or more) hold all of them against each other, a group that has waited for REC_ARRIVE_POLLS polls per step, about as
+// long as the chain takes one workgroup, is left to its first workgroup alone, and the others end.  That one plays all of them in
+// turn, with the same phases, sums and exchange, reading the weights from memory at every step: the same results bit for bit at
+// 0.1 to 0.4 ms a step (width 1024: 60 to 90 times the time of the group).
 //
 // Measured (1024 steps, batch 32, width 1024): exact backpropagation of the RNN 14.5 -> 3.3 ms, forward of the GRU 20.9 ->
 // 3.7 ms; 1.6 us per dependent product, of which 0.3 us are waiting for data that is not there yet: the rest is one
@@ -38,7 +41,9 @@ typedef float float4v __attribute__((ext_vector_type(4)));
 
 constexpr unsigned REC_EMPTY = 0xFFFFFFFFu;    // two bf16 NaNs of a pattern that publish() never stores
 constexpr int REC_SLOTS = 4;                   // steps a vector's slots are deep
-constexpr int REC_SPIN_LIMIT = 1 << 24;
+constexpr int REC_SPIN_LIMIT = 1 << 24;        // polls inside the chain (bounded only so that a fault elsewhere cannot hang it)
+constexpr int REC_ARRIVE_POLLS = 256;          // polls per step for the rest of a group to start
+constexpr unsigned REC_ALONE = 1u << 31;       // in a group's word beside the number of workgroups that have started
 constexpr int REC_COLS = 32;                   // channels per workgroup
 constexpr int REC_MAX_WG = 64;
 constexpr int REC_UNITS = 4;                   // exchanged vectors at most
@@ -184,222 +189,305 @@ __device__ __forceinline__ float sigmoid1(float a) { return 1.f / (1.f + expf(-a
 
 enum { K_RNN = 0, K_GATED = 1, K_LSTM = 2, K_GRU = 3 };
 
-// this workgroup's group and member number, in the order of starting
-__device__ __forceinline__ void take_number(int* counter, int wpg, int& group, int& member) {
-  __shared__ int number;
-  if (threadIdx.x == 0) number = atomicAdd(counter, 1);
+// This workgroup's group and member number, in the order of starting; true once the whole group has started, false if its first
+// member is to go on alone.  The counter of the launch, then a word per group.  (One thread divides by wpg, in vector registers;
+// the kernels do not divide by it again, for the compiler would take this quotient's reciprocal there, leave the result in a
+// vector register and put every operand load whose address depends on it into a loop over the lanes: 11 % on the GRU.)
+__device__ __forceinline__ bool take_place(const RecArgs& a, int wpg, int& group, int& member) {
+  __shared__ int place[3];
+  if (threadIdx.x == 0) {
+    const int n = atomicAdd(a.counter, 1), limit = a.wait != REC_WAIT ? 0 : a.L < REC_SPIN_LIMIT / REC_ARRIVE_POLLS ? (int)a.L * REC_ARRIVE_POLLS : REC_SPIN_LIMIT;
+    const int g = n / wpg;
+    unsigned* word = reinterpret_cast<unsigned*>(a.counter) + 1 + g;
+    unsigned w = atomicAdd(word, 1u) + 1u;
+    for (int polls = 0; !(w & REC_ALONE) && w != (unsigned)wpg; ++polls) {
+      if (polls < limit) {
+        __builtin_amdgcn_s_sleep(8);
+        w = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      } else {                           // (fails only where another workgroup has started, or given up, in between)
+        const unsigned was = atomicCAS(word, w, w | REC_ALONE);
+        w = was == w ? w | REC_ALONE : was;
+      }
+    }
+    place[0] = g;
+    place[1] = n - g * wpg;
+    place[2] = (w & REC_ALONE) != 0;
+  }
   __syncthreads();
-  const int n = __builtin_amdgcn_readfirstlane(number);
-  group = n / wpg;
-  member = n - group * wpg;
+  group = __builtin_amdgcn_readfirstlane(place[0]);
+  member = __builtin_amdgcn_readfirstlane(place[1]);
+  return __builtin_amdgcn_readfirstlane(place[2]) == 0;
 }
 
-template <int KIND, int KQ, int RT>
-__global__ __launch_bounds__(256, 1) void rec_forward_kernel(RecArgs a, int wpg) {
-  constexpr int SLOTS = KIND == K_LSTM ? 4 : KIND == K_RNN ? 1 : 2;
+// Which channels and rows a thread has in the elementwise part: two channels (from c on) of RT rows.
+template <int RT>
+struct Place {
+  int row[RT];            // (past the batch: its last row, nothing of it is stored)
+  int c;
+  bool on[RT], on_f[RT];  // inside the state, inside the inner state
+  __device__ __forceinline__ void set(int group, int member, int N, int width, int width_f) {
+    c = member * REC_COLS + 8 * (threadIdx.x >> 6) + 2 * (threadIdx.x & 3);
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) {
+      const int r = group * 16 * RT + 16 * rt + ((threadIdx.x >> 2) & 15);
+      on[rt] = r < N && c < width;
+      on_f[rt] = r < N && c < width_f;
+      row[rt] = r < N ? r : N - 1;
+    }
+  }
+};
+// f(member): this workgroup's own, or (ALONE) all of the group's in turn
+template <bool ALONE, typename F>
+__device__ __forceinline__ void members(int own, int wpg, F f) {
+  if (!ALONE) { f(own); return; }
+#pragma unroll 1
+  for (int m = 0; m < wpg; ++m) f(m);
+}
+
+// ALONE: one workgroup plays every member of its group; what a member keeps in registers from phase to phase it reads again
+// (the thread that wrote it reads it).
+template <int KIND, int KQ, int RT, bool ALONE, int SLOTS>
+__device__ __forceinline__ void forward_chain(const RecArgs& a, const Ring& ring, int own, Partials<RT, SLOTS>& part) {
   constexpr int UNITS = KIND == K_LSTM ? 4 : KIND == K_GRU ? 3 : 2;
-  __shared__ __attribute__((aligned(16))) Partials<RT, SLOTS> part;
+  constexpr bool TWO = KIND == K_RNN || KIND == K_GRU;       // two dependent products per step
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  int group, member;
-  take_number(a.counter, wpg, group, member);
-  const Ring ring = {reinterpret_cast<char*>(a.ring), wpg, (int)gridDim.x / wpg, RT, group};
-  const int row0 = group * 16 * RT, col0 = member * REC_COLS;
   const int N = (int)a.N, H = (int)a.H, F = (int)a.F, D = (int)a.D;
-  Weights<KQ> w[UNITS];
+  Weights<KQ> w[ALONE ? 1 : UNITS];
+  auto weights = [&](int u, int member) __attribute__((always_inline)) -> Weights<KQ>& {
+    Weights<KQ>& t = w[ALONE ? 0 : u];
+    const int col0 = member * REC_COLS;
+    if (KIND == K_RNN && u == 1) t.load((const bf16_t*)a.W2, F, col0, D, F, wave, lane);
+    else t.load((const bf16_t*)a.W1 + (KIND == K_RNN ? 0 : (long)u * H * H), H, col0, KIND == K_RNN ? F : H, H, wave, lane);
+    return t;
+  };
+  if (!ALONE) {
 #pragma unroll
-  for (int u = 0; u < UNITS; ++u) {
-    if (KIND == K_RNN && u == 1) w[u].load((const bf16_t*)a.W2, F, col0, D, F, wave, lane);
-    else w[u].load((const bf16_t*)a.W1 + (KIND == K_RNN ? 0 : (long)u * H * H), H, col0, KIND == K_RNN ? F : H, H, wave, lane);
+    for (int u = 0; u < UNITS; ++u) weights(u, own);
   }
   Operand<KQ, RT> in;
   // exchanged: unit 0 the (hidden) state, unit 1 the RNN's inner state or the GRU's r (.) x
   // this thread's share of the elementwise part: two channels of RT rows
-  const int my_row = (tid >> 2) & 15, my_col = 8 * (tid >> 6) + 2 * (tid & 3), c = col0 + my_col;
-  int row[RT];
-  bool on[RT], on_f[RT];
+  const int my_row = (tid >> 2) & 15, my_col = 8 * (tid >> 6) + 2 * (tid & 3);
+  Place<RT> at;
   float2 xs[RT];                     // the state's (LSTM: the cell's) two channels, as stored
-#pragma unroll
-  for (int rt = 0; rt < RT; ++rt) {
-    const int r = row0 + 16 * rt + my_row;
-    on[rt] = r < N && c < (KIND == K_RNN ? D : H);
-    on_f[rt] = r < N && c < (KIND == K_RNN ? F : H);
-    row[rt] = r < N ? r : N - 1;
-    xs[rt] = on[rt] ? un2(ld2((const bf16_t*)a.x + (long)row[rt] * D + c)) : make_float2(0.f, 0.f);
-    publish(ring, 0, 0, rt, member, on[rt] ? ld2((const bf16_t*)a.x + (long)row[rt] * D + (KIND == K_LSTM ? H : 0) + c) : 0u);
-  }
-  bool dead = false;
-  int set = 0;
   const long sx = (long)N * D, sf = (long)N * F;
   bf16_t* x = (bf16_t*)a.x;
   bf16_t* z = (bf16_t*)a.z;
   bf16_t* lam = (bf16_t*)a.lambda_tok;
+  auto place = [&](int member) __attribute__((always_inline)) {      // where the member's channels are, and its state at this step
+    at.set(ring.group, member, N, KIND == K_RNN ? D : H, KIND == K_RNN ? F : H);
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) xs[rt] = at.on[rt] ? un2(ld2(x + (long)at.row[rt] * D + at.c)) : make_float2(0.f, 0.f);
+  };
+  members<ALONE>(own, ring.wpg, [&](int member) __attribute__((always_inline)) {
+    place(member);
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+      publish(ring, 0, 0, rt, member, at.on[rt] ? ld2(x + (long)at.row[rt] * D + (KIND == K_LSTM ? H : 0) + at.c) : 0u);
+  });
+  bool dead = false;
+  int set = 0;
 #pragma unroll 1
   for (long l = 0; l < a.L; ++l, x += sx, z += sf) {
-    // what does not depend on the step before is on its way while the operands are waited for
     float2 ux[RT][SLOTS], un[RT], lm[RT];
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt) {
-#pragma unroll
-      for (int q = 0; q < SLOTS; ++q)
-        ux[rt][q] = on_f[rt] ? ldf2(a.ux + l * sf + (long)row[rt] * F + (KIND == K_RNN ? 0 : q * H) + c) : make_float2(0.f, 0.f);
-      if (KIND == K_GRU) un[rt] = on[rt] ? ldf2(a.ux + l * sf + (long)row[rt] * F + 2 * H + c) : make_float2(0.f, 0.f);
-      if (KIND == K_RNN) {
-        lm[rt] = make_float2(1.f, 1.f);
-        if (a.lambda && on[rt]) lm[rt] = ldf2(a.lambda + l * D + c);
-        else if (lam && on[rt]) lm[rt] = un2(ld2(lam + l * sx + (long)row[rt] * D + c));
-      }
-    }
-    in.load(ring, 0, l, wave, lane, dead);
-#pragma unroll
-    for (int u = 0; u < SLOTS; ++u) {
-      float4v acc[RT][2];
-      clear(acc);
-      multiply(acc, w[u], in);
-      put(part, set, u, acc, wave, lane);
-    }
-    meet();
-    if (l > 0) {       // every workgroup of the group has left step l - 1
-      empty<RT>(ring, 0, l - 1, member);
-      if (KIND == K_RNN || KIND == K_GRU) empty<RT>(ring, 1, l - 1, member);
-    }
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt) {
-      const int pr = 16 * rt + my_row, pc = my_col;
-      float2 s[SLOTS];
-#pragma unroll
-      for (int q = 0; q < SLOTS; ++q) {
-        s[q] = get(part, set, q, pr, pc);
-        s[q].x += ux[rt][q].x; s[q].y += ux[rt][q].y;
-      }
-      const long xo = (long)row[rt] * D + c, fo = (long)row[rt] * F + c;
-      if (KIND == K_RNN) {
-        if (a.tanh_act) s[0] = map2([&](int i) { return tanhf(at2(s[0], i)); });
-        const unsigned zw = pk(s[0]);
-        publish(ring, 1, l, rt, member, on_f[rt] ? zw : 0u);
-        if (on_f[rt]) st2(z + fo, zw);
-      } else if (KIND == K_GATED) {
-        const float2 u = map2([&](int i) { return sigmoid1(at2(s[0], i)); });
-        const float2 cc = map2([&](int i) { return tanhf(at2(s[SLOTS > 1 ? 1 : 0], i)); });
-        const float2 av = make_float2(1.f - u.x, 1.f - u.y);
-        const unsigned o = pk(map2([&](int i) { return fmaf(at2(av, i), at2(xs[rt], i), at2(u, i) * at2(cc, i)); }));
-        publish(ring, 0, l + 1, rt, member, on[rt] ? o : 0u);
-        if (on[rt]) {
-          st2(x + sx + xo, o);
-          st2(z + fo, pk(u));
-          st2(z + fo + H, pk(cc));
-          st2(lam + l * sx + xo, pk(av));
-        }
-        xs[rt] = un2(o);
-      } else if (KIND == K_LSTM) {
-        constexpr int S1 = SLOTS > 1 ? 1 : 0, S2 = SLOTS > 2 ? 2 : 0, S3 = SLOTS > 3 ? 3 : 0;
-        const float2 ig = map2([&](int i) { return sigmoid1(at2(s[0], i)); });
-        const float2 fg = map2([&](int i) { return sigmoid1(at2(s[S1], i)); });
-        const float2 og = map2([&](int i) { return sigmoid1(at2(s[S2], i)); });
-        const float2 gg = map2([&](int i) { return tanhf(at2(s[S3], i)); });
-        const float2 cn = map2([&](int i) { return fmaf(at2(fg, i), at2(xs[rt], i), at2(ig, i) * at2(gg, i)); });
-        const float2 hn = map2([&](int i) { return at2(og, i) * tanhf(at2(cn, i)); });
-        const unsigned cw = pk(cn), hw = pk(hn);
-        publish(ring, 0, l + 1, rt, member, on[rt] ? hw : 0u);
-        if (on[rt]) {
-          st2(x + sx + xo + H, hw);
-          st2(x + sx + xo, cw);
-          st2(z + fo, pk(ig));
-          st2(z + fo + H, pk(fg));
-          st2(z + fo + 2 * H, pk(og));
-          st2(z + fo + 3 * H, pk(gg));
-          st2(lam + l * sx + xo, pk(fg));
-          st2(lam + l * sx + xo + H, 0u);
-        }
-        xs[rt] = un2(cw);
-      } else {
-        const float2 r = map2([&](int i) { return sigmoid1(at2(s[SLOTS > 1 ? 1 : 0], i)); });
-        const unsigned zw = pk(map2([&](int i) { return sigmoid1(at2(s[0], i)); }));
-        publish(ring, 1, l, rt, member, on[rt] ? pk(make_float2(r.x * xs[rt].x, r.y * xs[rt].y)) : 0u);
-        if (on[rt]) {
-          st2(z + fo, zw);
-          st2(z + fo + H, pk(r));
-        }
-        ux[rt][0] = un2(zw);         // (the second half of the step works on the stored gate)
-      }
-    }
-    set ^= 1;
-    if (KIND == K_RNN || KIND == K_GRU) {
-      in.load(ring, 1, l, wave, lane, dead);
-      float4v acc[RT][2];
-      clear(acc);
-      multiply(acc, w[UNITS - 1], in);
-      put(part, set, 0, acc, wave, lane);
-      meet();
+    // what does not depend on the step before is on its way while the operands are waited for
+    auto read_step = [&]() __attribute__((always_inline)) {
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) {
-        float2 s = get(part, set, 0, 16 * rt + my_row, my_col);
-        const long xo = (long)row[rt] * D + c;
+#pragma unroll
+        for (int q = 0; q < SLOTS; ++q)
+          ux[rt][q] = at.on_f[rt] ? ldf2(a.ux + l * sf + (long)at.row[rt] * F + (KIND == K_RNN ? 0 : q * H) + at.c) : make_float2(0.f, 0.f);
+        if (KIND == K_GRU) un[rt] = at.on[rt] ? ldf2(a.ux + l * sf + (long)at.row[rt] * F + 2 * H + at.c) : make_float2(0.f, 0.f);
         if (KIND == K_RNN) {
-          const unsigned o = pk(map2([&](int i) { return at2(s, i) + at2(lm[rt], i) * at2(xs[rt], i); }));
-          publish(ring, 0, l + 1, rt, member, on[rt] ? o : 0u);
-          if (on[rt]) st2(x + sx + xo, o);
-          xs[rt] = un2(o);
-        } else {
-          const float2 zg = ux[rt][0];
-          const float2 nn = map2([&](int i) { return tanhf(at2(s, i) + at2(un[rt], i)); });
-          const float2 av = make_float2(1.f - zg.x, 1.f - zg.y);
-          const unsigned o = pk(map2([&](int i) { return fmaf(at2(av, i), at2(xs[rt], i), at2(zg, i) * at2(nn, i)); }));
-          publish(ring, 0, l + 1, rt, member, on[rt] ? o : 0u);
-          if (on[rt]) {
+          lm[rt] = make_float2(1.f, 1.f);
+          if (a.lambda && at.on[rt]) lm[rt] = ldf2(a.lambda + l * D + at.c);
+          else if (lam && at.on[rt]) lm[rt] = un2(ld2(lam + l * sx + (long)at.row[rt] * D + at.c));
+        }
+      }
+    };
+    members<ALONE>(own, ring.wpg, [&](int member) __attribute__((always_inline)) {
+      if (ALONE) place(member);
+      read_step();
+      in.load(ring, 0, l, wave, lane, dead);
+#pragma unroll
+      for (int u = 0; u < SLOTS; ++u) {
+        float4v acc[RT][2];
+        clear(acc);
+        multiply(acc, ALONE ? weights(u, member) : w[ALONE ? 0 : u], in);
+        put(part, set, u, acc, wave, lane);
+      }
+      meet();
+      if (l > 0) {       // every workgroup of the group has left step l - 1
+        empty<RT>(ring, 0, l - 1, member);
+        if (TWO) empty<RT>(ring, 1, l - 1, member);
+      }
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) {
+        const int pr = 16 * rt + my_row, pc = my_col;
+        float2 s[SLOTS];
+#pragma unroll
+        for (int q = 0; q < SLOTS; ++q) {
+          s[q] = get(part, set, q, pr, pc);
+          s[q].x += ux[rt][q].x; s[q].y += ux[rt][q].y;
+        }
+        const long xo = (long)at.row[rt] * D + at.c, fo = (long)at.row[rt] * F + at.c;
+        if (KIND == K_RNN) {
+          if (a.tanh_act) s[0] = map2([&](int i) { return tanhf(at2(s[0], i)); });
+          const unsigned zw = pk(s[0]);
+          publish(ring, 1, l, rt, member, at.on_f[rt] ? zw : 0u);
+          if (at.on_f[rt]) st2(z + fo, zw);
+        } else if (KIND == K_GATED) {
+          const float2 u = map2([&](int i) { return sigmoid1(at2(s[0], i)); });
+          const float2 cc = map2([&](int i) { return tanhf(at2(s[SLOTS > 1 ? 1 : 0], i)); });
+          const float2 av = make_float2(1.f - u.x, 1.f - u.y);
+          const unsigned o = pk(map2([&](int i) { return fmaf(at2(av, i), at2(xs[rt], i), at2(u, i) * at2(cc, i)); }));
+          publish(ring, 0, l + 1, rt, member, at.on[rt] ? o : 0u);
+          if (at.on[rt]) {
             st2(x + sx + xo, o);
-            st2(z + (long)row[rt] * F + 2 * H + c, pk(nn));
+            st2(z + fo, pk(u));
+            st2(z + fo + H, pk(cc));
             st2(lam + l * sx + xo, pk(av));
           }
           xs[rt] = un2(o);
+        } else if (KIND == K_LSTM) {
+          constexpr int S1 = SLOTS > 1 ? 1 : 0, S2 = SLOTS > 2 ? 2 : 0, S3 = SLOTS > 3 ? 3 : 0;
+          const float2 ig = map2([&](int i) { return sigmoid1(at2(s[0], i)); });
+          const float2 fg = map2([&](int i) { return sigmoid1(at2(s[S1], i)); });
+          const float2 og = map2([&](int i) { return sigmoid1(at2(s[S2], i)); });
+          const float2 gg = map2([&](int i) { return tanhf(at2(s[S3], i)); });
+          const float2 cn = map2([&](int i) { return fmaf(at2(fg, i), at2(xs[rt], i), at2(ig, i) * at2(gg, i)); });
+          const float2 hn = map2([&](int i) { return at2(og, i) * tanhf(at2(cn, i)); });
+          const unsigned cw = pk(cn), hw = pk(hn);
+          publish(ring, 0, l + 1, rt, member, at.on[rt] ? hw : 0u);
+          if (at.on[rt]) {
+            st2(x + sx + xo + H, hw);
+            st2(x + sx + xo, cw);
+            st2(z + fo, pk(ig));
+            st2(z + fo + H, pk(fg));
+            st2(z + fo + 2 * H, pk(og));
+            st2(z + fo + 3 * H, pk(gg));
+            st2(lam + l * sx + xo, pk(fg));
+            st2(lam + l * sx + xo + H, 0u);
+          }
+          xs[rt] = un2(cw);
+        } else {
+          const float2 r = map2([&](int i) { return sigmoid1(at2(s[SLOTS > 1 ? 1 : 0], i)); });
+          const unsigned zw = pk(map2([&](int i) { return sigmoid1(at2(s[0], i)); }));
+          publish(ring, 1, l, rt, member, at.on[rt] ? pk(make_float2(r.x * xs[rt].x, r.y * xs[rt].y)) : 0u);
+          if (at.on[rt]) {
+            st2(z + fo, zw);
+            st2(z + fo + H, pk(r));
+          }
+          ux[rt][0] = un2(zw);         // (the second half of the step works on the stored gate)
         }
       }
       set ^= 1;
+    });
+    if (TWO) {
+      members<ALONE>(own, ring.wpg, [&](int member) __attribute__((always_inline)) {
+        if (ALONE) {
+          place(member);
+          read_step();
+          if (KIND == K_GRU) {
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt)
+              ux[rt][0] = at.on[rt] ? un2(ld2(z + (long)at.row[rt] * F + at.c)) : make_float2(0.f, 0.f);
+          }
+        }
+        in.load(ring, 1, l, wave, lane, dead);
+        float4v acc[RT][2];
+        clear(acc);
+        multiply(acc, ALONE ? weights(UNITS - 1, member) : w[ALONE ? 0 : UNITS - 1], in);
+        put(part, set, 0, acc, wave, lane);
+        meet();
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) {
+          float2 s = get(part, set, 0, 16 * rt + my_row, my_col);
+          const long xo = (long)at.row[rt] * D + at.c;
+          if (KIND == K_RNN) {
+            const unsigned o = pk(map2([&](int i) { return at2(s, i) + at2(lm[rt], i) * at2(xs[rt], i); }));
+            publish(ring, 0, l + 1, rt, member, at.on[rt] ? o : 0u);
+            if (at.on[rt]) st2(x + sx + xo, o);
+            xs[rt] = un2(o);
+          } else {
+            const float2 zg = ux[rt][0];
+            const float2 nn = map2([&](int i) { return tanhf(at2(s, i) + at2(un[rt], i)); });
+            const float2 av = make_float2(1.f - zg.x, 1.f - zg.y);
+            const unsigned o = pk(map2([&](int i) { return fmaf(at2(av, i), at2(xs[rt], i), at2(zg, i) * at2(nn, i)); }));
+            publish(ring, 0, l + 1, rt, member, at.on[rt] ? o : 0u);
+            if (at.on[rt]) {
+              st2(x + sx + xo, o);
+              st2(z + (long)at.row[rt] * F + 2 * H + at.c, pk(nn));
+              st2(lam + l * sx + xo, pk(av));
+            }
+            xs[rt] = un2(o);
+          }
+        }
+        set ^= 1;
+      });
     }
   }
 }
 
+template <int KIND, int KQ, int RT>
+__global__ __launch_bounds__(256, 1) void rec_forward_kernel(RecArgs a, int wpg, int groups) {
+  constexpr int SLOTS = KIND == K_LSTM ? 4 : KIND == K_RNN ? 1 : 2;
+  __shared__ __attribute__((aligned(16))) Partials<RT, SLOTS> part;
+  int group, member;
+  const bool together = take_place(a, wpg, group, member);
+  const Ring ring = {reinterpret_cast<char*>(a.ring), wpg, groups, RT, group};
+  if (together) forward_chain<KIND, KQ, RT, false>(a, ring, member, part);
+  else if (member == 0) forward_chain<KIND, KQ, RT, true>(a, ring, member, part);
+}
+
 // Exact backpropagation: g[l] = (da_l W1 + what goes past the product) (+ e_l) + lambda_l (.) g[l+1], l = L-1 .. 0; da as in
 // gated_cell.hip.  Weights transposed: Wt1 = W1^T [H][F] (GRU: [W_z; W_r]^T [H][2H]), Wt2 = W2^T [F][D] (RNN) or W_n^T [H][H].
-template <int KIND, int KQ, int RT>
-__global__ __launch_bounds__(256, 1) void rec_backward_kernel(RecArgs a, int wpg) {
+template <int KIND, int KQ, int RT, bool ALONE>
+__device__ __forceinline__ void backward_chain(const RecArgs& a, const Ring& ring, int own, Partials<RT, 1>& part) {
   constexpr int UNITS = KIND == K_LSTM ? 4 : KIND == K_GRU ? 3 : 2;
   constexpr bool TWO = KIND == K_RNN || KIND == K_GRU;       // two dependent products per step
   constexpr int U0 = TWO ? 1 : 0;                            // first unit of the (second) product with W1
-  __shared__ __attribute__((aligned(16))) Partials<RT, 1> part;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  int group, member;
-  take_number(a.counter, wpg, group, member);
-  const Ring ring = {reinterpret_cast<char*>(a.ring), wpg, (int)gridDim.x / wpg, RT, group};
-  const int row0 = group * 16 * RT, col0 = member * REC_COLS;
   const int N = (int)a.N, H = (int)a.H, F = (int)a.F, D = (int)a.D;
-  Weights<KQ> w[UNITS];
-  if (TWO) w[0].load((const bf16_t*)a.Wt2, KIND == K_RNN ? D : H, col0, KIND == K_RNN ? F : H, KIND == K_RNN ? D : H, wave, lane);
-  const int Ku = KIND == K_RNN ? F : H;                      // contraction length of a unit of W1
+  Weights<KQ> w[ALONE ? 1 : UNITS];
+  auto weights = [&](int u, int member) __attribute__((always_inline)) -> Weights<KQ>& {
+    Weights<KQ>& t = w[ALONE ? 0 : u];
+    const int col0 = member * REC_COLS;
+    if (TWO && u == 0) t.load((const bf16_t*)a.Wt2, KIND == K_RNN ? D : H, col0, KIND == K_RNN ? F : H, KIND == K_RNN ? D : H, wave, lane);
+    else t.load((const bf16_t*)a.Wt1 + (long)(u - U0) * H, KIND == K_GRU ? 2 * H : F, col0, KIND == K_RNN ? D : H, KIND == K_RNN ? F : H, wave, lane);
+    return t;
+  };
+  if (!ALONE) {
 #pragma unroll
-  for (int u = U0; u < UNITS; ++u)
-    w[u].load((const bf16_t*)a.Wt1 + (long)(u - U0) * H, KIND == K_GRU ? 2 * H : F, col0, KIND == K_RNN ? D : H, Ku, wave, lane);
+    for (int u = 0; u < UNITS; ++u) weights(u, own);
+  }
   Operand<KQ, RT> in;
   // exchanged: the cells' da, a unit per gate; the RNN's da is unit 0 and its state gradient unit 1
-  const int my_row = (tid >> 2) & 15, my_col = 8 * (tid >> 6) + 2 * (tid & 3), c = col0 + my_col;
-  int row[RT];
-  bool on[RT], on_f[RT];
+  const int my_row = (tid >> 2) & 15, my_col = 8 * (tid >> 6) + 2 * (tid & 3);
+  Place<RT> at;
   float2 gs[RT], gc[RT];             // the gradient's two channels as stored (LSTM: hidden and cell part)
   const long sx = (long)N * D, sf = (long)N * F;
   bf16_t* g = (bf16_t*)a.g + a.L * sx;
   const int ho = KIND == K_LSTM ? H : 0;
+  auto place = [&](int member) __attribute__((always_inline)) {      // where the member's channels are, and its gradient (g points at it)
+    at.set(ring.group, member, N, KIND == K_RNN ? D : H, KIND == K_RNN ? F : H);
 #pragma unroll
-  for (int rt = 0; rt < RT; ++rt) {
-    const int r = row0 + 16 * rt + my_row;
-    on[rt] = r < N && c < (KIND == K_RNN ? D : H);
-    on_f[rt] = r < N && c < (KIND == K_RNN ? F : H);
-    row[rt] = r < N ? r : N - 1;
-    gs[rt] = gc[rt] = make_float2(0.f, 0.f);
-    if (on[rt]) gs[rt] = un2(ld2(g + (long)row[rt] * D + ho + c));
-    if (KIND == K_LSTM && on[rt]) gc[rt] = un2(ld2(g + (long)row[rt] * D + c));
-    if (KIND == K_RNN) publish(ring, 1, a.L, rt, member, on[rt] ? ld2(g + (long)row[rt] * D + c) : 0u);
-  }
+    for (int rt = 0; rt < RT; ++rt) {
+      gs[rt] = gc[rt] = make_float2(0.f, 0.f);
+      if (at.on[rt]) gs[rt] = un2(ld2(g + (long)at.row[rt] * D + ho + at.c));
+      if (KIND == K_LSTM && at.on[rt]) gc[rt] = un2(ld2(g + (long)at.row[rt] * D + at.c));
+    }
+  };
+  members<ALONE>(own, ring.wpg, [&](int member) __attribute__((always_inline)) {
+    place(member);
+    if (KIND == K_RNN) {
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt)
+        publish(ring, 1, a.L, rt, member, at.on[rt] ? ld2(g + (long)at.row[rt] * D + at.c) : 0u);
+    }
+  });
   bool dead = false;
   int set = 0;
   const bf16_t* x = (const bf16_t*)a.x + (a.L - 1) * sx;
@@ -409,106 +497,146 @@ __global__ __launch_bounds__(256, 1) void rec_backward_kernel(RecArgs a, int wpg
   const bf16_t* e = (const bf16_t*)a.e;
 #pragma unroll 1
   for (long l = a.L - 1; l >= 0; --l, x -= sx, z -= sf, g -= sx) {
-    // what does not depend on the step after is on its way while the operands are waited for
     unsigned lw[RT], lw2[RT], ew[RT], ew2[RT], zw[RT][4], xw[RT], xn[RT];
     float2 lmf[RT];
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt) {
-      const long xo = (long)row[rt] * D + c, fo = (long)row[rt] * F + c;
-      lmf[rt] = make_float2(1.f, 1.f);
-      lw[rt] = lw2[rt] = ew[rt] = ew2[rt] = xw[rt] = xn[rt] = 0u;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) zw[rt][q] = 0u;
-      if (on[rt]) {
-        if (a.lambda) lmf[rt] = ldf2(a.lambda + l * D + c);
-        else if (lamt) lw[rt] = ld2(lamt + l * sx + xo + ho);
-        if (e) ew[rt] = ld2(e + l * sx + xo + ho);
-        if (KIND == K_LSTM) {
-          lw2[rt] = ld2(lamt + l * sx + xo);
-          if (e) ew2[rt] = ld2(e + l * sx + xo);
-          xn[rt] = ld2(x + sx + xo);
-        }
-        if (KIND != K_RNN) {
-          xw[rt] = ld2(x + xo);
-#pragma unroll
-          for (int q = 0; q < (KIND == K_GATED ? 2 : KIND == K_GRU ? 3 : 4); ++q) zw[rt][q] = ld2(z + fo + q * H);
-        }
-      }
-      if (KIND == K_RNN && on_f[rt]) {
-        if (dphi) zw[rt][0] = ld2(dphi + l * sf + fo);
-        else if (a.tanh_act) zw[rt][0] = ld2(z + fo);
-      }
-    }
     float2 past[RT], pastc[RT];      // what reaches g[l] (hidden, cell) past the product with W1
+    // what does not depend on the step after is on its way while the operands are waited for
+    auto read_step = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt) {
-      past[rt] = pastc[rt] = make_float2(0.f, 0.f);
-      const float2 G = gs[rt], xv = un2(xw[rt]);
-      if (KIND == K_GATED) {
-        const float2 u = un2(zw[rt][0]), cc = un2(zw[rt][1]);
-        const float2 du = map2([&](int i) { return at2(G, i) * (at2(cc, i) - at2(xv, i)) * at2(u, i) * (1.f - at2(u, i)); });
-        const float2 dc = map2([&](int i) { return at2(G, i) * at2(u, i) * (1.f - at2(cc, i) * at2(cc, i)); });
-        publish(ring, 0, l, rt, member, on[rt] ? pk(du) : 0u);
-        publish(ring, 1, l, rt, member, on[rt] ? pk(dc) : 0u);
-      } else if (KIND == K_LSTM) {
-        const float2 ig = un2(zw[rt][0]), fg = un2(zw[rt][1]), og = un2(zw[rt][2]), gg = un2(zw[rt][3]), cn = un2(xn[rt]);
-        const float2 tc = map2([&](int i) { return tanhf(at2(cn, i)); });
-        const float2 th = map2([&](int i) { return at2(G, i) * at2(og, i) * (1.f - at2(tc, i) * at2(tc, i)); });
-        const float2 dct = make_float2(gc[rt].x + th.x, gc[rt].y + th.y);
-        const float2 di = map2([&](int i) { return at2(dct, i) * at2(gg, i) * at2(ig, i) * (1.f - at2(ig, i)); });
-        const float2 df = map2([&](int i) { return at2(dct, i) * at2(xv, i) * at2(fg, i) * (1.f - at2(fg, i)); });
-        const float2 dO = map2([&](int i) { return at2(G, i) * at2(tc, i) * at2(og, i) * (1.f - at2(og, i)); });
-        const float2 dg = map2([&](int i) { return at2(dct, i) * at2(ig, i) * (1.f - at2(gg, i) * at2(gg, i)); });
-        publish(ring, 0, l, rt, member, on[rt] ? pk(di) : 0u);
-        publish(ring, 1, l, rt, member, on[rt] ? pk(df) : 0u);
-        publish(ring, 2, l, rt, member, on[rt] ? pk(dO) : 0u);
-        publish(ring, 3, l, rt, member, on[rt] ? pk(dg) : 0u);
-        pastc[rt] = make_float2(th.x * fg.x, th.y * fg.y);
-      } else if (KIND == K_GRU) {
-        const float2 zg = un2(zw[rt][0]), nn = un2(zw[rt][2]);
-        const float2 dn = map2([&](int i) { return at2(G, i) * at2(zg, i) * (1.f - at2(nn, i) * at2(nn, i)); });
-        const float2 dz = map2([&](int i) { return at2(G, i) * (at2(nn, i) - at2(xv, i)) * at2(zg, i) * (1.f - at2(zg, i)); });
-        publish(ring, 2, l, rt, member, on[rt] ? pk(dn) : 0u);
-        publish(ring, 0, l, rt, member, on[rt] ? pk(dz) : 0u);
+      for (int rt = 0; rt < RT; ++rt) {
+        const long xo = (long)at.row[rt] * D + at.c, fo = (long)at.row[rt] * F + at.c;
+        lmf[rt] = make_float2(1.f, 1.f);
+        lw[rt] = lw2[rt] = ew[rt] = ew2[rt] = xw[rt] = xn[rt] = 0u;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) zw[rt][q] = 0u;
+        if (at.on[rt]) {
+          if (a.lambda) lmf[rt] = ldf2(a.lambda + l * D + at.c);
+          else if (lamt) lw[rt] = ld2(lamt + l * sx + xo + ho);
+          if (e) ew[rt] = ld2(e + l * sx + xo + ho);
+          if (KIND == K_LSTM) {
+            lw2[rt] = ld2(lamt + l * sx + xo);
+            if (e) ew2[rt] = ld2(e + l * sx + xo);
+            xn[rt] = ld2(x + sx + xo);
+          }
+          if (KIND != K_RNN) {
+            xw[rt] = ld2(x + xo);
+#pragma unroll
+            for (int q = 0; q < (KIND == K_GATED ? 2 : KIND == K_GRU ? 3 : 4); ++q) zw[rt][q] = ld2(z + fo + q * H);
+          }
+        }
+        if (KIND == K_RNN && at.on_f[rt]) {
+          if (dphi) zw[rt][0] = ld2(dphi + l * sf + fo);
+          else if (a.tanh_act) zw[rt][0] = ld2(z + fo);
+        }
       }
-    }
-    if (TWO) {       // RNN: da = (g W2) (.) act'; GRU: what comes back through the candidate's product, dn W_n
+    };
+    // the LSTM's gradient at the cell state through the hidden part
+    auto through_h = [&](int rt) __attribute__((always_inline)) {
+      const float2 og = un2(zw[rt][2]), cn = un2(xn[rt]);
+      const float2 tc = map2([&](int i) { return tanhf(at2(cn, i)); });
+      return map2([&](int i) { return at2(gs[rt], i) * at2(og, i) * (1.f - at2(tc, i) * at2(tc, i)); });
+    };
+    // what the cells' elementwise parts leave for the products
+    auto publish_gates = [&](int member) __attribute__((always_inline)) {
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) {
+        const float2 G = gs[rt], xv = un2(xw[rt]);
+        if (KIND == K_GATED) {
+          const float2 u = un2(zw[rt][0]), cc = un2(zw[rt][1]);
+          const float2 du = map2([&](int i) { return at2(G, i) * (at2(cc, i) - at2(xv, i)) * at2(u, i) * (1.f - at2(u, i)); });
+          const float2 dc = map2([&](int i) { return at2(G, i) * at2(u, i) * (1.f - at2(cc, i) * at2(cc, i)); });
+          publish(ring, 0, l, rt, member, at.on[rt] ? pk(du) : 0u);
+          publish(ring, 1, l, rt, member, at.on[rt] ? pk(dc) : 0u);
+        } else if (KIND == K_LSTM) {
+          const float2 ig = un2(zw[rt][0]), fg = un2(zw[rt][1]), og = un2(zw[rt][2]), gg = un2(zw[rt][3]), cn = un2(xn[rt]);
+          const float2 tc = map2([&](int i) { return tanhf(at2(cn, i)); });
+          const float2 th = through_h(rt);
+          pastc[rt] = make_float2(th.x * fg.x, th.y * fg.y);
+          const float2 dct = make_float2(gc[rt].x + th.x, gc[rt].y + th.y);
+          const float2 di = map2([&](int i) { return at2(dct, i) * at2(gg, i) * at2(ig, i) * (1.f - at2(ig, i)); });
+          const float2 df = map2([&](int i) { return at2(dct, i) * at2(xv, i) * at2(fg, i) * (1.f - at2(fg, i)); });
+          const float2 dO = map2([&](int i) { return at2(G, i) * at2(tc, i) * at2(og, i) * (1.f - at2(og, i)); });
+          const float2 dg = map2([&](int i) { return at2(dct, i) * at2(ig, i) * (1.f - at2(gg, i) * at2(gg, i)); });
+          publish(ring, 0, l, rt, member, at.on[rt] ? pk(di) : 0u);
+          publish(ring, 1, l, rt, member, at.on[rt] ? pk(df) : 0u);
+          publish(ring, 2, l, rt, member, at.on[rt] ? pk(dO) : 0u);
+          publish(ring, 3, l, rt, member, at.on[rt] ? pk(dg) : 0u);
+        } else if (KIND == K_GRU) {
+          const float2 zg = un2(zw[rt][0]), nn = un2(zw[rt][2]);
+          const float2 dn = map2([&](int i) { return at2(G, i) * at2(zg, i) * (1.f - at2(nn, i) * at2(nn, i)); });
+          const float2 dz = map2([&](int i) { return at2(G, i) * (at2(nn, i) - at2(xv, i)) * at2(zg, i) * (1.f - at2(zg, i)); });
+          publish(ring, 2, l, rt, member, at.on[rt] ? pk(dn) : 0u);
+          publish(ring, 0, l, rt, member, at.on[rt] ? pk(dz) : 0u);
+        }
+      }
+    };
+    // RNN: g W2; GRU: what comes back through the candidate's product, dn W_n
+    auto first_product = [&](int member) __attribute__((always_inline)) {
       in.load(ring, KIND == K_RNN ? 1 : 2, KIND == K_RNN ? l + 1 : l, wave, lane, dead);
       float4v acc[RT][2];
       clear(acc);
-      multiply(acc, w[0], in);
+      multiply(acc, ALONE ? weights(0, member) : w[0], in);
       put(part, set, 0, acc, wave, lane);
       meet();
-      if (l + 1 < a.L) {       // every workgroup of the group has left step l + 1
-        empty<RT>(ring, 0, l + 1, member);
-        empty<RT>(ring, 1, KIND == K_RNN ? l + 2 : l + 1, member);
-        if (KIND == K_GRU) empty<RT>(ring, 2, l + 1, member);
+    };
+    members<ALONE>(own, ring.wpg, [&](int member) __attribute__((always_inline)) {
+      if (ALONE) place(member);
+      read_step();
+      publish_gates(member);
+    });
+    if (TWO) {
+      members<ALONE>(own, ring.wpg, [&](int member) __attribute__((always_inline)) {
+        if (ALONE) { place(member); read_step(); }
+        first_product(member);
+        if (l + 1 < a.L) {       // every workgroup of the group has left step l + 1
+          empty<RT>(ring, 0, l + 1, member);
+          empty<RT>(ring, 1, KIND == K_RNN ? l + 2 : l + 1, member);
+          if (KIND == K_GRU) empty<RT>(ring, 2, l + 1, member);
+        }
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) {
+          const float2 s = get(part, set, 0, 16 * rt + my_row, my_col);
+          if (KIND == K_RNN) {
+            float2 v = s;
+            const float2 t = un2(zw[rt][0]);
+            if (dphi) v = make_float2(s.x * t.x, s.y * t.y);
+            else if (a.tanh_act) v = make_float2(s.x * (1.f - t.x * t.x), s.y * (1.f - t.y * t.y));
+            publish(ring, 0, l, rt, member, at.on_f[rt] ? pk(v) : 0u);
+          } else {
+            const float2 r = un2(zw[rt][1]), xv = un2(xw[rt]);
+            const float2 dr = map2([&](int i) { return at2(s, i) * at2(xv, i) * at2(r, i) * (1.f - at2(r, i)); });
+            publish(ring, 1, l, rt, member, at.on[rt] ? pk(dr) : 0u);
+            past[rt] = make_float2(s.x * r.x, s.y * r.y);
+          }
+        }
+        set ^= 1;
+      });
+    }
+    members<ALONE>(own, ring.wpg, [&](int member) __attribute__((always_inline)) {
+      if (ALONE) { place(member); read_step(); }
+      if (KIND == K_GRU && ALONE) {      // (the sum that the member's registers hold otherwise)
+        first_product(member);
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) {
+          const float2 s = get(part, set, 0, 16 * rt + my_row, my_col), r = un2(zw[rt][1]);
+          past[rt] = make_float2(s.x * r.x, s.y * r.y);
+        }
+        set ^= 1;
       }
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) {
-        const float2 s = get(part, set, 0, 16 * rt + my_row, my_col);
-        if (KIND == K_RNN) {
-          float2 v = s;
-          const float2 t = un2(zw[rt][0]);
-          if (dphi) v = make_float2(s.x * t.x, s.y * t.y);
-          else if (a.tanh_act) v = make_float2(s.x * (1.f - t.x * t.x), s.y * (1.f - t.y * t.y));
-          publish(ring, 0, l, rt, member, on_f[rt] ? pk(v) : 0u);
-        } else {
-          const float2 r = un2(zw[rt][1]), xv = un2(xw[rt]);
-          const float2 dr = map2([&](int i) { return at2(s, i) * at2(xv, i) * at2(r, i) * (1.f - at2(r, i)); });
-          publish(ring, 1, l, rt, member, on[rt] ? pk(dr) : 0u);
-          past[rt] = make_float2(s.x * r.x, s.y * r.y);
+        if (KIND != K_GRU) past[rt] = make_float2(0.f, 0.f);
+        if (KIND == K_LSTM && ALONE) {
+          const float2 th = through_h(rt), fg = un2(zw[rt][1]);
+          pastc[rt] = make_float2(th.x * fg.x, th.y * fg.y);
         }
       }
-      set ^= 1;
-    }
-    {
       float4v acc[RT][2];
       clear(acc);
 #pragma unroll
       for (int u = U0; u < UNITS; ++u) {
         in.load(ring, u - U0, l, wave, lane, dead);
-        multiply(acc, w[u], in);
+        multiply(acc, ALONE ? weights(u, member) : w[ALONE ? 0 : u], in);
       }
       put(part, set, 0, acc, wave, lane);
       meet();
@@ -521,28 +649,39 @@ __global__ __launch_bounds__(256, 1) void rec_backward_kernel(RecArgs a, int wpg
         const float2 s = get(part, set, 0, 16 * rt + my_row, my_col);
         const float2 ev = un2(ew[rt]), lm = lamt ? un2(lw[rt]) : lmf[rt];
         const unsigned o = pk(map2([&](int i) { return (at2(s, i) + at2(past[rt], i) + at2(ev, i)) + at2(lm, i) * at2(gs[rt], i); }));
-        const long xo = (long)row[rt] * D + c - sx;          // g points at g[l + 1]
-        if (KIND == K_RNN) publish(ring, 1, l, rt, member, on[rt] ? o : 0u);
-        if (on[rt]) st2(g + xo + ho, o);
+        const long xo = (long)at.row[rt] * D + at.c - sx;    // g points at g[l + 1]
+        if (KIND == K_RNN) publish(ring, 1, l, rt, member, at.on[rt] ? o : 0u);
+        if (at.on[rt]) st2(g + xo + ho, o);
         gs[rt] = un2(o);
         if (KIND == K_LSTM) {
           const float2 e2 = un2(ew2[rt]), l2 = un2(lw2[rt]);
           const unsigned oc = pk(map2([&](int i) { return (at2(pastc[rt], i) + at2(e2, i)) + at2(l2, i) * at2(gc[rt], i); }));
-          if (on[rt]) st2(g + xo, oc);
+          if (at.on[rt]) st2(g + xo, oc);
           gc[rt] = un2(oc);
         }
       }
       set ^= 1;
-    }
+    });
   }
 }
 
-// the empty word into every slot (n 16-byte pieces), zeros into the block behind them, and the counter at zero
-__global__ __launch_bounds__(256) void rec_fill_kernel(uint4* p, long n, int* counter) {
+template <int KIND, int KQ, int RT>
+__global__ __launch_bounds__(256, 1) void rec_backward_kernel(RecArgs a, int wpg, int groups) {
+  __shared__ __attribute__((aligned(16))) Partials<RT, 1> part;
+  int group, member;
+  const bool together = take_place(a, wpg, group, member);
+  const Ring ring = {reinterpret_cast<char*>(a.ring), wpg, groups, RT, group};
+  if (together) backward_chain<KIND, KQ, RT, false>(a, ring, member, part);
+  else if (member == 0) backward_chain<KIND, KQ, RT, true>(a, ring, member, part);
+}
+
+// the empty word into every slot (n 16-byte pieces), zeros into the block behind them, the counter at zero and the groups' words
+__global__ __launch_bounds__(256) void rec_fill_kernel(uint4* p, long n, int* counter, unsigned word) {
   const long i = (long)blockIdx.x * 256 + threadIdx.x;
   const unsigned w = i < n ? REC_EMPTY : 0u;
   if (i < n + 64) p[i] = make_uint4(w, w, w, w);
   if (i == 0) *counter = 0;
+  if (i < REC_MAX_WG) counter[1 + i] = (int)word;
 }
 
 inline long rec_width(const RecArgs& a) { return a.F > a.D && a.kind == K_RNN ? a.F : a.kind == K_RNN ? a.D : a.H; }
@@ -561,9 +700,9 @@ hipError_t launch_rec(const RecArgs& a, bool forward, hipStream_t s) {
   const long wgs = (a.N + 16 * RT - 1) / (16 * RT) * wpg;
   const long n16 = REC_UNITS * REC_SLOTS * wgs * RT * 64;
   hipLaunchKernelGGL(rec_fill_kernel, dim3((unsigned)((n16 + 64 + 255) / 256)), dim3(256), 0, s, reinterpret_cast<uint4*>(a.ring), n16,
-                     a.counter);
-  if (forward) hipLaunchKernelGGL((rec_forward_kernel<KIND, KQ, RT>), dim3((unsigned)wgs), dim3(256), 0, s, a, (int)wpg);
-  else hipLaunchKernelGGL((rec_backward_kernel<KIND, KQ, RT>), dim3((unsigned)wgs), dim3(256), 0, s, a, (int)wpg);
+                     a.counter, a.wait == REC_ALONE_ANYHOW ? REC_ALONE : 0u);
+  if (forward) hipLaunchKernelGGL((rec_forward_kernel<KIND, KQ, RT>), dim3((unsigned)wgs), dim3(256), 0, s, a, (int)wpg, (int)(wgs / wpg));
+  else hipLaunchKernelGGL((rec_backward_kernel<KIND, KQ, RT>), dim3((unsigned)wgs), dim3(256), 0, s, a, (int)wpg, (int)(wgs / wpg));
   return hipGetLastError();
 }
 template <int KIND>
@@ -580,6 +719,7 @@ hipError_t launch_rec_kind(const RecArgs& a, bool forward, hipStream_t s) {
 
 }  // namespace
 
+static_assert((1 + REC_MAX_WG) * sizeof(int) <= RECURRENT_COUNTER_BYTES, "a counter and a word per group");
 size_t recurrent_ring_bytes() { return (size_t)REC_UNITS * REC_SLOTS * REC_MAX_WG * 2 * 1024 + 1024; }
 // What fits: bf16, widths whose weights the registers hold (1024) and at most 64 workgroups (two row tiles each: 64 rows at
 // width 1024, 128 at 512).  Everything else goes step by step (7 us per product against 1.6).

@@ -132,6 +132,30 @@ def _same_numbers(got, want, what):
     H.assert_close(np.where(np.isfinite(want), got, 0), np.where(np.isfinite(want), want, 0), H.TOL["bf16"], what)
 
 
+# Groups whose workgroups do not get to run side by side are left to one workgroup: all of them (wait 2), or those whose
+# workgroups do not all start at the same moment (wait 1).  The same results bit for bit.
+@pytest.mark.parametrize("wait", [1, 2])
+@pytest.mark.parametrize("kind,L,N,H", [("rnn", 1, 1, 8), ("rnn", 9, 17, 264), ("rnn", 6, 64, 1024), ("token", 7, 15, 72),
+                                        ("gated", 9, 33, 136), ("gated", 6, 64, 1000), ("lstm", 1, 5, 24), ("lstm", 9, 16, 520),
+                                        ("lstm", 6, 64, 1024), ("gru", 3, 1, 40), ("gru", 9, 31, 256), ("gru", 6, 64, 1024)])
+def test_chains_along_time_by_one_workgroup(B, kind, L, N, H, wait):
+    import ctypes as C
+    import torch
+    w = _chain(kind, L, N, H)
+    inp, st, sv, p = _setup(B, w)
+    q = B.allocate(w, inp)
+    B.hbp_forward(p)
+    b = q.buffers()
+    f = B.lib().hbp_internal_chains
+    s = torch.cuda.current_stream().cuda_stream
+    assert f(C.byref(q.desc), 1, wait, C.byref(b), C.c_void_p(s)) == B.HBP_OK
+    for n in ("x", "z", "lam"):
+        assert torch.equal(getattr(p, n), getattr(q, n)), n
+    B.hbp_exact_backward(p)
+    assert f(C.byref(q.desc), 0, wait, C.byref(b), C.c_void_p(s)) == B.HBP_OK
+    assert torch.equal(p.g, q.g)
+
+
 # fp32 products: around the 32- and 64-wide tiles, contractions that end inside a chunk of 32 or leave a wavefront's
 # quarter empty, and enough blocks (40 x 4 x 4 tiles of 64) for the wide tiles
 @pytest.mark.parametrize("L,N,d,d_ff", [(2, 1, 8, 8), (2, 31, 40, 24), (3, 65, 32, 72), (2, 130, 264, 136), (40, 250, 72, 232)])
