@@ -95,6 +95,38 @@ def test_chains_along_time_with_nan_rows_and_on_two_streams(B, kind):
     assert bool(q.x[1:, 3].isnan().all()) and not bool(p.x.isnan().any())
 
 
+@pytest.mark.parametrize("kind,H", [("rnn", 264), ("gated", 64), ("lstm", 72), ("gru", 256)])
+def test_chains_along_time_in_a_graph(B, kind, H):
+    """Forward and exact backpropagation recorded into a HIP graph: every replay, with eager chains and synchronisations
+    between them, gives the eager result bit for bit."""
+    import torch
+    w = _chain(kind, 9, 20, H)
+    inp, st, sv, p = _setup(B, w)
+
+    def both():
+        B.hbp_forward(p)
+        B.hbp_exact_backward(p)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        both()
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    want = [t.clone() for t in (p.x, p.z, p.g)]
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        both()
+    for _ in range(3):
+        p.x[0] += 1
+        both()                                   # eager chains of other values between the replays
+        torch.cuda.synchronize()
+        p.x[0].copy_(want[0][0])
+        p.g.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip((p.x, p.z, p.g), want))
+
+
 # An infinity in the last block of 32 channels, at widths whose quarters of the contraction reach past it: saturated gates
 # stay finite, and gradients are infinite, not NaN.  One step, so that what follows does not mix the two.
 @pytest.mark.parametrize("kind", ["rnn", "token", "gated", "lstm", "gru"])
@@ -176,6 +208,22 @@ def test_short_contractions_on_whole_tiles(B, d):
     H.assert_close(H.to_np(p.z), sv["z"], H.TOL["bf16"], f"{w.name} z")
     H.assert_close(H.to_np(p.dphi), sv["dphi"], H.TOL["bf16"], f"{w.name} act'")
     _check_backward(B, w, p, st, sv, inp, w.name)
+
+
+# Two and more whole 256-wide tiles per workgroup, with contractions of five and seven slices (an odd number: singly), so that the
+# waits after an epilogue count its operations: the fused operands of the backward pass (narrow d), of the residual sum
+# (narrow d_ff) and GELU.  Then products of 512 whole tiles in one matrix with remainders of rows and columns, whose parts
+# start inside the second output and the coefficients per channel.
+@pytest.mark.parametrize("N,d,d_ff,act", [(33280, 160, 1024, "gelu"), (33280, 224, 1024, "tanh"), (33280, 1024, 160, "gelu"),
+                                          (16640, 2048, 224, "gelu"), (16400, 512, 2056, "gelu"), (16400, 2056, 128, "gelu")])
+def test_several_tiles_per_workgroup(B, N, d, d_ff, act):
+    w = synth.scaled(W["resnet_like"], name=f"mlp_{N}_{d}_{d_ff}", L=1, N=N, d=d, d_ff=d_ff, w2_scale=0.7, act=act, ks=(1,))
+    inp, st, sv, p = _forward_matches(B, w)
+    H.assert_close(H.to_np(p.z), sv["z"], H.TOL["bf16"], f"{w.name} z")
+    if act == "gelu":
+        H.assert_close(H.to_np(p.dphi), sv["dphi"], H.TOL["bf16"], f"{w.name} act'")
+    B.hbp_exact_backward(p)
+    H.assert_close(H.to_np(p.g)[0], O.exact_backward(st, sv, inp["e"])[0], H.TOL["bf16"], f"{w.name} g[0]")
 
 
 # the norm's kernels: rows held by 16, 32 or 64 lanes and one to eight vectors per lane, the last partly past the width, and
