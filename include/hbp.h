@@ -314,11 +314,12 @@ const char* hbp_status_string(hbp_status s);
  * class since the previous read into ms[HBP_PROF_CLASSES] and
  * launches[HBP_PROF_CLASSES] (both HOST arrays), and forgets them. */
 enum {
-  HBP_PROF_VJP1 = 0,    /* da = (g W2) (.) act'      (step (i), first contraction)  */
+  HBP_PROF_VJP1 = 0,    /* da = (g W2) (.) act'      (step (i), first contraction); exact backpropagation of a chain along time
+                         * that runs in one launch: all of it */
   HBP_PROF_VJP2 = 1,    /* dn = da W1                (step (i), second contraction) */
   HBP_PROF_SCAN = 2,    /* residual-path scan        (step (ii), and w^0)           */
   HBP_PROF_DW = 3,      /* parameter-gradient contractions over tokens              */
-  HBP_PROF_FORWARD = 4, /* forward support kernels                                  */
+  HBP_PROF_FORWARD = 4, /* forward support kernels, chains along time among them    */
   HBP_PROF_OTHER = 5,   /* copies, split-K reductions                               */
   HBP_PROF_ATTN = 6,    /* attention between its two matrices, forward and backward  */
   HBP_PROF_CLASSES = 7

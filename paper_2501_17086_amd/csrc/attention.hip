@@ -986,7 +986,7 @@ __global__ __launch_bounds__(64 * AT_WAVES, DHP == 128 ? 1 : DHP == 64 && PAD ? 
 // rows having been read out, and the positions are taken as keys: dk, dv over the query tiles that see them.  Under a
 // causal mask that is w + 1 + 8 - w steps either way: every wavefront has the same number.  Nothing is streamed, each
 // tensor is read from memory once, and the arithmetic is that of the two-kernel form, in the same order per output
-// element.  What bounds it is memory (80 flop per byte at 256 positions): the problem's 66 KB of LDS let two workgroups
+// element.  What bounds it is memory (80 flop per byte at 256 positions): the problem's 74 KB of LDS (64 columns) let two workgroups
 // share a compute unit, so that one's loads run under the other's products.  All four tensors in LDS (130 KB, one
 // workgroup of eight wavefronts) took 531 us for 12 layers of 512 problems of 256, this form 472,
 // and 406 with the results leaving through LDS (store_tile).

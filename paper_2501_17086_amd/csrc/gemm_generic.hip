@@ -1,7 +1,6 @@
-// Generic strided GEMM with fp32 FMA accumulation, for operands whose addresses
-// or strides the MFMA kernels cannot read in vectors (bf16 not a multiple of 8
-// elements, fp32 not a multiple of 4).  64x64 tile per workgroup,
-// 16-deep K slices staged through LDS, 4x4 outputs per thread.
+// Generic strided GEMM with fp32 FMA accumulation, for what the matrix-core kernels refuse: operands that are not 16-byte
+// aligned, bf16 matrices with more than 2^22 columns, fp32 products of more than 32 x 65535 rows or 65535 matrices.
+// 64x64 tile per workgroup, 16-deep K slices staged through LDS, 4x4 outputs per thread.
 #include "hbp_common.h"
 
 namespace hbp {

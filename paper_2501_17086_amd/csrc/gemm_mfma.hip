@@ -124,12 +124,6 @@ __device__ __forceinline__ void unpack4(uint2 r, float (&o)[4]) {
   o[0] = __uint_as_float(r.x << 16); o[1] = __uint_as_float(r.x & 0xFFFF0000u);
   o[2] = __uint_as_float(r.y << 16); o[3] = __uint_as_float(r.y & 0xFFFF0000u);
 }
-__device__ __forceinline__ void store4(bf16_t* p, const float (&v)[4]) {
-  *reinterpret_cast<uint2*>(p) = make_uint2(pack2(v[0], v[1]), pack2(v[2], v[3]));
-}
-__device__ __forceinline__ void store4(float* p, const float (&v)[4]) {
-  *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
-}
 
 // Division of numbers below 2^31 by a fixed d: (n m) >> sh with m = floor(2^sh / d) + 1, sh = 31 + ceil(log2 d) (the method
 // of Granlund and Montgomery).  The hardware has no integer division, and a tile's coordinates took two 64-bit and five
@@ -201,48 +195,18 @@ enum FastEpi {
 };
 
 // Straight-line epilogue from the registers for a tile fully inside the matrix (fp32 output).
-template <int FAST>
-__device__ __forceinline__ void epilogue_fast_fn(const GemmArgs& g, const TileCoord& tc, const float16v (&acc)[4][2],
-                                                 int wm0, int wn0, int lane) {
-  constexpr bool HAS_AUX = FAST == FAST_MUL_AUX || FAST == FAST_MUL_1MZ2 || FAST == FAST_ADD_AUX;
-  const long off0 = (tc.m0 + wm0 + (lane & 31)) * g.ldc + tc.n0 + wn0 + 4 * (lane >> 5);   // this lane's first element
-  const bf16_t* aux = reinterpret_cast<const bf16_t*>(g.aux) + tc.batch * g.aux_sb + off0;
+__device__ __forceinline__ void epilogue_f32(const GemmArgs& g, const TileCoord& tc, const float16v (&acc)[4][2], int wm0, int wn0,
+                                             int lane) {
   const long cb = g.split_k > 1 ? ((long)tc.split * g.batch + tc.batch) * g.c_sb : tc.batch * g.c_sb;
-  float* cf = reinterpret_cast<float*>(g.C) + cb + off0;
-  bf16_t* chp = reinterpret_cast<bf16_t*>(g.C) + cb + off0;
-  uint2 auxv[2][8];
-  if (HAS_AUX) {
+  float* c = reinterpret_cast<float*>(g.C) + cb + (tc.m0 + wm0 + (lane & 31)) * g.ldc + tc.n0 + wn0 + 4 * (lane >> 5);
 #pragma unroll
-    for (int jq = 0; jq < 8; ++jq) auxv[0][jq] = *reinterpret_cast<const uint2*>(aux + 8 * jq);
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    if (HAS_AUX && i + 1 < 4) {
-#pragma unroll
-      for (int jq = 0; jq < 8; ++jq)
-        auxv[(i + 1) & 1][jq] = *reinterpret_cast<const uint2*>(aux + (long)(32 * (i + 1)) * g.ldc + 8 * jq);
-    }
+  for (int i = 0; i < 4; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        float v[4];
-#pragma unroll
-        for (int x = 0; x < 4; ++x) v[x] = acc[i][j][4 * q + x];
-        if (HAS_AUX) {
-          float t[4];
-          unpack4(auxv[i & 1][4 * j + q], t);
-#pragma unroll
-          for (int x = 0; x < 4; ++x) {
-            if (FAST == FAST_MUL_AUX) v[x] *= t[x];
-            else if (FAST == FAST_ADD_AUX) v[x] += t[x];
-            else v[x] *= (1.f - t[x] * t[x]);
-          }
-        }
-        const long ro = (long)(32 * i) * g.ldc + 32 * j + 8 * q;
-        if (FAST == FAST_STORE_F32) store4(cf + ro, v); else store4(chp + ro, v);
-      }
-  }
+      for (int q = 0; q < 4; ++q)
+        *reinterpret_cast<float4*>(c + (long)(32 * i) * g.ldc + 32 * j + 8 * q) =
+            make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
 }
 
 // The lean form of the kernel, for launches in which every tile lies inside the
@@ -526,7 +490,7 @@ __global__ __launch_bounds__(NTHR, 1) void gemm_mfma_lean_kernel(GemmArgs g, Wal
 
   // One slice: load phase, barrier, compute phase, barrier.
   // Barrier intervals ("ticks"): group 0 loads slice c in tick 2c and multiplies it in tick 2c+1;
-  // group 1 does the same one tick later.  Slice c+4 is issued in the load phase of slice c into
+  // group 1 does the same one tick later.  Slice c+3 is issued in the load phase of slice c into
   // the stage of slice c-1, which its last reader (group 1, tick 2c-1) has left.  Every wave waits
   // for its own share of slice c+1 at the end of its load phase of slice c, a barrier or more
   // before the first reader of slice c+1 starts.
@@ -607,7 +571,7 @@ __global__ __launch_bounds__(NTHR, 1) void gemm_mfma_lean_kernel(GemmArgs g, Wal
   // slice 0 has landed once at most the pro - 1 slices after it are outstanding
   if (PAIR) {              // (issued: B of slice 0, the first pair of A, B of slices 1 and 2)
     if (pro == 3) wait_vm<4>(); else wait_vm<0>();
-  } else if (pro >= 4) wait_vm<3 * PER_SLICE>(); else if (pro == 3) wait_vm<2 * PER_SLICE>();
+  } else if (pro == 3) wait_vm<2 * PER_SLICE>();
   else if (pro == 2) wait_vm<PER_SLICE>(); else wait_vm<0>();
   __builtin_amdgcn_s_barrier();                 // slice 0 is in LDS
   if (grp == 1) __builtin_amdgcn_s_barrier();   // group 1 runs one tick behind
@@ -638,7 +602,7 @@ __global__ __launch_bounds__(NTHR, 1) void gemm_mfma_lean_kernel(GemmArgs g, Wal
       if (PAIR) step(no, yes, a2, true); else step(no, no, a2, true);
     }
     if (has_aux<FAST>() && !EARLY) { fetch_aux(aux0, g, cc, wm0, wn0, lane, 0); fetch_aux(aux1, g, cc, wm0, wn0, lane, 1); }
-    if (FAST == FAST_STORE_F32) epilogue_fast_fn<FAST>(g, cc, acc, wm0, wn0, lane);
+    if (FAST == FAST_STORE_F32) epilogue_f32(g, cc, acc, wm0, wn0, lane);
     else epilogue_staged_fn<FAST>(g, cc, acc, wm0, wn0, lane, smem + LEAN_NST * STAGE_BYTES + wave * 4096, aux0, aux1);
     if (TOGETHER && grp == 1) {
       __builtin_amdgcn_sched_barrier(0);
@@ -720,31 +684,32 @@ inline bool has_lean(const GemmArgs& g, bool a_kc, bool b_kc) {
   if (!a_kc) return g.mode == EPI_STORE && !g.addf && (g.c_is_f32 || g.split_k > 1);     // parameter gradients
   if (g.addf || g.split_k > 1) return false;
   if (g.c_is_f32) return b_kc && g.mode == EPI_STORE;                                    // the recurrent kinds' U xin
-  if (g.mode == EPI_STORE || g.mode == EPI_MUL_AUX || g.mode == EPI_MUL_1MZ2 || g.mode == EPI_ADD_AUX) return true;
-  if (g.mode == EPI_ACT_GELU) return b_kc && g.out2;                                     // forward
-  return g.mode == EPI_RESID && b_kc && g.aux && !g.lambda_mn;
+  if (g.mode == EPI_STORE) return true;
+  if (!b_kc) return g.mode == EPI_MUL_AUX || g.mode == EPI_MUL_1MZ2 || g.mode == EPI_ADD_AUX;   // block VJPs
+  if (g.mode == EPI_ACT_GELU) return g.out2;                                             // forward
+  return g.mode == EPI_RESID && g.aux && !g.lambda_mn;
 }
-template <bool B_KC>
-hipError_t launch_lean_kc(const GemmArgs& g, hipStream_t s) {
-  if constexpr (B_KC) {
-    if (g.c_is_f32) return launch_lean<true, true, FAST_STORE_F32>(g, s);
-  }
+hipError_t launch_lean_nn(const GemmArgs& g, hipStream_t s) {
   switch (g.mode) {
-    case EPI_STORE: return launch_lean<true, B_KC, FAST_STORE>(g, s);
-    case EPI_MUL_AUX: return launch_lean<true, B_KC, FAST_MUL_AUX>(g, s);
-    case EPI_MUL_1MZ2: return launch_lean<true, B_KC, FAST_MUL_1MZ2>(g, s);
-    case EPI_ADD_AUX: return launch_lean<true, B_KC, FAST_ADD_AUX>(g, s);
-    default: break;
+    case EPI_STORE: return launch_lean<true, false, FAST_STORE>(g, s);
+    case EPI_MUL_AUX: return launch_lean<true, false, FAST_MUL_AUX>(g, s);
+    case EPI_MUL_1MZ2: return launch_lean<true, false, FAST_MUL_1MZ2>(g, s);
+    case EPI_ADD_AUX: return launch_lean<true, false, FAST_ADD_AUX>(g, s);
+    default: return hipErrorInvalidValue;
   }
-  if constexpr (B_KC) {
-    if (g.mode == EPI_ACT_GELU) return launch_lean<true, true, FAST_ACT_GELU>(g, s);
-    if (g.mode == EPI_RESID) return launch_lean<true, true, FAST_RESID>(g, s);
+}
+hipError_t launch_lean_nt(const GemmArgs& g, hipStream_t s) {
+  if (g.c_is_f32) return launch_lean<true, true, FAST_STORE_F32>(g, s);
+  switch (g.mode) {
+    case EPI_STORE: return launch_lean<true, true, FAST_STORE>(g, s);
+    case EPI_ACT_GELU: return launch_lean<true, true, FAST_ACT_GELU>(g, s);
+    case EPI_RESID: return launch_lean<true, true, FAST_RESID>(g, s);
+    default: return hipErrorInvalidValue;
   }
-  return hipErrorInvalidValue;
 }
 hipError_t launch_lean_for(const GemmArgs& g, bool a_kc, bool b_kc, hipStream_t s) {
   if (!a_kc) return launch_lean<false, false, FAST_STORE_F32>(g, s);
-  return b_kc ? launch_lean_kc<true>(g, s) : launch_lean_kc<false>(g, s);
+  return b_kc ? launch_lean_nt(g, s) : launch_lean_nn(g, s);
 }
 
 // rows m0 .. m1 and columns n0 .. n1 of a product

@@ -209,8 +209,8 @@ CASES = {
                                         d_ff=256, loss_every_state=True, w2_scale=0.3, ks=(0, 2, 5)),
     # contractions over 8192 and more token rows: the parameter gradients are computed in several shares of the
     # token range (split-K) whose partial sums a second kernel adds up.  Whole 256-wide tiles (the aligned
-    # kernel); widths of 320 = 256 + 64 and 640 = 512 + 128 (aligned part plus row / column remainders on the
-    # general kernel, each with its own shares); a narrow dU (128 columns: the general kernel alone); the cells.
+    # kernel); widths of 320 = 256 + 64 and 640 = 512 + 128, and a narrow dU of 128 columns (tiles of 128 or 64 with
+    # clamped edges, with the same shares); the cells.
     "mlp_splitk": synth.scaled(W["resnet_like"], name="mlp_splitk", L=2, N=8192, d=256, d_ff=512,
                                w2_scale=1 / np.sqrt(2.0), ks=(0, 2)),
     "mlp_splitk_odd": synth.scaled(W["resnet_like"], name="mlp_splitk_odd", L=2, N=8192, d=320, d_ff=640,
