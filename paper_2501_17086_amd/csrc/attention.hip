@@ -921,9 +921,11 @@ __global__ __launch_bounds__(64 * AT_WAVES, DHP == 128 ? 1 : DHP == 64 && PAD ? 
     float16v s, dp;
 #pragma unroll
     for (int g = 0; g < 4; ++g) {       // the statistics of the lane's 16 queries: rows 8 g + 4 hh .. + 3
-      const float4 a4 = *reinterpret_cast<const float4*>(st + 8 * g + 4 * hh);
       const float4 d4 = *reinterpret_cast<const float4*>(st + 32 + 8 * g + 4 * hh);
-      // the products start from -L2 / c and -D: they come out as (s c - L2) / c and dP - D
+      // the products start from -L2 / c and -D: they come out as (s c - L2) / c and dP - D (EXACT: s, without the roundings of
+      // the sum at the height of L2 / c)
+      float4 a4 = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (!EXACT) a4 = *reinterpret_cast<const float4*>(st + 8 * g + 4 * hh);
       s[4 * g] = a4.x * ninv_c; s[4 * g + 1] = a4.y * ninv_c; s[4 * g + 2] = a4.z * ninv_c; s[4 * g + 3] = a4.w * ninv_c;
       dp[4 * g] = -d4.x; dp[4 * g + 1] = -d4.y; dp[4 * g + 2] = -d4.z; dp[4 * g + 3] = -d4.w;
     }
@@ -934,9 +936,12 @@ __global__ __launch_bounds__(64 * AT_WAVES, DHP == 128 ? 1 : DHP == 64 && PAD ? 
     }
     __builtin_amdgcn_sched_barrier(0);   // (keeps the second products' operand reads below: fewer live registers)
     float pr[16], ds[16];
+    float4 l4 = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      pr[r] = fast_exp2(s[r] * c);
+      if (EXACT && r % 4 == 0) l4 = *reinterpret_cast<const float4*>(st + tile_row_of(r, hh));
+      const float L2r = r % 4 == 0 ? l4.x : r % 4 == 1 ? l4.y : r % 4 == 2 ? l4.z : l4.w;
+      pr[r] = fast_exp2(EXACT ? fmaf(s[r], c, -L2r) : s[r] * c);
       if (MASKED) {
         const int qi = q0 + tile_row_of(r, hh);
         if (!(qi < T && (!CAUSAL || kj <= qi))) pr[r] = 0.f;
@@ -1134,9 +1139,10 @@ __global__ __launch_bounds__(256, DHP == 128 ? 1 : 2) void attn_bwd_short_mfma_k
       float16v s, dp;
 #pragma unroll
       for (int g = 0; g < 4; ++g) {       // the statistics of the lane's 16 queries: rows 8 g + 4 hh .. + 3
-        const float4 a4 = *reinterpret_cast<const float4*>(st + 8 * g + 4 * hh);
         const float4 d4 = *reinterpret_cast<const float4*>(st + 32 + 8 * g + 4 * hh);
-        // the products start from -L2 / c and -D: they come out as (s c - L2) / c and dP - D
+        // the products start from -L2 / c and -D: they come out as (s c - L2) / c and dP - D (EXACT: s)
+        float4 a4 = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (!EXACT) a4 = *reinterpret_cast<const float4*>(st + 8 * g + 4 * hh);
         s[4 * g] = a4.x * ninv_c; s[4 * g + 1] = a4.y * ninv_c; s[4 * g + 2] = a4.z * ninv_c; s[4 * g + 3] = a4.w * ninv_c;
         dp[4 * g] = -d4.x; dp[4 * g + 1] = -d4.y; dp[4 * g + 2] = -d4.z; dp[4 * g + 3] = -d4.w;
       }
@@ -1159,9 +1165,12 @@ __global__ __launch_bounds__(256, DHP == 128 ? 1 : 2) void attn_bwd_short_mfma_k
         }
       __builtin_amdgcn_sched_barrier(0);
       float pr[16], ds[16];
+      float4 l4 = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        pr[r] = fast_exp2(s[r] * c);
+        if (EXACT && r % 4 == 0) l4 = *reinterpret_cast<const float4*>(st + tile_row_of(r, hh));
+        const float L2r = r % 4 == 0 ? l4.x : r % 4 == 1 ? l4.y : r % 4 == 2 ? l4.z : l4.w;
+        pr[r] = fast_exp2(EXACT ? fmaf(s[r], c, -L2r) : s[r] * c);
         if (MASKED) {
           const int qi = 32 * qt + tile_row_of(r, hh);
           if (!(qi < T && (!CAUSAL || ri <= qi))) pr[r] = 0.f;

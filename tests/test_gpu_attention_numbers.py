@@ -69,19 +69,23 @@ def gradients(p, q, k, v, do, lse):
 
 
 @pytest.mark.parametrize("eps", EPS)
+@pytest.mark.parametrize("score", [0, 13])
 @pytest.mark.parametrize("dh,heads,T", SHAPES)
-def test_backward_probabilities(dh, heads, T, eps):
-    """Scores of zero and row statistics of BASE and BASE + eps in turn, gradients of +1 and -1 in turn: dv sums P, dk sums dS."""
+def test_backward_probabilities(dh, heads, T, score, eps):
+    """Equal scores (in base 2) and row statistics BASE and BASE + eps above them in turn, gradients of +1 and -1 in turn: dv sums P,
+    dk sums dS."""
     p = block(dh, heads, T)
     unit = torch.zeros((T, dh), device="cuda")
     unit[:, 0] = 1
     sign = torch.ones((T, 1), device="cuda")
     sign[1::2] = -1
-    lse = torch.full((T,), BASE, device="cuda")
+    k = unit * bf(score * np.log(2) * np.sqrt(dh))
+    t = float(k[0, 0]) / np.sqrt(dh) / np.log(2)
+    lse = torch.full((T,), t + BASE, device="cuda")
     lse[1::2] += eps
-    dq, dk, dv = gradients(p, unit, unit * 0, unit, unit * sign, lse)
-    lo, hi = (float(t) for t in lse[:2])
-    want = (T // 2) * (2.0 ** -lo - 2.0 ** -hi)
+    dq, dk, dv = gradients(p, unit, k, unit, unit * sign, lse)
+    lo, hi = (float(x) for x in lse[:2])
+    want = (T // 2) * (2.0 ** (t - lo) - 2.0 ** (t - hi))
     assert np.abs(dv[..., 0] / want - 1).max() < TOL, np.abs(dv[..., 0] / want - 1).max()
     assert np.abs(dk[..., 0] / (want / np.sqrt(dh)) - 1).max() < TOL, np.abs(dk[..., 0] / (want / np.sqrt(dh)) - 1).max()
 
