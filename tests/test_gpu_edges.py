@@ -128,12 +128,12 @@ def test_chains_along_time_in_a_graph(B, kind, H):
 
 
 # An infinity in the last block of 32 channels, at widths whose quarters of the contraction reach past it: saturated gates
-# stay finite, and gradients are infinite, not NaN.  One step, so that what follows does not mix the two.
+# stay finite, and gradients are infinite, not NaN.  It meets one step's product, so that what follows does not mix the two.
 @pytest.mark.parametrize("kind", ["rnn", "token", "gated", "lstm", "gru"])
 @pytest.mark.parametrize("H_", [24, 72, 264, 600])
 def test_chains_along_time_with_infinities(B, kind, H_):
     import torch
-    w = _chain(kind, 1, 5, H_)
+    w = _chain(kind, 2, 5, H_)
     inp, st, _, p = _setup(B, w)
     c = w.d - 3                                    # (the LSTM's hidden part comes second)
     inp["x0"][2, c] = np.inf
