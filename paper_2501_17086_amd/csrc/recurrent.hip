@@ -189,34 +189,44 @@ __device__ __forceinline__ float sigmoid1(float a) { return 1.f / (1.f + expf(-a
 
 enum { K_RNN = 0, K_GATED = 1, K_LSTM = 2, K_GRU = 3 };
 
-// This workgroup's group and member number, in the order of starting; true once the whole group has started, false if its first
-// member is to go on alone.  The counter of the launch, then a word per group.  (One thread divides by wpg, in vector registers;
-// the kernels do not divide by it again, for the compiler would take this quotient's reciprocal there, leave the result in a
-// vector register and put every operand load whose address depends on it into a loop over the lanes: 11 % on the GRU.)
-__device__ __forceinline__ bool take_place(const RecArgs& a, int wpg, int& group, int& member) {
-  __shared__ int place[3];
+// This workgroup's group and member number, in the order of starting.  The counter of the launch, then a word per group: how many
+// of it have started (`started`, thread 0: with this one), and whether it has been given up.  (One thread divides by wpg, in
+// vector registers; the kernels do not divide by it again, for the compiler would take this quotient's reciprocal there, leave
+// the result in a vector register and put every operand load whose address depends on it into a loop over the lanes: 11 % on
+// the GRU.)
+__device__ __forceinline__ void take_place(const RecArgs& a, int wpg, int& group, int& member, unsigned& started) {
+  __shared__ int place[2];
+  started = 0;
   if (threadIdx.x == 0) {
-    const int n = atomicAdd(a.counter, 1), limit = a.wait != REC_WAIT ? 0 : a.L < REC_SPIN_LIMIT / REC_ARRIVE_POLLS ? (int)a.L * REC_ARRIVE_POLLS : REC_SPIN_LIMIT;
-    const int g = n / wpg;
-    unsigned* word = reinterpret_cast<unsigned*>(a.counter) + 1 + g;
-    unsigned w = atomicAdd(word, 1u) + 1u;
+    const int n = atomicAdd(a.counter, 1), g = n / wpg;
+    started = atomicAdd(reinterpret_cast<unsigned*>(a.counter) + 1 + g, 1u) + 1u;
+    place[0] = g;
+    place[1] = n - g * wpg;
+  }
+  __syncthreads();
+  group = __builtin_amdgcn_readfirstlane(place[0]);
+  member = __builtin_amdgcn_readfirstlane(place[1]);
+}
+// true once the whole group has started, false if its first member is to go on alone
+__device__ __forceinline__ bool all_started(const RecArgs& a, int wpg, int group, unsigned started) {
+  __shared__ int given_up;
+  if (threadIdx.x == 0) {
+    const int limit = a.wait != REC_WAIT ? 0 : a.L < REC_SPIN_LIMIT / REC_ARRIVE_POLLS ? (int)a.L * REC_ARRIVE_POLLS : REC_SPIN_LIMIT;
+    unsigned* word = reinterpret_cast<unsigned*>(a.counter) + 1 + group;
+    unsigned w = started;
     for (int polls = 0; !(w & REC_ALONE) && w != (unsigned)wpg; ++polls) {
       if (polls < limit) {
-        __builtin_amdgcn_s_sleep(8);
+        __builtin_amdgcn_s_sleep(2);
         w = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       } else {                           // (fails only where another workgroup has started, or given up, in between)
         const unsigned was = atomicCAS(word, w, w | REC_ALONE);
         w = was == w ? w | REC_ALONE : was;
       }
     }
-    place[0] = g;
-    place[1] = n - g * wpg;
-    place[2] = (w & REC_ALONE) != 0;
+    given_up = (w & REC_ALONE) != 0;
   }
   __syncthreads();
-  group = __builtin_amdgcn_readfirstlane(place[0]);
-  member = __builtin_amdgcn_readfirstlane(place[1]);
-  return __builtin_amdgcn_readfirstlane(place[2]) == 0;
+  return __builtin_amdgcn_readfirstlane(given_up) == 0;
 }
 
 // Which channels and rows a thread has in the elementwise part: two channels (from c on) of RT rows.
@@ -244,10 +254,10 @@ __device__ __forceinline__ void members(int own, int wpg, F f) {
   for (int m = 0; m < wpg; ++m) f(m);
 }
 
-// ALONE: one workgroup plays every member of its group; what a member keeps in registers from phase to phase it reads again
+// False, with nothing done, if the group has been given up.  ALONE: one workgroup plays every member of its group; what a member keeps in registers from phase to phase it reads again
 // (the thread that wrote it reads it).
 template <int KIND, int KQ, int RT, bool ALONE, int SLOTS>
-__device__ __forceinline__ void forward_chain(const RecArgs& a, const Ring& ring, int own, Partials<RT, SLOTS>& part) {
+__device__ __forceinline__ bool forward_chain(const RecArgs& a, const Ring& ring, int own, unsigned started, Partials<RT, SLOTS>& part) {
   constexpr int UNITS = KIND == K_LSTM ? 4 : KIND == K_GRU ? 3 : 2;
   constexpr bool TWO = KIND == K_RNN || KIND == K_GRU;       // two dependent products per step
   const int tid = threadIdx.x, lane = tid & 63;
@@ -264,6 +274,7 @@ __device__ __forceinline__ void forward_chain(const RecArgs& a, const Ring& ring
   if (!ALONE) {
 #pragma unroll
     for (int u = 0; u < UNITS; ++u) weights(u, own);
+    if (!all_started(a, ring.wpg, ring.group, started)) return false;     // (while the weights are on their way)
   }
   Operand<KQ, RT> in;
   // exchanged: unit 0 the (hidden) state, unit 1 the RNN's inner state or the GRU's r (.) x
@@ -428,6 +439,7 @@ __device__ __forceinline__ void forward_chain(const RecArgs& a, const Ring& ring
       });
     }
   }
+  return true;
 }
 
 template <int KIND, int KQ, int RT>
@@ -435,16 +447,17 @@ __global__ __launch_bounds__(256, 1) void rec_forward_kernel(RecArgs a, int wpg,
   constexpr int SLOTS = KIND == K_LSTM ? 4 : KIND == K_RNN ? 1 : 2;
   __shared__ __attribute__((aligned(16))) Partials<RT, SLOTS> part;
   int group, member;
-  const bool together = take_place(a, wpg, group, member);
+  unsigned started;
+  take_place(a, wpg, group, member, started);
   const Ring ring = {reinterpret_cast<char*>(a.ring), wpg, groups, RT, group};
-  if (together) forward_chain<KIND, KQ, RT, false>(a, ring, member, part);
-  else if (member == 0) forward_chain<KIND, KQ, RT, true>(a, ring, member, part);
+  if (!forward_chain<KIND, KQ, RT, false>(a, ring, member, started, part) && member == 0)
+    forward_chain<KIND, KQ, RT, true>(a, ring, member, started, part);
 }
 
 // Exact backpropagation: g[l] = (da_l W1 + what goes past the product) (+ e_l) + lambda_l (.) g[l+1], l = L-1 .. 0; da as in
 // gated_cell.hip.  Weights transposed: Wt1 = W1^T [H][F] (GRU: [W_z; W_r]^T [H][2H]), Wt2 = W2^T [F][D] (RNN) or W_n^T [H][H].
 template <int KIND, int KQ, int RT, bool ALONE>
-__device__ __forceinline__ void backward_chain(const RecArgs& a, const Ring& ring, int own, Partials<RT, 1>& part) {
+__device__ __forceinline__ bool backward_chain(const RecArgs& a, const Ring& ring, int own, unsigned started, Partials<RT, 1>& part) {
   constexpr int UNITS = KIND == K_LSTM ? 4 : KIND == K_GRU ? 3 : 2;
   constexpr bool TWO = KIND == K_RNN || KIND == K_GRU;       // two dependent products per step
   constexpr int U0 = TWO ? 1 : 0;                            // first unit of the (second) product with W1
@@ -462,6 +475,7 @@ __device__ __forceinline__ void backward_chain(const RecArgs& a, const Ring& rin
   if (!ALONE) {
 #pragma unroll
     for (int u = 0; u < UNITS; ++u) weights(u, own);
+    if (!all_started(a, ring.wpg, ring.group, started)) return false;     // (while the weights are on their way)
   }
   Operand<KQ, RT> in;
   // exchanged: the cells' da, a unit per gate; the RNN's da is unit 0 and its state gradient unit 1
@@ -531,9 +545,12 @@ __device__ __forceinline__ void backward_chain(const RecArgs& a, const Ring& rin
       }
     };
     // the LSTM's gradient at the cell state through the hidden part
-    auto through_h = [&](int rt) __attribute__((always_inline)) {
-      const float2 og = un2(zw[rt][2]), cn = un2(xn[rt]);
-      const float2 tc = map2([&](int i) { return tanhf(at2(cn, i)); });
+    auto tanh_c = [&](int rt) __attribute__((always_inline)) {
+      const float2 cn = un2(xn[rt]);
+      return map2([&](int i) { return tanhf(at2(cn, i)); });
+    };
+    auto through_h = [&](int rt, float2 tc) __attribute__((always_inline)) {
+      const float2 og = un2(zw[rt][2]);
       return map2([&](int i) { return at2(gs[rt], i) * at2(og, i) * (1.f - at2(tc, i) * at2(tc, i)); });
     };
     // what the cells' elementwise parts leave for the products
@@ -548,9 +565,8 @@ __device__ __forceinline__ void backward_chain(const RecArgs& a, const Ring& rin
           publish(ring, 0, l, rt, member, at.on[rt] ? pk(du) : 0u);
           publish(ring, 1, l, rt, member, at.on[rt] ? pk(dc) : 0u);
         } else if (KIND == K_LSTM) {
-          const float2 ig = un2(zw[rt][0]), fg = un2(zw[rt][1]), og = un2(zw[rt][2]), gg = un2(zw[rt][3]), cn = un2(xn[rt]);
-          const float2 tc = map2([&](int i) { return tanhf(at2(cn, i)); });
-          const float2 th = through_h(rt);
+          const float2 ig = un2(zw[rt][0]), fg = un2(zw[rt][1]), og = un2(zw[rt][2]), gg = un2(zw[rt][3]);
+          const float2 tc = tanh_c(rt), th = through_h(rt, tc);
           pastc[rt] = make_float2(th.x * fg.x, th.y * fg.y);
           const float2 dct = make_float2(gc[rt].x + th.x, gc[rt].y + th.y);
           const float2 di = map2([&](int i) { return at2(dct, i) * at2(gg, i) * at2(ig, i) * (1.f - at2(ig, i)); });
@@ -627,7 +643,7 @@ __device__ __forceinline__ void backward_chain(const RecArgs& a, const Ring& rin
       for (int rt = 0; rt < RT; ++rt) {
         if (KIND != K_GRU) past[rt] = make_float2(0.f, 0.f);
         if (KIND == K_LSTM && ALONE) {
-          const float2 th = through_h(rt), fg = un2(zw[rt][1]);
+          const float2 th = through_h(rt, tanh_c(rt)), fg = un2(zw[rt][1]);
           pastc[rt] = make_float2(th.x * fg.x, th.y * fg.y);
         }
       }
@@ -663,16 +679,18 @@ __device__ __forceinline__ void backward_chain(const RecArgs& a, const Ring& rin
       set ^= 1;
     });
   }
+  return true;
 }
 
 template <int KIND, int KQ, int RT>
 __global__ __launch_bounds__(256, 1) void rec_backward_kernel(RecArgs a, int wpg, int groups) {
   __shared__ __attribute__((aligned(16))) Partials<RT, 1> part;
   int group, member;
-  const bool together = take_place(a, wpg, group, member);
+  unsigned started;
+  take_place(a, wpg, group, member, started);
   const Ring ring = {reinterpret_cast<char*>(a.ring), wpg, groups, RT, group};
-  if (together) backward_chain<KIND, KQ, RT, false>(a, ring, member, part);
-  else if (member == 0) backward_chain<KIND, KQ, RT, true>(a, ring, member, part);
+  if (!backward_chain<KIND, KQ, RT, false>(a, ring, member, started, part) && member == 0)
+    backward_chain<KIND, KQ, RT, true>(a, ring, member, started, part);
 }
 
 // the empty word into every slot (n 16-byte pieces), zeros into the block behind them, the counter at zero and the groups' words
