@@ -254,8 +254,8 @@ __device__ __forceinline__ void members(int own, int wpg, F f) {
   for (int m = 0; m < wpg; ++m) f(m);
 }
 
-// False, with nothing done, if the group has been given up.  ALONE: one workgroup plays every member of its group; what a member keeps in registers from phase to phase it reads again
-// (the thread that wrote it reads it).
+// False, with nothing done, if the group has been given up.  ALONE: one workgroup plays every member of its group; what a member
+// keeps in registers from phase to phase it reads again (the thread that wrote it reads it).
 template <int KIND, int KQ, int RT, bool ALONE, int SLOTS>
 __device__ __forceinline__ bool forward_chain(const RecArgs& a, const Ring& ring, int own, unsigned started, Partials<RT, SLOTS>& part) {
   constexpr int UNITS = KIND == K_LSTM ? 4 : KIND == K_GRU ? 3 : 2;
