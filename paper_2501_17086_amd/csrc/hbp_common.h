@@ -218,10 +218,10 @@ struct RecArgs {
   int* counter;         // device scratch, RECURRENT_COUNTER_BYTES
   void* ring;           // device scratch, recurrent_ring_bytes()
   int wait;             // for the rest of a group to start: REC_WAIT, or (tests) REC_WAIT_NOT: give up at the first look,
-                        // REC_ALONE_ANYHOW: every group's first workgroup goes on alone
+                        // REC_ALONE_ANYHOW: every group's first workgroup goes on alone, REC_ANYWHERE: no groups on one XCD
 };
-enum { REC_WAIT = 0, REC_WAIT_NOT = 1, REC_ALONE_ANYHOW = 2 };
-constexpr size_t RECURRENT_COUNTER_BYTES = 512;
+enum { REC_WAIT = 0, REC_WAIT_NOT = 1, REC_ALONE_ANYHOW = 2, REC_ANYWHERE = 3 };
+constexpr size_t RECURRENT_COUNTER_BYTES = 4096;
 size_t recurrent_ring_bytes();
 bool recurrent_ok(const RecArgs& a);
 hipError_t launch_recurrent(const RecArgs& a, bool forward, hipStream_t s);

@@ -5,31 +5,37 @@
 // hundred KB) but the hand-over between dependent steps: as launches of their own they cost 7 us each.  Here
 //   - a workgroup of four wavefronts owns 32 channels and keeps their rows of every weight matrix in registers for the
 //     whole chain (each wavefront a quarter of the contraction, as operands of v_mfma_f32_16x16x32_bf16);
-//   - the batch is cut into groups of 16 RT rows that never exchange anything; the ceil(width / 32) workgroups of a
-//     group exchange the vectors that the next product contracts over through memory, with device-scope accesses, in
+//   - the batch is cut into groups of 8, 16 or 32 rows that never exchange anything; the ceil(width / 32) workgroups of a
+//     group exchange the vectors that the next product contracts over, past the compute units' own caches, in
 //     the order of the matrix instruction's operand: a workgroup's 32 channels of 16 rows are 1 KB, and a reader takes
 //     16 bytes per lane, consecutive over the wavefront;
+//   - a group's workgroups are on one XCD, and what they exchange stays in its L2: 0.29 us from a store to the load that sees it,
+//     0.46 us between two XCDs.  Every launch brings as many workgroups to each of the eight XCDs (ids are dealt to them in
+//     turn) as a group has; those of an XCD form teams, a team's first workgroup claims a group, and who has none ends;
 //   - there are no flags and no barriers across workgroups: a slot is empty (a word that no result has) until its
 //     owner writes it, and a reader re-reads its operands until that word is gone.  A hand-over is then one store and
 //     one load.  A vector's slots are four deep, one per step in turn: once a workgroup has read the whole of a step's
-//     first vector, every other one has left the step before, and it empties its own slots of that step.  They are
-//     used again four steps later, and what a reader waits for in between was written after the owner had waited
-//     for its own reads, which a wavefront's earlier stores (the emptying among them) precede;
+//     first vector, every other one has left the step before, and it empties its own slots of that step, before it asks for the
+//     next operands.  They are used again four steps later, and what a reader waits for in between was written after the owner
+//     had waited for those operands, which a wavefront's earlier stores (the emptying among them) precede;
 //   - the four quarters of a product are added through LDS (one workgroup barrier per product), and the elementwise
 //     part of the cell runs on the sums, two channels of a row per thread, the state staying in registers.
-// Workgroups take their place in a group in the order they start (a device counter), and a group begins once all of its
-// workgroups have started: from then on each of them keeps running, so that every wait inside the chain ends.  One group of a
-// launch at most is incomplete at any time, and at most 64 workgroups are launched, a quarter of the compute units, so that
-// this is soon the case.  Where it is not, because other kernels hold the compute units, or incomplete groups of many launches
-// (nine or more) hold all of them against each other, a group that has waited for REC_ARRIVE_POLLS polls per step, about as
-// long as the chain takes one workgroup, is left to its first workgroup alone, and the others end.  That one plays all of them in
-// turn, with the same phases, sums and exchange, reading the weights from memory at every step: the same results bit for bit at
-// 0.1 to 0.4 ms a step (width 1024: 60 to 90 times the time of the group).
+// A group begins once all of its workgroups have started: from then on each of them keeps running, so that every wait inside the
+// chain ends.  If a group has not got together on one XCD after a poll per step (other kernels hold its compute units), it is
+// given up, and a second launch, which otherwise ends at once, takes what is left: its workgroups, at most 64 in all, a quarter
+// of the compute units, may be anywhere and exchange through memory.  They take their place in a group in the order they start (a
+// device counter).  One group of a launch at most is incomplete at any time, so that this is soon the case.  Where it is not,
+// because other kernels hold the compute units, or incomplete groups of many launches (nine or more) hold all of them against
+// each other, a group that has waited for REC_ARRIVE_POLLS polls per step, about as long as the chain takes one workgroup, is
+// left to its first workgroup alone, and the others end.  That one plays all of them in turn, reading the weights from memory at
+// every step: 0.1 to 0.4 ms a step (width 1024: 60 to 90 times the time of the group).  The sums have the same order in every
+// form: the same results bit for bit.
 //
-// Measured (1024 steps, batch 32, width 1024): exact backpropagation of the RNN 14.5 -> 3.3 ms, forward of the GRU 20.9 ->
-// 3.7 ms; 1.6 us per dependent product, of which 0.3 us are waiting for data that is not there yet: the rest is one
-// trip to memory for the operand, 16 MFMAs, the sum through LDS and the cell.  Read as 8-byte pieces of the row-major
-// states instead of packed operands the same hand-over took 3.8 us, and a group's workgroups on one XCD did not help.
+// Measured (1024 steps, batch 32, width 1024): exact backpropagation of the RNN 14.5 ms as launches of their own, 3.3 through
+// memory, 1.7 on one XCD with groups of 8 rows; forward of the GRU 20.9, 3.6 and 2.4.  0.8 us per dependent product: about 0.4 from
+// a store to the operands in registers, the rest 16 MFMAs, the sum through LDS and the cell.  Groups of 16 rows: 2.0 ms (a
+// workgroup reads 32 KB per product then, 500 cycles); inputs of a step read when it begins: loads return in order, so the wait
+// for the operands met a trip to memory, 10 % more; per-step addresses in 64 bits and branches around edges: 5 %.
 #include "hbp_common.h"
 
 namespace hbp {
@@ -44,8 +50,14 @@ constexpr int REC_SLOTS = 4;                   // steps a vector's slots are dee
 constexpr int REC_SPIN_LIMIT = 1 << 24;        // polls inside the chain (bounded only so that a fault elsewhere cannot hang it)
 constexpr int REC_ARRIVE_POLLS = 256;          // polls per step for the rest of a group to start
 constexpr unsigned REC_ALONE = 1u << 31;       // in a group's word beside the number of workgroups that have started
+constexpr int REC_PAUSE = 5;                    // times 64 cycles (0: 2.18 ms for 1024 steps of the RNN, 3: 2.04, 5: 2.02, 8: 2.18)
 constexpr int REC_COLS = 32;                   // channels per workgroup
 constexpr int REC_MAX_WG = 64;
+constexpr int REC_XCDS = 16;                   // XCDs that a launch may meet (the chip has eight)
+constexpr int REC_TEAMS = 32;                  // teams of workgroups on one of them
+constexpr int REC_LOCAL_GROUPS = 256;
+constexpr int REC_LOCAL_POLLS = 1;             // polls per step for the rest of a team to start
+constexpr int HW_XCC_ID = 20 | (3 << 11);      // hwreg(HW_REG_XCC_ID), its four bits
 constexpr int REC_UNITS = 4;                   // exchanged vectors at most
 constexpr int RED_LD = 36;                     // floats per row of a partial block in LDS
 
@@ -67,90 +79,168 @@ struct Weights {
   }
 };
 
-// The exchanged vectors of a launch: unit u, step slot, group, 16-row tile, block of 32 channels -> 1 KB, in which row r
-// and channels 8 q .. 8 q + 7 of the block are the 16 bytes of lane 16 q + r; behind them 1 KB of zeros.
-struct Ring {
+// Everything inside the chain goes through buffer accesses: a lane's place in a row is a 32-bit offset that stays the same, a
+// step's place is in the (scalar) base, and a lane outside the batch or the width has an offset past the end, where loads give
+// zero and stores do nothing: no branches and no address arithmetic per step.
+typedef unsigned uint4v __attribute__((ext_vector_type(4)));
+typedef unsigned uint2v __attribute__((ext_vector_type(2)));
+constexpr unsigned REC_OUTSIDE = 0x80000000u;
+// n bytes from p on
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer(const void* p, long n) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)n, 0x00027000);
+}
+// a step's n bytes of an array along time (n = 0: there is none)
+struct Rows {
   char* base;
-  int wpg, groups, rts, group;
-  __device__ __forceinline__ unsigned at(int u, long step, int rt, int block) const {
-    return (unsigned)((((u * REC_SLOTS + (int)(step & (REC_SLOTS - 1))) * groups + group) * rts + rt) * wpg + block) * 1024u;
+  long n;
+  __device__ __forceinline__ __amdgpu_buffer_rsrc_t buf() const { return buffer(base, n); }
+  __device__ __forceinline__ void next(bool go) { base += go ? n : 0; }
+  __device__ __forceinline__ void before(bool go) { base -= go ? n : 0; }
+};
+// (an offset as it is in a register: not computed again, and not behind a branch, where it is used)
+__device__ __forceinline__ unsigned kept(unsigned v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+
+// Rows per group and how a workgroup's threads share them: RT tiles of 16 rows, or (RT = 0) half a tile.
+//
+// The exchanged vectors of a launch: unit u, step slot, group, 16-row tile, block of 32 channels -> 1 KB, in which row r
+// and channels 8 q .. 8 q + 7 of the block are the 16 bytes of lane 16 q + r.  Half a tile: a pair of blocks is 1 KB, the even
+// one's row r is lane 16 q + r and the odd one's lane 16 q + 8 + r: one load brings two blocks.
+// LOCAL: the group is on one XCD, whose L2 is where its stores meet its loads; otherwise stores go to memory.
+template <int RT> constexpr int rec_tiles() { return RT ? RT : 1; }
+template <int RT> constexpr int rec_rows() { return RT ? 16 * RT : 8; }
+template <int RT> constexpr int rec_block() { return RT ? 1024 : 512; }       // bytes of a block
+template <bool LOCAL, int RT>
+struct Ring {
+  __amdgpu_buffer_rsrc_t buf;
+  int wpg, group;
+  int slot, tile, mine;           // bytes of a step's slot of one unit, of a row tile; where the group's part of a slot is
+  unsigned word;                  // where a thread's word of a block is
+  __device__ __forceinline__ Ring(char* base, int wpg_, int groups, int group_)
+      : wpg(wpg_), group(group_) {
+    tile = RT ? wpg * 1024 : (wpg + 1) / 2 * 1024;
+    mine = group * rec_tiles<RT>() * tile;
+    slot = groups * rec_tiles<RT>() * tile;
+    buf = buffer(base, (long)REC_UNITS * REC_SLOTS * slot);
+    const int t = threadIdx.x;
+    word = kept(RT ? t * 4 : t < 128 ? (t >> 5) * 256 + (t & 31) * 4 : REC_OUTSIDE);
   }
-  __device__ __forceinline__ unsigned zeros() const { return (unsigned)(REC_UNITS * REC_SLOTS * groups * rts * wpg) * 1024u; }
+  __device__ __forceinline__ int at(int u, long step, int rt, int block) const {
+    return (u * REC_SLOTS + ((int)step & (REC_SLOTS - 1))) * slot + mine + rt * tile + (RT ? block * 1024 : (block >> 1) * 1024 + (block & 1) * 128);
+  }
+  __device__ __forceinline__ void put(int place, unsigned w) const {
+    __builtin_amdgcn_raw_buffer_store_b32(w, buf, (int)word, place, LOCAL ? 0 : 16);
+  }
 };
 
-// This wavefront's operands of 16 RT rows out of a vector: its quarter of the blocks.  Past the last one it reads zeros: the
+// This wavefront's operands of the group's rows out of a vector: its quarter of the blocks.  Past the last one it has zeros: the
 // weights there are zeros too, but against a repeated block they would turn an infinity of its into NaN.
 template <int KQ, int RT>
 struct Operand {
-  bf16x8 a[RT][KQ];
-  // re-reads until no word is empty any more
-  __device__ __forceinline__ void load(const Ring& ring, int u, long step, int wave, int lane, bool& dead) {
-    typedef unsigned uint4v __attribute__((ext_vector_type(4)));
-    const __amdgpu_buffer_rsrc_t rsrc =
-        __builtin_amdgcn_make_buffer_rsrc(ring.base, 0, ring.zeros() + 1024, 0x00027000);
-    for (int spins = 0;; ++spins) {
-      uint4v q[RT][KQ];
-      asm volatile("" ::: "memory");           // (every pass reads again)
+  static constexpr int TILES = rec_tiles<RT>(), LOADS = RT ? KQ : KQ / 2;
+  uint4v q[TILES][LOADS];
+  unsigned off[LOADS];
+  template <bool LOCAL>
+  __device__ __forceinline__ void set(const Ring<LOCAL, RT>& ring, int wave, int lane) {
 #pragma unroll
-      for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-        for (int s = 0; s < KQ; ++s) {
-          const int kb = wave * KQ + s;
-          // (a plain 16-byte load at device scope: sc1; every 4-byte word of it is either empty or whole)
-          q[rt][s] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane * 16, (int)(kb < ring.wpg ? ring.at(u, step, rt, kb) : ring.zeros()), 16);
-        }
-      unsigned top = 0;
-#pragma unroll
-      for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-        for (int s = 0; s < KQ; ++s) {
-          top = max(max(top, q[rt][s].x), q[rt][s].y);
-          top = max(max(top, q[rt][s].z), q[rt][s].w);
-          a[rt][s] = __builtin_bit_cast(bf16x8, q[rt][s]);
-        }
-      if (dead || !__any(top == REC_EMPTY)) return;
-      if (spins >= REC_SPIN_LIMIT) dead = true;
+    for (int s = 0; s < LOADS; ++s) {
+      const int n = wave * LOADS + s, block = RT ? n : 2 * n + ((lane >> 3) & 1);
+      off[s] = kept(block < ring.wpg ? n * 1024 + lane * 16 : REC_OUTSIDE);
     }
+  }
+  // The first time after a short pause: what the other workgroups publish at the same time as this one takes about that long to
+  // be seen, and operands read too early are read twice.
+  template <bool LOCAL, bool AGAIN = false>
+  __device__ __forceinline__ void ask(const Ring<LOCAL, RT>& ring, int u, long step) {
+    if (!AGAIN) __builtin_amdgcn_s_sleep(REC_PAUSE);
+    asm volatile("" ::: "memory");             // (every pass reads again)
+#pragma unroll
+    for (int s = 0; s < LOADS; ++s)
+#pragma unroll
+      for (int rt = 0; rt < TILES; ++rt)
+        // (a plain 16-byte load past the compute unit's own cache: sc1; every 4-byte word of it is either empty or whole)
+        q[rt][s] = __builtin_amdgcn_raw_buffer_load_b128(ring.buf, (int)off[s], ring.at(u, step, rt, 0), 16);
+  }
+  // block s (half a tile: with its neighbour; what the weights of the one make of the other's rows is never looked at)
+  __device__ __forceinline__ bf16x8 a(int rt, int s) const { return __builtin_bit_cast(bf16x8, q[rt][RT ? s : s / 2]); }
+  __device__ __forceinline__ bool missing() const {
+    unsigned top = 0;
+#pragma unroll
+    for (int s = 0; s < LOADS; ++s)
+#pragma unroll
+      for (int rt = 0; rt < TILES; ++rt) {
+        top = max(max(top, q[rt][s].x), q[rt][s].y);
+        top = max(max(top, q[rt][s].z), q[rt][s].w);
+      }
+    return __any(top == REC_EMPTY);
+  }
+  // until no word of what was asked for is empty any more, all of it is read again.  (Each block waited for by itself, and only
+  // what was missing read again, or the products begun on every pass: 10 to 20 % slower.)  The first look stands by itself, so
+  // that it does not wait for what was issued after the operands, as it would at the head of the loop.
+  template <bool LOCAL>
+  __device__ __forceinline__ void wait(const Ring<LOCAL, RT>& ring, int u, long step, bool& dead) {
+    if (dead || !missing()) return;
+    int spins = 0;
+    do {
+      if (++spins >= REC_SPIN_LIMIT) dead = true;
+      ask<LOCAL, true>(ring, u, step);
+    } while (missing() && !dead);
   }
 };
 
-// acc += this wavefront's quarter of the product
-template <int KQ, int RT>
-__device__ __forceinline__ void multiply(float4v (&acc)[RT][2], const Weights<KQ>& w, const Operand<KQ, RT>& o) {
-#pragma unroll
-  for (int s = 0; s < KQ; ++s)
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-      for (int ct = 0; ct < 2; ++ct)
-        // weights first: lane l, element r <-> channel 16 ct + 4 (l / 16) + r, row l % 16
-        acc[rt][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w.w[s][ct], o.a[rt][s], acc[rt][ct], 0, 0, 0);
-}
+// A wavefront's quarter of a product: the blocks of even and of odd number summed apart, in every form of the kernel
 template <int RT>
-__device__ __forceinline__ void clear(float4v (&acc)[RT][2]) {
+struct Product {
+  float4v v[2][RT ? RT : 1][2];
+  __device__ __forceinline__ void clear() {
 #pragma unroll
-  for (int rt = 0; rt < RT; ++rt)
+    for (int i = 0; i < 4 * (RT ? RT : 1); ++i) v[i & 1][i >> 2][(i >> 1) & 1] = float4v{0.f, 0.f, 0.f, 0.f};
+  }
+};
+// acc += block s (weights first: lane l, element r <-> channel 16 ct + 4 (l / 16) + r, row l % 16)
+template <int KQ, int RT>
+__device__ __forceinline__ void multiply(Product<RT>& acc, const Weights<KQ>& w, const Operand<KQ, RT>& o, int s) {
 #pragma unroll
-    for (int ct = 0; ct < 2; ++ct) acc[rt][ct] = float4v{0.f, 0.f, 0.f, 0.f};
-}
-
-// Partial products of the four wavefronts, two sets used in turn (a set is rewritten two barriers after it was read).
-template <int RT, int SLOTS>
-struct Partials { float v[2][SLOTS][4][16 * RT][RED_LD]; };
-template <int RT, int SLOTS>
-__device__ __forceinline__ void put(Partials<RT, SLOTS>& p, int set, int slot, const float4v (&acc)[RT][2], int wave, int lane) {
-#pragma unroll
-  for (int rt = 0; rt < RT; ++rt)
+  for (int rt = 0; rt < (RT ? RT : 1); ++rt)
 #pragma unroll
     for (int ct = 0; ct < 2; ++ct)
-      *reinterpret_cast<float4v*>(&p.v[set][slot][wave][16 * rt + (lane & 15)][16 * ct + 4 * (lane >> 4)]) = acc[rt][ct];
+      acc.v[s & 1][rt][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w.w[s][ct], o.a(rt, s), acc.v[s & 1][rt][ct], 0, 0, 0);
+}
+template <int KQ, int RT>
+__device__ __forceinline__ void multiply_all(Product<RT>& acc, const Weights<KQ>& w, const Operand<KQ, RT>& o) {
+#pragma unroll
+  for (int s = 0; s < KQ; ++s) multiply(acc, w, o, s);
+}
+
+// Partial products of the four wavefronts, two sets used in turn (a set is rewritten two barriers after it was read).  Half a
+// tile: its 8 rows' even blocks in rows 0 to 7, the odd ones in rows 8 to 15.
+template <int RT, int SLOTS>
+struct Partials { float v[2][SLOTS][4][16 * (RT ? RT : 1)][RED_LD]; };
+template <int RT, int SLOTS>
+__device__ __forceinline__ void put(Partials<RT, SLOTS>& p, int set, int slot, const Product<RT>& acc, int wave, int lane) {
+#pragma unroll
+  for (int rt = 0; rt < (RT ? RT : 1); ++rt)
+#pragma unroll
+    for (int ct = 0; ct < 2; ++ct) {
+      float4v t;
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        t[i] = RT ? acc.v[0][rt][ct][i] + acc.v[1][rt][ct][i] : (lane & 8) ? acc.v[1][rt][ct][i] : acc.v[0][rt][ct][i];
+      *reinterpret_cast<float4v*>(&p.v[set][slot][wave][16 * rt + (lane & 15)][16 * ct + 4 * (lane >> 4)]) = t;
+    }
 }
 template <int RT, int SLOTS>
 __device__ __forceinline__ float2 get(const Partials<RT, SLOTS>& p, int set, int slot, int row, int col) {
   float2 s = make_float2(0.f, 0.f);
 #pragma unroll
   for (int w = 0; w < 4; ++w) {
-    const float2 t = *reinterpret_cast<const float2*>(&p.v[set][slot][w][row][col]);
+    float2 t = *reinterpret_cast<const float2*>(&p.v[set][slot][w][row][col]);
+    if (RT == 0) {
+      const float2 o = *reinterpret_cast<const float2*>(&p.v[set][slot][w][row + 8][col]);
+      t.x += o.x; t.y += o.y;
+    }
     s.x += t.x; s.y += t.y;
   }
   return s;
@@ -165,22 +255,19 @@ __device__ __forceinline__ void meet() {
 
 // two channels of a row
 __device__ __forceinline__ float2 un2(unsigned w) { return make_float2(__uint_as_float(w << 16), __uint_as_float(w & 0xFFFF0000u)); }
-__device__ __forceinline__ unsigned ld2(const bf16_t* p) { return *reinterpret_cast<const unsigned*>(p); }
-__device__ __forceinline__ float2 ldf2(const float* p) { return *reinterpret_cast<const float2*>(p); }
 __device__ __forceinline__ unsigned pk(float2 v) { return pack_bf16x2(v.x, v.y); }
-__device__ __forceinline__ void st2(bf16_t* p, unsigned w) { *reinterpret_cast<unsigned*>(p) = w; }
-// for other workgroups: device scope, and never the empty word (a pair of NaNs of that pattern changes its first sign).
-// Thread t writes word t of its workgroup's block.
-__device__ __forceinline__ void publish(const Ring& ring, int u, long step, int rt, int member, unsigned w) {
-  __hip_atomic_store(reinterpret_cast<unsigned*>(ring.base + ring.at(u, step, rt, member)) + threadIdx.x,
-                     w == REC_EMPTY ? 0xFFFF7FFFu : w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+__device__ __forceinline__ unsigned bld2(__amdgpu_buffer_rsrc_t b, unsigned off, int more = 0) { return __builtin_amdgcn_raw_buffer_load_b32(b, (int)off, more, 0); }
+__device__ __forceinline__ float2 bldf2(__amdgpu_buffer_rsrc_t b, unsigned off, int more = 0) {
+  return __builtin_bit_cast(float2, (uint2v)__builtin_amdgcn_raw_buffer_load_b64(b, (int)off, more, 0));
 }
-template <int RT>
-__device__ __forceinline__ void empty(const Ring& ring, int u, long step, int member) {
+__device__ __forceinline__ void bst2(unsigned w, __amdgpu_buffer_rsrc_t b, unsigned off, int more = 0) { __builtin_amdgcn_raw_buffer_store_b32(w, b, (int)off, more, 0); }
+// for other workgroups, at ring.at(...): never the empty word (a pair of NaNs of that pattern changes its first sign)
+template <bool LOCAL, int RT>
+__device__ __forceinline__ void publish(const Ring<LOCAL, RT>& ring, int place, unsigned w) { ring.put(place, w == REC_EMPTY ? 0xFFFF7FFFu : w); }
+template <bool LOCAL, int RT>
+__device__ __forceinline__ void empty(const Ring<LOCAL, RT>& ring, int u, long step, int member) {
 #pragma unroll
-  for (int rt = 0; rt < RT; ++rt)
-    __hip_atomic_store(reinterpret_cast<unsigned*>(ring.base + ring.at(u, step, rt, member)) + threadIdx.x, REC_EMPTY,
-                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  for (int rt = 0; rt < rec_tiles<RT>(); ++rt) ring.put(ring.at(u, step, rt, member), REC_EMPTY);
 }
 template <typename F>
 __device__ __forceinline__ float2 map2(F f) { return make_float2(f(0), f(1)); }
@@ -189,30 +276,71 @@ __device__ __forceinline__ float sigmoid1(float a) { return 1.f / (1.f + expf(-a
 
 enum { K_RNN = 0, K_GATED = 1, K_LSTM = 2, K_GRU = 3 };
 
-// This workgroup's group and member number, in the order of starting.  The counter of the launch, then a word per group: how many
-// of it have started (`started`, thread 0: with this one), and whether it has been given up.  (One thread divides by wpg, in
-// vector registers; the kernels do not divide by it again, for the compiler would take this quotient's reciprocal there, leave
-// the result in a vector register and put every operand load whose address depends on it into a loop over the lanes: 11 % on
-// the GRU.)
-__device__ __forceinline__ void take_place(const RecArgs& a, int wpg, int& group, int& member, unsigned& started) {
+// The words that a launch's workgroups find their places with, all zero before it
+struct PlaceWords {
+  int ticket;                              // workgroups of the launch that may be anywhere, in the order of starting
+  unsigned group[REC_MAX_WG];              // and per group how many of them have started, and whether it has been given up
+  unsigned local[REC_LOCAL_GROUPS];        // the same of the launch with groups on one XCD each
+  int claimed;                             // groups that have an XCD
+  int on_xcd[REC_XCDS];                    // workgroups started on an XCD
+  int team[REC_XCDS][REC_TEAMS];           // the group of the XCD's workgroups wpg t .. wpg t + wpg - 1, plus one
+};
+static_assert(sizeof(PlaceWords) <= RECURRENT_COUNTER_BYTES, "the words' place in the workspace");
+
+// This workgroup's group and member number (group -1: none, it ends) and how many of the group have started (`started`, thread 0:
+// with this one).  LOCAL: the workgroups of an XCD form teams in the order of starting; the first of a team claims the next
+// group.  Otherwise groups are filled in the order of starting, those that the other launch has done being left out.  (One thread
+// divides by wpg, in vector registers; the kernels do not divide by it again, for the compiler would take this quotient's
+// reciprocal there, leave the result in a vector register and put every operand load whose address depends on it into a loop
+// over the lanes: 11 % on the GRU.)
+template <bool LOCAL>
+__device__ __forceinline__ void take_place(const RecArgs& a, int wpg, int groups, int per, int locals, int& group, int& member, unsigned& started) {
   __shared__ int place[2];
   started = 0;
   if (threadIdx.x == 0) {
-    const int n = atomicAdd(a.counter, 1), g = n / wpg;
-    started = atomicAdd(reinterpret_cast<unsigned*>(a.counter) + 1 + g, 1u) + 1u;
+    PlaceWords* w = reinterpret_cast<PlaceWords*>(a.counter);
+    int g = -1, m = 0;
+    if (LOCAL) {
+      const int xcd = (int)__builtin_amdgcn_s_getreg(HW_XCC_ID) & (REC_XCDS - 1);
+      const int n = atomicAdd(&w->on_xcd[xcd], 1), t = n / wpg;
+      m = n - t * wpg;
+      if (t < REC_TEAMS) {
+        int c;
+        if (m == 0) {
+          c = atomicAdd(&w->claimed, 1) + 1;
+          __hip_atomic_store(&w->team[xcd][t], c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        } else {                           // (its first workgroup has started, and claims without waiting)
+          while ((c = __hip_atomic_load(&w->team[xcd][t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == 0) __builtin_amdgcn_s_sleep(1);
+        }
+        g = c <= groups ? c - 1 : -1;
+      }
+      if (g >= 0) started = atomicAdd(&w->local[g], 1u) + 1u;
+    } else {
+      const int n = atomicAdd(&w->ticket, 1);
+      g = n / wpg;
+      m = n - g * wpg;
+      bool done = locals > 0;
+      for (int i = g * per; i < g * per + per && i < locals; ++i)
+        done = done && __hip_atomic_load(&w->local[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)wpg;
+      if (done) g = -1;
+      else started = atomicAdd(&w->group[g], 1u) + 1u;
+    }
     place[0] = g;
-    place[1] = n - g * wpg;
+    place[1] = m;
   }
   __syncthreads();
   group = __builtin_amdgcn_readfirstlane(place[0]);
   member = __builtin_amdgcn_readfirstlane(place[1]);
 }
-// true once the whole group has started, false if its first member is to go on alone
+// true once the whole group has started, false if it has been given up
+template <bool LOCAL>
 __device__ __forceinline__ bool all_started(const RecArgs& a, int wpg, int group, unsigned started) {
   __shared__ int given_up;
   if (threadIdx.x == 0) {
-    const int limit = a.wait != REC_WAIT ? 0 : a.L < REC_SPIN_LIMIT / REC_ARRIVE_POLLS ? (int)a.L * REC_ARRIVE_POLLS : REC_SPIN_LIMIT;
-    unsigned* word = reinterpret_cast<unsigned*>(a.counter) + 1 + group;
+    constexpr int POLLS = LOCAL ? REC_LOCAL_POLLS : REC_ARRIVE_POLLS;
+    const int limit = a.wait == REC_WAIT_NOT || a.wait == REC_ALONE_ANYHOW ? 0 : a.L < REC_SPIN_LIMIT / POLLS ? (int)a.L * POLLS : REC_SPIN_LIMIT;
+    PlaceWords* words = reinterpret_cast<PlaceWords*>(a.counter);
+    unsigned* word = LOCAL ? &words->local[group] : &words->group[group];
     unsigned w = started;
     for (int polls = 0; !(w & REC_ALONE) && w != (unsigned)wpg; ++polls) {
       if (polls < limit) {
@@ -229,20 +357,31 @@ __device__ __forceinline__ bool all_started(const RecArgs& a, int wpg, int group
   return __builtin_amdgcn_readfirstlane(given_up) == 0;
 }
 
-// Which channels and rows a thread has in the elementwise part: two channels (from c on) of RT rows.
+// Which channels and rows a thread has in the elementwise part: two channels of a row per tile (half a tile: the first two
+// wavefronts, 128 threads).
 template <int RT>
 struct Place {
-  int row[RT];            // (past the batch: its last row, nothing of it is stored)
-  int c;
-  bool on[RT], on_f[RT];  // inside the state, inside the inner state
-  __device__ __forceinline__ void set(int group, int member, int N, int width, int width_f) {
-    c = member * REC_COLS + 8 * (threadIdx.x >> 6) + 2 * (threadIdx.x & 3);
+  static constexpr int TILES = rec_tiles<RT>();
+  int row, col;                                       // in a tile, among the workgroup's channels
+  bool on[TILES], on_f[TILES];                        // inside the state, inside the inner state
+  unsigned x2[TILES], f2[TILES], f4[TILES], c4[TILES];   // bytes to the place: state and inner state in bf16, inner state and channel in fp32
+  __device__ __forceinline__ Place() {
+    const int t = threadIdx.x;
+    row = RT ? (t >> 2) & 15 : (t >> 2) & 7;
+    col = (RT ? 8 * (t >> 6) : 8 * ((t >> 5) & 3)) + 2 * (t & 3);
+  }
+  __device__ __forceinline__ void set(int group, int member, int N, int D, int F, int width, int width_f) {
+    const int c = member * REC_COLS + col;
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt) {
-      const int r = group * 16 * RT + 16 * rt + ((threadIdx.x >> 2) & 15);
-      on[rt] = r < N && c < width;
-      on_f[rt] = r < N && c < width_f;
-      row[rt] = r < N ? r : N - 1;
+    for (int rt = 0; rt < TILES; ++rt) {
+      const int r = group * rec_rows<RT>() + 16 * rt + row;
+      const bool in = r < N && (RT || threadIdx.x < 128);
+      on[rt] = in && c < width;
+      on_f[rt] = in && c < width_f;
+      x2[rt] = kept(on[rt] ? (unsigned)(r * D + c) * 2 : REC_OUTSIDE);
+      f2[rt] = kept(on_f[rt] ? (unsigned)(r * F + c) * 2 : REC_OUTSIDE);
+      f4[rt] = kept(on_f[rt] ? (unsigned)(r * F + c) * 4 : REC_OUTSIDE);
+      c4[rt] = kept(on[rt] ? (unsigned)c * 4 : REC_OUTSIDE);
     }
   }
 };
@@ -256,10 +395,13 @@ __device__ __forceinline__ void members(int own, int wpg, F f) {
 
 // False, with nothing done, if the group has been given up.  ALONE: one workgroup plays every member of its group; what a member
 // keeps in registers from phase to phase it reads again (the thread that wrote it reads it).
-template <int KIND, int KQ, int RT, bool ALONE, int SLOTS>
-__device__ __forceinline__ bool forward_chain(const RecArgs& a, const Ring& ring, int own, unsigned started, Partials<RT, SLOTS>& part) {
+// A phase publishes what it leaves for others first of all; its results, the emptying of slots and the question for the next
+// phase's operands come after that, in the time that the others' words need to arrive.
+template <int KIND, int KQ, int RT, bool ALONE, bool LOCAL, int SLOTS>
+__device__ __forceinline__ bool forward_chain(const RecArgs& a, const Ring<LOCAL, RT>& ring, int own, unsigned started, Partials<RT, SLOTS>& part) {
   constexpr int UNITS = KIND == K_LSTM ? 4 : KIND == K_GRU ? 3 : 2;
   constexpr bool TWO = KIND == K_RNN || KIND == K_GRU;       // two dependent products per step
+  constexpr int TILES = rec_tiles<RT>();
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int N = (int)a.N, H = (int)a.H, F = (int)a.F, D = (int)a.D;
@@ -274,193 +416,228 @@ __device__ __forceinline__ bool forward_chain(const RecArgs& a, const Ring& ring
   if (!ALONE) {
 #pragma unroll
     for (int u = 0; u < UNITS; ++u) weights(u, own);
-    if (!all_started(a, ring.wpg, ring.group, started)) return false;     // (while the weights are on their way)
+    if (!all_started<LOCAL>(a, ring.wpg, ring.group, started)) return false;     // (while the weights are on their way)
   }
   Operand<KQ, RT> in;
+  in.set(ring, wave, lane);
   // exchanged: unit 0 the (hidden) state, unit 1 the RNN's inner state or the GRU's r (.) x
-  // this thread's share of the elementwise part: two channels of RT rows
-  const int my_row = (tid >> 2) & 15, my_col = 8 * (tid >> 6) + 2 * (tid & 3);
   Place<RT> at;
-  float2 xs[RT];                     // the state's (LSTM: the cell's) two channels, as stored
+  float2 xs[TILES];                     // the state's (LSTM: the cell's) two channels, as stored
   const long sx = (long)N * D, sf = (long)N * F;
-  bf16_t* x = (bf16_t*)a.x;
-  bf16_t* z = (bf16_t*)a.z;
-  bf16_t* lam = (bf16_t*)a.lambda_tok;
+  const int h2 = 2 * H, h4 = 4 * H;  // a gate's distance in bytes
+  Rows x = {(char*)a.x, 2 * sx}, z = {(char*)a.z, 2 * sf};         // of this step
+  Rows lam = {(char*)a.lambda_tok, a.lambda_tok ? 2 * sx : 0};
+  Rows ux = {(char*)a.ux, 4 * sf}, lc = {(char*)a.lambda, a.lambda ? 4L * D : 0}, lt = lam;      // of the step to be read
   auto place = [&](int member) __attribute__((always_inline)) {      // where the member's channels are, and its state at this step
-    at.set(ring.group, member, N, KIND == K_RNN ? D : H, KIND == K_RNN ? F : H);
+    at.set(ring.group, member, N, D, F, KIND == K_RNN ? D : H, KIND == K_RNN ? F : H);
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt) xs[rt] = at.on[rt] ? un2(ld2(x + (long)at.row[rt] * D + at.c)) : make_float2(0.f, 0.f);
+    for (int rt = 0; rt < TILES; ++rt) xs[rt] = un2(bld2(x.buf(), at.x2[rt]));
   };
   members<ALONE>(own, ring.wpg, [&](int member) __attribute__((always_inline)) {
     place(member);
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt)
-      publish(ring, 0, 0, rt, member, at.on[rt] ? ld2(x + (long)at.row[rt] * D + (KIND == K_LSTM ? H : 0) + at.c) : 0u);
+    for (int rt = 0; rt < TILES; ++rt) publish(ring, ring.at(0, 0, rt, member), bld2(x.buf(), at.x2[rt], KIND == K_LSTM ? h2 : 0));
   });
+  if (!ALONE) in.ask(ring, 0, 0);
   bool dead = false;
   int set = 0;
-#pragma unroll 1
-  for (long l = 0; l < a.L; ++l, x += sx, z += sf) {
-    float2 ux[RT][SLOTS], un[RT], lm[RT];
-    // what does not depend on the step before is on its way while the operands are waited for
-    auto read_step = [&]() __attribute__((always_inline)) {
+  // what a step takes besides the state before it
+  struct Inputs { float2 ux[TILES][SLOTS], un[TILES], lm[TILES]; unsigned lw[TILES]; };
+  auto read_step = [&](Inputs& v) __attribute__((always_inline)) {
+    const __amdgpu_buffer_rsrc_t ub = ux.buf(), lb = lc.buf(), tb = lt.buf();
 #pragma unroll
-      for (int rt = 0; rt < RT; ++rt) {
+    for (int rt = 0; rt < TILES; ++rt) {
 #pragma unroll
-        for (int q = 0; q < SLOTS; ++q)
-          ux[rt][q] = at.on_f[rt] ? ldf2(a.ux + l * sf + (long)at.row[rt] * F + (KIND == K_RNN ? 0 : q * H) + at.c) : make_float2(0.f, 0.f);
-        if (KIND == K_GRU) un[rt] = at.on[rt] ? ldf2(a.ux + l * sf + (long)at.row[rt] * F + 2 * H + at.c) : make_float2(0.f, 0.f);
-        if (KIND == K_RNN) {
-          lm[rt] = make_float2(1.f, 1.f);
-          if (a.lambda && at.on[rt]) lm[rt] = ldf2(a.lambda + l * D + at.c);
-          else if (lam && at.on[rt]) lm[rt] = un2(ld2(lam + l * sx + (long)at.row[rt] * D + at.c));
-        }
+      for (int q = 0; q < SLOTS; ++q) v.ux[rt][q] = bldf2(ub, at.f4[rt], KIND == K_RNN ? 0 : q * h4);
+      if (KIND == K_GRU) v.un[rt] = bldf2(ub, at.f4[rt], 2 * h4);
+      if (KIND == K_RNN) {
+        v.lm[rt] = bldf2(lb, at.c4[rt]);
+        v.lw[rt] = bld2(tb, at.x2[rt]);
       }
-    };
+    }
+  };
+  // the step to be read becomes the next one, or stays the last one
+  auto advance = [&](bool more) __attribute__((always_inline)) { ux.next(more); lc.next(more); lt.next(more); };
+  Inputs now, next;
+  if (!ALONE) { read_step(now); advance(a.L > 1); if (!TWO) { read_step(next); advance(a.L > 2); } }
+#pragma unroll 1
+  for (long l = 0; l < a.L; ++l) {
+    const __amdgpu_buffer_rsrc_t zb = z.buf(), lb = lam.buf();
+    x.next(true);
+    const __amdgpu_buffer_rsrc_t xb = x.buf();       // of x[l + 1]
     members<ALONE>(own, ring.wpg, [&](int member) __attribute__((always_inline)) {
-      if (ALONE) place(member);
-      read_step();
-      in.load(ring, 0, l, wave, lane, dead);
+      if (ALONE) { x.base -= x.n; place(member); x.base += x.n; read_step(now); in.ask(ring, 0, l); }
+      in.wait(ring, 0, l, dead);
+      if (!ALONE && TWO) { read_step(next); advance(l + 2 < a.L); }
 #pragma unroll
       for (int u = 0; u < SLOTS; ++u) {
-        float4v acc[RT][2];
-        clear(acc);
-        multiply(acc, ALONE ? weights(u, member) : w[ALONE ? 0 : u], in);
+        Product<RT> acc;
+        acc.clear();
+        multiply_all(acc, ALONE ? weights(u, member) : w[ALONE ? 0 : u], in);
         put(part, set, u, acc, wave, lane);
       }
       meet();
-      if (l > 0) {       // every workgroup of the group has left step l - 1
-        empty<RT>(ring, 0, l - 1, member);
-        if (TWO) empty<RT>(ring, 1, l - 1, member);
-      }
+      unsigned zw[TILES], rw[TILES], ow[TILES], cw[TILES], gw[TILES], aw[TILES], hw[TILES];     // what the phase leaves, packed
 #pragma unroll
-      for (int rt = 0; rt < RT; ++rt) {
-        const int pr = 16 * rt + my_row, pc = my_col;
+      for (int rt = 0; rt < TILES; ++rt) {
+        const int pr = 16 * rt + at.row, pc = at.col;
         float2 s[SLOTS];
 #pragma unroll
         for (int q = 0; q < SLOTS; ++q) {
           s[q] = get(part, set, q, pr, pc);
-          s[q].x += ux[rt][q].x; s[q].y += ux[rt][q].y;
+          s[q].x += now.ux[rt][q].x; s[q].y += now.ux[rt][q].y;
         }
-        const long xo = (long)at.row[rt] * D + at.c, fo = (long)at.row[rt] * F + at.c;
+        constexpr int S1 = SLOTS > 1 ? 1 : 0, S2 = SLOTS > 2 ? 2 : 0, S3 = SLOTS > 3 ? 3 : 0;
         if (KIND == K_RNN) {
           if (a.tanh_act) s[0] = map2([&](int i) { return tanhf(at2(s[0], i)); });
-          const unsigned zw = pk(s[0]);
-          publish(ring, 1, l, rt, member, at.on_f[rt] ? zw : 0u);
-          if (at.on_f[rt]) st2(z + fo, zw);
+          zw[rt] = pk(s[0]);
+          publish(ring, ring.at(1, l, rt, member), at.on_f[rt] ? zw[rt] : 0u);
         } else if (KIND == K_GATED) {
           const float2 u = map2([&](int i) { return sigmoid1(at2(s[0], i)); });
-          const float2 cc = map2([&](int i) { return tanhf(at2(s[SLOTS > 1 ? 1 : 0], i)); });
+          const float2 cc = map2([&](int i) { return tanhf(at2(s[S1], i)); });
           const float2 av = make_float2(1.f - u.x, 1.f - u.y);
-          const unsigned o = pk(map2([&](int i) { return fmaf(at2(av, i), at2(xs[rt], i), at2(u, i) * at2(cc, i)); }));
-          publish(ring, 0, l + 1, rt, member, at.on[rt] ? o : 0u);
-          if (at.on[rt]) {
-            st2(x + sx + xo, o);
-            st2(z + fo, pk(u));
-            st2(z + fo + H, pk(cc));
-            st2(lam + l * sx + xo, pk(av));
-          }
-          xs[rt] = un2(o);
+          ow[rt] = pk(map2([&](int i) { return fmaf(at2(av, i), at2(xs[rt], i), at2(u, i) * at2(cc, i)); }));
+          publish(ring, ring.at(0, l + 1, rt, member), at.on[rt] ? ow[rt] : 0u);
+          zw[rt] = pk(u); cw[rt] = pk(cc); aw[rt] = pk(av);
+          xs[rt] = un2(ow[rt]);
         } else if (KIND == K_LSTM) {
-          constexpr int S1 = SLOTS > 1 ? 1 : 0, S2 = SLOTS > 2 ? 2 : 0, S3 = SLOTS > 3 ? 3 : 0;
           const float2 ig = map2([&](int i) { return sigmoid1(at2(s[0], i)); });
           const float2 fg = map2([&](int i) { return sigmoid1(at2(s[S1], i)); });
           const float2 og = map2([&](int i) { return sigmoid1(at2(s[S2], i)); });
           const float2 gg = map2([&](int i) { return tanhf(at2(s[S3], i)); });
           const float2 cn = map2([&](int i) { return fmaf(at2(fg, i), at2(xs[rt], i), at2(ig, i) * at2(gg, i)); });
           const float2 hn = map2([&](int i) { return at2(og, i) * tanhf(at2(cn, i)); });
-          const unsigned cw = pk(cn), hw = pk(hn);
-          publish(ring, 0, l + 1, rt, member, at.on[rt] ? hw : 0u);
-          if (at.on[rt]) {
-            st2(x + sx + xo + H, hw);
-            st2(x + sx + xo, cw);
-            st2(z + fo, pk(ig));
-            st2(z + fo + H, pk(fg));
-            st2(z + fo + 2 * H, pk(og));
-            st2(z + fo + 3 * H, pk(gg));
-            st2(lam + l * sx + xo, pk(fg));
-            st2(lam + l * sx + xo + H, 0u);
-          }
-          xs[rt] = un2(cw);
+          hw[rt] = pk(hn);
+          publish(ring, ring.at(0, l + 1, rt, member), at.on[rt] ? hw[rt] : 0u);
+          cw[rt] = pk(cn); zw[rt] = pk(ig); rw[rt] = pk(fg); ow[rt] = pk(og); gw[rt] = pk(gg);
+          xs[rt] = un2(cw[rt]);
         } else {
-          const float2 r = map2([&](int i) { return sigmoid1(at2(s[SLOTS > 1 ? 1 : 0], i)); });
-          const unsigned zw = pk(map2([&](int i) { return sigmoid1(at2(s[0], i)); }));
-          publish(ring, 1, l, rt, member, at.on[rt] ? pk(make_float2(r.x * xs[rt].x, r.y * xs[rt].y)) : 0u);
-          if (at.on[rt]) {
-            st2(z + fo, zw);
-            st2(z + fo + H, pk(r));
-          }
-          ux[rt][0] = un2(zw);         // (the second half of the step works on the stored gate)
+          const float2 r = map2([&](int i) { return sigmoid1(at2(s[S1], i)); });
+          publish(ring, ring.at(1, l, rt, member), at.on[rt] ? pk(make_float2(r.x * xs[rt].x, r.y * xs[rt].y)) : 0u);
+          rw[rt] = pk(r);
+          now.ux[rt][0] = s[0];
         }
       }
+      auto results = [&]() __attribute__((always_inline)) {
+#pragma unroll
+      for (int rt = 0; rt < TILES; ++rt) {
+        if (KIND == K_RNN) bst2(zw[rt], zb, at.f2[rt]);
+        if (KIND == K_GATED) {
+          bst2(ow[rt], xb, at.x2[rt]);
+          bst2(zw[rt], zb, at.f2[rt]);
+          bst2(cw[rt], zb, at.f2[rt], h2);
+          bst2(aw[rt], lb, at.x2[rt]);
+        }
+        if (KIND == K_LSTM) {
+          bst2(hw[rt], xb, at.x2[rt], h2);
+          bst2(cw[rt], xb, at.x2[rt]);
+          bst2(zw[rt], zb, at.f2[rt]);
+          bst2(rw[rt], zb, at.f2[rt], h2);
+          bst2(ow[rt], zb, at.f2[rt], 2 * h2);
+          bst2(gw[rt], zb, at.f2[rt], 3 * h2);
+          bst2(rw[rt], lb, at.x2[rt]);
+          bst2(0u, lb, at.x2[rt], h2);
+        }
+        if (KIND == K_GRU) {       // (the second half of the step works on the stored gate)
+          const float2 s = now.ux[rt][0];
+          zw[rt] = pk(map2([&](int i) { return sigmoid1(at2(s, i)); }));
+          now.ux[rt][0] = un2(zw[rt]);
+          bst2(zw[rt], zb, at.f2[rt]);
+          bst2(rw[rt], zb, at.f2[rt], h2);
+        }
+      }
+      };
+      if (KIND == K_RNN) results();
+      // every workgroup of the group has left step l - 1 (before the first step: slots that are empty yet)
+      empty(ring, 0, l - 1, member);
+      if (TWO) empty(ring, 1, l - 1, member);
+      if (!ALONE) {
+        if (TWO) in.ask(ring, 1, l);
+        else {
+          in.ask(ring, 0, l + 1);
+          now = next;
+          read_step(next);
+          advance(l + 3 < a.L);
+        }
+      }
+      if (KIND != K_RNN) results();
       set ^= 1;
     });
     if (TWO) {
       members<ALONE>(own, ring.wpg, [&](int member) __attribute__((always_inline)) {
         if (ALONE) {
-          place(member);
-          read_step();
+          x.base -= x.n; place(member); x.base += x.n;
+          read_step(now);
           if (KIND == K_GRU) {
 #pragma unroll
-            for (int rt = 0; rt < RT; ++rt)
-              ux[rt][0] = at.on[rt] ? un2(ld2(z + (long)at.row[rt] * F + at.c)) : make_float2(0.f, 0.f);
+            for (int rt = 0; rt < TILES; ++rt) now.ux[rt][0] = un2(bld2(zb, at.f2[rt]));
           }
+          in.ask(ring, 1, l);
         }
-        in.load(ring, 1, l, wave, lane, dead);
-        float4v acc[RT][2];
-        clear(acc);
-        multiply(acc, ALONE ? weights(UNITS - 1, member) : w[ALONE ? 0 : UNITS - 1], in);
+        in.wait(ring, 1, l, dead);
+        Product<RT> acc;
+        acc.clear();
+        multiply_all(acc, ALONE ? weights(UNITS - 1, member) : w[ALONE ? 0 : UNITS - 1], in);
         put(part, set, 0, acc, wave, lane);
         meet();
+        unsigned ow[TILES], nw[TILES], aw[TILES];
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt) {
-          float2 s = get(part, set, 0, 16 * rt + my_row, my_col);
-          const long xo = (long)at.row[rt] * D + at.c;
+        for (int rt = 0; rt < TILES; ++rt) {
+          float2 s = get(part, set, 0, 16 * rt + at.row, at.col);
           if (KIND == K_RNN) {
-            const unsigned o = pk(map2([&](int i) { return at2(s, i) + at2(lm[rt], i) * at2(xs[rt], i); }));
-            publish(ring, 0, l + 1, rt, member, at.on[rt] ? o : 0u);
-            if (at.on[rt]) st2(x + sx + xo, o);
-            xs[rt] = un2(o);
+            const float2 lm = a.lambda ? now.lm[rt] : a.lambda_tok ? un2(now.lw[rt]) : make_float2(1.f, 1.f);
+            ow[rt] = pk(map2([&](int i) { return at2(s, i) + at2(lm, i) * at2(xs[rt], i); }));
           } else {
-            const float2 zg = ux[rt][0];
-            const float2 nn = map2([&](int i) { return tanhf(at2(s, i) + at2(un[rt], i)); });
+            const float2 zg = now.ux[rt][0];
+            const float2 nn = map2([&](int i) { return tanhf(at2(s, i) + at2(now.un[rt], i)); });
             const float2 av = make_float2(1.f - zg.x, 1.f - zg.y);
-            const unsigned o = pk(map2([&](int i) { return fmaf(at2(av, i), at2(xs[rt], i), at2(zg, i) * at2(nn, i)); }));
-            publish(ring, 0, l + 1, rt, member, at.on[rt] ? o : 0u);
-            if (at.on[rt]) {
-              st2(x + sx + xo, o);
-              st2(z + (long)at.row[rt] * F + 2 * H + at.c, pk(nn));
-              st2(lam + l * sx + xo, pk(av));
-            }
-            xs[rt] = un2(o);
+            ow[rt] = pk(map2([&](int i) { return fmaf(at2(av, i), at2(xs[rt], i), at2(zg, i) * at2(nn, i)); }));
+            nw[rt] = pk(nn); aw[rt] = pk(av);
+          }
+          publish(ring, ring.at(0, l + 1, rt, member), at.on[rt] ? ow[rt] : 0u);
+          xs[rt] = un2(ow[rt]);
+        }
+#pragma unroll
+        for (int rt = 0; rt < TILES; ++rt) {
+          bst2(ow[rt], xb, at.x2[rt]);
+          if (KIND == K_GRU) {
+            bst2(nw[rt], zb, at.f2[rt], 2 * h2);
+            bst2(aw[rt], lb, at.x2[rt]);
           }
         }
+        if (!ALONE) in.ask(ring, 0, l + 1);
+        if (!ALONE) now = next;
         set ^= 1;
       });
     }
+    if (ALONE) advance(l + 1 < a.L);
+    z.next(true);
+    lam.next(true);
   }
   return true;
 }
 
-template <int KIND, int KQ, int RT>
-__global__ __launch_bounds__(256, 1) void rec_forward_kernel(RecArgs a, int wpg, int groups) {
+template <int KIND, int KQ, int RT, bool LOCAL>
+__global__ __launch_bounds__(256, 1) void rec_forward_kernel(RecArgs a, int wpg, int groups, int per, int locals) {
   constexpr int SLOTS = KIND == K_LSTM ? 4 : KIND == K_RNN ? 1 : 2;
   __shared__ __attribute__((aligned(16))) Partials<RT, SLOTS> part;
   int group, member;
   unsigned started;
-  take_place(a, wpg, group, member, started);
-  const Ring ring = {reinterpret_cast<char*>(a.ring), wpg, groups, RT, group};
-  if (!forward_chain<KIND, KQ, RT, false>(a, ring, member, started, part) && member == 0)
-    forward_chain<KIND, KQ, RT, true>(a, ring, member, started, part);
+  take_place<LOCAL>(a, wpg, groups, per, locals, group, member, started);
+  if (group < 0) return;
+  const Ring<LOCAL, RT> ring(reinterpret_cast<char*>(a.ring), wpg, groups, group);
+  const bool done = forward_chain<KIND, KQ, RT, false>(a, ring, member, started, part);
+  if (!LOCAL && !done && member == 0) forward_chain<KIND, KQ, RT, true>(a, ring, member, started, part);
 }
 
 // Exact backpropagation: g[l] = (da_l W1 + what goes past the product) (+ e_l) + lambda_l (.) g[l+1], l = L-1 .. 0; da as in
 // gated_cell.hip.  Weights transposed: Wt1 = W1^T [H][F] (GRU: [W_z; W_r]^T [H][2H]), Wt2 = W2^T [F][D] (RNN) or W_n^T [H][H].
-template <int KIND, int KQ, int RT, bool ALONE>
-__device__ __forceinline__ bool backward_chain(const RecArgs& a, const Ring& ring, int own, unsigned started, Partials<RT, 1>& part) {
+template <int KIND, int KQ, int RT, bool ALONE, bool LOCAL>
+__device__ __forceinline__ bool backward_chain(const RecArgs& a, const Ring<LOCAL, RT>& ring, int own, unsigned started, Partials<RT, 1>& part) {
   constexpr int UNITS = KIND == K_LSTM ? 4 : KIND == K_GRU ? 3 : 2;
   constexpr bool TWO = KIND == K_RNN || KIND == K_GRU;       // two dependent products per step
   constexpr int U0 = TWO ? 1 : 0;                            // first unit of the (second) product with W1
+  constexpr int TILES = rec_tiles<RT>();
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int N = (int)a.N, H = (int)a.H, F = (int)a.F, D = (int)a.D;
@@ -475,97 +652,93 @@ __device__ __forceinline__ bool backward_chain(const RecArgs& a, const Ring& rin
   if (!ALONE) {
 #pragma unroll
     for (int u = 0; u < UNITS; ++u) weights(u, own);
-    if (!all_started(a, ring.wpg, ring.group, started)) return false;     // (while the weights are on their way)
+    if (!all_started<LOCAL>(a, ring.wpg, ring.group, started)) return false;     // (while the weights are on their way)
   }
-  Operand<KQ, RT> in;
+  Operand<KQ, RT> in, in2;
+  in.set(ring, wave, lane);
+  in2.set(ring, wave, lane);
   // exchanged: the cells' da, a unit per gate; the RNN's da is unit 0 and its state gradient unit 1
-  const int my_row = (tid >> 2) & 15, my_col = 8 * (tid >> 6) + 2 * (tid & 3);
   Place<RT> at;
-  float2 gs[RT], gc[RT];             // the gradient's two channels as stored (LSTM: hidden and cell part)
-  const long sx = (long)N * D, sf = (long)N * F;
-  bf16_t* g = (bf16_t*)a.g + a.L * sx;
-  const int ho = KIND == K_LSTM ? H : 0;
-  auto place = [&](int member) __attribute__((always_inline)) {      // where the member's channels are, and its gradient (g points at it)
-    at.set(ring.group, member, N, KIND == K_RNN ? D : H, KIND == K_RNN ? F : H);
+  float2 gs[TILES], gc[TILES];             // the gradient's two channels as stored (LSTM: hidden and cell part)
+  const long sx = (long)N * D, sf = (long)N * F, last = a.L - 1;
+  const int h2 = 2 * H, ho = KIND == K_LSTM ? h2 : 0;        // a gate's distance in bytes, and the hidden part's
+  Rows g = {(char*)a.g + 2 * sx * a.L, 2 * sx};              // g[l + 1]
+  // the inputs of the step to be read (x: states l and l + 1)
+  Rows lc = {(char*)a.lambda + (a.lambda ? 4 * last * D : 0), a.lambda ? 4L * D : 0};
+  Rows lt = {(char*)a.lambda_tok + (a.lambda_tok ? 2 * last * sx : 0), a.lambda_tok ? 2 * sx : 0};
+  Rows e = {(char*)a.e + (a.e ? 2 * last * sx : 0), a.e ? 2 * sx : 0};
+  Rows x = {(char*)a.x + 2 * last * sx, 2 * sx};
+  Rows z = {(char*)(KIND == K_RNN && a.dphi ? a.dphi : a.z) + 2 * last * sf, 2 * sf};
+  auto place = [&](int member) __attribute__((always_inline)) {      // where the member's channels are, and its gradient
+    at.set(ring.group, member, N, D, F, KIND == K_RNN ? D : H, KIND == K_RNN ? F : H);
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt) {
-      gs[rt] = gc[rt] = make_float2(0.f, 0.f);
-      if (at.on[rt]) gs[rt] = un2(ld2(g + (long)at.row[rt] * D + ho + at.c));
-      if (KIND == K_LSTM && at.on[rt]) gc[rt] = un2(ld2(g + (long)at.row[rt] * D + at.c));
+    for (int rt = 0; rt < TILES; ++rt) {
+      gs[rt] = un2(bld2(g.buf(), at.x2[rt], ho));
+      gc[rt] = KIND == K_LSTM ? un2(bld2(g.buf(), at.x2[rt])) : make_float2(0.f, 0.f);
     }
   };
   members<ALONE>(own, ring.wpg, [&](int member) __attribute__((always_inline)) {
     place(member);
     if (KIND == K_RNN) {
 #pragma unroll
-      for (int rt = 0; rt < RT; ++rt)
-        publish(ring, 1, a.L, rt, member, at.on[rt] ? ld2(g + (long)at.row[rt] * D + at.c) : 0u);
+      for (int rt = 0; rt < TILES; ++rt) publish(ring, ring.at(1, a.L, rt, member), bld2(g.buf(), at.x2[rt]));
     }
   });
+  if (!ALONE && KIND == K_RNN) in.ask(ring, 1, a.L);
   bool dead = false;
   int set = 0;
-  const bf16_t* x = (const bf16_t*)a.x + (a.L - 1) * sx;
-  const bf16_t* z = (const bf16_t*)a.z + (a.L - 1) * sf;
-  const bf16_t* lamt = (const bf16_t*)a.lambda_tok;
-  const bf16_t* dphi = (const bf16_t*)a.dphi;
-  const bf16_t* e = (const bf16_t*)a.e;
-#pragma unroll 1
-  for (long l = a.L - 1; l >= 0; --l, x -= sx, z -= sf, g -= sx) {
-    unsigned lw[RT], lw2[RT], ew[RT], ew2[RT], zw[RT][4], xw[RT], xn[RT];
-    float2 lmf[RT];
-    float2 past[RT], pastc[RT];      // what reaches g[l] (hidden, cell) past the product with W1
-    // what does not depend on the step after is on its way while the operands are waited for
-    auto read_step = [&]() __attribute__((always_inline)) {
+  // what a step takes besides the gradient above it
+  struct Inputs {
+    unsigned lw[TILES], lw2[TILES], ew[TILES], ew2[TILES], zw[TILES][4], xw[TILES], xn[TILES];
+    float2 lmf[TILES];
+  };
+  auto read_step = [&](Inputs& v) __attribute__((always_inline)) {
+    const __amdgpu_buffer_rsrc_t lb = lc.buf(), tb = lt.buf(), eb = e.buf(), xb = x.buf(), zb = z.buf();
+    const __amdgpu_buffer_rsrc_t nb = buffer(x.base + x.n, x.n);
 #pragma unroll
-      for (int rt = 0; rt < RT; ++rt) {
-        const long xo = (long)at.row[rt] * D + at.c, fo = (long)at.row[rt] * F + at.c;
-        lmf[rt] = make_float2(1.f, 1.f);
-        lw[rt] = lw2[rt] = ew[rt] = ew2[rt] = xw[rt] = xn[rt] = 0u;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) zw[rt][q] = 0u;
-        if (at.on[rt]) {
-          if (a.lambda) lmf[rt] = ldf2(a.lambda + l * D + at.c);
-          else if (lamt) lw[rt] = ld2(lamt + l * sx + xo + ho);
-          if (e) ew[rt] = ld2(e + l * sx + xo + ho);
-          if (KIND == K_LSTM) {
-            lw2[rt] = ld2(lamt + l * sx + xo);
-            if (e) ew2[rt] = ld2(e + l * sx + xo);
-            xn[rt] = ld2(x + sx + xo);
-          }
-          if (KIND != K_RNN) {
-            xw[rt] = ld2(x + xo);
-#pragma unroll
-            for (int q = 0; q < (KIND == K_GATED ? 2 : KIND == K_GRU ? 3 : 4); ++q) zw[rt][q] = ld2(z + fo + q * H);
-          }
-        }
-        if (KIND == K_RNN && at.on_f[rt]) {
-          if (dphi) zw[rt][0] = ld2(dphi + l * sf + fo);
-          else if (a.tanh_act) zw[rt][0] = ld2(z + fo);
-        }
+    for (int rt = 0; rt < TILES; ++rt) {
+      if (KIND == K_RNN) v.lmf[rt] = bldf2(lb, at.c4[rt]);
+      v.lw[rt] = bld2(tb, at.x2[rt], ho);
+      v.ew[rt] = bld2(eb, at.x2[rt], ho);
+      if (KIND == K_LSTM) {
+        v.lw2[rt] = bld2(tb, at.x2[rt]);
+        v.ew2[rt] = bld2(eb, at.x2[rt]);
+        v.xn[rt] = bld2(nb, at.x2[rt]);
       }
-    };
+      if (KIND != K_RNN) v.xw[rt] = bld2(xb, at.x2[rt]);
+#pragma unroll
+      for (int q = 0; q < (KIND == K_RNN ? 1 : KIND == K_GATED ? 2 : KIND == K_GRU ? 3 : 4); ++q) v.zw[rt][q] = bld2(zb, at.f2[rt], q * h2);
+    }
+  };
+  // the step to be read becomes the one before, or stays the first
+  auto advance = [&](bool more) __attribute__((always_inline)) { lc.before(more); lt.before(more); e.before(more); x.before(more); z.before(more); };
+  Inputs now, next;
+  if (!ALONE) { read_step(now); advance(last > 0); }
+#pragma unroll 1
+  for (long l = last; l >= 0; --l) {
+    float2 past[TILES], pastc[TILES];      // what reaches g[l] (hidden, cell) past the product with W1
     // the LSTM's gradient at the cell state through the hidden part
     auto tanh_c = [&](int rt) __attribute__((always_inline)) {
-      const float2 cn = un2(xn[rt]);
+      const float2 cn = un2(now.xn[rt]);
       return map2([&](int i) { return tanhf(at2(cn, i)); });
     };
     auto through_h = [&](int rt, float2 tc) __attribute__((always_inline)) {
-      const float2 og = un2(zw[rt][2]);
+      const float2 og = un2(now.zw[rt][2]);
       return map2([&](int i) { return at2(gs[rt], i) * at2(og, i) * (1.f - at2(tc, i) * at2(tc, i)); });
     };
     // what the cells' elementwise parts leave for the products
     auto publish_gates = [&](int member) __attribute__((always_inline)) {
 #pragma unroll
-      for (int rt = 0; rt < RT; ++rt) {
-        const float2 G = gs[rt], xv = un2(xw[rt]);
+      for (int rt = 0; rt < TILES; ++rt) {
+        const float2 G = gs[rt], xv = un2(now.xw[rt]);
         if (KIND == K_GATED) {
-          const float2 u = un2(zw[rt][0]), cc = un2(zw[rt][1]);
+          const float2 u = un2(now.zw[rt][0]), cc = un2(now.zw[rt][1]);
           const float2 du = map2([&](int i) { return at2(G, i) * (at2(cc, i) - at2(xv, i)) * at2(u, i) * (1.f - at2(u, i)); });
           const float2 dc = map2([&](int i) { return at2(G, i) * at2(u, i) * (1.f - at2(cc, i) * at2(cc, i)); });
-          publish(ring, 0, l, rt, member, at.on[rt] ? pk(du) : 0u);
-          publish(ring, 1, l, rt, member, at.on[rt] ? pk(dc) : 0u);
+          publish(ring, ring.at(0, l, rt, member), at.on[rt] ? pk(du) : 0u);
+          publish(ring, ring.at(1, l, rt, member), at.on[rt] ? pk(dc) : 0u);
         } else if (KIND == K_LSTM) {
-          const float2 ig = un2(zw[rt][0]), fg = un2(zw[rt][1]), og = un2(zw[rt][2]), gg = un2(zw[rt][3]);
+          const float2 ig = un2(now.zw[rt][0]), fg = un2(now.zw[rt][1]), og = un2(now.zw[rt][2]), gg = un2(now.zw[rt][3]);
           const float2 tc = tanh_c(rt), th = through_h(rt, tc);
           pastc[rt] = make_float2(th.x * fg.x, th.y * fg.y);
           const float2 dct = make_float2(gc[rt].x + th.x, gc[rt].y + th.y);
@@ -573,133 +746,162 @@ __device__ __forceinline__ bool backward_chain(const RecArgs& a, const Ring& rin
           const float2 df = map2([&](int i) { return at2(dct, i) * at2(xv, i) * at2(fg, i) * (1.f - at2(fg, i)); });
           const float2 dO = map2([&](int i) { return at2(G, i) * at2(tc, i) * at2(og, i) * (1.f - at2(og, i)); });
           const float2 dg = map2([&](int i) { return at2(dct, i) * at2(ig, i) * (1.f - at2(gg, i) * at2(gg, i)); });
-          publish(ring, 0, l, rt, member, at.on[rt] ? pk(di) : 0u);
-          publish(ring, 1, l, rt, member, at.on[rt] ? pk(df) : 0u);
-          publish(ring, 2, l, rt, member, at.on[rt] ? pk(dO) : 0u);
-          publish(ring, 3, l, rt, member, at.on[rt] ? pk(dg) : 0u);
+          publish(ring, ring.at(0, l, rt, member), at.on[rt] ? pk(di) : 0u);
+          publish(ring, ring.at(1, l, rt, member), at.on[rt] ? pk(df) : 0u);
+          publish(ring, ring.at(2, l, rt, member), at.on[rt] ? pk(dO) : 0u);
+          publish(ring, ring.at(3, l, rt, member), at.on[rt] ? pk(dg) : 0u);
         } else if (KIND == K_GRU) {
-          const float2 zg = un2(zw[rt][0]), nn = un2(zw[rt][2]);
+          const float2 zg = un2(now.zw[rt][0]), nn = un2(now.zw[rt][2]);
           const float2 dn = map2([&](int i) { return at2(G, i) * at2(zg, i) * (1.f - at2(nn, i) * at2(nn, i)); });
           const float2 dz = map2([&](int i) { return at2(G, i) * (at2(nn, i) - at2(xv, i)) * at2(zg, i) * (1.f - at2(zg, i)); });
-          publish(ring, 2, l, rt, member, at.on[rt] ? pk(dn) : 0u);
-          publish(ring, 0, l, rt, member, at.on[rt] ? pk(dz) : 0u);
+          publish(ring, ring.at(2, l, rt, member), at.on[rt] ? pk(dn) : 0u);
+          publish(ring, ring.at(0, l, rt, member), at.on[rt] ? pk(dz) : 0u);
         }
       }
     };
     // RNN: g W2; GRU: what comes back through the candidate's product, dn W_n
     auto first_product = [&](int member) __attribute__((always_inline)) {
-      in.load(ring, KIND == K_RNN ? 1 : 2, KIND == K_RNN ? l + 1 : l, wave, lane, dead);
-      float4v acc[RT][2];
-      clear(acc);
-      multiply(acc, ALONE ? weights(0, member) : w[0], in);
+      constexpr int U = KIND == K_RNN ? 1 : 2;
+      const long at_l = KIND == K_RNN ? l + 1 : l;
+      if (ALONE) in.ask(ring, U, at_l);
+      in.wait(ring, U, at_l, dead);
+      if (!ALONE) { read_step(next); advance(l > 1); }
+      Product<RT> acc;
+      acc.clear();
+      multiply_all(acc, ALONE ? weights(0, member) : w[0], in);
       put(part, set, 0, acc, wave, lane);
       meet();
     };
-    members<ALONE>(own, ring.wpg, [&](int member) __attribute__((always_inline)) {
-      if (ALONE) place(member);
-      read_step();
-      publish_gates(member);
-    });
+    // the operands of the product with W1: the first two units are asked for together, each later one as soon as its registers are
+    // free (the LSTM with two row tiles has registers for one unit: 24 would be spilled)
+    constexpr int HELD = UNITS - U0 == 1 || (KIND == K_LSTM && RT == 2) ? 1 : 2;
+    auto ask_second = [&]() __attribute__((always_inline)) {
+      in.ask(ring, 0, l);
+      if (HELD == 2) in2.ask(ring, 1, l);
+    };
+    if (KIND != K_RNN) {
+      members<ALONE>(own, ring.wpg, [&](int member) __attribute__((always_inline)) {
+        if (ALONE) { place(member); read_step(now); }
+        publish_gates(member);
+        if (!ALONE) {
+          if (TWO) in.ask(ring, 2, l);
+          else { ask_second(); read_step(next); advance(l > 1); }
+        }
+      });
+    }
     if (TWO) {
       members<ALONE>(own, ring.wpg, [&](int member) __attribute__((always_inline)) {
-        if (ALONE) { place(member); read_step(); }
+        if (ALONE) { place(member); read_step(now); }
         first_product(member);
-        if (l + 1 < a.L) {       // every workgroup of the group has left step l + 1
-          empty<RT>(ring, 0, l + 1, member);
-          empty<RT>(ring, 1, KIND == K_RNN ? l + 2 : l + 1, member);
-          if (KIND == K_GRU) empty<RT>(ring, 2, l + 1, member);
-        }
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt) {
-          const float2 s = get(part, set, 0, 16 * rt + my_row, my_col);
+        for (int rt = 0; rt < TILES; ++rt) {
+          const float2 s = get(part, set, 0, 16 * rt + at.row, at.col);
           if (KIND == K_RNN) {
-            float2 v = s;
-            const float2 t = un2(zw[rt][0]);
-            if (dphi) v = make_float2(s.x * t.x, s.y * t.y);
-            else if (a.tanh_act) v = make_float2(s.x * (1.f - t.x * t.x), s.y * (1.f - t.y * t.y));
-            publish(ring, 0, l, rt, member, at.on_f[rt] ? pk(v) : 0u);
+            const float2 t = un2(now.zw[rt][0]);
+            const float2 v = map2([&](int i) { return at2(s, i) * (a.dphi ? at2(t, i) : a.tanh_act ? 1.f - at2(t, i) * at2(t, i) : 1.f); });
+            publish(ring, ring.at(0, l, rt, member), at.on_f[rt] ? pk(v) : 0u);
           } else {
-            const float2 r = un2(zw[rt][1]), xv = un2(xw[rt]);
+            const float2 r = un2(now.zw[rt][1]), xv = un2(now.xw[rt]);
             const float2 dr = map2([&](int i) { return at2(s, i) * at2(xv, i) * at2(r, i) * (1.f - at2(r, i)); });
-            publish(ring, 1, l, rt, member, at.on[rt] ? pk(dr) : 0u);
+            publish(ring, ring.at(1, l, rt, member), at.on[rt] ? pk(dr) : 0u);
             past[rt] = make_float2(s.x * r.x, s.y * r.y);
           }
+        }
+        // every workgroup of the group has left step l + 1 (at the last step: slots that are empty yet)
+        empty(ring, 0, l + 1, member);
+        empty(ring, 1, KIND == K_RNN ? l + 2 : l + 1, member);
+        if (KIND == K_GRU) empty(ring, 2, l + 1, member);
+        if (!ALONE) {
+          ask_second();
         }
         set ^= 1;
       });
     }
     members<ALONE>(own, ring.wpg, [&](int member) __attribute__((always_inline)) {
-      if (ALONE) { place(member); read_step(); }
+      if (ALONE) { place(member); read_step(now); }
       if (KIND == K_GRU && ALONE) {      // (the sum that the member's registers hold otherwise)
         first_product(member);
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt) {
-          const float2 s = get(part, set, 0, 16 * rt + my_row, my_col), r = un2(zw[rt][1]);
+        for (int rt = 0; rt < TILES; ++rt) {
+          const float2 s = get(part, set, 0, 16 * rt + at.row, at.col), r = un2(now.zw[rt][1]);
           past[rt] = make_float2(s.x * r.x, s.y * r.y);
         }
         set ^= 1;
       }
 #pragma unroll
-      for (int rt = 0; rt < RT; ++rt) {
+      for (int rt = 0; rt < TILES; ++rt) {
         if (KIND != K_GRU) past[rt] = make_float2(0.f, 0.f);
         if (KIND == K_LSTM && ALONE) {
-          const float2 th = through_h(rt, tanh_c(rt)), fg = un2(zw[rt][1]);
+          const float2 th = through_h(rt, tanh_c(rt)), fg = un2(now.zw[rt][1]);
           pastc[rt] = make_float2(th.x * fg.x, th.y * fg.y);
         }
       }
-      float4v acc[RT][2];
-      clear(acc);
+      if (ALONE) ask_second();
+      Product<RT> acc;
+      acc.clear();
 #pragma unroll
-      for (int u = U0; u < UNITS; ++u) {
-        in.load(ring, u - U0, l, wave, lane, dead);
-        multiply(acc, ALONE ? weights(u, member) : w[ALONE ? 0 : u], in);
+      for (int u = 0; u < UNITS - U0; ++u) {
+        Operand<KQ, RT>& o = HELD == 2 && (u & 1) ? in2 : in;
+        o.wait(ring, u, l, dead);
+        multiply_all(acc, ALONE ? weights(u + U0, member) : w[ALONE ? 0 : u + U0], o);
+        if (u + HELD < UNITS - U0) o.ask(ring, u + HELD, l);
       }
       put(part, set, 0, acc, wave, lane);
       meet();
-      if (!TWO && l + 1 < a.L) {
+      unsigned o[TILES], oc[TILES];
 #pragma unroll
-        for (int u = 0; u < UNITS; ++u) empty<RT>(ring, u, l + 1, member);
-      }
-#pragma unroll
-      for (int rt = 0; rt < RT; ++rt) {
-        const float2 s = get(part, set, 0, 16 * rt + my_row, my_col);
-        const float2 ev = un2(ew[rt]), lm = lamt ? un2(lw[rt]) : lmf[rt];
-        const unsigned o = pk(map2([&](int i) { return (at2(s, i) + at2(past[rt], i) + at2(ev, i)) + at2(lm, i) * at2(gs[rt], i); }));
-        const long xo = (long)at.row[rt] * D + at.c - sx;    // g points at g[l + 1]
-        if (KIND == K_RNN) publish(ring, 1, l, rt, member, at.on[rt] ? o : 0u);
-        if (at.on[rt]) st2(g + xo + ho, o);
-        gs[rt] = un2(o);
+      for (int rt = 0; rt < TILES; ++rt) {
+        const float2 s = get(part, set, 0, 16 * rt + at.row, at.col);
+        const float2 ev = un2(now.ew[rt]), lm = a.lambda_tok ? un2(now.lw[rt]) : KIND == K_RNN && a.lambda ? now.lmf[rt] : make_float2(1.f, 1.f);
+        o[rt] = pk(map2([&](int i) { return (at2(s, i) + at2(past[rt], i) + at2(ev, i)) + at2(lm, i) * at2(gs[rt], i); }));
+        if (KIND == K_RNN) publish(ring, ring.at(1, l, rt, member), at.on[rt] ? o[rt] : 0u);
+        gs[rt] = un2(o[rt]);
         if (KIND == K_LSTM) {
-          const float2 e2 = un2(ew2[rt]), l2 = un2(lw2[rt]);
-          const unsigned oc = pk(map2([&](int i) { return (at2(pastc[rt], i) + at2(e2, i)) + at2(l2, i) * at2(gc[rt], i); }));
-          if (at.on[rt]) st2(g + xo, oc);
-          gc[rt] = un2(oc);
+          const float2 e2 = un2(now.ew2[rt]), l2 = un2(now.lw2[rt]);
+          oc[rt] = pk(map2([&](int i) { return (at2(pastc[rt], i) + at2(e2, i)) + at2(l2, i) * at2(gc[rt], i); }));
+          gc[rt] = un2(oc[rt]);
         }
       }
+      if (!TWO) {
+#pragma unroll
+        for (int u = 0; u < UNITS; ++u) empty(ring, u, l + 1, member);
+      }
+      const __amdgpu_buffer_rsrc_t gb = buffer(g.base - g.n, g.n);       // g[l]
+#pragma unroll
+      for (int rt = 0; rt < TILES; ++rt) {
+        bst2(o[rt], gb, at.x2[rt], ho);
+        if (KIND == K_LSTM) bst2(oc[rt], gb, at.x2[rt]);
+      }
+      if (!ALONE && KIND == K_RNN) in.ask(ring, 1, l);
+      if (!ALONE) now = next;
       set ^= 1;
     });
+    if (ALONE) advance(l > 0);
+    g.before(true);
   }
   return true;
 }
 
-template <int KIND, int KQ, int RT>
-__global__ __launch_bounds__(256, 1) void rec_backward_kernel(RecArgs a, int wpg, int groups) {
+template <int KIND, int KQ, int RT, bool LOCAL>
+__global__ __launch_bounds__(256, 1) void rec_backward_kernel(RecArgs a, int wpg, int groups, int per, int locals) {
   __shared__ __attribute__((aligned(16))) Partials<RT, 1> part;
   int group, member;
   unsigned started;
-  take_place(a, wpg, group, member, started);
-  const Ring ring = {reinterpret_cast<char*>(a.ring), wpg, groups, RT, group};
-  if (!backward_chain<KIND, KQ, RT, false>(a, ring, member, started, part) && member == 0)
-    backward_chain<KIND, KQ, RT, true>(a, ring, member, started, part);
+  take_place<LOCAL>(a, wpg, groups, per, locals, group, member, started);
+  if (group < 0) return;
+  const Ring<LOCAL, RT> ring(reinterpret_cast<char*>(a.ring), wpg, groups, group);
+  const bool done = backward_chain<KIND, KQ, RT, false>(a, ring, member, started, part);
+  if (!LOCAL && !done && member == 0) backward_chain<KIND, KQ, RT, true>(a, ring, member, started, part);
 }
 
-// the empty word into every slot (n 16-byte pieces), zeros into the block behind them, the counter at zero and the groups' words
-__global__ __launch_bounds__(256) void rec_fill_kernel(uint4* p, long n, int* counter, unsigned word) {
+// the empty word into every slot (n 16-byte pieces); the words of the places at zero, but for those of the groups (`word`)
+__global__ __launch_bounds__(256) void rec_fill_kernel(uint4* p, long n, PlaceWords* places, unsigned word) {
   const long i = (long)blockIdx.x * 256 + threadIdx.x;
-  const unsigned w = i < n ? REC_EMPTY : 0u;
-  if (i < n + 64) p[i] = make_uint4(w, w, w, w);
-  if (i == 0) *counter = 0;
-  if (i < REC_MAX_WG) counter[1 + i] = (int)word;
+  if (i < n) p[i] = make_uint4(REC_EMPTY, REC_EMPTY, REC_EMPTY, REC_EMPTY);
+  if (blockIdx.x == 0) {
+    for (int j = threadIdx.x; j < (int)(sizeof(PlaceWords) / 4); j += 256)
+      reinterpret_cast<unsigned*>(places)[j] = j >= 1 && j < 1 + REC_MAX_WG ? word : 0u;
+  }
 }
 
 inline long rec_width(const RecArgs& a) { return a.F > a.D && a.kind == K_RNN ? a.F : a.kind == K_RNN ? a.D : a.H; }
@@ -711,34 +913,58 @@ inline int rec_row_tiles(const RecArgs& a) {
   return 0;
 }
 inline bool ok16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
+// The groups on one XCD each: of 8 rows where every XCD of the eight then has a compute unit for each workgroup, else of 16.
+// Half the rows are half the bytes that a workgroup reads in every phase (32 KB at width 1024 and 16 rows, 500 cycles at a
+// compute unit's 64 bytes), for the same number of matrix instructions.
+inline bool rec_half(const RecArgs& a, long wpg) {
+  const long n = (a.N + 7) / 8;
+  return (n + 7) / 8 * wpg <= 32 && n * ((wpg + 1) / 2) <= REC_MAX_WG * 2;       // (and the vectors fit their memory)
+}
 
-template <int KIND, int KQ, int RT>
+// RT: row tiles of the groups anywhere, RTL: of those on one XCD
+template <int KIND, int KQ, int RT, int RTL>
 hipError_t launch_rec(const RecArgs& a, bool forward, hipStream_t s) {
   const long wpg = (rec_width(a) + REC_COLS - 1) / REC_COLS;
-  const long wgs = (a.N + 16 * RT - 1) / (16 * RT) * wpg;
-  const long n16 = REC_UNITS * REC_SLOTS * wgs * RT * 64;
-  hipLaunchKernelGGL(rec_fill_kernel, dim3((unsigned)((n16 + 64 + 255) / 256)), dim3(256), 0, s, reinterpret_cast<uint4*>(a.ring), n16,
-                     a.counter, a.wait == REC_ALONE_ANYHOW ? REC_ALONE : 0u);
-  if (forward) hipLaunchKernelGGL((rec_forward_kernel<KIND, KQ, RT>), dim3((unsigned)wgs), dim3(256), 0, s, a, (int)wpg, (int)(wgs / wpg));
-  else hipLaunchKernelGGL((rec_backward_kernel<KIND, KQ, RT>), dim3((unsigned)wgs), dim3(256), 0, s, a, (int)wpg, (int)(wgs / wpg));
+  const int groups = (int)((a.N + rec_rows<RT>() - 1) / rec_rows<RT>()), locals = (int)((a.N + rec_rows<RTL>() - 1) / rec_rows<RTL>());
+  const long ring = (long)REC_UNITS * REC_SLOTS * groups * RT * wpg * 1024;
+  const long ring_local = (long)REC_UNITS * REC_SLOTS * locals * (RTL ? wpg : (wpg + 1) / 2) * 1024;
+  const long n16 = (ring + ring_local) / 16;
+  const bool local = a.wait == REC_WAIT;
+  hipLaunchKernelGGL(rec_fill_kernel, dim3((unsigned)((n16 + 255) / 256)), dim3(256), 0, s, reinterpret_cast<uint4*>(a.ring), n16,
+                     reinterpret_cast<PlaceWords*>(a.counter), a.wait == REC_ALONE_ANYHOW ? REC_ALONE : 0u);
+  // enough workgroups that every XCD of the eight has a group's number of them for each group it can be asked to take
+  const dim3 everywhere((unsigned)(8 * wpg * ((locals + 7) / 8))), anywhere((unsigned)(groups * wpg));
+  RecArgs l = a;
+  l.ring = reinterpret_cast<char*>(a.ring) + ring;
+  const int per = rec_rows<RT>() / rec_rows<RTL>();
+  if (forward) {
+    if (local) hipLaunchKernelGGL((rec_forward_kernel<KIND, KQ, RTL, true>), everywhere, dim3(256), 0, s, l, (int)wpg, locals, 1, 0);
+    hipLaunchKernelGGL((rec_forward_kernel<KIND, KQ, RT, false>), anywhere, dim3(256), 0, s, a, (int)wpg, groups, per, local ? locals : 0);
+  } else {
+    if (local) hipLaunchKernelGGL((rec_backward_kernel<KIND, KQ, RTL, true>), everywhere, dim3(256), 0, s, l, (int)wpg, locals, 1, 0);
+    hipLaunchKernelGGL((rec_backward_kernel<KIND, KQ, RT, false>), anywhere, dim3(256), 0, s, a, (int)wpg, groups, per, local ? locals : 0);
+  }
   return hipGetLastError();
+}
+template <int KIND, int KQ>
+hipError_t launch_rec_rows(const RecArgs& a, bool forward, hipStream_t s) {
+  const bool half = rec_half(a, (rec_width(a) + REC_COLS - 1) / REC_COLS);
+  if (rec_row_tiles(a) == 1) return half ? launch_rec<KIND, KQ, 1, 0>(a, forward, s) : launch_rec<KIND, KQ, 1, 1>(a, forward, s);
+  return half ? launch_rec<KIND, KQ, 2, 0>(a, forward, s) : launch_rec<KIND, KQ, 2, 1>(a, forward, s);
 }
 template <int KIND>
 hipError_t launch_rec_kind(const RecArgs& a, bool forward, hipStream_t s) {
-  const int rt = rec_row_tiles(a);
   const long K = KIND == K_RNN ? rec_width(a) : a.H;
-  if (rt == 1) {
-    if (K <= 256) return launch_rec<KIND, 2, 1>(a, forward, s);
-    return K <= 512 ? launch_rec<KIND, 4, 1>(a, forward, s) : launch_rec<KIND, 8, 1>(a, forward, s);
-  }
-  if (K <= 256) return launch_rec<KIND, 2, 2>(a, forward, s);
-  return K <= 512 ? launch_rec<KIND, 4, 2>(a, forward, s) : launch_rec<KIND, 8, 2>(a, forward, s);
+  if (K <= 256) return launch_rec_rows<KIND, 2>(a, forward, s);
+  if (K <= 512) return launch_rec_rows<KIND, 4>(a, forward, s);
+  return launch_rec_rows<KIND, 8>(a, forward, s);
 }
 
 }  // namespace
 
-static_assert((1 + REC_MAX_WG) * sizeof(int) <= RECURRENT_COUNTER_BYTES, "a counter and a word per group");
-size_t recurrent_ring_bytes() { return (size_t)REC_UNITS * REC_SLOTS * REC_MAX_WG * 2 * 1024 + 1024; }
+// the groups anywhere (at most REC_MAX_WG workgroups of two tiles), and those on one XCD each: at most 8 x 32 workgroups of half
+// a tile, or twice REC_MAX_WG of a tile
+size_t recurrent_ring_bytes() { return (size_t)REC_UNITS * REC_SLOTS * REC_MAX_WG * 2 * 1024 * 2; }
 // What fits: bf16, widths whose weights the registers hold (1024) and at most 64 workgroups (two row tiles each: 64 rows at
 // width 1024, 128 at 512).  Everything else goes step by step (7 us per product against 1.6).
 bool recurrent_ok(const RecArgs& a) {

@@ -188,6 +188,29 @@ def test_chains_along_time_by_one_workgroup(B, kind, L, N, H, wait):
     assert torch.equal(p.g, q.g)
 
 
+# Groups on one XCD each (of 8 rows, or of 16 where there would be too many) against groups whose workgroups may be anywhere
+# (wait 3; of 16 or 32 rows): the same results bit for bit.  Odd numbers of blocks, a last group with one row, more groups than
+# XCDs, the widest with every compute unit taken.
+@pytest.mark.parametrize("kind,L,N,H", [("rnn", 9, 1, 8), ("rnn", 7, 9, 96), ("rnn", 5, 1030, 32), ("token", 6, 96, 672), ("token", 9, 33, 520),
+                                        ("gated", 5, 65, 512), ("gated", 6, 17, 40), ("lstm", 5, 64, 1024), ("lstm", 8, 25, 264),
+                                        ("gru", 5, 96, 672), ("gru", 9, 31, 1000), ("gru", 6, 64, 1024)])
+def test_chains_on_one_xcd_and_anywhere(B, kind, L, N, H):
+    import ctypes as C
+    import torch
+    w = _chain(kind, L, N, H)
+    inp, st, sv, p = _setup(B, w)
+    q = B.allocate(w, inp)
+    B.hbp_forward(p)
+    B.hbp_exact_backward(p)
+    b = q.buffers()
+    f = B.lib().hbp_internal_chains
+    s = torch.cuda.current_stream().cuda_stream
+    assert f(C.byref(q.desc), 1, 3, C.byref(b), C.c_void_p(s)) == B.HBP_OK
+    assert f(C.byref(q.desc), 0, 3, C.byref(b), C.c_void_p(s)) == B.HBP_OK
+    for n in ("x", "z", "lam", "g"):
+        assert torch.equal(getattr(p, n), getattr(q, n)), n
+
+
 # fp32 products: around the 32- and 64-wide tiles, contractions that end inside a chunk of 32 or leave a wavefront's
 # quarter empty, and enough blocks (40 x 4 x 4 tiles of 64) for the wide tiles
 @pytest.mark.parametrize("L,N,d,d_ff", [(2, 1, 8, 8), (2, 31, 40, 24), (3, 65, 32, 72), (2, 130, 264, 136), (40, 250, 72, 232)])
