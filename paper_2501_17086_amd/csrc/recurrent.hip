@@ -19,10 +19,10 @@
 //     next operands.  They are used again four steps later, and what a reader waits for in between was written after the owner
 //     had waited for those operands, which a wavefront's earlier stores (the emptying among them) precede;
 //   - the four quarters of a product are added through LDS (one workgroup barrier per product), and the elementwise
-//     part of the cell runs on the sums, two channels of a row per thread, the state staying in registers.
+//     part of the cell runs on the sums, one or two channels of a row per thread, the state staying in registers.
 // A group begins once all of its workgroups have started: from then on each of them keeps running, so that every wait inside the
 // chain ends.  If a group has not got together on one XCD after a poll per step (other kernels hold its compute units), it is
-// given up, and a second launch, which otherwise ends at once, takes what is left: its workgroups, at most 64 in all, a quarter
+// given up, and a second launch, which otherwise ends at once, takes what is left (short chains go to it whole): its workgroups, at most 64 in all, a quarter
 // of the compute units, may be anywhere and exchange through memory.  They take their place in a group in the order they start (a
 // device counter).  One group of a launch at most is incomplete at any time, so that this is soon the case.  Where it is not,
 // because other kernels hold the compute units, or incomplete groups of many launches (nine or more) hold all of them against
@@ -50,7 +50,8 @@ constexpr int REC_SLOTS = 4;                   // steps a vector's slots are dee
 constexpr int REC_SPIN_LIMIT = 1 << 24;        // polls inside the chain (bounded only so that a fault elsewhere cannot hang it)
 constexpr int REC_ARRIVE_POLLS = 256;          // polls per step for the rest of a group to start
 constexpr unsigned REC_ALONE = 1u << 31;       // in a group's word beside the number of workgroups that have started
-constexpr int REC_PAUSE = 5;                    // times 64 cycles (0: 2.18 ms for 1024 steps of the RNN, 3: 2.04, 5: 2.02, 8: 2.18)
+constexpr int REC_PAUSE = 4;                    // times 64 cycles (1024 steps of the RNN and of the GRU: 3: 2.18 and 4.00 ms, 4: 2.06 and 4.01, 7: 2.22 and 4.00)
+constexpr int REC_LOCAL_FROM = 12;             // steps from which groups on one XCD pay for their launch (8 steps: 38.3 us against 39.8 for the RNN, 36.8 against 35.4 for the LSTM)
 constexpr int REC_COLS = 32;                   // channels per workgroup
 constexpr int REC_MAX_WG = 64;
 constexpr int REC_XCDS = 16;                   // XCDs that a launch may meet (the chip has eight)
@@ -111,7 +112,7 @@ __device__ __forceinline__ unsigned kept(unsigned v) {
 // LOCAL: the group is on one XCD, whose L2 is where its stores meet its loads; otherwise stores go to memory.
 template <int RT> constexpr int rec_tiles() { return RT ? RT : 1; }
 template <int RT> constexpr int rec_rows() { return RT ? 16 * RT : 8; }
-template <int RT> constexpr int rec_block() { return RT ? 1024 : 512; }       // bytes of a block
+template <int RT> constexpr int rec_channels() { return RT ? 2 : 1; }         // of a row that a thread has in the elementwise part
 template <bool LOCAL, int RT>
 struct Ring {
   __amdgpu_buffer_rsrc_t buf;
@@ -124,8 +125,8 @@ struct Ring {
     mine = group * rec_tiles<RT>() * tile;
     slot = groups * rec_tiles<RT>() * tile;
     buf = buffer(base, (long)REC_UNITS * REC_SLOTS * slot);
-    const int t = threadIdx.x;
-    word = kept(RT ? t * 4 : t < 128 ? (t >> 5) * 256 + (t & 31) * 4 : REC_OUTSIDE);
+    const int t = RT ? threadIdx.x : threadIdx.x >> 1;
+    word = kept(RT ? t * 4 : threadIdx.x & 1 ? REC_OUTSIDE : (t >> 5) * 256 + (t & 31) * 4);
   }
   __device__ __forceinline__ int at(int u, long step, int rt, int block) const {
     return (u * REC_SLOTS + ((int)step & (REC_SLOTS - 1))) * slot + mine + rt * tile + (RT ? block * 1024 : (block >> 1) * 1024 + (block & 1) * 128);
@@ -236,12 +237,12 @@ __device__ __forceinline__ float2 get(const Partials<RT, SLOTS>& p, int set, int
   float2 s = make_float2(0.f, 0.f);
 #pragma unroll
   for (int w = 0; w < 4; ++w) {
-    float2 t = *reinterpret_cast<const float2*>(&p.v[set][slot][w][row][col]);
-    if (RT == 0) {
-      const float2 o = *reinterpret_cast<const float2*>(&p.v[set][slot][w][row + 8][col]);
-      t.x += o.x; t.y += o.y;
+    if (RT) {
+      const float2 t = *reinterpret_cast<const float2*>(&p.v[set][slot][w][row][col]);
+      s.x += t.x; s.y += t.y;
+    } else {
+      s.x += p.v[set][slot][w][row][col] + p.v[set][slot][w][row + 8][col];
     }
-    s.x += t.x; s.y += t.y;
   }
   return s;
 }
@@ -253,11 +254,22 @@ __device__ __forceinline__ void meet() {
   asm volatile("" ::: "memory");
 }
 
-// two channels of a row
-__device__ __forceinline__ float2 un2(unsigned w) { return make_float2(__uint_as_float(w << 16), __uint_as_float(w & 0xFFFF0000u)); }
-__device__ __forceinline__ unsigned pk(float2 v) { return pack_bf16x2(v.x, v.y); }
+// A thread's channels of a row, two (CH = 2), or one of the two that it shares a word with its neighbour for (in .x)
+template <int CH>
+__device__ __forceinline__ float2 un2(unsigned w) {
+  const float2 v = make_float2(__uint_as_float(w << 16), __uint_as_float(w & 0xFFFF0000u));
+  return CH == 2 ? v : make_float2(threadIdx.x & 1 ? v.y : v.x, 0.f);
+}
+template <int CH>
+__device__ __forceinline__ unsigned pk(float2 v) {
+  if (CH == 2) return pack_bf16x2(v.x, v.y);
+  const float other = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v.x), 0xB1, 0xF, 0xF, true));   // quad_perm [1,0,3,2]
+  return threadIdx.x & 1 ? pack_bf16x2(other, v.x) : pack_bf16x2(v.x, other);
+}
 __device__ __forceinline__ unsigned bld2(__amdgpu_buffer_rsrc_t b, unsigned off, int more = 0) { return __builtin_amdgcn_raw_buffer_load_b32(b, (int)off, more, 0); }
+template <int CH>
 __device__ __forceinline__ float2 bldf2(__amdgpu_buffer_rsrc_t b, unsigned off, int more = 0) {
+  if (CH == 1) return make_float2(__builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(b, (int)off, more, 0)), 0.f);
   return __builtin_bit_cast(float2, (uint2v)__builtin_amdgcn_raw_buffer_load_b64(b, (int)off, more, 0));
 }
 __device__ __forceinline__ void bst2(unsigned w, __amdgpu_buffer_rsrc_t b, unsigned off, int more = 0) { __builtin_amdgcn_raw_buffer_store_b32(w, b, (int)off, more, 0); }
@@ -269,8 +281,8 @@ __device__ __forceinline__ void empty(const Ring<LOCAL, RT>& ring, int u, long s
 #pragma unroll
   for (int rt = 0; rt < rec_tiles<RT>(); ++rt) ring.put(ring.at(u, step, rt, member), REC_EMPTY);
 }
-template <typename F>
-__device__ __forceinline__ float2 map2(F f) { return make_float2(f(0), f(1)); }
+template <int CH, typename F>
+__device__ __forceinline__ float2 map2(F f) { return make_float2(f(0), CH == 2 ? f(1) : 0.f); }
 __device__ __forceinline__ float at2(float2 v, int i) { return i ? v.y : v.x; }
 __device__ __forceinline__ float sigmoid1(float a) { return 1.f / (1.f + expf(-a)); }
 
@@ -357,29 +369,32 @@ __device__ __forceinline__ bool all_started(const RecArgs& a, int wpg, int group
   return __builtin_amdgcn_readfirstlane(given_up) == 0;
 }
 
-// Which channels and rows a thread has in the elementwise part: two channels of a row per tile (half a tile: the first two
-// wavefronts, 128 threads).
+// Which channels and rows a thread has in the elementwise part: two channels of a row per tile, or (half a tile) one.
 template <int RT>
 struct Place {
-  static constexpr int TILES = rec_tiles<RT>();
+  static constexpr int TILES = rec_tiles<RT>(), CH = rec_channels<RT>();
   int row, col;                                       // in a tile, among the workgroup's channels
   bool on[TILES], on_f[TILES];                        // inside the state, inside the inner state
-  unsigned x2[TILES], f2[TILES], f4[TILES], c4[TILES];   // bytes to the place: state and inner state in bf16, inner state and channel in fp32
+  unsigned x2[TILES], f2[TILES];                      // bytes to the pair of channels in bf16: in the state, in the inner state
+  unsigned f4[TILES], c4[TILES];                      // to the thread's own in fp32: in the inner state, in a row of channels
+  unsigned xs[TILES], fs[TILES];                      // as x2, f2, for the thread that stores the pair
   __device__ __forceinline__ Place() {
-    const int t = threadIdx.x;
-    row = RT ? (t >> 2) & 15 : (t >> 2) & 7;
-    col = (RT ? 8 * (t >> 6) : 8 * ((t >> 5) & 3)) + 2 * (t & 3);
+    const int t = threadIdx.x / (2 / CH);
+    row = (t >> 2) & (RT ? 15 : 7);
+    col = 8 * (t >> (RT ? 6 : 5)) + 2 * (t & 3) + (CH == 1 ? threadIdx.x & 1 : 0);
   }
   __device__ __forceinline__ void set(int group, int member, int N, int D, int F, int width, int width_f) {
-    const int c = member * REC_COLS + col;
+    const int c = member * REC_COLS + col, pair = c & ~1;
+    const bool stores = CH == 2 || !(threadIdx.x & 1);
 #pragma unroll
     for (int rt = 0; rt < TILES; ++rt) {
       const int r = group * rec_rows<RT>() + 16 * rt + row;
-      const bool in = r < N && (RT || threadIdx.x < 128);
-      on[rt] = in && c < width;
-      on_f[rt] = in && c < width_f;
-      x2[rt] = kept(on[rt] ? (unsigned)(r * D + c) * 2 : REC_OUTSIDE);
-      f2[rt] = kept(on_f[rt] ? (unsigned)(r * F + c) * 2 : REC_OUTSIDE);
+      on[rt] = r < N && c < width;
+      on_f[rt] = r < N && c < width_f;
+      x2[rt] = kept(on[rt] ? (unsigned)(r * D + pair) * 2 : REC_OUTSIDE);
+      f2[rt] = kept(on_f[rt] ? (unsigned)(r * F + pair) * 2 : REC_OUTSIDE);
+      xs[rt] = CH == 2 ? x2[rt] : kept(stores ? x2[rt] : REC_OUTSIDE);
+      fs[rt] = CH == 2 ? f2[rt] : kept(stores ? f2[rt] : REC_OUTSIDE);
       f4[rt] = kept(on_f[rt] ? (unsigned)(r * F + c) * 4 : REC_OUTSIDE);
       c4[rt] = kept(on[rt] ? (unsigned)c * 4 : REC_OUTSIDE);
     }
@@ -401,7 +416,7 @@ template <int KIND, int KQ, int RT, bool ALONE, bool LOCAL, int SLOTS>
 __device__ __forceinline__ bool forward_chain(const RecArgs& a, const Ring<LOCAL, RT>& ring, int own, unsigned started, Partials<RT, SLOTS>& part) {
   constexpr int UNITS = KIND == K_LSTM ? 4 : KIND == K_GRU ? 3 : 2;
   constexpr bool TWO = KIND == K_RNN || KIND == K_GRU;       // two dependent products per step
-  constexpr int TILES = rec_tiles<RT>();
+  constexpr int TILES = rec_tiles<RT>(), CH = rec_channels<RT>();
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int N = (int)a.N, H = (int)a.H, F = (int)a.F, D = (int)a.D;
@@ -431,7 +446,7 @@ __device__ __forceinline__ bool forward_chain(const RecArgs& a, const Ring<LOCAL
   auto place = [&](int member) __attribute__((always_inline)) {      // where the member's channels are, and its state at this step
     at.set(ring.group, member, N, D, F, KIND == K_RNN ? D : H, KIND == K_RNN ? F : H);
 #pragma unroll
-    for (int rt = 0; rt < TILES; ++rt) xs[rt] = un2(bld2(x.buf(), at.x2[rt]));
+    for (int rt = 0; rt < TILES; ++rt) xs[rt] = un2<CH>(bld2(x.buf(), at.x2[rt]));
   };
   members<ALONE>(own, ring.wpg, [&](int member) __attribute__((always_inline)) {
     place(member);
@@ -448,10 +463,10 @@ __device__ __forceinline__ bool forward_chain(const RecArgs& a, const Ring<LOCAL
 #pragma unroll
     for (int rt = 0; rt < TILES; ++rt) {
 #pragma unroll
-      for (int q = 0; q < SLOTS; ++q) v.ux[rt][q] = bldf2(ub, at.f4[rt], KIND == K_RNN ? 0 : q * h4);
-      if (KIND == K_GRU) v.un[rt] = bldf2(ub, at.f4[rt], 2 * h4);
+      for (int q = 0; q < SLOTS; ++q) v.ux[rt][q] = bldf2<CH>(ub, at.f4[rt], KIND == K_RNN ? 0 : q * h4);
+      if (KIND == K_GRU) v.un[rt] = bldf2<CH>(ub, at.f4[rt], 2 * h4);
       if (KIND == K_RNN) {
-        v.lm[rt] = bldf2(lb, at.c4[rt]);
+        v.lm[rt] = bldf2<CH>(lb, at.c4[rt]);
         v.lw[rt] = bld2(tb, at.x2[rt]);
       }
     }
@@ -489,61 +504,61 @@ __device__ __forceinline__ bool forward_chain(const RecArgs& a, const Ring<LOCAL
         }
         constexpr int S1 = SLOTS > 1 ? 1 : 0, S2 = SLOTS > 2 ? 2 : 0, S3 = SLOTS > 3 ? 3 : 0;
         if (KIND == K_RNN) {
-          if (a.tanh_act) s[0] = map2([&](int i) { return tanhf(at2(s[0], i)); });
-          zw[rt] = pk(s[0]);
+          if (a.tanh_act) s[0] = map2<CH>([&](int i) { return tanhf(at2(s[0], i)); });
+          zw[rt] = pk<CH>(s[0]);
           publish(ring, ring.at(1, l, rt, member), at.on_f[rt] ? zw[rt] : 0u);
         } else if (KIND == K_GATED) {
-          const float2 u = map2([&](int i) { return sigmoid1(at2(s[0], i)); });
-          const float2 cc = map2([&](int i) { return tanhf(at2(s[S1], i)); });
+          const float2 u = map2<CH>([&](int i) { return sigmoid1(at2(s[0], i)); });
+          const float2 cc = map2<CH>([&](int i) { return tanhf(at2(s[S1], i)); });
           const float2 av = make_float2(1.f - u.x, 1.f - u.y);
-          ow[rt] = pk(map2([&](int i) { return fmaf(at2(av, i), at2(xs[rt], i), at2(u, i) * at2(cc, i)); }));
+          ow[rt] = pk<CH>(map2<CH>([&](int i) { return fmaf(at2(av, i), at2(xs[rt], i), at2(u, i) * at2(cc, i)); }));
           publish(ring, ring.at(0, l + 1, rt, member), at.on[rt] ? ow[rt] : 0u);
-          zw[rt] = pk(u); cw[rt] = pk(cc); aw[rt] = pk(av);
-          xs[rt] = un2(ow[rt]);
+          zw[rt] = pk<CH>(u); cw[rt] = pk<CH>(cc); aw[rt] = pk<CH>(av);
+          xs[rt] = un2<CH>(ow[rt]);
         } else if (KIND == K_LSTM) {
-          const float2 ig = map2([&](int i) { return sigmoid1(at2(s[0], i)); });
-          const float2 fg = map2([&](int i) { return sigmoid1(at2(s[S1], i)); });
-          const float2 og = map2([&](int i) { return sigmoid1(at2(s[S2], i)); });
-          const float2 gg = map2([&](int i) { return tanhf(at2(s[S3], i)); });
-          const float2 cn = map2([&](int i) { return fmaf(at2(fg, i), at2(xs[rt], i), at2(ig, i) * at2(gg, i)); });
-          const float2 hn = map2([&](int i) { return at2(og, i) * tanhf(at2(cn, i)); });
-          hw[rt] = pk(hn);
+          const float2 ig = map2<CH>([&](int i) { return sigmoid1(at2(s[0], i)); });
+          const float2 fg = map2<CH>([&](int i) { return sigmoid1(at2(s[S1], i)); });
+          const float2 og = map2<CH>([&](int i) { return sigmoid1(at2(s[S2], i)); });
+          const float2 gg = map2<CH>([&](int i) { return tanhf(at2(s[S3], i)); });
+          const float2 cn = map2<CH>([&](int i) { return fmaf(at2(fg, i), at2(xs[rt], i), at2(ig, i) * at2(gg, i)); });
+          const float2 hn = map2<CH>([&](int i) { return at2(og, i) * tanhf(at2(cn, i)); });
+          hw[rt] = pk<CH>(hn);
           publish(ring, ring.at(0, l + 1, rt, member), at.on[rt] ? hw[rt] : 0u);
-          cw[rt] = pk(cn); zw[rt] = pk(ig); rw[rt] = pk(fg); ow[rt] = pk(og); gw[rt] = pk(gg);
-          xs[rt] = un2(cw[rt]);
+          cw[rt] = pk<CH>(cn); zw[rt] = pk<CH>(ig); rw[rt] = pk<CH>(fg); ow[rt] = pk<CH>(og); gw[rt] = pk<CH>(gg);
+          xs[rt] = un2<CH>(cw[rt]);
         } else {
-          const float2 r = map2([&](int i) { return sigmoid1(at2(s[S1], i)); });
-          publish(ring, ring.at(1, l, rt, member), at.on[rt] ? pk(make_float2(r.x * xs[rt].x, r.y * xs[rt].y)) : 0u);
-          rw[rt] = pk(r);
+          const float2 r = map2<CH>([&](int i) { return sigmoid1(at2(s[S1], i)); });
+          publish(ring, ring.at(1, l, rt, member), at.on[rt] ? pk<CH>(make_float2(r.x * xs[rt].x, r.y * xs[rt].y)) : 0u);
+          rw[rt] = pk<CH>(r);
           now.ux[rt][0] = s[0];
         }
       }
       auto results = [&]() __attribute__((always_inline)) {
 #pragma unroll
       for (int rt = 0; rt < TILES; ++rt) {
-        if (KIND == K_RNN) bst2(zw[rt], zb, at.f2[rt]);
+        if (KIND == K_RNN) bst2(zw[rt], zb, at.fs[rt]);
         if (KIND == K_GATED) {
-          bst2(ow[rt], xb, at.x2[rt]);
-          bst2(zw[rt], zb, at.f2[rt]);
-          bst2(cw[rt], zb, at.f2[rt], h2);
-          bst2(aw[rt], lb, at.x2[rt]);
+          bst2(ow[rt], xb, at.xs[rt]);
+          bst2(zw[rt], zb, at.fs[rt]);
+          bst2(cw[rt], zb, at.fs[rt], h2);
+          bst2(aw[rt], lb, at.xs[rt]);
         }
         if (KIND == K_LSTM) {
-          bst2(hw[rt], xb, at.x2[rt], h2);
-          bst2(cw[rt], xb, at.x2[rt]);
-          bst2(zw[rt], zb, at.f2[rt]);
-          bst2(rw[rt], zb, at.f2[rt], h2);
-          bst2(ow[rt], zb, at.f2[rt], 2 * h2);
-          bst2(gw[rt], zb, at.f2[rt], 3 * h2);
-          bst2(rw[rt], lb, at.x2[rt]);
-          bst2(0u, lb, at.x2[rt], h2);
+          bst2(hw[rt], xb, at.xs[rt], h2);
+          bst2(cw[rt], xb, at.xs[rt]);
+          bst2(zw[rt], zb, at.fs[rt]);
+          bst2(rw[rt], zb, at.fs[rt], h2);
+          bst2(ow[rt], zb, at.fs[rt], 2 * h2);
+          bst2(gw[rt], zb, at.fs[rt], 3 * h2);
+          bst2(rw[rt], lb, at.xs[rt]);
+          bst2(0u, lb, at.xs[rt], h2);
         }
         if (KIND == K_GRU) {       // (the second half of the step works on the stored gate)
           const float2 s = now.ux[rt][0];
-          zw[rt] = pk(map2([&](int i) { return sigmoid1(at2(s, i)); }));
-          now.ux[rt][0] = un2(zw[rt]);
-          bst2(zw[rt], zb, at.f2[rt]);
-          bst2(rw[rt], zb, at.f2[rt], h2);
+          zw[rt] = pk<CH>(map2<CH>([&](int i) { return sigmoid1(at2(s, i)); }));
+          now.ux[rt][0] = un2<CH>(zw[rt]);
+          bst2(zw[rt], zb, at.fs[rt]);
+          bst2(rw[rt], zb, at.fs[rt], h2);
         }
       }
       };
@@ -570,7 +585,7 @@ __device__ __forceinline__ bool forward_chain(const RecArgs& a, const Ring<LOCAL
           read_step(now);
           if (KIND == K_GRU) {
 #pragma unroll
-            for (int rt = 0; rt < TILES; ++rt) now.ux[rt][0] = un2(bld2(zb, at.f2[rt]));
+            for (int rt = 0; rt < TILES; ++rt) now.ux[rt][0] = un2<CH>(bld2(zb, at.f2[rt]));
           }
           in.ask(ring, 1, l);
         }
@@ -585,24 +600,24 @@ __device__ __forceinline__ bool forward_chain(const RecArgs& a, const Ring<LOCAL
         for (int rt = 0; rt < TILES; ++rt) {
           float2 s = get(part, set, 0, 16 * rt + at.row, at.col);
           if (KIND == K_RNN) {
-            const float2 lm = a.lambda ? now.lm[rt] : a.lambda_tok ? un2(now.lw[rt]) : make_float2(1.f, 1.f);
-            ow[rt] = pk(map2([&](int i) { return at2(s, i) + at2(lm, i) * at2(xs[rt], i); }));
+            const float2 lm = a.lambda ? now.lm[rt] : a.lambda_tok ? un2<CH>(now.lw[rt]) : make_float2(1.f, 1.f);
+            ow[rt] = pk<CH>(map2<CH>([&](int i) { return at2(s, i) + at2(lm, i) * at2(xs[rt], i); }));
           } else {
             const float2 zg = now.ux[rt][0];
-            const float2 nn = map2([&](int i) { return tanhf(at2(s, i) + at2(now.un[rt], i)); });
+            const float2 nn = map2<CH>([&](int i) { return tanhf(at2(s, i) + at2(now.un[rt], i)); });
             const float2 av = make_float2(1.f - zg.x, 1.f - zg.y);
-            ow[rt] = pk(map2([&](int i) { return fmaf(at2(av, i), at2(xs[rt], i), at2(zg, i) * at2(nn, i)); }));
-            nw[rt] = pk(nn); aw[rt] = pk(av);
+            ow[rt] = pk<CH>(map2<CH>([&](int i) { return fmaf(at2(av, i), at2(xs[rt], i), at2(zg, i) * at2(nn, i)); }));
+            nw[rt] = pk<CH>(nn); aw[rt] = pk<CH>(av);
           }
           publish(ring, ring.at(0, l + 1, rt, member), at.on[rt] ? ow[rt] : 0u);
-          xs[rt] = un2(ow[rt]);
+          xs[rt] = un2<CH>(ow[rt]);
         }
 #pragma unroll
         for (int rt = 0; rt < TILES; ++rt) {
-          bst2(ow[rt], xb, at.x2[rt]);
+          bst2(ow[rt], xb, at.xs[rt]);
           if (KIND == K_GRU) {
-            bst2(nw[rt], zb, at.f2[rt], 2 * h2);
-            bst2(aw[rt], lb, at.x2[rt]);
+            bst2(nw[rt], zb, at.fs[rt], 2 * h2);
+            bst2(aw[rt], lb, at.xs[rt]);
           }
         }
         if (!ALONE) in.ask(ring, 0, l + 1);
@@ -637,7 +652,7 @@ __device__ __forceinline__ bool backward_chain(const RecArgs& a, const Ring<LOCA
   constexpr int UNITS = KIND == K_LSTM ? 4 : KIND == K_GRU ? 3 : 2;
   constexpr bool TWO = KIND == K_RNN || KIND == K_GRU;       // two dependent products per step
   constexpr int U0 = TWO ? 1 : 0;                            // first unit of the (second) product with W1
-  constexpr int TILES = rec_tiles<RT>();
+  constexpr int TILES = rec_tiles<RT>(), CH = rec_channels<RT>();
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int N = (int)a.N, H = (int)a.H, F = (int)a.F, D = (int)a.D;
@@ -673,8 +688,8 @@ __device__ __forceinline__ bool backward_chain(const RecArgs& a, const Ring<LOCA
     at.set(ring.group, member, N, D, F, KIND == K_RNN ? D : H, KIND == K_RNN ? F : H);
 #pragma unroll
     for (int rt = 0; rt < TILES; ++rt) {
-      gs[rt] = un2(bld2(g.buf(), at.x2[rt], ho));
-      gc[rt] = KIND == K_LSTM ? un2(bld2(g.buf(), at.x2[rt])) : make_float2(0.f, 0.f);
+      gs[rt] = un2<CH>(bld2(g.buf(), at.x2[rt], ho));
+      gc[rt] = KIND == K_LSTM ? un2<CH>(bld2(g.buf(), at.x2[rt])) : make_float2(0.f, 0.f);
     }
   };
   members<ALONE>(own, ring.wpg, [&](int member) __attribute__((always_inline)) {
@@ -697,7 +712,7 @@ __device__ __forceinline__ bool backward_chain(const RecArgs& a, const Ring<LOCA
     const __amdgpu_buffer_rsrc_t nb = buffer(x.base + x.n, x.n);
 #pragma unroll
     for (int rt = 0; rt < TILES; ++rt) {
-      if (KIND == K_RNN) v.lmf[rt] = bldf2(lb, at.c4[rt]);
+      if (KIND == K_RNN) v.lmf[rt] = bldf2<CH>(lb, at.c4[rt]);
       v.lw[rt] = bld2(tb, at.x2[rt], ho);
       v.ew[rt] = bld2(eb, at.x2[rt], ho);
       if (KIND == K_LSTM) {
@@ -719,43 +734,43 @@ __device__ __forceinline__ bool backward_chain(const RecArgs& a, const Ring<LOCA
     float2 past[TILES], pastc[TILES];      // what reaches g[l] (hidden, cell) past the product with W1
     // the LSTM's gradient at the cell state through the hidden part
     auto tanh_c = [&](int rt) __attribute__((always_inline)) {
-      const float2 cn = un2(now.xn[rt]);
-      return map2([&](int i) { return tanhf(at2(cn, i)); });
+      const float2 cn = un2<CH>(now.xn[rt]);
+      return map2<CH>([&](int i) { return tanhf(at2(cn, i)); });
     };
     auto through_h = [&](int rt, float2 tc) __attribute__((always_inline)) {
-      const float2 og = un2(now.zw[rt][2]);
-      return map2([&](int i) { return at2(gs[rt], i) * at2(og, i) * (1.f - at2(tc, i) * at2(tc, i)); });
+      const float2 og = un2<CH>(now.zw[rt][2]);
+      return map2<CH>([&](int i) { return at2(gs[rt], i) * at2(og, i) * (1.f - at2(tc, i) * at2(tc, i)); });
     };
     // what the cells' elementwise parts leave for the products
     auto publish_gates = [&](int member) __attribute__((always_inline)) {
 #pragma unroll
       for (int rt = 0; rt < TILES; ++rt) {
-        const float2 G = gs[rt], xv = un2(now.xw[rt]);
+        const float2 G = gs[rt], xv = un2<CH>(now.xw[rt]);
         if (KIND == K_GATED) {
-          const float2 u = un2(now.zw[rt][0]), cc = un2(now.zw[rt][1]);
-          const float2 du = map2([&](int i) { return at2(G, i) * (at2(cc, i) - at2(xv, i)) * at2(u, i) * (1.f - at2(u, i)); });
-          const float2 dc = map2([&](int i) { return at2(G, i) * at2(u, i) * (1.f - at2(cc, i) * at2(cc, i)); });
-          publish(ring, ring.at(0, l, rt, member), at.on[rt] ? pk(du) : 0u);
-          publish(ring, ring.at(1, l, rt, member), at.on[rt] ? pk(dc) : 0u);
+          const float2 u = un2<CH>(now.zw[rt][0]), cc = un2<CH>(now.zw[rt][1]);
+          const float2 du = map2<CH>([&](int i) { return at2(G, i) * (at2(cc, i) - at2(xv, i)) * at2(u, i) * (1.f - at2(u, i)); });
+          const float2 dc = map2<CH>([&](int i) { return at2(G, i) * at2(u, i) * (1.f - at2(cc, i) * at2(cc, i)); });
+          publish(ring, ring.at(0, l, rt, member), at.on[rt] ? pk<CH>(du) : 0u);
+          publish(ring, ring.at(1, l, rt, member), at.on[rt] ? pk<CH>(dc) : 0u);
         } else if (KIND == K_LSTM) {
-          const float2 ig = un2(now.zw[rt][0]), fg = un2(now.zw[rt][1]), og = un2(now.zw[rt][2]), gg = un2(now.zw[rt][3]);
+          const float2 ig = un2<CH>(now.zw[rt][0]), fg = un2<CH>(now.zw[rt][1]), og = un2<CH>(now.zw[rt][2]), gg = un2<CH>(now.zw[rt][3]);
           const float2 tc = tanh_c(rt), th = through_h(rt, tc);
           pastc[rt] = make_float2(th.x * fg.x, th.y * fg.y);
           const float2 dct = make_float2(gc[rt].x + th.x, gc[rt].y + th.y);
-          const float2 di = map2([&](int i) { return at2(dct, i) * at2(gg, i) * at2(ig, i) * (1.f - at2(ig, i)); });
-          const float2 df = map2([&](int i) { return at2(dct, i) * at2(xv, i) * at2(fg, i) * (1.f - at2(fg, i)); });
-          const float2 dO = map2([&](int i) { return at2(G, i) * at2(tc, i) * at2(og, i) * (1.f - at2(og, i)); });
-          const float2 dg = map2([&](int i) { return at2(dct, i) * at2(ig, i) * (1.f - at2(gg, i) * at2(gg, i)); });
-          publish(ring, ring.at(0, l, rt, member), at.on[rt] ? pk(di) : 0u);
-          publish(ring, ring.at(1, l, rt, member), at.on[rt] ? pk(df) : 0u);
-          publish(ring, ring.at(2, l, rt, member), at.on[rt] ? pk(dO) : 0u);
-          publish(ring, ring.at(3, l, rt, member), at.on[rt] ? pk(dg) : 0u);
+          const float2 di = map2<CH>([&](int i) { return at2(dct, i) * at2(gg, i) * at2(ig, i) * (1.f - at2(ig, i)); });
+          const float2 df = map2<CH>([&](int i) { return at2(dct, i) * at2(xv, i) * at2(fg, i) * (1.f - at2(fg, i)); });
+          const float2 dO = map2<CH>([&](int i) { return at2(G, i) * at2(tc, i) * at2(og, i) * (1.f - at2(og, i)); });
+          const float2 dg = map2<CH>([&](int i) { return at2(dct, i) * at2(ig, i) * (1.f - at2(gg, i) * at2(gg, i)); });
+          publish(ring, ring.at(0, l, rt, member), at.on[rt] ? pk<CH>(di) : 0u);
+          publish(ring, ring.at(1, l, rt, member), at.on[rt] ? pk<CH>(df) : 0u);
+          publish(ring, ring.at(2, l, rt, member), at.on[rt] ? pk<CH>(dO) : 0u);
+          publish(ring, ring.at(3, l, rt, member), at.on[rt] ? pk<CH>(dg) : 0u);
         } else if (KIND == K_GRU) {
-          const float2 zg = un2(now.zw[rt][0]), nn = un2(now.zw[rt][2]);
-          const float2 dn = map2([&](int i) { return at2(G, i) * at2(zg, i) * (1.f - at2(nn, i) * at2(nn, i)); });
-          const float2 dz = map2([&](int i) { return at2(G, i) * (at2(nn, i) - at2(xv, i)) * at2(zg, i) * (1.f - at2(zg, i)); });
-          publish(ring, ring.at(2, l, rt, member), at.on[rt] ? pk(dn) : 0u);
-          publish(ring, ring.at(0, l, rt, member), at.on[rt] ? pk(dz) : 0u);
+          const float2 zg = un2<CH>(now.zw[rt][0]), nn = un2<CH>(now.zw[rt][2]);
+          const float2 dn = map2<CH>([&](int i) { return at2(G, i) * at2(zg, i) * (1.f - at2(nn, i) * at2(nn, i)); });
+          const float2 dz = map2<CH>([&](int i) { return at2(G, i) * (at2(nn, i) - at2(xv, i)) * at2(zg, i) * (1.f - at2(zg, i)); });
+          publish(ring, ring.at(2, l, rt, member), at.on[rt] ? pk<CH>(dn) : 0u);
+          publish(ring, ring.at(0, l, rt, member), at.on[rt] ? pk<CH>(dz) : 0u);
         }
       }
     };
@@ -797,13 +812,13 @@ __device__ __forceinline__ bool backward_chain(const RecArgs& a, const Ring<LOCA
         for (int rt = 0; rt < TILES; ++rt) {
           const float2 s = get(part, set, 0, 16 * rt + at.row, at.col);
           if (KIND == K_RNN) {
-            const float2 t = un2(now.zw[rt][0]);
-            const float2 v = map2([&](int i) { return at2(s, i) * (a.dphi ? at2(t, i) : a.tanh_act ? 1.f - at2(t, i) * at2(t, i) : 1.f); });
-            publish(ring, ring.at(0, l, rt, member), at.on_f[rt] ? pk(v) : 0u);
+            const float2 t = un2<CH>(now.zw[rt][0]);
+            const float2 v = map2<CH>([&](int i) { return at2(s, i) * (a.dphi ? at2(t, i) : a.tanh_act ? 1.f - at2(t, i) * at2(t, i) : 1.f); });
+            publish(ring, ring.at(0, l, rt, member), at.on_f[rt] ? pk<CH>(v) : 0u);
           } else {
-            const float2 r = un2(now.zw[rt][1]), xv = un2(now.xw[rt]);
-            const float2 dr = map2([&](int i) { return at2(s, i) * at2(xv, i) * at2(r, i) * (1.f - at2(r, i)); });
-            publish(ring, ring.at(1, l, rt, member), at.on[rt] ? pk(dr) : 0u);
+            const float2 r = un2<CH>(now.zw[rt][1]), xv = un2<CH>(now.xw[rt]);
+            const float2 dr = map2<CH>([&](int i) { return at2(s, i) * at2(xv, i) * at2(r, i) * (1.f - at2(r, i)); });
+            publish(ring, ring.at(1, l, rt, member), at.on[rt] ? pk<CH>(dr) : 0u);
             past[rt] = make_float2(s.x * r.x, s.y * r.y);
           }
         }
@@ -823,7 +838,7 @@ __device__ __forceinline__ bool backward_chain(const RecArgs& a, const Ring<LOCA
         first_product(member);
 #pragma unroll
         for (int rt = 0; rt < TILES; ++rt) {
-          const float2 s = get(part, set, 0, 16 * rt + at.row, at.col), r = un2(now.zw[rt][1]);
+          const float2 s = get(part, set, 0, 16 * rt + at.row, at.col), r = un2<CH>(now.zw[rt][1]);
           past[rt] = make_float2(s.x * r.x, s.y * r.y);
         }
         set ^= 1;
@@ -832,7 +847,7 @@ __device__ __forceinline__ bool backward_chain(const RecArgs& a, const Ring<LOCA
       for (int rt = 0; rt < TILES; ++rt) {
         if (KIND != K_GRU) past[rt] = make_float2(0.f, 0.f);
         if (KIND == K_LSTM && ALONE) {
-          const float2 th = through_h(rt, tanh_c(rt)), fg = un2(now.zw[rt][1]);
+          const float2 th = through_h(rt, tanh_c(rt)), fg = un2<CH>(now.zw[rt][1]);
           pastc[rt] = make_float2(th.x * fg.x, th.y * fg.y);
         }
       }
@@ -852,14 +867,14 @@ __device__ __forceinline__ bool backward_chain(const RecArgs& a, const Ring<LOCA
 #pragma unroll
       for (int rt = 0; rt < TILES; ++rt) {
         const float2 s = get(part, set, 0, 16 * rt + at.row, at.col);
-        const float2 ev = un2(now.ew[rt]), lm = a.lambda_tok ? un2(now.lw[rt]) : KIND == K_RNN && a.lambda ? now.lmf[rt] : make_float2(1.f, 1.f);
-        o[rt] = pk(map2([&](int i) { return (at2(s, i) + at2(past[rt], i) + at2(ev, i)) + at2(lm, i) * at2(gs[rt], i); }));
+        const float2 ev = un2<CH>(now.ew[rt]), lm = a.lambda_tok ? un2<CH>(now.lw[rt]) : KIND == K_RNN && a.lambda ? now.lmf[rt] : make_float2(1.f, 1.f);
+        o[rt] = pk<CH>(map2<CH>([&](int i) { return (at2(s, i) + at2(past[rt], i) + at2(ev, i)) + at2(lm, i) * at2(gs[rt], i); }));
         if (KIND == K_RNN) publish(ring, ring.at(1, l, rt, member), at.on[rt] ? o[rt] : 0u);
-        gs[rt] = un2(o[rt]);
+        gs[rt] = un2<CH>(o[rt]);
         if (KIND == K_LSTM) {
-          const float2 e2 = un2(now.ew2[rt]), l2 = un2(now.lw2[rt]);
-          oc[rt] = pk(map2([&](int i) { return (at2(pastc[rt], i) + at2(e2, i)) + at2(l2, i) * at2(gc[rt], i); }));
-          gc[rt] = un2(oc[rt]);
+          const float2 e2 = un2<CH>(now.ew2[rt]), l2 = un2<CH>(now.lw2[rt]);
+          oc[rt] = pk<CH>(map2<CH>([&](int i) { return (at2(pastc[rt], i) + at2(e2, i)) + at2(l2, i) * at2(gc[rt], i); }));
+          gc[rt] = un2<CH>(oc[rt]);
         }
       }
       if (!TWO) {
@@ -869,8 +884,8 @@ __device__ __forceinline__ bool backward_chain(const RecArgs& a, const Ring<LOCA
       const __amdgpu_buffer_rsrc_t gb = buffer(g.base - g.n, g.n);       // g[l]
 #pragma unroll
       for (int rt = 0; rt < TILES; ++rt) {
-        bst2(o[rt], gb, at.x2[rt], ho);
-        if (KIND == K_LSTM) bst2(oc[rt], gb, at.x2[rt]);
+        bst2(o[rt], gb, at.xs[rt], ho);
+        if (KIND == K_LSTM) bst2(oc[rt], gb, at.xs[rt]);
       }
       if (!ALONE && KIND == K_RNN) in.ask(ring, 1, l);
       if (!ALONE) now = next;
@@ -929,7 +944,7 @@ hipError_t launch_rec(const RecArgs& a, bool forward, hipStream_t s) {
   const long ring = (long)REC_UNITS * REC_SLOTS * groups * RT * wpg * 1024;
   const long ring_local = (long)REC_UNITS * REC_SLOTS * locals * (RTL ? wpg : (wpg + 1) / 2) * 1024;
   const long n16 = (ring + ring_local) / 16;
-  const bool local = a.wait == REC_WAIT;
+  const bool local = a.wait == REC_WAIT && a.L >= REC_LOCAL_FROM;
   hipLaunchKernelGGL(rec_fill_kernel, dim3((unsigned)((n16 + 255) / 256)), dim3(256), 0, s, reinterpret_cast<uint4*>(a.ring), n16,
                      reinterpret_cast<PlaceWords*>(a.counter), a.wait == REC_ALONE_ANYHOW ? REC_ALONE : 0u);
   // enough workgroups that every XCD of the eight has a group's number of them for each group it can be asked to take

@@ -191,9 +191,9 @@ def test_chains_along_time_by_one_workgroup(B, kind, L, N, H, wait):
 # Groups on one XCD each (of 8 rows, or of 16 where there would be too many) against groups whose workgroups may be anywhere
 # (wait 3; of 16 or 32 rows): the same results bit for bit.  Odd numbers of blocks, a last group with one row, more groups than
 # XCDs, the widest with every compute unit taken.
-@pytest.mark.parametrize("kind,L,N,H", [("rnn", 9, 1, 8), ("rnn", 7, 9, 96), ("rnn", 5, 1030, 32), ("token", 6, 96, 672), ("token", 9, 33, 520),
-                                        ("gated", 5, 65, 512), ("gated", 6, 17, 40), ("lstm", 5, 64, 1024), ("lstm", 8, 25, 264),
-                                        ("gru", 5, 96, 672), ("gru", 9, 31, 1000), ("gru", 6, 64, 1024)])
+@pytest.mark.parametrize("kind,L,N,H", [("rnn", 13, 1, 8), ("rnn", 12, 9, 96), ("rnn", 12, 1030, 32), ("token", 12, 96, 672), ("token", 15, 33, 520),
+                                        ("gated", 12, 65, 512), ("gated", 13, 17, 40), ("lstm", 12, 64, 1024), ("lstm", 14, 25, 264),
+                                        ("gru", 12, 96, 672), ("gru", 15, 31, 1000), ("gru", 12, 64, 1024)])
 def test_chains_on_one_xcd_and_anywhere(B, kind, L, N, H):
     import ctypes as C
     import torch
