@@ -46,7 +46,7 @@
 //   accumulator the MFMAs are issued with the operands exchanged (B fragment
 //               first), which leaves a lane with one output row and groups of
 //               four consecutive output columns.
-//   lean        every tile inside the matrix, K a multiple of 32 per split, the hot
+//   lean        every tile inside the matrix, K a multiple of 32, the hot
 //               epilogues.  Straight-line: its epilogues issue a
 //               known number of memory operations, so the copies stay counted
 //               across them.  bf16 tiles leave through 4 KB of wave-private LDS
@@ -137,11 +137,11 @@ inline FastDiv fast_div(unsigned d) {
   while ((1ull << s) < d) ++s;
   return {(unsigned)((1ull << (31 + s)) / d + 1), 31 + s};
 }
-// the tile walk of a launch: every tile's share of the contraction is KT slices
+// the tile walk of a launch: a tile's share of the contraction is KT slices, one more in the first `longer` of the shares
 struct Walk {
   FastDiv by_mn, by_grp, by_split;
   unsigned tiles_mn, grp_tiles;      // tiles per matrix, and per block of GROUP_M tile rows
-  int tiles_m, split, KT, total, per_xcd;
+  int tiles_m, split, KT, longer, total, per_xcd;
 };
 inline Walk make_walk(const GemmArgs& g) {
   Walk w;
@@ -153,16 +153,17 @@ inline Walk make_walk(const GemmArgs& g) {
   w.by_mn = fast_div(w.tiles_mn);
   w.by_grp = fast_div(w.grp_tiles);
   w.by_split = fast_div((unsigned)g.split_k);
-  w.KT = (int)(g.K / g.split_k / BK);
+  w.KT = (int)(g.K / BK / g.split_k);
+  w.longer = (int)(g.K / BK % g.split_k);
   w.total = (int)((long)w.tiles_mn * g.batch * g.split_k);
   w.per_xcd = (w.total + 7) / 8;
   return w;
 }
 
-// coordinates of one output tile and the start of its share of the contraction
+// coordinates of one output tile, its share of the contraction: the start and the number of slices
 struct TileCoord {
   long batch, m0, n0, k_begin;
-  int split;
+  int split, kt;
 };
 
 __device__ __forceinline__ TileCoord decode_tile(const Walk& w, int t) {
@@ -179,7 +180,8 @@ __device__ __forceinline__ TileCoord decode_tile(const Walk& w, int t) {
   const unsigned batch = w.by_split(zb);
   c.batch = batch;
   c.split = (int)(zb - batch * (unsigned)w.split);
-  c.k_begin = (long)c.split * w.KT * BK;
+  c.kt = w.KT + (c.split < w.longer);
+  c.k_begin = ((long)c.split * w.KT + (c.split < w.longer ? c.split : w.longer)) * BK;
   return c;
 }
 
@@ -402,8 +404,11 @@ __global__ __launch_bounds__(NTHR, 1) void gemm_mfma_lean_kernel(GemmArgs g, Wal
   const int t_stride = ONE_AT_A_TIME ? (int)gridDim.x : wpx;
   int t = (ONE_AT_A_TIME ? xcd * wpx : xcd * walk.per_xcd) + (int)(blockIdx.x >> 3);
   const int t_end = !ONE_AT_A_TIME && (xcd + 1) * walk.per_xcd < walk.total ? (xcd + 1) * walk.per_xcd : walk.total;
-  const int KT = walk.KT;
   if (t >= t_end) return;
+  // Shares of unequal length are met by the parameter gradients alone (the only split launches); elsewhere a launch's one
+  // length stays in a scalar register.
+  constexpr bool SHARES = !A_KC;
+  auto slices_of = [&](const TileCoord& c) { return SHARES ? c.kt : walk.KT; };
 
   const long lda = A_KC ? g.a_sm : g.a_sk;
   const long ldb = B_KC ? g.b_sn : g.b_sk;
@@ -429,7 +434,7 @@ __global__ __launch_bounds__(NTHR, 1) void gemm_mfma_lean_kernel(GemmArgs g, Wal
                                                 (A_KC ? c.m0 * lda + c.k_begin : c.m0 + c.k_begin * lda));
     qb = reinterpret_cast<const unsigned char*>(reinterpret_cast<const bf16_t*>(g.B) + c.batch * g.b_sb +
                                                 (B_KC ? c.n0 * ldb + c.k_begin : c.n0 + c.k_begin * ldb));
-    p_left = KT;
+    p_left = slices_of(c);
   };
   auto copy_slice = [&]() {
     if (PAIR) {
@@ -582,6 +587,7 @@ __global__ __launch_bounds__(NTHR, 1) void gemm_mfma_lean_kernel(GemmArgs g, Wal
   constexpr std::integral_constant<int, EARLY ? 1 : 0> a1{};
   constexpr std::integral_constant<int, EARLY ? 2 : 0> a2{};
   while (true) {
+    const int KT = slices_of(cc);
     if (!EARLY) {
       step(yes, no, a0, !PAIR && KT == 1);
       if (PAIR) step(no, yes, a0, KT == 2);
@@ -753,7 +759,7 @@ bool launch_gemm_mfma(const GemmArgs& g, hipStream_t s, hipError_t* err) {
   const bool act = g.mode == EPI_ACT_GELU || g.mode == EPI_ACT_TANH;
   if (!(a_kc && (b_kc || (b_rc && !act))) && !(a_rc && b_rc && !act)) return false;
   // (a fused operand is asked for two slices before a tile's end, the first two being waited for otherwise: four at least)
-  if (has_lean(g, a_kc, b_kc) && g.K % ((long)g.split_k * BK) == 0 && (g.mode == EPI_STORE || g.K >= 4 * BK)) {
+  if (has_lean(g, a_kc, b_kc) && g.K % BK == 0 && g.K / BK >= g.split_k && (g.mode == EPI_STORE || g.K >= 4 * BK)) {
     const long hm = g.M / BM * BM, hn = g.N / BN * BN;
     const long tiles = (hm / BM) * (hn / BN) * g.batch * g.split_k;
     if (hm == g.M && hn == g.N) {

@@ -37,23 +37,33 @@ struct Workspace {
   size_t off_v, off_da, off_part, off_scan, off_wt, off_pre, off_m, off_tmp, off_dqkv, off_dsum, off_counter, total;
 };
 
-// split-K factor for a parameter-gradient GEMM with `tiles` output tiles and a
-// contraction of length K: enough workgroups to fill the 256 CUs, at least 2048
-// rows of the contraction each.  Few tiles (up to 32): once, which halves the
-// partial sums to write and add up.  More: twice, so that each XCD (an eighth of
-// the workgroups, sharing one L2) works on whole shares of the contraction, whose
-// tiles share operand panels (measured: 64 tiles at 4 shares are 25 % slower than
-// at 8).
-int pick_split(long tiles, long K) {
-  long want = ((tiles <= 32 ? 256 : 512) + tiles - 1) / tiles;
+// Shares of the contraction (length K, at least 2048 rows each) for a parameter gradient of `tiles` output tiles of 256 x 256.
+// bf16: each compute unit takes one tile's share at a time, and the last round of 256 costs as much as a full one: the number of
+// shares with the least estimated time, from what was seen: 0.93 us per slice of 32 in every compute unit (1.15 PFLOP/s), 13 us
+// to store a round's tiles, 0.05 us per partial tile in the sum and 5 us for its launch.  Shares differ by a slice at most, so
+// any number will do.  All parameter gradients of a stack, us, with 512 / tiles shares (or the next number below that divides the
+// slices) and with these: 12 transformer layers of width 256 on 32768 tokens (shares of W1, Wqkv, Wo: 8, 8, 16; now 5, 7, 16) 1729
+// / 1507, 3 of width 1024 on 16384 (2, 2, 8; 4, 7, 5) 2397 / 2258, 4 of width 768 on 8192 1041 / 951, the GRU's 1024 steps of 32
+// x 1024 663 / 620, the LSTM's 512 steps 394 / 373.
+int pick_split(const hbp_desc* d, long tiles, long K) {
   long cap = K / 2048;
   if (cap < 1) cap = 1;
+  if (cap > 64) cap = 64;
+  if (d->dtype == HBP_BF16 && K % 32 == 0) {
+    long best = 1;
+    double least = 0;
+    for (long s = 1; s <= cap; ++s) {
+      const double slices = (double)((K / 32 + s - 1) / s);
+      const double cost = (double)((tiles * s + 255) / 256) * (0.93 * slices + 13.0) + (s > 1 ? 5.0 + 0.05 * (double)(tiles * s) : 0.0);
+      if (s == 1 || cost < least) { least = cost; best = s; }
+    }
+    return (int)best;
+  }
+  // other kernels, smaller tiles: twice the compute units in tiles of 256 x 256 (few tiles: once, which halves the partial sums)
+  long want = ((tiles <= 32 ? 256 : 512) + tiles - 1) / tiles;
   if (want > cap) want = cap;
-  if (want > 64) want = 64;
   if (want < 1) want = 1;
-  // the aligned kernel needs every share of the contraction to be a whole number of 32-row slices:
-  // take the largest such factor below the wanted one when there is one
-  if (K % 32 == 0)
+  if (K % 32 == 0)      // shares of whole slices of 32 where there is such a number
     for (long s = want; s >= 1; --s)
       if ((K / 32) % s == 0) return (int)s;
   return (int)want;
@@ -61,22 +71,24 @@ int pick_split(long tiles, long K) {
 
 long tiles_of(long M, long N) { return ((M + 255) / 256) * ((N + 255) / 256); }
 
-struct Splits { int s_w2, s_w1, s_u, s_qkv, s_o; };
+struct Splits { int s_w2, s_w1, s_u, s_qkv, s_o, s_cand; };
 
 Splits param_splits(const hbp_desc* d) {
-  Splits s{1, 1, 1, 1, 1};
+  Splits s{1, 1, 1, 1, 1, 1};
   if (tfm(d)) {
     const long nb = d->L / 2;
-    s.s_w2 = s.s_w1 = pick_split(tiles_of(d->d, d->d_ff) * nb, d->N);
-    s.s_qkv = pick_split(tiles_of(3 * d->d, d->d) * nb, d->N);
-    s.s_o = pick_split(tiles_of(d->d, d->d) * nb, d->N);
+    s.s_w2 = s.s_w1 = pick_split(d, tiles_of(d->d, d->d_ff) * nb, d->N);
+    s.s_qkv = pick_split(d, tiles_of(3 * d->d, d->d) * nb, d->N);
+    s.s_o = pick_split(d, tiles_of(d->d, d->d) * nb, d->N);
     return s;
   }
   const long nb = shared_w(d) ? 1 : d->L;
   const long K = shared_w(d) ? d->L * d->N : d->N;
-  s.s_w2 = pick_split(tiles_of(d->d, d->d_ff) * nb, K);
-  s.s_w1 = s.s_w2;
-  if (recurrent(d)) s.s_u = pick_split(tiles_of(d->d_ff, d->d_in), K);
+  if (!cell(d)) s.s_w2 = pick_split(d, tiles_of(d->d, d->d_ff) * nb, K);
+  // (the standard GRU: the two gates' rows and the candidate's are products of their own)
+  s.s_w1 = pick_split(d, tiles_of(gru(d) ? 2 * d->d : d->d_ff, hidden_w(d)) * nb, K);
+  if (gru(d)) s.s_cand = pick_split(d, tiles_of(d->d, d->d), K);
+  if (recurrent(d)) s.s_u = pick_split(d, tiles_of(d->d_ff, d->d_in), K);
   return s;
 }
 
@@ -91,15 +103,13 @@ Workspace carve(const hbp_desc* d) {
   Splits sp = param_splits(d);
   const size_t nb = shared_w(d) ? 1 : tfm(d) ? (size_t)d->L / 2 : (size_t)d->L;
   size_t part = 0;
-  if (sp.s_w2 > 1) part = (size_t)sp.s_w2 * nb * d->d * d->d_ff * 4;
-  if (tfm(d)) {
-    if (sp.s_qkv > 1 && (size_t)sp.s_qkv * nb * 3 * d->d * d->d * 4 > part) part = (size_t)sp.s_qkv * nb * 3 * d->d * d->d * 4;
-    if (sp.s_o > 1 && (size_t)sp.s_o * nb * d->d * d->d * 4 > part) part = (size_t)sp.s_o * nb * d->d * d->d * 4;
-  }
-  if (sp.s_u > 1) {
-    size_t pu = (size_t)sp.s_u * d->d_ff * d->d_in * 4;
-    if (pu > part) part = pu;
-  }
+  auto partials = [&part](int split, size_t n) { if (split > 1 && (size_t)split * n * 4 > part) part = (size_t)split * n * 4; };
+  partials(sp.s_w2, nb * d->d * d->d_ff);
+  partials(sp.s_w1, nb * hidden_w(d) * (gru(d) ? 2 * d->d : d->d_ff));
+  partials(sp.s_cand, (size_t)d->d * d->d);
+  partials(sp.s_qkv, nb * 3 * d->d * d->d);
+  partials(sp.s_o, nb * d->d * d->d);
+  partials(sp.s_u, (size_t)d->d_ff * d->d_in);
   w.off_part = o; o = align_up(o + part, 256);
   w.off_scan = o; o = align_up(o + scan_chunk_ws_bytes(d->L, d->N, d->d, d->norm == HBP_NORM_RMS), 256);
   // transposed copies of the shared weights for step-by-step backpropagation through time
@@ -1168,7 +1178,7 @@ hbp_status hbp_param_grads(const hbp_desc* d, hbp_buffers* b, void* stream) {
     const long H = d->d;
     HBP_RUN(tn_gemm(d, da, d->d_ff, 0, bb.y, H, 0, bb.dW1, 2 * H, H, K, 1, sp.s_w1, part, s));
     HBP_RUN(tn_gemm(d, at(da, (size_t)2 * H * es), d->d_ff, 0, at((const void*)b->workspace, w.off_v), H, 0,
-                    bb.dW1 + 2 * H * H, H, H, K, 1, sp.s_w1, part, s));
+                    bb.dW1 + 2 * H * H, H, H, K, 1, sp.s_cand, part, s));
   } else
   HBP_RUN(tn_gemm(d, da, d->d_ff, d->N * d->d_ff, at((const void*)bb.y, (size_t)hidden_off(d) * es), d->d,
                   d->N * d->d, bb.dW1, d->d_ff, hidden_w(d), K, nb, sp.s_w1, part, s));

@@ -249,6 +249,15 @@ def test_several_tiles_per_workgroup(B, N, d, d_ff, act):
     H.assert_close(H.to_np(p.g)[0], O.exact_backward(st, sv, inp["e"])[0], H.TOL["bf16"], f"{w.name} g[0]")
 
 
+# parameter gradients whose contraction is shared out unequally (193 slices of 32 in 3 shares, 258 in 4, 321 in 5),
+# and the sum of 3, 4 and 5 shares
+@pytest.mark.parametrize("L,N,d,d_ff", [(2, 6176, 256, 256), (2, 8256, 256, 512), (1, 10272, 512, 256)])
+def test_unequal_shares_of_a_contraction(B, L, N, d, d_ff):
+    w = synth.scaled(W["resnet_like"], name=f"mlp_{N}_{d}_{d_ff}", L=L, N=N, d=d, d_ff=d_ff, w2_scale=0.7, ks=(1,))
+    inp, st, sv, p = _forward_matches(B, w)
+    _check_backward(B, w, p, st, sv, inp, w.name)
+
+
 # the norm's kernels: rows held by 16, 32 or 64 lanes and one to eight vectors per lane, the last partly past the width, and
 # a row count that leaves part of a wavefront without rows; in front of the block (y, rinv) and after the sum, in place
 @pytest.mark.parametrize("post", ["none", "rms"])
