@@ -140,6 +140,23 @@ __global__ void splitk_reduce_kernel(const float* __restrict__ part, float* __re
     out[i] = s;
   }
 }
+// The same, four elements at a time and four shares' loads in flight (n a multiple of 4, everything 16-byte aligned): bound by
+// memory.  Sums of 2 or 4 shares of 50 MB at 4.4 TB/s with the loop above, at 5.4 with this; 16 shares of 4 MB 15.4 -> 11.4 us.
+__global__ __launch_bounds__(256) void splitk_reduce4_kernel(const float4* __restrict__ part, float4* __restrict__ out, long n4,
+                                                             int split) {
+  const long i = (long)blockIdx.x * 256 + threadIdx.x;
+  if (i >= n4) return;
+  const float4* p = part + i;
+  float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+  auto add = [&s](const float4& t) { s.x += t.x; s.y += t.y; s.z += t.z; s.w += t.w; };
+  int q = 0;
+  for (; q + 4 <= split; q += 4, p += 4 * n4) {
+    const float4 t0 = p[0], t1 = p[n4], t2 = p[2 * n4], t3 = p[3 * n4];
+    add(t0); add(t1); add(t2); add(t3);
+  }
+  for (; q < split; ++q, p += n4) add(*p);
+  out[i] = s;
+}
 
 }  // namespace
 
@@ -153,6 +170,12 @@ hipError_t launch_gemm_generic(int dtype, const GemmArgs& g, hipStream_t s) {
 }
 
 hipError_t launch_splitk_reduce(const float* part, float* out, long n, int split, hipStream_t s) {
+  if (n % 4 == 0 && (reinterpret_cast<uintptr_t>(part) & 15) == 0 && (reinterpret_cast<uintptr_t>(out) & 15) == 0 &&
+      n / 1024 < (1L << 30)) {
+    hipLaunchKernelGGL(splitk_reduce4_kernel, dim3((unsigned)((n / 4 + 255) / 256)), dim3(256), 0, s,
+                       reinterpret_cast<const float4*>(part), reinterpret_cast<float4*>(out), n / 4, split);
+    return hipGetLastError();
+  }
   long blocks = (n + 255) / 256;
   if (blocks > 4096) blocks = 4096;
   hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)blocks), dim3(256), 0, s, part, out, n, split);
