@@ -3,6 +3,7 @@
 #pragma once
 #include "gelu.h"
 #include "hbp_common.h"
+#include <atomic>
 
 namespace hbp {
 namespace {
@@ -45,6 +46,21 @@ __device__ __forceinline__ void wait_vm() {
 // GELU and its derivative, on v_exp_f32 and v_rcp_f32
 __device__ __forceinline__ void gelu_both(float a, float& z, float& dz) {
   gelu_pair(a, z, dz, [](float x) { return __builtin_amdgcn_exp2f(x); }, [](float x) { return __builtin_amdgcn_rcpf(x); });
+}
+
+// Raises a kernel's dynamic shared-memory limit once per device (one flag array per kernel instantiation; setting
+// the attribute twice from two threads is harmless, so a relaxed flag is enough).
+constexpr int MAX_DEVICES = 64;
+inline hipError_t raise_lds_limit(const void* kern, int bytes, std::atomic<bool> (&done)[MAX_DEVICES]) {
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  if (dev < 0 || dev >= MAX_DEVICES) return hipErrorInvalidDevice;
+  if (done[dev].load(std::memory_order_acquire)) return hipSuccess;
+  e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  if (e != hipSuccess) return e;
+  done[dev].store(true, std::memory_order_release);
+  return hipSuccess;
 }
 
 }  // namespace

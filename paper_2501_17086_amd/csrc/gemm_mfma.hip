@@ -61,7 +61,6 @@
 //               list walks 8 x 8 blocks of tiles, so the tiles an XCD works on
 //               at one time share operand panels.
 #include "gemm_device.h"
-#include <atomic>
 #include <type_traits>
 
 namespace hbp {
@@ -623,21 +622,6 @@ __global__ __launch_bounds__(NTHR, 1) void gemm_mfma_lean_kernel(GemmArgs g, Wal
   if (grp == 0) __builtin_amdgcn_s_barrier();   // matches group 1's last barrier
 }
 
-// Raises a kernel's dynamic shared-memory limit once per device (one flag array per kernel instantiation; setting
-// the attribute twice from two threads is harmless, so a relaxed flag is enough).
-constexpr int MAX_DEVICES = 64;
-inline hipError_t raise_lds_limit(const void* kern, int bytes, std::atomic<bool> (&done)[MAX_DEVICES]) {
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e != hipSuccess) return e;
-  if (dev < 0 || dev >= MAX_DEVICES) return hipErrorInvalidDevice;
-  if (done[dev].load(std::memory_order_acquire)) return hipSuccess;
-  e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-  if (e != hipSuccess) return e;
-  done[dev].store(true, std::memory_order_release);
-  return hipSuccess;
-}
-
 template <bool A_KC, bool B_KC, int FAST, bool ONE_AT_A_TIME, bool PAIR>
 hipError_t launch_lean_walk(const GemmArgs& g, hipStream_t s) {
   static std::atomic<bool> attr_set[MAX_DEVICES];
@@ -680,9 +664,15 @@ constexpr long SPLIT_FROM = 512;
 // 128 x 128 tiles once they give most compute units one, else 64 x 64.  Measured, 128 / 64: 24 tiles of 128 (1000 x 328 x
 // 1304) 18.9 / 10.1 us, 128 tiles (2048 x 1024 x 4096) 42.3 / 28.0, 192 tiles (4096 x 768 x 3072) 36.4 / 37.2, 288 tiles
 // (1000 x 328 x 1304, batch 12) 27.1 / 33.4, 768 tiles (3000 x 1000 x 4000, batch 4) 122 / 222.
+// The smallest launches: the smaller tiles, whose wavefronts share the contraction, as long as every compute unit has at most
+// one.  Measured, 64 x 64 / 64 x 32 / 32 x 32: 1000 x 328 x 1304 (176 tiles of 64 x 32, 352 of 32 x 32) 10.2 / 8.2 / 10.6 us,
+// 512 x 768 x 3072 (192, 384) 15.9 / 11.9 / 16.0, 1024 x 256 x 1200 (128, 256) 8.3 / 7.9 / 6.6, 100 x 512 x 2048 (32, 64)
+// 12.5 / 7.6 / 6.3; beyond: 600 x 1000 x 4000 (320, 608) 21.9 / 26.8 / 25.7, 1200 x 768 x 256 (456, 912) 4.7 / 6.8 / 10.1.
 inline hipError_t launch_tile_for(const GemmArgs& g, hipStream_t s) {
-  const long tiles = (g.M + 127) / 128 * ((g.N + 127) / 128) * g.batch * g.split_k;
-  return launch_gemm_tile(g, tiles >= 192 ? 128 : 64, s);
+  auto tiles = [&g](long tm, long tn) { return (g.M + tm - 1) / tm * ((g.N + tn - 1) / tn) * g.batch * g.split_k; };
+  if (tiles(128, 128) >= 192) return launch_gemm_tile(g, 128, 128, s);
+  if (tiles(32, 32) <= 256) return launch_gemm_tile(g, 32, 32, s);
+  return tiles(64, 32) <= 256 ? launch_gemm_tile(g, 64, 32, s) : launch_gemm_tile(g, 64, 64, s);
 }
 
 // does the lean kernel have this pairing's epilogue?

@@ -3,6 +3,7 @@
 //
 //   workgroup   256 threads (2 x 2 wavefronts), one output tile of 128 x 128 or 64 x 64; two workgroups share a
 //               compute unit (64 KB of LDS each), so that one's epilogue and fill run under the other's products.
+//               (Launches that leave compute units without a tile: gemm_small_kernel below, 64 x 32 or 32 x 32.)
 //   K pipeline  slices of 32 (128-wide tile) or 64 (64-wide) of both operands go global -> LDS directly through a ring
 //               of four 16 KB stages, three slices ahead; one counted wait and one barrier per slice.
 //   edges       a lane's source row (or its chunk of 8 rows) is clamped to the matrix once per tile, so the main loop is
@@ -20,19 +21,19 @@ namespace {
 
 constexpr int NST = 4, NTHR = 256;
 
-// One operand tile of T rows x BK of the contraction in LDS.
-template <int T, int BK, bool KC>
+// One operand tile of T rows x BK of the contraction in LDS, copied by NW wavefronts.
+template <int T, int BK, bool KC, int NW = 4>
 struct Tile {
   static constexpr int BYTES = T * BK * 2;
-  static constexpr int COPIES = BYTES / 1024 / 4;                // per wavefront and slice, 1 KB each
+  static constexpr int COPIES = BYTES / 1024 / NW;               // per wavefront and slice, 1 KB each
   static constexpr int CPR = KC ? BK / 8 : T / 8;                // 16-byte chunks per LDS row
   // the XOR on the chunk index of LDS row r (KC: a matrix row; RC: a contraction index)
   static __device__ __forceinline__ int swz(int r) {
     if (KC) return BK == 32 ? (r >> 2) & 3 : (r >> 1) & 7;
-    return T == 128 ? 4 * (r & 3) : 4 * ((r >> 1) & 1);
+    return T == 128 ? 4 * (r & 3) : T == 64 ? 4 * ((r >> 1) & 1) : 0;   // (32: four rows are the 64 banks)
   }
   // LDS row and logical chunk of this lane's 16 bytes of copy i
-  static __device__ __forceinline__ int lane_row(int i, int wave, int lane) { return (wave + 4 * i) * (64 / CPR) + lane / CPR; }
+  static __device__ __forceinline__ int lane_row(int i, int wave, int lane) { return (wave + NW * i) * (64 / CPR) + lane / CPR; }
   static __device__ __forceinline__ int lane_chunk(int i, int wave, int lane) {
     return (lane % CPR) ^ swz(lane_row(i, wave, lane));
   }
@@ -63,6 +64,56 @@ struct Tile {
     return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
   }
 };
+
+__device__ __forceinline__ bool fuses_aux(const GemmArgs& g) {
+  return g.split_k == 1 && (g.mode == EPI_MUL_AUX || g.mode == EPI_MUL_1MZ2 || g.mode == EPI_RESID || g.mode == EPI_ADD_AUX);
+}
+// 8 consecutive sums of a row, at element off of C: what the launch fuses, and the store.  ra: the fused operand there; lm: the
+// columns' coefficients (EPI_RESID without coefficients per element).
+template <bool ACT>
+__device__ __forceinline__ void finish8(const GemmArgs& g, long batch, int split, long off, bool use_aux, float (&v)[8],
+                                        const Raw8<bf16_t>& ra, const float (&lm)[8]) {
+  if (g.split_k > 1) {
+    store8(reinterpret_cast<float*>(g.C) + ((long)split * g.batch + batch) * g.c_sb + off, v);
+    return;
+  }
+  if (g.addf) {
+    float f[8];
+    load8(g.addf + batch * g.addf_sb + off, f);
+#pragma unroll
+    for (int x = 0; x < 8; ++x) v[x] += f[x];
+  }
+  if (ACT) {
+    if (g.mode == EPI_ACT_GELU) {
+      float dz[8];
+#pragma unroll
+      for (int x = 0; x < 8; ++x) gelu_both(v[x], v[x], dz[x]);
+      store8(reinterpret_cast<bf16_t*>(g.out2) + batch * g.out2_sb + off, dz);
+    } else {
+#pragma unroll
+      for (int x = 0; x < 8; ++x) v[x] = tanhf(v[x]);
+    }
+  } else if (use_aux) {
+    float f[8];
+    ra.unpack(f);
+    if (g.mode == EPI_MUL_AUX) {
+#pragma unroll
+      for (int x = 0; x < 8; ++x) v[x] *= f[x];
+    } else if (g.mode == EPI_MUL_1MZ2) {
+#pragma unroll
+      for (int x = 0; x < 8; ++x) v[x] *= (1.f - f[x] * f[x]);
+    } else if (g.mode == EPI_ADD_AUX) {
+#pragma unroll
+      for (int x = 0; x < 8; ++x) v[x] += f[x];
+    } else {
+      float l8[8];
+      if (g.lambda_mn) load8(reinterpret_cast<const bf16_t*>(g.lambda_mn) + batch * g.aux_sb + off, l8);
+#pragma unroll
+      for (int x = 0; x < 8; ++x) v[x] = fmaf(g.lambda_mn ? l8[x] : lm[x], f[x], v[x]);
+    }
+  }
+  if (g.c_is_f32) store8(reinterpret_cast<float*>(g.C) + batch * g.c_sb + off, v);
+  else store8(reinterpret_cast<bf16_t*>(g.C) + batch * g.c_sb + off, v);}
 
 // T x T output tile per workgroup.  ACT: the forward's activations (kept out of the other kernels' registers).
 template <int T, int BK, bool A_KC, bool B_KC, bool ACT>
@@ -173,18 +224,15 @@ __global__ __launch_bounds__(NTHR, 2) void gemm_tile_kernel(GemmArgs g, int tile
   static_assert(4 * 32 * LD * 4 <= NST * STAGE, "the staging area reuses the ring");
   __syncthreads();                                         // the last slice has been read by everyone
   float* stg = reinterpret_cast<float*>(smem) + wave * 32 * LD;
-  const long off_b = batch * g.c_sb;
   const bf16_t* aux = g.aux ? reinterpret_cast<const bf16_t*>(g.aux) + batch * g.aux_sb : nullptr;
-  const bf16_t* lmn = g.lambda_mn ? reinterpret_cast<const bf16_t*>(g.lambda_mn) + batch * g.aux_sb : nullptr;
   const float* lam = g.lambda ? g.lambda + batch * g.lambda_sb : nullptr;
-  const bool use_aux = g.split_k == 1 && (g.mode == EPI_MUL_AUX || g.mode == EPI_MUL_1MZ2 || g.mode == EPI_RESID ||
-                                          g.mode == EPI_ADD_AUX);
+  const bool use_aux = fuses_aux(g);
   const long col = n0 + wn0 + 8 * (lane % LPR);
   const long col_in = col < g.N ? col : g.N - 8;           // (loads are clamped, stores guarded)
   float lm[8];
 #pragma unroll
   for (int x = 0; x < 8; ++x) lm[x] = 1.f;
-  if (!ACT && use_aux && lam && !lmn) load8(lam + col_in, lm);
+  if (!ACT && use_aux && lam && !g.lambda_mn) load8(lam + col_in, lm);
 #pragma unroll
   for (int i = 0; i < NB; ++i) {
     const long row0 = m0 + wm0 + 32 * i + lane / LPR;
@@ -209,51 +257,149 @@ __global__ __launch_bounds__(NTHR, 2) void gemm_tile_kernel(GemmArgs g, int tile
       float v[8];
       load8(stg + (lane / LPR + ps * RPP) * LD + 8 * (lane % LPR), v);
       if (row >= g.M || col >= g.N) continue;
-      const long off = row * g.ldc + col;
-      if (g.split_k > 1) {
-        store8(reinterpret_cast<float*>(g.C) + ((long)split * g.batch + batch) * g.c_sb + off, v);
-        continue;
-      }
-      if (g.addf) {
-        float f[8];
-        load8(g.addf + batch * g.addf_sb + off, f);
-#pragma unroll
-        for (int x = 0; x < 8; ++x) v[x] += f[x];
-      }
-      if (ACT) {
-        if (g.mode == EPI_ACT_GELU) {
-          float dz[8];
-#pragma unroll
-          for (int x = 0; x < 8; ++x) gelu_both(v[x], v[x], dz[x]);
-          store8(reinterpret_cast<bf16_t*>(g.out2) + batch * g.out2_sb + off, dz);
-        } else {
-#pragma unroll
-          for (int x = 0; x < 8; ++x) v[x] = tanhf(v[x]);
-        }
-      } else if (use_aux) {
-        float f[8];
-        ra[ps].unpack(f);
-        if (g.mode == EPI_MUL_AUX) {
-#pragma unroll
-          for (int x = 0; x < 8; ++x) v[x] *= f[x];
-        } else if (g.mode == EPI_MUL_1MZ2) {
-#pragma unroll
-          for (int x = 0; x < 8; ++x) v[x] *= (1.f - f[x] * f[x]);
-        } else if (g.mode == EPI_ADD_AUX) {
-#pragma unroll
-          for (int x = 0; x < 8; ++x) v[x] += f[x];
-        } else {
-          float l8[8];
-          if (lmn) load8(lmn + off, l8);
-#pragma unroll
-          for (int x = 0; x < 8; ++x) v[x] = fmaf(lmn ? l8[x] : lm[x], f[x], v[x]);
-        }
-      }
-      if (g.c_is_f32) store8(reinterpret_cast<float*>(g.C) + off_b + off, v);
-      else store8(reinterpret_cast<bf16_t*>(g.C) + off_b + off, v);
+      finish8<ACT>(g, batch, split, row * g.ldc + col, use_aux, v, ra[ps], lm);
     }
     __builtin_amdgcn_wave_barrier();                       // the next rows' writes stay behind these reads
   }
+}
+
+// Launches of few tiles: a workgroup of four wavefronts owns TM x 32 of C and the wavefronts share the contraction out, each
+// taking every fourth slice of 64 through an LDS ring of its own (no barrier in the loop); the four sums meet in LDS.
+// What bounds such a launch is the time a compute unit takes to stream its tile's operands from L2, about 64 KB of requests in
+// flight over their latency.  Here 96 KB are asked for ahead (the 64 x 64 kernel: 48), over more compute units.  The fused operand
+// is asked for before the first slice.  MEASURED_SMALL
+template <int TM, int STG, bool A_KC, bool B_KC, bool ACT>
+__global__ __launch_bounds__(NTHR, 1) void gemm_small_kernel(GemmArgs g, int tiles_m, int tiles_n, int total, int per_xcd) {
+  constexpr int TN = 32, BK = 64, NB = TM / 32;
+  typedef Tile<TM, BK, A_KC, 1> TA;
+  typedef Tile<TN, BK, B_KC, 1> TB;
+  constexpr int STAGE = TA::BYTES + TB::BYTES;
+  constexpr int PER = TA::COPIES + TB::COPIES;
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem_dyn[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  unsigned char* const ring = smem_dyn + wave * (STG * STAGE);
+  const unsigned lds0 = (unsigned)__builtin_amdgcn_readfirstlane(
+      (int)(unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)ring);
+
+  const int t = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);    // (dealt as above)
+  if (t >= total) return;
+  const unsigned tiles_mn = (unsigned)tiles_m * tiles_n;
+  const unsigned zb = (unsigned)t / tiles_mn, rem = (unsigned)t - zb * tiles_mn;
+  const unsigned gr = rem / (8u * tiles_n), in_gr = rem - gr * 8u * tiles_n;
+  const unsigned left = tiles_m - gr * 8u, gm = left < 8u ? left : 8u;
+  const long m0 = (long)(gr * 8u + in_gr % gm) * TM, n0 = (long)(in_gr / gm) * TN;
+  const long batch = zb / (unsigned)g.split_k;
+  const int split = (int)(zb % (unsigned)g.split_k);
+  const long kchunk = ((g.K + g.split_k - 1) / g.split_k + 31) / 32 * 32;
+  const long k_begin = (long)split * kchunk;
+  const long k_end = k_begin + kchunk < g.K ? k_begin + kchunk : g.K;
+  const int KT = k_end > k_begin ? (int)((k_end - k_begin + BK - 1) / BK) : 0;
+  const int mine = KT > wave ? (KT - wave + 3) / 4 : 0;                      // slices wave, wave + 4, ..
+
+  // this thread's piece of the result, 8 columns of a row (TM 32: of the first 128 threads)
+  const int prow = tid >> 2, pcol = 8 * (tid & 3);
+  const bool writes = prow < TM && m0 + prow < g.M && n0 + pcol < g.N;
+  const bool use_aux = fuses_aux(g);
+  const long off = (m0 + prow) * g.ldc + n0 + pcol;
+  Raw8<bf16_t> ra;
+  ra.v = make_uint4(0, 0, 0, 0);
+  float lm[8];
+#pragma unroll
+  for (int x = 0; x < 8; ++x) lm[x] = 1.f;
+  if (!ACT && use_aux && writes) {
+    ra.load(reinterpret_cast<const bf16_t*>(g.aux) + batch * g.aux_sb + off);
+    if (g.lambda && !g.lambda_mn) load8(g.lambda + batch * g.lambda_sb + n0 + pcol, lm);
+  }
+
+  const long lda = A_KC ? g.a_sm : g.a_sk, ldb = B_KC ? g.b_sn : g.b_sk;
+  const long k_mine = k_begin + (long)wave * BK;
+  const bf16_t* pa = reinterpret_cast<const bf16_t*>(g.A) + batch * g.a_sb + (A_KC ? m0 * lda + k_mine : m0 + k_mine * lda);
+  const bf16_t* pb = reinterpret_cast<const bf16_t*>(g.B) + batch * g.b_sb + (B_KC ? n0 * ldb + k_mine : n0 + k_mine * ldb);
+  const long step_a = 4 * (A_KC ? BK : BK * lda), step_b = 4 * (B_KC ? BK : BK * ldb);
+  unsigned offa[TA::COPIES], offb[TB::COPIES];
+#pragma unroll
+  for (int i = 0; i < TA::COPIES; ++i) offa[i] = TA::source(lda, g.M - m0, i, 0, lane);
+#pragma unroll
+  for (int i = 0; i < TB::COPIES; ++i) offb[i] = TB::source(ldb, g.N - n0, i, 0, lane);
+  auto issue = [&](int s) __attribute__((always_inline)) {
+    const unsigned dst = lds0 + (unsigned)(s % STG) * STAGE;
+    const long k_left = k_end - k_mine - (long)s * (4 * BK);
+    if (k_left >= BK) {
+#pragma unroll
+      for (int i = 0; i < TA::COPIES; ++i) dma16_s(offa[i], pa, dst + 1024u * i);
+#pragma unroll
+      for (int i = 0; i < TB::COPIES; ++i) dma16_s(offb[i], pb, dst + TA::BYTES + 1024u * i);
+    } else {
+#pragma unroll
+      for (int i = 0; i < TA::COPIES; ++i)
+        dma16(TA::in_tail(k_left, i, 0, lane) ? reinterpret_cast<const void*>(reinterpret_cast<const char*>(pa) + offa[i])
+                                              : reinterpret_cast<const void*>(g_zero_chunks + lane), dst + 1024u * i);
+#pragma unroll
+      for (int i = 0; i < TB::COPIES; ++i)
+        dma16(TB::in_tail(k_left, i, 0, lane) ? reinterpret_cast<const void*>(reinterpret_cast<const char*>(pb) + offb[i])
+                                              : reinterpret_cast<const void*>(g_zero_chunks + lane),
+              dst + TA::BYTES + 1024u * i);
+    }
+    pa += step_a;
+    pb += step_b;
+  };
+
+  float16v acc[NB];
+#pragma unroll
+  for (int i = 0; i < NB; ++i)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
+#pragma unroll 1
+  for (int s = 0; s < STG - 1 && s < mine; ++s) issue(s);
+#pragma unroll 1
+  for (int s = 0; s < mine; ++s) {
+    // slice s has landed once only the copies of the slices after it are outstanding; and the reads of slice s - 1, whose
+    // stage the next copies go to, have returned
+    if (STG > 3 && s + 2 < mine) wait_vm_lds<2 * PER>();
+    else if (s + 1 < mine) wait_vm_lds<PER>();
+    else wait_vm_lds<0>();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    if (s + STG - 1 < mine) issue(s + STG - 1);
+    const unsigned char* st = ring + (s % STG) * STAGE;
+    bf16x8 fa[NB][4], fb[4];
+#pragma unroll
+    for (int h = 0; h < 4; ++h) {
+      fb[h] = TB::frag(st + TA::BYTES, 0, 16 * h, lane);
+#pragma unroll
+      for (int i = 0; i < NB; ++i) fa[i][h] = TA::frag(st, 32 * i, 16 * h, lane);
+    }
+#pragma unroll
+    for (int h = 0; h < 4; ++h)
+#pragma unroll
+      for (int i = 0; i < NB; ++i) acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[h], fa[i][h], acc[i], 0, 0, 0);
+  }
+
+  constexpr int LD = TN + 4;
+  static_assert(TM * LD * 4 <= STG * STAGE, "a wavefront's sums reuse its ring");
+  wait_vm_lds<0>();                                        // its last slice has been read
+  asm volatile("" ::: "memory");
+  float* own = reinterpret_cast<float*>(ring);
+#pragma unroll
+  for (int i = 0; i < NB; ++i)
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      *reinterpret_cast<float4*>(own + (32 * i + (lane & 31)) * LD + 8 * q + 4 * (lane >> 5)) =
+          make_float4(acc[i][4 * q], acc[i][4 * q + 1], acc[i][4 * q + 2], acc[i][4 * q + 3]);
+  __syncthreads();
+  if (!writes) return;
+  float v[8];
+  const float* sums = reinterpret_cast<const float*>(smem_dyn) + prow * LD + pcol;
+  load8(sums, v);
+#pragma unroll
+  for (int w = 1; w < 4; ++w) {
+    float f[8];
+    load8(sums + w * (STG * STAGE / 4), f);
+#pragma unroll
+    for (int x = 0; x < 8; ++x) v[x] += f[x];
+  }
+  finish8<ACT>(g, batch, split, off, use_aux, v, ra, lm);
 }
 
 template <int T, int BK, bool A_KC, bool B_KC, bool ACT>
@@ -275,10 +421,35 @@ hipError_t launch_pairing(const GemmArgs& g, hipStream_t s) {
   return a_kc ? launch_one<T, BK, true, false, false>(g, s) : launch_one<T, BK, false, false, false>(g, s);
 }
 
+template <int TM, int STG, bool A_KC, bool B_KC, bool ACT>
+hipError_t launch_small_one(const GemmArgs& g, hipStream_t s) {
+  static std::atomic<bool> attr_set[MAX_DEVICES];
+  auto kern = gemm_small_kernel<TM, STG, A_KC, B_KC, ACT>;
+  constexpr int lds = 4 * STG * (TM + 32) * 64 * 2;
+  const hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kern), lds, attr_set);
+  if (e != hipSuccess) return e;
+  const long tiles_m = (g.M + TM - 1) / TM, tiles_n = (g.N + 31) / 32;
+  const long total = tiles_m * tiles_n * g.batch * g.split_k;
+  if (total > (1L << 28)) return hipErrorInvalidValue;
+  const long per_xcd = (total + 7) / 8;
+  hipLaunchKernelGGL(kern, dim3((unsigned)(8 * per_xcd)), dim3(NTHR), lds, s, g, (int)tiles_m, (int)tiles_n, (int)total,
+                     (int)per_xcd);
+  return hipGetLastError();
+}
+template <int TM, int STG>
+hipError_t launch_small(const GemmArgs& g, hipStream_t s) {
+  const bool a_kc = g.a_sk == 1, b_kc = g.b_sk == 1;
+  if (a_kc && b_kc)
+    return g.mode == EPI_ACT_GELU || g.mode == EPI_ACT_TANH ? launch_small_one<TM, STG, true, true, true>(g, s)
+                                                            : launch_small_one<TM, STG, true, true, false>(g, s);
+  return a_kc ? launch_small_one<TM, STG, true, false, false>(g, s) : launch_small_one<TM, STG, false, false, false>(g, s);
+}
+
 }  // namespace
 
-hipError_t launch_gemm_tile(const GemmArgs& g, int tile, hipStream_t s) {
-  return tile == 128 ? launch_pairing<128, 32>(g, s) : launch_pairing<64, 64>(g, s);
+hipError_t launch_gemm_tile(const GemmArgs& g, int tm, int tn, hipStream_t s) {
+  if (tn == 32) return tm == 32 ? launch_small<32, 4>(g, s) : launch_small<64, 3>(g, s);
+  return tm == 128 ? launch_pairing<128, 32>(g, s) : launch_pairing<64, 64>(g, s);
 }
 
 }  // namespace hbp

@@ -155,8 +155,9 @@ bool gemm_f32_ok(const GemmArgs& g);
 hipError_t launch_gemm_f32(const GemmArgs& g, hipStream_t s);
 // fast bf16 MFMA path; returns false when the shape/layout is not covered
 bool launch_gemm_mfma(const GemmArgs& g, hipStream_t s, hipError_t* err);
-// the same contractions on tiles of 128 x 128 or 64 x 64, any size (called through launch_gemm_mfma, which checks the layout)
-hipError_t launch_gemm_tile(const GemmArgs& g, int tile, hipStream_t s);
+// the same contractions on tiles of 128 x 128, 64 x 64, 64 x 32 or 32 x 32, any size (called through launch_gemm_mfma, which
+// checks the layout)
+hipError_t launch_gemm_tile(const GemmArgs& g, int tm, int tn, hipStream_t s);
 
 // Multi-head self-attention on rows [q | k | v] (3 d wide, head h in columns h dh .. of each third), `seqs` sequences of
 // T consecutive rows each; o and dout are d wide.  lse and dsum hold one float per (sequence, head, position).

@@ -32,6 +32,18 @@ def test_products_around_the_tile_edges(B, N, d, d_ff):
     _check_backward(B, w, p, st, sv, inp, w.name)
 
 
+# few tiles, the wavefronts sharing the contraction: 64 x 32 tiles (257 to 512 blocks of 32 x 32) and 32 x 32 ones, contractions
+# of one to 17 slices of 64 (wavefronts with none, with one more than others, with a last slice that ends inside), tokens,
+# widths and inner widths that end inside a tile
+@pytest.mark.parametrize("N,d,d_ff", [(1000, 328, 1304), (520, 1032, 72), (250, 520, 1096), (33, 1096, 264), (640, 512, 200),
+                                      (96, 40, 1288)])
+def test_products_of_few_tiles(B, N, d, d_ff):
+    w = synth.scaled(W["resnet_like"], name=f"mlp_{N}_{d}_{d_ff}", L=2, N=N, d=d, d_ff=d_ff, w2_scale=0.7, ks=(1,))
+    inp, st, sv, p = _forward_matches(B, w)
+    H.assert_close(H.to_np(p.z), sv["z"], H.TOL["bf16"], f"{w.name} z")
+    _check_backward(B, w, p, st, sv, inp, w.name)
+
+
 # head widths around the 32, 64 and 128 columns that the matrix-core kernels pad to (136: the plain kernels), on sequence
 # lengths of one ragged tile, one workgroup, past the whole-problem kernels (128 / 256 positions) and past a block of tiles
 @pytest.mark.parametrize("causal", [True, False])
