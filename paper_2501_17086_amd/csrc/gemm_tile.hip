@@ -1,11 +1,12 @@
 // bf16 GEMM on the matrix cores for the shapes the 256 x 256 kernel does not serve well: sizes that are no multiple of
 // its tile, few output tiles, and every epilogue it does not have.
 //
-//   workgroup   256 threads (2 x 2 wavefronts), one output tile of 128 x 128 or 64 x 64; two workgroups share a
-//               compute unit (64 KB of LDS each), so that one's epilogue and fill run under the other's products.
+//   workgroup   256 threads (2 x 2 wavefronts), one output tile of 128 x 128 or 64 x 64; two or three workgroups share a
+//               compute unit (64 or 48 KB of LDS each), so that one's epilogue and fill run under the others' products.
 //               (Launches that leave compute units without a tile: gemm_small_kernel below, 64 x 32 or 32 x 32.)
-//   K pipeline  slices of 32 (128-wide tile) or 64 (64-wide) of both operands go global -> LDS directly through a ring
-//               of four 16 KB stages, three slices ahead; one counted wait and one barrier per slice.
+//   K pipeline  slices of 32 or 64 of both operands go global -> LDS directly through a ring of three or four stages of
+//               16 KB (128-wide tiles in slices of 64: 32 KB), two or three slices ahead; one counted wait and one barrier
+//               per slice.
 //   edges       a lane's source row (or its chunk of 8 rows) is clamped to the matrix once per tile, so the main loop is
 //               the same for every tile; what such lanes produce is never stored.  Only a last, partial slice of
 //               the contraction is special: its chunks past the end are copied from a zero-filled device array.
@@ -19,7 +20,7 @@ namespace hbp {
 
 namespace {
 
-constexpr int NST = 4, NTHR = 256;
+constexpr int NTHR = 256;
 
 // One operand tile of T rows x BK of the contraction in LDS, copied by NW wavefronts.
 template <int T, int BK, bool KC, int NW = 4>
@@ -113,17 +114,19 @@ __device__ __forceinline__ void finish8(const GemmArgs& g, long batch, int split
     }
   }
   if (g.c_is_f32) store8(reinterpret_cast<float*>(g.C) + batch * g.c_sb + off, v);
-  else store8(reinterpret_cast<bf16_t*>(g.C) + batch * g.c_sb + off, v);}
+  else store8(reinterpret_cast<bf16_t*>(g.C) + batch * g.c_sb + off, v);
+}
 
-// T x T output tile per workgroup.  ACT: the forward's activations (kept out of the other kernels' registers).
-template <int T, int BK, bool A_KC, bool B_KC, bool ACT>
-__global__ __launch_bounds__(NTHR, 2) void gemm_tile_kernel(GemmArgs g, int tiles_m, int tiles_n, int total, int per_xcd) {
+// T x T output tile per workgroup, a ring of NST stages, WGS workgroups per compute unit.  ACT: the forward's activations (kept
+// out of the other kernels' registers).
+template <int T, int BK, int NST, int WGS, bool A_KC, bool B_KC, bool ACT>
+__global__ __launch_bounds__(NTHR, WGS) void gemm_tile_kernel(GemmArgs g, int tiles_m, int tiles_n, int total, int per_xcd) {
   typedef Tile<T, BK, A_KC> TA;
   typedef Tile<T, BK, B_KC> TB;
   constexpr int STAGE = TA::BYTES + TB::BYTES;
   constexpr int PER = TA::COPIES + TB::COPIES;             // copies per wavefront and slice
   constexpr int W = T / 2, NB = W / 32;                    // a wavefront's block: W x W, NB x NB MFMA blocks
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[NST * STAGE];
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm0 = (wave >> 1) * W, wn0 = (wave & 1) * W;
@@ -191,8 +194,8 @@ __global__ __launch_bounds__(NTHR, 2) void gemm_tile_kernel(GemmArgs g, int tile
 #pragma unroll 1
   for (int s = 0; s < KT; ++s) {
     // this wavefront's share of slice s has landed once only the copies of the slices after it are outstanding
-    if (s + 2 < KT) wait_vm<2 * PER>();
-    else if (s + 2 == KT) wait_vm<PER>();
+    if (NST > 3 && s + 2 < KT) wait_vm<2 * PER>();
+    else if (s + 1 < KT) wait_vm<PER>();
     else wait_vm<0>();
     asm volatile("" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
@@ -275,10 +278,10 @@ __global__ __launch_bounds__(NTHR, 1) void gemm_small_kernel(GemmArgs g, int til
   typedef Tile<TN, BK, B_KC, 1> TB;
   constexpr int STAGE = TA::BYTES + TB::BYTES;
   constexpr int PER = TA::COPIES + TB::COPIES;
-  extern __shared__ __attribute__((aligned(1024))) unsigned char smem_dyn[];
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  unsigned char* const ring = smem_dyn + wave * (STG * STAGE);
+  unsigned char* const ring = smem + wave * (STG * STAGE);
   const unsigned lds0 = (unsigned)__builtin_amdgcn_readfirstlane(
       (int)(unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)ring);
 
@@ -390,7 +393,7 @@ __global__ __launch_bounds__(NTHR, 1) void gemm_small_kernel(GemmArgs g, int til
   __syncthreads();
   if (!writes) return;
   float v[8];
-  const float* sums = reinterpret_cast<const float*>(smem_dyn) + prow * LD + pcol;
+  const float* sums = reinterpret_cast<const float*>(smem) + prow * LD + pcol;
   load8(sums, v);
 #pragma unroll
   for (int w = 1; w < 4; ++w) {
@@ -402,23 +405,30 @@ __global__ __launch_bounds__(NTHR, 1) void gemm_small_kernel(GemmArgs g, int til
   finish8<ACT>(g, batch, split, off, use_aux, v, ra, lm);
 }
 
-template <int T, int BK, bool A_KC, bool B_KC, bool ACT>
+template <int T, int BK, int NST, int WGS, bool A_KC, bool B_KC, bool ACT>
 hipError_t launch_one(const GemmArgs& g, hipStream_t s) {
+  auto kern = gemm_tile_kernel<T, BK, NST, WGS, A_KC, B_KC, ACT>;
+  constexpr int lds = NST * 2 * T * BK * 2;
+  if (lds > 65536) {
+    static std::atomic<bool> attr_set[MAX_DEVICES];
+    const hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kern), lds, attr_set);
+    if (e != hipSuccess) return e;
+  }
   const long tiles_m = (g.M + T - 1) / T, tiles_n = (g.N + T - 1) / T;
   const long total = tiles_m * tiles_n * g.batch * g.split_k;
   if (total > (1L << 28)) return hipErrorInvalidValue;
   const long per_xcd = (total + 7) / 8;
-  hipLaunchKernelGGL((gemm_tile_kernel<T, BK, A_KC, B_KC, ACT>), dim3((unsigned)(8 * per_xcd)), dim3(NTHR), 0, s, g,
-                     (int)tiles_m, (int)tiles_n, (int)total, (int)per_xcd);
+  hipLaunchKernelGGL(kern, dim3((unsigned)(8 * per_xcd)), dim3(NTHR), lds, s, g, (int)tiles_m, (int)tiles_n, (int)total,
+                     (int)per_xcd);
   return hipGetLastError();
 }
-template <int T, int BK>
+template <int T, int BK, int NST, int WGS>
 hipError_t launch_pairing(const GemmArgs& g, hipStream_t s) {
   const bool a_kc = g.a_sk == 1, b_kc = g.b_sk == 1;
   if (a_kc && b_kc)
-    return g.mode == EPI_ACT_GELU || g.mode == EPI_ACT_TANH ? launch_one<T, BK, true, true, true>(g, s)
-                                                            : launch_one<T, BK, true, true, false>(g, s);
-  return a_kc ? launch_one<T, BK, true, false, false>(g, s) : launch_one<T, BK, false, false, false>(g, s);
+    return g.mode == EPI_ACT_GELU || g.mode == EPI_ACT_TANH ? launch_one<T, BK, NST, WGS, true, true, true>(g, s)
+                                                            : launch_one<T, BK, NST, WGS, true, true, false>(g, s);
+  return a_kc ? launch_one<T, BK, NST, WGS, true, false, false>(g, s) : launch_one<T, BK, NST, WGS, false, false, false>(g, s);
 }
 
 template <int TM, int STG, bool A_KC, bool B_KC, bool ACT>
@@ -449,7 +459,17 @@ hipError_t launch_small(const GemmArgs& g, hipStream_t s) {
 
 hipError_t launch_gemm_tile(const GemmArgs& g, int tm, int tn, hipStream_t s) {
   if (tn == 32) return tm == 32 ? launch_small<32, 4>(g, s) : launch_small<64, 3>(g, s);
-  return tm == 128 ? launch_pairing<128, 32>(g, s) : launch_pairing<64, 64>(g, s);
+  if (tm == 64) return launch_pairing<64, 64, 4, 2>(g, s);
+  const long tiles = (g.M + 127) / 128 * ((g.N + 127) / 128) * g.batch * g.split_k;
+  // One tile per compute unit at most: slices of 64, whole 128-byte lines of a K-contiguous operand, 96 KB asked for ahead.  From
+  // 512 on, the first operand K-contiguous: three workgroups per compute unit on rings of three stages, whose last round is
+  // shorter and whose epilogues run under two others' products.  Measured, us, two workgroups and four stages of 32 / the other:
+  // 192 tiles (3000 x 1000 x 2000) 27.7 / 24.5, 256 (8192 x 512 x 2048) 27.6 / 26.5, (4096 x 1024 x 4096) 44.2 / 43.0;
+  // 1000 (16000 x 1024 x 256 with GELU) 34.8 / 31.8, 1034 (12000 x 1304 x 328) 34.4 / 32.8, 512 (32768 x 256 x 1024) 36.7 / 36.0.
+  // Beyond those lines: 384 tiles (4096 x 1536 x 1536) 28.2 / 28.6 with three, 35.6 with slices of 64; both operands with
+  // contiguous rows, 341 tiles, 21.1 / 24.1 with three.
+  if (tiles <= 256) return launch_pairing<128, 64, 4, 1>(g, s);
+  return tiles >= 512 && g.a_sk == 1 ? launch_pairing<128, 32, 3, 3>(g, s) : launch_pairing<128, 32, 4, 2>(g, s);
 }
 
 }  // namespace hbp

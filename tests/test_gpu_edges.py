@@ -44,6 +44,18 @@ def test_products_of_few_tiles(B, N, d, d_ff):
     _check_backward(B, w, p, st, sv, inp, w.name)
 
 
+# 128 x 128 tiles with contractions that end inside a slice: 192 to 256 of them (slices of 64: the block VJPs of the first, the
+# forward of the second, the parameter gradients of the last), 400 and 450 (four stages), 512 and more (three workgroups per
+# compute unit: the VJPs of the third, the forward of the fourth)
+@pytest.mark.parametrize("N,d,d_ff", [(1500, 1000, 1096), (3100, 1000, 1096), (4200, 1000, 1096), (8200, 1000, 1096),
+                                      (104, 1288, 1288)])
+def test_products_on_wide_tiles(B, N, d, d_ff):
+    w = synth.scaled(W["resnet_like"], name=f"mlp_{N}_{d}_{d_ff}", L=2, N=N, d=d, d_ff=d_ff, w2_scale=0.7, ks=(1,))
+    inp, st, sv, p = _forward_matches(B, w)
+    H.assert_close(H.to_np(p.z), sv["z"], H.TOL["bf16"], f"{w.name} z")
+    _check_backward(B, w, p, st, sv, inp, w.name)
+
+
 # head widths around the 32, 64 and 128 columns that the matrix-core kernels pad to (136: the plain kernels), on sequence
 # lengths of one ragged tile, one workgroup, past the whole-problem kernels (128 / 256 positions) and past a block of tiles
 @pytest.mark.parametrize("causal", [True, False])
