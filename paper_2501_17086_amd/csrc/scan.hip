@@ -223,12 +223,17 @@ __device__ __forceinline__ float wave_sum_dpp(float v) {
   return (r0 + r1) + (r2 + r3);
 }
 
-// The wave-per-row scan for rows of exactly NCH * 512 channels with the plain recurrence (no re-split, no
+// The wave-per-row scan for rows of up to 2048 channels with the plain recurrence (no re-split, no
 // mask, coefficients per channel or 1), written as a software pipeline: the loads of layer l - 1 (block input
 // gradient, normalised input, coefficients, 1/rms; all as raw 16-byte vectors) are issued before the values of
 // layer l are touched, without a branch between them, so that a wave always has two layers' loads in flight
 // (the layer index is clamped at the bottom instead of guarded: the last stage is loaded twice).
-template <typename T, int NCH, bool HAS_E, bool HAS_LAM>
+// RAGGED: a width that is no multiple of 512, or few rows.  Lanes past the width repeat the row's last 8 channels, count nothing
+// and store nothing.  Up to 1024 channels the loads of three layers are ahead: with a wavefront or two per SIMD a layer takes
+// the latency of its loads over the number of layers ahead.  Measured, two iterations with their contractions (inner width 8), us,
+// unpipelined or a layer ahead / as here: 12 layers of 1000 x 328 67 / 55, 16 of 16384 x 256 363 / 345, 8 of 16384 x 768 540 / 491,
+// 8 of 8192 x 1800 736 / 605, 12 of 1000 x 512 65 / 57, 12 of 4096 x 1024 228 / 214.
+template <typename T, int NCH, bool HAS_E, bool HAS_LAM, bool RAGGED>
 __global__ __launch_bounds__(256) void scan_rows_pipe_kernel(ScanArgs a) {
   const int lane = threadIdx.x & 63;
   const long row = (long)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
@@ -239,8 +244,12 @@ __global__ __launch_bounds__(256) void scan_rows_pipe_kernel(ScanArgs a) {
   const T* __restrict__ y = reinterpret_cast<const T*>(a.y);
   const T* __restrict__ e = reinterpret_cast<const T*>(a.e);
   const float inv_d = 1.0f / (float)a.d;
-  const long off = row * a.d + lane * 8;          // chunk j: + 512 j
-  const long loff = lane * 8;
+  constexpr int STAGES = RAGGED && NCH <= 2 ? 4 : 2;
+  // chunk j: channels 512 j + 8 lane .. + 7; only the last can lie past the width
+  const long last = 512 * (NCH - 1) + lane * 8;
+  const bool on = !RAGGED || last < a.d;
+  const long loff = lane * 8, loff_end = on ? last : a.d - 8;
+  auto chunk = [&](int j) { return RAGGED && j == NCH - 1 ? loff_end : loff + 512 * j; };
 
   struct Stage {
     Raw8<T> v[NCH], y[NCH], e[HAS_E ? NCH : 1];
@@ -248,34 +257,37 @@ __global__ __launch_bounds__(256) void scan_rows_pipe_kernel(ScanArgs a) {
     float rinv;
   };
   auto issue = [&](Stage& st, long l) {
-    const long base = l * layer + off;
+    const long base = l * layer + row * a.d;
 #pragma unroll
     for (int j = 0; j < NCH; ++j) {
-      if (NCH == 1) {     // narrow rows: measured faster with the streamed operands read non-temporally (+13 %);
-        st.v[j].load_nt(dn + base + 512 * j);          // wider rows: measured slower (-3 %)
-        st.y[j].load_nt(y + base + 512 * j);
-        if (HAS_E) st.e[HAS_E ? j : 0].load_nt(e + base + 512 * j);
+      const long c = chunk(j);
+      if (NCH == 1 && !RAGGED) {     // narrow rows: measured faster with the streamed operands read non-temporally (+13 %);
+        st.v[j].load_nt(dn + base + c);                    // wider rows: measured slower (-3 %)
+        st.y[j].load_nt(y + base + c);
+        if (HAS_E) st.e[HAS_E ? j : 0].load_nt(e + base + c);
       } else {
-        st.v[j].load(dn + base + 512 * j);
-        st.y[j].load(y + base + 512 * j);
-        if (HAS_E) st.e[HAS_E ? j : 0].load(e + base + 512 * j);
+        st.v[j].load(dn + base + c);
+        st.y[j].load(y + base + c);
+        if (HAS_E) st.e[HAS_E ? j : 0].load(e + base + c);
       }
-      if (HAS_LAM) st.lam[HAS_LAM ? j : 0].load(a.lambda + l * a.d + loff + 512 * j);
+      if (HAS_LAM) st.lam[HAS_LAM ? j : 0].load(a.lambda + l * a.d + c);
     }
     st.rinv = a.rinv[l * a.N + row];
   };
   float carry[NCH][8];
 #pragma unroll
-  for (int j = 0; j < NCH; ++j) load8(g + a.l_hi * layer + off + 512 * j, carry[j]);
+  for (int j = 0; j < NCH; ++j) load8(g + a.l_hi * layer + row * a.d + chunk(j), carry[j]);
   auto consume = [&](const Stage& st, long l) {
     float v[NCH][8], yy[NCH][8];
     float dot = 0.f;
 #pragma unroll
     for (int j = 0; j < NCH; ++j) {
+      const float inner = dot;      // (what lies past the width: left out)
       st.v[j].unpack(v[j]);
       st.y[j].unpack(yy[j]);
 #pragma unroll
       for (int i = 0; i < 8; ++i) dot = fmaf(v[j][i], yy[j][i], dot);
+      if (RAGGED && j == NCH - 1 && !on) dot = inner;
     }
     const float m = wave_sum_dpp(dot) * inv_d;
     const float r = st.rinv;
@@ -299,19 +311,21 @@ __global__ __launch_bounds__(256) void scan_rows_pipe_kernel(ScanArgs a) {
 #pragma unroll
         for (int i = 0; i < 8; ++i) carry[j][i] += t[i];
       }
-      store8(g + l * layer + off + 512 * j, carry[j]);
+      if (!RAGGED || j < NCH - 1 || on) store8(g + l * layer + row * a.d + chunk(j), carry[j]);
     }
   };
-  Stage s0, s1;
+  Stage st[STAGES];
   long l = a.l_hi - 1;
-  issue(s0, l);
+  auto within = [&](long k) { return k > a.l_lo ? k : a.l_lo; };
+#pragma unroll
+  for (int i = 0; i < STAGES - 1; ++i) issue(st[i], within(l - i));
   while (true) {
-    issue(s1, l - 1 > a.l_lo ? l - 1 : a.l_lo);
-    consume(s0, l);
-    if (--l < a.l_lo) break;
-    issue(s0, l - 1 > a.l_lo ? l - 1 : a.l_lo);
-    consume(s1, l);
-    if (--l < a.l_lo) break;
+#pragma unroll
+    for (int i = 0; i < STAGES; ++i) {
+      issue(st[(i + STAGES - 1) % STAGES], within(l - (STAGES - 1)));
+      consume(st[i], l);
+      if (--l < a.l_lo) return;
+    }
   }
 }
 
@@ -965,13 +979,21 @@ hipError_t launch_scan_t(const ScanArgs& args, hipStream_t s) {
       }
       return hipGetLastError();
     }
-    if (a.d % 512 == 0 && nch <= 4 && !a.mask && !a.lambda_tok) {    // whole 512-channel chunks: the pipelined form
-#define HBP_ROWS_PIPE(N_)                                                                                          \
-      do {                                                                                                         \
-        if (a.e && a.lambda) hipLaunchKernelGGL((scan_rows_pipe_kernel<T, N_, true, true>), grid, block, 0, s, a);      \
-        else if (a.e) hipLaunchKernelGGL((scan_rows_pipe_kernel<T, N_, true, false>), grid, block, 0, s, a);            \
-        else if (a.lambda) hipLaunchKernelGGL((scan_rows_pipe_kernel<T, N_, false, true>), grid, block, 0, s, a);       \
-        else hipLaunchKernelGGL((scan_rows_pipe_kernel<T, N_, false, false>), grid, block, 0, s, a);                    \
+    // the pipelined form (of its two, the one with three layers' loads ahead from four layers on; up to 4096 rows, four
+    // wavefronts per SIMD, for whole chunks of 512, too: above, memory is the bound and the other's registers are fewer)
+    if (nch <= 4 && !a.mask && !a.lambda_tok && (a.d % 512 == 0 || a.l_hi - a.l_lo >= 4)) {
+      const bool ragged = a.d % 512 || (nch <= 2 && a.N <= 4096 && a.l_hi - a.l_lo >= 4);
+#define HBP_ROWS_PIPE_AS(N_, R_)                                                                                        \
+      do {                                                                                                              \
+        if (a.e && a.lambda) hipLaunchKernelGGL((scan_rows_pipe_kernel<T, N_, true, true, R_>), grid, block, 0, s, a);  \
+        else if (a.e) hipLaunchKernelGGL((scan_rows_pipe_kernel<T, N_, true, false, R_>), grid, block, 0, s, a);        \
+        else if (a.lambda) hipLaunchKernelGGL((scan_rows_pipe_kernel<T, N_, false, true, R_>), grid, block, 0, s, a);   \
+        else hipLaunchKernelGGL((scan_rows_pipe_kernel<T, N_, false, false, R_>), grid, block, 0, s, a);                \
+      } while (0)
+#define HBP_ROWS_PIPE(N_)                                                                                               \
+      do {                                                                                                              \
+        if (ragged) HBP_ROWS_PIPE_AS(N_, true);                                                                         \
+        else HBP_ROWS_PIPE_AS(N_, false);                                                                               \
       } while (0)
       switch (nch) {
         case 1: HBP_ROWS_PIPE(1); break;
@@ -980,6 +1002,7 @@ hipError_t launch_scan_t(const ScanArgs& args, hipStream_t s) {
         default: HBP_ROWS_PIPE(4); break;
       }
 #undef HBP_ROWS_PIPE
+#undef HBP_ROWS_PIPE_AS
       return hipGetLastError();
     }
     switch (nch) {

@@ -282,6 +282,18 @@ def test_unequal_shares_of_a_contraction(B, L, N, d, d_ff):
     _check_backward(B, w, p, st, sv, inp, w.name)
 
 
+# the scan of rows with a norm: widths around the chunks of 512 (a last chunk of one vector, of all but one, none), one to nine
+# layers (fewer than the three that are loaded ahead, and every remainder), fewer rows than a workgroup's four, more rows
+# than the line for whole chunks, coefficients of 1 and per channel
+@pytest.mark.parametrize("lam", ["one", "uniform"])
+@pytest.mark.parametrize("L,N,d", [(1, 3, 40), (3, 5, 520), (4, 1, 8), (5, 7, 504), (6, 33, 512), (7, 9, 520), (9, 6, 1016),
+                                   (5, 2, 1024), (6, 5, 1032), (4, 3, 1544), (8, 5, 2040), (4, 4100, 512), (4, 2, 2056)])
+def test_scan_of_rows(B, L, N, d, lam):
+    w = synth.scaled(W["resnet_like"], name=f"rows_{L}_{N}_{d}_{lam}", L=L, N=N, d=d, d_ff=16, lam=lam, w2_scale=0.7, ks=(1, 2))
+    inp, st, sv, p = _forward_matches(B, w)
+    _check_backward(B, w, p, st, sv, inp, w.name)
+
+
 # the norm's kernels: rows held by 16, 32 or 64 lanes and one to eight vectors per lane, the last partly past the width, and
 # a row count that leaves part of a wavefront without rows; in front of the block (y, rinv) and after the sum, in place
 @pytest.mark.parametrize("post", ["none", "rms"])
