@@ -37,16 +37,22 @@ struct Workspace {
   size_t off_v, off_da, off_part, off_scan, off_wt, off_pre, off_m, off_tmp, off_dqkv, off_dsum, off_counter, total;
 };
 
-// Shares of the contraction (length K, at least 2048 rows each) for a parameter gradient of `tiles` output tiles of 256 x 256.
-// bf16: each compute unit takes one tile's share at a time, and the last round of 256 costs as much as a full one: the number of
-// shares with the least estimated time, from what was seen: 0.93 us per slice of 32 in every compute unit (1.15 PFLOP/s), 13 us
-// to store a round's tiles, 0.05 us per partial tile in the sum and 5 us for its launch.  Shares differ by a slice at most, so
-// any number will do.  All parameter gradients of a stack, us, with 512 / tiles shares (or the next number below that divides the
-// slices) and with these: 12 transformer layers of width 256 on 32768 tokens (shares of W1, Wqkv, Wo: 8, 8, 16; now 5, 7, 16) 1729
-// / 1507, 3 of width 1024 on 16384 (2, 2, 8; 4, 7, 5) 2397 / 2258, 4 of width 768 on 8192 1041 / 951, the GRU's 1024 steps of 32
-// x 1024 663 / 620, the LSTM's 512 steps 394 / 373.
-int pick_split(const hbp_desc* d, long tiles, long K) {
+// The partial sums of a parameter gradient take at most this much: shares are taken to fill the chip, and what does that without
+// them has none.
+constexpr long PARTIAL_BYTES = 256L << 20;
+
+// Shares of the contraction (length K, at least 2048 rows each) for a parameter gradient of `tiles` output tiles of 256 x 256, `out`
+// elements in all.  bf16: each compute unit takes one tile's share at a time, and the last round of 256 costs as much as a full
+// one: the number of shares with the least estimated time, from what was seen: 0.93 us per slice of 32 in every compute unit
+// (1.15 PFLOP/s), 13 us to store a round's tiles, 0.05 us per partial tile in the sum and 5 us for its launch.  Shares differ by a
+// slice at most, so any number will do.  All parameter gradients of a stack, us, with 512 / tiles shares (or the next number below
+// that divides the slices) and with these: 12 transformer layers of width 256 on 32768 tokens (shares of W1, Wqkv, Wo: 8, 8, 16;
+// now 5, 7, 16) 1729 / 1507, 3 of width 1024 on 16384 (2, 4, 8; 4, 5, 5) 2397 / 2258, 4 of width 768 on 8192 1041 / 951, the GRU's
+// 1024 steps of 32 x 1024 663 / 620, the LSTM's 512 steps 394 / 373.  Without the bound 46 blocks of 1024 x 4096 on 32768 tokens
+// would take two shares, 1.5 GB, for an estimated 0.3 %; 8 of 768 x 3072 on 16384 four, 288 MB, at 1920 us, where three take 1864.
+int pick_split(const hbp_desc* d, long tiles, long out, long K) {
   long cap = K / 2048;
+  if (cap > PARTIAL_BYTES / 4 / out) cap = PARTIAL_BYTES / 4 / out;
   if (cap < 1) cap = 1;
   if (cap > 64) cap = 64;
   if (d->dtype == HBP_BF16 && K % 32 == 0) {
@@ -77,18 +83,19 @@ Splits param_splits(const hbp_desc* d) {
   Splits s{1, 1, 1, 1, 1, 1};
   if (tfm(d)) {
     const long nb = d->L / 2;
-    s.s_w2 = s.s_w1 = pick_split(d, tiles_of(d->d, d->d_ff) * nb, d->N);
-    s.s_qkv = pick_split(d, tiles_of(3 * d->d, d->d) * nb, d->N);
-    s.s_o = pick_split(d, tiles_of(d->d, d->d) * nb, d->N);
+    s.s_w2 = s.s_w1 = pick_split(d, tiles_of(d->d, d->d_ff) * nb, d->d * d->d_ff * nb, d->N);
+    s.s_qkv = pick_split(d, tiles_of(3 * d->d, d->d) * nb, 3 * d->d * d->d * nb, d->N);
+    s.s_o = pick_split(d, tiles_of(d->d, d->d) * nb, d->d * d->d * nb, d->N);
     return s;
   }
   const long nb = shared_w(d) ? 1 : d->L;
   const long K = shared_w(d) ? d->L * d->N : d->N;
-  if (!cell(d)) s.s_w2 = pick_split(d, tiles_of(d->d, d->d_ff) * nb, K);
+  if (!cell(d)) s.s_w2 = pick_split(d, tiles_of(d->d, d->d_ff) * nb, d->d * d->d_ff * nb, K);
   // (the standard GRU: the two gates' rows and the candidate's are products of their own)
-  s.s_w1 = pick_split(d, tiles_of(gru(d) ? 2 * d->d : d->d_ff, hidden_w(d)) * nb, K);
-  if (gru(d)) s.s_cand = pick_split(d, tiles_of(d->d, d->d), K);
-  if (recurrent(d)) s.s_u = pick_split(d, tiles_of(d->d_ff, d->d_in), K);
+  const long m1 = gru(d) ? 2 * d->d : d->d_ff;
+  s.s_w1 = pick_split(d, tiles_of(m1, hidden_w(d)) * nb, m1 * hidden_w(d) * nb, K);
+  if (gru(d)) s.s_cand = pick_split(d, tiles_of(d->d, d->d), d->d * d->d, K);
+  if (recurrent(d)) s.s_u = pick_split(d, tiles_of(d->d_ff, d->d_in), d->d_ff * d->d_in, K);
   return s;
 }
 

@@ -52,6 +52,18 @@ def test_workspace_size_scales():
     assert a >= 4 * 16 * (64 + 128) * 2
 
 
+# Everything in a depth stack's workspace but the partial sums of the parameter gradients is a multiple of the token count, and
+# 2048 tokens have no partial sums: what is left at a larger count are those, at most 256 MB.
+@pytest.mark.parametrize("kind", [dict(), dict(dtype="f32"), dict(kind="transformer", seq_len=64)])
+@pytest.mark.parametrize("d,d_ff", [(64, 128), (256, 1024), (328, 1304), (768, 3072), (1024, 4096), (1536, 1536), (2048, 8192)])
+def test_partial_sums_take_a_bounded_part_of_the_workspace(kind, d, d_ff):
+    kind = dict(kind, heads=d // 8 if kind.get("kind") else 0)
+    for L in (2, 6, 36, 46):
+        for N in (4096, 8192, 16384, 32768, 131072):
+            lin = B.workspace_size(_desc(**kind, L=L, N=2048, d=d, d_ff=d_ff))
+            assert B.workspace_size(_desc(**kind, L=L, N=N, d=d, d_ff=d_ff)) <= lin * (N // 2048) + (256 << 20), (L, N)
+
+
 @pytest.mark.parametrize("field,value,status", [
     ("L", 0, 1), ("N", -1, 1), ("d", 0, 1), ("d", 60, 2), ("d_ff", 100, 2), ("kind", 7, 1), ("dtype", 3, 1),
     ("act", 5, 1), ("norm", 2, 1), ("lambda_kind", 9, 1), ("loss_every_state", 2, 1), ("struct_size", 12, 1),
