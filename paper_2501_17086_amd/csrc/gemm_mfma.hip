@@ -651,16 +651,6 @@ hipError_t launch_lean(const GemmArgs& g, hipStream_t s) {
   return one_at_a_time ? launch_lean_walk<A_KC, B_KC, FAST, true, false>(g, s)
                        : launch_lean_walk<A_KC, B_KC, FAST, false, false>(g, s);
 }
-// The lean kernel's share of a chip whose compute units take one 256 x 256 tile each at a time: below about 0.55 of the
-// last round filled (up to 140 tiles, or 257 to 281) the tiles of 128 x 128 are faster.  Measured, lean / 128 tile:
-// 64 tiles (8192 x 512 x 2048) 39.3 / 27.7 us, 128 tiles (2048 x 4096 x 1024) 29.0 / 25.0, 192 tiles (4096 x 3072 x 768
-// with GELU) 47.9 / 64.8, 256 tiles (8192 x 2048 x 512) 28.8 / 31.0, (16384 x 1024 x 4096) 110 / 179.
-inline bool fills_chip(long tiles) { return tiles * 100 >= (tiles + 255) / 256 * 256 * 55; }
-// Sizes that are no multiple of the tile: from two rounds of whole tiles on, these go to the lean kernel and the rest to
-// the tile kernel in launches of its own; below, everything to the tile kernel (3000 x 1000 x 4000, batch 4, 132 whole
-// tiles: 163 us in parts, 122 us whole).
-constexpr long SPLIT_FROM = 512;
-
 // 128 x 128 tiles once they give most compute units one, else 64 x 64.  Measured, 128 / 64: 24 tiles of 128 (1000 x 328 x
 // 1304) 18.9 / 10.1 us, 128 tiles (2048 x 1024 x 4096) 42.3 / 28.0, 192 tiles (4096 x 768 x 3072) 36.4 / 37.2, 288 tiles
 // (1000 x 328 x 1304, batch 12) 27.1 / 33.4, 768 tiles (3000 x 1000 x 4000, batch 4) 122 / 222.
@@ -753,8 +743,8 @@ bool launch_gemm_mfma(const GemmArgs& g, hipStream_t s, hipError_t* err) {
     const long hm = g.M / BM * BM, hn = g.N / BN * BN;
     const long tiles = (hm / BM) * (hn / BN) * g.batch * g.split_k;
     if (hm == g.M && hn == g.N) {
-      if (fills_chip(tiles)) { *err = launch_lean_for(g, a_kc, b_kc, s); return true; }
-    } else if (tiles >= SPLIT_FROM) {
+      if (gemm_fills_chip(tiles)) { *err = launch_lean_for(g, a_kc, b_kc, s); return true; }
+    } else if (tiles >= GEMM_SPLIT_FROM) {
       // the whole tiles, then the remaining columns of all rows, then the remaining rows (disjoint blocks of C)
       *err = launch_lean_for(part_of(g, 0, hm, 0, hn), a_kc, b_kc, s);
       if (*err == hipSuccess && hn < g.N) *err = launch_tile_for(part_of(g, 0, g.M, hn, g.N), s);

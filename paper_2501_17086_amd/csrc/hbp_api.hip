@@ -41,31 +41,53 @@ struct Workspace {
 // them has none.
 constexpr long PARTIAL_BYTES = 256L << 20;
 
-// Shares of the contraction (length K, at least 2048 rows each) for a parameter gradient of `tiles` output tiles of 256 x 256, `out`
-// elements in all.  bf16: each compute unit takes one tile's share at a time, and the last round of 256 costs as much as a full
-// one: the number of shares with the least estimated time, from what was seen: 0.93 us per slice of 32 in every compute unit
-// (1.15 PFLOP/s), 13 us to store a round's tiles, 0.05 us per partial tile in the sum and 5 us for its launch.  Shares differ by a
-// slice at most, so any number will do.  All parameter gradients of a stack, us, with 512 / tiles shares (or the next number below
-// that divides the slices) and with these: 12 transformer layers of width 256 on 32768 tokens (shares of W1, Wqkv, Wo: 8, 8, 16;
-// now 5, 7, 16) 1729 / 1507, 3 of width 1024 on 16384 (2, 4, 8; 4, 5, 5) 2397 / 2258, 4 of width 768 on 8192 1041 / 951, the GRU's
-// 1024 steps of 32 x 1024 663 / 620, the LSTM's 512 steps 394 / 373.  Without the bound 46 blocks of 1024 x 4096 on 32768 tokens
-// would take two shares, 1.5 GB, for an estimated 0.3 %; 8 of 768 x 3072 on 16384 four, 288 MB, at 1920 us, where three take 1864.
-int pick_split(const hbp_desc* d, long tiles, long out, long K) {
+long tiles_of(long M, long N, long t = 256) { return ((M + t - 1) / t) * ((N + t - 1) / t); }
+
+// Estimated time (us) of a bf16 parameter gradient of M x N x batch whose contraction of `slices` slices of 32 is cut into s shares,
+// on the kernel that launch_gemm_mfma takes.  The figures were fitted to the times of 22 stacks with every number of shares (the
+// number chosen is 2 % slower than the best at the median): the 256 x 256 kernel 0.93 us per slice in every compute unit (1.15
+// PFLOP/s) and 13 us to store a round's 256 tiles; tiles of 128, of which 512 run at a time, 0.97 us per slice and 12 us to store
+// with two in every compute unit, 0.5 and 5 with one; whole tiles and remainders in launches of their own 1.2 times the two and 110
+// us; the sum of the shares 5 us and 5.2 TB/s.
+double share_time(long M, long N, long batch, long slices, long s) {
+  const double sl = (double)((slices + s - 1) / s);
+  auto wide = [sl](long tiles) { return (double)((tiles + 255) / 256) * (0.93 * sl + 13.0); };
+  auto narrow = [sl](long tiles) {
+    const long left = tiles % 512;
+    return (double)(tiles / 512) * (0.97 * sl + 12.0) + (left == 0 ? 0.0 : left <= 256 ? 0.5 * sl + 5.0 : 0.97 * sl + 5.0);
+  };
+  const long n128 = tiles_of(M, N, 128) * batch * s, whole = (M / 256) * (N / 256) * batch * s;
+  double t = M % 256 == 0 && N % 256 == 0 ? (gemm_fills_chip(whole) ? wide(whole) : narrow(n128))
+             : whole >= GEMM_SPLIT_FROM   ? 1.2 * (wide(whole) + narrow(n128 - 4 * whole)) + 110.0
+                                          : narrow(n128);
+  if (s > 1) t += 5.0 + (double)(M * N * batch * s) * 4.0 / 5.2e6;
+  return t;
+}
+// Shares of the contraction (length K, at least 2048 rows each) for a parameter gradient of M x N x batch.  bf16: the number with
+// the least estimated time; shares differ by a slice at most, so any number will do.  All parameter gradients of a stack, us, with
+// 512 / tiles shares of 256 x 256 (or the next number below that divides the slices) and with these: 12 transformer layers of width
+// 256 on 32768 tokens (shares of W1, Wqkv, Wo: 8, 8, 16; now 5, 7, 16) 1729 / 1507, 3 of width 1024 on 16384 (2, 4, 8; 4, 5, 5)
+// 2397 / 2258, 4 of width 768 on 8192 1041 / 951, the GRU's 1024 steps of 32 x 1024 663 / 620, the LSTM's 512 steps 394 / 373.
+// Ragged widths, counted in tiles of 256 (which do not run there) / of 128: 2 blocks of 520 x 2080 on 32768 tokens (shares 4 / 3) 845
+// / 776, 1 on 16384 (8 / 3) 225 / 206, 1 of 1000 x 4000 on 16384 (4 / 1) 593 / 570, 24 of 136 x 544 on 8192 (3 / 1) 343 / 323.
+// Without the bound on the partial sums 46 blocks of 1024 x 4096 on 32768 tokens would take two shares, 1.5 GB, for an estimated
+// 0.3 %; 8 of 768 x 3072 on 16384 four, 288 MB, at 1920 us, where three take 1864.
+int pick_split(const hbp_desc* d, long M, long N, long batch, long K) {
   long cap = K / 2048;
-  if (cap > PARTIAL_BYTES / 4 / out) cap = PARTIAL_BYTES / 4 / out;
+  if (cap > PARTIAL_BYTES / 4 / (M * N * batch)) cap = PARTIAL_BYTES / 4 / (M * N * batch);
   if (cap < 1) cap = 1;
   if (cap > 64) cap = 64;
   if (d->dtype == HBP_BF16 && K % 32 == 0) {
     long best = 1;
     double least = 0;
     for (long s = 1; s <= cap; ++s) {
-      const double slices = (double)((K / 32 + s - 1) / s);
-      const double cost = (double)((tiles * s + 255) / 256) * (0.93 * slices + 13.0) + (s > 1 ? 5.0 + 0.05 * (double)(tiles * s) : 0.0);
-      if (s == 1 || cost < least) { least = cost; best = s; }
+      const double t = share_time(M, N, batch, K / 32, s);
+      if (s == 1 || t < least) { least = t; best = s; }
     }
     return (int)best;
   }
   // other kernels, smaller tiles: twice the compute units in tiles of 256 x 256 (few tiles: once, which halves the partial sums)
+  const long tiles = tiles_of(M, N) * batch;
   long want = ((tiles <= 32 ? 256 : 512) + tiles - 1) / tiles;
   if (want > cap) want = cap;
   if (want < 1) want = 1;
@@ -75,27 +97,24 @@ int pick_split(const hbp_desc* d, long tiles, long out, long K) {
   return (int)want;
 }
 
-long tiles_of(long M, long N) { return ((M + 255) / 256) * ((N + 255) / 256); }
-
 struct Splits { int s_w2, s_w1, s_u, s_qkv, s_o, s_cand; };
 
 Splits param_splits(const hbp_desc* d) {
   Splits s{1, 1, 1, 1, 1, 1};
   if (tfm(d)) {
     const long nb = d->L / 2;
-    s.s_w2 = s.s_w1 = pick_split(d, tiles_of(d->d, d->d_ff) * nb, d->d * d->d_ff * nb, d->N);
-    s.s_qkv = pick_split(d, tiles_of(3 * d->d, d->d) * nb, 3 * d->d * d->d * nb, d->N);
-    s.s_o = pick_split(d, tiles_of(d->d, d->d) * nb, d->d * d->d * nb, d->N);
+    s.s_w2 = s.s_w1 = pick_split(d, d->d, d->d_ff, nb, d->N);
+    s.s_qkv = pick_split(d, 3 * d->d, d->d, nb, d->N);
+    s.s_o = pick_split(d, d->d, d->d, nb, d->N);
     return s;
   }
   const long nb = shared_w(d) ? 1 : d->L;
   const long K = shared_w(d) ? d->L * d->N : d->N;
-  if (!cell(d)) s.s_w2 = pick_split(d, tiles_of(d->d, d->d_ff) * nb, d->d * d->d_ff * nb, K);
+  if (!cell(d)) s.s_w2 = pick_split(d, d->d, d->d_ff, nb, K);
   // (the standard GRU: the two gates' rows and the candidate's are products of their own)
-  const long m1 = gru(d) ? 2 * d->d : d->d_ff;
-  s.s_w1 = pick_split(d, tiles_of(m1, hidden_w(d)) * nb, m1 * hidden_w(d) * nb, K);
-  if (gru(d)) s.s_cand = pick_split(d, tiles_of(d->d, d->d), d->d * d->d, K);
-  if (recurrent(d)) s.s_u = pick_split(d, tiles_of(d->d_ff, d->d_in), d->d_ff * d->d_in, K);
+  s.s_w1 = pick_split(d, gru(d) ? 2 * d->d : d->d_ff, hidden_w(d), nb, K);
+  if (gru(d)) s.s_cand = pick_split(d, d->d, d->d, 1, K);
+  if (recurrent(d)) s.s_u = pick_split(d, d->d_ff, d->d_in, 1, K);
   return s;
 }
 

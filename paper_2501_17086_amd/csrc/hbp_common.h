@@ -153,6 +153,15 @@ hipError_t launch_gemm_generic(int dtype, const GemmArgs& g, hipStream_t s);
 // the same for fp32 storage on the matrix cores, where the layout allows it
 bool gemm_f32_ok(const GemmArgs& g);
 hipError_t launch_gemm_f32(const GemmArgs& g, hipStream_t s);
+// The 256 x 256 kernel's share of a chip whose compute units take one tile each at a time: below about 0.55 of the
+// last round filled (up to 140 tiles, or 257 to 281) the tiles of 128 x 128 are faster.  Measured, lean / 128 tile:
+// 64 tiles (8192 x 512 x 2048) 39.3 / 27.7 us, 128 tiles (2048 x 4096 x 1024) 29.0 / 25.0, 192 tiles (4096 x 3072 x 768
+// with GELU) 47.9 / 64.8, 256 tiles (8192 x 2048 x 512) 28.8 / 31.0, (16384 x 1024 x 4096) 110 / 179.
+inline bool gemm_fills_chip(long tiles) { return tiles * 100 >= (tiles + 255) / 256 * 256 * 55; }
+// Sizes that are no multiple of the tile: from two rounds of whole tiles on, these go to the lean kernel and the rest to
+// the tile kernel in launches of its own; below, everything to the tile kernel (3000 x 1000 x 4000, batch 4, 132 whole
+// tiles: 163 us in parts, 122 us whole).
+constexpr long GEMM_SPLIT_FROM = 512;
 // fast bf16 MFMA path; returns false when the shape/layout is not covered
 bool launch_gemm_mfma(const GemmArgs& g, hipStream_t s, hipError_t* err);
 // the same contractions on tiles of 128 x 128, 64 x 64, 64 x 32 or 32 x 32, any size (called through launch_gemm_mfma, which

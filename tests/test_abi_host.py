@@ -64,6 +64,16 @@ def test_partial_sums_take_a_bounded_part_of_the_workspace(kind, d, d_ff):
             assert B.workspace_size(_desc(**kind, L=L, N=N, d=d, d_ff=d_ff)) <= lin * (N // 2048) + (256 << 20), (L, N)
 
 
+# Shares of the contraction, from the partial sums' place in the workspace (dW1 and dW2 share it): ragged widths go to tiles of 128,
+# of which 512 run at a time (2 x 85 tiles in 3 shares: one round), whole ones to tiles of 256 (64 in 4 shares: one round of 256).
+@pytest.mark.parametrize("L,N,d,d_ff,shares", [(2, 32768, 520, 2080, 3), (1, 16384, 520, 2080, 3), (1, 16384, 1000, 4000, 1),
+                                               (24, 8192, 136, 544, 1), (12, 8192, 200, 800, 3), (1, 16384, 1024, 4096, 4),
+                                               (10, 16384, 256, 1024, 6)])
+def test_shares_are_counted_in_the_tiles_that_run(L, N, d, d_ff, shares):
+    partial = B.workspace_size(_desc(L=L, N=N, d=d, d_ff=d_ff)) - B.workspace_size(_desc(L=L, N=2048, d=d, d_ff=d_ff)) * (N // 2048)
+    assert round(partial / (L * d * d_ff * 4)) == (shares if shares > 1 else 0)
+
+
 @pytest.mark.parametrize("field,value,status", [
     ("L", 0, 1), ("N", -1, 1), ("d", 0, 1), ("d", 60, 2), ("d_ff", 100, 2), ("kind", 7, 1), ("dtype", 3, 1),
     ("act", 5, 1), ("norm", 2, 1), ("lambda_kind", 9, 1), ("loss_every_state", 2, 1), ("struct_size", 12, 1),
