@@ -226,13 +226,11 @@ __device__ __forceinline__ float wave_sum_dpp(float v) {
 // The wave-per-row scan for rows of up to 2048 channels with the plain recurrence (no re-split, no
 // mask, coefficients per channel or 1), written as a software pipeline: the loads of layer l - 1 (block input
 // gradient, normalised input, coefficients, 1/rms; all as raw 16-byte vectors) are issued before the values of
-// layer l are touched, without a branch between them, so that a wave always has two layers' loads in flight
-// (the layer index is clamped at the bottom instead of guarded: the last stage is loaded twice).
+// layer l are touched, without a branch between them, so that a wave always has two layers' loads in flight, or four
+// (the layer index is clamped at the bottom instead of guarded: the last layer is loaded once more per stage ahead).
 // RAGGED: a width that is no multiple of 512, or few rows.  Lanes past the width repeat the row's last 8 channels, count nothing
-// and store nothing.  Up to 1024 channels the loads of three layers are ahead: with a wavefront or two per SIMD a layer takes
-// the latency of its loads over the number of layers ahead.  Measured, two iterations with their contractions (inner width 8), us,
-// unpipelined or a layer ahead / as here: 12 layers of 1000 x 328 67 / 55, 16 of 16384 x 256 363 / 345, 8 of 16384 x 768 540 / 491,
-// 8 of 8192 x 1800 736 / 605, 12 of 1000 x 512 65 / 57, 12 of 4096 x 1024 228 / 214.
+// and store nothing.  Up to 1024 channels the loads of three layers are ahead, in four stages: with a wavefront or two per SIMD a
+// layer takes the latency of its loads over the number of layers ahead.  Where it is taken, and what it gives: launch_scan_t.
 template <typename T, int NCH, bool HAS_E, bool HAS_LAM, bool RAGGED>
 __global__ __launch_bounds__(256) void scan_rows_pipe_kernel(ScanArgs a) {
   const int lane = threadIdx.x & 63;
@@ -979,10 +977,19 @@ hipError_t launch_scan_t(const ScanArgs& args, hipStream_t s) {
       }
       return hipGetLastError();
     }
-    // the pipelined form (of its two, the one with three layers' loads ahead from four layers on; up to 4096 rows, four
-    // wavefronts per SIMD, for whole chunks of 512, too: above, memory is the bound and the other's registers are fewer)
-    if (nch <= 4 && !a.mask && !a.lambda_tok && (a.d % 512 == 0 || a.l_hi - a.l_lo >= 4)) {
-      const bool ragged = a.d % 512 || (nch <= 2 && a.N <= 4096 && a.l_hi - a.l_lo >= 4);
+    // The pipelined form: whole chunks of 512, and from four layers on ragged widths where its kernel is the faster one.  Up to
+    // 1024 channels that is a matter of few rows (a layer of 4 MB, 8192 rows in bf16 and 4096 in fp32): three layers' loads ahead
+    // take the registers of three wavefronts, and with many rows others would run in their place.  Measured, scans of two iterations
+    // over 12 layers, us, unpipelined / this form: bf16 1000 x 328 45 / 32, 6000 x 256 65 / 59, 4096 x 504 70 / 67, 8192 x 504 132 / 155,
+    // 32768 x 128 259 / 260 (with coefficients of 1: 224 / 190), 8192 x 768 259 / 224, 32768 x 1000 1214 / 1241; fp32 4096 x 128 60 / 53,
+    // 16384 x 128 184 / 207, 2048 x 504 72 / 67, 4096 x 504 130 / 146, 1000 x 1000 74 / 68, 3000 x 1000 199 / 206.  Rows of 512 channels,
+    // at most 4096 of them, take the same kernel (two stages / this form, bf16 1000 rows 42 / 32, fp32 3000 122 / 91), of 1024 not
+    // (fp32 1000 rows 65 / 68, bf16 4096 0.93 to 1.0 times).
+    constexpr long es = sizeof(T);
+    const bool whole = a.d % 512 == 0, four = a.l_hi - a.l_lo >= 4;
+    const bool few = a.N * a.d * es <= (4L << 20) && a.N * es <= 16384;
+    const bool ragged = whole ? four && nch == 1 && a.N <= 4096 : four && (nch > 2 || few || (es == 2 && (nch == 2 || a.d <= 128)));
+    if (nch <= 4 && !a.mask && !a.lambda_tok && (whole || ragged)) {
 #define HBP_ROWS_PIPE_AS(N_, R_)                                                                                        \
       do {                                                                                                              \
         if (a.e && a.lambda) hipLaunchKernelGGL((scan_rows_pipe_kernel<T, N_, true, true, R_>), grid, block, 0, s, a);  \

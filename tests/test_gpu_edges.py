@@ -294,6 +294,18 @@ def test_scan_of_rows(B, L, N, d, lam):
     _check_backward(B, w, p, st, sv, inp, w.name)
 
 
+# the same in fp32, and on both sides of the lines up to which few rows of a ragged width take the pipelined form (a layer of 4 MB,
+# 8192 rows in bf16 and 4096 in fp32; widths to 128 in bf16: any number)
+@pytest.mark.parametrize("dtype,L,N,d", [("f32", 4, 3, 40), ("f32", 5, 9, 504), ("f32", 7, 6, 512), ("f32", 6, 5, 520), ("f32", 5, 3, 1024),
+                                         ("f32", 4, 4096, 40), ("f32", 4, 4100, 40), ("f32", 5, 2048, 512), ("f32", 4, 2049, 520),
+                                         ("f32", 4, 5, 1544), ("bf16", 4, 8192, 136), ("bf16", 4, 8200, 136), ("bf16", 4, 8200, 128),
+                                         ("bf16", 4, 4200, 504), ("bf16", 4, 2100, 1000)])
+def test_scan_of_rows_around_the_lines_of_its_forms(B, dtype, L, N, d):
+    w = synth.scaled(W["resnet_like"], name=f"rows_{dtype}_{L}_{N}_{d}", dtype=dtype, L=L, N=N, d=d, d_ff=16, w2_scale=0.7, ks=(1,))
+    inp, st, sv, p = _forward_matches(B, w)
+    _check_backward(B, w, p, st, sv, inp, w.name)
+
+
 # the norm's kernels: rows held by 16, 32 or 64 lanes and one to eight vectors per lane, the last partly past the width, and
 # a row count that leaves part of a wavefront without rows; in front of the block (y, rinv) and after the sum, in place
 @pytest.mark.parametrize("post", ["none", "rms"])
