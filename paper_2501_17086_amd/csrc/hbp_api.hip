@@ -1165,6 +1165,19 @@ __attribute__((visibility("default"))) hbp_status hbp_internal_chains(const hbp_
   return forward ? run_forward(d, b, stream, wait) : run_exact_backward(d, b, stream, wait);
 }
 
+// For tests: the groups on one XCD of a chain, the workgroups of each, and where in the workspace the last call left the numbers (32
+// bits, one per group) of those that have started.
+__attribute__((visibility("default"))) hbp_status hbp_internal_chain_groups(const hbp_desc* d, int* groups, int* members, size_t* offset) {
+  HBP_RUN(check_desc(d));
+  if (!recurrent(d) || d->dtype != HBP_BF16) return HBP_E_UNSUPPORTED;
+  RecArgs a{};
+  a.kind = d->kind == HBP_RNN ? 0 : d->kind == HBP_GATED ? 1 : d->kind == HBP_LSTM ? 2 : 3;
+  a.N = d->N; a.H = hidden_w(d); a.D = d->d; a.F = d->d_ff;
+  recurrent_on_xcd(a, groups, members, offset);
+  *offset += carve(d).off_counter;
+  return HBP_OK;
+}
+
 hbp_status hbp_param_grads(const hbp_desc* d, hbp_buffers* b, void* stream) {
   HBP_RUN(check_desc(d));
   HBP_RUN(check_bufs(d, b, NEED_PG));

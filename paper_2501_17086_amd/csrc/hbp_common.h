@@ -228,13 +228,18 @@ struct RecArgs {
   int* counter;         // device scratch, RECURRENT_COUNTER_BYTES
   void* ring;           // device scratch, recurrent_ring_bytes()
   int wait;             // for the rest of a group to start: REC_WAIT, or (tests) REC_WAIT_NOT: give up at the first look,
-                        // REC_ALONE_ANYHOW: every group's first workgroup goes on alone, REC_ANYWHERE: no groups on one XCD
+                        // REC_ALONE_ANYHOW: every group's first workgroup goes on alone, REC_ANYWHERE: no groups on one XCD,
+                        // REC_ON_XCD: groups on one XCD whatever the number of steps, with time to get together, but for those
+                        // whose number modulo 16 has its bit set in wait >> 8: given up before they start
 };
-enum { REC_WAIT = 0, REC_WAIT_NOT = 1, REC_ALONE_ANYHOW = 2, REC_ANYWHERE = 3 };
+enum { REC_WAIT = 0, REC_WAIT_NOT = 1, REC_ALONE_ANYHOW = 2, REC_ANYWHERE = 3, REC_ON_XCD = 4 };
 constexpr size_t RECURRENT_COUNTER_BYTES = 4096;
 size_t recurrent_ring_bytes();
 bool recurrent_ok(const RecArgs& a);
 hipError_t launch_recurrent(const RecArgs& a, bool forward, hipStream_t s);
+// for tests: the groups on one XCD of a launch, the workgroups of each, and the bytes in `counter` before the words (one per group)
+// that say how many of them have started
+void recurrent_on_xcd(const RecArgs& a, int* groups, int* members, size_t* offset);
 
 // out[i] = sum_s part[s][i], i < n
 hipError_t launch_splitk_reduce(const float* part, float* out, long n, int split, hipStream_t s);

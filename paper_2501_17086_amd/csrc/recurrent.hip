@@ -37,6 +37,7 @@
 // workgroup reads 32 KB per product then, 500 cycles); inputs of a step read when it begins: loads return in order, so the wait
 // for the operands met a trip to memory, 10 % more; per-step addresses in 64 bits and branches around edges: 5 %.
 #include "hbp_common.h"
+#include <cstddef>
 
 namespace hbp {
 
@@ -349,8 +350,10 @@ template <bool LOCAL>
 __device__ __forceinline__ bool all_started(const RecArgs& a, int wpg, int group, unsigned started) {
   __shared__ int given_up;
   if (threadIdx.x == 0) {
-    constexpr int POLLS = LOCAL ? REC_LOCAL_POLLS : REC_ARRIVE_POLLS;
-    const int limit = a.wait == REC_WAIT_NOT || a.wait == REC_ALONE_ANYHOW ? 0 : a.L < REC_SPIN_LIMIT / POLLS ? (int)a.L * POLLS : REC_SPIN_LIMIT;
+    const int polls_per_step = LOCAL && a.wait == REC_WAIT ? REC_LOCAL_POLLS : REC_ARRIVE_POLLS;
+    const int limit = a.wait == REC_WAIT_NOT || a.wait == REC_ALONE_ANYHOW ? 0
+                      : a.L < REC_SPIN_LIMIT / polls_per_step              ? (int)a.L * polls_per_step
+                                                                           : REC_SPIN_LIMIT;
     PlaceWords* words = reinterpret_cast<PlaceWords*>(a.counter);
     unsigned* word = LOCAL ? &words->local[group] : &words->group[group];
     unsigned w = started;
@@ -909,13 +912,18 @@ __global__ __launch_bounds__(256, 1) void rec_backward_kernel(RecArgs a, int wpg
   if (!LOCAL && !done && member == 0) backward_chain<KIND, KQ, RT, true>(a, ring, member, started, part);
 }
 
-// the empty word into every slot (n 16-byte pieces); the words of the places at zero, but for those of the groups (`word`)
-__global__ __launch_bounds__(256) void rec_fill_kernel(uint4* p, long n, PlaceWords* places, unsigned word) {
+// the empty word into every slot (n 16-byte pieces); the words of the places at zero, but for those of the groups (`word`) and of
+// the groups on one XCD whose number modulo 16 has its bit set in `gone`
+__global__ __launch_bounds__(256) void rec_fill_kernel(uint4* p, long n, PlaceWords* places, unsigned word, unsigned gone) {
   const long i = (long)blockIdx.x * 256 + threadIdx.x;
   if (i < n) p[i] = make_uint4(REC_EMPTY, REC_EMPTY, REC_EMPTY, REC_EMPTY);
   if (blockIdx.x == 0) {
+    constexpr int LOCAL0 = offsetof(PlaceWords, local) / 4;
     for (int j = threadIdx.x; j < (int)(sizeof(PlaceWords) / 4); j += 256)
-      reinterpret_cast<unsigned*>(places)[j] = j >= 1 && j < 1 + REC_MAX_WG ? word : 0u;
+      reinterpret_cast<unsigned*>(places)[j] =
+          j >= 1 && j < 1 + REC_MAX_WG                                                              ? word
+          : j >= LOCAL0 && j < LOCAL0 + REC_LOCAL_GROUPS && ((gone >> ((j - LOCAL0) & 15)) & 1u) ? REC_ALONE
+                                                                                                   : 0u;
   }
 }
 
@@ -944,9 +952,10 @@ hipError_t launch_rec(const RecArgs& a, bool forward, hipStream_t s) {
   const long ring = (long)REC_UNITS * REC_SLOTS * groups * RT * wpg * 1024;
   const long ring_local = (long)REC_UNITS * REC_SLOTS * locals * (RTL ? wpg : (wpg + 1) / 2) * 1024;
   const long n16 = (ring + ring_local) / 16;
-  const bool local = a.wait == REC_WAIT && a.L >= REC_LOCAL_FROM;
+  const bool on_xcd = (a.wait & 255) == REC_ON_XCD, local = on_xcd || (a.wait == REC_WAIT && a.L >= REC_LOCAL_FROM);
   hipLaunchKernelGGL(rec_fill_kernel, dim3((unsigned)((n16 + 255) / 256)), dim3(256), 0, s, reinterpret_cast<uint4*>(a.ring), n16,
-                     reinterpret_cast<PlaceWords*>(a.counter), a.wait == REC_ALONE_ANYHOW ? REC_ALONE : 0u);
+                     reinterpret_cast<PlaceWords*>(a.counter), a.wait == REC_ALONE_ANYHOW ? REC_ALONE : 0u,
+                     on_xcd ? (unsigned)a.wait >> 8 : 0u);
   // enough workgroups that every XCD of the eight has a group's number of them for each group it can be asked to take
   const dim3 everywhere((unsigned)(8 * wpg * ((locals + 7) / 8))), anywhere((unsigned)(groups * wpg));
   RecArgs l = a;
@@ -987,6 +996,12 @@ bool recurrent_ok(const RecArgs& a) {
   if (a.N * a.F > (1L << 30) || a.N * a.D > (1L << 30)) return false;
   return ok16(a.x) && ok16(a.z) && ok16(a.W1) && ok16(a.W2) && ok16(a.Wt1) && ok16(a.Wt2) && ok16(a.g) &&
          ok16(a.ring) && ok16(a.ux) && ok16(a.lambda) && ok16(a.lambda_tok) && ok16(a.e) && ok16(a.dphi);
+}
+void recurrent_on_xcd(const RecArgs& a, int* groups, int* members, size_t* offset) {
+  const long wpg = (rec_width(a) + REC_COLS - 1) / REC_COLS;
+  *groups = (int)(rec_half(a, wpg) ? (a.N + 7) / 8 : (a.N + 15) / 16);
+  *members = (int)wpg;
+  *offset = offsetof(PlaceWords, local);
 }
 hipError_t launch_recurrent(const RecArgs& a, bool forward, hipStream_t s) {
   switch (a.kind) {

@@ -84,7 +84,10 @@ def _chain(kind, L, N, H, inner=None, **kw):
 @pytest.mark.parametrize("kind,L,N,H", [("rnn", 1, 1, 8), ("rnn", 9, 17, 264), ("rnn", 6, 64, 1024), ("token", 7, 15, 72),
                                         ("gated", 2, 16, 32), ("gated", 9, 33, 136), ("gated", 5, 65, 1024), ("lstm", 1, 5, 24),
                                         ("lstm", 9, 16, 520), ("lstm", 6, 64, 1024), ("gru", 3, 1, 40), ("gru", 9, 31, 256),
-                                        ("gru", 6, 48, 1000), ("gru", 4, 8, 1032)])
+                                        ("gru", 6, 48, 1000), ("gru", 4, 8, 1032),
+                                        # from 12 steps on: groups on one XCD, of 8 rows or of 16
+                                        ("rnn", 13, 17, 264), ("rnn", 12, 144, 224), ("token", 12, 9, 40), ("gated", 14, 33, 136),
+                                        ("lstm", 12, 20, 520), ("gru", 13, 31, 256), ("gru", 12, 40, 1000)])
 def test_chains_along_time(B, kind, L, N, H):
     w = _chain(kind, L, N, H)
     inp, st, sv, p = _forward_matches(B, w)
@@ -119,12 +122,13 @@ def test_chains_along_time_with_nan_rows_and_on_two_streams(B, kind):
     assert bool(q.x[1:, 3].isnan().all()) and not bool(p.x.isnan().any())
 
 
+@pytest.mark.parametrize("L", [9, 13])           # groups anywhere, groups on one XCD
 @pytest.mark.parametrize("kind,H", [("rnn", 264), ("gated", 64), ("lstm", 72), ("gru", 256)])
-def test_chains_along_time_in_a_graph(B, kind, H):
+def test_chains_along_time_in_a_graph(B, kind, H, L):
     """Forward and exact backpropagation recorded into a HIP graph: every replay, with eager chains and synchronisations
     between them, gives the eager result bit for bit."""
     import torch
-    w = _chain(kind, 9, 20, H)
+    w = _chain(kind, L, 20, H)
     inp, st, sv, p = _setup(B, w)
 
     def both():
@@ -153,9 +157,11 @@ def test_chains_along_time_in_a_graph(B, kind, H):
 
 # An infinity in the last block of 32 channels, at widths whose quarters of the contraction reach past it: saturated gates
 # stay finite, and gradients are infinite, not NaN.  It meets one step's product, so that what follows does not mix the two.
+# (wait: groups anywhere, as such a short chain has them, and on one XCD, where two blocks share an operand)
+@pytest.mark.parametrize("wait", [0, 4])
 @pytest.mark.parametrize("kind", ["rnn", "token", "gated", "lstm", "gru"])
 @pytest.mark.parametrize("H_", [24, 72, 264, 600])
-def test_chains_along_time_with_infinities(B, kind, H_):
+def test_chains_along_time_with_infinities(B, kind, H_, wait):
     import torch
     w = _chain(kind, 2, 5, H_)
     inp, st, _, p = _setup(B, w)
@@ -169,15 +175,15 @@ def test_chains_along_time_with_infinities(B, kind, H_):
     st = H.oracle_stack(w, inp)
     with np.errstate(invalid="ignore", over="ignore"):
         sv = O.forward(st, inp["x0"], inp["xin"])
-        B.hbp_forward(p)
+        _run_chain(B, p, 1, wait)
         _same_numbers(H.to_np(p.x)[1], sv["x"][1], f"{w.name} x[1]")
         # backward on a finite state
         inp["x0"][2, c], p.x[0, 2, c] = 0, 0
         sv = O.forward(st, inp["x0"], inp["xin"])
-        B.hbp_forward(p)
+        _run_chain(B, p, 1, wait)
         inp["e"][1, 2, c] = np.inf
         p.e[1, 2, c] = float("inf")
-        B.hbp_exact_backward(p)
+        _run_chain(B, p, 0, wait)
         _same_numbers(H.to_np(p.g)[0], O.exact_backward(st, sv, inp["e"])[0], f"{w.name} g[0]")
 
 
@@ -212,27 +218,91 @@ def test_chains_along_time_by_one_workgroup(B, kind, L, N, H, wait):
     assert torch.equal(p.g, q.g)
 
 
-# Groups on one XCD each (of 8 rows, or of 16 where there would be too many) against groups whose workgroups may be anywhere
-# (wait 3; of 16 or 32 rows): the same results bit for bit.  Odd numbers of blocks, a last group with one row, more groups than
-# XCDs, the widest with every compute unit taken.
-@pytest.mark.parametrize("kind,L,N,H", [("rnn", 13, 1, 8), ("rnn", 12, 9, 96), ("rnn", 12, 1030, 32), ("token", 12, 96, 672), ("token", 15, 33, 520),
-                                        ("gated", 12, 65, 512), ("gated", 13, 17, 40), ("lstm", 12, 64, 1024), ("lstm", 14, 25, 264),
-                                        ("gru", 12, 96, 672), ("gru", 15, 31, 1000), ("gru", 12, 64, 1024)])
-def test_chains_on_one_xcd_and_anywhere(B, kind, L, N, H):
+ANYWHERE, ON_XCD = 3, 4
+
+
+def _run_chain(B, p, forward, wait):
     import ctypes as C
+    import torch
+    b = p.buffers()
+    f = B.lib().hbp_internal_chains
+    assert f(C.byref(p.desc), forward, wait, C.byref(b), C.c_void_p(torch.cuda.current_stream().cuda_stream)) == B.HBP_OK
+
+
+def _groups_on_xcd(B, p):
+    """Per group on one XCD of p's last chain how many workgroups have started and whether it was given up; workgroups of each."""
+    import ctypes as C
+    import torch
+    n, m, o = C.c_int(), C.c_int(), C.c_size_t()
+    assert B.lib().hbp_internal_chain_groups(C.byref(p.desc), C.byref(n), C.byref(m), C.byref(o)) == B.HBP_OK
+    torch.cuda.synchronize()
+    words = p.workspace[o.value:o.value + 4 * n.value].view(torch.int32).cpu().numpy().astype(np.uint32)
+    return words & 0x7FFFFFFF, words >> 31 == 1, m.value
+
+
+# Groups on one XCD each (of 8 rows, or of 16 where there would be too many) against groups whose workgroups may be anywhere
+# (of 16 or 32 rows): the same results bit for bit, and the former did all of it.  Odd numbers of blocks, a last group with one row,
+# more groups than XCDs, the widest with every compute unit taken; chains of one step and of more than the four slots.
+@pytest.mark.parametrize("kind,L,N,H", [("rnn", 13, 1, 8), ("rnn", 2, 9, 96), ("rnn", 12, 1030, 32), ("token", 12, 96, 672), ("token", 15, 33, 520),
+                                        ("rnn", 6, 144, 224), ("gated", 12, 65, 512), ("gated", 13, 17, 40), ("lstm", 12, 64, 1024),
+                                        ("lstm", 14, 25, 264), ("lstm", 5, 144, 224), ("gru", 12, 96, 672), ("gru", 15, 31, 1000),
+                                        ("gru", 12, 64, 1024), ("gru", 2, 126, 512)])
+def test_chains_on_one_xcd_and_anywhere(B, kind, L, N, H):
     import torch
     w = _chain(kind, L, N, H)
     inp, st, sv, p = _setup(B, w)
     q = B.allocate(w, inp)
-    B.hbp_forward(p)
-    B.hbp_exact_backward(p)
-    b = q.buffers()
-    f = B.lib().hbp_internal_chains
-    s = torch.cuda.current_stream().cuda_stream
-    assert f(C.byref(q.desc), 1, 3, C.byref(b), C.c_void_p(s)) == B.HBP_OK
-    assert f(C.byref(q.desc), 0, 3, C.byref(b), C.c_void_p(s)) == B.HBP_OK
+    for forward in (1, 0):
+        p.workspace.zero_()
+        _run_chain(B, p, forward, ON_XCD)
+        started, gone, members = _groups_on_xcd(B, p)
+        assert (started == members).all() and not gone.any()
+        _run_chain(B, q, forward, ANYWHERE)
     for n in ("x", "z", "lam", "g"):
         assert torch.equal(getattr(p, n), getattr(q, n)), n
+
+
+# Some groups on one XCD are given up before they start, as where other kernels hold its compute units: the second launch does them
+# again, together with those that share a larger group of its own, and leaves out the larger groups of which all is done.  Groups
+# of 8 rows in larger ones of 16 and 32, of 16 in 16 and 32; none, some and all given up; a last larger group that is not whole.
+@pytest.mark.parametrize("gone", [0x0002, 0x4921, 0x00F0, 0xFFFF])
+@pytest.mark.parametrize("kind,L,N,H", [("rnn", 9, 76, 96), ("token", 6, 64, 1024), ("rnn", 5, 144, 224), ("token", 3, 96, 672),
+                                        ("gated", 6, 76, 96), ("gated", 5, 58, 1000), ("lstm", 6, 64, 1024), ("lstm", 7, 70, 264),
+                                        ("lstm", 3, 96, 672), ("gru", 7, 76, 96), ("gru", 6, 64, 1024), ("gru", 5, 90, 672),
+                                        ("gru", 1, 144, 224)])
+def test_chains_of_which_groups_on_one_xcd_are_given_up(B, kind, L, N, H, gone):
+    import torch
+    w = _chain(kind, L, N, H)
+    inp, st, sv, p = _setup(B, w)
+    q = B.allocate(w, inp)
+    for forward in (1, 0):
+        p.workspace.zero_()
+        _run_chain(B, p, forward, ON_XCD | gone << 8)
+        started, given_up, members = _groups_on_xcd(B, p)
+        want = np.array([bool(gone >> (j % 16) & 1) for j in range(len(started))])
+        assert np.array_equal(given_up, want) and (started[~want] == members).all()
+        _run_chain(B, q, forward, ANYWHERE)
+    for n in ("x", "z", "lam", "g"):
+        assert torch.equal(getattr(p, n), getattr(q, n)), n
+
+
+# Four chains at once, each as wide as the chip: some groups do not get together on an XCD and are left to the second launch.
+@pytest.mark.parametrize("kind,N,H", [("rnn", 64, 1024), ("lstm", 128, 512), ("gru", 64, 1024)])
+def test_four_chains_at_once(B, kind, N, H):
+    import torch
+    w = _chain(kind, 40, N, H)
+    inp, st, sv, p = _setup(B, w)
+    B.hbp_forward(p)
+    B.hbp_exact_backward(p)
+    others = [(B.allocate(w, inp), torch.cuda.Stream()) for _ in range(4)]
+    torch.cuda.synchronize()
+    for step in (B.hbp_forward, B.hbp_exact_backward):
+        for q, s in others:
+            step(q, stream=s.cuda_stream)
+    torch.cuda.synchronize()
+    for q, _ in others:
+        for n in ("x", "z", "lam", "g"):
+            assert n == "lam" and p.lam is None or torch.equal(getattr(p, n), getattr(q, n)), n
 
 
 # fp32 products: around the 32- and 64-wide tiles, contractions that end inside a chunk of 32 or leave a wavefront's
