@@ -938,10 +938,14 @@ inline int rec_row_tiles(const RecArgs& a) {
 inline bool ok16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 // The groups on one XCD each: of 8 rows where every XCD of the eight then has a compute unit for each workgroup, else of 16.
 // Half the rows are half the bytes that a workgroup reads in every phase (32 KB at width 1024 and 16 rows, 500 cycles at a
-// compute unit's 64 bytes), for the same number of matrix instructions.
+// compute unit's 64 bytes), for the same number of matrix instructions.  Widths to 512, where those bytes weigh less: only as long as
+// that leaves half of the chip to others.  Measured, 512 steps of 128 x 512, ms, all of the chip in groups of 8 / half of it in groups
+// of 16, one call | two at once | four: RNN forward 0.82 / 0.83 | 1.30 / 1.24 | 2.35 / 2.39, GRU 1.10 / 1.19 | 1.64 / 1.62 | 6.1 / 2.3,
+// LSTM 1.32 / 1.52 | 4.3 / 2.0 | 6.4 / 5.1, exact backpropagation of the GRU 1.00 / 0.99 | 1.22 / 1.28 | 4.7 / 1.4; 64 x 1024: GRU
+// 1.18 / 1.53 | 2.3 / 1.6 | 4.5 / 4.7, exact 1.13 / 1.21 | 2.2 / 1.3 | 4.1 / 4.0, LSTM 1.54 / 1.82 | 2.9 / 1.9 | 5.2 / 5.2.
 inline bool rec_half(const RecArgs& a, long wpg) {
-  const long n = (a.N + 7) / 8;
-  return (n + 7) / 8 * wpg <= 32 && n * ((wpg + 1) / 2) <= REC_MAX_WG * 2;       // (and the vectors fit their memory)
+  const long n = (a.N + 7) / 8, xcds = wpg > 16 ? 8 : 4;
+  return (n + xcds - 1) / xcds * wpg <= 32 && n * ((wpg + 1) / 2) <= REC_MAX_WG * 2;       // (and the vectors fit their memory)
 }
 
 // RT: row tiles of the groups anywhere, RTL: of those on one XCD
