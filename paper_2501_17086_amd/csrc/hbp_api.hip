@@ -156,7 +156,7 @@ Workspace carve(const hbp_desc* d) {
   if (tfm(d)) o = align_up(o + (size_t)(d->L / 2) * d->N * 3 * d->d * es, 256);
   w.off_dsum = o;
   if (tfm(d)) o = align_up(o + (size_t)(d->L / 2) * d->N * d->heads * 4, 256);
-  // the chain kernels' counters and what their workgroups exchange (2 MB)
+  // the chain kernels' counters and what their workgroups exchange (4 MB)
   w.off_counter = o;
   if (recurrent(d) && d->dtype == HBP_BF16) o += RECURRENT_COUNTER_BYTES + recurrent_ring_bytes();
   w.total = o;

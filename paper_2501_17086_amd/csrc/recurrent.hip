@@ -22,14 +22,23 @@
 //     part of the cell runs on the sums, one or two channels of a row per thread, the state staying in registers.
 // A group begins once all of its workgroups have started: from then on each of them keeps running, so that every wait inside the
 // chain ends.  If a group has not got together on one XCD after a poll per step (other kernels hold its compute units), it is
-// given up, and a second launch, which otherwise ends at once, takes what is left (short chains go to it whole): its workgroups, at most 64 in all, a quarter
-// of the compute units, may be anywhere and exchange through memory.  They take their place in a group in the order they start (a
-// device counter).  One group of a launch at most is incomplete at any time, so that this is soon the case.  Where it is not,
-// because other kernels hold the compute units, or incomplete groups of many launches (nine or more) hold all of them against
-// each other, a group that has waited for REC_ARRIVE_POLLS polls per step, about as long as the chain takes one workgroup, is
-// left to its first workgroup alone, and the others end.  That one plays all of them in turn, reading the weights from memory at
-// every step: 0.1 to 0.4 ms a step (width 1024: 60 to 90 times the time of the group).  The sums have the same order in every
-// form: the same results bit for bit.
+// given up, and a second launch, which otherwise ends at once, takes what is left (short chains go to it whole): its workgroups, at
+// most 64 in all, a quarter of the compute units, may be anywhere and exchange through memory.  They take their place in a group in
+// the order they start (a device counter).  One group of that launch at most is incomplete at any time, so that this is soon the
+// case.  Where it is not, because other kernels hold the compute units, or incomplete groups of many launches (nine or more) hold all
+// of them against each other, a group that has waited for REC_ARRIVE_POLLS polls per step, about as long as the chain takes one
+// workgroup, is left to its first workgroup alone, and the others end.  That one plays all of them in turn, reading the weights from
+// memory at every step: 0.1 to 0.4 ms a step (width 1024: 60 to 90 times the time of the group).  The sums have the same order in
+// every form: the same results bit for bit.
+//
+// The launch with groups on one XCD keeps up to 256 workgroups running, one per compute unit (64 rows of width 1024; 32 rows: 128).
+// What other streams do meanwhile waits for it, other chains among it, and three or more of those that need a compute unit per
+// workgroup may also keep each other's groups from getting together, which the second launch then does.  512 steps at width 1024, ms
+// for 1, 2, 4 and 8 calls at once, all of them with 64 workgroups anywhere / as it is: 32 rows, forward of the RNN 1.50, 1.91, 3.72,
+// 6.0 / 0.85, 1.18, 2.42, 3.7, of the GRU 1.77, 1.99, 2.29, 4.6 / 1.11, 1.21, 3.3, 6.6, of the LSTM 1.67, 1.83, 2.18, 4.3 / 1.42,
+// 1.55, 3.6, 7.2; exact backpropagation of the RNN 1.63, 2.21, 4.22, 7.0 / 0.84, 1.12, 2.20, 3.5, of the GRU 1.95, 2.32, 2.55, 5.1 /
+// 0.98, 1.16, 3.0, 5.0; 64 rows, forward of the RNN 2.17, 2.51, 2.77, 5.5 / 0.88, 1.37, 2.67, 7.7, of the GRU 2.69, 2.90, 3.33, 9.1 /
+// 1.18, 2.27, 4.5, 9.2.  One or two calls gain in every kind; from three on the wide GRU and LSTM lose, by 1.75 times at most.
 //
 // Measured (1024 steps, batch 32, width 1024): exact backpropagation of the RNN 14.5 ms as launches of their own, 3.3 through
 // memory, 1.7 on one XCD with groups of 8 rows; forward of the GRU 20.9, 3.6 and 2.4.  0.8 us per dependent product: about 0.4 from
@@ -51,8 +60,12 @@ constexpr int REC_SLOTS = 4;                   // steps a vector's slots are dee
 constexpr int REC_SPIN_LIMIT = 1 << 24;        // polls inside the chain (bounded only so that a fault elsewhere cannot hang it)
 constexpr int REC_ARRIVE_POLLS = 256;          // polls per step for the rest of a group to start
 constexpr unsigned REC_ALONE = 1u << 31;       // in a group's word beside the number of workgroups that have started
-constexpr int REC_PAUSE = 4;                    // times 64 cycles (1024 steps of the RNN and of the GRU: 3: 2.18 and 4.00 ms, 4: 2.06 and 4.01, 7: 2.22 and 4.00)
-constexpr int REC_LOCAL_FROM = 12;             // steps from which groups on one XCD pay for their launch (8 steps: 38.3 us against 39.8 for the RNN, 36.8 against 35.4 for the LSTM)
+// times 64 cycles (1024 steps of the RNN and of the GRU: 3: 2.18 and 4.00 ms, 4: 2.06 and 4.01, 7: 2.22 and 4.00)
+constexpr int REC_PAUSE = 4;
+// Steps from which groups on one XCD pay for their launch.  Groups anywhere / on one XCD, us, 8 steps of 32 x 1024: RNN 39.8 / 38.3,
+// LSTM 35.4 / 36.8; 12 steps, forward: RNN 50.4 / 40.6, gated cell 41.0 / 39.2, LSTM 60.9 / 57.2, GRU 57.9 / 50.5; 1 x 64: 29.9 / 25.2,
+// 23.8 / 24.2, 32.3 / 29.4, 32.4 / 29.6; backwards 54.0 / 46.2, 47.4 / 39.8, 65.8 / 55.5, 57.3 / 50.8.
+constexpr int REC_LOCAL_FROM = 12;
 constexpr int REC_COLS = 32;                   // channels per workgroup
 constexpr int REC_MAX_WG = 64;
 constexpr int REC_XCDS = 16;                   // XCDs that a launch may meet (the chip has eight)
@@ -130,7 +143,8 @@ struct Ring {
     word = kept(RT ? t * 4 : threadIdx.x & 1 ? REC_OUTSIDE : (t >> 5) * 256 + (t & 31) * 4);
   }
   __device__ __forceinline__ int at(int u, long step, int rt, int block) const {
-    return (u * REC_SLOTS + ((int)step & (REC_SLOTS - 1))) * slot + mine + rt * tile + (RT ? block * 1024 : (block >> 1) * 1024 + (block & 1) * 128);
+    return (u * REC_SLOTS + ((int)step & (REC_SLOTS - 1))) * slot + mine + rt * tile +
+           (RT ? block * 1024 : (block >> 1) * 1024 + (block & 1) * 128);
   }
   __device__ __forceinline__ void put(int place, unsigned w) const {
     __builtin_amdgcn_raw_buffer_store_b32(w, buf, (int)word, place, LOCAL ? 0 : 16);
@@ -267,16 +281,22 @@ __device__ __forceinline__ unsigned pk(float2 v) {
   const float other = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v.x), 0xB1, 0xF, 0xF, true));   // quad_perm [1,0,3,2]
   return threadIdx.x & 1 ? pack_bf16x2(other, v.x) : pack_bf16x2(v.x, other);
 }
-__device__ __forceinline__ unsigned bld2(__amdgpu_buffer_rsrc_t b, unsigned off, int more = 0) { return __builtin_amdgcn_raw_buffer_load_b32(b, (int)off, more, 0); }
+__device__ __forceinline__ unsigned bld2(__amdgpu_buffer_rsrc_t b, unsigned off, int more = 0) {
+  return __builtin_amdgcn_raw_buffer_load_b32(b, (int)off, more, 0);
+}
 template <int CH>
 __device__ __forceinline__ float2 bldf2(__amdgpu_buffer_rsrc_t b, unsigned off, int more = 0) {
   if (CH == 1) return make_float2(__builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(b, (int)off, more, 0)), 0.f);
   return __builtin_bit_cast(float2, (uint2v)__builtin_amdgcn_raw_buffer_load_b64(b, (int)off, more, 0));
 }
-__device__ __forceinline__ void bst2(unsigned w, __amdgpu_buffer_rsrc_t b, unsigned off, int more = 0) { __builtin_amdgcn_raw_buffer_store_b32(w, b, (int)off, more, 0); }
+__device__ __forceinline__ void bst2(unsigned w, __amdgpu_buffer_rsrc_t b, unsigned off, int more = 0) {
+  __builtin_amdgcn_raw_buffer_store_b32(w, b, (int)off, more, 0);
+}
 // for other workgroups, at ring.at(...): never the empty word (a pair of NaNs of that pattern changes its first sign)
 template <bool LOCAL, int RT>
-__device__ __forceinline__ void publish(const Ring<LOCAL, RT>& ring, int place, unsigned w) { ring.put(place, w == REC_EMPTY ? 0xFFFF7FFFu : w); }
+__device__ __forceinline__ void publish(const Ring<LOCAL, RT>& ring, int place, unsigned w) {
+  ring.put(place, w == REC_EMPTY ? 0xFFFF7FFFu : w);
+}
 template <bool LOCAL, int RT>
 __device__ __forceinline__ void empty(const Ring<LOCAL, RT>& ring, int u, long step, int member) {
 #pragma unroll
@@ -307,7 +327,8 @@ static_assert(sizeof(PlaceWords) <= RECURRENT_COUNTER_BYTES, "the words' place i
 // reciprocal there, leave the result in a vector register and put every operand load whose address depends on it into a loop
 // over the lanes: 11 % on the GRU.)
 template <bool LOCAL>
-__device__ __forceinline__ void take_place(const RecArgs& a, int wpg, int groups, int per, int locals, int& group, int& member, unsigned& started) {
+__device__ __forceinline__ void take_place(const RecArgs& a, int wpg, int groups, int per, int locals, int& group, int& member,
+                                           unsigned& started) {
   __shared__ int place[2];
   started = 0;
   if (threadIdx.x == 0) {
@@ -416,7 +437,8 @@ __device__ __forceinline__ void members(int own, int wpg, F f) {
 // A phase publishes what it leaves for others first of all; its results, the emptying of slots and the question for the next
 // phase's operands come after that, in the time that the others' words need to arrive.
 template <int KIND, int KQ, int RT, bool ALONE, bool LOCAL, int SLOTS>
-__device__ __forceinline__ bool forward_chain(const RecArgs& a, const Ring<LOCAL, RT>& ring, int own, unsigned started, Partials<RT, SLOTS>& part) {
+__device__ __forceinline__ bool forward_chain(const RecArgs& a, const Ring<LOCAL, RT>& ring, int own, unsigned started,
+                                              Partials<RT, SLOTS>& part) {
   constexpr int UNITS = KIND == K_LSTM ? 4 : KIND == K_GRU ? 3 : 2;
   constexpr bool TWO = KIND == K_RNN || KIND == K_GRU;       // two dependent products per step
   constexpr int TILES = rec_tiles<RT>(), CH = rec_channels<RT>();
@@ -651,7 +673,8 @@ __global__ __launch_bounds__(256, 1) void rec_forward_kernel(RecArgs a, int wpg,
 // Exact backpropagation: g[l] = (da_l W1 + what goes past the product) (+ e_l) + lambda_l (.) g[l+1], l = L-1 .. 0; da as in
 // gated_cell.hip.  Weights transposed: Wt1 = W1^T [H][F] (GRU: [W_z; W_r]^T [H][2H]), Wt2 = W2^T [F][D] (RNN) or W_n^T [H][H].
 template <int KIND, int KQ, int RT, bool ALONE, bool LOCAL>
-__device__ __forceinline__ bool backward_chain(const RecArgs& a, const Ring<LOCAL, RT>& ring, int own, unsigned started, Partials<RT, 1>& part) {
+__device__ __forceinline__ bool backward_chain(const RecArgs& a, const Ring<LOCAL, RT>& ring, int own, unsigned started,
+                                               Partials<RT, 1>& part) {
   constexpr int UNITS = KIND == K_LSTM ? 4 : KIND == K_GRU ? 3 : 2;
   constexpr bool TWO = KIND == K_RNN || KIND == K_GRU;       // two dependent products per step
   constexpr int U0 = TWO ? 1 : 0;                            // first unit of the (second) product with W1
@@ -664,7 +687,8 @@ __device__ __forceinline__ bool backward_chain(const RecArgs& a, const Ring<LOCA
     Weights<KQ>& t = w[ALONE ? 0 : u];
     const int col0 = member * REC_COLS;
     if (TWO && u == 0) t.load((const bf16_t*)a.Wt2, KIND == K_RNN ? D : H, col0, KIND == K_RNN ? F : H, KIND == K_RNN ? D : H, wave, lane);
-    else t.load((const bf16_t*)a.Wt1 + (long)(u - U0) * H, KIND == K_GRU ? 2 * H : F, col0, KIND == K_RNN ? D : H, KIND == K_RNN ? F : H, wave, lane);
+    else t.load((const bf16_t*)a.Wt1 + (long)(u - U0) * H, KIND == K_GRU ? 2 * H : F, col0, KIND == K_RNN ? D : H,
+                KIND == K_RNN ? F : H, wave, lane);
     return t;
   };
   if (!ALONE) {
@@ -729,7 +753,9 @@ __device__ __forceinline__ bool backward_chain(const RecArgs& a, const Ring<LOCA
     }
   };
   // the step to be read becomes the one before, or stays the first
-  auto advance = [&](bool more) __attribute__((always_inline)) { lc.before(more); lt.before(more); e.before(more); x.before(more); z.before(more); };
+  auto advance = [&](bool more) __attribute__((always_inline)) {
+    lc.before(more); lt.before(more); e.before(more); x.before(more); z.before(more);
+  };
   Inputs now, next;
   if (!ALONE) { read_step(now); advance(last > 0); }
 #pragma unroll 1
@@ -816,7 +842,9 @@ __device__ __forceinline__ bool backward_chain(const RecArgs& a, const Ring<LOCA
           const float2 s = get(part, set, 0, 16 * rt + at.row, at.col);
           if (KIND == K_RNN) {
             const float2 t = un2<CH>(now.zw[rt][0]);
-            const float2 v = map2<CH>([&](int i) { return at2(s, i) * (a.dphi ? at2(t, i) : a.tanh_act ? 1.f - at2(t, i) * at2(t, i) : 1.f); });
+            const float2 v = map2<CH>([&](int i) {
+              return at2(s, i) * (a.dphi ? at2(t, i) : a.tanh_act ? 1.f - at2(t, i) * at2(t, i) : 1.f);
+            });
             publish(ring, ring.at(0, l, rt, member), at.on_f[rt] ? pk<CH>(v) : 0u);
           } else {
             const float2 r = un2<CH>(now.zw[rt][1]), xv = un2<CH>(now.xw[rt]);
@@ -870,7 +898,8 @@ __device__ __forceinline__ bool backward_chain(const RecArgs& a, const Ring<LOCA
 #pragma unroll
       for (int rt = 0; rt < TILES; ++rt) {
         const float2 s = get(part, set, 0, 16 * rt + at.row, at.col);
-        const float2 ev = un2<CH>(now.ew[rt]), lm = a.lambda_tok ? un2<CH>(now.lw[rt]) : KIND == K_RNN && a.lambda ? now.lmf[rt] : make_float2(1.f, 1.f);
+        const float2 ev = un2<CH>(now.ew[rt]);
+        const float2 lm = a.lambda_tok ? un2<CH>(now.lw[rt]) : KIND == K_RNN && a.lambda ? now.lmf[rt] : make_float2(1.f, 1.f);
         o[rt] = pk<CH>(map2<CH>([&](int i) { return (at2(s, i) + at2(past[rt], i) + at2(ev, i)) + at2(lm, i) * at2(gs[rt], i); }));
         if (KIND == K_RNN) publish(ring, ring.at(1, l, rt, member), at.on[rt] ? o[rt] : 0u);
         gs[rt] = un2<CH>(o[rt]);
@@ -994,7 +1023,7 @@ hipError_t launch_rec_kind(const RecArgs& a, bool forward, hipStream_t s) {
 // a tile, or twice REC_MAX_WG of a tile
 size_t recurrent_ring_bytes() { return (size_t)REC_UNITS * REC_SLOTS * REC_MAX_WG * 2 * 1024 * 2; }
 // What fits: bf16, widths whose weights the registers hold (1024) and at most 64 workgroups (two row tiles each: 64 rows at
-// width 1024, 128 at 512).  Everything else goes step by step (7 us per product against 1.6).
+// width 1024, 128 at 512).  Everything else goes step by step (7 us per product against 0.8 to 1.6).
 bool recurrent_ok(const RecArgs& a) {
   if (a.H % 8 || a.D % 8 || a.F % 8 || rec_width(a) > 1024 || rec_row_tiles(a) == 0) return false;
   if (a.N * a.F > (1L << 30) || a.N * a.D > (1L << 30)) return false;
