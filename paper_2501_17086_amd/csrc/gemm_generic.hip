@@ -131,6 +131,8 @@ __global__ __launch_bounds__(NT) void gemm_generic_kernel(GemmArgs g) {
   }
 }
 
+// Sum of the shares of a contraction, element by element: buffers that are not 16-byte aligned, which the interface asks for but the
+// kernels behind it do not need (gemm_generic_kernel takes such operands).
 __global__ void splitk_reduce_kernel(const float* __restrict__ part, float* __restrict__ out, long n, int split) {
   long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
   long stride = (long)gridDim.x * blockDim.x;
@@ -171,7 +173,7 @@ hipError_t launch_gemm_generic(int dtype, const GemmArgs& g, hipStream_t s) {
 
 hipError_t launch_splitk_reduce(const float* part, float* out, long n, int split, hipStream_t s) {
   if (n % 4 == 0 && (reinterpret_cast<uintptr_t>(part) & 15) == 0 && (reinterpret_cast<uintptr_t>(out) & 15) == 0 &&
-      n / 1024 < (1L << 30)) {
+      n < (1L << 33)) {                // (a grid of 2^31 threads)
     hipLaunchKernelGGL(splitk_reduce4_kernel, dim3((unsigned)((n / 4 + 255) / 256)), dim3(256), 0, s,
                        reinterpret_cast<const float4*>(part), reinterpret_cast<float4*>(out), n / 4, split);
     return hipGetLastError();

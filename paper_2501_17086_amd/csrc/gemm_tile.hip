@@ -428,7 +428,9 @@ hipError_t launch_pairing(const GemmArgs& g, hipStream_t s) {
   if (a_kc && b_kc)
     return g.mode == EPI_ACT_GELU || g.mode == EPI_ACT_TANH ? launch_one<T, BK, NST, WGS, true, true, true>(g, s)
                                                             : launch_one<T, BK, NST, WGS, true, true, false>(g, s);
-  return a_kc ? launch_one<T, BK, NST, WGS, true, false, false>(g, s) : launch_one<T, BK, NST, WGS, false, false, false>(g, s);
+  if (a_kc) return launch_one<T, BK, NST, WGS, true, false, false>(g, s);
+  if constexpr (WGS == 3) return hipErrorInvalidValue;     // (both operands with contiguous rows: two workgroups, below)
+  else return launch_one<T, BK, NST, WGS, false, false, false>(g, s);
 }
 
 template <int TM, int STG, bool A_KC, bool B_KC, bool ACT>
