@@ -343,13 +343,36 @@ def test_several_tiles_per_workgroup(B, N, d, d_ff, act):
     H.assert_close(H.to_np(p.g)[0], O.exact_backward(st, sv, inp["e"])[0], H.TOL["bf16"], f"{w.name} g[0]")
 
 
-# parameter gradients whose contraction is shared out unequally (193 slices of 32 in 3 shares, 258 in 4, 321 in 5),
-# and the sum of 3, 4 and 5 shares
+# parameter gradients whose contraction is shared out unequally (193 slices of 32 in 3 shares, 258 in 4, 321 in 5), on the
+# kernels of small tiles, and the sum of 3, 4 and 5 shares
 @pytest.mark.parametrize("L,N,d,d_ff", [(2, 6176, 256, 256), (2, 8256, 256, 512), (1, 10272, 512, 256)])
 def test_unequal_shares_of_a_contraction(B, L, N, d, d_ff):
     w = synth.scaled(W["resnet_like"], name=f"mlp_{N}_{d}_{d_ff}", L=L, N=N, d=d, d_ff=d_ff, w2_scale=0.7, ks=(1,))
     inp, st, sv, p = _forward_matches(B, w)
     _check_backward(B, w, p, st, sv, inp, w.name)
+
+
+# The same on the 256 x 256 kernel: 257 and 258 slices in 4 shares, 257 in 4 over 4 blocks and in 2 over 2 blocks that are taken one
+# at a time, 513 in 4 over 3 blocks (768 tiles, three for a workgroup).  Against 64-bit products of what the call read; dW2 is sums
+# of exact products, in 32 bits over 16416 tokens: 1e-5 (the root of their number times 2^-24 is 8e-6).
+@pytest.mark.parametrize("L,N,d,d_ff,shares", [(1, 8224, 1024, 4096, 4), (1, 8256, 1024, 4096, 4), (4, 8224, 512, 2048, 4),
+                                               (2, 8224, 1024, 4096, 2), (3, 16416, 1024, 4096, 4)])
+def test_unequal_shares_on_whole_tiles(B, L, N, d, d_ff, shares):
+    import torch
+    w = synth.scaled(W["resnet_like"], name=f"mlp_{L}_{N}_{d}_{d_ff}", L=L, N=N, d=d, d_ff=d_ff, w2_scale=0.7, ks=(1,))
+    inp = synth.make_inputs(w)
+    p = B.allocate(w, inp)
+    fewer = B.hbp_desc.from_buffer_copy(p.desc)
+    fewer.N = 2048                                   # (no shares: what is left of the workspace are the partial sums)
+    assert round((B.workspace_size(p.desc) - B.workspace_size(fewer) * N / 2048) / (L * d * d_ff * 4)) == shares
+    B.hbp_forward(p)
+    B.hbp_backward(p, 1)
+    B.hbp_param_grads(p)
+    for l in range(L):
+        g, W2 = p.g[l + 1].double(), p.W2[l].double()
+        H.assert_close(H.to_np(p.dW2)[l], (g.T @ p.z[l].double()).cpu().numpy(), 1e-5, f"{w.name} dW2[{l}]")
+        da = ((g @ W2) * p.dphi[l].double()).to(torch.bfloat16).double()
+        H.assert_close(H.to_np(p.dW1)[l], (da.T @ p.y[l].double()).cpu().numpy(), H.TOL["bf16"], f"{w.name} dW1[{l}]")
 
 
 # the scan of rows with a norm: widths around the chunks of 512 (a last chunk of one vector, of all but one, none), one to nine
