@@ -978,17 +978,24 @@ hipError_t launch_scan_t(const ScanArgs& args, hipStream_t s) {
       return hipGetLastError();
     }
     // The pipelined form: whole chunks of 512, and from four layers on ragged widths where its kernel is the faster one.  Up to
-    // 1024 channels that is a matter of few rows (a layer of 4 MB, 8192 rows in bf16 and 4096 in fp32): three layers' loads ahead
-    // take the registers of three wavefronts, and with many rows others would run in their place.  Measured, scans of two iterations
-    // over 12 layers, us, unpipelined / this form: bf16 1000 x 328 45 / 32, 6000 x 256 65 / 59, 4096 x 504 70 / 67, 8192 x 504 132 / 155,
-    // 32768 x 128 259 / 260 (with coefficients of 1: 224 / 190), 8192 x 768 259 / 224, 32768 x 1000 1214 / 1241; fp32 4096 x 128 60 / 53,
-    // 16384 x 128 184 / 207, 2048 x 504 72 / 67, 4096 x 504 130 / 146, 1000 x 1000 74 / 68, 3000 x 1000 199 / 206.  Rows of 512 channels,
-    // at most 4096 of them, take the same kernel (two stages / this form, bf16 1000 rows 42 / 32, fp32 3000 122 / 91), of 1024 not
-    // (fp32 1000 rows 65 / 68, bf16 4096 0.93 to 1.0 times).
+    // 1024 channels that is a matter of few rows (a layer of 4 MB, 6144 rows in bf16 and 4096 in fp32): three layers' loads ahead
+    // take the registers of three wavefronts, and with many rows others would run in their place.  bf16 with more: rows above 512
+    // channels; up to 256 for 12288 rows; up to 224, or 192 with coefficients to read, for any number.  With coefficients that is so
+    // over eight layers or more (the bottom layer is read three times more), else from 8193 to 12288 rows.  Measured, scans of two
+    // iterations over 12 layers (or 5: *), us, unpipelined / this form: bf16 1000 x 328 45 / 32, 6000 x 256 65 / 58, 4096 x 504 70 / 67, 8192
+    // x 504 132 / 155, 8192 x 768 259 / 224, 32768 x 1000 1214 / 1241, 24000 x 192 204 / 196, *8192 x 128 1.07 times, *11000 x 192 52 / 49,
+    // *24000 x 192 1.05 times (coefficients of 1: 11000 x 256 94 / 84, *24000 x 128 68 / 59); fp32 4096 x 128 60 / 53, 16384 x 128 184 /
+    // 207, 2048 x 504 72 / 67, 4096 x 504 130 / 146, 1000 x 1000 74 / 68, 3000 x 1000 199 / 206.  Rows of 512 channels, at most 4096 of
+    // them, take the same kernel (two stages / this form, bf16 1000 rows 42 / 32, fp32 3000 122 / 91), of 1024 not (fp32 1000 rows 65 /
+    // 68, bf16 4096 0.93 to 1.0 times).
     constexpr long es = sizeof(T);
-    const bool whole = a.d % 512 == 0, four = a.l_hi - a.l_lo >= 4;
-    const bool few = a.N * a.d * es <= (4L << 20) && a.N * es <= 16384;
-    const bool ragged = whole ? four && nch == 1 && a.N <= 4096 : four && (nch > 2 || few || (es == 2 && (nch == 2 || a.d <= 128)));
+    const long layers = a.l_hi - a.l_lo;
+    const bool whole = a.d % 512 == 0;
+    const bool few = a.N * a.d * es <= (4L << 20) && a.N <= (es == 2 ? 6144 : 4096);
+    const bool deep = !a.lambda || layers >= 8;
+    const bool many = es == 2 && a.N > 6144 &&
+                      ((a.d <= 256 && a.N <= 12288 && (deep || a.N > 8192)) || (deep && a.d <= (a.lambda ? 192 : 224)));
+    const bool ragged = layers >= 4 && (whole ? nch == 1 && a.N <= 4096 : nch > 2 || few || (nch == 1 ? many : es == 2));
     if (nch <= 4 && !a.mask && !a.lambda_tok && (whole || ragged)) {
 #define HBP_ROWS_PIPE_AS(N_, R_)                                                                                        \
       do {                                                                                                              \
