@@ -657,10 +657,13 @@ hipError_t launch_lean(const GemmArgs& g, hipStream_t s) {
 // The smallest launches: the smaller tiles, whose wavefronts share the contraction, as long as every compute unit has at most
 // one.  Measured, 64 x 64 / 64 x 32 / 32 x 32: 1000 x 328 x 1304 (176 tiles of 64 x 32, 352 of 32 x 32) 10.2 / 8.2 / 10.6 us,
 // 512 x 768 x 3072 (192, 384) 15.9 / 11.9 / 16.0, 1024 x 256 x 1200 (128, 256) 8.3 / 7.9 / 6.6, 100 x 512 x 2048 (32, 64)
-// 12.5 / 7.6 / 6.3; beyond: 600 x 1000 x 4000 (320, 608) 21.9 / 26.8 / 25.7, 1200 x 768 x 256 (456, 912) 4.7 / 6.8 / 10.1.
+// 12.5 / 7.6 / 6.3; not for a handful of rows and columns over one slice, which has nothing to share out (exact backpropagation of 6
+// blocks of 8 x 64 x 64 44.3 / - / 48.8 us, of 30 rows 47.6 / - / 49.9; their forward 37.3 / - / 39.9 and 43.6 / - / 40.3, of 3 x 16 x
+// 256 47.5 / - / 41.0); beyond: 600 x 1000 x 4000 (320, 608) 21.9 / 26.8 / 25.7, 1200 x 768 x 256 (456, 912) 4.7 / 6.8 / 10.1.
 inline hipError_t launch_tile_for(const GemmArgs& g, hipStream_t s) {
   auto tiles = [&g](long tm, long tn) { return (g.M + tm - 1) / tm * ((g.N + tn - 1) / tn) * g.batch * g.split_k; };
   if (tiles(128, 128) >= 192) return launch_gemm_tile(g, 128, 128, s);
+  if (g.M <= 16 && g.N <= 64 && g.K <= 64) return launch_gemm_tile(g, 64, 64, s);
   if (tiles(32, 32) <= 256) return launch_gemm_tile(g, 32, 32, s);
   return tiles(64, 32) <= 256 ? launch_gemm_tile(g, 64, 32, s) : launch_gemm_tile(g, 64, 64, s);
 }
