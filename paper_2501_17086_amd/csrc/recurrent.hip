@@ -62,6 +62,9 @@ constexpr int REC_ARRIVE_POLLS = 256;          // polls per step for the rest of
 constexpr unsigned REC_ALONE = 1u << 31;       // in a group's word beside the number of workgroups that have started
 // times 64 cycles (1024 steps of the RNN and of the GRU: 3: 2.18 and 4.00 ms, 4: 2.06 and 4.01, 7: 2.22 and 4.00)
 constexpr int REC_PAUSE = 4;
+// the same where a forward pass with two products per step exchanges through memory (11 steps of 32 x 1024, 0 / 4 / 8 / 12: RNN 56.7,
+// 47.8, 42.4, 42.8 us, GRU 57.2, 54.9, 51.2, 52.5)
+constexpr int REC_PAUSE_FAR = 8;
 // Steps from which groups on one XCD pay for their launch.  Groups anywhere / on one XCD, us, 8 steps of 32 x 1024: RNN 39.8 / 38.3,
 // LSTM 35.4 / 36.8; 12 steps, forward: RNN 50.4 / 40.6, gated cell 41.0 / 39.2, LSTM 60.9 / 57.2, GRU 57.9 / 50.5; 1 x 64: 29.9 / 25.2,
 // 23.8 / 24.2, 32.3 / 29.4, 32.4 / 29.6; backwards 54.0 / 46.2, 47.4 / 39.8, 65.8 / 55.5, 57.3 / 50.8.
@@ -168,9 +171,9 @@ struct Operand {
   }
   // The first time after a short pause: what the other workgroups publish at the same time as this one takes about that long to
   // be seen, and operands read too early are read twice.
-  template <bool LOCAL, bool AGAIN = false>
+  template <int PAUSE = REC_PAUSE, bool LOCAL>
   __device__ __forceinline__ void ask(const Ring<LOCAL, RT>& ring, int u, long step) {
-    if (!AGAIN) __builtin_amdgcn_s_sleep(REC_PAUSE);
+    if (PAUSE) __builtin_amdgcn_s_sleep(PAUSE);
     asm volatile("" ::: "memory");             // (every pass reads again)
 #pragma unroll
     for (int s = 0; s < LOADS; ++s)
@@ -201,7 +204,7 @@ struct Operand {
     int spins = 0;
     do {
       if (++spins >= REC_SPIN_LIMIT) dead = true;
-      ask<LOCAL, true>(ring, u, step);
+      ask<0>(ring, u, step);
     } while (missing() && !dead);
   }
 };
@@ -441,6 +444,9 @@ __device__ __forceinline__ bool forward_chain(const RecArgs& a, const Ring<LOCAL
                                               Partials<RT, SLOTS>& part) {
   constexpr int UNITS = KIND == K_LSTM ? 4 : KIND == K_GRU ? 3 : 2;
   constexpr bool TWO = KIND == K_RNN || KIND == K_GRU;       // two dependent products per step
+  // one product: a step's inputs are read two steps ahead, or (through memory, but for the LSTM with two row tiles) just before
+  constexpr bool AHEAD = !TWO && (LOCAL || (KIND == K_LSTM && RT == 2));
+  constexpr int PAUSE = LOCAL || !TWO ? REC_PAUSE : REC_PAUSE_FAR;
   constexpr int TILES = rec_tiles<RT>(), CH = rec_channels<RT>();
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -478,7 +484,7 @@ __device__ __forceinline__ bool forward_chain(const RecArgs& a, const Ring<LOCAL
 #pragma unroll
     for (int rt = 0; rt < TILES; ++rt) publish(ring, ring.at(0, 0, rt, member), bld2(x.buf(), at.x2[rt], KIND == K_LSTM ? h2 : 0));
   });
-  if (!ALONE) in.ask(ring, 0, 0);
+  if (!ALONE && (AHEAD || TWO)) in.template ask<PAUSE>(ring, 0, 0);
   bool dead = false;
   int set = 0;
   // what a step takes besides the state before it
@@ -499,7 +505,12 @@ __device__ __forceinline__ bool forward_chain(const RecArgs& a, const Ring<LOCAL
   // the step to be read becomes the next one, or stays the last one
   auto advance = [&](bool more) __attribute__((always_inline)) { ux.next(more); lc.next(more); lt.next(more); };
   Inputs now, next;
-  if (!ALONE) { read_step(now); advance(a.L > 1); if (!TWO) { read_step(next); advance(a.L > 2); } }
+  if (!ALONE) {
+    read_step(now);
+    advance(a.L > 1);
+    if (AHEAD) { read_step(next); advance(a.L > 2); }
+    if (!AHEAD && !TWO) in.template ask<PAUSE>(ring, 0, 0);
+  }
 #pragma unroll 1
   for (long l = 0; l < a.L; ++l) {
     const __amdgpu_buffer_rsrc_t zb = z.buf(), lb = lam.buf();
@@ -517,6 +528,13 @@ __device__ __forceinline__ bool forward_chain(const RecArgs& a, const Ring<LOCAL
         put(part, set, u, acc, wave, lane);
       }
       meet();
+      // every workgroup of the group has left step l - 1 (before the first step: slots that are empty yet).  To memory, the stores
+      // are on their way before the elementwise part: the operands asked for after them return after them.
+      auto empty_all = [&]() __attribute__((always_inline)) {
+        empty(ring, 0, l - 1, member);
+        if (TWO) empty(ring, 1, l - 1, member);
+      };
+      if (!LOCAL) empty_all();
       unsigned zw[TILES], rw[TILES], ow[TILES], cw[TILES], gw[TILES], aw[TILES], hw[TILES];     // what the phase leaves, packed
 #pragma unroll
       for (int rt = 0; rt < TILES; ++rt) {
@@ -587,20 +605,23 @@ __device__ __forceinline__ bool forward_chain(const RecArgs& a, const Ring<LOCAL
         }
       }
       };
-      if (KIND == K_RNN) results();
-      // every workgroup of the group has left step l - 1 (before the first step: slots that are empty yet)
-      empty(ring, 0, l - 1, member);
-      if (TWO) empty(ring, 1, l - 1, member);
+      constexpr bool RESULTS_FIRST = KIND == K_RNN || (!AHEAD && !TWO);
+      if (RESULTS_FIRST) results();
+      if (LOCAL) empty_all();
       if (!ALONE) {
-        if (TWO) in.ask(ring, 1, l);
-        else {
+        if (TWO) in.template ask<PAUSE>(ring, 1, l);
+        else if (AHEAD) {
           in.ask(ring, 0, l + 1);
           now = next;
           read_step(next);
           advance(l + 3 < a.L);
+        } else {                 // (through memory: the inputs' trip is part of the wait for the others' words)
+          read_step(now);
+          advance(l + 2 < a.L);
+          in.template ask<PAUSE>(ring, 0, l + 1);
         }
       }
-      if (KIND != K_RNN) results();
+      if (!RESULTS_FIRST) results();
       set ^= 1;
     });
     if (TWO) {
@@ -645,7 +666,7 @@ __device__ __forceinline__ bool forward_chain(const RecArgs& a, const Ring<LOCAL
             bst2(aw[rt], lb, at.xs[rt]);
           }
         }
-        if (!ALONE) in.ask(ring, 0, l + 1);
+        if (!ALONE) in.template ask<PAUSE>(ring, 0, l + 1);
         if (!ALONE) now = next;
         set ^= 1;
       });
@@ -984,8 +1005,8 @@ hipError_t launch_rec(const RecArgs& a, bool forward, hipStream_t s) {
   const int groups = (int)((a.N + rec_rows<RT>() - 1) / rec_rows<RT>()), locals = (int)((a.N + rec_rows<RTL>() - 1) / rec_rows<RTL>());
   const long ring = (long)REC_UNITS * REC_SLOTS * groups * RT * wpg * 1024;
   const long ring_local = (long)REC_UNITS * REC_SLOTS * locals * (RTL ? wpg : (wpg + 1) / 2) * 1024;
-  const long n16 = (ring + ring_local) / 16;
   const bool on_xcd = (a.wait & 255) == REC_ON_XCD, local = on_xcd || (a.wait == REC_WAIT && a.L >= REC_LOCAL_FROM);
+  const long n16 = (ring + (local ? ring_local : 0)) / 16;
   hipLaunchKernelGGL(rec_fill_kernel, dim3((unsigned)((n16 + 255) / 256)), dim3(256), 0, s, reinterpret_cast<uint4*>(a.ring), n16,
                      reinterpret_cast<PlaceWords*>(a.counter), a.wait == REC_ALONE_ANYHOW ? REC_ALONE : 0u,
                      on_xcd ? (unsigned)a.wait >> 8 : 0u);
