@@ -38,10 +38,13 @@
  *    d > 4096 with HBP_NORM_RMS, k < 0, a required pointer that is NULL, a
  *    workspace smaller than hbp_workspace_size() reports.  A failed launch
  *    gives HBP_E_DEVICE.
- *  - The recurrent kinds' forward pass and exact backpropagation run a whole chain in one launch (bf16, no norm, widths
- *    up to 1024, batches of up to 64 rows at that width): at most 64 workgroups, of which up to 32 wait for each other's
- *    results.  Any number of such calls may overlap.  Where 32 workgroups do not get to run side by side for a long time
- *    (other work holds the GPU), one of them computes the chain alone: the same results, at 0.1 to 0.4 ms a step.
+ *  - The recurrent kinds' forward pass and exact backpropagation run a whole chain in one or two launches (bf16, no norm,
+ *    widths up to 1024, batches of up to 64 rows at that width), whose workgroups wait for each other's results, up to 32 at
+ *    a time.  From 12 steps on up to 256 workgroups run, one per compute unit (64 rows of width 1024; 32 rows: 128): what
+ *    other streams have enqueued meanwhile waits for them.  Any number of such calls may overlap; three or more wide ones
+ *    mostly take turns.  Where the workgroups do not get to run side by side (other work holds the GPU), a second launch
+ *    of at most 64 workgroups takes what is left, and where 32 of those do not for a long time, one of them computes the
+ *    chain alone: the same results, at 0.1 to 0.4 ms a step.
  *  - State between calls: none that changes results.  The library keeps (a) a
  *    flag per kernel and device saying that the kernel's shared-memory limit
  *    has been raised (set on the first launch, idempotent, safe from several
