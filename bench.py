@@ -37,23 +37,23 @@ PEAK_HBM_GBS = 8000.0
 # report null.
 MEASURED_TRAFFIC = {
     "deep_large": {"source": "profiles/bench_deep_large_hbm_traffic.txt",
-                   "vjp1": 1.655e11, "vjp2": 8.332e10, "dw": 2.040e11, "scan": 1.546e10},
+                   "vjp1": 1.607e11, "vjp2": 8.449e10, "dw": 1.059e11, "scan": 1.542e10},
     "transformer_mlp": {"source": "profiles/bench_transformer_mlp_hbm_traffic.txt",
-                        "vjp1": 2.997e10, "vjp2": 1.118e10, "dw": 1.627e10, "scan": 3.826e9},
+                        "vjp1": 3.050e10, "vjp2": 1.119e10, "dw": 1.048e10, "scan": 3.827e9},
     "resnet_like": {"source": "profiles/bench_resnet_like_hbm_traffic.txt",
-                    "vjp1": 2.819e9, "vjp2": 1.609e9, "dw": 1.479e9, "scan": 6.508e8},
+                    "vjp1": 2.856e9, "vjp2": 1.610e9, "dw": 1.476e9, "scan": 6.513e8},
     "postnorm_mlp": {"source": "profiles/bench_postnorm_mlp_hbm_traffic.txt",
-                     "vjp1": 6.456e9, "vjp2": 2.760e9, "dw": 2.845e9, "scan": 1.149e9},
+                     "vjp1": 6.364e9, "vjp2": 2.760e9, "dw": 2.819e9, "scan": 1.149e9},
     "gated_rnn": {"source": "profiles/bench_gated_rnn_hbm_traffic.txt",
-                  "vjp1": 9.724e8, "vjp2": 9.398e8, "dw": 6.041e8, "scan": 6.409e8},
+                  "vjp1": 9.602e8, "vjp2": 9.397e8, "dw": 6.041e8, "scan": 6.446e8},
     "gpt2_paper": {"source": "profiles/bench_gpt2_paper_hbm_traffic.txt",
-                   "vjp1": 1.771e9, "vjp2": 6.923e8, "dw": 8.928e8, "attn": 1.618e9, "scan": 1.247e9},
+                   "vjp1": 1.772e9, "vjp2": 6.923e8, "dw": 8.759e8, "attn": 1.618e9, "scan": 1.247e9},
     "roberta_like": {"source": "profiles/bench_roberta_like_hbm_traffic.txt",
-                     "vjp1": 9.129e8, "vjp2": 4.291e8, "dw": 5.584e8, "attn": 6.071e8, "scan": 5.377e8},
+                     "vjp1": 9.180e8, "vjp2": 4.293e8, "dw": 5.223e8, "attn": 6.068e8, "scan": 5.377e8},
     "transformer_attn": {"source": "profiles/bench_transformer_attn_hbm_traffic.txt",
-                         "vjp1": 6.183e9, "vjp2": 1.835e9, "dw": 2.167e9, "attn": 3.897e9, "scan": 2.469e9},
+                         "vjp1": 6.214e9, "vjp2": 1.836e9, "dw": 2.177e9, "attn": 3.896e9, "scan": 2.469e9},
     "lstm_cell": {"source": "profiles/bench_lstm_cell_hbm_traffic.txt",
-                  "vjp1": 3.491e9, "vjp2": 2.148e9, "dw": 1.810e9, "scan": 1.702e9},
+                  "vjp1": 3.491e9, "vjp2": 2.148e9, "dw": 1.735e9, "scan": 1.702e9},
 }
 
 
