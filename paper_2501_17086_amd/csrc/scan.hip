@@ -92,6 +92,133 @@ __global__ __launch_bounds__(256) void scan_vec_kernel(ScanArgs a) {
   }
 }
 
+// The scan without a norm, its states shared out inside a workgroup: a thread per vector of channels alone walks a chain at 0.4 to 0.7 us
+// a state, most of the chip idle.  A workgroup owns 64 channels (of the flattened tokens: 128 bytes of a bf16 state) and takes SEG_N
+// segments of S states at a time, from the top down.  A segment's 8 lanes ask for all of its operands, reduce them to the segment's
+// map g_bottom = B + A (.) g_top, one wavefront walks the maps (a lane per channel), and every segment runs its recurrence from the
+// state entering it over the operands still in registers; the next segments' operands are on their way meanwhile.  Every element is
+// read once and written once, nothing crosses workgroups.  Latency bounds the small calls (2.2 us a launch at least), memory the
+// large ones: 4096 states of 32 x 1024 in bf16 132 us with coefficients per channel (4.2 TB/s), 170 with them per token (4.7); by
+// chunks handed from workgroup to workgroup (scan_sp_kernel) 158 and 184, 1024 states 42 -> 25 and 56 -> 32.
+// LAMK: 0 coefficients 1; 1 per channel (fp32 [L,d]); 2 per token.  NSRC: of dn and e how many there are.
+constexpr int SEG_CH = 64;
+template <typename T, int LAMK, int NSRC, int S, int SEG_N>
+__global__ __launch_bounds__(8 * SEG_N) void scan_seg_kernel(ScanArgs a) {
+  __shared__ __attribute__((aligned(16))) float map_a[SEG_N][SEG_CH], map_b[SEG_N][SEG_CH];
+  const int tid = threadIdx.x, lane8 = tid & 7, seg = tid >> 3;
+  const long layer = a.N * a.d;
+  const bool valid = (long)blockIdx.x * SEG_CH + lane8 * 8 < layer;
+  const long off = valid ? (long)blockIdx.x * SEG_CH + lane8 * 8 : layer - 8;      // (lanes past the end: the last vector, not stored)
+  const long c0 = off % a.d;
+  T* g = reinterpret_cast<T*>(a.g);
+  const T* src = reinterpret_cast<const T*>(a.dn ? a.dn : a.e);
+  const T* src2 = reinterpret_cast<const T*>(a.e);
+  const T* tok = reinterpret_cast<const T*>(a.lambda_tok);
+  const float rs = a.res_scale;
+  float walk = 0.f;                        // threads 0 .. 63: the channel's state above the segments to come
+  {
+    const long ch = (long)blockIdx.x * SEG_CH + tid;
+    const T* above = a.top ? reinterpret_cast<const T*>(a.top) : g + a.l_hi * layer;
+    if (tid < SEG_CH && ch < layer) walk = Elem<T>::load(above + ch);
+    if (a.top && seg == 0 && valid) {
+      float t[8];
+      load8(reinterpret_cast<const T*>(a.top) + off, t);
+      store8(g + a.l_hi * layer + off, t);
+    }
+  }
+  struct Raw {
+    Raw8<T> v[NSRC > 0 ? S : 1], v2[NSRC > 1 ? S : 1], tok[LAMK == 2 ? S : 1];
+    Raw8<float> lam[LAMK == 1 ? S : 1];
+  };
+  auto ask = [&](Raw& r, long l0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      const long l = l0 - s > a.l_lo ? l0 - s : a.l_lo;
+      if (NSRC > 0) r.v[NSRC > 0 ? s : 0].load(src + l * layer + off);
+      if (NSRC > 1) r.v2[NSRC > 1 ? s : 0].load(src2 + l * layer + off);
+      if (LAMK == 2) r.tok[LAMK == 2 ? s : 0].load(tok + l * layer + off);
+      if (LAMK == 1) r.lam[LAMK == 1 ? s : 0].load(a.lambda + l * a.d + c0);
+    }
+  };
+  // the wavefronts' words are in LDS (loads from memory stay in flight across it)
+  auto meet = [&]() __attribute__((always_inline)) {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0xC07F);
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  };
+  // the segment's states: l0, l0 - 1, .. l0 - S + 1; `next` is asked for ahead
+  auto block = [&](Raw& r, Raw& next, long l0) __attribute__((always_inline)) {
+    auto operands = [&](int s, float (&lam)[8], float (&v)[8]) __attribute__((always_inline)) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) { lam[i] = 1.f; v[i] = 0.f; }
+      if (LAMK == 2) r.tok[LAMK == 2 ? s : 0].unpack(lam);
+      if (LAMK == 1) r.lam[LAMK == 1 ? s : 0].unpack(lam);
+      if (NSRC > 0) r.v[NSRC > 0 ? s : 0].unpack(v);
+      if (NSRC > 1) {
+        float t[8];
+        r.v2[NSRC > 1 ? s : 0].unpack(t);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] += t[i];
+      }
+#pragma unroll
+      for (int i = 0; i < 8; ++i) lam[i] *= rs;
+    };
+    float A[8], B[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) { A[i] = 1.f; B[i] = 0.f; }
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      float lam[8], v[8];
+      operands(s, lam, v);
+      const bool on = l0 - s >= a.l_lo;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        B[i] = on ? fmaf(lam[i], B[i], v[i]) : B[i];
+        A[i] = on ? A[i] * lam[i] : A[i];
+      }
+    }
+    store8(&map_a[seg][lane8 * 8], A);
+    store8(&map_b[seg][lane8 * 8], B);
+    ask(next, l0 - SEG_N * S);
+    meet();
+    if (tid < SEG_CH) {                    // map_b[j] becomes the state entering segment j
+#pragma unroll
+      for (int j0 = 0; j0 < SEG_N; j0 += 8) {
+        float ma[8], mb[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) { ma[j] = map_a[j0 + j][tid]; mb[j] = map_b[j0 + j][tid]; }
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          map_b[j0 + j][tid] = walk;
+          walk = fmaf(ma[j], walk, mb[j]);
+        }
+      }
+    }
+    meet();
+    float carry[8];                        // (a thread rewrites of the maps what it has read here, the walker after a meeting)
+    load8(&map_b[seg][lane8 * 8], carry);
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      float lam[8], v[8];
+      operands(s, lam, v);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) carry[i] = fmaf(lam[i], carry[i], v[i]);
+      if (valid && l0 - s >= a.l_lo) store8(g + (l0 - s) * layer + off, carry);
+    }
+  };
+  Raw r0, r1;
+  long top = a.l_hi;
+  ask(r0, top - 1 - seg * S);
+#pragma unroll 1
+  while (true) {
+    block(r0, r1, top - 1 - seg * S);
+    if ((top -= SEG_N * S) <= a.l_lo) break;
+    block(r1, r0, top - 1 - seg * S);
+    if ((top -= SEG_N * S) <= a.l_lo) break;
+  }
+}
+
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
@@ -928,10 +1055,56 @@ hipError_t launch_scan_sp(const ScanArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
+// what the form with the states shared out inside a workgroup covers
+inline bool seg_covers(const ScanArgs& a) {
+  return a.blk_gamma == 0.f && !a.mask && !(a.norm_rms && a.dn);
+}
+// ... and where it is the faster one: up to half a million elements a state, fewer below 16 states.  Measured, us, the form before (a
+// thread per vector up to 255 states, from 256 on chunks) / this one, bf16 with a value stream: 2 states of 100 x 128 2.7 / 2.2, of 1000
+// x 512 3.1 / 5.1; 8 of 100 x 128 5.6 / 2.3, of 500 x 512 6.0 / 4.1; 12 of 1000 x 512 9.1 / 7.8 (without a stream 7.0 / 7.2); 24 of 1000 x
+// 512 17.3 / 12.1 (11.1 / 10.2); 100 of 32 x 512 70 / 5; 300 of 64 x 1024 63 / 16; beyond: 24 of 2000 x 512 22 / 20, 32 of 8192 x 512 129 / 144,
+// 12 of 16384 x 1024 166 / 218, 300 of 1024 x 1024 332 / 347.
+inline bool seg_pays(const ScanArgs& a) {
+  const long L = a.l_hi - a.l_lo;
+  return L >= 2 && a.N * a.d <= (L < 16 ? 32768 * L : 1L << 19);
+}
+template <typename T, int LAMK, int NSRC, int S, int SEG_N>
+hipError_t launch_seg_as(const ScanArgs& a, hipStream_t s) {
+  const dim3 grid((unsigned)((a.N * a.d + SEG_CH - 1) / SEG_CH)), block(8 * SEG_N);
+  hipLaunchKernelGGL((scan_seg_kernel<T, LAMK, NSRC, S, SEG_N>), grid, block, 0, s, a);
+  return hipGetLastError();
+}
+template <typename T, int S, int SEG_N>
+hipError_t launch_seg(const ScanArgs& a, hipStream_t s) {
+  const int nsrc = (a.dn ? 1 : 0) + (a.e ? 1 : 0), lamk = a.lambda_tok ? 2 : a.lambda ? 1 : 0;
+  switch (3 * lamk + nsrc) {
+    case 0: return launch_seg_as<T, 0, 0, S, SEG_N>(a, s);
+    case 1: return launch_seg_as<T, 0, 1, S, SEG_N>(a, s);
+    case 2: return launch_seg_as<T, 0, 2, S, SEG_N>(a, s);
+    case 3: return launch_seg_as<T, 1, 0, S, SEG_N>(a, s);
+    case 4: return launch_seg_as<T, 1, 1, S, SEG_N>(a, s);
+    case 5: return launch_seg_as<T, 1, 2, S, SEG_N>(a, s);
+    case 6: return launch_seg_as<T, 2, 0, S, SEG_N>(a, s);
+    case 7: return launch_seg_as<T, 2, 1, S, SEG_N>(a, s);
+    default: return launch_seg_as<T, 2, 2, S, SEG_N>(a, s);
+  }
+}
+// As many segments at a time as keep their walk short beside the rest: 8 of one state for 8 states, 8 of two for up to 32 or above
+// 65536 elements, else 32 of two; 64 of four for the fewest chains.  Measured, us, 8 x 1 / 8 x 2 / 32 x 2 / 64 x 4: 8 states of 1000 x 512
+// 5.8 / 7.2 / 18.5 / -, 24 of 64 x 512 3.5 / 3.3 / 3.4 / -, of 256 x 512 5.1 / 4.9 / 7.1 / -, 100 of 64 x 512 8.9 / 7.0 / 5.2 / 8.6, of 256 x 1024
+// 22 / 19 / 23 / 54, 1024 of 32 x 200 59 / 39 / 18.4 / 12.9, of 32 x 600 65 / 46 / 25 / 27.
+template <typename T>
+hipError_t launch_seg_for(const ScanArgs& a, hipStream_t s) {
+  const long L = a.l_hi - a.l_lo, n = a.N * a.d;
+  if (L <= 8) return launch_seg<T, 1, 8>(a, s);
+  if (L <= 32 || n > 65536) return launch_seg<T, 2, 8>(a, s);
+  return L > 256 && n <= 12288 ? launch_seg<T, 4, 64>(a, s) : launch_seg<T, 2, 32>(a, s);
+}
+
 template <typename T>
 hipError_t launch_scan_t(const ScanArgs& args, hipStream_t s) {
   ScanArgs a = args;
-  // only the walk without a norm reads the top state itself; the other forms find it in g
+  // the walk without a norm and the form with the states shared out read the top state themselves; the others find it in g
   auto seed = [&]() -> hipError_t {
     const void* top = a.top;
     a.top = nullptr;
@@ -953,6 +1126,7 @@ hipError_t launch_scan_t(const ScanArgs& args, hipStream_t s) {
     e = seed();
     return e == hipSuccess ? launch_scan_chunked<T>(a, s) : e;
   }
+  if (a.force == 0 && seg_covers(a) && seg_pays(a)) return launch_seg_for<T>(a, s);
   if (a.force == 0 && !a.mask && a.chunk_ws && use_chunked(a.l_hi - a.l_lo, a.N, a.d, rms)) {
     e = seed();
     if (e != hipSuccess) return e;

@@ -411,3 +411,38 @@ def test_row_norms(B, d, N, post):
     H.assert_close(H.to_np(p.rinv), sv["rpost" if post == "rms" else "rinv"], H.TOL["bf16"], f"{w.name} rinv")
     if post == "none":
         H.assert_close(H.to_np(p.y), sv["y"], H.TOL["bf16"], f"{w.name} y")
+
+
+# the scan of w^0 where its states are shared out inside a workgroup: chains around a segment, a block of segments and two of them
+# (8 of one state, 8 of two, 32 of two, 64 of four), 64-channel slabs that end inside, and the first sizes that keep other forms
+@pytest.mark.parametrize("L,N,d", [(1, 3, 40), (2, 1, 8), (8, 9, 40), (9, 5, 56), (16, 3, 8), (17, 7, 72), (31, 129, 520), (7, 300, 720), (7, 320, 720), (33, 9, 40),
+                                   (64, 3, 104), (65, 20, 200), (130, 64, 512), (257, 33, 2048), (256, 3, 72), (257, 5, 8),
+                                   (513, 2, 136), (1100, 1, 64), (40, 513, 1024), (20, 1030, 1024)])
+@pytest.mark.parametrize("dtype,lam,every,gamma", [("bf16", "token", True, 0.0), ("bf16", "channel", True, 0.3),
+                                                   ("bf16", "one", False, 0.02), ("f32", "channel", False, 0.0),
+                                                   ("f32", "token", True, 0.0), ("f32", "one", True, 0.1)])
+def test_scan_with_its_states_shared_out(B, L, N, d, dtype, lam, every, gamma):
+    import torch
+    if L * N * d > (1 << 24) and (dtype == "f32" or lam == "one"):
+        pytest.skip("the large sizes in bf16 with coefficients only: the oracle takes the time")
+    st = torch.bfloat16 if dtype == "bf16" else torch.float32
+    gen = torch.Generator().manual_seed(L + N + d)
+    lo = 0.6 if every else 0.97                    # (without a source a thousand coefficients leave something)
+    rand = lambda *s: torch.rand(s, generator=gen) * (1 - lo) + lo
+    e = torch.randn((L + 1, N, d) if every else (N, d), generator=gen).to(st)
+    lm = {"token": lambda: rand(L, N, d).to(st), "channel": lambda: rand(L, d), "one": lambda: None}[lam]()
+    desc = B.make_desc("rnn", dtype, "tanh", "none", L, N, d, 8, 8, lambda_channel=lam == "channel", lambda_token=lam == "token",
+                       loss_every_state=every, gamma=gamma)
+    z = lambda *s: torch.zeros(s, dtype=st, device="cuda")
+    p = B.Problem(desc=desc, W1=z(8, d), W2=z(d, 8), U=z(8, 8), lam=None if lm is None else lm.cuda(), xin=None, e=e.cuda(),
+                  g=torch.full((L + 1, N, d), float("nan"), dtype=st, device="cuda"))
+    p.workspace = torch.zeros(B.workspace_size(desc), dtype=torch.uint8, device="cuda")
+    B.hbp_initial_estimate(p, "auto")
+    torch.cuda.synchronize()
+    a = np.zeros((L + 1, N, d))
+    a[:] = e.double().numpy() if every else 0
+    a[L] = e[L].double().numpy() if every else e.double().numpy()
+    rows = [(1 - gamma) * (np.ones((1, d)) if lm is None else lm[l].double().numpy()) for l in range(L)]
+    want = O.cumsumprod_reverse(a, lambda l: rows[l])
+    for l in range(L + 1):
+        H.assert_close(H.to_np(p.g)[l], want[l], H.TOL[dtype], f"state {l}")
