@@ -277,6 +277,13 @@ template <int N>
 __device__ __forceinline__ void copies_in_flight() {
   __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
 }
+// ... and no LDS read either: the buffer that the next copies go to has been read
+template <int N>
+__device__ __forceinline__ void copies_in_flight_read() {
+  __builtin_amdgcn_s_waitcnt(0x0070 | (N & 15) | ((N >> 4) << 14));
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
 // A value loaded from memory before the loop is made to arrive here.  Without this the compiler places its own counted
 // waits for such loads at their first use inside the loop, and since it does not know of the direct copies, those
 // waits would also drain the copies that were just issued for three steps ahead, on every step.
@@ -460,9 +467,43 @@ __device__ __forceinline__ BlockOf block_of(const AttnArgs& a, int nblk) {
 }
 // grids from about four rounds of resident workgroups per XCD on: problem by problem
 constexpr long BY_PROBLEM_FROM = 4 * 1024;
-inline long attn_grid(const AttnArgs& a) {
-  const long P = a.seqs * a.heads, nblk = ((a.T + 31) / 32 + AT_WAVES - 1) / AT_WAVES;
+inline long attn_grid(const AttnArgs& a, bool shared = false) {
+  const long P = a.seqs * a.heads, nt = (a.T + 31) / 32, nblk = shared ? nt : (nt + AT_WAVES - 1) / AT_WAVES;
   return 8 * ((P + 7) / 8) * nblk;
+}
+
+// Few problems (SHARED): a workgroup takes ONE tile of 32 queries (keys) and its four wavefronts share the tiles of the other side
+// out, every fourth each, through rings of their own: no barrier in the loop, a quarter of its steps, four times the workgroups.
+// Their results, the sums of the second products (and in the forward pass the rows' maxima and sums), meet in LDS at the end.
+// Every workgroup streams for 32 rows then, not 128.
+template <int DHP, bool SHARED> constexpr int ring_stages() { return !SHARED ? AT_NST : DHP == 128 ? 2 : 3; }
+template <bool SHARED> constexpr int rings() { return SHARED ? AT_WAVES : 1; }
+// tiles first, first + 4, .. below end
+__device__ __forceinline__ int every_fourth(int end, int first) { return end > first ? (end - first + AT_WAVES - 1) / AT_WAVES : 0; }
+// acc of wavefront 0 becomes the sum of the four wavefronts', each times its f; `sums`: 256 bytes per accumulator and wavefront
+// (the rings, which everyone has left)
+template <int MB>
+__device__ __forceinline__ void meet_sums(float16v (&acc)[MB], float* sums, int wave, int lane, const float (&f)[AT_WAVES]) {
+#pragma unroll
+  for (int m = 0; m < MB; ++m)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) sums[((wave * MB + m) * 16 + r) * 64 + lane] = acc[m][r];
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < MB * 4; ++i) {                       // a quarter of the accumulators each
+    const int e = wave * MB * 4 + i;
+    float t = f[0] * sums[e * 64 + lane];
+#pragma unroll
+    for (int w = 1; w < AT_WAVES; ++w) t = fmaf(f[w], sums[(w * MB * 16 + e) * 64 + lane], t);
+    sums[e * 64 + lane] = t;
+  }
+  __syncthreads();
+  if (wave == 0) {
+#pragma unroll
+    for (int m = 0; m < MB; ++m)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[m][r] = sums[(m * 16 + r) * 64 + lane];
+  }
 }
 
 // One (sequence, head): wavefront-uniform byte pointers to row 0 of q, k, v (row stride 6 d bytes) and of the
@@ -608,39 +649,50 @@ __device__ __forceinline__ void redo_rows(float t, int rows_left, F f) {
 // buffer just freed, and the wavefront computes on pair t (or skips it when the causal mask hides the whole tile from
 // its rows).  No global load is issued inside the loop other than these copies, so the counted wait is exact.
 
-template <int DHP, bool PAD, bool CAUSAL>
-__global__ __launch_bounds__(64 * AT_WAVES, 2) void attn_fwd_mfma_kernel(AttnArgs a) {
+template <int DHP, bool PAD, bool CAUSAL, bool SHARED>
+__global__ __launch_bounds__(64 * AT_WAVES, SHARED ? 1 : 2) void attn_fwd_mfma_kernel(AttnArgs a) {
+  constexpr int NST = ring_stages<DHP, SHARED>();
   typedef Geo<DHP> G;
   constexpr bool EXACT = exact_scores<DHP, PAD>();
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[AT_NST][2][G::TB];   // [stage][k | v]
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[rings<SHARED>() * NST][2][G::TB];   // [stage][k | v]
   __shared__ __attribute__((aligned(256))) unsigned char staging[AT_WAVES][2048];   // [wave]: results on their way out
   const int lane = threadIdx.x & 63, hh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int T = (int)a.T, nt = (T + 31) >> 5;
-  const int nblk = (nt + AT_WAVES - 1) / AT_WAVES;
+  const int nblk = SHARED ? nt : (nt + AT_WAVES - 1) / AT_WAVES;
   const BlockOf bo = block_of(a, nblk);
   if (!bo.exists) return;
   const int blk = nblk - 1 - bo.slot;                              // long rows first
-  const int qt = AT_WAVES * blk + wave;
+  const int qt = SHARED ? blk : AT_WAVES * blk + wave;
   const bool live = qt < nt;                                       // a ragged workgroup's spare wavefronts only copy
   const unsigned p = bo.p;
   const Head hd = head_of(a, p);
   const unsigned ldb = (unsigned)(hd.ld * 2);
   const int dh = PAD ? a.dh : DHP, dh8 = dh >> 3;
-  const unsigned lds0 = lds_address(smem);
+  unsigned char (*const ring)[2][G::TB] = smem + (SHARED ? wave * NST : 0);
+  const unsigned lds0 = (unsigned)__builtin_amdgcn_readfirstlane((int)lds_address(ring));
   const bool ragged = (T & 31) != 0;
   const int q0 = 32 * qt, qi = q0 + (lane & 31);
   const float c = a.scale * LOG2E;
-  const int last_q = AT_WAVES * blk + AT_WAVES - 1 < nt - 1 ? AT_WAVES * blk + AT_WAVES - 1 : nt - 1;
+  const int last_q = SHARED ? qt : AT_WAVES * blk + AT_WAVES - 1 < nt - 1 ? AT_WAVES * blk + AT_WAVES - 1 : nt - 1;
   const int nkt = CAUSAL ? last_q + 1 : nt;                        // key tiles the workgroup streams
   const int own_nkt = CAUSAL ? qt + 1 : nt;                        // ... and those this wavefront's rows see
   const PairCopy<DHP> pc(ldb, ldb, dh8, wave, lane);
-  auto issue = [&](int kt) __attribute__((always_inline)) {        // this wavefront's share of the k and v tiles of key tile kt
+  // the i-th pair of the ring: key tile i, this wavefront's share of its copies, or (SHARED) the wavefront's i-th key tile, whole
+  const int n_ring = SHARED ? every_fourth(nkt, wave) : nkt;
+  auto tile_of = [&](int i) __attribute__((always_inline)) { return SHARED ? wave + AT_WAVES * i : i; };
+  auto issue = [&](int i) __attribute__((always_inline)) {
+    const int kt = tile_of(i), left = ragged && kt == nt - 1 ? T - 32 * kt : 32;
     const unsigned char* kb = hd.k + (long)(32 * kt) * ldb;
-    pc.issue(kb, kb + hd.d * 2, ldb, ldb, ragged && kt == nt - 1 ? T - 32 * kt : 32, dh8,
-             lds0 + (unsigned)(kt % AT_NST) * (2u * G::TB), wave, lane);
+    const unsigned dst = lds0 + (unsigned)(i % NST) * (2u * G::TB);
+    if (SHARED) {
+      copy_tile<DHP>(kb, ldb, left, dh8, dst, lane);
+      copy_tile<DHP>(kb + hd.d * 2, ldb, left, dh8, dst + G::TB, lane);
+    } else {
+      pc.issue(kb, kb + hd.d * 2, ldb, ldb, left, dh8, dst, wave, lane);
+    }
   };
-  for (int kt = 0; kt < AT_NST - 1 && kt < nkt; ++kt) issue(kt);
+  for (int i = 0; i < NST - 1 && i < n_ring; ++i) issue(i);
   bf16x8 fq[G::KK];
 #pragma unroll
   for (int kk = 0; kk < G::KK; ++kk) fq[kk] = own_cols_mem(hd.q + (long)(live ? q0 : 0) * ldb, ldb, live ? T - q0 : 1, kk, dh8, lane);
@@ -650,11 +702,11 @@ __global__ __launch_bounds__(64 * AT_WAVES, 2) void attn_fwd_mfma_kernel(AttnArg
   zero_acc(o);
   float m = -INFINITY, l = 0.f;
   // one tile of 32 keys; MASKED: the tile on the diagonal (causal) or the one that runs past the last key
-  auto step = [&](int kt, auto masked_c) __attribute__((always_inline)) {
+  auto step = [&](int i, auto masked_c) __attribute__((always_inline)) {
     constexpr bool MASKED = decltype(masked_c)::value;
-    const int k0 = 32 * kt;
-    const unsigned char* tk = smem[kt % AT_NST][0];
-    const unsigned char* tv = smem[kt % AT_NST][1];
+    const int k0 = 32 * tile_of(i);
+    const unsigned char* tk = ring[i % NST][0];
+    const unsigned char* tv = ring[i % NST][1];
     float16v s;
 #pragma unroll
     for (int r = 0; r < 16; ++r) s[r] = 0.f;
@@ -699,21 +751,46 @@ __global__ __launch_bounds__(64 * AT_WAVES, 2) void attn_fwd_mfma_kernel(AttnArg
 #pragma unroll
       for (int mb = 0; mb < G::MB; ++mb) o[mb] = pq.times(fv[mb][t], t, o[mb]);
   };
-  // tile kt complete and visible to the workgroup, the buffer of tile kt - 1 free and refilled
-  auto advance = [&](int kt) __attribute__((always_inline)) {
-    if (kt + AT_NST - 2 < nkt) copies_in_flight<G::PW * (AT_NST - 2)>();
-    else copies_in_flight<0>();
-    workgroup_handover();
-    if (kt + AT_NST - 1 < nkt) issue(kt + AT_NST - 1);
+  // pair i complete and visible to those that read it, the buffer of pair i - 1 free and refilled
+  auto advance = [&](int i) __attribute__((always_inline)) {
+    if (SHARED) {
+      if (i + NST - 2 < n_ring) copies_in_flight_read<2 * G::COPIES * (NST - 2)>();
+      else copies_in_flight_read<0>();
+    } else {
+      if (i + NST - 2 < n_ring) copies_in_flight<G::PW * (NST - 2)>();
+      else copies_in_flight<0>();
+      workgroup_handover();
+    }
+    if (i + NST - 1 < n_ring) issue(i + NST - 1);
   };
-  // whole tiles, then the masked one, then (causal) the tiles the workgroup streams for its later rows only
-  const int n_own = live ? own_nkt : 0;
-  const int n_plain = CAUSAL ? n_own - 1 : (ragged ? n_own - 1 : n_own);
-  int kt = 0;
-  for (; kt < n_plain; ++kt) { advance(kt); step(kt, std::false_type()); }
-  if (kt < n_own) { advance(kt); step(kt, std::true_type()); ++kt; }
-  for (; kt < nkt; ++kt) advance(kt);
-  if (live) {
+  // whole tiles, then the masked one (SHARED: of the wavefront that has it), then (causal) the tiles the workgroup streams for its
+  // later rows only
+  const int n_own = SHARED ? n_ring : live ? own_nkt : 0;
+  const bool masked_own = (CAUSAL || ragged) && (!SHARED || (nkt - 1) % AT_WAVES == wave);
+  const int n_plain = masked_own ? n_own - 1 : n_own;
+  int i = 0;
+  for (; i < n_plain; ++i) { advance(i); step(i, std::false_type()); }
+  if (i < n_own) { advance(i); step(i, std::true_type()); ++i; }
+  for (; i < n_ring; ++i) advance(i);
+  if (SHARED) {
+    __syncthreads();                                               // everyone has left the rings
+    float* const rows = reinterpret_cast<float*>(smem) + AT_WAVES * G::MB * 16 * 64;       // behind the sums: [wave][m | l][lane]
+    rows[2 * wave * 64 + lane] = m;
+    rows[(2 * wave + 1) * 64 + lane] = l;
+    __syncthreads();
+    float f[AT_WAVES], top = rows[lane];
+#pragma unroll
+    for (int w = 1; w < AT_WAVES; ++w) top = fmaxf(top, rows[2 * w * 64 + lane]);
+    l = 0.f;
+#pragma unroll
+    for (int w = 0; w < AT_WAVES; ++w) {                           // (a wavefront without a tile: m = -inf, f = 0)
+      f[w] = fast_exp2(rows[2 * w * 64 + lane] - top);
+      l = fmaf(f[w], rows[(2 * w + 1) * 64 + lane], l);
+    }
+    m = top;
+    meet_sums(o, reinterpret_cast<float*>(smem), wave, lane, f);
+  }
+  if (SHARED ? wave == 0 : live) {
     store_tile(reinterpret_cast<bf16_t*>(reinterpret_cast<unsigned char*>(a.o) + hd.wide_off) + (long)q0 * hd.d, hd.d, T - q0, o,
                1.f / l, dh, staging[wave], lane);
     if (hh == 0 && qi < T) a.lse[(long)p * a.T + qi] = m + log2f(l);
@@ -722,40 +799,51 @@ __global__ __launch_bounds__(64 * AT_WAVES, 2) void attn_fwd_mfma_kernel(AttnArg
 }
 
 // dq of four tiles of 32 queries; also leaves D = rowsum(do (.) o) of their queries for the dk/dv kernel
-template <int DHP, bool PAD, bool CAUSAL>
-__global__ __launch_bounds__(64 * AT_WAVES, 2) void attn_bwd_q_mfma_kernel(AttnArgs a) {
+template <int DHP, bool PAD, bool CAUSAL, bool SHARED>
+__global__ __launch_bounds__(64 * AT_WAVES, SHARED ? 1 : 2) void attn_bwd_q_mfma_kernel(AttnArgs a) {
+  constexpr int NST = ring_stages<DHP, SHARED>();
   typedef Geo<DHP> G;
   constexpr bool EXACT = exact_scores<DHP, PAD>();
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[AT_NST][2][G::TB];   // [stage][k | v]
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[rings<SHARED>() * NST][2][G::TB];   // [stage][k | v]
   __shared__ __attribute__((aligned(256))) unsigned char staging[AT_WAVES][2048];   // [wave]: results on their way out
   const int lane = threadIdx.x & 63, hh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int T = (int)a.T, nt = (T + 31) >> 5;
-  const int nblk = (nt + AT_WAVES - 1) / AT_WAVES;
+  const int nblk = SHARED ? nt : (nt + AT_WAVES - 1) / AT_WAVES;
   const BlockOf bo = block_of(a, nblk);
   if (!bo.exists) return;
   const int blk = nblk - 1 - bo.slot;
-  const int qt = AT_WAVES * blk + wave;
+  const int qt = SHARED ? blk : AT_WAVES * blk + wave;
   const bool live = qt < nt;
   const unsigned p = bo.p;
   const Head hd = head_of(a, p);
   const unsigned ldb = (unsigned)(hd.ld * 2), ldw = (unsigned)(hd.d * 2);
   const int dh = PAD ? a.dh : DHP, dh8 = dh >> 3;
-  const unsigned lds0 = lds_address(smem);
+  unsigned char (*const ring)[2][G::TB] = smem + (SHARED ? wave * NST : 0);
+  const unsigned lds0 = (unsigned)__builtin_amdgcn_readfirstlane((int)lds_address(ring));
   const bool ragged = (T & 31) != 0;
   const int q0 = live ? 32 * qt : 0, qi = 32 * qt + (lane & 31);
   const int qc = qi < T ? qi : T - 1;
   const float c = a.scale * LOG2E;
-  const int last_q = AT_WAVES * blk + AT_WAVES - 1 < nt - 1 ? AT_WAVES * blk + AT_WAVES - 1 : nt - 1;
+  const int last_q = SHARED ? qt : AT_WAVES * blk + AT_WAVES - 1 < nt - 1 ? AT_WAVES * blk + AT_WAVES - 1 : nt - 1;
   const int nkt = CAUSAL ? last_q + 1 : nt;
   const int own_nkt = CAUSAL ? qt + 1 : nt;
   const PairCopy<DHP> pc(ldb, ldb, dh8, wave, lane);
-  auto issue = [&](int kt) __attribute__((always_inline)) {
+  // the i-th pair of the ring: key tile i, this wavefront's share of its copies, or (SHARED) the wavefront's i-th key tile, whole
+  const int n_ring = SHARED ? every_fourth(nkt, wave) : nkt;
+  auto tile_of = [&](int i) __attribute__((always_inline)) { return SHARED ? wave + AT_WAVES * i : i; };
+  auto issue = [&](int i) __attribute__((always_inline)) {
+    const int kt = tile_of(i), left = ragged && kt == nt - 1 ? T - 32 * kt : 32;
     const unsigned char* kb = hd.k + (long)(32 * kt) * ldb;
-    pc.issue(kb, kb + hd.d * 2, ldb, ldb, ragged && kt == nt - 1 ? T - 32 * kt : 32, dh8,
-             lds0 + (unsigned)(kt % AT_NST) * (2u * G::TB), wave, lane);
+    const unsigned dst = lds0 + (unsigned)(i % NST) * (2u * G::TB);
+    if (SHARED) {
+      copy_tile<DHP>(kb, ldb, left, dh8, dst, lane);
+      copy_tile<DHP>(kb + hd.d * 2, ldb, left, dh8, dst + G::TB, lane);
+    } else {
+      pc.issue(kb, kb + hd.d * 2, ldb, ldb, left, dh8, dst, wave, lane);
+    }
   };
-  for (int kt = 0; kt < AT_NST - 1 && kt < nkt; ++kt) issue(kt);
+  for (int i = 0; i < NST - 1 && i < n_ring; ++i) issue(i);
   float L2 = a.lse[(long)p * a.T + qc];
   bf16x8 fq[G::KK], fdo[G::KK];
   float D = 0.f;
@@ -769,18 +857,18 @@ __global__ __launch_bounds__(64 * AT_WAVES, 2) void attn_bwd_q_mfma_kernel(AttnA
       D += dot8(fdo[kk], own_cols_mem(ob, ldw, T - q0, kk, dh8, lane));
     }
     D += __shfl_xor(D, 32, 64);
-    if (live && hh == 0 && qi < T) a.dsum[(long)p * a.T + qi] = D;
+    if ((SHARED ? wave == 0 : live) && hh == 0 && qi < T) a.dsum[(long)p * a.T + qi] = D;
 #pragma unroll
     for (int kk = 0; kk < G::KK; ++kk) { landed(fq[kk]); landed(fdo[kk]); }
     landed(L2);
   }
   float16v dq[G::MB];
   zero_acc(dq);
-  auto step = [&](int kt, auto masked_c) __attribute__((always_inline)) {
+  auto step = [&](int i, auto masked_c) __attribute__((always_inline)) {
     constexpr bool MASKED = decltype(masked_c)::value;
-    const int k0 = 32 * kt;
-    const unsigned char* tk = smem[kt % AT_NST][0];
-    const unsigned char* tv = smem[kt % AT_NST][1];
+    const int k0 = 32 * tile_of(i);
+    const unsigned char* tk = ring[i % NST][0];
+    const unsigned char* tv = ring[i % NST][1];
     float16v s, dp;
 #pragma unroll
     for (int r = 0; r < 16; ++r) { s[r] = 0.f; dp[r] = -D; }      // dp comes out as dP - D
@@ -827,21 +915,33 @@ __global__ __launch_bounds__(64 * AT_WAVES, 2) void attn_bwd_q_mfma_kernel(AttnA
       for (int mb = 0; mb < G::MB; ++mb)
         dq[mb] = dq_s.times(G::MB < 4 ? kr[mb][t] : frag_rows_lds<DHP>(tk, mb, t, lane), t, dq[mb]);
   };
-  // tile kt complete and visible to the workgroup, the buffer of tile kt - 1 free and refilled
-  auto advance = [&](int kt) __attribute__((always_inline)) {
-    if (kt + AT_NST - 2 < nkt) copies_in_flight<G::PW * (AT_NST - 2)>();
-    else copies_in_flight<0>();
-    workgroup_handover();
-    if (kt + AT_NST - 1 < nkt) issue(kt + AT_NST - 1);
+  // pair i complete and visible to those that read it, the buffer of pair i - 1 free and refilled
+  auto advance = [&](int i) __attribute__((always_inline)) {
+    if (SHARED) {
+      if (i + NST - 2 < n_ring) copies_in_flight_read<2 * G::COPIES * (NST - 2)>();
+      else copies_in_flight_read<0>();
+    } else {
+      if (i + NST - 2 < n_ring) copies_in_flight<G::PW * (NST - 2)>();
+      else copies_in_flight<0>();
+      workgroup_handover();
+    }
+    if (i + NST - 1 < n_ring) issue(i + NST - 1);
   };
-  // whole tiles, then the masked one, then (causal) the tiles the workgroup streams for its later rows only
-  const int n_own = live ? own_nkt : 0;
-  const int n_plain = CAUSAL ? n_own - 1 : (ragged ? n_own - 1 : n_own);
-  int kt = 0;
-  for (; kt < n_plain; ++kt) { advance(kt); step(kt, std::false_type()); }
-  if (kt < n_own) { advance(kt); step(kt, std::true_type()); ++kt; }
-  for (; kt < nkt; ++kt) advance(kt);
-  if (live) {
+  // whole tiles, then the masked one (SHARED: of the wavefront that has it), then (causal) the tiles the workgroup streams for its
+  // later rows only
+  const int n_own = SHARED ? n_ring : live ? own_nkt : 0;
+  const bool masked_own = (CAUSAL || ragged) && (!SHARED || (nkt - 1) % AT_WAVES == wave);
+  const int n_plain = masked_own ? n_own - 1 : n_own;
+  int i = 0;
+  for (; i < n_plain; ++i) { advance(i); step(i, std::false_type()); }
+  if (i < n_own) { advance(i); step(i, std::true_type()); ++i; }
+  for (; i < n_ring; ++i) advance(i);
+  if (SHARED) {
+    __syncthreads();                                               // everyone has left the rings
+    const float ones[AT_WAVES] = {1.f, 1.f, 1.f, 1.f};
+    meet_sums(dq, reinterpret_cast<float*>(smem), wave, lane, ones);
+  }
+  if (SHARED ? wave == 0 : live) {
     store_tile(reinterpret_cast<bf16_t*>(reinterpret_cast<unsigned char*>(a.dqkv) + (hd.q - reinterpret_cast<const unsigned char*>(a.qkv))) +
                    (long)q0 * hd.ld, hd.ld, T - q0, dq, a.scale, dh, staging[wave], lane);
     if (EXACT) redo_rows(not_finite(dq, 0.f), T - q0, [&](int r) { redo_q(a, hd, p, q0 + r, __shfl(D, r, 64), lane); });
@@ -851,72 +951,93 @@ __global__ __launch_bounds__(64 * AT_WAVES, 2) void attn_bwd_q_mfma_kernel(AttnA
 // dk, dv of four tiles of 32 keys (after the dq kernel: reads D).  128-wide heads hold 128 accumulators and 32 operand
 // registers per lane, and the parts of two sets of scores: one workgroup per compute unit with all 512 registers; narrower
 // ones fit three, or two where the scores are in three parts of 64 columns (in three, 40 registers spill).
-template <int DHP, bool PAD, bool CAUSAL>
-__global__ __launch_bounds__(64 * AT_WAVES, DHP == 128 ? 1 : DHP == 64 && PAD ? 2 : 3) void attn_bwd_kv_mfma_kernel(AttnArgs a) {
+template <int DHP, bool PAD, bool CAUSAL, bool SHARED>
+__global__ __launch_bounds__(64 * AT_WAVES, SHARED || DHP == 128 ? 1 : DHP == 64 && PAD ? 2 : 3) void attn_bwd_kv_mfma_kernel(AttnArgs a) {
+  constexpr int NST = ring_stages<DHP, SHARED>();
   typedef Geo<DHP> G;
   constexpr bool EXACT = exact_scores<DHP, PAD>();
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[AT_NST][2][G::TB];   // [stage][q | do]
-  __shared__ __attribute__((aligned(1024))) unsigned char own[AT_WAVES][G::TB];     // [wave]: the v rows of the wavefront's own keys
-  __shared__ __attribute__((aligned(256))) float stats[AT_WAVES][AT_NST][64];       // [wave][stage][L2 | D] (a copy per wavefront)
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[rings<SHARED>() * NST][2][G::TB];   // [stage][q | do]
+  __shared__ __attribute__((aligned(1024))) unsigned char own_v[SHARED ? 1 : AT_WAVES][G::TB];     // [wave]: the v rows of its own keys
+  __shared__ __attribute__((aligned(256))) float stats[AT_WAVES][NST][64];          // [wave][stage][L2 | D] (a copy per wavefront)
   const int lane = threadIdx.x & 63, hh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int T = (int)a.T, nt = (T + 31) >> 5;
-  const BlockOf bo = block_of(a, (nt + AT_WAVES - 1) / AT_WAVES);
+  const BlockOf bo = block_of(a, SHARED ? nt : (nt + AT_WAVES - 1) / AT_WAVES);
   if (!bo.exists) return;
   const int blk = bo.slot;                                         // causal: early keys see the most queries
-  const int kt = AT_WAVES * blk + wave;
+  const int kt = SHARED ? blk : AT_WAVES * blk + wave;
   const bool live = kt < nt;
   const unsigned p = bo.p;
   const Head hd = head_of(a, p);
   const unsigned ldb = (unsigned)(hd.ld * 2), ldw = (unsigned)(hd.d * 2);
   const int dh = PAD ? a.dh : DHP, dh8 = dh >> 3;
   const unsigned char* dob = reinterpret_cast<const unsigned char*>(a.dout) + hd.wide_off;
-  const unsigned lds0 = lds_address(smem), lds_s = lds_address(stats[wave]);
+  unsigned char (*const ring)[2][G::TB] = smem + (SHARED ? wave * NST : 0);
+  unsigned char* const own = own_v[SHARED ? 0 : wave];
+  const unsigned lds0 = (unsigned)__builtin_amdgcn_readfirstlane((int)lds_address(ring)), lds_s = lds_address(stats[wave]);
   const bool ragged = (T & 31) != 0;
   const int k0 = live ? 32 * kt : 0, kj = 32 * kt + (lane & 31);
   const float c = a.scale * LOG2E;
   const float ninv_c = -1.0f / c;
   // lanes 0..31 fetch the row statistic of query l of each tile, lanes 32..63 its D
   const float* stat_src = (hh == 0 ? a.lse : a.dsum) + (long)p * a.T;
-  const int q_first = CAUSAL ? AT_WAVES * blk : 0;                 // query tiles the workgroup streams: q_first .. nt - 1
+  const int q_first = CAUSAL ? SHARED ? kt : AT_WAVES * blk : 0;                 // query tiles the workgroup streams: q_first .. nt - 1
   const int own_first = CAUSAL ? kt : 0;                           // ... and the first one this wavefront's keys are seen by
   const PairCopy<DHP> pc(ldb, ldw, dh8, wave, lane);
-  auto issue = [&](int qt) __attribute__((always_inline)) {       // a share of the q and do tiles, and the statistics, of query tile qt
-    const int q0 = 32 * qt, b = qt % AT_NST;
+  // the i-th pair of the ring: query tile q_first + i, this wavefront's share of its copies, or (SHARED) the wavefront's i-th
+  // query tile, whole; and the statistics
+  const int n_ring = SHARED ? every_fourth(nt - q_first, wave) : nt - q_first;
+  auto tile_of = [&](int i) __attribute__((always_inline)) { return q_first + (SHARED ? wave + AT_WAVES * i : i); };
+  auto issue = [&](int i) __attribute__((always_inline)) {
+    const int qt = tile_of(i), q0 = 32 * qt, b = i % NST;
     const int left = ragged && qt == nt - 1 ? T - q0 : 32;
-    pc.issue(hd.q + (long)q0 * ldb, dob + (long)q0 * ldw, ldb, ldw, left, dh8, lds0 + (unsigned)b * (2u * G::TB), wave, lane);
+    const unsigned char* qb = hd.q + (long)q0 * ldb;
+    const unsigned char* db = dob + (long)q0 * ldw;
+    const unsigned dst = lds0 + (unsigned)b * (2u * G::TB);
+    if (SHARED) {
+      copy_tile<DHP>(qb, ldb, left, dh8, dst, lane);
+      copy_tile<DHP>(db, ldw, left, dh8, dst + G::TB, lane);
+    } else {
+      pc.issue(qb, db, ldb, ldw, left, dh8, dst, wave, lane);
+    }
     const int r = (lane & 31) < left ? (lane & 31) : left - 1;
     copy4_to_lds(stat_src + q0 + r, lds_s + (unsigned)b * 256u);
   };
   // The wavefront's own v tile stays in LDS for the whole loop (copied before the ring's first tiles, so it has landed
   // when the first of those has), its own k tile in registers: LDS and registers then both leave room for three
   // workgroups on a compute unit (heads of up to 64 columns).
-  copy_tile<DHP>(hd.v + (long)k0 * ldb, ldb, T - k0, dh8, lds_address(own[wave]), lane);
-  const unsigned char* ov = own[wave];
-  if (PAD) {          // the v tile is an operand that is contracted along its columns: zeros past the head's width
-    copies_in_flight<0>();
-    asm volatile("" ::: "memory");
-    for (int i = lane; i < 32 * (G::CPR - dh8); i += 64) {
-      const int r = i / (G::CPR - dh8), ch = dh8 + i % (G::CPR - dh8);
-      *reinterpret_cast<uint4*>(own[wave] + r * G::RB + ((ch ^ G::swz(r)) << 4)) = make_uint4(0u, 0u, 0u, 0u);
+  // (SHARED: one v tile for the four, copied by the first of them; they meet once it has landed)
+  if (!SHARED || wave == 0) {
+    copy_tile<DHP>(hd.v + (long)k0 * ldb, ldb, T - k0, dh8, lds_address(own), lane);
+    if (PAD) {          // the v tile is an operand that is contracted along its columns: zeros past the head's width
+      copies_in_flight<0>();
+      asm volatile("" ::: "memory");
+      for (int i = lane; i < 32 * (G::CPR - dh8); i += 64) {
+        const int r = i / (G::CPR - dh8), ch = dh8 + i % (G::CPR - dh8);
+        *reinterpret_cast<uint4*>(own + r * G::RB + ((ch ^ G::swz(r)) << 4)) = make_uint4(0u, 0u, 0u, 0u);
+      }
+      __builtin_amdgcn_wave_barrier();
     }
-    __builtin_amdgcn_wave_barrier();
   }
-  for (int qt = q_first; qt < q_first + AT_NST - 1 && qt < nt; ++qt) issue(qt);
+  for (int i = 0; i < NST - 1 && i < n_ring; ++i) issue(i);
   bf16x8 fk[G::KK];
 #pragma unroll
   for (int kk = 0; kk < G::KK; ++kk) fk[kk] = own_cols_mem(hd.k + (long)k0 * ldb, ldb, T - k0, kk, dh8, lane);
 #pragma unroll
   for (int kk = 0; kk < G::KK; ++kk) landed(fk[kk]);
+  if (SHARED) {
+    copies_in_flight_read<0>();
+    workgroup_handover();
+  }
   float16v dk[G::MB], dv[G::MB];
   zero_acc(dk);
   zero_acc(dv);
   // one tile of 32 queries; MASKED: the tile on the diagonal (causal) or the one that runs past the last query
-  auto step = [&](int qt, auto masked_c) __attribute__((always_inline)) {
+  auto step = [&](int i, auto masked_c) __attribute__((always_inline)) {
     constexpr bool MASKED = decltype(masked_c)::value;
-    const int q0 = 32 * qt, b = qt % AT_NST;
-    const unsigned char* tq = smem[b][0];
-    const unsigned char* td = smem[b][1];
+    const int q0 = 32 * tile_of(i), b = i % NST;
+    const unsigned char* tq = ring[b][0];
+    const unsigned char* td = ring[b][1];
     const float* st = stats[wave][b];
     float16v s, dp;
 #pragma unroll
@@ -932,7 +1053,7 @@ __global__ __launch_bounds__(64 * AT_WAVES, DHP == 128 ? 1 : DHP == 64 && PAD ? 
 #pragma unroll
     for (int kk = 0; kk < G::KK; ++kk) {
       s = mfma(frag_cols_lds<DHP>(tq, kk, lane), fk[kk], s);
-      dp = mfma(frag_cols_lds<DHP>(td, kk, lane), frag_cols_lds<DHP>(ov, kk, lane), dp);
+      dp = mfma(frag_cols_lds<DHP>(td, kk, lane), frag_cols_lds<DHP>(own, kk, lane), dp);
     }
     __builtin_amdgcn_sched_barrier(0);   // (keeps the second products' operand reads below: fewer live registers)
     float pr[16], ds[16];
@@ -959,25 +1080,38 @@ __global__ __launch_bounds__(64 * AT_WAVES, DHP == 128 ? 1 : DHP == 64 && PAD ? 
 #pragma unroll
       for (int t = 0; t < 2; ++t) dk[mb] = ss.times(frag_rows_lds<DHP>(tq, mb, t, lane), t, dk[mb]);
   };
-  auto advance = [&](int qt) __attribute__((always_inline)) {
-    if (qt + AT_NST - 2 < nt) copies_in_flight<(G::PW + 1) * (AT_NST - 2)>();
-    else copies_in_flight<0>();
-    workgroup_handover();
-    if (qt + AT_NST - 1 < nt) issue(qt + AT_NST - 1);
+  auto advance = [&](int i) __attribute__((always_inline)) {
+    if (SHARED) {
+      if (i + NST - 2 < n_ring) copies_in_flight_read<(2 * G::COPIES + 1) * (NST - 2)>();
+      else copies_in_flight_read<0>();
+    } else {
+      if (i + NST - 2 < n_ring) copies_in_flight<(G::PW + 1) * (NST - 2)>();
+      else copies_in_flight<0>();
+      workgroup_handover();
+    }
+    if (i + NST - 1 < n_ring) issue(i + NST - 1);
   };
   // (causal) the tiles streamed for the workgroup's earlier keys only, the tile on the diagonal, whole tiles, a ragged last one
-  int qt = q_first;
-  const int first = live ? own_first : nt;
-  for (; qt < first; ++qt) advance(qt);
-  if (CAUSAL && qt < nt) { advance(qt); step(qt, std::true_type()); ++qt; }
-  const int plain_end = ragged ? nt - 1 : nt;
-  for (; qt < plain_end; ++qt) { advance(qt); step(qt, std::false_type()); }
-  if (qt < nt) { advance(qt); step(qt, std::true_type()); }
-  if (live) {                  // (the wavefront's own v tile has served)
+  int i = 0;
+  const int skip = SHARED ? 0 : live ? own_first - q_first : n_ring;
+  for (; i < skip; ++i) advance(i);
+  if (CAUSAL && (!SHARED || wave == 0) && i < n_ring) { advance(i); step(i, std::true_type()); ++i; }
+  const bool ragged_own = ragged && (!SHARED || (nt - 1 - q_first) % AT_WAVES == wave);
+  const int plain_end = ragged_own ? n_ring - 1 : n_ring;
+  for (; i < plain_end; ++i) { advance(i); step(i, std::false_type()); }
+  if (i < n_ring) { advance(i); step(i, std::true_type()); }
+  if (SHARED) {
+    __syncthreads();                                               // everyone has left the rings
+    const float ones[AT_WAVES] = {1.f, 1.f, 1.f, 1.f};
+    meet_sums(dk, reinterpret_cast<float*>(smem), wave, lane, ones);
+    __syncthreads();
+    meet_sums(dv, reinterpret_cast<float*>(smem), wave, lane, ones);
+  }
+  if (SHARED ? wave == 0 : live) {                                 // (the own v tile has served)
     bf16_t* first = reinterpret_cast<bf16_t*>(reinterpret_cast<unsigned char*>(a.dqkv) + (hd.k - reinterpret_cast<const unsigned char*>(a.qkv))) +
                     (long)k0 * hd.ld;
-    store_tile(first, hd.ld, T - k0, dk, a.scale, dh, own[wave], lane);
-    store_tile(first + hd.d, hd.ld, T - k0, dv, 1.f, dh, own[wave], lane);
+    store_tile(first, hd.ld, T - k0, dk, a.scale, dh, own, lane);
+    store_tile(first + hd.d, hd.ld, T - k0, dv, 1.f, dh, own, lane);
     if (EXACT)
       redo_rows(not_finite(dv, not_finite(dk, 0.f)), T - k0,
                 [&](int r) { redo_kv(a, hd, p, k0 + r, [&](int i) { return a.dsum[(long)p * a.T + i]; }, lane); });
@@ -1220,18 +1354,35 @@ __global__ __launch_bounds__(256, DHP == 128 ? 1 : 2) void attn_bwd_short_mfma_k
 
 inline bool use_mfma(int dtype, const AttnArgs& a) { return dtype == 1 && a.dh <= 128; }
 
+// The form with shared tiles: one workgroup per compute unit at most (of 104 to 138 KB of LDS), or, where two fit (32 columns) or a
+// mask makes half of them short, two; from four tiles a sequence on.  us, forward / dq / dk, dv (or both of them in one kernel, up to
+// 256 positions), heads x columns, sequences of positions, the form before -> this one: 2 x 32, 1 of 1024 25 / 22 / 33 -> 11 / 11 / 15;
+// 2 x 32, 8 of 1024 27 / 25 / 35 -> 17 / 16 / 20; 4 x 64, 1 of 1024 24 / 20 / 29 -> 13 / 13 / 16; 2 x 128, 2 of 1024, causal, 41 / 43 / 68
+// -> 19 / 21 / 27; 8 x 128, 4 of 435, causal, 20 / 23 / 36 -> 17 / 20 / 25; 8 x 64, 4 of 512, causal, 15 / 14 / 18 -> 12 / 14 / 15; 4 x 64,
+// 8 of 256, causal, 11 / 19 -> 7 / 15; 8 x 32, 4 of 256 9 / 26 -> 7 / 14.  Beyond: 8 x 64, 2 of 600 16 / 15 / 19 -> 16 / 17 / 21, 4 x 64, 4 of
+// 1024 25 / 21 / 29 -> 24 / 22 / 30, 8 of 1024 26 / 24 / 32 -> 43 / 42 / 58; T = 128: 6.3 / 9.5 -> 5.5 / 12, T = 64: 5.0 -> 5.5.
+inline bool shares_tiles(const AttnArgs& a, bool two) {
+  const long nt = (a.T + 31) / 32;
+  return nt >= 4 && a.seqs * a.heads * nt <= (two ? 512 : 256);
+}
 template <int DHP, bool PAD, bool CAUSAL>
 hipError_t launch_fwd(const AttnArgs& a, hipStream_t s) {
   AttnArgs m = a;
+  if (shares_tiles(a, DHP == 32 || CAUSAL)) {
+    hipLaunchKernelGGL((attn_fwd_mfma_kernel<DHP, PAD, CAUSAL, true>), dim3((unsigned)attn_grid(a, true)), dim3(64 * AT_WAVES), 0, s, m);
+    return hipGetLastError();
+  }
   m.by_problem = attn_grid(a) >= BY_PROBLEM_FROM;
-  hipLaunchKernelGGL((attn_fwd_mfma_kernel<DHP, PAD, CAUSAL>), dim3((unsigned)attn_grid(a)), dim3(64 * AT_WAVES), 0, s, m);
+  hipLaunchKernelGGL((attn_fwd_mfma_kernel<DHP, PAD, CAUSAL, false>), dim3((unsigned)attn_grid(a)), dim3(64 * AT_WAVES), 0, s, m);
   return hipGetLastError();
 }
 // sequences whose tiles two workgroups' LDS holds: a whole problem per workgroup
 template <int DHP> constexpr long short_T() { return DHP == 128 ? 128 : 256; }
 template <int DHP, bool PAD, bool CAUSAL>
 hipError_t launch_bwd(const AttnArgs& a, hipStream_t s) {
-  if (a.T <= short_T<DHP>()) {
+  const bool is_short = a.T <= short_T<DHP>();
+  const bool shared = (!is_short || a.T > 128) && shares_tiles(a, DHP == 32 || (CAUSAL && !is_short));
+  if (is_short && !shared) {
     const long P = a.seqs * a.heads;
     if (P > 0x7fffffffL) return hipErrorInvalidValue;
     const dim3 grid((unsigned)P);
@@ -1242,13 +1393,20 @@ hipError_t launch_bwd(const AttnArgs& a, hipStream_t s) {
     }
     return hipGetLastError();
   }
-  const dim3 grid((unsigned)attn_grid(a)), block(64 * AT_WAVES);
+  const dim3 block(64 * AT_WAVES);
+  if (shared) {
+    const dim3 grid((unsigned)attn_grid(a, true));
+    hipLaunchKernelGGL((attn_bwd_q_mfma_kernel<DHP, PAD, CAUSAL, true>), grid, block, 0, s, a);
+    hipLaunchKernelGGL((attn_bwd_kv_mfma_kernel<DHP, PAD, CAUSAL, true>), grid, block, 0, s, a);
+    return hipGetLastError();
+  }
+  const dim3 grid((unsigned)attn_grid(a));
   // dq is bound by its tile stream and gains from one XCD per problem; dk/dv is bound by its arithmetic and by the
   // tail, and keeps the longest-first order (by_problem = 0 as the caller leaves it)
   AttnArgs m = a;
   m.by_problem = attn_grid(a) >= BY_PROBLEM_FROM;
-  hipLaunchKernelGGL((attn_bwd_q_mfma_kernel<DHP, PAD, CAUSAL>), grid, block, 0, s, m);
-  hipLaunchKernelGGL((attn_bwd_kv_mfma_kernel<DHP, PAD, CAUSAL>), grid, block, 0, s, a);
+  hipLaunchKernelGGL((attn_bwd_q_mfma_kernel<DHP, PAD, CAUSAL, false>), grid, block, 0, s, m);
+  hipLaunchKernelGGL((attn_bwd_kv_mfma_kernel<DHP, PAD, CAUSAL, false>), grid, block, 0, s, a);
   return hipGetLastError();
 }
 

@@ -69,6 +69,20 @@ def test_attention_head_widths(B, dh, T, causal):
     _check_backward(B, w, p, st, sv, inp, w.name, exact=False)
 
 
+# problems enough that a workgroup's wavefronts take a tile each (above), fewer, so that they share one's tiles, and the numbers at
+# which that changes (256 or 512 tiles), on widths with one, two and four blocks of columns
+@pytest.mark.parametrize("dh,heads,seqs,T,causal", [(24, 4, 26, 257, True), (40, 4, 26, 257, False), (64, 4, 16, 300, True),
+                                                    (104, 3, 20, 290, False), (128, 2, 30, 290, True), (32, 2, 32, 256, True),
+                                                    (32, 2, 33, 256, True), (64, 2, 16, 250, False), (64, 2, 17, 250, False),
+                                                    (64, 1, 1, 1000, True), (128, 1, 1, 520, False), (48, 1, 2, 513, True)])
+def test_attention_with_shared_tiles(B, dh, heads, seqs, T, causal):
+    w = synth.scaled(W["gpt2_paper"], name=f"tfm_dh{dh}_T{T}_x{heads * seqs}", L=2, N=seqs * T, seq_len=T, d=heads * dh, heads=heads,
+                     d_ff=64, w1_std=0.0, w2_std=0.0, w2_scale=0.6, causal=causal, ks=(1,))
+    inp, st, sv, p = _forward_matches(B, w)
+    H.assert_close(H.to_np(p.attn_o), sv["o"][0::2], H.TOL["bf16"], f"{w.name} attention output")
+    _check_backward(B, w, p, st, sv, inp, w.name, exact=False)
+
+
 _KINDS = {"rnn": ("gated_rnn_contractive", 1, 1), "token": ("gated_rnn_token_gates", 1, 1), "gated": ("gru_cell", 1, 2),
           "lstm": ("lstm_cell", 2, 4), "gru": ("gru_std_cell", 1, 3)}
 
