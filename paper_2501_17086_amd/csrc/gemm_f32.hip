@@ -8,11 +8,13 @@
 //   32-wide tiles  four wavefronts share one 32 x 32 block and split the contraction in quarters, added through LDS: four
 //                  times the workgroups and a quarter of the chain
 //   64-wide tiles  four wavefronts own a 32 x 32 block each: half the operand bytes per flop, for launches that fill the chip
-// Rows past the matrix repeat the last one and are not stored; k past the end are zeros in both operands.
-// Measured against the LDS-tiled fma kernel (gemm_generic.hip, which keeps what is not 16-byte aligned), us:
-// 128 x 64 x 256, 8 blocks 28.9 -> 5.0 (32 wide); 64 x 256 x 128, 8 blocks 18.0 -> 5.2; 512 x 128 x 512, 8 blocks 73 -> 12;
-// 1024 x 256 x 1024, 12 blocks 182 -> 93 (64 wide, 70 TFLOP/s).  Relative error against 64 bits 1.5e-7 .. 2.9e-7 with 32-wide
-// tiles (the quarters are sums of their own) and 2.9e-7 .. 5.7e-7 with 64-wide ones, where the fma kernel has 2.9e-7 .. 5.7e-7.
+// Rows past the matrix repeat the last one and are not stored; k past the end are zeros in both operands.  What is fused into the
+// result is asked for behind the first operands.
+// Measured, us (before: addresses in 64 bits and values selected lane by lane, the fused operand read at the end): 128 x 256 x 64, 8
+// blocks, with act' 5.3 -> 3.9; 128 x 64 x 256 5.1 -> 4.7; 338 x 384 x 96, 10 blocks, with act' 15.8 -> 9.3; 384 x 96 x 338, parameter gradients
+// of 10 blocks, 13.7 -> 8.6; 1024 x 256 x 1024, 12 blocks, 95 -> 71 (64 wide, 91 TFLOP/s), parameter gradients 96 -> 60; one block of 338 x
+// 96 x 384, both operands K-contiguous, 6.1 -> 6.6.  Relative error against 64 bits 1.5e-7 .. 2.9e-7 with 32-wide tiles (the quarters are
+// sums of their own) and 2.9e-7 .. 5.7e-7 with 64-wide ones.
 #include "hbp_common.h"
 
 namespace hbp {
@@ -23,95 +25,123 @@ typedef float float16v __attribute__((ext_vector_type(16)));
 
 constexpr int CH = 32;      // contraction indices per chunk: 16 per lane half
 
-// one operand's 16 values per lane of the chunk at k0
-template <bool KC, bool TAIL>
-__device__ __forceinline__ void load_chunk(float (&v)[CH / 2], const float* p, long ld, long k0, long k_end, int h) {
+// One operand: a lane's place in a chunk is a 32-bit byte offset that stays the same, the chunk's is in the scalar base, and
+// a lane past the contraction's end gets an offset outside the buffer, where loads give zero.  (Addresses in 64 bits per lane and
+// values selected one by one were most of a short contraction's time: a wavefront issues a vector instruction every four cycles.)
+typedef float float4v __attribute__((ext_vector_type(4)));
+constexpr unsigned OUTSIDE = 0x80000000u;
+template <bool KC>
+struct Operand {
+  const char* base;         // of the next chunk
+  unsigned off;             // this lane's row and half in it
+  int ld4;                  // bytes between two k (row-contiguous)
+  // row0: the block's first row, `rows` of them; k: the first contraction index
+  __device__ __forceinline__ Operand(const void* p, long ld, long row0, long rows, long k, int r, int h) {
+    base = reinterpret_cast<const char*>(p) + (KC ? row0 * ld + k : k * ld + row0) * 4;
+    ld4 = (int)ld * 4;
+    const int rc = r < rows ? r : (int)rows - 1;
+    off = KC ? (unsigned)(rc * ld4 + 16 * h) : (unsigned)(4 * h * ld4 + 4 * rc);
+  }
+  // the lane's 16 values of the next chunk, `left` contraction indices of it there
+  template <bool TAIL>
+  __device__ __forceinline__ void load(float (&v)[CH / 2], int left, int h) {
+    const __amdgpu_buffer_rsrc_t b = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base), 0, 0x7fffffff, 0x00027000);
 #pragma unroll
-  for (int u = 0; u < CH / 8; ++u) {
-    const long k = k0 + 8 * u + 4 * h;
-    if (KC) {               // (k_end is a multiple of 4 here: a group of four is inside or outside as a whole)
-      const bool in = !TAIL || k < k_end;
-      const float4 t = *reinterpret_cast<const float4*>(p + (in ? k : k_end - 4));
-      v[4 * u] = in ? t.x : 0.f; v[4 * u + 1] = in ? t.y : 0.f; v[4 * u + 2] = in ? t.z : 0.f; v[4 * u + 3] = in ? t.w : 0.f;
-    } else {
+    for (int u = 0; u < CH / 8; ++u) {
+      if (KC) {             // (`left` is a multiple of 4 here: a group of four is inside or outside as a whole)
+        const unsigned o = !TAIL || 8 * u + 4 * h < left ? off : OUTSIDE;
+        const float4v t = __builtin_bit_cast(float4v, __builtin_amdgcn_raw_buffer_load_b128(b, (int)o, 32 * u, 0));
 #pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const bool in = !TAIL || k + s < k_end;
-        const float t = p[(in ? k + s : k_end - 1) * ld];
-        v[4 * u + s] = in ? t : 0.f;
+        for (int s = 0; s < 4; ++s) v[4 * u + s] = t[s];
+      } else {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          const unsigned o = !TAIL || 8 * u + 4 * h + s < left ? off : OUTSIDE;
+          v[4 * u + s] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(b, (int)o, (8 * u + s) * ld4, 0));
+        }
       }
     }
+    base += KC ? CH * 4 : (long)CH * ld4;
   }
-}
-__device__ __forceinline__ void multiply(float16v& acc, const float (&a)[CH / 2], const float (&b)[CH / 2]) {
+};
+// a chunk's products, eight contraction indices at a time as long as there are any of the `left`  (A path of its own for whole chunks
+// puts all of their loads before the first product: 5 to 15 % slower.)
+__device__ __forceinline__ void multiply(float16v& acc, const float (&a)[CH / 2], const float (&b)[CH / 2], int left) {
 #pragma unroll
-  for (int i = 0; i < CH / 2; ++i)
-    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(b[i], a[i], acc, 0, 0, 0);   // lane l: output row l % 32
+  for (int u = 0; u < CH / 8; ++u) {
+    if (8 * u >= left) break;
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(b[4 * u + s], a[4 * u + s], acc, 0, 0, 0);   // lane l: output row l % 32
+  }
 }
 
 __device__ __forceinline__ float gelu_f(float a) { return 0.5f * a * (1.0f + erff(a * 0.70710678118654752440f)); }
 __device__ __forceinline__ float gelu_grad_f(float a) {
   return 0.5f * (1.0f + erff(a * 0.70710678118654752440f)) + a * __expf(-0.5f * a * a) * 0.39894228040143267794f;
 }
-__device__ __forceinline__ void load4(const float* p, float (&o)[4]) {
-  const float4 t = *reinterpret_cast<const float4*>(p);
-  o[0] = t.x; o[1] = t.y; o[2] = t.z; o[3] = t.w;
-}
 __device__ __forceinline__ void store4(float* p, const float (&v)[4]) {
   *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
 }
 
-// four consecutive columns of a row of the result
-__device__ __forceinline__ void finish(const GemmArgs& g, long batch, int split, long row, long col, float (&v)[4]) {
-  if (row >= g.M || col >= g.N) return;
-  const long off = row * g.ldc + col;
-  float* C = reinterpret_cast<float*>(g.C);
-  if (g.split_k > 1) { store4(C + ((long)split * g.batch + batch) * g.c_sb + off, v); return; }
-  if (g.addf) {
-    float t[4];
-    load4(g.addf + batch * g.addf_sb + off, t);
-#pragma unroll
-    for (int x = 0; x < 4; ++x) v[x] += t[x];
+// four consecutive columns of a row of the result: what is fused into them is asked for (early: the operands' trip hides it) ...
+struct Fused {
+  float4v aux, lam, add;
+  bool in;
+  long off;
+  __device__ __forceinline__ void ask(const GemmArgs& g, long batch, long row, long col) {
+    in = row < g.M && col < g.N;
+    off = row * g.ldc + col;
+    aux = add = float4v{0.f, 0.f, 0.f, 0.f};
+    lam = float4v{1.f, 1.f, 1.f, 1.f};
+    if (!in || g.split_k > 1) return;
+    if (g.addf) add = *reinterpret_cast<const float4v*>(g.addf + batch * g.addf_sb + off);
+    if (g.mode == EPI_MUL_AUX || g.mode == EPI_MUL_1MZ2 || g.mode == EPI_RESID || g.mode == EPI_ADD_AUX)
+      aux = *reinterpret_cast<const float4v*>(reinterpret_cast<const float*>(g.aux) + batch * g.aux_sb + off);
+    if (g.mode == EPI_RESID && g.lambda_mn)
+      lam = *reinterpret_cast<const float4v*>(reinterpret_cast<const float*>(g.lambda_mn) + batch * g.aux_sb + off);
+    else if (g.mode == EPI_RESID && g.lambda) lam = *reinterpret_cast<const float4v*>(g.lambda + batch * g.lambda_sb + col);
   }
-  float t[4] = {0.f, 0.f, 0.f, 0.f};
-  if (g.mode == EPI_MUL_AUX || g.mode == EPI_MUL_1MZ2 || g.mode == EPI_RESID || g.mode == EPI_ADD_AUX)
-    load4(reinterpret_cast<const float*>(g.aux) + batch * g.aux_sb + off, t);
-  switch (g.mode) {
-    case EPI_MUL_AUX:
+  // ... and applied
+  __device__ __forceinline__ void finish(const GemmArgs& g, long batch, int split, float (&v)[4]) const {
+    if (!in) return;
+    float* C = reinterpret_cast<float*>(g.C);
+    if (g.split_k > 1) { store4(C + ((long)split * g.batch + batch) * g.c_sb + off, v); return; }
 #pragma unroll
-      for (int x = 0; x < 4; ++x) v[x] *= t[x];
-      break;
-    case EPI_MUL_1MZ2:
+    for (int x = 0; x < 4; ++x) v[x] += add[x];
+    switch (g.mode) {
+      case EPI_MUL_AUX:
 #pragma unroll
-      for (int x = 0; x < 4; ++x) v[x] *= (1.f - t[x] * t[x]);
-      break;
-    case EPI_ACT_GELU: {
-      float d[4];
+        for (int x = 0; x < 4; ++x) v[x] *= aux[x];
+        break;
+      case EPI_MUL_1MZ2:
 #pragma unroll
-      for (int x = 0; x < 4; ++x) { d[x] = gelu_grad_f(v[x]); v[x] = gelu_f(v[x]); }
-      store4(reinterpret_cast<float*>(g.out2) + batch * g.out2_sb + off, d);
-      break;
+        for (int x = 0; x < 4; ++x) v[x] *= (1.f - aux[x] * aux[x]);
+        break;
+      case EPI_ACT_GELU: {
+        float d[4];
+#pragma unroll
+        for (int x = 0; x < 4; ++x) { d[x] = gelu_grad_f(v[x]); v[x] = gelu_f(v[x]); }
+        store4(reinterpret_cast<float*>(g.out2) + batch * g.out2_sb + off, d);
+        break;
+      }
+      case EPI_ACT_TANH:
+#pragma unroll
+        for (int x = 0; x < 4; ++x) v[x] = tanhf(v[x]);
+        break;
+      case EPI_RESID:
+#pragma unroll
+        for (int x = 0; x < 4; ++x) v[x] = fmaf(lam[x], aux[x], v[x]);
+        break;
+      case EPI_ADD_AUX:
+#pragma unroll
+        for (int x = 0; x < 4; ++x) v[x] += aux[x];
+        break;
+      default: break;
     }
-    case EPI_ACT_TANH:
-#pragma unroll
-      for (int x = 0; x < 4; ++x) v[x] = tanhf(v[x]);
-      break;
-    case EPI_RESID: {
-      float l4[4] = {1.f, 1.f, 1.f, 1.f};
-      if (g.lambda_mn) load4(reinterpret_cast<const float*>(g.lambda_mn) + batch * g.aux_sb + off, l4);
-      else if (g.lambda) load4(g.lambda + batch * g.lambda_sb + col, l4);
-#pragma unroll
-      for (int x = 0; x < 4; ++x) v[x] = fmaf(l4[x], t[x], v[x]);
-      break;
-    }
-    case EPI_ADD_AUX:
-#pragma unroll
-      for (int x = 0; x < 4; ++x) v[x] += t[x];
-      break;
-    default: break;
+    store4(C + batch * g.c_sb + off, v);
   }
-  store4(C + batch * g.c_sb + off, v);
-}
+};
 
 template <int T, bool A_KC, bool B_KC>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
@@ -119,13 +149,10 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
   __shared__ __attribute__((aligned(16))) float red[SPLIT ? 4 : 1][32][36];
   const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const long batch = blockIdx.z / g.split_k;
-  const int split = (int)(blockIdx.z % g.split_k);
+  const long batch = blockIdx.z / (unsigned)g.split_k;
+  const int split = (int)(blockIdx.z % (unsigned)g.split_k);
   const long m0 = (long)blockIdx.y * T + (SPLIT ? 0 : 32 * (wave >> 1)), n0 = (long)blockIdx.x * T + (SPLIT ? 0 : 32 * (wave & 1));
-  const long m = m0 + r < g.M ? m0 + r : g.M - 1, n = n0 + r < g.N ? n0 + r : g.N - 1;
   const long lda = A_KC ? g.a_sm : g.a_sk, ldb = B_KC ? g.b_sn : g.b_sk;
-  const float* pa = reinterpret_cast<const float*>(g.A) + batch * g.a_sb + m * g.a_sm;
-  const float* pb = reinterpret_cast<const float*>(g.B) + batch * g.b_sb + n * g.b_sn;
   const long kchunk = ((g.K + g.split_k - 1) / g.split_k + 15) / 16 * 16;
   long k = (long)split * kchunk, k_end = k + kchunk < g.K ? k + kchunk : g.K;
   if (SPLIT) {              // this wavefront's quarter
@@ -133,31 +160,42 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
     k += wave * q;
     k_end = k + q < k_end ? k + q : k_end;
   }
+  // (a wavefront's block may lie outside the matrix as a whole: it computes the last row or column again and stores nothing)
+  const long ma = m0 < g.M ? m0 : g.M - 1, nb = n0 < g.N ? n0 : g.N - 1;
+  int left = k_end > k ? (int)(k_end - k) : 0;             // contraction indices to load
+  Operand<A_KC> A(reinterpret_cast<const float*>(g.A) + batch * g.a_sb, lda, ma, g.M - ma, left ? k : 0, r, h);
+  Operand<B_KC> B(reinterpret_cast<const float*>(g.B) + batch * g.b_sb, ldb, nb, g.N - nb, left ? k : 0, r, h);
   float16v acc;
 #pragma unroll
   for (int i = 0; i < 16; ++i) acc[i] = 0.f;
   float a0[CH / 2], b0[CH / 2], a1[CH / 2], b1[CH / 2];
-  auto load = [&](float (&a)[CH / 2], float (&b)[CH / 2], long k0) __attribute__((always_inline)) {
-    if (k0 + CH <= k_end) {
-      load_chunk<A_KC, false>(a, pa, lda, k0, k_end, h);
-      load_chunk<B_KC, false>(b, pb, ldb, k0, k_end, h);
+  auto load = [&](float (&a)[CH / 2], float (&b)[CH / 2]) __attribute__((always_inline)) {
+    if (left >= CH) {
+      A.template load<false>(a, left, h);
+      B.template load<false>(b, left, h);
     } else {
-      load_chunk<A_KC, true>(a, pa, lda, k0, k_end, h);
-      load_chunk<B_KC, true>(b, pb, ldb, k0, k_end, h);
+      A.template load<true>(a, left, h);
+      B.template load<true>(b, left, h);
     }
+    left -= CH;
   };
-  if (k < k_end) {
-    load(a0, b0, k);
-    while (true) {
-      if (k + CH < k_end) load(a1, b1, k + CH);
-      multiply(acc, a0, b0);
-      k += CH;
-      if (k >= k_end) break;
-      if (k + CH < k_end) load(a0, b0, k + CH);
-      multiply(acc, a1, b1);
-      k += CH;
-      if (k >= k_end) break;
-    }
+  int todo = left;          // ... and to multiply
+  const int row = tid >> 3, c0 = (tid & 7) * 4;            // SPLIT: this thread's piece of the result
+  Fused f[SPLIT ? 1 : 4];
+  if (left > 0) load(a0, b0);
+  if (SPLIT) {
+    f[0].ask(g, batch, m0 + row, n0 + c0);
+  } else {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) f[SPLIT ? 0 : q].ask(g, batch, m0 + r, n0 + 8 * q + 4 * h);
+  }
+  while (todo > 0) {
+    if (left > 0) load(a1, b1);
+    multiply(acc, a0, b0, todo);
+    if ((todo -= CH) <= 0) break;
+    if (left > 0) load(a0, b0);
+    multiply(acc, a1, b1, todo);
+    todo -= CH;
   }
   if (SPLIT) {
 #pragma unroll
@@ -165,19 +203,18 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
       *reinterpret_cast<float4*>(&red[SPLIT ? wave : 0][r][8 * q + 4 * h]) =
           make_float4(acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]);
     __syncthreads();
-    const int row = tid >> 3, c0 = (tid & 7) * 4;
     float v[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
       const float4 t = *reinterpret_cast<const float4*>(&red[SPLIT ? p : 0][row][c0]);
       v[0] += t.x; v[1] += t.y; v[2] += t.z; v[3] += t.w;
     }
-    finish(g, batch, split, m0 + row, n0 + c0, v);
+    f[0].finish(g, batch, split, v);
   } else {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       float v[4] = {acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
-      finish(g, batch, split, m0 + r, n0 + 8 * q + 4 * h, v);
+      f[SPLIT ? 0 : q].finish(g, batch, split, v);
     }
   }
 }
@@ -208,8 +245,8 @@ bool gemm_f32_ok(const GemmArgs& g) {
   return (g.M + 31) / 32 <= 65535 && g.batch * g.split_k <= 65535;
 }
 // 64-wide tiles once there are two per compute unit.  Measured, 32 / 64 wide: 128 tiles of 64 (512 x 128 x 512, batch 8)
-// 11.9 / 17.6 us, 384 (1000 x 200 x 808, batch 6) 49.1 / 57.0, 512 (512 x 512 x 128, batch 8) 18.5 / 14.3, 768 (1024 x
-// 256 x 1024, batch 12) 99.8 / 92.5, 3072 (1024 x 1024 x 256, batch 12) 133 / 104.
+// 10.7 / 16.8 us, 384 (1000 x 200 x 808, batch 6) 39.2 / 39.6, 440 (700 x 256 x 1024, batch 10) 46.6 / 49.3, 512 (512 x 512 x 128,
+// batch 8) 13.9 / 12.9, 768 (1024 x 256 x 1024, batch 12) 74.4 / 70.9, 3072 (1024 x 1024 x 256, batch 12) 99 / 92.
 hipError_t launch_gemm_f32(const GemmArgs& g, hipStream_t s) {
   const long tiles = (g.M + 63) / 64 * ((g.N + 63) / 64) * g.batch * g.split_k;
   return tiles >= 512 ? launch_pairing<64>(g, s) : launch_pairing<32>(g, s);
