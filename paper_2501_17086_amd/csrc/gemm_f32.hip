@@ -143,15 +143,16 @@ struct Fused {
   }
 };
 
+// one tile: column bx, row by, batch and share bz
 template <int T, bool A_KC, bool B_KC>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
+__device__ __forceinline__ void gemm_f32_body(const GemmArgs& g, unsigned bx, unsigned by, unsigned bz) {
   constexpr bool SPLIT = T == 32;
   __shared__ __attribute__((aligned(16))) float red[SPLIT ? 4 : 1][32][36];
   const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const long batch = blockIdx.z / (unsigned)g.split_k;
-  const int split = (int)(blockIdx.z % (unsigned)g.split_k);
-  const long m0 = (long)blockIdx.y * T + (SPLIT ? 0 : 32 * (wave >> 1)), n0 = (long)blockIdx.x * T + (SPLIT ? 0 : 32 * (wave & 1));
+  const long batch = bz / (unsigned)g.split_k;
+  const int split = (int)(bz % (unsigned)g.split_k);
+  const long m0 = (long)by * T + (SPLIT ? 0 : 32 * (wave >> 1)), n0 = (long)bx * T + (SPLIT ? 0 : 32 * (wave & 1));
   const long lda = A_KC ? g.a_sm : g.a_sk, ldb = B_KC ? g.b_sn : g.b_sk;
   const long kchunk = ((g.K + g.split_k - 1) / g.split_k + 15) / 16 * 16;
   long k = (long)split * kchunk, k_end = k + kchunk < g.K ? k + kchunk : g.K;
@@ -220,6 +221,18 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
 }
 
 template <int T, bool A_KC, bool B_KC>
+__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
+  gemm_f32_body<T, A_KC, B_KC>(g, blockIdx.x, blockIdx.y, blockIdx.z);
+}
+// several products' tiles in one list (both operands with contiguous rows)
+template <int T>
+__global__ __launch_bounds__(256) void gemm_f32_group_kernel(GemmGroup q) {
+  const int t = (int)blockIdx.x, i = q.of(t);
+  const unsigned r = (unsigned)(t - q.start[i]), tn = (unsigned)q.tiles_n[i], row = r / tn, tm = (unsigned)q.tiles_m[i], z = row / tm;
+  gemm_f32_body<T, false, false>(q.g[i], r - row * tn, row - z * tm, z);
+}
+
+template <int T, bool A_KC, bool B_KC>
 hipError_t launch_one(const GemmArgs& g, hipStream_t s) {
   const dim3 grid((unsigned)((g.N + T - 1) / T), (unsigned)((g.M + T - 1) / T), (unsigned)(g.batch * g.split_k));
   hipLaunchKernelGGL((gemm_f32_kernel<T, A_KC, B_KC>), grid, dim3(256), 0, s, g);
@@ -250,6 +263,22 @@ bool gemm_f32_ok(const GemmArgs& g) {
 hipError_t launch_gemm_f32(const GemmArgs& g, hipStream_t s) {
   const long tiles = (g.M + 63) / 64 * ((g.N + 63) / 64) * g.batch * g.split_k;
   return tiles >= 512 ? launch_pairing<64>(g, s) : launch_pairing<32>(g, s);
+}
+// parameter gradients that fill the chip together at most (32-wide tiles by the line above)
+bool launch_gemm_f32_group(const GemmArgs* g, int n, hipStream_t s, hipError_t* err) {
+  *err = hipSuccess;
+  if (n < 2 || n > GEMM_GROUP) return false;
+  long tiles = 0;
+  for (int i = 0; i < n; ++i) {
+    if (!gemm_f32_ok(g[i]) || g[i].a_sm != 1 || g[i].b_sn != 1 || g[i].a_sk == 1 || g[i].b_sk == 1) return false;
+    tiles += (g[i].M + 63) / 64 * ((g[i].N + 63) / 64) * g[i].batch * g[i].split_k;
+  }
+  if (tiles >= 512) return false;
+  GemmGroup q;
+  if (!make_group(q, g, n, 32, 32)) return false;
+  hipLaunchKernelGGL(gemm_f32_group_kernel<32>, dim3((unsigned)q.total), dim3(256), 0, s, q);
+  *err = hipGetLastError();
+  return true;
 }
 
 }  // namespace hbp

@@ -723,8 +723,9 @@ inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 
 
 }  // namespace
 
-bool launch_gemm_mfma(const GemmArgs& g, hipStream_t s, hipError_t* err) {
-  *err = hipSuccess;
+namespace {
+// the layouts, sizes and alignments that the bf16 kernels take
+bool covered(const GemmArgs& g) {
   const bool a_kc = g.a_sk == 1, a_rc = g.a_sm == 1;
   const bool b_kc = g.b_sk == 1, b_rc = g.b_sn == 1;
   if (!(a_kc || a_rc) || !(b_kc || b_rc)) return false;
@@ -740,22 +741,56 @@ bool launch_gemm_mfma(const GemmArgs& g, hipStream_t s, hipError_t* err) {
   if (g.split_k > 1 && g.mode != EPI_STORE) return false;
   if (g.M <= 0 || g.N <= 0 || g.K <= 0 || g.batch <= 0 || g.split_k <= 0) return false;
   const bool act = g.mode == EPI_ACT_GELU || g.mode == EPI_ACT_TANH;
-  if (!(a_kc && (b_kc || (b_rc && !act))) && !(a_rc && b_rc && !act)) return false;
+  return (a_kc && (b_kc || (b_rc && !act))) || (a_rc && b_rc && !act);
+}
+// whether the 256 x 256 kernel takes the launch: whole, or (sizes that are no multiple of its tile) the whole tiles of it
+enum Lean { LEAN_NOT, LEAN_WHOLE, LEAN_PART };
+Lean lean_share(const GemmArgs& g) {
+  const bool a_kc = g.a_sk == 1, b_kc = g.b_sk == 1;
   // (a fused operand is asked for two slices before a tile's end, the first two being waited for otherwise: four at least)
-  if (has_lean(g, a_kc, b_kc) && g.K % BK == 0 && g.K / BK >= g.split_k && (g.mode == EPI_STORE || g.K >= 4 * BK)) {
+  if (!has_lean(g, a_kc, b_kc) || g.K % BK != 0 || g.K / BK < g.split_k || (g.mode != EPI_STORE && g.K < 4 * BK)) return LEAN_NOT;
+  const long hm = g.M / BM * BM, hn = g.N / BN * BN;
+  const long tiles = (hm / BM) * (hn / BN) * g.batch * g.split_k;
+  if (hm == g.M && hn == g.N) return gemm_fills_chip(tiles) ? LEAN_WHOLE : LEAN_NOT;
+  return tiles >= GEMM_SPLIT_FROM ? LEAN_PART : LEAN_NOT;
+}
+}  // namespace
+
+bool launch_gemm_mfma(const GemmArgs& g, hipStream_t s, hipError_t* err) {
+  *err = hipSuccess;
+  if (!covered(g)) return false;
+  const bool a_kc = g.a_sk == 1, b_kc = g.b_sk == 1;
+  const Lean lean = lean_share(g);
+  if (lean == LEAN_WHOLE) {
+    *err = launch_lean_for(g, a_kc, b_kc, s);
+  } else if (lean == LEAN_PART) {
+    // the whole tiles, then the remaining columns of all rows, then the remaining rows (disjoint blocks of C)
     const long hm = g.M / BM * BM, hn = g.N / BN * BN;
-    const long tiles = (hm / BM) * (hn / BN) * g.batch * g.split_k;
-    if (hm == g.M && hn == g.N) {
-      if (gemm_fills_chip(tiles)) { *err = launch_lean_for(g, a_kc, b_kc, s); return true; }
-    } else if (tiles >= GEMM_SPLIT_FROM) {
-      // the whole tiles, then the remaining columns of all rows, then the remaining rows (disjoint blocks of C)
-      *err = launch_lean_for(part_of(g, 0, hm, 0, hn), a_kc, b_kc, s);
-      if (*err == hipSuccess && hn < g.N) *err = launch_tile_for(part_of(g, 0, g.M, hn, g.N), s);
-      if (*err == hipSuccess && hm < g.M) *err = launch_tile_for(part_of(g, hm, g.M, 0, hn), s);
-      return true;
-    }
+    *err = launch_lean_for(part_of(g, 0, hm, 0, hn), a_kc, b_kc, s);
+    if (*err == hipSuccess && hn < g.N) *err = launch_tile_for(part_of(g, 0, g.M, hn, g.N), s);
+    if (*err == hipSuccess && hm < g.M) *err = launch_tile_for(part_of(g, hm, g.M, 0, hn), s);
+  } else {
+    *err = launch_tile_for(g, s);
   }
-  *err = launch_tile_for(g, s);
+  return true;
+}
+
+// the tiles as for one product with all of their tiles (launch_tile_for)
+bool launch_gemm_mfma_group(const GemmArgs* g, int n, hipStream_t s, hipError_t* err) {
+  *err = hipSuccess;
+  if (n < 2 || n > GEMM_GROUP) return false;
+  long t128 = 0, t3232 = 0, t6432 = 0;
+  for (int i = 0; i < n; ++i) {
+    if (!covered(g[i]) || lean_share(g[i]) != LEAN_NOT || g[i].b_sn != 1 || (g[i].a_sk == 1) != (g[0].a_sk == 1)) return false;
+    if (g[i].b_sk == 1 || (g[i].a_sk == 1 && g[i].a_sm == 1)) return false;       // (a single column: either layout)
+    auto tiles = [&g, i](long tm, long tn) { return (g[i].M + tm - 1) / tm * ((g[i].N + tn - 1) / tn) * g[i].batch * g[i].split_k; };
+    t128 += tiles(128, 128); t3232 += tiles(32, 32); t6432 += tiles(64, 32);
+  }
+  if (t128 > (1L << 24)) return false;
+  *err = t128 >= 192     ? launch_gemm_tile_group(g, n, 128, 128, s)
+         : t3232 <= 256  ? launch_gemm_tile_group(g, n, 32, 32, s)
+         : t6432 <= 256  ? launch_gemm_tile_group(g, n, 64, 32, s)
+                         : launch_gemm_tile_group(g, n, 64, 64, s);
   return true;
 }
 

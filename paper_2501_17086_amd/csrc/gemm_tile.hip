@@ -118,9 +118,9 @@ __device__ __forceinline__ void finish8(const GemmArgs& g, long batch, int split
 }
 
 // T x T output tile per workgroup, a ring of NST stages, WGS workgroups per compute unit.  ACT: the forward's activations (kept
-// out of the other kernels' registers).
-template <int T, int BK, int NST, int WGS, bool A_KC, bool B_KC, bool ACT>
-__global__ __launch_bounds__(NTHR, WGS) void gemm_tile_kernel(GemmArgs g, int tiles_m, int tiles_n, int total, int per_xcd) {
+// out of the other kernels' registers).  t: the tile's number in the product's list.
+template <int T, int BK, int NST, bool A_KC, bool B_KC, bool ACT>
+__device__ __forceinline__ void gemm_tile_body(const GemmArgs& g, int tiles_m, int tiles_n, int t) {
   typedef Tile<T, BK, A_KC> TA;
   typedef Tile<T, BK, B_KC> TB;
   constexpr int STAGE = TA::BYTES + TB::BYTES;
@@ -132,9 +132,6 @@ __global__ __launch_bounds__(NTHR, WGS) void gemm_tile_kernel(GemmArgs g, int ti
   const int wm0 = (wave >> 1) * W, wn0 = (wave & 1) * W;
   const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
 
-  // ids are dealt to the 8 XCDs in turn: each takes a contiguous eighth of the tile list, in blocks of 8 tile rows
-  const int t = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
-  if (t >= total) return;
   const unsigned tiles_mn = (unsigned)tiles_m * tiles_n;
   const unsigned zb = (unsigned)t / tiles_mn, rem = (unsigned)t - zb * tiles_mn;
   const unsigned gr = rem / (8u * tiles_n), in_gr = rem - gr * 8u * tiles_n;
@@ -266,13 +263,29 @@ __global__ __launch_bounds__(NTHR, WGS) void gemm_tile_kernel(GemmArgs g, int ti
   }
 }
 
+// ids are dealt to the 8 XCDs in turn: each takes a contiguous eighth of the tile list, in blocks of 8 tile rows
+__device__ __forceinline__ int tile_of_id(int per_xcd) { return (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3); }
+template <int T, int BK, int NST, int WGS, bool A_KC, bool B_KC, bool ACT>
+__global__ __launch_bounds__(NTHR, WGS) void gemm_tile_kernel(GemmArgs g, int tiles_m, int tiles_n, int total, int per_xcd) {
+  const int t = tile_of_id(per_xcd);
+  if (t < total) gemm_tile_body<T, BK, NST, A_KC, B_KC, ACT>(g, tiles_m, tiles_n, t);
+}
+// several products' tiles in one list
+template <int T, int BK, int NST, int WGS, bool A_KC, bool B_KC>
+__global__ __launch_bounds__(NTHR, WGS) void gemm_tile_group_kernel(GemmGroup q) {
+  const int t = tile_of_id(q.per_xcd);
+  if (t >= q.total) return;
+  const int i = q.of(t);
+  gemm_tile_body<T, BK, NST, A_KC, B_KC, false>(q.g[i], q.tiles_m[i], q.tiles_n[i], t - q.start[i]);
+}
+
 // Launches of few tiles: a workgroup of four wavefronts owns TM x 32 of C and the wavefronts share the contraction out, each
 // taking every fourth slice of 64 through an LDS ring of its own (no barrier in the loop); the four sums meet in LDS.
 // What bounds such a launch is the time a compute unit takes to stream its tile's operands, about 64 KB of requests in flight over
 // their latency.  Here 96 KB are asked for ahead (the 64 x 64 kernel: 48), over more compute units: 1200 x 256 x 1024 8.3 -> 6.2
 // us, 54 GB/s per compute unit.  The fused operand is asked for before the first slice.
 template <int TM, int STG, bool A_KC, bool B_KC, bool ACT>
-__global__ __launch_bounds__(NTHR, 1) void gemm_small_kernel(GemmArgs g, int tiles_m, int tiles_n, int total, int per_xcd) {
+__device__ __forceinline__ void gemm_small_body(const GemmArgs& g, int tiles_m, int tiles_n, int t) {
   constexpr int TN = 32, BK = 64, NB = TM / 32;
   typedef Tile<TM, BK, A_KC, 1> TA;
   typedef Tile<TN, BK, B_KC, 1> TB;
@@ -285,8 +298,6 @@ __global__ __launch_bounds__(NTHR, 1) void gemm_small_kernel(GemmArgs g, int til
   const unsigned lds0 = (unsigned)__builtin_amdgcn_readfirstlane(
       (int)(unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)ring);
 
-  const int t = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);    // (dealt as above)
-  if (t >= total) return;
   const unsigned tiles_mn = (unsigned)tiles_m * tiles_n;
   const unsigned zb = (unsigned)t / tiles_mn, rem = (unsigned)t - zb * tiles_mn;
   const unsigned gr = rem / (8u * tiles_n), in_gr = rem - gr * 8u * tiles_n;
@@ -405,6 +416,19 @@ __global__ __launch_bounds__(NTHR, 1) void gemm_small_kernel(GemmArgs g, int til
   finish8<ACT>(g, batch, split, off, use_aux, v, ra, lm);
 }
 
+template <int TM, int STG, bool A_KC, bool B_KC, bool ACT>
+__global__ __launch_bounds__(NTHR, 1) void gemm_small_kernel(GemmArgs g, int tiles_m, int tiles_n, int total, int per_xcd) {
+  const int t = tile_of_id(per_xcd);
+  if (t < total) gemm_small_body<TM, STG, A_KC, B_KC, ACT>(g, tiles_m, tiles_n, t);
+}
+template <int TM, int STG, bool A_KC, bool B_KC>
+__global__ __launch_bounds__(NTHR, 1) void gemm_small_group_kernel(GemmGroup q) {
+  const int t = tile_of_id(q.per_xcd);
+  if (t >= q.total) return;
+  const int i = q.of(t);
+  gemm_small_body<TM, STG, A_KC, B_KC, false>(q.g[i], q.tiles_m[i], q.tiles_n[i], t - q.start[i]);
+}
+
 template <int T, int BK, int NST, int WGS, bool A_KC, bool B_KC, bool ACT>
 hipError_t launch_one(const GemmArgs& g, hipStream_t s) {
   auto kern = gemm_tile_kernel<T, BK, NST, WGS, A_KC, B_KC, ACT>;
@@ -457,8 +481,42 @@ hipError_t launch_small(const GemmArgs& g, hipStream_t s) {
   return a_kc ? launch_small_one<TM, STG, true, false, false>(g, s) : launch_small_one<TM, STG, false, false, false>(g, s);
 }
 
+template <typename K>
+hipError_t launch_group(K kern, int lds, std::atomic<bool> (&attr_set)[MAX_DEVICES], const GemmGroup& q, hipStream_t s) {
+  if (lds > 65536) {
+    const hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kern), lds, attr_set);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(kern, dim3((unsigned)(8 * q.per_xcd)), dim3(NTHR), lds, s, q);
+  return hipGetLastError();
+}
+template <int T, int BK, int NST, int WGS>
+hipError_t launch_tile_group(const GemmGroup& q, hipStream_t s) {
+  static std::atomic<bool> attr_set[2][MAX_DEVICES];
+  constexpr int lds = NST * 2 * T * BK * 2;
+  if (q.g[0].a_sk == 1) return launch_group(gemm_tile_group_kernel<T, BK, NST, WGS, true, false>, lds, attr_set[0], q, s);
+  if constexpr (WGS == 3) return hipErrorInvalidValue;
+  else return launch_group(gemm_tile_group_kernel<T, BK, NST, WGS, false, false>, lds, attr_set[1], q, s);
+}
+template <int TM, int STG>
+hipError_t launch_small_group(const GemmGroup& q, hipStream_t s) {
+  static std::atomic<bool> attr_set[2][MAX_DEVICES];
+  constexpr int lds = 4 * STG * (TM + 32) * 64 * 2;
+  return q.g[0].a_sk == 1 ? launch_group(gemm_small_group_kernel<TM, STG, true, false>, lds, attr_set[0], q, s)
+                          : launch_group(gemm_small_group_kernel<TM, STG, false, false>, lds, attr_set[1], q, s);
+}
+
 }  // namespace
 
+// (B with contiguous rows; the lines are those of launch_gemm_tile below)
+hipError_t launch_gemm_tile_group(const GemmArgs* g, int n, int tm, int tn, hipStream_t s) {
+  GemmGroup q;
+  if (!make_group(q, g, n, tm, tn)) return hipErrorInvalidValue;
+  if (tn == 32) return tm == 32 ? launch_small_group<32, 4>(q, s) : launch_small_group<64, 3>(q, s);
+  if (tm == 64) return launch_tile_group<64, 64, 4, 2>(q, s);
+  if (q.total <= 256) return launch_tile_group<128, 64, 4, 1>(q, s);
+  return q.total >= 512 && g[0].a_sk == 1 ? launch_tile_group<128, 32, 3, 3>(q, s) : launch_tile_group<128, 32, 4, 2>(q, s);
+}
 hipError_t launch_gemm_tile(const GemmArgs& g, int tm, int tn, hipStream_t s) {
   if (tn == 32) return tm == 32 ? launch_small<32, 4>(g, s) : launch_small<64, 3>(g, s);
   if (tm == 64) return launch_pairing<64, 64, 4, 2>(g, s);

@@ -162,6 +162,38 @@ inline bool gemm_fills_chip(long tiles) { return tiles * 100 >= (tiles + 255) / 
 // the tile kernel in launches of its own; below, everything to the tile kernel (3000 x 1000 x 4000, batch 4, 132 whole
 // tiles: 163 us in parts, 122 us whole).
 constexpr long GEMM_SPLIT_FROM = 512;
+// Products of one pairing of layouts (both operands of each with the same index contiguous) that do not depend on each other, in one
+// launch: where all of them go to the kernels for few tiles, a launch costs more than a product's share of the chip does.  False, with
+// nothing done, where that is not so.
+constexpr int GEMM_GROUP = 4;
+struct GemmGroup {
+  GemmArgs g[GEMM_GROUP];
+  int start[GEMM_GROUP];      // first tile of each in the launch's list (past the last product: past the last tile)
+  int tiles_m[GEMM_GROUP], tiles_n[GEMM_GROUP];
+  int total, per_xcd;
+  __device__ __forceinline__ int of(int t) const { return (t >= start[1]) + (t >= start[2]) + (t >= start[3]); }
+};
+// n products in tiles of tm x tn; false: too many tiles
+inline bool make_group(GemmGroup& q, const GemmArgs* g, int n, int tm, int tn) {
+  long total = 0;
+  for (int i = 0; i < GEMM_GROUP; ++i) {
+    q.g[i] = g[i < n ? i : n - 1];
+    q.start[i] = (int)total;
+    if (i >= n) continue;
+    const long m = (g[i].M + tm - 1) / tm, c = (g[i].N + tn - 1) / tn;
+    q.tiles_m[i] = (int)m;
+    q.tiles_n[i] = (int)c;
+    total += m * c * g[i].batch * g[i].split_k;
+    if (total > (1L << 28)) return false;
+  }
+  for (int i = n; i < GEMM_GROUP; ++i) { q.start[i] = (int)total; q.tiles_m[i] = q.tiles_n[i] = 1; }
+  q.total = (int)total;
+  q.per_xcd = (int)((total + 7) / 8);
+  return true;
+}
+bool launch_gemm_mfma_group(const GemmArgs* g, int n, hipStream_t s, hipError_t* err);
+bool launch_gemm_f32_group(const GemmArgs* g, int n, hipStream_t s, hipError_t* err);
+hipError_t launch_gemm_tile_group(const GemmArgs* g, int n, int tm, int tn, hipStream_t s);
 // fast bf16 MFMA path; returns false when the shape/layout is not covered
 bool launch_gemm_mfma(const GemmArgs& g, hipStream_t s, hipError_t* err);
 // the same contractions on tiles of 128 x 128, 64 x 64, 64 x 32 or 32 x 32, any size (called through launch_gemm_mfma, which

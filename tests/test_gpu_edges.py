@@ -44,6 +44,18 @@ def test_products_of_few_tiles(B, N, d, d_ff):
     _check_backward(B, w, p, st, sv, inp, w.name)
 
 
+# several products in one launch (a transformer's first and second contractions in pairs, its four parameter gradients), on each kind
+# of tile: 32 x 32, 64 x 32, 64 x 64 and 128 x 128, products of one tile beside larger ones, sizes that end inside a tile and a slice
+@pytest.mark.parametrize("dtype,N,T,d,d_ff", [("bf16", 9, 9, 16, 8), ("bf16", 40, 8, 64, 72), ("bf16", 200, 40, 136, 264),
+                                              ("bf16", 520, 40, 200, 1032), ("bf16", 1000, 40, 264, 1096), ("bf16", 2960, 40, 520, 2056),
+                                              ("f32", 9, 9, 16, 8), ("f32", 120, 40, 72, 264)])
+def test_products_in_one_launch(B, dtype, N, T, d, d_ff):
+    w = synth.scaled(W["gpt2_paper"], name=f"tfm_{dtype}_{N}_{d}_{d_ff}", L=4, N=N, seq_len=T, d=d, heads=1 if d < 64 else d // 8,
+                     d_ff=d_ff, dtype=dtype, w1_std=0.0, w2_std=0.0, w2_scale=0.6, ks=(1, 2))
+    inp, st, sv, p = _forward_matches(B, w)
+    _check_backward(B, w, p, st, sv, inp, w.name, exact=False)
+
+
 # 128 x 128 tiles with contractions that end inside a slice: 192 to 256 of them (slices of 64: the block VJPs of the first, the
 # forward of the second, the parameter gradients of the last), 400 and 450 (four stages), 512 and more (three workgroups per
 # compute unit: the VJPs of the third, the forward of the fourth)
