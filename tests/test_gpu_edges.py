@@ -120,6 +120,17 @@ def test_chains_along_time(B, kind, L, N, H):
     _check_backward(B, w, p, st, sv, inp, w.name)
 
 
+# the fifth wavefront's reading ahead: chains shorter and longer than the four steps it is ahead by, widths whose last block of 32 channels
+# and last piece of 16 inputs end inside, the rows past the batch, with and without it (the gated cell's two rows; width 1024)
+@pytest.mark.parametrize("kind,L,N,H", [("rnn", 12, 3, 8), ("rnn", 13, 33, 504), ("token", 17, 3, 264), ("gated", 16, 2, 24),
+                                        ("gated", 16, 3, 24), ("gated", 12, 17, 1000), ("lstm", 15, 9, 488), ("gru", 12, 65, 56),
+                                        ("gru", 14, 7, 504)])
+def test_chains_that_read_ahead(B, kind, L, N, H):
+    w = _chain(kind, L, N, H)
+    inp, st, sv, p = _forward_matches(B, w)
+    _check_backward(B, w, p, st, sv, inp, w.name)
+
+
 @pytest.mark.parametrize("d,d_ff,act", [(40, 296, "tanh"), (296, 40, "tanh"), (64, 64, "identity")])
 def test_chains_along_time_of_two_widths(B, d, d_ff, act):
     w = synth.scaled(W["gated_rnn_contractive"], name=f"rnn_{d}_{d_ff}_{act}", L=7, N=20, d=d, d_ff=d_ff, d_in=16, act=act,
