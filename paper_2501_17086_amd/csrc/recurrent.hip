@@ -38,7 +38,9 @@
 // 6.0 / 0.85, 1.18, 2.42, 3.7, of the GRU 1.77, 1.99, 2.29, 4.6 / 1.11, 1.21, 3.3, 6.6, of the LSTM 1.67, 1.83, 2.18, 4.3 / 1.42,
 // 1.55, 3.6, 7.2; exact backpropagation of the RNN 1.63, 2.21, 4.22, 7.0 / 0.84, 1.12, 2.20, 3.5, of the GRU 1.95, 2.32, 2.55, 5.1 /
 // 0.98, 1.16, 3.0, 5.0; 64 rows, forward of the RNN 2.17, 2.51, 2.77, 5.5 / 0.88, 1.37, 2.67, 7.7, of the GRU 2.69, 2.90, 3.33, 9.1 /
-// 1.18, 2.27, 4.5, 9.2.  One or two calls gain in every kind; from three on the wide GRU and LSTM lose, by 1.75 times at most.
+// 1.18, 2.27, 4.5, 9.2.  One or two calls gain in every kind; from three on the wide GRU and LSTM lose, by 1.75 times at most.  Where a fifth
+// wavefront reads ahead (read_ahead) a second workgroup no longer fits beside the first: without / with it, gated cell 32 x 1024 0.83, 1.37,
+// 2.2, 3.8 / 0.75, 0.84, 2.6, 4.7, LSTM 64 x 512 1.21, 1.66, 2.0, 3.9 / 1.02, 1.10, 2.3, 4.4, GRU 64 x 512 1.01, 1.67, 1.8, 3.6 / 0.95, 1.11, 2.2, 5.8.
 //
 // Measured (1024 steps, batch 32, width 1024): exact backpropagation of the RNN 14.5 ms as launches of their own, 3.3 through
 // memory, 1.7 on one XCD with groups of 8 rows; forward of the GRU 20.9, 3.6 and 2.4.  0.8 us per dependent product: about 0.4 from
