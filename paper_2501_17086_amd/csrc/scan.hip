@@ -1063,10 +1063,12 @@ inline bool seg_covers(const ScanArgs& a) {
 // thread per vector up to 255 states, from 256 on chunks) / this one, bf16 with a value stream: 2 states of 100 x 128 2.7 / 2.2, of 1000
 // x 512 3.1 / 5.1; 8 of 100 x 128 5.6 / 2.3, of 500 x 512 6.0 / 4.1; 12 of 1000 x 512 9.1 / 7.8 (without a stream 7.0 / 7.2); 24 of 1000 x
 // 512 17.3 / 12.1 (11.1 / 10.2); 100 of 32 x 512 70 / 5; 300 of 64 x 1024 63 / 16; beyond: 24 of 2000 x 512 22 / 20, 32 of 8192 x 512 129 / 144,
-// 12 of 16384 x 1024 166 / 218, 300 of 1024 x 1024 332 / 347.
+// 12 of 16384 x 1024 166 / 218, 300 of 1024 x 1024 332 / 347; the longest in bf16: 4096 of 32 x 2048 316 / 292, of 64 x 2048 597 / 699 (fp32, by
+// three passes before, 4096 of 32 x 2048 1136 / 656).
+template <typename T>
 inline bool seg_pays(const ScanArgs& a) {
-  const long L = a.l_hi - a.l_lo;
-  return L >= 2 && a.N * a.d <= (L < 16 ? 32768 * L : 1L << 19);
+  const long L = a.l_hi - a.l_lo, n = a.N * a.d;
+  return L >= 2 && n <= (L < 16 ? 32768 * L : 1L << 19) && (sizeof(T) == 4 || L * n <= (1L << 28));
 }
 template <typename T, int LAMK, int NSRC, int S, int SEG_N>
 hipError_t launch_seg_as(const ScanArgs& a, hipStream_t s) {
@@ -1089,15 +1091,18 @@ hipError_t launch_seg(const ScanArgs& a, hipStream_t s) {
     default: return launch_seg_as<T, 2, 2, S, SEG_N>(a, s);
   }
 }
-// As many segments at a time as keep their walk short beside the rest: 8 of one state for 8 states, 8 of two for up to 32 or above
-// 65536 elements, else 32 of two; 64 of four for the fewest chains.  Measured, us, 8 x 1 / 8 x 2 / 32 x 2 / 64 x 4: 8 states of 1000 x 512
-// 5.8 / 7.2 / 18.5 / -, 24 of 64 x 512 3.5 / 3.3 / 3.4 / -, of 256 x 512 5.1 / 4.9 / 7.1 / -, 100 of 64 x 512 8.9 / 7.0 / 5.2 / 8.6, of 256 x 1024
-// 22 / 19 / 23 / 54, 1024 of 32 x 200 59 / 39 / 18.4 / 12.9, of 32 x 600 65 / 46 / 25 / 27.
+// As many segments at a time as keep their walk short beside the rest: 8 of one state for 8 states, 8 of two for up to 32 or where the
+// elements fill the chip by themselves, else 32 of two; 64 of four for the fewest chains.  Measured, us, 8 x 1 / 8 x 2 / 32 x 2 / 64 x 4: 8
+// states of 1000 x 512 5.8 / 7.2 / 18.5 / -, 24 of 64 x 512 3.5 / 3.3 / 3.4 / -, of 256 x 512 5.1 / 4.9 / 7.1 / -, 100 of 64 x 512 8.9 / 7.0 / 5.2 /
+// 8.6, of 256 x 1024 22 / 19 / 23 / 54, 1024 of 32 x 200 59 / 39 / 18.4 / 12.9, of 32 x 600 65 / 46 / 25 / 27.  8 x 2 / 32 x 2 with coefficients
+// per channel | per token: 1024 of 32 x 1024 45 / 24 | 46 / 32, 2048 of 32 x 1536 122 / 104 | 125 / 134, 1024 of 64 x 1024 66 / 61 | 74 / 88, 2048
+// of 64 x 1024 127 / 137 | 145 / 176, 4096 of 32 x 1024 213 / 134 | 212 / 170, of 32 x 2048 252 / 279 | 292 / 348.
 template <typename T>
 hipError_t launch_seg_for(const ScanArgs& a, hipStream_t s) {
   const long L = a.l_hi - a.l_lo, n = a.N * a.d;
   if (L <= 8) return launch_seg<T, 1, 8>(a, s);
-  if (L <= 32 || n > 65536) return launch_seg<T, 2, 8>(a, s);
+  const bool fills = n > 65536 || (n >= 49152 && a.lambda_tok) || (n == 65536 && L >= 2048);
+  if (L <= 32 || fills) return launch_seg<T, 2, 8>(a, s);
   return L > 256 && n <= 12288 ? launch_seg<T, 4, 64>(a, s) : launch_seg<T, 2, 32>(a, s);
 }
 
@@ -1126,7 +1131,7 @@ hipError_t launch_scan_t(const ScanArgs& args, hipStream_t s) {
     e = seed();
     return e == hipSuccess ? launch_scan_chunked<T>(a, s) : e;
   }
-  if (a.force == 0 && seg_covers(a) && seg_pays(a)) return launch_seg_for<T>(a, s);
+  if (a.force == 0 && seg_covers(a) && seg_pays<T>(a)) return launch_seg_for<T>(a, s);
   if (a.force == 0 && !a.mask && a.chunk_ws && use_chunked(a.l_hi - a.l_lo, a.N, a.d, rms)) {
     e = seed();
     if (e != hipSuccess) return e;

@@ -454,7 +454,8 @@ def test_row_norms(B, d, N, post):
 # (8 of one state, 8 of two, 32 of two, 64 of four), 64-channel slabs that end inside, and the first sizes that keep other forms
 @pytest.mark.parametrize("L,N,d", [(1, 3, 40), (2, 1, 8), (8, 9, 40), (9, 5, 56), (16, 3, 8), (17, 7, 72), (31, 129, 520), (7, 300, 720), (7, 320, 720), (33, 9, 40),
                                    (64, 3, 104), (65, 20, 200), (130, 64, 512), (257, 33, 2048), (256, 3, 72), (257, 5, 8),
-                                   (513, 2, 136), (1100, 1, 64), (40, 513, 1024), (20, 1030, 1024)])
+                                   (513, 2, 136), (1100, 1, 64), (40, 513, 1024), (20, 1030, 1024), (40, 24, 2048),
+                                   (35, 32, 2048)])
 @pytest.mark.parametrize("dtype,lam,every,gamma", [("bf16", "token", True, 0.0), ("bf16", "channel", True, 0.3),
                                                    ("bf16", "one", False, 0.02), ("f32", "channel", False, 0.0),
                                                    ("f32", "token", True, 0.0), ("f32", "one", True, 0.1)])
