@@ -23,6 +23,7 @@
 // Everything else (fp32 storage, wider heads) takes plain one-wavefront-per-query (per-key) kernels.
 #include "hbp_common.h"
 
+#include <cfloat>
 #include <type_traits>
 
 namespace hbp {
@@ -700,7 +701,8 @@ __global__ __launch_bounds__(64 * AT_WAVES, SHARED ? 1 : 2) void attn_fwd_mfma_k
   for (int kk = 0; kk < G::KK; ++kk) landed(fq[kk]);
   float16v o[G::MB];
   zero_acc(o);
-  float m = -INFINITY, l = 0.f;
+  // (the row's maximum starts from the lowest finite number: a first tile whose scores are all minus infinity weighs nothing then)
+  float m = -FLT_MAX, l = 0.f;
   // one tile of 32 keys; MASKED: the tile on the diagonal (causal) or the one that runs past the last key
   auto step = [&](int i, auto masked_c) __attribute__((always_inline)) {
     constexpr bool MASKED = decltype(masked_c)::value;
@@ -733,7 +735,7 @@ __global__ __launch_bounds__(64 * AT_WAVES, SHARED ? 1 : 2) void attn_fwd_mfma_k
       tmax = fmaxf(tmax, sv[r]);
     }
     tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
-    const float mn = fmaxf(m, tmax);          // finite: every tile has a key its queries may see
+    const float mn = fmaxf(m, tmax);
     const float alpha = fast_exp2(m - mn);
     float ps = 0.f;
 #pragma unroll
@@ -783,13 +785,14 @@ __global__ __launch_bounds__(64 * AT_WAVES, SHARED ? 1 : 2) void attn_fwd_mfma_k
     for (int w = 1; w < AT_WAVES; ++w) top = fmaxf(top, rows[2 * w * 64 + lane]);
     l = 0.f;
 #pragma unroll
-    for (int w = 0; w < AT_WAVES; ++w) {                           // (a wavefront without a tile: m = -inf, f = 0)
+    for (int w = 0; w < AT_WAVES; ++w) {                           // (a wavefront without a tile: sums of zero)
       f[w] = fast_exp2(rows[2 * w * 64 + lane] - top);
       l = fmaf(f[w], rows[(2 * w + 1) * 64 + lane], l);
     }
     m = top;
     meet_sums(o, reinterpret_cast<float*>(smem), wave, lane, f);
   }
+  if (!(l > 0.f)) l = NAN;                                         // no score above minus infinity: NaN, as the plain kernel has it
   if (SHARED ? wave == 0 : live) {
     store_tile(reinterpret_cast<bf16_t*>(reinterpret_cast<unsigned char*>(a.o) + hd.wide_off) + (long)q0 * hd.d, hd.d, T - q0, o,
                1.f / l, dh, staging[wave], lane);

@@ -228,3 +228,40 @@ def test_backward_with_infinities(dh, heads, T, causal, plant):
     bad = ~np.isfinite(want).all(1)
     assert np.array_equal(~np.isfinite(got).all(1), bad), (np.flatnonzero(bad), np.flatnonzero(~np.isfinite(got).all(1)))
     assert np.linalg.norm(got[~bad] - want[~bad]) <= 1e-2 * np.linalg.norm(want[~bad]) + 1e-30
+
+
+# ---- keys whose scores are all minus infinity weigh nothing, whichever of a wavefront's tiles they fill ----
+# few problems (a workgroup's wavefronts share one tile's keys out: key tiles 0 to 3 are each one's first) and many (a tile each)
+@pytest.mark.parametrize("plant", ["inf_key", "overflow"])
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("dh,heads,T,tile", [(64, 2, 200, t) for t in range(7)] + [(64, 52, 320, 0), (64, 52, 320, 3), (24, 2, 130, 0),
+                                                                                  (32, 2, 130, 2), (56, 2, 200, 1), (128, 2, 200, 3)])
+def test_forward_with_hidden_keys(dh, heads, T, tile, causal, plant):
+    d = dh * heads
+    p = block(dh, heads, T, causal=causal)
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    x = torch.randn((T, d), generator=gen, device="cuda")
+    wqkv = torch.randn((3 * d, d), generator=gen, device="cuda") * (0.7 / np.sqrt(d))
+    # the last column of every head: a positive query, and from column 0 of the input a key of minus infinity, or a finite one whose
+    # product with the query is
+    hidden = slice(32 * tile, min(32 * tile + 32, T))
+    x[:, 0], x[:, 1] = 0, 1
+    x[hidden, 0] = 2e38
+    wqkv[:, :2] = 0
+    last = torch.arange(heads, device="cuda") * dh + dh - 1
+    wqkv[last] = 0
+    wqkv[last, 1] = 16
+    wqkv[d + last, 0] = -100 if plant == "inf_key" else -1
+    p.x[0], p.Wqkv[0] = x, wqkv
+    B.hbp_forward(p)
+    q, k, v = heads_of(p.qkv[0], 1, T, heads, 3)
+    assert np.isinf(k[0, :, hidden, -1]).all() if plant == "inf_key" else np.isfinite(k).all()
+    k[0, :, hidden, -1] = -np.inf
+    got = heads_of(p.attn_o[0], 1, T, heads, 1)[0]
+    lse = p.lse[0].double().cpu().numpy().reshape(1, heads, T)
+    with np.errstate(invalid="ignore"):
+        for h in {0, 1, heads - 1}:
+            o, L = plain_forward(q[0, h], k[0, h], v[0, h], causal)
+            assert np.isfinite(L).sum() == (T - 32 if causal and tile == 0 else T)      # (the others see hidden keys only)
+            assert_same(got[0, h], o, f"o, head {h}")
+            assert_same(lse[0, h], L, f"lse, head {h}")
