@@ -484,3 +484,69 @@ def test_scan_with_its_states_shared_out(B, L, N, d, dtype, lam, every, gamma):
     want = O.cumsumprod_reverse(a, lambda l: rows[l])
     for l in range(L + 1):
         H.assert_close(H.to_np(p.g)[l], want[l], H.TOL[dtype], f"state {l}")
+
+
+def _walk(a, lam, top):
+    """Every state of g_l = lam_l g_{l+1} + a_l in float32, one after the other."""
+    g = [np.asarray(top, np.float32)]
+    for l in range(len(lam) - 1, -1, -1):
+        g.append((lam[l].astype(np.float64) * g[-1] + a[l]).astype(np.float32))
+    return np.stack(g[::-1])
+
+
+# the same scan with infinities, NaNs, coefficients of zero, above one and so large or small that the product of a segment's leaves the
+# range of fp32: what comes out is what the walk from state to state gives, in every segment below too.  Chains of each form (segments of
+# one, two and four states), a column of its own for each case, others of ordinary numbers beside it.
+@pytest.mark.parametrize("L", [7, 21, 100, 300])
+@pytest.mark.parametrize("dtype,lam", [("bf16", "token"), ("bf16", "channel"), ("f32", "token"), ("f32", "channel")])
+def test_scan_of_segments_with_special_values(B, L, dtype, lam):
+    import torch
+    st = torch.bfloat16 if dtype == "bf16" else torch.float32
+    N, d = 3, 136
+    gen = torch.Generator().manual_seed(L)
+    e = torch.randn((L + 1, N, d), generator=gen)
+    lm = torch.rand((L, N, d) if lam == "token" else (L, d), generator=gen) * 0.4 + 0.6
+    inf, m = float("inf"), L // 2
+    tops = {3: inf, 5: -inf, 7: float("nan"), 9: 0.0, 11: 0.0, 13: 1.0, 15: 1e30, 17: -inf, 19: 1e30, 66: inf, 131: 0.0}
+    for c, v in tops.items():
+        e[:, :, c] = 0
+        e[L, :, c] = v
+    e[m, :, 20], e[m, :, 22], e[L - 1, :, 24], e[1, :, 26] = inf, float("nan"), -inf, inf
+    lm[..., 3] = lm[..., 66] = 1e-30       # products vanish: an infinite state stays infinite
+    lm[m, ..., 5] = 0                      # 0 times an infinity from there on
+    lm[..., 9] = 1e30                      # products overflow: a state of zero stays zero
+    lm[..., 11] = 1e30                     # ... and one that is given a value late does what it does by itself
+    e[0, :, 11] = 1.0
+    lm[..., 13] = 1e-25
+    lm[::2, ..., 15], lm[1::2, ..., 15] = (1e30, 1e-30) if L % 2 == 0 else (1e-30, 1e30)
+    lm[..., 19] = lm[..., 15].flip(0) if L % 2 == 0 else 1 / lm[..., 15]       # (the state in between overflows)
+    lm[m, ..., 17] = -2.0
+    lm[m, ..., 30] = 0
+    lm[m:m + 5, ..., 32] = 1.75            # above one
+    lm[m, ..., 131] = inf                  # ... and an infinite coefficient
+    e[m, :, 131] = 0
+    lm[m, ..., 133] = inf
+    lm[0, ..., 135] = float("nan")
+    e, lm = e.to(st), (lm.to(st) if lam == "token" else lm)
+    desc = B.make_desc("rnn", dtype, "tanh", "none", L, N, d, 8, 8, lambda_channel=lam == "channel", lambda_token=lam == "token",
+                       loss_every_state=True)
+    z = lambda *s: torch.zeros(s, dtype=st, device="cuda")
+    p = B.Problem(desc=desc, W1=z(8, d), W2=z(d, 8), U=z(8, 8), lam=lm.cuda(), xin=None, e=e.cuda(),
+                  g=torch.full((L + 1, N, d), 5.0, dtype=st, device="cuda"))
+    p.workspace = torch.zeros(B.workspace_size(desc), dtype=torch.uint8, device="cuda")
+    B.hbp_initial_estimate(p, "auto")
+    torch.cuda.synchronize()
+    rows = lm.float().numpy()
+    with np.errstate(over="ignore", invalid="ignore", under="ignore"):
+        want = _walk(e[:L].double().numpy(), [np.broadcast_to(r, (N, d)) for r in rows], e[L].float().numpy())
+        want = torch.from_numpy(want).to(st).double().numpy()
+    got = p.g.double().cpu().numpy()
+    cols = lambda bad: sorted(set(np.argwhere(bad)[:, 2]))
+    assert not cols(np.isnan(got) != np.isnan(want)), ("NaN", cols(np.isnan(got) != np.isnan(want)))
+    i = np.isinf(want)
+    assert not cols((np.isinf(got) != i) | (i & (got != want))), ("infinities", cols((np.isinf(got) != i) | (i & (got != want))))
+    f = np.isfinite(want)
+    # two roundings to the storage type that may fall apart, and the sums' order over a few states
+    got, want = got[f], want[f]
+    off = np.abs(got - want) > (2.0 ** -7 if dtype == "bf16" else 1e-5) * (np.abs(want) + 1.0)
+    assert not off.any(), (got[off], want[off])
