@@ -265,20 +265,20 @@ hipError_t launch_gemm_f32(const GemmArgs& g, hipStream_t s) {
   return tiles >= 512 ? launch_pairing<64>(g, s) : launch_pairing<32>(g, s);
 }
 // parameter gradients that fill the chip together at most (32-wide tiles by the line above)
-bool launch_gemm_f32_group(const GemmArgs* g, int n, hipStream_t s, hipError_t* err) {
-  *err = hipSuccess;
+bool gemm_f32_group_ok(const GemmArgs* g, int n) {
   if (n < 2 || n > GEMM_GROUP) return false;
   long tiles = 0;
   for (int i = 0; i < n; ++i) {
     if (!gemm_f32_ok(g[i]) || g[i].a_sm != 1 || g[i].b_sn != 1 || g[i].a_sk == 1 || g[i].b_sk == 1) return false;
     tiles += (g[i].M + 63) / 64 * ((g[i].N + 63) / 64) * g[i].batch * g[i].split_k;
   }
-  if (tiles >= 512) return false;
+  return tiles < 512;
+}
+hipError_t launch_gemm_f32_group(const GemmArgs* g, int n, hipStream_t s) {
   GemmGroup q;
-  if (!make_group(q, g, n, 32, 32)) return false;
+  if (!make_group(q, g, n, 32, 32)) return hipErrorInvalidValue;
   hipLaunchKernelGGL(gemm_f32_group_kernel<32>, dim3((unsigned)q.total), dim3(256), 0, s, q);
-  *err = hipGetLastError();
-  return true;
+  return hipGetLastError();
 }
 
 }  // namespace hbp

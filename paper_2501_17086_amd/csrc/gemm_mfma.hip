@@ -775,35 +775,36 @@ bool launch_gemm_mfma(const GemmArgs& g, hipStream_t s, hipError_t* err) {
   return true;
 }
 
+namespace {
+long tiles_of(const GemmArgs& g, long tm, long tn) { return (g.M + tm - 1) / tm * ((g.N + tn - 1) / tn) * g.batch * g.split_k; }
+}  // namespace
 // The tiles as for one product with all of their tiles (launch_tile_for).  Not where a product is long enough for itself: parameter
 // gradients in tiles of 128 go together if that takes fewer rounds of the 512 that run at a time, or is short, up to 2048 tiles (two
 // products) or 4096 (a transformer's four).  Measured, passes of one or two iterations, us, apart / together: two products, 8 blocks of 1000
 // x 360 x 1440 (288 + 288 tiles) 156.7 / 163.4, 24 of 1000 x 200 x 800 (336 each) 126.6 / 131.4, 20 of 100 x 328 x 1304 (660) 74.0 / 68.2, 12 of
 // 200 x 520 x 2080 (1020, short) 107.7 / 103.9, 8 of 141 x 1152 x 4608 (2592) 152 / 159; four, 6 layers of 2736 x 512 (1152 in all) 847 / 753
 // with the VJPs', 3 of 1740 x 1024 (2304) 974 / 885.  VJPs always, but for contractions of 4096 and more (4 layers of 500 x 1536 893 / 904).
-bool launch_gemm_mfma_group(const GemmArgs* g, int n, hipStream_t s, hipError_t* err) {
-  *err = hipSuccess;
+bool gemm_mfma_group_ok(const GemmArgs* g, int n) {
   if (n < 2 || n > GEMM_GROUP) return false;
-  long t128 = 0, t3232 = 0, t6432 = 0, rounds = 0, longest = 0, shortest = 1L << 60;
+  long t128 = 0, rounds = 0, longest = 0, shortest = 1L << 60;
   for (int i = 0; i < n; ++i) {
     if (!covered(g[i]) || lean_share(g[i]) != LEAN_NOT || g[i].b_sn != 1 || (g[i].a_sk == 1) != (g[0].a_sk == 1)) return false;
     if (g[i].b_sk == 1 || (g[i].a_sk == 1 && g[i].a_sm == 1)) return false;       // (a single column: either layout)
-    auto tiles = [&g, i](long tm, long tn) { return (g[i].M + tm - 1) / tm * ((g[i].N + tn - 1) / tn) * g[i].batch * g[i].split_k; };
-    t128 += tiles(128, 128); t3232 += tiles(32, 32); t6432 += tiles(64, 32);
-    rounds += (tiles(128, 128) + 511) / 512;
+    t128 += tiles_of(g[i], 128, 128);
+    rounds += (tiles_of(g[i], 128, 128) + 511) / 512;
     longest = g[i].K > longest ? g[i].K : longest;
     shortest = g[i].K < shortest ? g[i].K : shortest;
   }
-  if (g[0].a_sk == 1) {
-    if (t128 > (1L << 24) || (shortest >= 4096 && t128 >= 192)) return false;
-  } else if (t128 >= 192) {
-    if (t128 > (n == 2 ? 2048 : 4096) || ((t128 + 511) / 512 >= rounds && longest > 256)) return false;
-  }
-  *err = t128 >= 192     ? launch_gemm_tile_group(g, n, 128, 128, s)
+  if (g[0].a_sk == 1) return t128 <= (1L << 24) && (shortest < 4096 || t128 < 192);
+  return t128 < 192 || (t128 <= (n == 2 ? 2048 : 4096) && ((t128 + 511) / 512 < rounds || longest <= 256));
+}
+hipError_t launch_gemm_mfma_group(const GemmArgs* g, int n, hipStream_t s) {
+  long t128 = 0, t3232 = 0, t6432 = 0;
+  for (int i = 0; i < n; ++i) { t128 += tiles_of(g[i], 128, 128); t3232 += tiles_of(g[i], 32, 32); t6432 += tiles_of(g[i], 64, 32); }
+  return t128 >= 192     ? launch_gemm_tile_group(g, n, 128, 128, s)
          : t3232 <= 256  ? launch_gemm_tile_group(g, n, 32, 32, s)
          : t6432 <= 256  ? launch_gemm_tile_group(g, n, 64, 32, s)
                          : launch_gemm_tile_group(g, n, 64, 64, s);
-  return true;
 }
 
 }  // namespace hbp

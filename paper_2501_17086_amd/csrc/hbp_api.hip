@@ -290,12 +290,11 @@ hbp_status run_gemm(const hbp_desc* d, const GemmArgs& ga, hipStream_t s, int cl
 // launch costs more than the product it holds (on the host 3 to 4 us, on the chip 2 to 3 of latency): parameter gradients of 9 blocks
 // of 89 x 128 x 512 in one launch of two products, an iteration of a small transformer in four launches instead of six.
 hbp_status run_gemms(const hbp_desc* d, const GemmArgs* g, int n, hipStream_t s, int cls) {
-  {
+  const bool bf16 = d->dtype == HBP_BF16;
+  if (bf16 ? gemm_mfma_group_ok(g, n) : gemm_f32_group_ok(g, n)) {
     ProfScope ps(cls, s);
-    hipError_t err = hipSuccess;
-    if (d->dtype == HBP_BF16 ? launch_gemm_mfma_group(g, n, s, &err) : launch_gemm_f32_group(g, n, s, &err))
-      return err == hipSuccess ? HBP_OK : HBP_E_DEVICE;
-    if (n == 1) return launch_gemm(d, g[0], s) == hipSuccess ? HBP_OK : HBP_E_DEVICE;
+    HBP_TRY(bf16 ? launch_gemm_mfma_group(g, n, s) : launch_gemm_f32_group(g, n, s));
+    return HBP_OK;
   }
   for (int i = 0; i < n; ++i) {
     const hbp_status st = run_gemm(d, g[i], s, cls);

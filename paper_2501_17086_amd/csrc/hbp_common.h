@@ -163,8 +163,7 @@ inline bool gemm_fills_chip(long tiles) { return tiles * 100 >= (tiles + 255) / 
 // tiles: 163 us in parts, 122 us whole).
 constexpr long GEMM_SPLIT_FROM = 512;
 // Products of one pairing of layouts (both operands of each with the same index contiguous) that do not depend on each other, in one
-// launch: where all of them go to the kernels for few tiles, a launch costs more than a product's share of the chip does.  False, with
-// nothing done, where that is not so.
+// launch: where all of them go to the kernels for few tiles, a launch costs more than a product's share of the chip does.
 constexpr int GEMM_GROUP = 4;
 struct GemmGroup {
   GemmArgs g[GEMM_GROUP];
@@ -191,8 +190,10 @@ inline bool make_group(GemmGroup& q, const GemmArgs* g, int n, int tm, int tn) {
   q.per_xcd = (int)((total + 7) / 8);
   return true;
 }
-bool launch_gemm_mfma_group(const GemmArgs* g, int n, hipStream_t s, hipError_t* err);
-bool launch_gemm_f32_group(const GemmArgs* g, int n, hipStream_t s, hipError_t* err);
+bool gemm_mfma_group_ok(const GemmArgs* g, int n);
+bool gemm_f32_group_ok(const GemmArgs* g, int n);
+hipError_t launch_gemm_mfma_group(const GemmArgs* g, int n, hipStream_t s);      // (where ..._ok)
+hipError_t launch_gemm_f32_group(const GemmArgs* g, int n, hipStream_t s);
 hipError_t launch_gemm_tile_group(const GemmArgs* g, int n, int tm, int tn, hipStream_t s);
 // fast bf16 MFMA path; returns false when the shape/layout is not covered
 bool launch_gemm_mfma(const GemmArgs& g, hipStream_t s, hipError_t* err);

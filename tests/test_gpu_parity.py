@@ -657,3 +657,33 @@ def test_calls_can_be_captured_in_a_graph_and_replayed(B, name):
         torch.cuda.synchronize()
         assert torch.equal(p.g, ref_g)
         assert torch.equal(p.dW1, ref_w)
+
+
+# what hbp_profile_read counts: one launch for products that share it, one for each product that has its own
+@pytest.mark.parametrize("name,kw,want", [
+    ("mlp", dict(L=2, N=40, d=64, d_ff=128), {"dw": 1}),
+    ("mlp", dict(L=64, N=64, d=512, d_ff=512), {"dw": 2}),                    # 256 tiles of 256 x 256: the kernel for those, twice
+    ("mlp", dict(L=2, N=40, d=64, d_ff=128, dtype="f32"), {"dw": 1}),
+    ("tfm", dict(L=4, N=40, d=64, d_ff=128), {"vjp1": 1, "vjp2": 1, "dw": 1}),
+    ("tfm", dict(L=4, N=40, d=64, d_ff=128, dtype="f32"), {"vjp1": 2, "vjp2": 2, "dw": 1}),
+])
+def test_launches_are_counted(B, name, kw, want):
+    if name == "mlp":
+        w = synth.scaled(W["resnet_like"], name="count", w2_scale=0.2, **kw)
+    else:
+        w = synth.scaled(W["gpt2_paper"], name="count", seq_len=20, heads=2, w1_std=0.0, w2_std=0.0, w2_scale=0.6, **kw)
+    inp = synth.make_inputs(w)
+    p = B.allocate(w, inp)
+    B.hbp_forward(p)
+    B.hbp_backward(p, 1)
+    B.profile_enable(True)
+    try:
+        B.profile_read()
+        B.hbp_param_grads(p)
+        dw = B.profile_read()
+        B.hbp_backward(p, 1)
+        it = B.profile_read()
+    finally:
+        B.profile_enable(False)
+    got = {"dw": dw["dw"][1], "vjp1": it["vjp1"][1], "vjp2": it["vjp2"][1]}
+    assert {k: got[k] for k in want} == want
