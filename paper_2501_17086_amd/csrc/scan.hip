@@ -104,9 +104,9 @@ __global__ __launch_bounds__(256) void scan_vec_kernel(ScanArgs a) {
 // infinity, an infinity times 0).  Either shows in the state that a segment ends with: such a workgroup walks its channels once more,
 // from state to state (a product that underflows is off by 2^-149 of the state entering, which nothing shows).  The test costs 0 to 2 %:
 // 4096 states of 32 x 1024 131 -> 133 us, 12 of 1000 x 328 5.4 -> 5.5.
-// LAMK: 0 coefficients 1; 1 per channel (fp32 [L,d]); 2 per token.  NSRC: of dn and e how many there are.
+// LAMK: 0 coefficients 1; 1 per channel (fp32 [L,d]); 2 per token.  SRC: a value stream (dn or e).
 constexpr int SEG_CH = 64;
-template <typename T, int LAMK, int NSRC, int S, int SEG_N>
+template <typename T, int LAMK, bool SRC, int S, int SEG_N>
 __global__ __launch_bounds__(8 * SEG_N) void scan_seg_kernel(ScanArgs a) {
   __shared__ __attribute__((aligned(16))) float map_a[SEG_N][SEG_CH], map_b[SEG_N][SEG_CH];
   __shared__ int walk_again;
@@ -117,7 +117,6 @@ __global__ __launch_bounds__(8 * SEG_N) void scan_seg_kernel(ScanArgs a) {
   const long c0 = off % a.d;
   T* g = reinterpret_cast<T*>(a.g);
   const T* src = reinterpret_cast<const T*>(a.dn ? a.dn : a.e);
-  const T* src2 = reinterpret_cast<const T*>(a.e);
   const T* tok = reinterpret_cast<const T*>(a.lambda_tok);
   const float rs = a.res_scale;
   if (SEG_N > 8 && tid == 0) walk_again = 0;
@@ -134,15 +133,14 @@ __global__ __launch_bounds__(8 * SEG_N) void scan_seg_kernel(ScanArgs a) {
     }
   }
   struct Raw {
-    Raw8<T> v[NSRC > 0 ? S : 1], v2[NSRC > 1 ? S : 1], tok[LAMK == 2 ? S : 1];
+    Raw8<T> v[SRC ? S : 1], tok[LAMK == 2 ? S : 1];
     Raw8<float> lam[LAMK == 1 ? S : 1];
   };
   auto ask = [&](Raw& r, long l0) __attribute__((always_inline)) {
 #pragma unroll
     for (int s = 0; s < S; ++s) {
       const long l = l0 - s > a.l_lo ? l0 - s : a.l_lo;
-      if (NSRC > 0) r.v[NSRC > 0 ? s : 0].load(src + l * layer + off);
-      if (NSRC > 1) r.v2[NSRC > 1 ? s : 0].load(src2 + l * layer + off);
+      if (SRC) r.v[SRC ? s : 0].load(src + l * layer + off);
       if (LAMK == 2) r.tok[LAMK == 2 ? s : 0].load(tok + l * layer + off);
       if (LAMK == 1) r.lam[LAMK == 1 ? s : 0].load(a.lambda + l * a.d + c0);
     }
@@ -161,13 +159,7 @@ __global__ __launch_bounds__(8 * SEG_N) void scan_seg_kernel(ScanArgs a) {
       for (int i = 0; i < 8; ++i) { lam[i] = 1.f; v[i] = 0.f; }
       if (LAMK == 2) r.tok[LAMK == 2 ? s : 0].unpack(lam);
       if (LAMK == 1) r.lam[LAMK == 1 ? s : 0].unpack(lam);
-      if (NSRC > 0) r.v[NSRC > 0 ? s : 0].unpack(v);
-      if (NSRC > 1) {
-        float t[8];
-        r.v2[NSRC > 1 ? s : 0].unpack(t);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) v[i] += t[i];
-      }
+      if (SRC) r.v[SRC ? s : 0].unpack(v);
 #pragma unroll
       for (int i = 0; i < 8; ++i) lam[i] *= rs;
     };
@@ -248,13 +240,7 @@ __global__ __launch_bounds__(8 * SEG_N) void scan_seg_kernel(ScanArgs a) {
     for (int i = 0; i < 8; ++i) { lam[i] = 1.f; v[i] = 0.f; }
     if (LAMK == 2) load8(tok + l * layer + at, lam);
     if (LAMK == 1) load8(a.lambda + l * a.d + at % a.d, lam);
-    if (NSRC > 0) load8(src + l * layer + at, v);
-    if (NSRC > 1) {
-      float t[8];
-      load8(src2 + l * layer + at, t);
-#pragma unroll
-      for (int i = 0; i < 8; ++i) v[i] += t[i];
-    }
+    if (SRC) load8(src + l * layer + at, v);
 #pragma unroll
     for (int i = 0; i < 8; ++i) carry[i] = fmaf(rs * lam[i], carry[i], v[i]);
     store8(g + l * layer + at, carry);
@@ -1099,7 +1085,7 @@ hipError_t launch_scan_sp(const ScanArgs& a, hipStream_t s) {
 
 // what the form with the states shared out inside a workgroup covers
 inline bool seg_covers(const ScanArgs& a) {
-  return a.blk_gamma == 0.f && !a.mask && !(a.norm_rms && a.dn);
+  return a.blk_gamma == 0.f && !a.mask && !(a.norm_rms && a.dn) && !(a.dn && a.e);
 }
 // ... and where it is the faster one: up to half a million elements a state, fewer below 16 states.  Measured, us, the form before (a
 // thread per vector up to 255 states, from 256 on chunks) / this one, bf16 with a value stream: 2 states of 100 x 128 2.7 / 2.2, of 1000
@@ -1112,26 +1098,18 @@ inline bool seg_pays(const ScanArgs& a) {
   const long L = a.l_hi - a.l_lo, n = a.N * a.d;
   return L >= 2 && n <= (L < 16 ? 32768 * L : 1L << 19) && (sizeof(T) == 4 || L * n <= (1L << 28));
 }
-template <typename T, int LAMK, int NSRC, int S, int SEG_N>
+template <typename T, int LAMK, bool SRC, int S, int SEG_N>
 hipError_t launch_seg_as(const ScanArgs& a, hipStream_t s) {
   const dim3 grid((unsigned)((a.N * a.d + SEG_CH - 1) / SEG_CH)), block(8 * SEG_N);
-  hipLaunchKernelGGL((scan_seg_kernel<T, LAMK, NSRC, S, SEG_N>), grid, block, 0, s, a);
+  hipLaunchKernelGGL((scan_seg_kernel<T, LAMK, SRC, S, SEG_N>), grid, block, 0, s, a);
   return hipGetLastError();
 }
 template <typename T, int S, int SEG_N>
 hipError_t launch_seg(const ScanArgs& a, hipStream_t s) {
-  const int nsrc = (a.dn ? 1 : 0) + (a.e ? 1 : 0), lamk = a.lambda_tok ? 2 : a.lambda ? 1 : 0;
-  switch (3 * lamk + nsrc) {
-    case 0: return launch_seg_as<T, 0, 0, S, SEG_N>(a, s);
-    case 1: return launch_seg_as<T, 0, 1, S, SEG_N>(a, s);
-    case 2: return launch_seg_as<T, 0, 2, S, SEG_N>(a, s);
-    case 3: return launch_seg_as<T, 1, 0, S, SEG_N>(a, s);
-    case 4: return launch_seg_as<T, 1, 1, S, SEG_N>(a, s);
-    case 5: return launch_seg_as<T, 1, 2, S, SEG_N>(a, s);
-    case 6: return launch_seg_as<T, 2, 0, S, SEG_N>(a, s);
-    case 7: return launch_seg_as<T, 2, 1, S, SEG_N>(a, s);
-    default: return launch_seg_as<T, 2, 2, S, SEG_N>(a, s);
-  }
+  const bool src = a.dn || a.e;
+  if (a.lambda_tok) return src ? launch_seg_as<T, 2, true, S, SEG_N>(a, s) : launch_seg_as<T, 2, false, S, SEG_N>(a, s);
+  if (a.lambda) return src ? launch_seg_as<T, 1, true, S, SEG_N>(a, s) : launch_seg_as<T, 1, false, S, SEG_N>(a, s);
+  return src ? launch_seg_as<T, 0, true, S, SEG_N>(a, s) : launch_seg_as<T, 0, false, S, SEG_N>(a, s);
 }
 // As many segments at a time as keep their walk short beside the rest: 8 of one state for 8 states, 8 of two for up to 32 or where the
 // elements fill the chip by themselves, else 32 of two; 64 of four for the fewest chains.  Measured, us, 8 x 1 / 8 x 2 / 32 x 2 / 64 x 4: 8
