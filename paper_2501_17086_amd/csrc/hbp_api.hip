@@ -137,6 +137,8 @@ Workspace carve(const hbp_desc* d) {
   partials(sp.s_o, nb * d->d * d->d);
   partials(sp.s_u, (size_t)d->d_ff * d->d_in);
   w.off_part = o; o = align_up(o + part, 256);
+  // (also where gamma is 0 and the form with the states shared out, which needs none, takes every scan: a call may bring another gamma,
+  // whose iterations scan in chunks, with the same workspace)
   w.off_scan = o; o = align_up(o + scan_chunk_ws_bytes(d->L, d->N, d->d, d->norm == HBP_NORM_RMS), 256);
   // transposed copies of the shared weights for step-by-step backpropagation through time
   w.off_wt = o;

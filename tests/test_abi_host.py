@@ -74,6 +74,14 @@ def test_shares_are_counted_in_the_tiles_that_run(L, N, d, d_ff, shares):
     assert round(partial / (L * d * d_ff * 4)) == (shares if shares > 1 else 0)
 
 
+# hbp_backward may be called with another gamma than the workspace was sized with
+@pytest.mark.parametrize("kind", [dict(kind="rnn", act="tanh", norm="none", d_in=64, L=1024, N=32, d=256, d_ff=256),
+                                  dict(kind="gru", act="tanh", norm="none", d_in=64, L=1024, N=32, d=256, d_ff=768, lambda_token=True),
+                                  dict(norm="none", L=300, N=16, d=128, d_ff=256), dict(L=12, N=4096, d=512, d_ff=2048)])
+def test_one_workspace_serves_every_gamma(kind):
+    assert len({B.workspace_size(_desc(**kind, gamma=g)) for g in (0.0, 0.2, 1.0)}) == 1
+
+
 @pytest.mark.parametrize("field,value,status", [
     ("L", 0, 1), ("N", -1, 1), ("d", 0, 1), ("d", 60, 2), ("d_ff", 100, 2), ("kind", 7, 1), ("dtype", 3, 1),
     ("act", 5, 1), ("norm", 2, 1), ("lambda_kind", 9, 1), ("loss_every_state", 2, 1), ("struct_size", 12, 1),
