@@ -11,9 +11,11 @@
 // Rows past the matrix repeat the last one and are not stored; k past the end are zeros in both operands.  What is fused into the
 // result is asked for behind the first operands.
 // Measured, us (before: addresses in 64 bits and values selected lane by lane, the fused operand read at the end): 128 x 256 x 64, 8
-// blocks, with act' 5.3 -> 3.9; 128 x 64 x 256 5.1 -> 4.7; 338 x 384 x 96, 10 blocks, with act' 15.8 -> 9.3; 384 x 96 x 338, parameter gradients
-// of 10 blocks, 13.7 -> 8.6; 1024 x 256 x 1024, 12 blocks, 95 -> 71 (64 wide, 91 TFLOP/s), parameter gradients 96 -> 60; one block of 338 x
-// 96 x 384, both operands K-contiguous, 6.1 -> 6.6.  Relative error against 64 bits 1.5e-7 .. 2.9e-7 with 32-wide tiles (the quarters are
+// blocks, with act' 5.2 -> 3.5; 128 x 64 x 256 5.1 -> 4.7; 338 x 384 x 96, 10 blocks, with act' 15.8 -> 8.4; 384 x 96 x 338, parameter gradients
+// of 10 blocks, 13.7 -> 8.4; 1024 x 256 x 1024, 12 blocks, 96 -> 71 (64 wide, 91 TFLOP/s), parameter gradients 96 -> 61.  One block, both
+// operands K-contiguous (the forward's pairing: two chunks asked for before the fused operand; after the first chunk, as in the others, it
+// delays the second): 338 x 384 x 96 4.7 -> 3.9, 338 x 96 x 128 3.5 -> 3.4, x 256 5.3 -> 5.0, x 384 6.05 -> 6.23, x 512 7.3 -> 7.15, 300 x 200 x
+// 800 10.4 -> 9.3, 1000 x 256 x 1024 11.3 -> 11.2.  Relative error against 64 bits 1.5e-7 .. 2.9e-7 with 32-wide tiles (the quarters are
 // sums of their own) and 2.9e-7 .. 5.7e-7 with 64-wide ones.
 #include "hbp_common.h"
 
@@ -183,20 +185,36 @@ __device__ __forceinline__ void gemm_f32_body(const GemmArgs& g, unsigned bx, un
   int todo = left;          // ... and to multiply
   const int row = tid >> 3, c0 = (tid & 7) * 4;            // SPLIT: this thread's piece of the result
   Fused f[SPLIT ? 1 : 4];
-  if (left > 0) load(a0, b0);
-  if (SPLIT) {
-    f[0].ask(g, batch, m0 + row, n0 + c0);
-  } else {
+  auto ask = [&]() __attribute__((always_inline)) {
+    if (SPLIT) {
+      f[0].ask(g, batch, m0 + row, n0 + c0);
+    } else {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) f[SPLIT ? 0 : q].ask(g, batch, m0 + r, n0 + 8 * q + 4 * h);
-  }
-  while (todo > 0) {
+      for (int q = 0; q < 4; ++q) f[SPLIT ? 0 : q].ask(g, batch, m0 + r, n0 + 8 * q + 4 * h);
+    }
+  };
+  if (left > 0) load(a0, b0);
+  if constexpr (A_KC && B_KC) {          // two chunks on their way before the fused operand
     if (left > 0) load(a1, b1);
-    multiply(acc, a0, b0, todo);
-    if ((todo -= CH) <= 0) break;
-    if (left > 0) load(a0, b0);
-    multiply(acc, a1, b1, todo);
-    todo -= CH;
+    ask();
+    while (todo > 0) {
+      multiply(acc, a0, b0, todo);
+      if ((todo -= CH) <= 0) break;
+      if (left > 0) load(a0, b0);
+      multiply(acc, a1, b1, todo);
+      if ((todo -= CH) <= 0) break;
+      if (left > 0) load(a1, b1);
+    }
+  } else {
+    ask();
+    while (todo > 0) {
+      if (left > 0) load(a1, b1);
+      multiply(acc, a0, b0, todo);
+      if ((todo -= CH) <= 0) break;
+      if (left > 0) load(a0, b0);
+      multiply(acc, a1, b1, todo);
+      todo -= CH;
+    }
   }
   if (SPLIT) {
 #pragma unroll
