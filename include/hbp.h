@@ -42,9 +42,11 @@
  *    widths up to 1024, batches of up to 64 rows at that width), whose workgroups wait for each other's results, up to 32 at
  *    a time.  From 12 steps on up to 256 workgroups run, one per compute unit (64 rows of width 1024; 32 rows: 128): what
  *    other streams have enqueued meanwhile waits for them.  Any number of such calls may overlap; three or more wide ones
- *    mostly take turns.  Where the workgroups do not get to run side by side (other work holds the GPU), a second launch
- *    of at most 64 workgroups takes what is left, and where 32 of those do not for a long time, one of them computes the
- *    chain alone: the same results, at 0.1 to 0.4 ms a step.
+ *    mostly take turns.  On up to 512 channels (gated cell: 1024) a workgroup may take a compute unit for itself where
+ *    two would fit: one or two calls at once are up to 1.6 times as fast for it, four or eight up to 1.4 times as slow.
+ *    Where the workgroups do not get to run side by side (other work holds the GPU), a second launch of at most 64
+ *    workgroups takes what is left, and where 32 of those do not for a long time, one of them computes the chain alone:
+ *    the same results, at 0.1 to 0.4 ms a step.
  *  - State between calls: none that changes results.  The library keeps (a) a
  *    flag per kernel and device saying that the kernel's shared-memory limit
  *    has been raised (set on the first launch, idempotent, safe from several

@@ -39,8 +39,10 @@
 // 1.55, 3.6, 7.2; exact backpropagation of the RNN 1.63, 2.21, 4.22, 7.0 / 0.84, 1.12, 2.20, 3.5, of the GRU 1.95, 2.32, 2.55, 5.1 /
 // 0.98, 1.16, 3.0, 5.0; 64 rows, forward of the RNN 2.17, 2.51, 2.77, 5.5 / 0.88, 1.37, 2.67, 7.7, of the GRU 2.69, 2.90, 3.33, 9.1 /
 // 1.18, 2.27, 4.5, 9.2.  One or two calls gain in every kind; from three on the wide GRU and LSTM lose, by 1.75 times at most.  Where a fifth
-// wavefront reads ahead (read_ahead) a second workgroup no longer fits beside the first: without / with it, gated cell 32 x 1024 0.83, 1.37,
-// 2.2, 3.8 / 0.75, 0.84, 2.6, 4.7, LSTM 64 x 512 1.21, 1.66, 2.0, 3.9 / 1.02, 1.10, 2.3, 4.4, GRU 64 x 512 1.01, 1.67, 1.8, 3.6 / 0.95, 1.11, 2.2, 5.8.
+// wavefront reads ahead (read_ahead) a second workgroup no longer fits beside the first, which keeps two calls apart and makes more of
+// them wait: without / with it, gated cell 32 x 1024 0.82, 1.34, 2.2, 4.1 / 0.75, 0.83, 2.3, 4.5, exact backpropagation of 64 x 512 0.66,
+// 0.91, 1.3, 2.9 / 0.59, 0.89, 1.0, 3.1, LSTM 64 x 512 1.21, 1.66, 2.0, 4.4 / 1.02, 1.09, 2.2, 4.4, exact backpropagation of the RNN 64 x 512
+// 0.75, 0.91, 1.4, 2.6 / 0.68, 0.85, 1.1, 3.1 (to 3.7); the GRU at REC_GRU_AHEAD.
 //
 // Measured (1024 steps, batch 32, width 1024): exact backpropagation of the RNN 14.5 ms as launches of their own, 3.3 through
 // memory, 1.7 on one XCD with groups of 8 rows; forward of the GRU 20.9, 3.6 and 2.4.  0.8 us per dependent product: about 0.4 from
@@ -691,6 +693,12 @@ __device__ __forceinline__ bool forward_chain(const RecArgs& a, const Ring<LOCAL
 // (400 of 20 x 200 642 / 674; above, 500 of 64 x 512, 1153 / 1040), nor for one or two rows of that width for the gated cell (500 steps 509 /
 // 539, of four rows 528 / 506).
 constexpr int READ_AHEAD = 4;
+// A workgroup of five wavefronts has a compute unit for itself; of four, two share one.  The GRU of 257 to 512 channels gains the least
+// from reading ahead, and does so only with up to this many workgroups, of which four calls at once still find a place.  512 steps, ms for
+// 1, 2, 4 and 8 calls at once, without / with it: 64 x 512 (128 workgroups), forward 1.01, 1.67, 1.82, 3.6 / 0.95, 1.12, 2.3, 4.4, exact
+// backpropagation 0.82, 1.18, 1.46, 2.8 / 0.78, 0.92, 1.8, 3.5; 48 x 384 (72), forward 0.95, 1.24, 1.58, 3.2 / 0.89, 1.00, 2.56, 3.7; 32 x
+// 512 (64), forward 0.95, 1.57, 2.8, 3.2 / 0.88, 0.98, 1.9, 2.3 (3.1), exact 0.82, 0.93, 1.4, 2.8 / 0.77, 0.80, 0.98, 2.6.
+constexpr int REC_GRU_AHEAD = 64;
 template <int KIND, int KQ, bool FORWARD> constexpr bool reads_ahead() {
   return (KQ < 8 || KIND == K_GATED) && (FORWARD || KIND == K_RNN || KIND == K_GATED || (KIND == K_GRU && KQ == 4));
 }
@@ -1110,11 +1118,14 @@ hipError_t launch_rec(const RecArgs& a, bool forward, hipStream_t s) {
   const int per = rec_rows<RT>() / rec_rows<RTL>();
   auto on_xcds = [&](auto kern, bool ahead) { hipLaunchKernelGGL(kern, everywhere, dim3(ahead ? 320 : 256), 0, s, l, (int)wpg, locals, 1, 0); };
   constexpr bool FW = reads_ahead<KIND, KQ, true>(), BW = reads_ahead<KIND, KQ, false>();
+  constexpr bool GRU4 = KIND == K_GRU && KQ == 4, GATED2 = KIND == K_GATED && KQ == 2;
+  const bool crowded = GRU4 && locals * wpg > REC_GRU_AHEAD;
   if (forward) {
-    if (local) on_xcds(rec_forward_kernel<KIND, KQ, RTL, true, FW>, FW);
+    if (local && crowded) on_xcds(rec_forward_kernel<KIND, KQ, RTL, true, FW && !GRU4>, false);
+    else if (local) on_xcds(rec_forward_kernel<KIND, KQ, RTL, true, FW>, FW);
     hipLaunchKernelGGL((rec_forward_kernel<KIND, KQ, RT, false, false>), anywhere, dim3(256), 0, s, a, (int)wpg, groups, per, local ? locals : 0);
   } else {
-    if (local && KIND == K_GATED && KQ == 2 && a.N <= 2) on_xcds(rec_backward_kernel<KIND, KQ, RTL, true, BW && !(KIND == K_GATED && KQ == 2)>, false);
+    if (local && (crowded || (GATED2 && a.N <= 2))) on_xcds(rec_backward_kernel<KIND, KQ, RTL, true, BW && !GRU4 && !GATED2>, false);
     else if (local) on_xcds(rec_backward_kernel<KIND, KQ, RTL, true, BW>, BW);
     hipLaunchKernelGGL((rec_backward_kernel<KIND, KQ, RT, false, false>), anywhere, dim3(256), 0, s, a, (int)wpg, groups, per, local ? locals : 0);
   }

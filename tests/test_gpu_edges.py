@@ -121,10 +121,11 @@ def test_chains_along_time(B, kind, L, N, H):
 
 
 # the fifth wavefront's reading ahead: chains shorter and longer than the four steps it is ahead by, widths whose last block of 32 channels
-# and last piece of 16 inputs end inside, the rows past the batch, with and without it (the gated cell's two rows; width 1024)
+# and last piece of 16 inputs end inside, the rows past the batch, with and without it (the gated cell's two rows; width 1024; the
+# GRU's 80 workgroups)
 @pytest.mark.parametrize("kind,L,N,H", [("rnn", 12, 3, 8), ("rnn", 13, 33, 504), ("token", 17, 3, 264), ("gated", 16, 2, 24),
                                         ("gated", 16, 3, 24), ("gated", 12, 17, 1000), ("lstm", 15, 9, 488), ("gru", 12, 65, 56),
-                                        ("gru", 14, 7, 504)])
+                                        ("gru", 14, 7, 504), ("gru", 12, 32, 504), ("gru", 12, 33, 504)])
 def test_chains_that_read_ahead(B, kind, L, N, H):
     w = _chain(kind, L, N, H)
     inp, st, sv, p = _forward_matches(B, w)
