@@ -783,7 +783,10 @@ long tiles_of(const GemmArgs& g, long tm, long tn) { return (g.M + tm - 1) / tm 
 // products) or 4096 (a transformer's four).  Measured, passes of one or two iterations, us, apart / together: two products, 8 blocks of 1000
 // x 360 x 1440 (288 + 288 tiles) 156.7 / 163.4, 24 of 1000 x 200 x 800 (336 each) 126.6 / 131.4, 20 of 100 x 328 x 1304 (660) 74.0 / 68.2, 12 of
 // 200 x 520 x 2080 (1020, short) 107.7 / 103.9, 8 of 141 x 1152 x 4608 (2592) 152 / 159; four, 6 layers of 2736 x 512 (1152 in all) 847 / 753
-// with the VJPs', 3 of 1740 x 1024 (2304) 974 / 885.  VJPs always, but for contractions of 4096 and more (4 layers of 500 x 1536 893 / 904).
+// with the VJPs', 3 of 1740 x 1024 (2304) 974 / 885.  VJPs always, but for contractions of 4096 and more past a tile per
+// compute unit: the second ones of 4 layers of 256 x 1536 (192 tiles) 657 / 603, of 2 of 400 x 1536 (192) 414 / 388, of 2 of 500 x 2048 (256)
+// 744 / 698, of 4 of 256 x 2048 (256) 956 / 828, of 3 of 640 x 1536 (360) 769 / 770, of 4 of 500 x 1536 (384) 851 / 893, of 4 of 384 x 2048 (384)
+// 1051 / 1103, of 2 of 1000 x 2048 (512) 1086 / 1163, of 2 of 1500 x 1536 (576) 954 / 949.
 bool gemm_mfma_group_ok(const GemmArgs* g, int n) {
   if (n < 2 || n > GEMM_GROUP) return false;
   long t128 = 0, rounds = 0, longest = 0, shortest = 1L << 60;
@@ -795,7 +798,7 @@ bool gemm_mfma_group_ok(const GemmArgs* g, int n) {
     longest = g[i].K > longest ? g[i].K : longest;
     shortest = g[i].K < shortest ? g[i].K : shortest;
   }
-  if (g[0].a_sk == 1) return t128 <= (1L << 24) && (shortest < 4096 || t128 < 192);
+  if (g[0].a_sk == 1) return t128 <= (1L << 24) && (shortest < 4096 || t128 <= 256);
   return t128 < 192 || (t128 <= (n == 2 ? 2048 : 4096) && ((t128 + 511) / 512 < rounds || longest <= 256));
 }
 hipError_t launch_gemm_mfma_group(const GemmArgs* g, int n, hipStream_t s) {
