@@ -1116,12 +1116,14 @@ hipError_t launch_seg(const ScanArgs& a, hipStream_t s) {
 // states of 1000 x 512 5.8 / 7.2 / 18.5 / -, 24 of 64 x 512 3.5 / 3.3 / 3.4 / -, of 256 x 512 5.1 / 4.9 / 7.1 / -, 100 of 64 x 512 8.9 / 7.0 / 5.2 /
 // 8.6, of 256 x 1024 22 / 19 / 23 / 54, 1024 of 32 x 200 59 / 39 / 18.4 / 12.9, of 32 x 600 65 / 46 / 25 / 27.  8 x 2 / 32 x 2 with coefficients
 // per channel | per token: 1024 of 32 x 1024 45 / 24 | 46 / 32, 2048 of 32 x 1536 122 / 104 | 125 / 134, 1024 of 64 x 1024 66 / 61 | 74 / 88, 2048
-// of 64 x 1024 127 / 137 | 145 / 176, 4096 of 32 x 1024 213 / 134 | 212 / 170, of 32 x 2048 252 / 279 | 292 / 348.
+// of 64 x 1024 129 / 136 | 145 / 173, 4096 of 32 x 1024 213 / 134 | 212 / 170, of 32 x 2048 255 / 276 | 290 / 348.  Between: 1024 of 32 x 1792
+// 52 / 44 | 83 / 85, of 32 x 1920 65 / 67 | 77 / 86, 2048 of 32 x 1536 124 / 105 | 125 / 133, of 32 x 1792 140 / 140 | 159 / 168, of 32 x 1920
+// 152 / 147 | 154 / 170, of 32 x 2056 161 / 164 | 150 / 177, 4096 of 32 x 1920 303 / 295 | 304 / 344.
 template <typename T>
 hipError_t launch_seg_for(const ScanArgs& a, hipStream_t s) {
   const long L = a.l_hi - a.l_lo, n = a.N * a.d;
   if (L <= 8) return launch_seg<T, 1, 8>(a, s);
-  const bool fills = n > 65536 || (n >= 49152 && a.lambda_tok) || (n == 65536 && L >= 2048);
+  const bool fills = n > 65536 || (n >= 49152 && a.lambda_tok) || (n > 61440 && L >= 2048);
   if (L <= 32 || fills) return launch_seg<T, 2, 8>(a, s);
   return L > 256 && n <= 12288 ? launch_seg<T, 4, 64>(a, s) : launch_seg<T, 2, 32>(a, s);
 }
