@@ -5,9 +5,9 @@
 // the row's sum of exp2(s log2 e), and the backward kernels rebuild P tile by tile from q and k.
 //
 // bf16 storage with heads of up to 128 columns runs on the matrix cores (v_mfma_f32_32x32x16_bf16; the width is padded
-// to 32, 64 or 128).  A workgroup of four wavefronts owns
-// four tiles of 32 queries (forward, dq) or 32 keys (dk, dv), one per wavefront, and streams the other side's tiles
-// through a ring of LDS buffers that all four read:
+// to 32, 64 or 128).  A workgroup of four wavefronts owns four tiles of 32 queries (forward, dq) or 32 keys (dk, dv), one per
+// wavefront, and streams the other side's tiles through a ring of LDS buffers that all four read; or, where there are few
+// problems, it owns one tile, and each wavefront streams every fourth tile of the other side through a ring of its own:
 //   - the MFMA is issued so that a lane owns one query (dk/dv kernel: one key) and its 16 accumulator registers run
 //     over 16 of the streamed tile's 32 keys (queries): row statistics, the running rescale of the output and the
 //     factor dP - D are per-lane scalars (D and the row statistic enter as the accumulators' start values);
@@ -15,9 +15,11 @@
 //     width, which plain kernels with fp32 scores served before), are fed back as the second product's operand straight from the
 //     registers: the contraction index of an MFMA is a dummy, so it is enough that the other operand is fetched
 //     in the same (permuted) order of keys, which the transposing LDS read ds_read_b64_tr_b16 does from the tile;
-//   - tiles reach LDS by direct copies (global_load_lds_dwordx4, no staging registers) issued three steps ahead, each
-//     wavefront copying a quarter of every pair of tiles; the loop holds no other global load, so a counted s_waitcnt tells a
-//     wavefront that its share of the next tile has landed, and one barrier per step completes the hand-over;
+//   - tiles reach LDS by direct copies (global_load_lds_dwordx4, no staging registers) issued steps ahead; the loop holds no
+//     other global load, so a counted s_waitcnt tells a wavefront that its copies of the next pair of tiles have landed.  Of
+//     a shared ring each wavefront copies a quarter of every pair, three steps ahead, and one barrier per step completes the
+//     hand-over.  A wavefront with a ring of its own copies whole pairs, one or two steps ahead, and meets no barrier in the
+//     loop; the four wavefronts' sums (forward: and the rows' maxima and sums) meet in LDS at the end;
 //   - dq on one side and dk, dv on the other are two kernels that each rebuild S: seven products instead of five,
 //     no atomics, results bitwise repeatable.
 // Everything else (fp32 storage, wider heads) takes plain one-wavefront-per-query (per-key) kernels.
@@ -643,8 +645,8 @@ __device__ __forceinline__ void redo_rows(float t, int rows_left, F f) {
   for (; rows != 0; rows &= rows - 1) f(__ffs((int)rows) - 1);
 }
 
-// The three kernels share one shape.  A workgroup of four wavefronts owns four consecutive tiles of 32 queries
-// (dk/dv kernel: keys), one per wavefront, and streams the tiles of the other side through a ring of AT_NST buffer
+// The three kernels share one shape (SHARED: as described there).  A workgroup of four wavefronts owns four consecutive tiles of
+// 32 queries (dk/dv kernel: keys), one per wavefront, and streams the tiles of the other side through a ring of AT_NST buffer
 // pairs that all four read: at step t each wavefront waits for its own share of pair t, the workgroup meets at a
 // barrier (pair t complete; everyone done with pair t-1), its copies of pair t + AT_NST - 1 go out into the
 // buffer just freed, and the wavefront computes on pair t (or skips it when the causal mask hides the whole tile from
@@ -801,7 +803,7 @@ __global__ __launch_bounds__(64 * AT_WAVES, SHARED ? 1 : 2) void attn_fwd_mfma_k
   }
 }
 
-// dq of four tiles of 32 queries; also leaves D = rowsum(do (.) o) of their queries for the dk/dv kernel
+// dq of four tiles of 32 queries (SHARED: of one); also leaves D = rowsum(do (.) o) of their queries for the dk/dv kernel
 template <int DHP, bool PAD, bool CAUSAL, bool SHARED>
 __global__ __launch_bounds__(64 * AT_WAVES, SHARED ? 1 : 2) void attn_bwd_q_mfma_kernel(AttnArgs a) {
   constexpr int NST = ring_stages<DHP, SHARED>();
@@ -951,7 +953,7 @@ __global__ __launch_bounds__(64 * AT_WAVES, SHARED ? 1 : 2) void attn_bwd_q_mfma
   }
 }
 
-// dk, dv of four tiles of 32 keys (after the dq kernel: reads D).  128-wide heads hold 128 accumulators and 32 operand
+// dk, dv of four tiles of 32 keys (SHARED: of one; after the dq kernel: reads D).  128-wide heads hold 128 accumulators and 32 operand
 // registers per lane, and the parts of two sets of scores: one workgroup per compute unit with all 512 registers; narrower
 // ones fit three, or two where the scores are in three parts of 64 columns (in three, 40 registers spill).
 template <int DHP, bool PAD, bool CAUSAL, bool SHARED>

@@ -162,8 +162,9 @@ inline bool gemm_fills_chip(long tiles) { return tiles * 100 >= (tiles + 255) / 
 // the tile kernel in launches of its own; below, everything to the tile kernel (3000 x 1000 x 4000, batch 4, 132 whole
 // tiles: 163 us in parts, 122 us whole).
 constexpr long GEMM_SPLIT_FROM = 512;
-// Products of one pairing of layouts (both operands of each with the same index contiguous) that do not depend on each other, in one
-// launch: where all of them go to the kernels for few tiles, a launch costs more than a product's share of the chip does.
+// Products that do not depend on each other in one launch, where a launch costs more than a product's share of the chip does: all with B
+// row-contiguous and A of one kind (bf16: K-contiguous, the VJPs, or row-contiguous, the parameter gradients; fp32: the latter), none of them
+// on the 256 x 256 kernel, on the tiles for a product with all of their tiles; the lines are in ..._group_ok.
 constexpr int GEMM_GROUP = 4;
 struct GemmGroup {
   GemmArgs g[GEMM_GROUP];

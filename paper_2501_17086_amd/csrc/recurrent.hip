@@ -687,10 +687,11 @@ __device__ __forceinline__ bool forward_chain(const RecArgs& a, const Ring<LOCAL
 // waits for them where it waits for the exchanged words behind them.  The words land in a corner of LDS that nobody reads (direct
 // copies: no register waits for one).  It meets every barrier of the chain, which keeps it in step.
 // Measured, us, without / with it: 1024 steps of 32 x 1024, gated cell, forward, 1729 / 1439; 500 of 64 x 512, forward, LSTM 1142 / 957,
-// gated cell 660 / 592, GRU 940 / 874, exact backpropagation of the RNN 793 / 720; 400 of 20 x 200, forward, GRU 633 / 589, RNN 526 / 492.
+// gated cell 660 / 592, exact backpropagation of the RNN 793 / 720; 400 of 20 x 200, forward, GRU 633 / 589, RNN 526 / 492; the GRU of more
+// channels at REC_GRU_AHEAD.
 // Not for the LSTM and the GRU above 512 channels, whose registers do not leave room (two of five wavefronts share a SIMD: 256 each), nor the
 // RNN (1024 steps of 32 x 1024 1650 / 1700, exact 1940 / 2130), nor backwards for the LSTM (no change) and the GRU of up to 256 channels
-// (400 of 20 x 200 642 / 674; above, 500 of 64 x 512, 1153 / 1040), nor for one or two rows of that width for the gated cell (500 steps 509 /
+// (400 of 20 x 200 642 / 674), nor for one or two rows of that width for the gated cell (500 steps 509 /
 // 539, of four rows 528 / 506).
 constexpr int READ_AHEAD = 4;
 // A workgroup of five wavefronts has a compute unit for itself; of four, two share one.  The GRU of 257 to 512 channels gains the least
@@ -1002,7 +1003,8 @@ __device__ __forceinline__ bool backward_chain(const RecArgs& a, const Ring<LOCA
       for (int u = 0; u < UNITS - U0; ++u) {
         Operand<KQ, RT>& o = HELD == 2 && (u & 1) ? in2 : in;
         o.wait(ring, u, l, dead);
-        // (one product per step: behind the first operands, so that reading those again does not wait for memory)
+        // (one product per step: behind the first operands, so that reading those again does not wait for memory; 1024 steps of
+        // 32 x 1024 on one XCD 4 to 5 % faster for the gated cell and 2.8 % for the LSTM, 8 to 11 steps through memory the same)
         if (!ALONE && !TWO && u == 0) { read_step(next); advance(l > 1); }
         multiply_all(acc, ALONE ? weights(u + U0, member) : w[ALONE ? 0 : u + U0], o);
         if (u + HELD < UNITS - U0) o.ask(ring, u + HELD, l);
