@@ -783,22 +783,33 @@ long tiles_of(const GemmArgs& g, long tm, long tn) { return (g.M + tm - 1) / tm 
 // products) or 4096 (a transformer's four).  Measured, passes of one or two iterations, us, apart / together: two products, 8 blocks of 1000
 // x 360 x 1440 (288 + 288 tiles) 156.7 / 163.4, 24 of 1000 x 200 x 800 (336 each) 126.6 / 131.4, 20 of 100 x 328 x 1304 (660) 74.0 / 68.2, 12 of
 // 200 x 520 x 2080 (1020, short) 107.7 / 103.9, 8 of 141 x 1152 x 4608 (2592) 152 / 159; four, 6 layers of 2736 x 512 (1152 in all) 847 / 753
-// with the VJPs', 3 of 1740 x 1024 (2304) 974 / 885.  VJPs always, but for contractions of 4096 and more past a tile per
-// compute unit: the second ones of 4 layers of 256 x 1536 (192 tiles) 657 / 603, of 2 of 400 x 1536 (192) 414 / 388, of 2 of 500 x 2048 (256)
-// 744 / 698, of 4 of 256 x 2048 (256) 956 / 828, of 3 of 640 x 1536 (360) 769 / 770, of 4 of 500 x 1536 (384) 851 / 893, of 4 of 384 x 2048 (384)
-// 1051 / 1103, of 2 of 1000 x 2048 (512) 1086 / 1163, of 2 of 1500 x 1536 (576) 954 / 949.
+// with the VJPs', 3 of 1740 x 1024 (2304) 974 / 885.
+// Block VJPs in tiles of 128 go together but where contractions are long and a compute unit has as many tiles either way (256 at a time,
+// a remainder counting as 256): then two or three share one longer.  From contractions of 1536 on that is so past 512 tiles, from 4096 on at
+// any number; a wide and a narrow product (the first contractions) fill each other's last round at any length.  Measured,
+// gradients of k = 2, us, second contractions apart / together (the first iteration's tiles, the second's): 2 layers of 8900 x 256 (contractions
+// of 1024 and 768; 280 + 280, 140 + 280) 387 / 366, of 15300 x 256 (480 + 480, 240 + 480) 586 / 580; of 2400 x 512 (2048 and 1536; 152 + 152, 76 +
+// 152) 251 / 229, of 4400 x 512 (280 + 280, 140 + 280) 443 / 421, of 7168 x 512 (448 + 448, 224 + 448) 597 / 625; of 2200 x 1024 (2048 and 3072; 288
+// + 288, 144 + 288) 532 / 515, of 3000 x 1024 (384 + 384, 192 + 384) 622 / 640, 4 of 1500 (384 + 384, 288 + 384) 692 / 685; 4096 and more: 4 of 256 x
+// 1536 (96 + 96) 657 / 603, 2 of 500 x 2048 (128 + 128) 744 / 698, 4 of 500 x 1536 (192 + 192) 851 / 893, 4 of 384 x 2048 (192 + 192) 1051 / 1103,
+// 2 of 1500 x 1536 (288 + 288) 954 / 949.  First ones alone: 2 of 3000 x 768 (1152 + 288) 516 / 488, of 4000 x 1024 (2048 + 512) 1100 / 1062.
 bool gemm_mfma_group_ok(const GemmArgs* g, int n) {
   if (n < 2 || n > GEMM_GROUP) return false;
-  long t128 = 0, rounds = 0, longest = 0, shortest = 1L << 60;
+  long t128 = 0, rounds = 0, per_cu = 0, longest = 0;
+  bool wide = false;                       // one wide, one narrow
   for (int i = 0; i < n; ++i) {
     if (!covered(g[i]) || lean_share(g[i]) != LEAN_NOT || g[i].b_sn != 1 || (g[i].a_sk == 1) != (g[0].a_sk == 1)) return false;
     if (g[i].b_sk == 1 || (g[i].a_sk == 1 && g[i].a_sm == 1)) return false;       // (a single column: either layout)
-    t128 += tiles_of(g[i], 128, 128);
-    rounds += (tiles_of(g[i], 128, 128) + 511) / 512;
+    const long t = tiles_of(g[i], 128, 128);
+    t128 += t;
+    rounds += (t + 511) / 512;
+    per_cu += (t + 255) / 256;
     longest = g[i].K > longest ? g[i].K : longest;
-    shortest = g[i].K < shortest ? g[i].K : shortest;
+    wide = wide || g[i].N != g[0].N;
   }
-  if (g[0].a_sk == 1) return t128 <= (1L << 24) && (shortest < 4096 || t128 <= 256);
+  if (g[0].a_sk == 1)
+    return t128 <= (1L << 24) &&
+           (longest < 1536 || wide || (longest < 4096 && t128 <= 512) || (t128 + 255) / 256 < per_cu);
   return t128 < 192 || (t128 <= (n == 2 ? 2048 : 4096) && ((t128 + 511) / 512 < rounds || longest <= 256));
 }
 hipError_t launch_gemm_mfma_group(const GemmArgs* g, int n, hipStream_t s) {

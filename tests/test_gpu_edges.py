@@ -46,10 +46,11 @@ def test_products_of_few_tiles(B, N, d, d_ff):
 
 # several products in one launch (a transformer's first and second contractions in pairs, its four parameter gradients), on each kind
 # of tile: 32 x 32, 64 x 32, 64 x 64 and 128 x 128, products of one tile beside larger ones, sizes that end inside a tile and a slice; the
-# second contractions in tiles of 128 up to a tile per compute unit (240 and, of 4096 and more, 220) and, apart, past it (264)
+# second contractions in tiles of 128: 240, of 4096 and more 220 (a tile per compute unit) and, apart, 264; of 2056 660 (together) and 880
 @pytest.mark.parametrize("dtype,N,T,d,d_ff", [("bf16", 9, 9, 16, 8), ("bf16", 40, 8, 64, 72), ("bf16", 200, 40, 136, 264),
                                               ("bf16", 520, 40, 200, 1032), ("bf16", 1000, 40, 264, 1096), ("bf16", 2960, 40, 520, 2056),
                                               ("bf16", 1520, 40, 520, 2056), ("bf16", 520, 40, 1368, 4104), ("bf16", 680, 40, 1368, 4104),
+                                              ("bf16", 4200, 40, 520, 2056), ("bf16", 5600, 40, 520, 2056),
                                               ("f32", 9, 9, 16, 8), ("f32", 120, 40, 72, 264)])
 def test_products_in_one_launch(B, dtype, N, T, d, d_ff):
     w = synth.scaled(W["gpt2_paper"], name=f"tfm_{dtype}_{N}_{d}_{d_ff}", L=4, N=N, seq_len=T, d=d, heads=1 if d < 64 else d // 8,
