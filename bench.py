@@ -45,7 +45,7 @@ MEASURED_TRAFFIC = {
     "postnorm_mlp": {"source": "profiles/bench_postnorm_mlp_hbm_traffic.txt",
                      "vjp1": 6.364e9, "vjp2": 2.760e9, "dw": 2.819e9, "scan": 1.149e9},
     "gated_rnn": {"source": "profiles/bench_gated_rnn_hbm_traffic.txt",
-                  "vjp1": 9.697e8, "vjp2": 9.398e8, "dw": 6.041e8, "scan": 5.561e8},
+                  "vjp1": 9.481e8, "vjp2": 9.398e8, "dw": 6.041e8, "scan": 5.546e8},
     "gpt2_paper": {"source": "profiles/bench_gpt2_paper_hbm_traffic.txt",
                    "vjp1": 1.772e9, "vjp2": 6.923e8, "dw": 8.759e8, "attn": 1.618e9, "scan": 1.247e9},
     "roberta_like": {"source": "profiles/bench_roberta_like_hbm_traffic.txt",
@@ -53,7 +53,7 @@ MEASURED_TRAFFIC = {
     "transformer_attn": {"source": "profiles/bench_transformer_attn_hbm_traffic.txt",
                          "vjp1": 6.214e9, "vjp2": 1.836e9, "dw": 2.177e9, "attn": 3.896e9, "scan": 2.469e9},
     "lstm_cell": {"source": "profiles/bench_lstm_cell_hbm_traffic.txt",
-                  "vjp1": 3.491e9, "vjp2": 2.148e9, "dw": 1.723e9, "scan": 1.611e9},
+                  "vjp1": 3.491e9, "vjp2": 2.148e9, "dw": 1.735e9, "scan": 1.611e9},
 }
 
 
